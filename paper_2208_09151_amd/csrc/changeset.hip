@@ -22,6 +22,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <mutex>
+#include <vector>
 
 #include "common.hpp"
 #include "primitives.hpp"
@@ -389,6 +390,20 @@ __device__ __forceinline__ uint32_t block_sum_u32(uint32_t v, uint32_t* red) {
   return s;
 }
 
+// Sum of counts[0 .. n) by the whole block.
+__device__ __forceinline__ uint32_t block_prefix_of(const uint32_t* __restrict__ counts, int64_t n,
+                                                    uint32_t* red) {
+  uint32_t s = 0;
+  for (int64_t q = threadIdx.x; q < n; q += TB) s += counts[q];
+  return block_sum_u32(s, red);
+}
+
+__device__ __forceinline__ uint64_t shfl_u64(uint64_t v, int src) {
+  const uint32_t lo = __shfl((uint32_t)v, src, WAVE);
+  const uint32_t hi = __shfl((uint32_t)(v >> 32), src, WAVE);
+  return ((uint64_t)hi << 32) | lo;
+}
+
 __device__ __forceinline__ void dead_bit_set(const State& st, uint32_t v) {
   atomicOr(&st.dead_bits[v >> 5], 1u << (v & 31));
   atomicAdd(&st.dead_part[v >> PART_SHIFT], 1u);
@@ -656,25 +671,11 @@ constexpr int MARK_ITEMS = 8;   // lines / accesses per thread in the mark phase
 // iteration's accesses by their new key (a histogram H_i of next_iter alone), and the number
 // to drop is the iteration's length minus R_i[i], the residents keyed to it.  So the threshold
 // bucket j* of every iteration, the number of rows to drop from it, and R_{i+1} follow from S
-// histograms in front of the loop.  What depends on the cache is which accesses are hits: the
-// split of bucket j* into residents and incoming rows (it decides the class the id select runs
-// on) and the size of the changeset.  The touch phase counts those and marks the members of
-// bucket j* of both classes on the way, so that the loop needs neither the threshold launch
-// over histograms of the state nor a marking launch.
-constexpr int STATIC_S_MAX = 2048;      // iterations up to which the S x (S + 1) histograms are kept
-constexpr int64_t TOUCH_FEW = 400000;   // accesses of an iteration below which a thread of k_touch_static takes four
-
-struct StaticIter {      // per iteration, written by k_static_roll
-  int32_t jstar;         // threshold bucket, S + 1: nothing is dropped
-  int32_t rem;           // rows to drop from bucket j*
-  int32_t res_idle;      // residents of bucket j* that the iteration does not access
-  int32_t acc_jstar;     // accesses of the iteration whose new key is j*
-  int32_t res_above;     // residents above j* that the iteration does not access
-  int32_t pad;
-};
+// histograms of the trace.  stays.hpp turns them into the changesets.
+#include "stays.hpp"
 
 // H[i][k] = accesses of iteration i whose next accessed iteration is k.  blockIdx.y = iteration.
-__global__ __launch_bounds__(TB) void k_key_hists(const int32_t* __restrict__ next_iter,
+__global__ __launch_bounds__(TB) void k_key_hists(const uint64_t* __restrict__ ends,
                                                   const int64_t* __restrict__ off, int32_t S,
                                                   uint32_t* __restrict__ hists) {
   extern __shared__ uint32_t lds_h[];   // S + 1 bins
@@ -687,227 +688,94 @@ __global__ __launch_bounds__(TB) void k_key_hists(const int32_t* __restrict__ ne
 #pragma unroll
   for (int t = 0; t < TOUCH_ITEMS; ++t) {
     const int64_t p = base + t * TB + threadIdx.x;
-    if (p < n) atomicAdd(&lds_h[next_iter[lo + p]], 1u);
+    if (p < n) atomicAdd(&lds_h[stay_next(ends[lo + p])], 1u);
   }
   __syncthreads();
   for (int j = i + 1 + threadIdx.x; j <= S; j += TB)
     if (lds_h[j]) atomicAdd(&hists[(int64_t)i * (S + 1) + j], lds_h[j]);
 }
 
-// One block: the thresholds of all iterations, one after the other.  rhist holds R_0 (the
-// residents of the start state by key).  Bins are walked as r = S - j, `per` consecutive r to a
-// thread; a bin's word packs (idle residents << 32 | candidates).
-__global__ __launch_bounds__(BIG) void k_static_roll(State st, const uint32_t* __restrict__ hists,
-                                                     const int64_t* __restrict__ off,
-                                                     StaticIter* __restrict__ plan,
-                                                     int64_t* __restrict__ miss_count) {
-  __shared__ uint32_t s_res[STATIC_S_MAX + 1];
-  __shared__ uint64_t slots[BIG / WAVE];
-  __shared__ int32_t s_jstar, s_rem;
+// One block of NT threads: the thresholds of all iterations, one after the other.  rhist holds R_0
+// (the residents of the start state by key).  Bins are walked as r = S - j, PER consecutive r to a
+// thread, which keeps their counts in registers.
+template <int NT, int PER>
+__global__ __launch_bounds__(NT) void k_static_roll(State st, const uint32_t* __restrict__ hists,
+                                                    const int64_t* __restrict__ off,
+                                                    Cut* __restrict__ cuts,
+                                                    int64_t* __restrict__ miss_count) {
+  __shared__ uint32_t slots[2][NT / WAVE];
+  __shared__ int32_t s_cut[2][3];                     // j*, rem, candidates of bucket j* that stay
+  __shared__ uint32_t s_due[2];                       // residents keyed to the iteration
   const int32_t S = st.S;
-  const int per = (S + 1 + BIG - 1) / BIG;            // at most 3
-  const int r0 = threadIdx.x * per;
-  for (int j = threadIdx.x; j <= S; j += BIG) s_res[j] = st.rhist[j];
-  // the histogram values and the length of an iteration are requested an iteration ahead
-  uint32_t ahead[3] = {0, 0, 0};
-  for (int t = 0; t < per; ++t) {
+  const int r0 = threadIdx.x * PER;
+  uint32_t res[PER], ahead[PER];
+#pragma unroll
+  for (int t = 0; t < PER; ++t) {
     const int j = S - (r0 + t);
-    if (j > 0) ahead[t] = hists[j];
+    res[t] = j >= 0 ? st.rhist[j] : 0u;
+    ahead[t] = j > 0 ? hists[j] : 0u;                 // requested an iteration ahead from here on
+    if (j == 0) s_due[0] = res[t];
   }
   int64_t n_ahead = off[1] - off[0];
   __syncthreads();
   for (int32_t i = 0; i < S; ++i) {
-    const int64_t n = n_ahead;
-    const int64_t drop = n - (int64_t)s_res[i];       // the misses: the cache is full
-    uint64_t word[3];
-    uint64_t mine = 0;
-    for (int t = 0; t < per; ++t) {
+    const int now = i & 1;
+    const int64_t drop = n_ahead - (int64_t)s_due[now];   // the misses: the cache is full
+    uint32_t cand[PER];
+    uint32_t mine = 0;
+#pragma unroll
+    for (int t = 0; t < PER; ++t) {
       const int j = S - (r0 + t);
-      word[t] = 0;
-      if (j > i) {                                     // (no candidate has a key up to i)
-        const uint64_t idle = s_res[j];
-        word[t] = (idle << 32) | (idle + ahead[t]);
-      }
-      mine += word[t];
+      cand[t] = j > i ? res[t] + ahead[t] : 0u;       // (no candidate has a key up to i)
+      mine += cand[t];
     }
     if (i + 1 < S) {
-      for (int t = 0; t < per; ++t) {
+#pragma unroll
+      for (int t = 0; t < PER; ++t) {
         const int j = S - (r0 + t);
         ahead[t] = j > i + 1 ? hists[(int64_t)(i + 1) * (S + 1) + j] : 0u;
       }
       n_ahead = off[i + 2] - off[i + 1];
     }
     if (threadIdx.x == 0) {
-      s_jstar = S + 1;
-      s_rem = 0;
+      s_cut[now][0] = S + 1;
+      s_cut[now][1] = 0;
+    }
+    // exclusive prefix over the threads with one barrier
+    const uint32_t inc = wave_inclusive_scan(mine);
+    if (lane_id() == WAVE - 1) slots[now][threadIdx.x / WAVE] = inc;
+    __syncthreads();
+    int64_t before = inc - mine;
+    for (int q = 0; q < (int)(threadIdx.x / WAVE); ++q) before += slots[now][q];
+    if (drop > 0)
+#pragma unroll
+      for (int t = 0; t < PER; ++t) {
+        if (before <= drop && before + cand[t] > drop) {
+          s_cut[now][0] = S - (r0 + t);
+          s_cut[now][1] = (int32_t)(drop - before);
+          s_cut[now][2] = (int32_t)(cand[t] - (drop - before));
+        }
+        before += cand[t];
+      }
+    __syncthreads();
+    const int32_t jstar = s_cut[now][0], rem = s_cut[now][1];
+    if (threadIdx.x == 0) {
+      Cut c{};
+      c.jstar = jstar;
+      c.rem = rem;
+      c.T = -1;
+      if (jstar == S) c.n_res = (uint32_t)s_cut[now][2];   // for k_never_parts
+      cuts[i] = c;
       miss_count[i] = drop;
     }
-    // exclusive prefix over the threads with one barrier (see block_prefix_one_barrier)
-    const uint64_t inc = wave_inclusive_scan(mine);
-    if (lane_id() == WAVE - 1) slots[threadIdx.x / WAVE] = inc;
-    __syncthreads();
-    uint64_t before = inc - mine;
-    for (int q = 0; q < (int)(threadIdx.x / WAVE); ++q) before += slots[q];
-    StaticIter me{};
-    bool found = false;
-    if (drop > 0)
-      for (int t = 0; t < per; ++t) {
-        const int j = S - (r0 + t);
-        const int64_t cum = (int64_t)(before & 0xFFFFFFFFull), c = (int64_t)(word[t] & 0xFFFFFFFFull);
-        if (j > i && cum <= drop && cum + c > drop) {
-          me.jstar = j;
-          me.rem = (int32_t)(drop - cum);
-          me.res_idle = (int32_t)(word[t] >> 32);
-          me.acc_jstar = (int32_t)(c - (int64_t)(word[t] >> 32));
-          me.res_above = (int32_t)(before >> 32);
-          found = true;
-        }
-        before += word[t];
-      }
-    if (found) {
-      plan[i] = me;
-      s_jstar = me.jstar;
-      s_rem = me.rem;
-    }
-    __syncthreads();
-    const int32_t jstar = s_jstar, rem = s_rem;
-    if (threadIdx.x == 0 && jstar > S) {
-      StaticIter none{};
-      none.jstar = S + 1;
-      plan[i] = none;
-    }
     // R_{i+1}: everything below j* stays, bucket j* loses rem, everything above goes
-    for (int t = 0; t < per; ++t) {
+#pragma unroll
+    for (int t = 0; t < PER; ++t) {
       const int j = S - (r0 + t);
-      if (j < 0) continue;
-      const uint32_t c = (uint32_t)(word[t] & 0xFFFFFFFFull);
-      s_res[j] = j <= i ? 0u : j < jstar ? c : j == jstar ? c - (uint32_t)rem : 0u;
+      res[t] = j < jstar ? cand[t] : j == jstar ? cand[t] - (uint32_t)rem : 0u;
+      if (j == i + 1) s_due[now ^ 1] = res[t];
     }
     __syncthreads();
-  }
-}
-
-// k_touch with the threshold bucket known (ITEMS accesses per thread: four while an iteration is
-// bound by the latency of its chain, eight once it is bound by its scattered accesses): no histograms; hits keyed to or above j* are
-// counted (ctr[0], ctr[1]), and the members of bucket j* mark themselves, refreshed residents
-// in the residents' scratch bitmap, misses in the incoming rows'.  The blocks from
-// touch_blocks on walk the cache lines and mark the residents of bucket j* that the iteration
-// does not access (a line that a touch block refreshes to j* meanwhile may be marked by both:
-// the part count goes to whoever sets the bit).
-__device__ __forceinline__ void mark_once(uint32_t* bits, uint32_t* part, uint32_t v) {
-  const uint32_t bit = 1u << (v & 31);
-  if (!(atomicOr(&bits[v >> 5], bit) & bit)) atomicAdd(&part[v >> PART_SHIFT], 1u);
-}
-
-template <int ITEMS>
-__global__ __launch_bounds__(TB) void k_touch_static(State st, Iter it,
-                                                     const StaticIter* __restrict__ plan,
-                                                     uint32_t* __restrict__ ctr,
-                                                     int64_t touch_blocks) {
-  __shared__ uint32_t red[TB / WAVE];
-  const StaticIter si = plan[it.i];
-  const int32_t jstar = si.jstar;
-  const bool mark_res = jstar < st.S;     // (bucket "never": the standing dead-row bitmap serves)
-  if ((int64_t)blockIdx.x >= touch_blocks) {
-    if (!mark_res || si.res_idle == 0) return;
-    const int64_t base = ((int64_t)blockIdx.x - touch_blocks) * (TB * MARK_ITEMS);
-#pragma unroll
-    for (int t = 0; t < MARK_ITEMS; ++t) {
-      const int64_t l = base + t * TB + threadIdx.x;
-      if (l < st.cap && st.res_next[l] == jstar)
-        mark_once(st.bitmap, st.sel_part, (uint32_t)st.res_id[l]);
-    }
-    return;
-  }
-  const int64_t base = (int64_t)blockIdx.x * (TB * ITEMS);
-  int32_t v[ITEMS], line[ITEMS], nx[ITEMS];
-#pragma unroll
-  for (int t = 0; t < ITEMS; ++t) {
-    int64_t p = base + t * TB + threadIdx.x;
-    p = p < it.n ? p : base;
-    v[t] = it.ids[p];
-    nx[t] = it.next[p];
-  }
-#pragma unroll
-  for (int t = 0; t < ITEMS; ++t) line[t] = st.addr[v[t]];
-  uint32_t at_jstar = 0, above = 0;
-#pragma unroll
-  for (int t = 0; t < ITEMS; ++t) {
-    const int64_t p = base + t * TB + threadIdx.x;
-    if (p >= it.n) continue;
-    st.acc_line[p] = line[t];
-    if (it.src_line) it.src_line[p] = line[t];   // the state is C_i here
-    if (line[t] >= 0) {
-      st.res_next[line[t]] = nx[t];
-      if (nx[t] == st.S) dead_bit_set(st, (uint32_t)v[t]);   // the row's last access
-      if (nx[t] == jstar) {
-        ++at_jstar;
-        if (mark_res) mark_once(st.bitmap, st.sel_part, (uint32_t)v[t]);
-      } else if (nx[t] > jstar) {
-        ++above;
-      }
-    } else if (nx[t] == jstar) {
-      mark_once(st.bitmap_in, st.sel_part_in, (uint32_t)v[t]);
-    }
-  }
-  // (a block has at most TB * ITEMS accesses: the two counts share a word)
-  const uint32_t both = block_sum_u32((at_jstar << 16) | above, red);
-  if (threadIdx.x == 0) {
-    if (both >> 16) atomicAdd(&ctr[0], both >> 16);
-    if (both & 0xFFFFu) atomicAdd(&ctr[1], both & 0xFFFFu);
-  }
-}
-
-// One block: the rest of the iteration's decision (what p_threshold decides inside bucket j*),
-// the size of the changeset, and the id select.
-__global__ __launch_bounds__(BIG) void k_decide(State st, int32_t i,
-                                                const StaticIter* __restrict__ plan,
-                                                uint32_t* __restrict__ ctr, Outputs o,
-                                                int64_t evict_tiles) {
-  const StaticIter si = plan[i];
-  const int64_t hits_at = ctr[0], hits_above = ctr[1];
-  __syncthreads();                       // every thread has read the counters
-  if (threadIdx.x == 0) {
-    ctr[0] = 0;
-    ctr[1] = 0;
-    Ctrl c{};
-    c.jstar = si.jstar;
-    c.mode_in = MODE_ALL;
-    c.mode_res = MODE_ALL;
-    c.T = -1;
-    int64_t from_res = 0;
-    if (si.jstar <= st.S) {
-      const int64_t R = (int64_t)si.res_idle + hits_at, I = (int64_t)si.acc_jstar - hits_at;
-      const int64_t rem = si.rem;
-      if (rem == 0) {
-      } else if (rem < I) {
-        c.mode_in = MODE_SELECT; c.keep = (int32_t)(I - rem);
-      } else if (rem == I) {
-        c.mode_in = MODE_NONE;
-      } else {
-        c.mode_in = MODE_NONE; c.mode_res = MODE_SELECT;
-        from_res = rem - I;
-        c.keep = (int32_t)(R - from_res);
-        c.use_dead = si.jstar == st.S;
-      }
-      c.n_change = (int32_t)((int64_t)si.res_above + hits_above + from_res);
-      c.marked = (si.jstar < st.S && R > 0 ? MARKED_RES : 0) | (I > 0 ? MARKED_IN : 0);
-    }
-    *st.ctrl = c;
-    o.cs_offsets[i + 1] = o.cs_offsets[i] + c.n_change;
-  }
-  __syncthreads();
-  const Ctrl c = *st.ctrl;
-  if (c.mode_res == MODE_SELECT) {
-    if (c.use_dead) {
-      p_bits_find<BIG>(st, st.dead_bits, st.dead_part, true);
-      if (st.dead_scatter)
-        for (int64_t q = threadIdx.x; q < evict_tiles; q += BIG) st.evict_tiles[q] = 0;
-    } else {
-      p_bits_find<BIG>(st, st.bitmap, st.sel_part, false);
-    }
-  } else if (c.mode_in == MODE_SELECT) {
-    p_bits_find<BIG>(st, st.bitmap_in, st.sel_part_in, false);
   }
 }
 
@@ -1029,13 +897,10 @@ __device__ void p_evict_flags(const State& st, const Ctrl& c, int64_t vb) {
   if (threadIdx.x == 0) st.evict_tiles[vb] = total;
 }
 
-constexpr int IN_ITEMS = 8;        // accesses per thread in the insertion phases ...
-constexpr int IN_ITEMS_MANY = 4;   // ... of an iteration with TOUCH_FEW accesses or more (smaller tiles
-                                   // rank and place faster once the phases are bound by their accesses)
+constexpr int IN_ITEMS = 8;        // accesses per thread in the insertion phases
 
 // Insertions per tile of TB*IN_ITEMS accesses; incoming rows that marked themselves for the
 // select take their word of the scratch bitmap back to zero.
-template <int IN_ITEMS>
 __device__ void p_in_count(const State& st, const Ctrl& c, const Iter& it, int64_t vb) {
   __shared__ uint32_t red[TB / WAVE];
   const int64_t base = (vb * TB + threadIdx.x) * IN_ITEMS;
@@ -1065,7 +930,6 @@ __device__ void p_in_count(const State& st, const Ctrl& c, const Iter& it, int64
 // or, dead rows of a large cache, by the scatter from the bitmap (the blocks then stride over
 // the stretch above T); the next in_tiles blocks: insertions per tile; one more block takes
 // the part counts of the scratch bitmap back to zero.
-template <int IN_ITEMS>
 __global__ __launch_bounds__(TB) void k_flags(State st, Iter it, int64_t evict_tiles,
                                               int64_t in_tiles) {
   const Ctrl c = *st.ctrl;
@@ -1077,7 +941,7 @@ __global__ __launch_bounds__(TB) void k_flags(State st, Iter it, int64_t evict_t
       p_evict_flags(st, c, vb);
     }
   } else if (vb < evict_tiles + in_tiles) {
-    if (c.n_change > 0 || (c.marked & MARKED_IN)) p_in_count<IN_ITEMS>(st, c, it, vb - evict_tiles);
+    if (c.n_change > 0 || (c.marked & MARKED_IN)) p_in_count(st, c, it, vb - evict_tiles);
   } else {
     if (c.marked & MARKED_RES)
       for (int64_t q = threadIdx.x; q < st.parts; q += TB) st.sel_part[q] = 0;
@@ -1102,20 +966,6 @@ __device__ __forceinline__ void finish_line(const State& st, int32_t line, int32
   st.res_id[line] = v;
   st.res_next[line] = key;
   st.addr[v] = line;
-}
-
-// Sum of counts[0 .. n) by the whole block.
-__device__ __forceinline__ uint32_t block_prefix_of(const uint32_t* __restrict__ counts, int64_t n,
-                                                    uint32_t* red) {
-  uint32_t s = 0;
-  for (int64_t q = threadIdx.x; q < n; q += TB) s += counts[q];
-  return block_sum_u32(s, red);
-}
-
-__device__ __forceinline__ uint64_t shfl_u64(uint64_t v, int src) {
-  const uint32_t lo = __shfl((uint32_t)v, src, WAVE);
-  const uint32_t hi = __shfl((uint32_t)(v >> 32), src, WAVE);
-  return ((uint64_t)hi << 32) | lo;
 }
 
 // One wave per tile of 64 flag words: the evicted lines in line order.  The tile's set bits
@@ -1193,7 +1043,6 @@ __device__ void p_evict_emit(const State& st, const Ctrl& c, const Iter& it, con
 // The inserted positions of one tile of accesses in position order; the block's insertions
 // are first gathered in LDS by rank and then dealt one to a thread, for the same reason as
 // above.
-template <int IN_ITEMS>
 __device__ void p_in_emit(const State& st, const Ctrl& c, const Iter& it, const Outputs& o,
                           int64_t vb) {
   __shared__ uint32_t smem[TB / WAVE + 1];
@@ -1243,13 +1092,12 @@ __device__ void p_in_emit(const State& st, const Ctrl& c, const Iter& it, const 
   }
 }
 
-template <int IN_ITEMS>
 __global__ __launch_bounds__(TB) void k_emit_pair(State st, Iter it, Outputs o, int64_t evict_tiles) {
   const Ctrl c = *st.ctrl;
   if (c.n_change <= 0) return;
   const int64_t evict_blocks = (evict_tiles + TB / WAVE - 1) / (TB / WAVE);
   if ((int64_t)blockIdx.x < evict_blocks) p_evict_emit(st, c, it, o, blockIdx.x, evict_tiles);
-  else p_in_emit<IN_ITEMS>(st, c, it, o, blockIdx.x - evict_blocks);
+  else p_in_emit(st, c, it, o, blockIdx.x - evict_blocks);
 }
 
 // popcount of one part of a bitmap (the part counts of the dead-row bitmap after a resumed
@@ -1457,7 +1305,7 @@ __global__ __launch_bounds__(TB) void k_ins_emit(const uint32_t* __restrict__ bi
     word &= word - 1;
     in_ids[rank] = ids[p];
     in_positions[rank] = p - lds_off[iter_of(lds_off, S, p)];
-    ins_cand[rank] = -1;
+    if (ins_cand) ins_cand[rank] = -1;
     ++rank;
   }
 }
@@ -2073,9 +1921,9 @@ __global__ __launch_bounds__(TB) void k_step_emit(State st, int64_t evict_tiles,
 
 struct Workspace {
   uint64_t *pairs_a, *pairs_b, *heads_a, *heads_b;
-  uint32_t* key_hists;      // [S x (S + 1)] accesses per iteration and next accessed iteration (S <= STATIC_S_MAX)
-  StaticIter* static_plan;  // [S]
-  uint32_t* touch_ctr;      // [2] hits keyed to / above the threshold bucket, of the running iteration
+  uint32_t* key_hists;      // [S x (S + 1)] accesses per iteration and next accessed iteration (S <= STATIC_S_MAX),
+                            // later the table of stays.hpp
+  Cut* cuts;                // [S]
   uint32_t* hist;
   uint32_t* head_tiles;
   int32_t* next_iter;
@@ -2111,8 +1959,7 @@ Workspace carve(void* base, int64_t num_nodes, int64_t total, int32_t S, int64_t
   w.head_tiles = a.take<uint32_t>(w.look_tiles + 1 + scan_scratch_elems(w.look_tiles + 1));
   w.next_iter = a.take<int32_t>(t);
   w.key_hists = a.take<uint32_t>(S <= STATIC_S_MAX ? (size_t)S * (S + 1) : 0);
-  w.static_plan = a.take<StaticIter>(S);
-  w.touch_ctr = a.take<uint32_t>(2);
+  w.cuts = a.take<Cut>(S);
   w.first_of = a.take<int32_t>(num_nodes);   // resumed superbatches only
   w.d_offsets = a.take<int64_t>(S + 1);
   w.d_ready = a.take<int64_t>(S);
@@ -2140,7 +1987,7 @@ Workspace carve(void* base, int64_t num_nodes, int64_t total, int32_t S, int64_t
   st.fault = a.take<int32_t>(1);
   w.evict_tiles = ceil_div(c, (int64_t)EVICT_TILE);
   st.evict_words = a.take<uint64_t>(w.evict_tiles * WAVE);
-  w.in_tiles = ceil_div(max_n > 0 ? max_n : 1, (int64_t)TB * IN_ITEMS_MANY);
+  w.in_tiles = ceil_div(max_n > 0 ? max_n : 1, (int64_t)TB * IN_ITEMS);
   st.evict_tiles = a.take<uint32_t>(w.evict_tiles);
   st.in_tiles = a.take<uint32_t>(w.in_tiles);
   w.max_change = max_n < c ? max_n : c;
@@ -2196,6 +2043,226 @@ extern "C" size_t ginex_changeset_workspace_bytes(int64_t num_nodes, int64_t tot
 
 namespace ginex {
 namespace {
+
+// The changesets of a full cache whose state (res_id, addr, rhist and, for a carried cache,
+// res_next, dead_bits, dead_part) is set up, from the node-sorted accesses (see stays.hpp).
+// `ends`: the other buffer of the sort, `rows`: a word per distinct row.  last_head: the last row of
+// C_0, null for a carried cache.
+int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, uint64_t* ends,
+                  uint64_t* rows, int64_t distinct, const uint64_t* last_head, const int32_t* ids,
+                  const int64_t* ids_offsets, int64_t total, int32_t S, int32_t* in_ids, int32_t* out_ids, int32_t* in_positions,
+                  int64_t cs_capacity, int64_t* cs_offsets, int64_t* miss_count, int32_t* src_line,
+                  int64_t* total_changes, bool carried, int32_t* final_ids, hipStream_t st) {
+  const State& state = w.st;
+  const Plan& pl = w.plan;
+  const size_t off_lds = sizeof(int32_t) * (S + 1);
+  Stays q{ends, w.d_offsets, ids, w.key_hists, w.cuts, w.next_iter, pl.cand_id, S};
+  int64_t longest = 0;
+  for (int32_t i = 0; i < S; ++i)
+    longest = std::max<int64_t>(longest, ids_offsets[i + 1] - ids_offsets[i]);
+
+  // both ends of every stay, the thresholds, the table
+  hipLaunchKernelGGL(k_stay_ends, dim3((unsigned)w.look_tiles), dim3(TB), off_lds, st, sorted, total,
+                     w.d_offsets, S, last_head, state.addr, ends);
+  GINEX_HIP(fill_async<uint32_t>(w.key_hists, (int64_t)S * (S + 1), 0u, st));
+  hipLaunchKernelGGL(k_key_hists, dim3((unsigned)ceil_div(longest, TB * TOUCH_ITEMS), (unsigned)S),
+                     dim3(TB), sizeof(uint32_t) * (S + 1), st, ends, w.d_offsets, S, w.key_hists);
+  if (S < 256)
+    hipLaunchKernelGGL((k_static_roll<256, 1>), dim3(1), dim3(256), 0, st, state, w.key_hists,
+                       w.d_offsets, w.cuts, miss_count);
+  else
+    hipLaunchKernelGGL((k_static_roll<BIG, 3>), dim3(1), dim3(BIG), 0, st, state, w.key_hists,
+                       w.d_offsets, w.cuts, miss_count);
+  hipLaunchKernelGGL(k_stay_table, dim3((unsigned)(S / WAVE + 1)), dim3(WAVE),
+                     sizeof(int32_t) * S, st, w.cuts, S, w.key_hists);
+  GINEX_LAUNCH_CHECK();
+  std::vector<Cut> cuts(S);
+  GINEX_HIP(hipMemcpyAsync(cuts.data(), w.cuts, sizeof(Cut) * S, hipMemcpyDeviceToHost, st));
+  GINEX_HIP(hipStreamSynchronize(st));
+
+  // the levels: a cut waits for the cuts of the bucket its own iteration's accesses come from, and for
+  // the earlier cuts of its bucket
+  std::vector<int32_t> jobs, level_of_bucket(S + 1, 0);
+  std::vector<std::vector<int32_t>> levels;
+  bool never = false;
+  for (int32_t t = 0; t < S; ++t) {
+    const Cut& c = cuts[t];
+    if (c.jstar == S) never = true;
+    if (c.jstar >= S || c.rem == 0) continue;
+    const int32_t l = std::max(level_of_bucket[t], level_of_bucket[c.jstar]);   // (levels count from 1)
+    level_of_bucket[c.jstar] = l + 1;
+    if ((int32_t)levels.size() <= l) levels.resize(l + 1);
+    levels[l].push_back(t);
+  }
+  for (const auto& level : levels) jobs.insert(jobs.end(), level.begin(), level.end());
+  int32_t* const d_jobs = reinterpret_cast<int32_t*>(w.d_ready);
+  if (!jobs.empty())
+    GINEX_HIP(hipMemcpyAsync(d_jobs, jobs.data(), sizeof(int32_t) * jobs.size(), hipMemcpyHostToDevice, st));
+  int64_t at = 0;
+  for (const auto& level : levels) {
+    int64_t blocks = 1;
+    for (const int32_t t : level) {
+      const int32_t j = cuts[t].jstar;
+      blocks = std::max(blocks, ceil_div(ids_offsets[t + 1] - ids_offsets[t] + ids_offsets[j + 1] -
+                                             ids_offsets[j], CUT_TILE));
+    }
+    const unsigned count = (unsigned)level.size();
+    hipLaunchKernelGGL(k_cut_members, dim3((unsigned)blocks, count), dim3(TB), 0, st, q, d_jobs + at);
+    hipLaunchKernelGGL(k_cut_decide, dim3(count), dim3(BIG), 0, st, q, d_jobs + at);
+    GINEX_LAUNCH_CHECK();
+    at += count;
+  }
+
+  // hits, misses, insertions
+  hipLaunchKernelGGL(k_stays_mark, dim3((unsigned)ceil_div(total, CUT_TILE)), dim3(TB), off_lds, st, q,
+                     total, src_line, pl.ins_bits);
+  uint32_t* const leave_start = reinterpret_cast<uint32_t*>(state.res_next);
+  // both sets of bits in node order where the members of the cuts were: a quarter byte per access in an
+  // array of four (padded to 256 bytes, so the last words have room in the smallest one too)
+  const int64_t words = ceil_div(total, WAVE);
+  uint64_t* const hit_words = reinterpret_cast<uint64_t*>(w.next_iter);
+  uint64_t* const ins_words = hit_words + words;
+  Never nv{};
+  nv.rows = rows;
+  hipLaunchKernelGGL(k_stays_links, dim3((unsigned)w.look_tiles), dim3(TB), off_lds, st, q, sorted, total,
+                     w.head_tiles, last_head, state.addr, nv, hit_words, ins_words, leave_start);
+  // bucket "never"
+  if (never) {
+    static_assert(NEVER_COUNTS <= PLAN_CAND_MAX && NEVER_LEVELS * (STATIC_S_MAX + 1) + NEVER_PARTS <= PLAN_CAND_MAX,
+                  "counters and limits sit in the candidate arrays of the planned path");
+    nv.counts = reinterpret_cast<uint32_t*>(pl.cand_line);
+    nv.idle = carried ? state.dead_bits : nullptr;
+    nv.distinct = distinct;
+    nv.num_nodes = state.num_nodes;
+    // parts, a power of two: [S x parts] counters, and a few thousand rows to a part (a cut looks at the
+    // rows of one part)
+    int64_t most = NEVER_PARTS;
+    while (most > 1 && (most * S > NEVER_COUNTS || most * 4096 > distinct)) most /= 2;
+    nv.shift = 5;                           // (whole words of the bitmap)
+    while (ceil_div(state.num_nodes, int64_t(1) << nv.shift) > most) ++nv.shift;
+    nv.parts = (int32_t)ceil_div(state.num_nodes, int64_t(1) << nv.shift);
+    uint32_t* const idle_counts = reinterpret_cast<uint32_t*>(pl.cand_id) + NEVER_LEVELS * (STATIC_S_MAX + 1);
+    GINEX_HIP(fill_async<uint32_t>(nv.counts, (int64_t)S * nv.parts, 0u, st));
+    const int64_t count_blocks = std::min<int64_t>(ceil_div(distinct, TB * 8), 2048);
+    hipLaunchKernelGGL(k_never_counts, dim3((unsigned)count_blocks), dim3(TB), sizeof(uint32_t) * S, st,
+                       nv, S);
+    if (carried)
+      hipLaunchKernelGGL(k_never_idle, dim3((unsigned)nv.parts), dim3(TB), 0, st, nv, idle_counts);
+    hipLaunchKernelGGL(k_never_parts, dim3(1), dim3(NEVER_PARTS), 0, st, nv, S, w.cuts,
+                       carried ? idle_counts : (const uint32_t*)nullptr);
+    hipLaunchKernelGGL(k_never_select, dim3((unsigned)nv.parts), dim3(BIG), sizeof(int32_t) * S, st, nv,
+                       S, w.cuts);
+    GINEX_LAUNCH_CHECK();
+  }
+  hipLaunchKernelGGL(k_never_lift, dim3(1), dim3(BIG), 0, st, w.cuts, S, pl.cand_id);
+  hipLaunchKernelGGL(k_ins_count, dim3((unsigned)S), dim3(TB), 0, st, pl.ins_bits, w.d_offsets,
+                     cs_offsets);
+  hipLaunchKernelGGL(k_ins_offsets, dim3(1), dim3(BIG), 0, st, cs_offsets, S);
+  GINEX_LAUNCH_CHECK();
+  std::vector<int64_t> cs(S + 1);
+  GINEX_HIP(hipMemcpyAsync(cs.data(), cs_offsets, sizeof(int64_t) * (S + 1), hipMemcpyDeviceToHost, st));
+  hipLaunchKernelGGL(k_bit_tiles, dim3((unsigned)pl.ins_tile_count), dim3(TB), 0, st, pl.ins_bits,
+                     pl.ins_words, pl.ins_tiles);
+  GINEX_HIP(fill_async<uint32_t>(pl.ins_tiles + pl.ins_tile_count, 1, 0u, st));
+  GINEX_HIP(exclusive_scan_inplace<uint32_t>(pl.ins_tiles, pl.ins_tile_count + 1,
+                                             pl.ins_tiles + pl.ins_tile_count + 1, st));
+  GINEX_HIP(hipStreamSynchronize(st));
+  const int64_t M = cs[S];
+  *total_changes = M;
+  if (M > cs_capacity)
+    return fail(GINEX_ERR_CAPACITY, "%s: %lld changeset records, capacity %lld", who, (long long)M,
+                (long long)cs_capacity);
+
+  // the insertion lists, and when every line is given up again
+  // (the ends are not read any more)
+  uint32_t* const leave_ins = reinterpret_cast<uint32_t*>(ends);
+  int32_t* const leaving = reinterpret_cast<int32_t*>(leave_ins + total);
+  if (M > 0) {
+    hipLaunchKernelGGL(k_ins_emit, dim3((unsigned)pl.ins_tile_count), dim3(TB), off_lds, st, pl.ins_bits,
+                       pl.ins_words, pl.ins_tiles, ids, w.d_offsets, S, in_ids, in_positions,
+                       pl.ins_base, (int32_t*)nullptr);
+    if (carried)
+      hipLaunchKernelGGL(k_stays_idle, dim3((unsigned)ceil_div(state.cap, TB)), dim3(TB), 0, st, q,
+                         state.res_id, state.res_next, state.cap, leave_start);
+    int levels = 1;
+    while ((1 << levels) <= S) ++levels;
+    const dim3 walk_grid((unsigned)ceil_div(total, WALK_TILE));
+    if (S <= NEVER_LDS_S)
+      hipLaunchKernelGGL(k_stays_walk<true>, walk_grid, dim3(TB), off_lds * (1 + levels), st, q, sorted,
+                         total, state.addr, hit_words, ins_words, pl.ins_bits, pl.ins_base, leave_ins,
+                         leave_start);
+    else
+      hipLaunchKernelGGL(k_stays_walk<false>, walk_grid, dim3(TB), off_lds, st, q, sorted, total,
+                         state.addr, hit_words, ins_words, pl.ins_bits, pl.ins_base, leave_ins,
+                         leave_start);
+    GINEX_HIP(fill_async<uint32_t>(pl.arr_cur, S + 1, 0u, st));
+    const int64_t place_blocks = std::min<int64_t>(ceil_div(M + state.cap, TB * 8), 512);
+    hipLaunchKernelGGL(k_leave_places, dim3((unsigned)place_blocks), dim3(TB), sizeof(uint32_t) * S, st,
+                       M, state.cap, S, leave_ins, leave_start, cs_offsets, pl.arr_cur, leaving);
+    GINEX_LAUNCH_CHECK();
+  }
+
+  // the lines
+  if (M > 0 || src_line) {
+    Step s{};
+    s.words = ceil_div(state.cap, 64);
+    // tiles of 512 lines while there are few of them (their counters are atomics that share cache
+    // lines), of 4096 for large caches (every block adds up the counters in front of its own)
+    const bool large = state.cap >= LARGE_CACHE;
+    s.tile_shift = large ? 12 : 9;
+    s.tiles = ceil_div(state.cap, int64_t(1) << s.tile_shift);
+    // flag words: evict_words, and the scratch bitmap over ids, which has room for them (cap is at
+    // most num_nodes, and the arrays of the workspace are padded to 256 bytes); the counters sit in
+    // the second scratch bitmap, one counter for 512 lines or more against one word for 32 ids
+    uint64_t* flags[2] = {state.evict_words, reinterpret_cast<uint64_t*>(state.bitmap)};
+    uint32_t* counts = state.bitmap_in;
+    GINEX_HIP(fill_async<uint64_t>(flags[0], s.words, 0ull, st));
+    GINEX_HIP(fill_async<uint64_t>(flags[1], s.words, 0ull, st));
+    GINEX_HIP(fill_async<uint32_t>(counts, 3 * s.tiles, 0u, st));
+    s.leaving = leaving;
+    s.leave_ins = leave_ins;
+    s.in_ids = in_ids;
+    s.out_ids = out_ids;
+    auto flag_blocks = [&](int32_t t) {
+      return t < S && cs[t + 1] > cs[t] ? std::min<int64_t>(ceil_div(cs[t + 1] - cs[t], TB), 256) : 0;
+    };
+    s.next = flags[0];
+    s.cnt_next = counts;
+    s.next_dst = 0;
+    s.next_n = cs[1];
+    s.next_filled = pl.arr_cur;
+    if (cs[1] > 0)
+      hipLaunchKernelGGL(k_step_flags, dim3((unsigned)flag_blocks(0)), dim3(TB), 0, st, s);
+    for (int32_t t = 0; t < S; ++t) {
+      s.now = flags[t & 1];
+      s.next = flags[(t + 1) & 1];
+      s.cnt_now = counts + (t % 3) * s.tiles;
+      s.cnt_next = counts + ((t + 1) % 3) * s.tiles;
+      s.cnt_clear = counts + ((t + 2) % 3) * s.tiles;
+      s.emit_blocks = M > 0 ? ceil_div(s.words, large ? 256 : 64) : 0;
+      s.flag_blocks = flag_blocks(t + 1);
+      s.dst = cs[t];
+      s.n_change = cs[t + 1] - cs[t];
+      s.next_dst = cs[t + 1];
+      s.next_n = t + 1 < S ? cs[t + 2] - cs[t + 1] : 0;
+      s.next_filled = pl.arr_cur + t + 1;
+      s.ids = ids + ids_offsets[t];
+      s.n = ids_offsets[t + 1] - ids_offsets[t];
+      s.src_line = src_line ? src_line + ids_offsets[t] : nullptr;
+      const int64_t blocks = s.emit_blocks + s.flag_blocks + (src_line ? ceil_div(s.n, TB * 4) : 0);
+      if (blocks > 0 && large)
+        hipLaunchKernelGGL(k_step_lines<256>, dim3((unsigned)blocks), dim3(TB), 0, st, state, s);
+      else if (blocks > 0)
+        hipLaunchKernelGGL(k_step_lines<64>, dim3((unsigned)blocks), dim3(TB), 0, st, state, s);
+    }
+    GINEX_LAUNCH_CHECK();
+  }
+  if (final_ids)
+    GINEX_HIP(hipMemcpyAsync(final_ids, state.res_id, sizeof(int32_t) * state.cap,
+                             hipMemcpyDeviceToDevice, st));
+  GINEX_HIP(hipStreamSynchronize(st));
+  return GINEX_OK;
+}
 
 // Both replacement policies share every kernel: a policy only decides the key an access
 // leaves behind (Belady: its next accessed iteration; LRU: S-1-i, so that the least
@@ -2349,26 +2416,36 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
   state.dead_only = start_ids && distinct <= cap && !(live_env && live_env[0] == '1');
   const bool planned = state.dead_only && allow_planned && S <= PLAN_S_MAX &&
                        !(plan_env && plan_env[0] == '0');
-  // the cache cannot hold every row: Belady needs the next accessed iteration of every access
-  // (the planned path reads what it needs from the sorted pairs)
-  if (!lru && !planned) {
-    hipLaunchKernelGGL(k_look_right, dim3((unsigned)w.look_tiles), dim3(TB), off_lds, st, sorted,
-                       total, w.d_offsets, S, w.next_iter);
-    GINEX_LAUNCH_CHECK();
-  }
-  GINEX_HIP(fill_async<int32_t>(state.fault, 1, 0, st));
-  GINEX_HIP(fill_async<int32_t>(state.addr, num_nodes, -1, st));
+  // Belady, otherwise: the changesets from the trace and the start state (stays.hpp;
+  // GINEX_STATIC_THRESHOLDS=0 keeps the loop over the cache state, the only way for LRU and for
+  // more iterations than the table of the stays is kept for)
+  const char* static_env = getenv("GINEX_STATIC_THRESHOLDS");
+  const bool stays = !lru && S <= STATIC_S_MAX && !(static_env && static_env[0] == '0');
+  const bool loop = !stays;   // (the loop still is the last way out of the planned path then)
   GINEX_HIP(fill_async<uint32_t>(state.rhist, S + 2, 0u, st));
-  GINEX_HIP(fill_async<uint32_t>(state.ihist, S + 2, 0u, st));
   GINEX_HIP(fill_async<uint32_t>(state.bitmap, state.words, 0u, st));
   GINEX_HIP(fill_async<uint32_t>(state.dead_bits, state.words, 0u, st));
-  GINEX_HIP(fill_async<uint32_t>(state.sel_part, state.parts, 0u, st));
-  GINEX_HIP(fill_async<uint32_t>(state.bitmap_in, state.words, 0u, st));
-  GINEX_HIP(fill_async<uint32_t>(state.sel_part_in, state.parts, 0u, st));
   GINEX_HIP(fill_async<uint32_t>(state.dead_part, state.parts, 0u, st));
-  GINEX_HIP(fill_async<uint64_t>(state.pair, w.max_change, 0ull, st));
-  if (state.dead_scatter)
-    GINEX_HIP(fill_async<uint64_t>(state.evict_words, w.evict_tiles * WAVE, 0ull, st));
+  if (loop || planned) {      // (the steps of the planned path use the fault word and the flag words)
+    GINEX_HIP(fill_async<int32_t>(state.fault, 1, 0, st));
+    if (state.dead_scatter)
+      GINEX_HIP(fill_async<uint64_t>(state.evict_words, w.evict_tiles * WAVE, 0ull, st));
+  }
+  if (loop) {
+    if (!lru && !planned) {   // the next accessed iteration of every access
+      hipLaunchKernelGGL(k_look_right, dim3((unsigned)w.look_tiles), dim3(TB), off_lds, st, sorted,
+                         total, w.d_offsets, S, w.next_iter);
+      GINEX_LAUNCH_CHECK();
+    }
+    GINEX_HIP(fill_async<uint32_t>(state.ihist, S + 2, 0u, st));
+    GINEX_HIP(fill_async<uint32_t>(state.sel_part, state.parts, 0u, st));
+    GINEX_HIP(fill_async<uint32_t>(state.bitmap_in, state.words, 0u, st));
+    GINEX_HIP(fill_async<uint32_t>(state.sel_part_in, state.parts, 0u, st));
+    GINEX_HIP(fill_async<uint64_t>(state.pair, w.max_change, 0ull, st));
+  }
+  // the loop looks every access up in the address table, and a carried state finds repeated rows
+  // there; the stays of a fresh superbatch only read entries that were written
+  if (loop || start_ids) GINEX_HIP(fill_async<int32_t>(state.addr, num_nodes, -1, st));
   {
     int64_t blocks = ceil_div(cap, TB * 8);
     if (blocks > 4096) blocks = 4096;
@@ -2561,34 +2638,24 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
     GINEX_HIP(fill_async<uint32_t>(state.bitmap, state.words, 0u, st));
     GINEX_HIP(fill_async<int64_t>(miss_count, S, 0, st));
     GINEX_HIP(fill_async<int64_t>(cs_offsets, S + 1, 0, st));
-    hipLaunchKernelGGL(k_look_right, dim3((unsigned)w.look_tiles), dim3(TB), off_lds, st, sorted,
-                       total, w.d_offsets, S, w.next_iter);
-    GINEX_LAUNCH_CHECK();
+    if (loop) {
+      hipLaunchKernelGGL(k_look_right, dim3((unsigned)w.look_tiles), dim3(TB), off_lds, st, sorted,
+                         total, w.d_offsets, S, w.next_iter);
+      GINEX_LAUNCH_CHECK();
+    }
+  }
+
+  if (stays) {
+    uint64_t* const ends = sorted == w.pairs_a ? w.pairs_b : w.pairs_a;
+    uint64_t* const rows = heads == w.heads_a ? w.heads_b : w.heads_a;
+    return stays_run(who, w, sorted, ends, rows, distinct, start_ids ? nullptr : heads + (cap - 1), ids,
+                     ids_offsets, total, S, in_ids, out_ids, in_positions, cs_capacity, cs_offsets, miss_count,
+                     src_line, total_changes, start_ids != nullptr, final_ids, st);
   }
 
   // part 3: the recurrence, with no host round trip between iterations
   const size_t touch_lds = sizeof(uint32_t) * 2 * (S + 1);
   Outputs outs{in_ids, out_ids, in_positions, cs_capacity, cs_offsets, miss_count};
-  // Belady with a cache that does not hold the superbatch: the threshold bucket of every
-  // iteration from histograms of next_iter alone, in front of the loop (GINEX_STATIC_THRESHOLDS=0:
-  // from histograms of the state, iteration by iteration, as LRU needs it)
-  const char* static_env = getenv("GINEX_STATIC_THRESHOLDS");
-  const bool static_thresholds = !lru && !state.dead_only && S <= STATIC_S_MAX &&
-                                 !(static_env && static_env[0] == '0');
-  if (static_thresholds) {
-    int64_t longest = 0;
-    for (int32_t i = 0; i < S; ++i)
-      longest = std::max<int64_t>(longest, ids_offsets[i + 1] - ids_offsets[i]);
-    GINEX_HIP(fill_async<uint32_t>(w.key_hists, (int64_t)S * (S + 1), 0u, st));
-    GINEX_HIP(fill_async<uint32_t>(w.touch_ctr, 2, 0u, st));
-    if (longest > 0)
-      hipLaunchKernelGGL(k_key_hists, dim3((unsigned)ceil_div(longest, TB * TOUCH_ITEMS), (unsigned)S),
-                         dim3(TB), sizeof(uint32_t) * (S + 1), st, w.next_iter, w.d_offsets, S,
-                         w.key_hists);
-    hipLaunchKernelGGL(k_static_roll, dim3(1), dim3(BIG), 0, st, state, w.key_hists, w.d_offsets,
-                       w.static_plan, miss_count);
-    GINEX_LAUNCH_CHECK();
-  }
   {
     const int64_t res_blocks = ceil_div(cap, TB * MARK_ITEMS);
     const int64_t evict_blocks = ceil_div(w.evict_tiles, TB / WAVE);
@@ -2602,38 +2669,6 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
       it.key = lru ? S - 1 - i : -1;
       it.lo_bin = lru ? S - 1 - i : i + 1;
       it.src_line = src_line ? src_line + lo : nullptr;
-      if (static_thresholds) {
-        if (it.n > 0) {
-          if (it.n < TOUCH_FEW) {
-            const int64_t touch_blocks = ceil_div(it.n, TB * 4);
-            hipLaunchKernelGGL(k_touch_static<4>, dim3((unsigned)(touch_blocks + res_blocks)), dim3(TB),
-                               0, st, state, it, w.static_plan, w.touch_ctr, touch_blocks);
-          } else {
-            const int64_t touch_blocks = ceil_div(it.n, TB * 8);
-            hipLaunchKernelGGL(k_touch_static<8>, dim3((unsigned)(touch_blocks + res_blocks)), dim3(TB),
-                               0, st, state, it, w.static_plan, w.touch_ctr, touch_blocks);
-          }
-        }
-        hipLaunchKernelGGL(k_decide, dim3(1), dim3(BIG), 0, st, state, i, w.static_plan, w.touch_ctr,
-                           outs, w.evict_tiles);
-        GINEX_LAUNCH_CHECK();
-        if (it.n == 0) continue;
-        if (it.n < TOUCH_FEW) {
-          const int64_t in_tiles = ceil_div(it.n, (int64_t)TB * IN_ITEMS);
-          hipLaunchKernelGGL(k_flags<IN_ITEMS>, dim3((unsigned)(w.evict_tiles + in_tiles + 1)), dim3(TB),
-                             0, st, state, it, w.evict_tiles, in_tiles);
-          hipLaunchKernelGGL(k_emit_pair<IN_ITEMS>, dim3((unsigned)(evict_blocks + in_tiles)), dim3(TB),
-                             0, st, state, it, outs, w.evict_tiles);
-        } else {
-          const int64_t in_tiles = ceil_div(it.n, (int64_t)TB * IN_ITEMS_MANY);
-          hipLaunchKernelGGL(k_flags<IN_ITEMS_MANY>, dim3((unsigned)(w.evict_tiles + in_tiles + 1)),
-                             dim3(TB), 0, st, state, it, w.evict_tiles, in_tiles);
-          hipLaunchKernelGGL(k_emit_pair<IN_ITEMS_MANY>, dim3((unsigned)(evict_blocks + in_tiles)),
-                             dim3(TB), 0, st, state, it, outs, w.evict_tiles);
-        }
-        GINEX_LAUNCH_CHECK();
-        continue;
-      }
       if (it.n > 0) {
         hipLaunchKernelGGL(k_touch, dim3((unsigned)ceil_div(it.n, TB * TOUCH_ITEMS)), dim3(TB),
                            touch_lds, st, state, it, (unsigned long long*)(miss_count + i));
@@ -2650,9 +2685,9 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
         hipLaunchKernelGGL(k_find, dim3(1), dim3(BIG), 0, st, state);
         GINEX_LAUNCH_CHECK();
       }
-      hipLaunchKernelGGL(k_flags<IN_ITEMS>, dim3((unsigned)(w.evict_tiles + in_tiles + 1)), dim3(TB), 0,
+      hipLaunchKernelGGL(k_flags, dim3((unsigned)(w.evict_tiles + in_tiles + 1)), dim3(TB), 0,
                          st, state, it, w.evict_tiles, in_tiles);
-      hipLaunchKernelGGL(k_emit_pair<IN_ITEMS>, dim3((unsigned)(evict_blocks + in_tiles)), dim3(TB), 0, st,
+      hipLaunchKernelGGL(k_emit_pair, dim3((unsigned)(evict_blocks + in_tiles)), dim3(TB), 0, st,
                          state, it, outs, w.evict_tiles);
       GINEX_LAUNCH_CHECK();
     }

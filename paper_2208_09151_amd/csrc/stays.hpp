@@ -1,0 +1,1009 @@
+// Belady changesets from the trace alone (Ginex Section 3.4), for a cache that is smaller than
+// the distinct rows of the superbatch.  Included by changeset.hip only.
+//
+// A stay is the time between two accesses of a row, from iteration i to iteration j (j = S: the
+// row is not accessed again; i = "start": the row is in the start state).  During its stay the
+// row's key is j.  k_static_roll knows, before anything is simulated, the threshold bucket j*_t
+// of every iteration t and how many rows it drops from that bucket (rem_t), so
+//   * a stay ends at the first t in [i, j) with j*_t < j, whatever the cache holds,
+//   * only where j*_t = j and rem_t > 0 the row is in the bucket that is cut, and there its
+//     class (incoming rows go first) and its id decide.
+// A table over (j, i) holds both the first t with j*_t < j and the first cut of bucket j from i on;
+// a cut is three words (kind, id limit T, nothing else).  Cuts of different iterations depend on
+// each other only through the accesses of iteration t itself (which of them hit: cuts of bucket
+// t) and through earlier cuts of the same bucket, so they are decided in a few levels of
+// independent cuts instead of one after the other.  The cuts of bucket "never" (j* = S, most of the
+// last iterations) decide no hit and no insertion; they follow after the others, see below.
+// With all cuts decided, hits, misses, insertions and the iteration that evicts every row
+// follow for all accesses at once, and the only thing left that is sequential is which line
+// an inserted row gets: one launch per iteration, whose work is the iteration's changes.
+// Before, an iteration was four launches that passed over its accesses and over all lines.
+#pragma once
+
+constexpr int STATIC_S_MAX = 2048;      // iterations up to which the (S + 1) x S table is kept
+enum { CUT_NONE = 0,      // nothing is dropped from bucket j*
+       CUT_IN_SOME = 1,   // incoming rows of the bucket with an id above T
+       CUT_IN_ALL = 2,    // all incoming rows of the bucket
+       CUT_RES = 3 };     // all incoming rows, and residents of the bucket with an id above T
+
+struct Cut {              // one per iteration
+  int32_t jstar;          // threshold bucket, S + 1: the iteration drops nothing
+  int32_t rem;            // rows to drop from it
+  int32_t kind;           // CUT_*
+  int32_t T;
+  uint32_t n_res, n_in;   // members of the bucket by class, while the cut is decided;
+                          // bucket "never": the part of the ids that is cut, rows that stay in it
+};
+
+// The ends of an access's two stays in one word: where and when the row was accessed before, when
+// it is accessed next.  Bit 63: the cut of this access's own iteration dropped it.
+constexpr uint32_t FROM_START = 0xFFFEu;    // no earlier access, but the start state holds the row
+constexpr uint32_t NO_STAY = 0xFFFFu;       // no earlier access: a miss
+constexpr uint64_t BYPASSED = 1ull << 63;
+constexpr uint32_t NO_CUT = 0xFFFFu;        // in the table: no cut ahead
+
+__device__ __forceinline__ uint32_t stay_prev_pos(uint64_t w) { return (uint32_t)w; }
+__device__ __forceinline__ uint32_t stay_prev(uint64_t w) { return (uint32_t)(w >> 32) & 0xFFFFu; }
+__device__ __forceinline__ int32_t stay_next(uint64_t w) { return (int32_t)(w >> 48) & 0x7FFF; }
+
+struct Stays {
+  uint64_t* ends;          // [total] see above (free once the insertions are marked)
+  const int64_t* off;      // [S + 1]
+  const int32_t* ids;      // [total]
+  const uint32_t* table;   // [(S + 1) * S]
+  Cut* cuts;               // [S]
+  int32_t* members;        // [total] members of the buckets that are being cut, bucket j at off[j]
+  const int32_t* never;    // [NEVER_LEVELS * (S + 1)] see k_never_lift
+  int32_t S;
+};
+
+// Is the row of a run head (first access of its row, in iteration `first`) in the start state?
+// Fresh superbatch: C_0 is the `cap` smallest (first access, id), the last of them *last_head.
+// Carried cache: the address table says.
+__device__ __forceinline__ bool in_start_state(uint32_t v, int32_t first, const uint64_t* last_head,
+                                               const int32_t* addr) {
+  return last_head ? (((uint64_t)(uint32_t)first << 32) | v) <= *last_head : addr[v] >= 0;
+}
+
+// One pass over the node-sorted pairs: the ends of every access's stays, written at its position
+// (one scattered word per access; bound by that store).
+__global__ __launch_bounds__(TB) void k_stay_ends(const uint64_t* __restrict__ sorted, int64_t n,
+                                                  const int64_t* __restrict__ off, int32_t S,
+                                                  const uint64_t* __restrict__ last_head,
+                                                  const int32_t* __restrict__ addr,
+                                                  uint64_t* __restrict__ ends) {
+  extern __shared__ int32_t lds_off[];
+  load_offsets(lds_off, off, S);
+  const int64_t base = (int64_t)blockIdx.x * LOOK_TILE;
+#pragma unroll
+  for (int i = 0; i < LOOK_ITEMS; ++i) {
+    const int64_t j = base + i * TB + threadIdx.x;
+    if (j >= n) continue;
+    const uint64_t cur = sorted[j];
+    const uint32_t v = (uint32_t)(cur >> 32), p = (uint32_t)cur;
+    uint32_t prev_pos = 0, prev = NO_STAY, next = (uint32_t)S;
+    const uint64_t left = j > 0 ? sorted[j - 1] : ~cur;
+    if ((uint32_t)(left >> 32) == v) {
+      prev_pos = (uint32_t)left;
+      prev = (uint32_t)iter_of(lds_off, S, (int32_t)prev_pos);
+    } else if (in_start_state(v, last_head ? iter_of(lds_off, S, (int32_t)p) : 0, last_head, addr)) {
+      prev = FROM_START;
+    }
+    if (j + 1 < n) {
+      const uint64_t r = sorted[j + 1];
+      if ((uint32_t)(r >> 32) == v) next = (uint32_t)iter_of(lds_off, S, (int32_t)(uint32_t)r);
+    }
+    ends[p] = ((uint64_t)next << 48) | ((uint64_t)prev << 32) | prev_pos;
+  }
+}
+
+// table[j][s], for a stay that ends at j and is followed from iteration s on: low half the first
+// t in [s, j) with j*_t < j (j if there is none), high half the first cut of bucket j in front of
+// that (NO_CUT).  One thread per j walks backwards; s >= j reads "reaches j".
+__global__ __launch_bounds__(WAVE) void k_stay_table(const Cut* __restrict__ cuts, int32_t S,
+                                                     uint32_t* __restrict__ table) {
+  extern __shared__ int32_t lds_js[];    // [S] j*, with the sign bit where nothing is cut
+  for (int t = threadIdx.x; t < S; t += WAVE)
+    lds_js[t] = cuts[t].rem > 0 ? cuts[t].jstar : ~cuts[t].jstar;
+  __syncthreads();
+  const int32_t j = blockIdx.x * WAVE + threadIdx.x;
+  if (j > S) return;
+  uint32_t end = (uint32_t)j, cut = NO_CUT;
+  for (int32_t t = S - 1; t >= 0; --t) {
+    if (t < j) {
+      const int32_t raw = lds_js[t];
+      const int32_t jstar = raw < 0 ? ~raw : raw;
+      if (jstar < j) {
+        end = (uint32_t)t;
+        cut = NO_CUT;
+      } else if (raw == j) {
+        cut = (uint32_t)t;
+      }
+    }
+    table[(int64_t)j * S + t] = (cut << 16) | end;
+  }
+}
+
+// The iteration that drops row v during its stay [i, j), j if none does; cuts from `limit` on are
+// not looked at (they may not have been decided yet).  own: the access that began the stay, as a
+// word of `ends` (its BYPASSED bit is read only if the cut of its own iteration is in bucket j).
+__device__ __forceinline__ int32_t stay_end(const Stays& q, uint32_t i, int32_t j, uint32_t v,
+                                            const uint64_t* own, int32_t limit) {
+  const uint32_t* row = q.table + (int64_t)j * q.S;
+  const uint32_t w = row[i == FROM_START ? 0u : i];
+  uint32_t t = w >> 16;
+  while (t != NO_CUT && (int32_t)t < limit) {
+    const Cut c = q.cuts[t];
+    if (c.kind == CUT_RES && (int32_t)v > c.T) return (int32_t)t;
+    if (t == i && own && (*own & BYPASSED)) return (int32_t)t;
+    if ((int32_t)t + 1 >= j) break;
+    t = row[t + 1] >> 16;
+  }
+  return (int32_t)(w & 0xFFFFu);
+}
+
+// Rows that are never accessed again sit in the bucket that most of the last iterations cut, so
+// their stays would meet cut after cut (108 of 200 iterations for a cache that holds two fifths of the
+// rows).  never[0][t]: ids above it leave that bucket in iteration t (-1: all of them);
+// never[k][t]: the smallest of 2^k entries from t on, so that the first iteration that drops a row is
+// found in NEVER_LEVELS steps (15.0 -> {WALK} ms for k_stays_walk on 154 M accesses).
+constexpr int NEVER_LEVELS = 12;   // 2^12 > STATIC_S_MAX
+
+__global__ __launch_bounds__(BIG) void k_never_lift(const Cut* __restrict__ cuts, int32_t S,
+                                                    int32_t* __restrict__ never) {
+  for (int32_t t = threadIdx.x; t <= S; t += BIG) {
+    int32_t T = -1;                 // t = S: the end of the superbatch stops every search
+    if (t < S) {
+      const Cut c = cuts[t];
+      T = c.jstar < S ? -1 : c.jstar == S && c.kind == CUT_RES ? c.T : INT32_MAX;
+    }
+    never[t] = T;
+  }
+  for (int k = 1; k < NEVER_LEVELS; ++k) {
+    __syncthreads();
+    const int32_t* below = never + (int64_t)(k - 1) * (S + 1);
+    for (int32_t t = threadIdx.x; t <= S; t += BIG) {
+      const int32_t u = t + (1 << (k - 1));
+      const int32_t a = below[t], b = below[u < S ? u : S];
+      never[(int64_t)k * (S + 1) + t] = a < b ? a : b;
+    }
+  }
+}
+
+// The iteration that drops row v, resident and never accessed again from iteration i on; S if none.
+// `never`: the array, or a copy of it in LDS; levels: as many as S needs.
+__device__ __forceinline__ int32_t never_end(const int32_t* never, int32_t S, int levels, int32_t i, uint32_t v) {
+  int32_t t = i;
+  for (int k = levels - 1; k >= 0; --k)
+    if (t + (1 << k) <= S && never[k * (S + 1) + t] >= (int32_t)v) t += 1 << k;
+  return t;
+}
+
+__device__ __forceinline__ int never_levels(int32_t S) { return 32 - __clz(S); }   // 2^levels > S
+
+// Does the access with these ends (iteration j, row v) hit?
+__device__ __forceinline__ bool stay_hits(const Stays& q, uint64_t ends, int32_t j, uint32_t v) {
+  const uint32_t prev = stay_prev(ends);
+  if (prev == NO_STAY) return false;
+  return stay_end(q, prev, j, v, prev == FROM_START ? nullptr : &q.ends[stay_prev_pos(ends)], j) == j;
+}
+
+// Is a miss of an iteration with cut c, next accessed in iteration `next`, inserted?  (One that is never
+// accessed again is not: where bucket "never" is cut, the iteration drops as many rows as it has
+// misses, incoming rows of the bucket first.)
+__device__ __forceinline__ bool stay_inserts(const Stays& q, const Cut& c, int32_t next, uint32_t v) {
+  return next < c.jstar ? next < q.S
+                        : next == c.jstar && next < q.S &&
+                              (c.kind == CUT_NONE || (c.kind == CUT_IN_SOME && (int32_t)v <= c.T));
+}
+
+// ---- the cuts -----------------------------------------------------------------------------------
+
+constexpr int CUT_ITEMS = 8;
+constexpr int CUT_TILE = TB * CUT_ITEMS;
+
+// Members of the buckets of a level's cuts (blockIdx.y = cut, jobs[] its iteration): the accesses of
+// iteration j whose row is resident since before t (class resident), and the accesses of
+// iteration t with key j (resident if they hit, else incoming).  Both lists are kept, residents as
+// ids from the front of bucket j's region, incoming rows as positions from its end.
+__global__ __launch_bounds__(TB) void k_cut_members(Stays q, const int32_t* __restrict__ jobs) {
+  __shared__ uint32_t smem[TB / WAVE + 1];
+  __shared__ uint32_t s_at[2];
+  const int32_t t = jobs[blockIdx.y];
+  Cut* cut = &q.cuts[t];
+  const int32_t j = cut->jstar;
+  const int64_t base = (int64_t)blockIdx.x * CUT_TILE;
+  const int64_t jo = q.off[j], nj = q.off[j + 1] - jo, to = q.off[t], nt = q.off[t + 1] - to;
+  if (base >= nj + nt) return;                    // uniform
+  uint64_t w[CUT_ITEMS];
+  uint32_t v[CUT_ITEMS], kind[CUT_ITEMS];         // kind 1: resident, 2: incoming
+  uint32_t n_res = 0, n_in = 0;
+#pragma unroll
+  for (int k = 0; k < CUT_ITEMS; ++k) {
+    int64_t x = base + k * TB + threadIdx.x;
+    x = x < nj + nt ? x : base;
+    const int64_t p = x < nj ? jo + x : to + (x - nj);
+    w[k] = q.ends[p];
+    v[k] = (uint32_t)q.ids[p];
+  }
+#pragma unroll
+  for (int k = 0; k < CUT_ITEMS; ++k) {
+    const int64_t x = base + k * TB + threadIdx.x;
+    kind[k] = 0;
+    if (x >= nj + nt) continue;
+    if (x < nj) {                                 // an access that ends a stay with key j
+      const uint32_t prev = stay_prev(w[k]);
+      if (prev == NO_STAY || (prev != FROM_START && (int32_t)prev >= t)) continue;
+      const int32_t end = stay_end(q, prev, j, v[k],
+                                   prev == FROM_START ? nullptr : &q.ends[stay_prev_pos(w[k])], t);
+      kind[k] = end >= t ? 1u : 0u;
+    } else if (stay_next(w[k]) == j) {            // an access of iteration t that begins one
+      kind[k] = stay_hits(q, w[k], t, v[k]) ? 1u : 2u;
+      if (kind[k] == 2) v[k] = (uint32_t)(to + (x - nj));
+    }
+    n_res += kind[k] == 1;
+    n_in += kind[k] == 2;
+  }
+  // one reservation per block and class
+  uint32_t tot_res, tot_in;
+  uint32_t at_res = block_exclusive_scan<uint32_t, TB>(n_res, smem, tot_res);
+  uint32_t at_in = block_exclusive_scan<uint32_t, TB>(n_in, smem, tot_in);
+  if (threadIdx.x == 0) {
+    s_at[0] = tot_res ? atomicAdd(&cut->n_res, tot_res) : 0u;
+    s_at[1] = tot_in ? atomicAdd(&cut->n_in, tot_in) : 0u;
+  }
+  __syncthreads();
+  at_res += s_at[0];
+  at_in += s_at[1];
+  // (distinct ids inside an iteration give at most nj members; the bound keeps repeated ones
+  // inside the region as well)
+#pragma unroll
+  for (int k = 0; k < CUT_ITEMS; ++k) {
+    if (kind[k] == 1) {
+      if (at_res < nj) q.members[jo + at_res] = (int32_t)v[k];
+      ++at_res;
+    } else if (kind[k] == 2) {
+      if (at_in < nj) q.members[jo + nj - 1 - at_in] = (int32_t)v[k];
+      ++at_in;
+    }
+  }
+}
+
+// One block of NT threads: the keep-th smallest (1-based) of the ids id(x), 0 <= x < n; entries with bit
+// 31 set do not count.  Radix select from the top, 11 + 10 + 10 bits.  0 < keep <= ids that count.
+template <int NT, typename Id>
+__device__ int32_t p_kth_smallest_id(int64_t n, int64_t keep, Id id) {
+  __shared__ uint32_t s_hist[2048];
+  __shared__ uint32_t s_scan[NT / WAVE + 1];
+  __shared__ uint32_t s_pick, s_below;
+  uint32_t prefix = 0;
+  int shift = 20, bits = 11;
+  uint32_t left = (uint32_t)keep;
+  for (int pass = 0; pass < 3; ++pass) {
+    for (int b = threadIdx.x; b < 2048; b += NT) s_hist[b] = 0;
+    if (threadIdx.x == 0) s_pick = s_below = 0;
+    __syncthreads();
+    for (int64_t x = threadIdx.x; x < n; x += NT) {
+      const uint32_t v = id(x);
+      if (v >> 31) continue;
+      if (pass == 0 || (v >> (shift + bits)) == prefix) atomicAdd(&s_hist[(v >> shift) & ((1u << bits) - 1u)], 1u);
+    }
+    __syncthreads();
+    constexpr int PER = 2048 / NT;
+    uint32_t mine = 0;
+    for (int b = 0; b < PER; ++b) mine += s_hist[threadIdx.x * PER + b];
+    uint32_t total;
+    uint32_t run = block_exclusive_scan<uint32_t, NT>(mine, s_scan, total);
+    for (int b = 0; b < PER; ++b) {
+      const uint32_t c = s_hist[threadIdx.x * PER + b];
+      if (run < left && run + c >= left) {
+        s_pick = (uint32_t)(threadIdx.x * PER + b);
+        s_below = run;
+      }
+      run += c;
+    }
+    __syncthreads();
+    prefix = (prefix << bits) | s_pick;
+    left -= s_below;
+    shift -= 10;
+    bits = 10;
+    __syncthreads();
+  }
+  return (int32_t)prefix;
+}
+
+// One block per cut of the level: which class is cut and where.
+__global__ __launch_bounds__(BIG) void k_cut_decide(Stays q, const int32_t* __restrict__ jobs) {
+  Cut* cut = &q.cuts[jobs[blockIdx.x]];
+  const Cut c = *cut;
+  const int64_t region = q.off[c.jstar], room = q.off[c.jstar + 1] - region;
+  const int64_t R = c.n_res < room ? c.n_res : room, I = c.n_in < room ? c.n_in : room;
+  const int64_t rem = c.rem;
+  int32_t kind, T = -1;
+  if (rem < I) {
+    kind = CUT_IN_SOME;
+    T = p_kth_smallest_id<BIG>(I, I - rem, [&](int64_t x) { return (uint32_t)q.ids[q.members[region + room - 1 - x]]; });
+  } else if (rem == I) {
+    kind = CUT_IN_ALL;
+  } else {
+    kind = CUT_RES;
+    const int64_t keep = R - (rem - I);
+    if (keep > 0)   // (always: a bucket that goes whole is not the threshold bucket)
+      T = p_kth_smallest_id<BIG>(R, keep, [&](int64_t x) { return (uint32_t)q.members[region + x]; });
+  }
+  // incoming rows that are dropped: the accesses that end their stays look for this mark
+  for (int64_t x = threadIdx.x; x < I; x += BIG) {
+    const int32_t p = q.members[region + room - 1 - x];
+    if (kind != CUT_IN_SOME || q.ids[p] > T) q.ends[p] |= BYPASSED;
+  }
+  __syncthreads();   // every thread has read the cut
+  if (threadIdx.x == 0) {
+    cut->kind = kind;
+    cut->T = T;
+  }
+}
+
+// ---- the lists and the evicting iterations ----------------------------------------------------------
+
+// Every access: hit or miss (src_line: 0 / -1, the lines follow), and whether a miss is an insertion
+// (bit p of ins_bits).  A miss that is never accessed again is none: where
+// bucket "never" is the one that is cut, the iteration drops as many rows as it has misses, incoming
+// rows of the bucket first.
+__global__ __launch_bounds__(TB) void k_stays_mark(Stays q, int64_t n, int32_t* __restrict__ src_line,
+                                                   uint32_t* __restrict__ ins_bits) {
+  extern __shared__ int32_t lds_off[];
+  load_offsets(lds_off, q.off, q.S);
+  const int64_t base = (int64_t)blockIdx.x * CUT_TILE;
+  int32_t i = iter_of(lds_off, q.S, (int32_t)base);   // of the tile's first access; advanced below
+  uint64_t w[CUT_ITEMS];
+#pragma unroll
+  for (int k = 0; k < CUT_ITEMS; ++k) {
+    const int64_t p = base + k * TB + threadIdx.x;
+    w[k] = q.ends[p < n ? p : base];
+  }
+#pragma unroll
+  for (int k = 0; k < CUT_ITEMS; ++k) {
+    const int64_t p = base + k * TB + threadIdx.x;
+    bool inserted = false, hit = false;
+    if (p < n) {
+      while (i + 1 < q.S && lds_off[i + 1] <= (int32_t)p) ++i;
+      const uint32_t prev = stay_prev(w[k]);
+      if (prev != NO_STAY) {
+        const uint32_t e = q.table[(int64_t)i * q.S + (prev == FROM_START ? 0u : prev)];
+        // (the id is read only where a cut has to be looked at)
+        hit = (e >> 16) == NO_CUT ? (int32_t)(e & 0xFFFFu) == i
+                                  : stay_hits(q, w[k], i, (uint32_t)q.ids[p]);
+      }
+      if (!hit) {
+        const Cut c = q.cuts[i];
+        const int32_t next = stay_next(w[k]);
+        inserted = stay_inserts(q, c, next, next == c.jstar ? (uint32_t)q.ids[p] : 0u);
+      }
+      if (src_line) src_line[p] = hit ? 0 : -1;
+    }
+    const uint64_t m = __ballot(inserted);
+    const int64_t first = base + k * TB + (threadIdx.x & ~(WAVE - 1));
+    if (lane_id() == 0 && first < n) ins_bits[first >> 5] = (uint32_t)m;
+    if (lane_id() == 32 && first + 32 < n) ins_bits[(first >> 5) + 1] = (uint32_t)(m >> 32);
+  }
+}
+
+// ---- the cuts of bucket "never" ---------------------------------------------------------------------
+//
+// The rows of the bucket are those whose last access hit (from that iteration on) and the
+// start-state rows the superbatch never accesses.  Iteration t, if it cuts the bucket, keeps the
+// keep_t of them with the smallest ids (keep_t is known from the thresholds), so one cut follows from
+// the one before.  The ids are divided into at most NEVER_PARTS parts; how many rows each part holds
+// after every cut needs no ids: the parts below the one that is cut keep all, the parts above lose
+// all.  One block walks the iterations over the parts' counts (k_never_parts: 0.7 us per iteration), and
+// what id the cut falls on is then found for all parts side by side, each from its own rows
+// (k_never_select).  Setting bits, counting, finding and clearing on one bitmap over all ids, cut
+// after cut, took 43 us per cut.
+constexpr int NEVER_PARTS = 1024;
+constexpr int64_t NEVER_COUNTS = int64_t(1) << 19;   // [S x parts] counters: fewer parts for many iterations
+
+struct Never {
+  uint64_t* rows;          // [distinct] id << 32 | iteration of its last access, if that hits (else NOT_HERE), by id
+  uint32_t* counts;        // [S * parts] rows that arrive in an iteration, by part
+  const uint32_t* idle;    // bitmap over ids: start-state rows without an access; null: a fresh superbatch
+  int64_t distinct, num_nodes;
+  int32_t parts, shift;    // part of an id = id >> shift
+};
+constexpr uint32_t NOT_HERE = 0xFFFFFFFFu;
+
+// counts[i][part], a block per stretch of rows (by id, so a block meets one or a few parts: it
+// counts per iteration in LDS and hands over where the part changes)
+__global__ __launch_bounds__(TB) void k_never_counts(Never nv, int32_t S) {
+  extern __shared__ uint32_t s_cnt[];     // [S]
+  const int64_t per = (((nv.distinct + gridDim.x - 1) / gridDim.x + TB - 1) / TB) * TB;
+  const int64_t first = (int64_t)blockIdx.x * per;
+  const int64_t last = first + per < nv.distinct ? first + per : nv.distinct;
+  if (first >= last) return;
+  for (int i = threadIdx.x; i < S; i += TB) s_cnt[i] = 0;
+  __syncthreads();
+  int32_t part = (int32_t)((nv.rows[first] >> 32) >> nv.shift);
+  const int32_t last_part = (int32_t)((nv.rows[last - 1] >> 32) >> nv.shift);
+  int64_t from = first;
+  while (true) {                          // uniform: one round per part of the stretch
+    int64_t lo = from, hi = last;         // the first row behind the part
+    if (part == last_part) lo = last;
+    while (lo < hi) {
+      const int64_t mid = (lo + hi) >> 1;
+      if ((int32_t)((nv.rows[mid] >> 32) >> nv.shift) <= part) lo = mid + 1; else hi = mid;
+    }
+    for (int64_t x = from + threadIdx.x; x < lo; x += TB) {
+      const uint32_t i = (uint32_t)nv.rows[x];
+      if (i != NOT_HERE) atomicAdd(&s_cnt[i], 1u);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < S; i += TB)
+      if (s_cnt[i]) {
+        atomicAdd(&nv.counts[(int64_t)i * nv.parts + part], s_cnt[i]);
+        s_cnt[i] = 0;
+      }
+    __syncthreads();
+    if (lo >= last) break;
+    from = lo;
+    part = (int32_t)((nv.rows[from] >> 32) >> nv.shift);
+  }
+}
+
+// start-state rows without an access, per part (blockIdx.x = part)
+__global__ __launch_bounds__(TB) void k_never_idle(Never nv, uint32_t* __restrict__ idle_counts) {
+  __shared__ uint32_t red[TB / WAVE];
+  const int64_t lo = (int64_t)blockIdx.x << nv.shift, hi = lo + (int64_t(1) << nv.shift);
+  uint32_t cnt = 0;                       // (parts are whole words)
+  for (int64_t w = (lo >> 5) + threadIdx.x; w < hi >> 5 && w * 32 < nv.num_nodes; w += TB)
+    cnt += __popc(nv.idle[w]);
+  const uint32_t total = block_sum_u32(cnt, red);
+  if (threadIdx.x == 0) idle_counts[blockIdx.x] = total;
+}
+
+// One block, a part per thread: which part every cut falls into and how many of its rows stay.
+__global__ __launch_bounds__(NEVER_PARTS) void k_never_parts(Never nv, int32_t S, Cut* __restrict__ cuts,
+                                                             const uint32_t* __restrict__ idle_counts) {
+  __shared__ uint32_t slots[2][NEVER_PARTS / WAVE];
+  int set = 0;                            // the two sets of slots take turns: one barrier per cut
+  const int32_t me = threadIdx.x;
+  const bool mine = me < nv.parts;
+  uint32_t have = mine && idle_counts ? idle_counts[me] : 0u;
+  constexpr int AHEAD = 4;                // arrivals and thresholds are requested AHEAD iterations early
+  uint32_t arrive[AHEAD];
+  Cut cut[AHEAD];
+#pragma unroll
+  for (int a = 0; a < AHEAD; ++a)
+    if (a < S) {
+      arrive[a] = mine ? nv.counts[(int64_t)a * nv.parts + me] : 0u;
+      cut[a] = cuts[a];
+    }
+  for (int32_t t0 = 0; t0 < S; t0 += AHEAD) {
+#pragma unroll
+    for (int a = 0; a < AHEAD; ++a) {
+      const int32_t t = t0 + a;
+      if (t >= S) break;                  // uniform
+      have += arrive[a];
+      const Cut c = cut[a];
+      if (t + AHEAD < S) {
+        arrive[a] = mine ? nv.counts[(int64_t)(t + AHEAD) * nv.parts + me] : 0u;
+        cut[a] = cuts[t + AHEAD];
+      }
+      if (c.jstar < S) have = 0;
+      if (c.jstar != S) continue;         // uniform
+      const uint32_t keep = c.n_res;      // (left there by k_static_roll)
+      uint32_t inc = wave_inclusive_scan(have);
+      if (lane_id() == WAVE - 1) slots[set][me / WAVE] = inc;
+      __syncthreads();
+      uint32_t before = inc - have, total = 0;
+#pragma unroll
+      for (int w = 0; w < NEVER_PARTS / WAVE; ++w) {
+        const uint32_t s = slots[set][w];
+        if (w < me / WAVE) before += s;
+        total += s;
+      }
+      set ^= 1;
+      if (keep >= total) {                // no resident goes
+        if (me == 0) {
+          cuts[t].kind = CUT_IN_ALL;
+          cuts[t].n_res = (uint32_t)nv.parts;
+        }
+        continue;                         // uniform
+      }
+      if (before < keep && before + have >= keep) {
+        cuts[t].kind = CUT_RES;
+        cuts[t].n_res = (uint32_t)me;
+        cuts[t].n_in = keep - before;
+        // the whole part stays: no look at its rows
+        cuts[t].T = keep == before + have ? (int32_t)((((int64_t)me + 1) << nv.shift) - 1) : -1;
+      }
+      if (before >= keep) have = 0;
+      else if (before + have > keep) have = keep - before;
+    }
+  }
+}
+
+// A block per part: the ids of the cuts that fall into it, in order.
+__global__ __launch_bounds__(BIG) void k_never_select(Never nv, int32_t S, Cut* __restrict__ cuts) {
+  extern __shared__ int32_t s_min[];      // [S] smallest limit of the part's cuts from iteration i on
+  __shared__ int32_t s_next, s_emptied;
+  const int32_t part = blockIdx.x;
+  int64_t from = 0, to = -1;              // the part's rows, found with its first cut
+  for (int i = threadIdx.x; i < S; i += BIG) s_min[i] = INT32_MAX;
+  int32_t done = -1;                      // the cut before
+  while (true) {
+    if (threadIdx.x == 0) {
+      s_next = S;
+      s_emptied = -1;
+    }
+    __syncthreads();
+    for (int32_t t = done + 1 + threadIdx.x; t < S; t += BIG)
+      if (cuts[t].jstar == S && cuts[t].kind == CUT_RES && cuts[t].n_res == (uint32_t)part && cuts[t].T < 0)
+        atomicMin(&s_next, t);
+    __syncthreads();
+    const int32_t t = s_next;
+    if (t >= S) return;                   // uniform
+    // the last iteration before t that emptied the part
+    for (int32_t e = threadIdx.x; e < t; e += BIG) {
+      const Cut c = cuts[e];
+      if (c.jstar < S || (c.jstar == S && c.kind == CUT_RES && c.n_res < (uint32_t)part)) atomicMax(&s_emptied, e);
+    }
+    if (to < 0) {                         // uniform
+      const uint64_t lo_id = (uint64_t)part << nv.shift, hi_id = lo_id + (1ull << nv.shift);
+      int64_t a = 0, b = nv.distinct;
+      while (a < b) {
+        const int64_t mid = (a + b) >> 1;
+        if ((nv.rows[mid] >> 32) < lo_id) a = mid + 1; else b = mid;
+      }
+      from = a;
+      b = nv.distinct;
+      while (a < b) {
+        const int64_t mid = (a + b) >> 1;
+        if ((nv.rows[mid] >> 32) < hi_id) a = mid + 1; else b = mid;
+      }
+      to = a;
+    }
+    __syncthreads();
+    const int32_t emptied = s_emptied;
+    const int64_t n = to - from, first_id = (int64_t)part << nv.shift;
+    const int64_t idle = nv.idle && emptied < 0 ? std::min<int64_t>(int64_t(1) << nv.shift, nv.num_nodes - first_id) : 0;
+    auto id = [&](int64_t x) -> uint32_t {
+      if (x < n) {
+        const uint64_t row = nv.rows[from + x];
+        const uint32_t i = (uint32_t)row, v = (uint32_t)(row >> 32);
+        return i != NOT_HERE && (int32_t)i <= t && (int32_t)i > emptied && (int32_t)v <= s_min[i] ? v : 0xFFFFFFFFu;
+      }
+      const uint32_t v = (uint32_t)(first_id + (x - n));
+      return (nv.idle[v >> 5] >> (v & 31) & 1u) && (int32_t)v <= s_min[0] ? v : 0xFFFFFFFFu;
+    };
+    const int32_t T = p_kth_smallest_id<BIG>(n + idle, cuts[t].n_in, id);
+    for (int32_t i = threadIdx.x; i <= t; i += BIG) s_min[i] = s_min[i] < T ? s_min[i] : T;
+    if (threadIdx.x == 0) cuts[t].T = T;
+    done = t;
+    __syncthreads();
+  }
+}
+
+// ---- one pass in node order: what every access's stay comes to ------------------------------------------
+//
+// A wave takes LINK_CHUNKS * 64 consecutive pairs, a block one tile of LOOK_TILE.  In node order the ends
+// of a stay are neighbours, so hits and insertions follow from the table (which stays in L2) without a
+// look at any per-access array; both are kept as bits in node order, word x / 64 for pair x.  (Reading
+// them as bits by position instead costs a random 128-byte line each: 0.3 ms per 33 M accesses.)
+// Written on the way: the row that ends a run and whether that access hit, for bucket "never", and
+// the iteration that evicts a start-state row that is gone before its first access.
+constexpr int LINK_CHUNKS = 8;
+static_assert(LINK_CHUNKS * TB == LOOK_TILE, "a block works on one tile of the run heads");
+
+__global__ __launch_bounds__(TB) void k_stays_links(Stays q, const uint64_t* __restrict__ sorted, int64_t n,
+                                                    const uint32_t* __restrict__ head_bases,
+                                                    const uint64_t* __restrict__ last_head,
+                                                    const int32_t* __restrict__ addr, Never nv,
+                                                    uint64_t* __restrict__ hit_words,
+                                                    uint64_t* __restrict__ ins_words,
+                                                    uint32_t* __restrict__ leave_start) {
+  extern __shared__ int32_t lds_off[];
+  __shared__ uint32_t s_heads[TB / WAVE];
+  load_offsets(lds_off, q.off, q.S);
+  const int lane = lane_id(), wave = threadIdx.x / WAVE;
+  const int64_t base = (int64_t)blockIdx.x * LOOK_TILE + wave * (WAVE * LINK_CHUNKS);
+  const int32_t start_end = last_head ? lds_off[(int32_t)(*last_head >> 32) + 1] : INT32_MAX;
+  // behind n: an id that no access has
+  uint64_t cur[LINK_CHUNKS + 1];
+#pragma unroll
+  for (int k = 0; k <= LINK_CHUNKS; ++k) {
+    const int64_t x = base + k * WAVE + (k < LINK_CHUNKS ? lane : 0);
+    cur[k] = x < n ? sorted[x] : ~0ull;
+  }
+  const uint64_t left = base > 0 && base - 1 < n ? sorted[base - 1] : ~0ull;
+  int32_t it[LINK_CHUNKS + 1];
+#pragma unroll
+  for (int k = 0; k <= LINK_CHUNKS; ++k)
+    it[k] = (cur[k] >> 32) != 0xFFFFFFFFull ? iter_of(lds_off, q.S, (int32_t)(uint32_t)cur[k]) : q.S;
+  // the next access of every pair's row, and whether the stay reaches it
+  int32_t next[LINK_CHUNKS];
+  uint32_t word[LINK_CHUNKS], more = 0, reach = 0, head = 0;      // bit k: chunk k
+#pragma unroll
+  for (int k = 0; k < LINK_CHUNKS; ++k) {
+    const uint32_t v = (uint32_t)(cur[k] >> 32);
+    uint32_t rv = __shfl_down(v, 1, WAVE), lv = __shfl_up(v, 1, WAVE);
+    int32_t rj = __shfl_down(it[k], 1, WAVE);
+    const uint32_t ov = __shfl((uint32_t)(cur[k + 1] >> 32), 0, WAVE);
+    const int32_t oj = __shfl(it[k + 1], 0, WAVE);
+    const uint32_t bv = k > 0 ? __shfl((uint32_t)(cur[k > 0 ? k - 1 : 0] >> 32), WAVE - 1, WAVE) : (uint32_t)(left >> 32);
+    if (lane == WAVE - 1) {
+      rv = ov;
+      rj = oj;
+    }
+    if (lane == 0) lv = bv;
+    const bool valid = v != 0xFFFFFFFFu;
+    more |= (valid && rv == v ? 1u : 0u) << k;
+    head |= (valid && lv != v ? 1u : 0u) << k;
+    next[k] = rv == v ? rj : q.S;
+    word[k] = valid && rv == v ? q.table[(int64_t)rj * q.S + it[k]] : 0u;
+  }
+#pragma unroll
+  for (int k = 0; k < LINK_CHUNKS; ++k)
+    if (more >> k & 1u) {
+      const bool r = (word[k] >> 16) == NO_CUT
+                         ? (int32_t)(word[k] & 0xFFFFu) == next[k]
+                         : stay_end(q, (uint32_t)it[k], next[k], (uint32_t)(cur[k] >> 32),
+                                    &q.ends[(uint32_t)cur[k]], next[k]) == next[k];
+      reach |= (r ? 1u : 0u) << k;
+    }
+  // the pair in front of the wave's stretch
+  bool left_reaches = false;
+  if ((left >> 32) != 0xFFFFFFFFull && (uint32_t)(left >> 32) == __shfl((uint32_t)(cur[0] >> 32), 0, WAVE)) {
+    const int32_t j = __shfl(it[0], 0, WAVE);
+    left_reaches = stay_end(q, (uint32_t)iter_of(lds_off, q.S, (int32_t)(uint32_t)left), j,
+                            (uint32_t)(left >> 32), &q.ends[(uint32_t)left], j) == j;
+  }
+  uint32_t hit = 0, heads = 0;
+#pragma unroll
+  for (int k = 0; k < LINK_CHUNKS; ++k) {
+    const uint32_t v = (uint32_t)(cur[k] >> 32), p = (uint32_t)cur[k];
+    bool reached = __shfl_up(reach, 1, WAVE) >> k & 1u;
+    const bool other = k > 0 ? __shfl(reach, WAVE - 1, WAVE) >> (k > 0 ? k - 1 : 0) & 1u : left_reaches;
+    if (lane == 0) reached = other;
+    bool h = reached;
+    if (head >> k & 1u) {
+      h = false;
+      if ((int32_t)p < start_end && in_start_state(v, it[k], last_head, addr)) {
+        const int32_t e = stay_end(q, FROM_START, it[k], v, nullptr, it[k]);
+        h = e == it[k];
+        if (!h) leave_start[addr[v]] = (uint32_t)e;
+      }
+    }
+    const bool valid = v != 0xFFFFFFFFu;
+    hit |= (valid && h ? 1u : 0u) << k;
+    bool in = false;
+    if (valid && !h && (more >> k & 1u)) in = stay_inserts(q, q.cuts[it[k]], next[k], v);
+    const uint64_t hw = __ballot(valid && h), iw = __ballot(in);
+    const int64_t x = base + k * WAVE;
+    if (lane == 0 && x < n) {
+      hit_words[x / WAVE] = hw;
+      ins_words[x / WAVE] = iw;
+    }
+    heads += __popcll(__ballot(head >> k & 1u));
+  }
+  // the last accesses, at the rank of their run
+  if (lane == 0) s_heads[wave] = heads;
+  __syncthreads();
+  int64_t r = head_bases[blockIdx.x];
+  for (int w = 0; w < wave; ++w) r += s_heads[w];
+#pragma unroll
+  for (int k = 0; k < LINK_CHUNKS; ++k) {
+    const uint64_t hm = __ballot(head >> k & 1u);
+    const bool last = (cur[k] >> 32) != 0xFFFFFFFFull && !(more >> k & 1u);
+    const uint64_t upto = lane == WAVE - 1 ? ~0ull : (2ull << lane) - 1ull;
+    if (last) nv.rows[r + __popcll(hm & upto) - 1] =
+        (cur[k] & 0xFFFFFFFF00000000ull) | (hit >> k & 1u ? (uint32_t)it[k] : NOT_HERE);
+    r += __popcll(hm);
+  }
+}
+
+// insertions of iteration i = set bits of its positions (blockIdx.x = i)
+__global__ __launch_bounds__(TB) void k_ins_count(const uint32_t* __restrict__ ins_bits,
+                                                  const int64_t* __restrict__ off,
+                                                  int64_t* __restrict__ cs_offsets) {
+  __shared__ uint32_t red[TB / WAVE];
+  const int64_t lo = off[blockIdx.x], hi = off[blockIdx.x + 1];
+  uint32_t cnt = 0;
+  if (hi > lo)
+    for (int64_t w = (lo >> 5) + threadIdx.x; w <= (hi - 1) >> 5; w += TB) {
+      uint32_t word = ins_bits[w];
+      if (w == lo >> 5) word &= ~((1u << (lo & 31)) - 1u);
+      if (w == (hi - 1) >> 5 && (hi & 31)) word &= (1u << (hi & 31)) - 1u;
+      cnt += __popc(word);
+    }
+  const uint32_t total = block_sum_u32(cnt, red);
+  if (threadIdx.x == 0) cs_offsets[blockIdx.x + 1] = total;
+}
+
+// cs_offsets[1 .. S] <- inclusive sums
+__global__ __launch_bounds__(BIG) void k_ins_offsets(int64_t* __restrict__ cs_offsets, int32_t S) {
+  __shared__ int64_t smem[BIG / WAVE + 1];
+  const int32_t per = (S + BIG - 1) / BIG, j0 = threadIdx.x * per;
+  int64_t mine = 0;
+  for (int32_t j = j0; j < j0 + per && j < S; ++j) mine += cs_offsets[j + 1];
+  int64_t total;
+  int64_t run = block_exclusive_scan<int64_t, BIG>(mine, smem, total);
+  for (int32_t j = j0; j < j0 + per && j < S; ++j) {
+    run += cs_offsets[j + 1];
+    cs_offsets[j + 1] = run;
+  }
+}
+
+// What becomes of the line of an inserted row (or of a start-state row): the iteration that evicts
+// it, LEAVES_NEXT if that is the one after its insertion, STAYS if none does.
+constexpr uint32_t STAYS = 0xFFFFFFFFu;
+constexpr uint32_t LEAVES_NEXT = 0xFFFFFFFEu;
+
+// The second pass in node order: for every insertion, and for the first access of every start-state row
+// that hits, the iteration that evicts the row.  A resident access is linked to its right neighbour if
+// that is a hit of the same row; the first stay that does not reach a hit gives the iteration for
+// all accesses linked to it, and only for those stays it is looked up.  A wave takes a stretch of
+// WALK_CHUNKS * 64 accesses; the words of hits and one shuffle serve 64 of them, from right to left,
+// and what no stay of a chunk settles comes from the chunk to its right (for the last chunk: from
+// behind the stretch, at most S accesses of one row).  Following the links access by access instead
+// (one thread per insertion) took 3.3 ms for 33 M accesses of 8.8 M rows and 32 ms for 154 M accesses
+// of rows that mostly stay, waves waiting for their longest row.
+constexpr int WALK_CHUNKS = 8;
+constexpr int64_t WALK_TILE = (int64_t)TB * WALK_CHUNKS;
+
+// The iteration that ends a resident's stay from iteration i on, which does not reach a hit (right: the
+// position of the row's next access, if there is one), as a record.
+__device__ __forceinline__ uint32_t walk_leaves(const Stays& q, const int32_t* lds_off, const int32_t* never,
+                                                uint32_t v, int32_t i, bool more, uint32_t right) {
+  const int32_t e = more ? stay_end(q, (uint32_t)i, iter_of(lds_off, q.S, (int32_t)right), v, nullptr, q.S)
+                         : never_end(never, q.S, never_levels(q.S), i, v);
+  return e < q.S ? (uint32_t)e : STAYS;
+}
+
+// NEVER_LDS: the limits of bucket "never" in LDS (their random reads are what a wave waits for most),
+// while that leaves room for eight blocks per CU.
+constexpr int32_t NEVER_LDS_S = 400;
+
+template <bool NEVER_LDS>
+__global__ __launch_bounds__(TB) void k_stays_walk(Stays q, const uint64_t* __restrict__ sorted,
+                                                   int64_t n, const int32_t* __restrict__ addr,
+                                                   const uint64_t* __restrict__ hit_words,
+                                                   const uint64_t* __restrict__ ins_words,
+                                                   const uint32_t* __restrict__ ins_bits,
+                                                   const uint32_t* __restrict__ ins_base,
+                                                   uint32_t* __restrict__ leave_ins,
+                                                   uint32_t* __restrict__ leave_start) {
+  extern __shared__ int32_t lds_off[];    // offsets [S + 1], limits [levels * (S + 1)]
+  const int32_t* never = q.never;
+  if (NEVER_LDS) {
+    int32_t* mine = lds_off + q.S + 1;
+    for (int x = threadIdx.x; x < never_levels(q.S) * (q.S + 1); x += TB) mine[x] = q.never[x];
+    never = mine;
+  }
+  load_offsets(lds_off, q.off, q.S);
+  const int lane = lane_id();
+  const int64_t base = ((int64_t)blockIdx.x * (TB / WAVE) + threadIdx.x / WAVE) * (WAVE * WALK_CHUNKS);
+  if (base >= n) return;                           // uniform over the wave
+  const int64_t words = (n + WAVE - 1) / WAVE;
+  uint64_t cur[WALK_CHUNKS + 1], hit[WALK_CHUNKS + 1], ins[WALK_CHUNKS];
+#pragma unroll
+  for (int k = 0; k <= WALK_CHUNKS; ++k) {
+    const int64_t x = base + k * WAVE + (k < WALK_CHUNKS ? lane : 0), w = base / WAVE + k;
+    cur[k] = x < n ? sorted[x] : ~0ull;            // behind n: an id that no access has
+    hit[k] = w < words ? hit_words[w] : 0ull;
+    if (k < WALK_CHUNKS) ins[k] = w < words ? ins_words[w] : 0ull;
+  }
+  const uint64_t left_of = base > 0 ? sorted[base - 1] : ~0ull;
+  uint64_t stops[WALK_CHUNKS];                     // the stays that do not reach a hit
+  uint32_t leave_of[WALK_CHUNKS];
+#pragma unroll
+  for (int k = 0; k < WALK_CHUNKS; ++k) {
+    const uint32_t v = (uint32_t)(cur[k] >> 32), p = (uint32_t)cur[k];
+    uint64_t right = ((uint64_t)__shfl_down(v, 1, WAVE) << 32) | __shfl_down(p, 1, WAVE);
+    const uint64_t other = shfl_u64(cur[k + 1], 0);
+    if (lane == WAVE - 1) right = other;
+    const uint64_t right_hits = (hit[k] >> 1) | (hit[k + 1] << (WAVE - 1));
+    const bool more = (uint32_t)(right >> 32) == v;
+    const bool end = !(more && (right_hits >> lane & 1));
+    stops[k] = __ballot(end);
+    leave_of[k] = STAYS;
+    if (end && ((hit[k] | ins[k]) >> lane & 1))
+      leave_of[k] = walk_leaves(q, lds_off, never, v, iter_of(lds_off, q.S, (int32_t)p), more, (uint32_t)right);
+  }
+  uint32_t carry = STAYS;
+#pragma unroll
+  for (int k = WALK_CHUNKS - 1; k >= 0; --k) {
+    if (k == WALK_CHUNKS - 1 && !(stops[k] >> (WAVE - 1))) {
+      // the stretch's last access is linked to the next stretch: on to the row's next stay that ends
+      // (at the latest with its last access)
+      for (int64_t ahead = base + WALK_CHUNKS * WAVE; ; ahead += WAVE) {
+        const int64_t y = ahead + lane, w = ahead / WAVE;
+        const uint64_t a = y < n ? sorted[y] : ~0ull, r = y + 1 < n ? sorted[y + 1] : ~0ull;
+        const bool more = y + 1 < n && (uint32_t)(r >> 32) == (uint32_t)(a >> 32);
+        const uint64_t h = w < words ? hit_words[w] : 0ull, h1 = w + 1 < words ? hit_words[w + 1] : 0ull;
+        const uint64_t m = __ballot(!(more && (((h >> 1) | (h1 << (WAVE - 1))) >> lane & 1)));
+        if (!m) continue;                          // (an access at or behind n ends)
+        const int at = __ffsll((unsigned long long)m) - 1;
+        uint32_t leaves = STAYS;
+        if (lane == at && y < n)
+          leaves = walk_leaves(q, lds_off, never, (uint32_t)(a >> 32), iter_of(lds_off, q.S, (int32_t)(uint32_t)a),
+                               more, (uint32_t)r);
+        carry = __shfl(leaves, at, WAVE);
+        break;
+      }
+    }
+    const uint64_t mine = stops[k] >> lane;        // stays that end, from this lane's on
+    const uint32_t found = __shfl(leave_of[k], mine ? lane + __ffsll((unsigned long long)mine) - 1 : lane, WAVE);
+    const uint32_t leaves = mine ? found : carry;
+    const uint32_t v = (uint32_t)(cur[k] >> 32), p = (uint32_t)cur[k];
+    if (ins[k] >> lane & 1)
+      leave_ins[ins_base[p >> 5] + __popc(ins_bits[p >> 5] & ((1u << (p & 31)) - 1u))] =
+          leaves == (uint32_t)(iter_of(lds_off, q.S, (int32_t)p) + 1) ? LEAVES_NEXT : leaves;
+    // a first access that hits is one of a start-state row
+    uint32_t lv = (uint32_t)__shfl_up(v, 1, WAVE);
+    const uint64_t before = k > 0 ? shfl_u64(cur[k > 0 ? k - 1 : 0], WAVE - 1) : left_of;
+    if (lane == 0) lv = (uint32_t)(before >> 32);
+    if ((hit[k] >> lane & 1) && lv != v) leave_start[addr[v]] = leaves;
+    carry = __shfl(leaves, 0, WAVE);
+  }
+}
+
+// Start-state rows that the superbatch never accesses (carried caches; keys: res_next).
+// leave_start may be the array of keys itself.
+__global__ __launch_bounds__(TB) void k_stays_idle(Stays q, const int32_t* __restrict__ res_id,
+                                                   const int32_t* res_next, int64_t cap,
+                                                   uint32_t* leave_start) {
+  const int64_t l = (int64_t)blockIdx.x * TB + threadIdx.x;
+  if (l >= cap || res_next[l] != q.S) return;
+  const int32_t e = never_end(q.never, q.S, never_levels(q.S), 0, (uint32_t)res_id[l]);
+  leave_start[l] = e < q.S ? (uint32_t)e : STAYS;
+}
+
+// Turns the evicting iterations into places of the per-iteration lists of evicted lines (list of
+// iteration e: from cs_offsets[e] on, filled[e] entries): a start-state row's line goes there now,
+// an insertion's record keeps the place for the step that learns its line.  A block counts per
+// iteration in LDS first, so that a counter sees one atomic per block.
+__global__ __launch_bounds__(TB) void k_leave_places(int64_t n_ins, int64_t cap, int32_t S,
+                                                     uint32_t* __restrict__ leave_ins,
+                                                     const uint32_t* __restrict__ leave_start,
+                                                     const int64_t* __restrict__ cs_offsets,
+                                                     uint32_t* __restrict__ filled,
+                                                     int32_t* __restrict__ leaving) {
+  extern __shared__ uint32_t s_cnt[];     // [S]
+  for (int e = threadIdx.x; e < S; e += TB) s_cnt[e] = 0;
+  __syncthreads();
+  const int64_t n = n_ins + cap;
+  const int64_t per = ((n + gridDim.x - 1) / gridDim.x + TB - 1) / TB * TB;
+  const int64_t first = (int64_t)blockIdx.x * per, last = first + per < n ? first + per : n;
+  for (int64_t x = first + threadIdx.x; x < last; x += TB) {
+    const uint32_t e = x < n_ins ? leave_ins[x] : leave_start[x - n_ins];
+    if (e < (uint32_t)S) atomicAdd(&s_cnt[e], 1u);
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < S; e += TB) {
+    const uint32_t c = s_cnt[e];
+    s_cnt[e] = c ? (uint32_t)cs_offsets[e] + atomicAdd(&filled[e], c) : 0u;
+  }
+  __syncthreads();
+  for (int64_t x = first + threadIdx.x; x < last; x += TB) {
+    const uint32_t e = x < n_ins ? leave_ins[x] : leave_start[x - n_ins];
+    if (e >= (uint32_t)S) continue;
+    const uint32_t at = atomicAdd(&s_cnt[e], 1u);
+    const bool room = (int64_t)at < cs_offsets[e + 1];   // (always, for distinct ids)
+    if (x < n_ins) leave_ins[x] = room ? at : STAYS;
+    else if (room) leaving[at] = (int32_t)(x - n_ins);
+  }
+}
+
+// ---- the lines: one launch per iteration -----------------------------------------------------------
+
+constexpr int64_t LARGE_CACHE = int64_t(1) << 21;   // lines from which tiles and blocks of the steps are larger
+
+struct Step {
+  uint64_t *now, *next;        // flag words: lines evicted by this iteration / the next one
+  uint32_t *cnt_now, *cnt_next, *cnt_clear;   // set flags per tile of 2^tile_shift lines; cnt_clear: to be zeroed
+  int64_t words, tiles;
+  int32_t tile_shift;
+  int64_t emit_blocks, flag_blocks;
+  int64_t dst, n_change;       // this iteration's records
+  int64_t next_dst, next_n;    // the next iteration's
+  const uint32_t* next_filled; // entries of the next iteration's list that stem from earlier iterations
+  int32_t* leaving;            // lists of evicted lines
+  const uint32_t* leave_ins;   // per insertion: place in `leaving`, LEAVES_NEXT or STAYS
+  const int32_t* in_ids;
+  int32_t* out_ids;
+  const int32_t* ids;          // this iteration's accesses
+  int32_t* src_line;           // null: not asked for
+  int64_t n;
+};
+
+__device__ __forceinline__ void flag_line(const Step& s, int32_t line) {
+  atomicOr((unsigned long long*)&s.next[line >> 6], 1ull << (line & 63));
+  atomicAdd(&s.cnt_next[line >> s.tile_shift], 1u);
+}
+
+// The flagged lines in line order take the iteration's insertions (a list known up front).  Roles
+// by block: [0, emit_blocks) lists and lines, LINE_WORDS flag words each; the next flag_blocks flag
+// the lines the next iteration evicts, as far as they were taken before this iteration (the others
+// are flagged by the emit blocks themselves); the rest looks up the lines of the iteration's hits.
+// Nothing one role reads is written by another: a row that hits is not inserted by the same
+// iteration, an evicted row keeps its address-table entry (its next access, a miss, does not
+// read it), and flags and counts alternate between two and three copies.
+template <int LINE_WORDS>   // flag words (64 lines each) a block of the emit role takes
+__global__ __launch_bounds__(TB) void k_step_lines(State st, Step s) {
+  constexpr int STEPS = LINE_WORDS == 64 ? 6 : 8;
+  static_assert(1 << STEPS == LINE_WORDS && LINE_WORDS <= TB, "a word per thread, found by bisection");
+  __shared__ uint32_t red[TB / WAVE], smem[TB / WAVE + 1];
+  __shared__ uint64_t s_word[LINE_WORDS];
+  __shared__ uint32_t s_incl[LINE_WORDS];
+  const int64_t b = blockIdx.x;
+  if (b >= s.emit_blocks + s.flag_blocks) {
+    constexpr int ITEMS = 4;
+    const int64_t base = (b - s.emit_blocks - s.flag_blocks) * (TB * ITEMS) + threadIdx.x;
+    int32_t v[ITEMS], mark[ITEMS];
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+      const int64_t p = base + k * TB;
+      v[k] = s.ids[p < s.n ? p : 0];
+      mark[k] = p < s.n ? s.src_line[p] : -1;
+    }
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k)
+      if (mark[k] >= 0) mark[k] = st.addr[v[k]];
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k)
+      if (mark[k] >= 0) s.src_line[base + k * TB] = mark[k];
+    return;
+  }
+  if (b >= s.emit_blocks) {
+    const int64_t have = *s.next_filled < s.next_n ? *s.next_filled : s.next_n;
+    for (int64_t x = (b - s.emit_blocks) * TB + threadIdx.x; x < have; x += s.flag_blocks * TB)
+      flag_line(s, s.leaving[s.next_dst + x]);
+    return;
+  }
+  const int64_t first_word = b * LINE_WORDS;
+  const int64_t first_tile = (first_word * 64) >> s.tile_shift;
+  const int64_t own_tiles = (LINE_WORDS * 64) >> s.tile_shift;
+  if (threadIdx.x < own_tiles && first_tile + threadIdx.x < s.tiles)
+    s.cnt_clear[first_tile + threadIdx.x] = 0;
+  if (s.n_change == 0) return;
+  uint64_t word = 0;
+  if (threadIdx.x < LINE_WORDS) {                  // whole waves
+    const int64_t at = first_word + threadIdx.x;
+    word = at < s.words ? s.now[at] : 0;
+    if (word) s.now[at] = 0;                       // consumed
+    s_word[threadIdx.x] = word;
+  }
+  const uint32_t flags = (uint32_t)__popcll(word);
+  uint32_t total;
+  const uint32_t ahead = block_exclusive_scan<uint32_t, TB>(flags, smem, total);
+  if (threadIdx.x < LINE_WORDS) s_incl[threadIdx.x] = ahead + flags;
+  if (total == 0) return;                          // uniform
+  const int64_t before = block_prefix_of(s.cnt_now, first_tile, red);
+  for (uint32_t k = threadIdx.x; k < total; k += TB) {
+    int lo = 0, hi = LINE_WORDS - 1;               // the word of the k-th flag
+#pragma unroll
+    for (int step = 0; step < STEPS; ++step) {
+      const int mid = (lo + hi) >> 1;
+      if (s_incl[mid] > k) hi = mid; else lo = mid + 1;
+    }
+    uint64_t bits = s_word[lo];
+    for (uint32_t skip = k - (s_incl[lo] - (uint32_t)__popcll(bits)); skip > 0; --skip) bits &= bits - 1;
+    const int32_t line = (int32_t)((first_word + lo) * 64 + (__ffsll((unsigned long long)bits) - 1));
+    const int64_t at = before + k;
+    if (at >= s.n_change) continue;                // (as many lines as insertions, for distinct ids)
+    const int32_t gone = st.res_id[line];
+    const int32_t comes = s.in_ids[s.dst + at];
+    const uint32_t leaves = s.leave_ins[s.dst + at];
+    s.out_ids[s.dst + at] = gone;
+    st.res_id[line] = comes;
+    st.addr[comes] = line;
+    if (leaves == LEAVES_NEXT) flag_line(s, line);
+    else if (leaves != STAYS) s.leaving[leaves] = line;
+  }
+}
+
+// the lines the first iteration evicts
+__global__ __launch_bounds__(TB) void k_step_flags(Step s) {
+  const int64_t have = *s.next_filled < s.next_n ? *s.next_filled : s.next_n;
+  for (int64_t x = (int64_t)blockIdx.x * TB + threadIdx.x; x < have; x += (int64_t)gridDim.x * TB)
+    flag_line(s, s.leaving[s.next_dst + x]);
+}
