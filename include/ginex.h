@@ -23,12 +23,12 @@
  *  - Environment switches, read at every call; none changes a result, only the way to it:
  *      GINEX_VALIDATE=1       check the documented preconditions on the device first
  *      GINEX_TRACE=1          ginex_changeset_resume reports on stderr which way it went
- *      GINEX_SAMPLER_LDS=0    seeds and first hop through the tables in HBM like the later hops
+ *      GINEX_SAMPLER_LDS=0    all hops through hash tables in HBM, none through tables in LDS
  *      GINEX_SAMPLER_TILES=n  at most n tiles of a batch per workgroup column of the sampler
  *      GINEX_DEAD_SCATTER=0/1 evictions among dead rows from a pass over the lines / from the id bitmap
  *      GINEX_LIVE_SELECT=1    no shortcut that relies on the cache holding the whole superbatch
- *      GINEX_STATIC_THRESHOLDS=0  Belady thresholds from histograms of the cache state, iteration by
- *                             iteration, instead of from the trace alone in front of the loop
+ *      GINEX_STATIC_THRESHOLDS=0  Belady changesets from a loop over the cache state, iteration by
+ *                             iteration, instead of from the trace alone
  *      GINEX_PLANNED=0/2      a carried cache that holds the whole superbatch: still the general
  *                             loop / the three-launch steps also where the replay would do
  */

@@ -33,9 +33,11 @@
 // The seeds go through the same count/scan/emit path as a stage with one candidate per
 // slot, which also removes repeated seeds.
 //
-// Where the hash set of a batch's seeds and first hop fits LDS (the usual case), those two
+// That is the way without LDS: seeds that do not fit it, fanouts above 32, workspaces without room for
+// buckets.  Where the hash set of a batch's seeds and first hop fits LDS (the usual case), those two
 // stages run in one workgroup per batch with the table in LDS instead (k_front_lds, further
-// down); the later hops, whose sets are far too large for that, run as described above.
+// down); the later hops, whose sets are far too large for one table there, go through tables in
+// LDS bucket by bucket (buckets.hpp) and share scan, emit and col with the way described above.
 #include <cstdlib>
 #include <cstring>
 #include <vector>
@@ -172,6 +174,7 @@ inline unsigned grid_blocks(int S, int64_t tiles_per_batch) {
 // many tiles per batch and a block strides over the tiles its batch really has.
 constexpr int64_t SLOT_TILES = 128;   // tiles of TB frontier slots
 constexpr int64_t PICK_TILES = 512;   // tiles of TB/G frontier nodes
+constexpr int64_t COPY_TILES = 64;    // blocks that copy a batch's list
 
 // GINEX_SAMPLER_TILES=n in the environment replaces both caps (any n >= 1 gives the same
 // result: only the assignment of tiles to blocks, and with it the order in which candidates
@@ -309,6 +312,8 @@ __device__ __forceinline__ void group_choose(uint32_t v, int64_t deg, int k, int
     }
   }
 }
+
+#include "buckets.hpp"
 
 template <int G, typename OffT, bool NC>
 __global__ __launch_bounds__(TB) void k_pick(Tables T, const OffT* __restrict__ offsets,
@@ -539,6 +544,8 @@ __global__ __launch_bounds__(TB) void k_emit(Tables T, const int32_t* __restrict
 // An id of an earlier stage carries its list position in its reference; an id that is new in
 // this stage is looked up through its slot, whose final value is PEND + the rank of the id's
 // first occurrence, whose entry in `cand` now holds the position.
+// BUCKETS: after k_bucket_dedup the reference is that rank itself.
+template <bool BUCKETS>
 __global__ __launch_bounds__(TB) void k_col(Tables T, const int32_t* __restrict__ nfront, int k,
                                             const int64_t* __restrict__ rowptr,
                                             int64_t rowptr_capacity,
@@ -554,7 +561,7 @@ __global__ __launch_bounds__(TB) void k_col(Tables T, const int32_t* __restrict_
   if (here.b < 0) return;
   const int b = here.b;
   const int nf = nfront[b];
-  const uint64_t* t = T.tab + T.tab_off[b];
+  const uint64_t* t = BUCKETS ? nullptr : T.tab + T.tab_off[b];
   const int32_t* cand_b = T.cand + b * T.cand_slots;
   for (int64_t tile = here.tile; tile * TB < nf; tile += tpb) {
     const int64_t idx = tile * TB + threadIdx.x;
@@ -584,7 +591,7 @@ __global__ __launch_bounds__(TB) void k_col(Tables T, const int32_t* __restrict_
           if (d < col_capacity) {
             const uint32_t where = ref[r];
             col[d] = where & OLD_ID ? (int32_t)(where & ~OLD_ID)
-                                    : cand_b[(uint32_t)t[where] - PEND];
+                                    : cand_b[BUCKETS ? where : (uint32_t)t[where] - PEND];
           }
         }
       }
@@ -661,10 +668,12 @@ struct Plan {
   int64_t stride_ids;                    // bound on the final list, per batch
   int64_t cand_slots, fr_slots, tiles;
   int64_t table_slots;                   // per batch, worst case (2 per list entry)
+  int64_t num_nodes;
+  int32_t most_buckets;                  // per batch, in any hop
   bool ok;
 };
 
-Plan make_plan(int64_t num_nodes, int64_t max_batch, const int32_t* fanout, int32_t H) {
+Plan make_plan(int64_t num_nodes, int64_t max_batch, const int32_t* fanout, int32_t H, int32_t S) {
   Plan p{};
   p.ok = true;
   // the seed stage has one slot per given seed (repeats included); after it a list never
@@ -672,8 +681,12 @@ Plan make_plan(int64_t num_nodes, int64_t max_batch, const int32_t* fanout, int3
   p.cand_slots = p.fr_slots = max_batch > 1 ? max_batch : 1;
   int64_t front = max_batch < num_nodes ? max_batch : num_nodes;
   if (front < 1) front = 1;
+  p.num_nodes = num_nodes;
+  p.most_buckets = 1;
   for (int h = 0; h < H; ++h) {
     p.stride_front[h] = front;
+    const int32_t buckets = bucket_count(front, fanout[h], num_nodes, S);
+    if (buckets > p.most_buckets) p.most_buckets = buckets;
     if (front * fanout[h] > p.cand_slots) p.cand_slots = front * fanout[h];
     if (front > p.fr_slots) p.fr_slots = front;
     int64_t next = front * (1 + (int64_t)fanout[h]);
@@ -703,6 +716,7 @@ struct Workspace {
   int32_t *nfront, *nlist_a, *nlist_b;
   int64_t *row_base, *col_base, *seed_off;
   int64_t* meta;
+  Buckets buckets;       // sits where the tables do: a hop uses one or the other
   size_t bytes;
 };
 
@@ -710,10 +724,30 @@ int64_t meta_elems(int32_t S, int32_t H) {
   return (int64_t)(S + 1) + (int64_t)S * (H + 1) + 2 * ((int64_t)S * H + 1) + 4;
 }
 
-Workspace carve(void* base, const Plan& p, int32_t S, int32_t H) {
+// with_buckets: room for the buckets as well, which on a small graph (where a list cannot outgrow the
+// graph but its candidates can) is more than the tables take.  A workspace without it still serves,
+// through the tables.
+Workspace carve(void* base, const Plan& p, int32_t S, int32_t H, bool with_buckets) {
   Arena a(base);
   Workspace w;
-  w.tab = a.take<uint64_t>((size_t)S * p.table_slots);
+  {
+    Buckets& q = w.buckets;
+    q = Buckets{};
+    q.list_tiles_at = ceil_div(p.fr_slots, TILE_NODES);
+    q.tiles = q.list_tiles_at + ceil_div(p.fr_slots, LIST_TILE);
+    q.list_at = p.cand_slots;
+    q.entries = p.cand_slots + p.fr_slots;
+    q.row = p.most_buckets + 1;
+    q.num_nodes = p.num_nodes;
+    Arena inside(base);
+    w.tab = inside.take<uint64_t>((size_t)S * p.table_slots);
+    const size_t tables = inside.used;
+    inside.used = 0;
+    q.id = inside.take<uint32_t>((size_t)S * q.entries);
+    q.rank = inside.take<uint16_t>((size_t)S * q.entries);
+    q.start = inside.take<uint16_t>((size_t)S * q.tiles * q.row);
+    a.used = with_buckets && inside.used > tables ? inside.used : tables;
+  }
   w.wlist = a.take<int32_t>((size_t)S * p.stride_ids);
   w.cand = a.take<int32_t>((size_t)S * p.cand_slots);
   w.ref = a.take<uint32_t>((size_t)S * p.cand_slots);
@@ -765,7 +799,7 @@ inline int64_t pick_tiles(int64_t front, int group) {
 // position, all without a table access outside the CU.  What crosses batches (where a
 // batch's adj segment starts) is left to k_stage_offsets; the picks' positions and the rows'
 // edge counts wait in the batch's scratch arrays until k_adj_copy moves them there.
-// The later hops do not fit (a batch's set reaches 10^5 ids) and keep the tables in HBM.
+// The later hops do not fit (a batch's set reaches 10^5 ids).
 constexpr int LDS_SLOTS = 16384;       // 128 KB
 constexpr int LDS_BLOCK = 1024;        // threads, and the most seeds a batch may have here
 constexpr int LDS_MAX_IDS = 12288;     // seeds + candidates of hop 0: load factor 0.75 at most
@@ -791,7 +825,7 @@ __device__ __forceinline__ uint32_t lds_place(unsigned long long* tab, uint32_t 
   }
 }
 
-template <int G, typename OffT, bool NC>
+template <int G, typename OffT, typename Pos, bool NC>
 __global__ __launch_bounds__(LDS_BLOCK) void k_front_lds(
     Tables T, const OffT* __restrict__ offsets, const int32_t* __restrict__ indices,
     const int64_t* __restrict__ nc_address_table, const int32_t* __restrict__ nc_cache_array,
@@ -848,43 +882,74 @@ __global__ __launch_bounds__(LDS_BLOCK) void k_front_lds(
     s_deg[tid] = (int32_t)(deg < 0x7FFFFFFF ? deg : 0x7FFFFFFF);
   }
   __syncthreads();
-  // One G-lane group per node and round; the reads of the picked neighbours of ROUNDS rounds
-  // are issued before any is inserted, so that they are in flight together.
-  constexpr int ROUNDS = 8;
-  const int sub = tid & (G - 1);
-  const int per_round = LDS_BLOCK / G;
-  for (int base = 0; base < n0; base += per_round * ROUNDS) {
-    uint32_t u[ROUNDS], rank[ROUNDS];
-#pragma unroll
-    for (int q = 0; q < ROUNDS; ++q) {
-      const int idx = base + q * per_round + tid / G;
-      const bool active = idx < n0;
-      const uint32_t v = active ? (uint32_t)list[idx] : 0u;
-      int64_t deg = active ? (int64_t)s_deg[idx] : 0;
+  if constexpr (G <= BUCKET_K_MAX) {
+    // one thread per node (see choose_picks): all reads of its neighbours are in flight together
+    if (tid < n0) {
+      const uint32_t v = (uint32_t)list[tid];
+      int64_t deg = (int64_t)s_deg[tid];
       if (deg == 0x7FFFFFFF) {   // saturated in LDS (a list of 2^31 entries or more): look again
         int64_t lo;
         bool cached;
         row_of<OffT, NC>(v, offsets, nc_address_table, nc_cache_array, lo, deg, cached);
       }
-      int c, slot;
-      int64_t pick;
-      group_choose<G>(v, deg, k, 0, seed, first_batch + (uint32_t)b, c, slot, pick);
-      rank[q] = 0xFFFFFFFFu;
-      u[q] = 0;
-      if (active && sub < c) {
-        const int64_t lo = s_lo[idx];
-        u[q] = (uint32_t)(lo < 0 ? nc_cache_array[~lo + pick] : indices[lo + pick]);
-        rank[q] = (uint32_t)(idx * k + slot);
-      }
-      if (active && sub == 0) s_cnt[idx] = (uint8_t)c;
-    }
+      Pos a[G];
+      choose_picks<G, Pos>(v, deg, k, 0, seed, first_batch + (uint32_t)b, a);
+      const int c = deg < k ? (int)deg : k;
+      const int64_t lo = s_lo[tid];
+      const int32_t* row = lo < 0 ? nc_cache_array + ~lo : indices + lo;
+      uint32_t u[G];
 #pragma unroll
-    for (int q = 0; q < ROUNDS; ++q)
-      if (rank[q] != 0xFFFFFFFFu) {
-        cand[rank[q]] = (int32_t)u[q];
-        const uint32_t h = lds_place(tab, u[q], PEND + rank[q], before);
-        ref[rank[q]] = before < PEND ? OLD_ID | before : h;
+      for (int i = 0; i < G; ++i)
+        if (i < c) u[i] = (uint32_t)row[a[i]];
+#pragma unroll
+      for (int i = 0; i < G; ++i)
+        if (i < c) {
+          const uint32_t rank = (uint32_t)(tid * k + pick_slot<G, Pos>(a, i));
+          cand[rank] = (int32_t)u[i];
+          const uint32_t h = lds_place(tab, u[i], PEND + rank, before);
+          ref[rank] = before < PEND ? OLD_ID | before : h;
+        }
+      s_cnt[tid] = (uint8_t)c;
+    }
+  } else {
+    // One G-lane group per node and round; the reads of the picked neighbours of ROUNDS rounds
+    // are issued before any is inserted, so that they are in flight together.
+    constexpr int ROUNDS = 8;
+    const int sub = tid & (G - 1);
+    const int per_round = LDS_BLOCK / G;
+    for (int base = 0; base < n0; base += per_round * ROUNDS) {
+      uint32_t u[ROUNDS], rank[ROUNDS];
+#pragma unroll
+      for (int q = 0; q < ROUNDS; ++q) {
+        const int idx = base + q * per_round + tid / G;
+        const bool active = idx < n0;
+        const uint32_t v = active ? (uint32_t)list[idx] : 0u;
+        int64_t deg = active ? (int64_t)s_deg[idx] : 0;
+        if (deg == 0x7FFFFFFF) {   // saturated in LDS (a list of 2^31 entries or more): look again
+          int64_t lo;
+          bool cached;
+          row_of<OffT, NC>(v, offsets, nc_address_table, nc_cache_array, lo, deg, cached);
+        }
+        int c, slot;
+        int64_t pick;
+        group_choose<G>(v, deg, k, 0, seed, first_batch + (uint32_t)b, c, slot, pick);
+        rank[q] = 0xFFFFFFFFu;
+        u[q] = 0;
+        if (active && sub < c) {
+          const int64_t lo = s_lo[idx];
+          u[q] = (uint32_t)(lo < 0 ? nc_cache_array[~lo + pick] : indices[lo + pick]);
+          rank[q] = (uint32_t)(idx * k + slot);
+        }
+        if (active && sub == 0) s_cnt[idx] = (uint8_t)c;
       }
+#pragma unroll
+      for (int q = 0; q < ROUNDS; ++q)
+        if (rank[q] != 0xFFFFFFFFu) {
+          cand[rank[q]] = (int32_t)u[q];
+          const uint32_t h = lds_place(tab, u[q], PEND + rank[q], before);
+          ref[rank[q]] = before < PEND ? OLD_ID | before : h;
+        }
+    }
   }
   __syncthreads();
   // per node: which of its picks are first occurrences (they hold their id's slot), and the
@@ -984,19 +1049,63 @@ void launch_pick(const Tables& T, const Plan& p, const ginex_csr_t* g, const int
   }
 }
 
+// Buckets are for hops whose picks a thread can keep in registers; the grid holds at most this many
+// workgroups per batch (they stride over the buckets a batch really has).
+constexpr int64_t BUCKET_GROUPS = 64;
+
+template <int K_MAX, typename OffT, typename Pos, bool NC>
+void launch_pick_tiles(const Tables& T, const Buckets& B, int64_t front, const ginex_csr_t* g,
+                       const int32_t* nfront, int k, int hop, int32_t S, uint64_t seed,
+                       uint32_t first_batch, hipStream_t st) {
+  const int64_t tpb = capped(ceil_div(front, TILE_NODES) + ceil_div(front, LIST_TILE), tile_cap(SLOT_TILES));
+  const int slots = TILE_NODES * k > LIST_TILE ? TILE_NODES * k : LIST_TILE;
+  hipLaunchKernelGGL((k_pick_tiles<K_MAX, OffT, Pos, NC>), dim3(grid_blocks(S, tpb)), dim3(TB),
+                     (sizeof(uint32_t) + sizeof(uint16_t)) * slots, st, T, B,
+                     static_cast<const OffT*>(g->offsets), g->indices, g->nc_address_table,
+                     g->nc_cache_array, nfront, k, hop, seed, first_batch, S, tpb, slots);
+}
+
+template <typename OffT, bool NC>
+void launch_pick_tiles(const Tables& T, const Buckets& B, int64_t front, const ginex_csr_t* g,
+                       const int32_t* nfront, int k, int hop, int32_t S, uint64_t seed,
+                       uint32_t first_batch, hipStream_t st) {
+  // row positions in 32 bits, unless a row could be longer than that
+  const bool wide = sizeof(OffT) == 8 && g->num_edges >= (int64_t(1) << 32);
+#define GINEX_TILES(K_MAX, Pos) \
+  launch_pick_tiles<K_MAX, OffT, Pos, NC>(T, B, front, g, nfront, k, hop, S, seed, first_batch, st)
+  if (wide) {
+    if constexpr (sizeof(OffT) == 8) {
+      if (k <= 16) GINEX_TILES(16, uint64_t);
+      else GINEX_TILES(BUCKET_K_MAX, uint64_t);
+    }
+  } else if (k <= 16) {
+    GINEX_TILES(16, uint32_t);
+  } else {
+    GINEX_TILES(BUCKET_K_MAX, uint32_t);
+  }
+#undef GINEX_TILES
+}
+
 template <typename OffT, bool NC>
 void launch_front(const Tables& T, const ginex_csr_t* g, const int32_t* seeds,
                   const int64_t* seed_off, int k, int32_t S, int32_t H, uint64_t seed,
                   uint32_t first_batch, const Meta& M, int32_t* nlist_seeds, uint64_t* batch_total,
                   hipStream_t st) {
   const OffT* off = static_cast<const OffT*>(g->offsets);
-#define GINEX_FRONT(G)                                                                          \
-  hipLaunchKernelGGL((k_front_lds<G, OffT, NC>), dim3((unsigned)S), dim3(LDS_BLOCK), 0, st, T, off, \
-                     g->indices, g->nc_address_table, g->nc_cache_array, seeds, seed_off, k, seed, \
-                     first_batch, H, M, nlist_seeds, batch_total)
-  if (k <= 16) GINEX_FRONT(16);
-  else if (k <= 32) GINEX_FRONT(32);
-  else GINEX_FRONT(64);
+  const bool wide = sizeof(OffT) == 8 && g->num_edges >= (int64_t(1) << 32);   // see launch_pick_tiles
+#define GINEX_FRONT(G, Pos)                                                                     \
+  hipLaunchKernelGGL((k_front_lds<G, OffT, Pos, NC>), dim3((unsigned)S), dim3(LDS_BLOCK), 0, st, T, \
+                     off, g->indices, g->nc_address_table, g->nc_cache_array, seeds, seed_off, k, \
+                     seed, first_batch, H, M, nlist_seeds, batch_total)
+  if (k > BUCKET_K_MAX || (wide && k > 16)) {   // (32 positions of 64 bits do not fit the registers)
+    GINEX_FRONT(64, uint64_t);
+  } else if (wide) {
+    if constexpr (sizeof(OffT) == 8) GINEX_FRONT(16, uint64_t);
+  } else if (k <= 16) {
+    GINEX_FRONT(16, uint32_t);
+  } else {
+    GINEX_FRONT(32, uint32_t);
+  }
 #undef GINEX_FRONT
 }
 
@@ -1008,12 +1117,12 @@ using namespace ginex;
 extern "C" size_t ginex_sample_workspace_bytes(int64_t num_nodes, int32_t S, int64_t max_batch,
                                                const int32_t* fanout, int32_t H) {
   if (check_shape(num_nodes, S, max_batch, fanout, H, "ginex_sample_workspace_bytes")) return 0;
-  const Plan p = make_plan(num_nodes, max_batch, fanout, H);
+  const Plan p = make_plan(num_nodes, max_batch, fanout, H, S);
   if (!p.ok) {
     set_error("ginex_sample_workspace_bytes: a batch could exceed 2^30 list entries");
     return 0;
   }
-  return carve(nullptr, p, S, H).bytes;
+  return carve(nullptr, p, S, H, true).bytes;
 }
 
 extern "C" int32_t ginex_sample_superbatch(
@@ -1047,9 +1156,11 @@ extern "C" int32_t ginex_sample_superbatch(
   }
   if (int32_t rc = check_shape(g->num_nodes, S, max_batch, fanout, H, who)) return rc;
   if (seed_offsets[S] > 0 && !seeds) return fail(GINEX_ERR_ARG, "%s: seeds is null", who);
-  const Plan p = make_plan(g->num_nodes, max_batch, fanout, H);
+  const Plan p = make_plan(g->num_nodes, max_batch, fanout, H, S);
   if (!p.ok) return fail(GINEX_ERR_ARG, "%s: a batch could exceed 2^30 list entries", who);
-  const Workspace w = carve(ws, p, S, H);
+  Workspace w = carve(ws, p, S, H, true);
+  const bool buckets_fit = ws_bytes >= w.bytes;
+  if (!buckets_fit) w = carve(ws, p, S, H, false);
   if (ws_bytes < w.bytes)
     return fail(GINEX_ERR_WORKSPACE, "%s: workspace of %zu bytes given, %zu needed", who, ws_bytes,
                 w.bytes);
@@ -1105,9 +1216,9 @@ extern "C" int32_t ginex_sample_superbatch(
   // Seeds and hop 0 of a batch in the LDS of one workgroup, when their hash set fits there
   // (GINEX_SAMPLER_LDS=0 keeps them on the tables in HBM; same result).
   const char* lds_env = getenv("GINEX_SAMPLER_LDS");
+  const bool lds = !(lds_env && lds_env[0] == '0');
   const bool front_lds = max_batch <= LDS_BLOCK &&
-                         max_batch * (1 + (int64_t)fanout[0]) <= LDS_MAX_IDS &&
-                         !(lds_env && lds_env[0] == '0');
+                         max_batch * (1 + (int64_t)fanout[0]) <= LDS_MAX_IDS && lds;
   if (front_lds) {
     const int k0 = fanout[0];
     if (g->nc_address_table) {
@@ -1149,31 +1260,59 @@ extern "C" int32_t ginex_sample_superbatch(
     const int32_t* nfront = stage < 0 ? w.nfront : nlist;
     const int64_t tpb = capped(ceil_div(front, TB), tile_cap(SLOT_TILES));
     const dim3 grid_slots(grid_blocks(S, tpb));
-    hipLaunchKernelGGL(k_table_plan, dim3(1), dim3(TB), 0, st, T, S, g->num_nodes, k, nfront,
-                       nlist, w.tab_total);
-    hipLaunchKernelGGL(k_table_clear, dim3(4096), dim3(TB), 0, st, T, w.tab_total, nfront, S, front);
-    GINEX_LAUNCH_CHECK();
-    if (stage >= 0) {
-      hipLaunchKernelGGL(k_reinsert, grid_slots, dim3(TB), 0, st, T, nlist, S, tpb);
+    // later hops: the hash sets in the LDS of a workgroup per bucket, where the picks of a node fit a
+    // thread's registers and the workspace has room (GINEX_SAMPLER_LDS=0: the tables in HBM)
+    const bool buckets = stage >= 0 && k <= BUCKET_K_MAX && buckets_fit && lds;
+    if (buckets) {
+      if (g->nc_address_table) {
+        if (g->offsets_64)
+          launch_pick_tiles<int64_t, true>(T, w.buckets, front, g, nfront, k, stage, S, rng_seed,
+                                           first_batch_index, st);
+        else
+          launch_pick_tiles<int32_t, true>(T, w.buckets, front, g, nfront, k, stage, S, rng_seed,
+                                           first_batch_index, st);
+      } else if (g->offsets_64) {
+        launch_pick_tiles<int64_t, false>(T, w.buckets, front, g, nfront, k, stage, S, rng_seed,
+                                          first_batch_index, st);
+      } else {
+        launch_pick_tiles<int32_t, false>(T, w.buckets, front, g, nfront, k, stage, S, rng_seed,
+                                          first_batch_index, st);
+      }
+      GINEX_LAUNCH_CHECK();
+      const int64_t groups = capped(bucket_count(front, k, g->num_nodes, S), tile_cap(BUCKET_GROUPS));
+      hipLaunchKernelGGL(k_bucket_dedup, dim3(grid_blocks(S, groups)), dim3(BUCKET_THREADS), 0, st, T,
+                         w.buckets, nfront, k, S, groups);
+      GINEX_LAUNCH_CHECK();
+      hipLaunchKernelGGL(k_tile_firsts, grid_slots, dim3(TB), sizeof(uint32_t) * TILE_NODES * k, st, T,
+                         w.buckets, nfront, k, w.tile_sums, p.tiles, S, tpb);
+      GINEX_LAUNCH_CHECK();
+    } else {
+      hipLaunchKernelGGL(k_table_plan, dim3(1), dim3(TB), 0, st, T, S, g->num_nodes, k, nfront,
+                         nlist, w.tab_total);
+      hipLaunchKernelGGL(k_table_clear, dim3(4096), dim3(TB), 0, st, T, w.tab_total, nfront, S, front);
+      GINEX_LAUNCH_CHECK();
+      if (stage >= 0) {
+        hipLaunchKernelGGL(k_reinsert, grid_slots, dim3(TB), 0, st, T, nlist, S, tpb);
+        GINEX_LAUNCH_CHECK();
+      }
+      if (stage < 0) {
+        hipLaunchKernelGGL(k_seed_stage, grid_slots, dim3(TB), 0, st, T, seeds, w.seed_off, nfront, S,
+                           tpb);
+      } else if (g->nc_address_table) {
+        if (g->offsets_64)
+          launch_pick<int64_t, true>(T, p, g, nfront, k, stage, S, rng_seed, first_batch_index, st);
+        else
+          launch_pick<int32_t, true>(T, p, g, nfront, k, stage, S, rng_seed, first_batch_index, st);
+      } else if (g->offsets_64) {
+        launch_pick<int64_t, false>(T, p, g, nfront, k, stage, S, rng_seed, first_batch_index, st);
+      } else {
+        launch_pick<int32_t, false>(T, p, g, nfront, k, stage, S, rng_seed, first_batch_index, st);
+      }
+      GINEX_LAUNCH_CHECK();
+      hipLaunchKernelGGL(k_count, grid_slots, dim3(TB), 0, st, T, nfront, w.tile_sums, p.tiles, S,
+                         tpb);
       GINEX_LAUNCH_CHECK();
     }
-    if (stage < 0) {
-      hipLaunchKernelGGL(k_seed_stage, grid_slots, dim3(TB), 0, st, T, seeds, w.seed_off, nfront, S,
-                         tpb);
-    } else if (g->nc_address_table) {
-      if (g->offsets_64)
-        launch_pick<int64_t, true>(T, p, g, nfront, k, stage, S, rng_seed, first_batch_index, st);
-      else
-        launch_pick<int32_t, true>(T, p, g, nfront, k, stage, S, rng_seed, first_batch_index, st);
-    } else if (g->offsets_64) {
-      launch_pick<int64_t, false>(T, p, g, nfront, k, stage, S, rng_seed, first_batch_index, st);
-    } else {
-      launch_pick<int32_t, false>(T, p, g, nfront, k, stage, S, rng_seed, first_batch_index, st);
-    }
-    GINEX_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_count, grid_slots, dim3(TB), 0, st, T, nfront, w.tile_sums, p.tiles, S,
-                       tpb);
-    GINEX_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_scan_batch, dim3(S), dim3(TB), 0, st, w.tile_sums, p.tiles, nfront,
                        w.batch_total);
     GINEX_LAUNCH_CHECK();
@@ -1186,8 +1325,12 @@ extern "C" int32_t ginex_sample_superbatch(
                        adj ? adj_col : (int32_t*)nullptr, col_capacity, w.col_base, S, tpb);
     GINEX_LAUNCH_CHECK();
     if (adj) {
-      hipLaunchKernelGGL(k_col, grid_slots, dim3(TB), 0, st, T, nfront, k, adj_rowptr,
-                         rowptr_capacity, w.row_base, adj_col, col_capacity, w.col_base, S, tpb);
+      if (buckets)
+        hipLaunchKernelGGL(k_col<true>, grid_slots, dim3(TB), 0, st, T, nfront, k, adj_rowptr,
+                           rowptr_capacity, w.row_base, adj_col, col_capacity, w.col_base, S, tpb);
+      else
+        hipLaunchKernelGGL(k_col<false>, grid_slots, dim3(TB), 0, st, T, nfront, k, adj_rowptr,
+                           rowptr_capacity, w.row_base, adj_col, col_capacity, w.col_base, S, tpb);
       GINEX_LAUNCH_CHECK();
     }
     int32_t* t = nlist; nlist = nlist_next; nlist_next = t;
@@ -1195,8 +1338,10 @@ extern "C" int32_t ginex_sample_superbatch(
   hipLaunchKernelGGL(k_ids_offsets, dim3(1), dim3(TB), 0, st, M, S, nlist);
   GINEX_LAUNCH_CHECK();
   if (ids_capacity > 0) {
-    hipLaunchKernelGGL(k_copy_ids, dim3((unsigned)ceil_div(p.stride_ids, TB * 4), S), dim3(TB), 0,
-                       st, T, M, nlist, ids, ids_capacity);
+    // (a capped grid like the others: sized for the longest possible list it was 260 000 blocks for
+    // 200 batches, nearly all of them empty)
+    hipLaunchKernelGGL(k_copy_ids, dim3((unsigned)capped(ceil_div(p.stride_ids, TB * 4), COPY_TILES), S),
+                       dim3(TB), 0, st, T, M, nlist, ids, ids_capacity);
     GINEX_LAUNCH_CHECK();
   }
   // the small host outputs sit back to back in the workspace: one copy brings them all over

@@ -146,7 +146,7 @@ __device__ __forceinline__ int32_t stay_end(const Stays& q, uint32_t i, int32_t 
 // their stays would meet cut after cut (108 of 200 iterations for a cache that holds two fifths of the
 // rows).  never[0][t]: ids above it leave that bucket in iteration t (-1: all of them);
 // never[k][t]: the smallest of 2^k entries from t on, so that the first iteration that drops a row is
-// found in NEVER_LEVELS steps (15.0 -> {WALK} ms for k_stays_walk on 154 M accesses).
+// found in NEVER_LEVELS steps (15.0 -> 3.5 ms for k_stays_walk on 154 M accesses).
 constexpr int NEVER_LEVELS = 12;   // 2^12 > STATIC_S_MAX
 
 __global__ __launch_bounds__(BIG) void k_never_lift(const Cut* __restrict__ cuts, int32_t S,

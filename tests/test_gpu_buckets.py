@@ -1,0 +1,104 @@
+"""The sampler's later hops through hash buckets in LDS: sizes at the edges of its tiles and of the
+fanouts it keeps in registers, ids that all fall into one bucket, and a workspace without room for
+buckets.  Everything is compared with the oracle element by element (tolerance zero)."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+
+from test_gpu_parity import check_sample, dev, ginex, small_graph  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def both(ginex, off, ind, batches, fanout, **kw):
+    seeds = np.concatenate(batches).astype(np.int32)
+    so = np.cumsum([0] + [len(b) for b in batches])
+    ref = oracle.sample_superbatch(off, ind, seeds, so, fanout, rng_seed=5, first_batch_index=2)
+    res = ginex.sample_superbatch(dev(off), dev(ind), dev(seeds), so, fanout, rng_seed=5,
+                                  first_batch_index=2, **kw)
+    check_sample(res, ref, len(batches), len(fanout))
+
+
+# more than 1024 seeds: the first hop's frontier has exactly as many nodes as the batch has seeds
+@pytest.mark.parametrize("k", [1, 16, 17, 32, 33])
+@pytest.mark.parametrize("offsets_64", [False, True])
+def test_frontiers_around_the_tile_sizes(ginex, k, offsets_64):  # noqa: F811
+    off, ind = small_graph(n=6000, e=150_000, offsets_64=offsets_64)
+    rng = np.random.default_rng(k)
+    batches = [rng.choice(6000, size=n, replace=False) for n in (1025, 2047, 2048, 2049, 2303, 2304, 2305, 3)]
+    both(ginex, off.numpy(), ind.numpy(), batches, (k, 3))
+
+
+def fmix32(h):
+    h = h.astype(np.uint32)
+    h ^= h >> np.uint32(16)
+    h *= np.uint32(0x85EBCA6B)
+    h ^= h >> np.uint32(13)
+    h *= np.uint32(0xC2B2AE35)
+    return h ^ (h >> np.uint32(16))
+
+
+# 6 400 ids in the first of 512 buckets, whose table has 4 096 slots: done in slices
+@pytest.mark.parametrize("repeats", [False, True])
+def test_ids_that_fall_into_one_bucket(ginex, repeats):  # noqa: F811
+    N, seeds, mid, k = 4_000_000, 20, 10, 32
+    ids = np.arange(1000, N, dtype=np.uint32)
+    pool = ids[fmix32(ids) < np.uint32((1 << 32) // 512)][:seeds * mid * k].astype(np.int64)
+    assert len(pool) == seeds * mid * k
+    if repeats:                       # and many of them twice
+        pool = pool[np.random.default_rng(1).integers(0, len(pool), len(pool))]
+    deg = np.zeros(N, dtype=np.int64)
+    deg[:seeds] = mid
+    deg[100:100 + seeds * mid] = k
+    off = np.zeros(N + 1, dtype=np.int64)
+    np.cumsum(deg, out=off[1:])
+    ind = np.empty(off[-1], dtype=np.int32)
+    ind[:seeds * mid] = 100 + np.arange(seeds * mid)
+    ind[seeds * mid:] = pool
+    both(ginex, off, ind, [np.arange(seeds)], (mid, k))
+
+
+def test_workspace_without_room_for_buckets(ginex):  # noqa: F811
+    """On a small graph the buckets take more room than the tables: a workspace that only has room
+    for the tables is still accepted, and gives the same result."""
+    off, ind = small_graph()
+    off, ind = off.cuda(), ind.cuda()
+    seeds = dev(np.arange(200, dtype=np.int32))
+    so, fo = np.array([0, 90, 200]), np.array([9, 9, 9], dtype=np.int32)
+    full = ginex.sample_superbatch(off, ind, seeds, so, fo)
+    lib = ginex._lib.load()
+    n = off.numel() - 1
+    need = lib.ginex_sample_workspace_bytes(n, 2, 110, fo.ctypes.data, 3)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    ids = torch.empty_like(full.ids)
+    rowptr, col = torch.empty_like(full.adj_rowptr), torch.empty_like(full.adj_col)
+    so = so.astype(np.int64)
+    ids_off, hops = np.zeros(3, np.int64), np.zeros(8, np.int64)
+    rows, cols, totals = np.zeros(7, np.int64), np.zeros(7, np.int64), np.zeros(3, np.int64)
+    g = ginex._lib.CsrDesc(n, ind.numel(), off.data_ptr(), int(off.dtype == torch.int64),
+                           ind.data_ptr(), None, None)
+    p = lambda a: C.c_void_p(a.ctypes.data if isinstance(a, np.ndarray) else a.data_ptr())  # noqa: E731
+
+    def call(nbytes):
+        rc = lib.ginex_sample_superbatch(
+            C.byref(g), p(seeds), p(so), 2, p(fo), 3, 0, 0, p(ids), ids.numel(), p(ids_off), p(hops),
+            p(rowptr), rowptr.numel(), p(col), col.numel(), p(rows), p(cols), p(totals), p(ws), nbytes,
+            C.c_void_p(torch.cuda.current_stream().cuda_stream))
+        if rc == 0:
+            assert torch.equal(ids, full.ids) and torch.equal(rowptr, full.adj_rowptr)
+            assert torch.equal(col, full.adj_col) and np.array_equal(hops, full.hop_sizes.ravel())
+        return rc
+
+    assert call(need) == 0
+    lo, hi = 0, need                  # the smallest size that is accepted
+    while lo < hi:
+        mid = (lo + hi) // 2
+        if call(mid) == 0:
+            hi = mid
+        else:
+            lo = mid + 1
+    assert lo < need
