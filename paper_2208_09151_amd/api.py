@@ -171,10 +171,10 @@ def sample_superbatch(offsets, indices, seeds, seed_offsets, fanout, rng_seed=0,
     if need == 0:
         raise GinexError(-1, lib.ginex_last_error().decode())
     ws = workspace if workspace is not None and workspace.numel() >= need else _workspace(need, dev)
-    cap_ids, cap_rows, cap_cols = sample_capacity(n, so, fo)
     if out is not None:
         ids, rowptr, col = out
     else:
+        cap_ids, cap_rows, cap_cols = sample_capacity(n, so, fo)
         ids = torch.empty(max(cap_ids, 1), dtype=torch.int32, device=dev)
         rowptr = torch.empty(max(cap_rows, 1), dtype=torch.int64, device=dev) if with_adj else None
         col = torch.empty(max(cap_cols, 1), dtype=torch.int32, device=dev) if with_adj else None
