@@ -781,35 +781,51 @@ __global__ __launch_bounds__(NT) void k_static_roll(State st, const uint32_t* __
 
 constexpr int EVICT_TILE = WAVE * WAVE;   // cache lines per tile: 64 flag words of 64 lines
 
-// The members of a class are distinct ids and the bitmap is all zero before the marking, so
-// every call sets a new bit: neither atomic needs its result.
-__device__ __forceinline__ void select_bit_set(const State& st, uint32_t v) {
-  atomicOr(&st.bitmap[v >> 5], 1u << (v & 31));
-  atomicAdd(&st.sel_part[v >> PART_SHIFT], 1u);
-}
-__device__ __forceinline__ void select_bit_set_in(const State& st, uint32_t v) {
-  atomicOr(&st.bitmap_in[v >> 5], 1u << (v & 31));
-  atomicAdd(&st.sel_part_in[v >> PART_SHIFT], 1u);
-}
+// Set the bit of every member of the selected class in bucket j* (distinct ids in an all-zero bitmap, so
+// no atomic needs its result) and count it in its part.  A graph of up to MARK_PARTS parts has only a
+// few cache lines of part counts, on which an atomic per member queues up (1 M nodes, 80 k members: 152 us):
+// there a block counts in LDS first (8 us).
+constexpr int MARK_PARTS = 256;
 
-// Set the bit of every member of the selected class in bucket j*.
-__device__ void p_mark_residents(const State& st, const Ctrl& c, int64_t vb) {
-  const int64_t base = vb * (TB * MARK_ITEMS);
-#pragma unroll
-  for (int t = 0; t < MARK_ITEMS; ++t) {
-    const int64_t s = base + t * TB + threadIdx.x;
-    if (s < st.cap && st.res_next[s] == c.jstar) select_bit_set(st, (uint32_t)st.res_id[s]);
+struct Marker {
+  uint32_t *bits, *part, *lds;
+  __device__ __forceinline__ void operator()(uint32_t v) const {
+    atomicOr(&bits[v >> 5], 1u << (v & 31));
+    atomicAdd(lds ? &lds[v >> PART_SHIFT] : &part[v >> PART_SHIFT], 1u);
   }
-}
+};
 
-__device__ void p_mark_incoming(const State& st, const Ctrl& c, const Iter& it, int64_t vb) {
-  const int64_t base = vb * (TB * MARK_ITEMS);
+// blocks [0, res_blocks): residents, the next in_blocks blocks: incoming rows; only one
+// class is selected, and none when the select runs on the dead rows.
+__global__ __launch_bounds__(TB) void k_mark(State st, Iter it, int64_t res_blocks) {
+  __shared__ uint32_t s_part[MARK_PARTS];
+  const Ctrl c = *st.ctrl;
+  const bool residents = (int64_t)blockIdx.x < res_blocks;
+  if (c.use_dead || (residents ? c.mode_res : c.mode_in) != MODE_SELECT) return;   // uniform
+  const bool in_lds = st.parts <= MARK_PARTS;
+  const Marker mark{residents ? st.bitmap : st.bitmap_in, residents ? st.sel_part : st.sel_part_in,
+                    in_lds ? s_part : nullptr};
+  for (int x = threadIdx.x; x < MARK_PARTS; x += TB) s_part[x] = 0;
+  __syncthreads();
+  if (residents) {
+    const int64_t base = (int64_t)blockIdx.x * (TB * MARK_ITEMS);
 #pragma unroll
-  for (int t = 0; t < MARK_ITEMS; ++t) {
-    const int64_t p = base + t * TB + threadIdx.x;
-    if (p < it.n && st.acc_line[p] < 0 && key_of(it, p) == c.jstar)
-      select_bit_set_in(st, (uint32_t)it.ids[p]);
+    for (int t = 0; t < MARK_ITEMS; ++t) {
+      const int64_t s = base + t * TB + threadIdx.x;
+      if (s < st.cap && st.res_next[s] == c.jstar) mark((uint32_t)st.res_id[s]);
+    }
+  } else {
+    const int64_t base = ((int64_t)blockIdx.x - res_blocks) * (TB * MARK_ITEMS);
+#pragma unroll
+    for (int t = 0; t < MARK_ITEMS; ++t) {
+      const int64_t p = base + t * TB + threadIdx.x;
+      if (p < it.n && st.acc_line[p] < 0 && key_of(it, p) == c.jstar) mark((uint32_t)it.ids[p]);
+    }
   }
+  __syncthreads();
+  if (in_lds)
+    for (int x = threadIdx.x; x < st.parts; x += TB)
+      if (s_part[x]) atomicAdd(&mark.part[x], s_part[x]);
 }
 
 // Large caches, evictions among the dead residents only (the usual case once a cache is
@@ -836,18 +852,6 @@ __device__ void p_dead_scatter(const State& st, const Ctrl& c, int64_t vb, int64
         atomicAdd(&st.evict_tiles[line / EVICT_TILE], 1u);
       }
     }
-  }
-}
-
-// blocks [0, res_blocks): residents, the next in_blocks blocks: incoming rows; only one
-// class is selected, and none when the select runs on the dead rows.
-__global__ __launch_bounds__(TB) void k_mark(State st, Iter it, int64_t res_blocks) {
-  const Ctrl c = *st.ctrl;
-  if (c.use_dead) return;
-  if ((int64_t)blockIdx.x < res_blocks) {
-    if (c.mode_res == MODE_SELECT) p_mark_residents(st, c, blockIdx.x);
-  } else if (c.mode_in == MODE_SELECT) {
-    p_mark_incoming(st, c, it, blockIdx.x - res_blocks);
   }
 }
 
@@ -972,19 +976,23 @@ __device__ __forceinline__ void finish_line(const State& st, int32_t line, int32
 // are dealt to the lanes round-robin by rank (lane l takes the l-th, (l+64)-th ... set bit,
 // located through the wave's running popcounts), so that the chain of dependent memory
 // operations behind every eviction is as long for a clustered tile as for an even one.
+// A small cache has few tiles, and under LRU an iteration may evict most of their lines: `split` waves
+// (a multiple of a block's) share a tile there, so that a wave has a few rounds to go instead of up to 64
+// (k_emit_pair on 104 857 lines, 28 k changes an iteration: 53 us with one wave per tile, 10 us with 16).
 __device__ void p_evict_emit(const State& st, const Ctrl& c, const Iter& it, const Outputs& o,
-                             int64_t vb, int64_t tiles) {
+                             int64_t vb, int64_t tiles, int32_t split) {
   __shared__ uint32_t red[TB / WAVE];
-  constexpr int TPB = TB / WAVE;                 // tiles per block
-  const int64_t first_tile = vb * TPB;
-  const int w = threadIdx.x / WAVE;
+  constexpr int TPB = TB / WAVE;                 // tiles per block, or waves of one tile
+  const int64_t first_tile = vb * TPB / split;
+  const int w = split == 1 ? threadIdx.x / WAVE : 0;
+  const uint32_t share = split == 1 ? 0u : (uint32_t)((vb * TPB + threadIdx.x / WAVE) % split);
   const int64_t tile = first_tile + w;
   // the block's own tiles first: most blocks of a large cache have nothing to emit
   uint32_t own[TPB];
   uint32_t any = 0;
 #pragma unroll
   for (int k = 0; k < TPB; ++k) {
-    own[k] = first_tile + k < tiles ? st.evict_tiles[first_tile + k] : 0;
+    own[k] = first_tile + k < tiles && (split == 1 || k == 0) ? st.evict_tiles[first_tile + k] : 0;
     any |= own[k];
   }
   if (!any) return;                              // uniform over the block
@@ -1002,7 +1010,7 @@ __device__ void p_evict_emit(const State& st, const Ctrl& c, const Iter& it, con
   const uint32_t total = __shfl(incl, WAVE - 1, WAVE);
   const int64_t dst = o.cs_offsets[it.i];
   const uint64_t tag = pair_tag(it.i);
-  for (uint32_t k0 = 0; k0 < total; k0 += WAVE) {        // uniform trip count: shuffles inside
+  for (uint32_t k0 = share * WAVE; k0 < total; k0 += split * WAVE) {   // uniform trip count: shuffles inside
     const uint32_t k = k0 + lane_id();
     int lo = 0, hi = WAVE - 1;                   // the first word whose running count exceeds k
 #pragma unroll
@@ -1092,11 +1100,11 @@ __device__ void p_in_emit(const State& st, const Ctrl& c, const Iter& it, const 
   }
 }
 
-__global__ __launch_bounds__(TB) void k_emit_pair(State st, Iter it, Outputs o, int64_t evict_tiles) {
+__global__ __launch_bounds__(TB) void k_emit_pair(State st, Iter it, Outputs o, int64_t evict_tiles,
+                                                  int64_t evict_blocks, int32_t split) {
   const Ctrl c = *st.ctrl;
   if (c.n_change <= 0) return;
-  const int64_t evict_blocks = (evict_tiles + TB / WAVE - 1) / (TB / WAVE);
-  if ((int64_t)blockIdx.x < evict_blocks) p_evict_emit(st, c, it, o, blockIdx.x, evict_tiles);
+  if ((int64_t)blockIdx.x < evict_blocks) p_evict_emit(st, c, it, o, blockIdx.x, evict_tiles, split);
   else p_in_emit(st, c, it, o, blockIdx.x - evict_blocks);
 }
 
@@ -2658,7 +2666,9 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
   Outputs outs{in_ids, out_ids, in_positions, cs_capacity, cs_offsets, miss_count};
   {
     const int64_t res_blocks = ceil_div(cap, TB * MARK_ITEMS);
-    const int64_t evict_blocks = ceil_div(w.evict_tiles, TB / WAVE);
+    // waves per tile of lines in k_emit_pair (one where a wave takes the flags of its tile back)
+    const int32_t split = state.dead_scatter || w.evict_tiles > 256 ? 1 : 16;
+    const int64_t evict_blocks = ceil_div(w.evict_tiles * split, TB / WAVE);
     for (int32_t i = 0; i < S; ++i) {
       Iter it;
       const int64_t lo = ids_offsets[i];
@@ -2688,7 +2698,7 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
       hipLaunchKernelGGL(k_flags, dim3((unsigned)(w.evict_tiles + in_tiles + 1)), dim3(TB), 0,
                          st, state, it, w.evict_tiles, in_tiles);
       hipLaunchKernelGGL(k_emit_pair, dim3((unsigned)(evict_blocks + in_tiles)), dim3(TB), 0, st,
-                         state, it, outs, w.evict_tiles);
+                         state, it, outs, w.evict_tiles, evict_blocks, split);
       GINEX_LAUNCH_CHECK();
     }
   }
