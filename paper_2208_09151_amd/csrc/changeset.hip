@@ -100,6 +100,16 @@ __device__ __forceinline__ void load_offsets(int32_t* lds_off, const int64_t* __
   __syncthreads();
 }
 
+__device__ __forceinline__ uint32_t block_sum_u32(uint32_t v, uint32_t* red) {
+  v = wave_reduce_sum(v);
+  __syncthreads();  // red may still be read from an earlier call
+  if (lane_id() == 0) red[threadIdx.x / WAVE] = v;
+  __syncthreads();
+  uint32_t s = 0;
+  for (int w = 0; w < (int)blockDim.x / WAVE; ++w) s += red[w];
+  return s;
+}
+
 // ---- part 1 -----------------------------------------------------------------------
 
 constexpr int LOOK_ITEMS = 8;
@@ -270,6 +280,129 @@ __global__ __launch_bounds__(TB) void k_init_state_resume(const int32_t* __restr
     if (lds_hist[j]) atomicAdd(&st.rhist[j], lds_hist[j]);
 }
 
+// The same without keys, for the ways that do not loop over the state.  What they need of a carried state:
+// which rows it holds, the lines of those the superbatch accesses, and its dead rows.  The rows
+// come in no order, so every access below is to a random place; the kernel above makes three of
+// them per line, two of them atomics on the memory side (2.05 ms for 27.75 M lines of 111 M nodes),
+// these one read of a 14 MB bitmap, one byte stored, and a table entry stored for the rows that are
+// accessed (k_hold 0.99 ms, the passes around it 0.15).  Whether all rows are distinct and in range shows in the number of bytes set.
+
+// bit v of `bits` for every head (heads in id order, so a word's bits are neighbours: a wave
+// gathers them and stores words that are its own)
+__global__ __launch_bounds__(TB) void k_accessed_bits(const uint64_t* __restrict__ heads, int64_t count,
+                                                      uint32_t* __restrict__ bits) {
+  const int64_t r = (int64_t)blockIdx.x * TB + threadIdx.x;
+  const uint32_t v = r < count ? (uint32_t)heads[r] : 0xFFFFFFFFu;
+  const uint32_t w = v >> 5;
+  uint32_t word = r < count ? 1u << (v & 31) : 0u;
+  const int lane = lane_id();
+#pragma unroll
+  for (int d = 1; d < WAVE; d <<= 1) {
+    const uint32_t other = __shfl_down(word, d, WAVE), ow = __shfl_down(w, d, WAVE);
+    if (lane + d < WAVE && ow == w) word |= other;
+  }
+  const uint32_t left = __shfl_up(w, 1, WAVE);   // (every lane takes part)
+  const bool leads = lane == 0 || left != w;
+  const uint32_t last = __shfl(w, WAVE - 1, WAVE);
+  if (r >= count || !leads) return;
+  if (lane == 0 || w == last) atomicOr(&bits[w], word);   // the word may have bits in the next wave, too
+  else bits[w] = word;
+}
+
+// held[v] = 1 and, for the rows that are accessed, addr[v] = line
+__global__ __launch_bounds__(TB) void k_hold(const int32_t* __restrict__ start_ids, int64_t cap,
+                                             int64_t num_nodes, const uint32_t* __restrict__ accessed,
+                                             uint8_t* __restrict__ held, int32_t* __restrict__ res_id,
+                                             int32_t* __restrict__ addr) {
+  constexpr int ITEMS = 8;
+  const int64_t base = (int64_t)blockIdx.x * (TB * ITEMS) + threadIdx.x;
+  int32_t v[ITEMS];
+  uint32_t word[ITEMS];
+#pragma unroll
+  for (int t = 0; t < ITEMS; ++t) {
+    const int64_t s = base + t * TB;
+    v[t] = s < cap ? start_ids[s] : -1;
+  }
+#pragma unroll
+  for (int t = 0; t < ITEMS; ++t) {
+    if (v[t] >= num_nodes) v[t] = -1;    // shows in the number of rows held
+    word[t] = v[t] >= 0 ? accessed[(uint32_t)v[t] >> 5] : 0u;
+  }
+#pragma unroll
+  for (int t = 0; t < ITEMS; ++t) {
+    if (v[t] < 0) continue;
+    held[v[t]] = 1;
+    res_id[base + t * TB] = v[t];
+    if (word[t] >> (v[t] & 31) & 1u) addr[v[t]] = (int32_t)(base + t * TB);
+  }
+}
+
+// The bytes as bits; the dead rows (held, not accessed) and their part counts; the number of rows held.
+// A block per part.
+__global__ __launch_bounds__(TB) void k_held_words(const uint8_t* __restrict__ held, State st,
+                                                   const uint32_t* __restrict__ accessed,
+                                                   uint32_t* __restrict__ held_bits,
+                                                   unsigned long long* __restrict__ rows) {
+  __shared__ uint32_t red[TB / WAVE];
+  uint32_t all = 0, dead = 0;
+  for (int t = threadIdx.x; t < PART_WORDS; t += TB) {
+    const int64_t w = (int64_t)blockIdx.x * PART_WORDS + t;
+    if (w >= st.words) break;
+    uint32_t word = 0;
+    const uint32_t* bytes = reinterpret_cast<const uint32_t*>(held) + w * 8;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const uint32_t x = bytes[q];       // four bytes of 0 or 1
+      word |= ((x | x >> 7 | x >> 14 | x >> 21) & 15u) << (4 * q);
+    }
+    const uint32_t gone = word & ~accessed[w];
+    held_bits[w] = word;
+    st.dead_bits[w] = gone;
+    all += __popc(word);
+    dead += __popc(gone);
+  }
+  const uint32_t n_dead = block_sum_u32(dead, red), n_all = block_sum_u32(all, red);
+  if (threadIdx.x == 0) {
+    st.dead_part[blockIdx.x] = n_dead;
+    if (n_all) atomicAdd(rows, (unsigned long long)n_all);
+  }
+}
+
+// rhist of a carried state: the rows held by their first access; bin S, the rows never accessed, gets
+// what is left (counted down from cap by every block)
+__global__ __launch_bounds__(TB) void k_held_hist(const uint64_t* __restrict__ heads, int64_t count,
+                                                  const uint32_t* __restrict__ held_bits, State st) {
+  extern __shared__ uint32_t lds_hist[];  // S bins
+  for (int j = threadIdx.x; j < st.S; j += TB) lds_hist[j] = 0;
+  __syncthreads();
+  const int64_t span = (int64_t)gridDim.x * TB;
+  for (int64_t r = (int64_t)blockIdx.x * TB + threadIdx.x; r < count; r += span) {
+    const uint64_t h = heads[r];
+    const uint32_t v = (uint32_t)h;
+    if (held_bits[v >> 5] >> (v & 31) & 1u) atomicAdd(&lds_hist[h >> 32], 1u);
+  }
+  __syncthreads();
+  uint32_t mine = 0;
+  for (int j = threadIdx.x; j < st.S; j += TB)
+    if (lds_hist[j]) {
+      atomicAdd(&st.rhist[j], lds_hist[j]);
+      mine += lds_hist[j];
+    }
+  mine = wave_reduce_sum(mine);
+  if (lane_id() == 0 && mine) atomicSub(&st.rhist[st.S], mine);
+  if (blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(&st.rhist[st.S], (uint32_t)st.cap);
+}
+
+// addr of the dead rows from lo_id up: the only ones of them that can be evicted
+__global__ __launch_bounds__(TB) void k_dead_lines(State st, const uint32_t* __restrict__ accessed,
+                                                   int64_t lo_id) {
+  const int64_t span = (int64_t)gridDim.x * TB;
+  for (int64_t s = (int64_t)blockIdx.x * TB + threadIdx.x; s < st.cap; s += span) {
+    const int32_t v = st.res_id[s];
+    if (v >= lo_id && !(accessed[(uint32_t)v >> 5] >> (v & 31) & 1u)) st.addr[v] = (int32_t)s;
+  }
+}
+
 // addr[node of rank r] = r for the first `count` heads (C_0 when everything fits)
 __global__ __launch_bounds__(TB) void k_scatter_rank(const uint64_t* __restrict__ heads,
                                                      int64_t count, int32_t* __restrict__ addr) {
@@ -379,16 +512,6 @@ struct Outputs {
   int64_t* cs_offsets;
   int64_t* miss_count;
 };
-
-__device__ __forceinline__ uint32_t block_sum_u32(uint32_t v, uint32_t* red) {
-  v = wave_reduce_sum(v);
-  __syncthreads();  // red may still be read from an earlier call
-  if (lane_id() == 0) red[threadIdx.x / WAVE] = v;
-  __syncthreads();
-  uint32_t s = 0;
-  for (int w = 0; w < (int)blockDim.x / WAVE; ++w) s += red[w];
-  return s;
-}
 
 // Sum of counts[0 .. n) by the whole block.
 __device__ __forceinline__ uint32_t block_prefix_of(const uint32_t* __restrict__ counts, int64_t n,
@@ -1180,7 +1303,8 @@ struct Plan {
 // cs_offsets[i + 1] (scanned afterwards) and to the bitmap over positions.
 __global__ __launch_bounds__(TB) void k_plan_heads(const uint64_t* __restrict__ sorted, int64_t n,
                                                    const int64_t* __restrict__ off, int32_t S,
-                                                   const int32_t* __restrict__ addr,
+                                                   const uint32_t* __restrict__ held,
+                                                   int32_t* __restrict__ addr,
                                                    uint32_t* __restrict__ ins_bits,
                                                    unsigned long long* __restrict__ miss_count,
                                                    unsigned long long* __restrict__ cs_offsets) {
@@ -1193,17 +1317,27 @@ __global__ __launch_bounds__(TB) void k_plan_heads(const uint64_t* __restrict__ 
   const int64_t tiles = (n + LOOK_TILE - 1) / LOOK_TILE;
   for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
     const int64_t base = tile * LOOK_TILE;
+    // pair, left neighbour and right neighbour of all items first, so that the reads are in flight together
+    uint64_t here[LOOK_ITEMS], left[LOOK_ITEMS], right[LOOK_ITEMS];
 #pragma unroll
     for (int i = 0; i < LOOK_ITEMS; ++i) {
       const int64_t j = base + i * TB + threadIdx.x;
-      if (j >= n || !run_head(sorted, j)) continue;
-      const uint64_t cur = sorted[j];
+      here[i] = j < n ? sorted[j] : ~0ull;
+      left[i] = j > 0 && j < n ? sorted[j - 1] : ~0ull;
+      right[i] = j + 1 < n ? sorted[j + 1] : ~0ull;
+    }
+#pragma unroll
+    for (int i = 0; i < LOOK_ITEMS; ++i) {
+      const int64_t j = base + i * TB + threadIdx.x;
+      const uint64_t cur = here[i];
       const uint32_t v = (uint32_t)(cur >> 32);
-      if (addr[v] >= 0) continue;
+      if (j >= n || (uint32_t)(left[i] >> 32) == v) continue;   // not the head of a run
+      if (held[v >> 5] >> (v & 31) & 1u) continue;
+      addr[v] = -1;                       // (until it is inserted, if it is)
       const int32_t p = (int32_t)(cur & 0xFFFFFFFFu);
       const int32_t it = iter_of(lds_off, S, p);
       atomicAdd(&h_miss[it], 1u);
-      if (j + 1 < n && (uint32_t)(sorted[j + 1] >> 32) == v) {
+      if ((uint32_t)(right[i] >> 32) == v) {
         atomicAdd(&h_ins[it], 1u);
         atomicOr(&ins_bits[p >> 5], 1u << (p & 31));
       }
@@ -1349,14 +1483,14 @@ __global__ __launch_bounds__(TB) void k_cand_start(const uint32_t* __restrict__ 
 // Is sorted[j] the last access of a row that is resident when it dies?  (A row the start state
 // does not hold is resident only if it was inserted, that is, if it has an earlier access.)
 __device__ __forceinline__ bool plan_arrival(const uint64_t* __restrict__ sorted, int64_t n,
-                                             int64_t j, const int32_t* __restrict__ addr,
+                                             int64_t j, const uint32_t* __restrict__ held,
                                              const int32_t* off, int32_t S,
                                              int32_t& v, int32_t& d, bool& inserted) {
   const uint64_t cur = sorted[j];
   v = (int32_t)(cur >> 32);
   if (j + 1 < n && (int32_t)(sorted[j + 1] >> 32) == v) return false;
   const bool earlier = j > 0 && (int32_t)(sorted[j - 1] >> 32) == v;
-  inserted = addr[v] < 0;
+  inserted = !(held[(uint32_t)v >> 5] >> (v & 31) & 1u);
   if (!earlier && inserted) return false;
   d = iter_of(off, S, (int32_t)(cur & 0xFFFFFFFFu));
   return true;
@@ -1373,7 +1507,7 @@ __device__ __forceinline__ bool plan_arrival(const uint64_t* __restrict__ sorted
 template <bool PLACE>
 __global__ __launch_bounds__(TB) void k_plan_arrivals(const uint64_t* __restrict__ sorted, int64_t n,
                                                       const int64_t* __restrict__ scalars,
-                                                      const int32_t* __restrict__ addr,
+                                                      const uint32_t* __restrict__ held,
                                                       const int64_t* __restrict__ off, int32_t S,
                                                       uint32_t* __restrict__ cand_bits,
                                                       const uint32_t* __restrict__ cand_base,
@@ -1393,7 +1527,7 @@ __global__ __launch_bounds__(TB) void k_plan_arrivals(const uint64_t* __restrict
   for (int64_t j = first + threadIdx.x; j < last; j += TB) {
     int32_t v, d;
     bool inserted;
-    if (!plan_arrival(sorted, n, j, addr, lds_off, S, v, d, inserted)) continue;
+    if (!plan_arrival(sorted, n, j, held, lds_off, S, v, d, inserted)) continue;
     if (!PLACE) atomicOr(&cand_bits[(uint32_t)v >> 5], 1u << (v & 31));
     atomicAdd(&s_cnt[d], 1u);
   }
@@ -1411,7 +1545,7 @@ __global__ __launch_bounds__(TB) void k_plan_arrivals(const uint64_t* __restrict
   for (int64_t j = first + threadIdx.x; j < last; j += TB) {
     int32_t v, d;
     bool inserted;
-    if (!plan_arrival(sorted, n, j, addr, lds_off, S, v, d, inserted)) continue;
+    if (!plan_arrival(sorted, n, j, held, lds_off, S, v, d, inserted)) continue;
     if (arr_ids) {                                   // the stepped path wants the rows themselves
       arr_ids[atomicAdd(&s_cnt[d], 1u)] = v;
       continue;
@@ -2052,12 +2186,13 @@ extern "C" size_t ginex_changeset_workspace_bytes(int64_t num_nodes, int64_t tot
 namespace ginex {
 namespace {
 
-// The changesets of a full cache whose state (res_id, addr, rhist and, for a carried cache,
-// res_next, dead_bits, dead_part) is set up, from the node-sorted accesses (see stays.hpp).
+// The changesets of a full cache whose state (res_id, addr of the accessed rows, rhist and, for a
+// carried cache, dead_bits) is set up, from the node-sorted accesses (see stays.hpp).
 // `ends`: the other buffer of the sort, `rows`: a word per distinct row.  last_head: the last row of
-// C_0, null for a carried cache.
+// C_0, null for a carried cache, whose rows are in held_bits; accessed: the superbatch's.
 int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, uint64_t* ends,
-                  uint64_t* rows, int64_t distinct, const uint64_t* last_head, const int32_t* ids,
+                  uint64_t* rows, int64_t distinct, const uint64_t* last_head,
+                  const uint32_t* held_bits, const uint32_t* accessed, const int32_t* ids,
                   const int64_t* ids_offsets, int64_t total, int32_t S, int32_t* in_ids, int32_t* out_ids, int32_t* in_positions,
                   int64_t cs_capacity, int64_t* cs_offsets, int64_t* miss_count, int32_t* src_line,
                   int64_t* total_changes, bool carried, int32_t* final_ids, hipStream_t st) {
@@ -2071,7 +2206,7 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
 
   // both ends of every stay, the thresholds, the table
   hipLaunchKernelGGL(k_stay_ends, dim3((unsigned)w.look_tiles), dim3(TB), off_lds, st, sorted, total,
-                     w.d_offsets, S, last_head, state.addr, ends);
+                     w.d_offsets, S, last_head, held_bits, ends);
   GINEX_HIP(fill_async<uint32_t>(w.key_hists, (int64_t)S * (S + 1), 0u, st));
   hipLaunchKernelGGL(k_key_hists, dim3((unsigned)ceil_div(longest, TB * TOUCH_ITEMS), (unsigned)S),
                      dim3(TB), sizeof(uint32_t) * (S + 1), st, ends, w.d_offsets, S, w.key_hists);
@@ -2133,7 +2268,7 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
   Never nv{};
   nv.rows = rows;
   hipLaunchKernelGGL(k_stays_links, dim3((unsigned)w.look_tiles), dim3(TB), off_lds, st, q, sorted, total,
-                     w.head_tiles, last_head, state.addr, nv, hit_words, ins_words, leave_start);
+                     w.head_tiles, last_head, held_bits, state.addr, nv, hit_words, ins_words, leave_start);
   // bucket "never"
   if (never) {
     static_assert(NEVER_COUNTS <= PLAN_CAND_MAX && NEVER_LEVELS * (STATIC_S_MAX + 1) + NEVER_PARTS <= PLAN_CAND_MAX,
@@ -2191,7 +2326,7 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
                        pl.ins_base, (int32_t*)nullptr);
     if (carried)
       hipLaunchKernelGGL(k_stays_idle, dim3((unsigned)ceil_div(state.cap, TB)), dim3(TB), 0, st, q,
-                         state.res_id, state.res_next, state.cap, leave_start);
+                         state.res_id, accessed, state.cap, leave_start);
     int levels = 1;
     while ((1 << levels) <= S) ++levels;
     const dim3 walk_grid((unsigned)ceil_div(total, WALK_TILE));
@@ -2451,27 +2586,44 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
     GINEX_HIP(fill_async<uint32_t>(state.sel_part_in, state.parts, 0u, st));
     GINEX_HIP(fill_async<uint64_t>(state.pair, w.max_change, 0ull, st));
   }
-  // the loop looks every access up in the address table, and a carried state finds repeated rows
-  // there; the stays of a fresh superbatch only read entries that were written
-  if (loop || start_ids) GINEX_HIP(fill_async<int32_t>(state.addr, num_nodes, -1, st));
+  // the loop looks every access up in the address table, and finds repeated rows of a carried state
+  // there; the other ways only read entries that were written
+  const bool for_loop = loop && !planned;   // (where the planned path gives up, the loop starts afresh)
+  if (for_loop) GINEX_HIP(fill_async<int32_t>(state.addr, num_nodes, -1, st));
+  // a carried state without the loop: bytes per row held in the array of first accesses, behind them
+  // the same as bits; the bitmap of accessed rows in the loop's scratch
+  uint8_t* const held = reinterpret_cast<uint8_t*>(w.first_of);
+  uint32_t* const held_bits = reinterpret_cast<uint32_t*>(held) + state.words * 8;
+  uint32_t* const accessed = state.bitmap_in;
   {
     int64_t blocks = ceil_div(cap, TB * 8);
     if (blocks > 4096) blocks = 4096;
     if (start_ids) {
       unsigned long long bad = 0;
-      GINEX_HIP(fill_async<int32_t>(w.first_of, num_nodes, S, st));
       GINEX_HIP(fill_async<unsigned long long>(w.d_counts, 1, 0ull, st));
-      hipLaunchKernelGGL(k_scatter_first, dim3((unsigned)ceil_div(distinct, TB)), dim3(TB), 0, st,
-                         heads, distinct, w.first_of);
-      hipLaunchKernelGGL(k_init_state_resume, dim3((unsigned)blocks), dim3(TB),
-                         sizeof(uint32_t) * (S + 1), st, start_ids, w.first_of, state, w.d_counts);
-      GINEX_LAUNCH_CHECK();
-      // the part counts of the dead rows the start state brought along
-      hipLaunchKernelGGL(k_part_count, dim3((unsigned)state.parts), dim3(TB), 0, st,
-                         state.dead_bits, state.words, state.dead_part);
+      if (for_loop) {
+        GINEX_HIP(fill_async<int32_t>(w.first_of, num_nodes, S, st));
+        hipLaunchKernelGGL(k_scatter_first, dim3((unsigned)ceil_div(distinct, TB)), dim3(TB), 0, st,
+                           heads, distinct, w.first_of);
+        hipLaunchKernelGGL(k_init_state_resume, dim3((unsigned)blocks), dim3(TB),
+                           sizeof(uint32_t) * (S + 1), st, start_ids, w.first_of, state, w.d_counts);
+        // the part counts of the dead rows the start state brought along
+        hipLaunchKernelGGL(k_part_count, dim3((unsigned)state.parts), dim3(TB), 0, st,
+                           state.dead_bits, state.words, state.dead_part);
+      } else {
+        GINEX_HIP(fill_async<uint32_t>(accessed, state.words, 0u, st));
+        GINEX_HIP(fill_async<uint64_t>(reinterpret_cast<uint64_t*>(held), state.words * 4, 0ull, st));
+        hipLaunchKernelGGL(k_accessed_bits, dim3((unsigned)ceil_div(distinct, TB)), dim3(TB), 0, st, heads,
+                           distinct, accessed);
+        hipLaunchKernelGGL(k_hold, dim3((unsigned)ceil_div(cap, TB * 8)), dim3(TB), 0, st, start_ids, cap,
+                           num_nodes, accessed, held, state.res_id, state.addr);
+        hipLaunchKernelGGL(k_held_words, dim3((unsigned)state.parts), dim3(TB), 0, st, held, state,
+                           accessed, held_bits, w.d_counts);
+      }
       GINEX_LAUNCH_CHECK();
       GINEX_HIP(hipMemcpyAsync(&bad, w.d_counts, sizeof(bad), hipMemcpyDeviceToHost, st));
       GINEX_HIP(hipStreamSynchronize(st));
+      if (!for_loop) bad = (unsigned long long)cap - bad;   // (rows held, so far)
       if (bad)
         return fail(GINEX_ERR_INPUT, "%s: %llu entries of start_ids are out of range or repeated",
                     who, bad);
@@ -2488,10 +2640,10 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
     GINEX_HIP(fill_async<uint32_t>(pl.arr_off, S + 2, 0u, st));
     GINEX_HIP(fill_async<uint32_t>(pl.cand_dead, PLAN_CAND_WORDS, 0u, st));
     {
-      int64_t blocks = w.look_tiles < 512 ? w.look_tiles : 512;
+      int64_t blocks = w.look_tiles < 1024 ? w.look_tiles : 1024;
       hipLaunchKernelGGL(k_plan_heads, dim3((unsigned)blocks), dim3(TB),
                          sizeof(int32_t) * (3 * (size_t)S + 1), st, sorted, total, w.d_offsets, S,
-                         state.addr, pl.ins_bits, (unsigned long long*)miss_count,
+                         held_bits, state.addr, pl.ins_bits, (unsigned long long*)miss_count,
                          (unsigned long long*)cs_offsets);
       hipLaunchKernelGGL(k_plan_scan, dim3(1), dim3(BIG), 0, st, state, sorted, total, cs_offsets,
                          pl.scalars);
@@ -2502,7 +2654,7 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
       hipLaunchKernelGGL(k_cand_start, dim3((unsigned)tail_blocks), dim3(TB), 0, st,
                          state.dead_bits, state.words, num_nodes, pl.scalars, state.bitmap);
       hipLaunchKernelGGL(k_plan_arrivals<false>, dim3((unsigned)tail_blocks), dim3(TB), 2 * off_lds, st,
-                         sorted, total, pl.scalars, state.addr, w.d_offsets, S, state.bitmap,
+                         sorted, total, pl.scalars, held_bits, w.d_offsets, S, state.bitmap,
                          pl.cand_base, num_nodes, pl, (int32_t*)nullptr);
       hipLaunchKernelGGL(k_plan_arrival_offsets, dim3(1), dim3(BIG), 0, st, pl.arr_off,
                          pl.arr_cur, S, pl.scalars);
@@ -2544,6 +2696,8 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
                            pl.ins_bits, pl.ins_words, pl.ins_tiles, ids, w.d_offsets, S, in_ids,
                            in_positions, pl.ins_base, pl.ins_cand);
         GINEX_LAUNCH_CHECK();
+        hipLaunchKernelGGL(k_dead_lines, dim3((unsigned)(ceil_div(cap, TB * 8) > 4096 ? 4096 : ceil_div(cap, TB * 8))),
+                           dim3(TB), 0, st, state, accessed, lo_id);
         int64_t tail_blocks = ceil_div(total - sc[PLAN_TAIL], TB);
         tail_blocks = tail_blocks < 1 ? 1 : (tail_blocks > 1024 ? 1024 : tail_blocks);
         if (stepped) {
@@ -2551,7 +2705,7 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
           // candidate numbers of the insertions for the replay, which does not run)
           int32_t* const arr_ids = pl.ins_cand;
           hipLaunchKernelGGL(k_plan_arrivals<true>, dim3((unsigned)tail_blocks), dim3(TB),
-                             2 * off_lds, st, sorted, total, pl.scalars, state.addr, w.d_offsets, S,
+                             2 * off_lds, st, sorted, total, pl.scalars, held_bits, w.d_offsets, S,
                              state.bitmap, pl.cand_base, num_nodes, pl, arr_ids);
           GINEX_LAUNCH_CHECK();
           std::vector<int64_t> cs(S + 1);
@@ -2609,7 +2763,7 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
         hipLaunchKernelGGL(k_cand_emit, dim3((unsigned)ctiles), dim3(TB), 0, st, state.bitmap,
                            state.dead_bits, lo_word, nwords, pl.cand_tiles, state.addr, pl);
         hipLaunchKernelGGL(k_plan_arrivals<true>, dim3((unsigned)tail_blocks), dim3(TB), 2 * off_lds, st,
-                           sorted, total, pl.scalars, state.addr, w.d_offsets, S, state.bitmap,
+                           sorted, total, pl.scalars, held_bits, w.d_offsets, S, state.bitmap,
                            pl.cand_base, num_nodes, pl, (int32_t*)nullptr);
         hipLaunchKernelGGL(k_plan_replay, dim3(1), dim3(BIG), 0, st, state, pl, ctiles, cs_offsets,
                            in_ids, out_ids);
@@ -2642,22 +2796,27 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
                            src_line, total_changes, init_ready, start_ids, final_ids, ws, ws_bytes,
                            stream, false);
     }
-    // not for this path: the loop, from the untouched start state
-    GINEX_HIP(fill_async<uint32_t>(state.bitmap, state.words, 0u, st));
-    GINEX_HIP(fill_async<int64_t>(miss_count, S, 0, st));
+    // not for this path
+    if (loop)
+      return changeset_run(who, lru, num_nodes, ids, ids_offsets, S, cap, init_ids, init_count,
+                           in_ids, out_ids, in_positions, cs_capacity, cs_offsets, miss_count,
+                           src_line, total_changes, init_ready, start_ids, final_ids, ws, ws_bytes,
+                           stream, false);
     GINEX_HIP(fill_async<int64_t>(cs_offsets, S + 1, 0, st));
-    if (loop) {
-      hipLaunchKernelGGL(k_look_right, dim3((unsigned)w.look_tiles), dim3(TB), off_lds, st, sorted,
-                         total, w.d_offsets, S, w.next_iter);
-      GINEX_LAUNCH_CHECK();
-    }
   }
 
   if (stays) {
+    if (start_ids) {
+      const int64_t hist_blocks = std::min<int64_t>(ceil_div(distinct, TB * 16), 1024);
+      hipLaunchKernelGGL(k_held_hist, dim3((unsigned)hist_blocks), dim3(TB), sizeof(uint32_t) * S, st,
+                         heads, distinct, held_bits, state);
+      GINEX_LAUNCH_CHECK();
+    }
     uint64_t* const ends = sorted == w.pairs_a ? w.pairs_b : w.pairs_a;
     uint64_t* const rows = heads == w.heads_a ? w.heads_b : w.heads_a;
-    return stays_run(who, w, sorted, ends, rows, distinct, start_ids ? nullptr : heads + (cap - 1), ids,
-                     ids_offsets, total, S, in_ids, out_ids, in_positions, cs_capacity, cs_offsets, miss_count,
+    return stays_run(who, w, sorted, ends, rows, distinct, start_ids ? nullptr : heads + (cap - 1),
+                     held_bits, accessed, ids, ids_offsets, total, S, in_ids, out_ids, in_positions,
+                     cs_capacity, cs_offsets, miss_count,
                      src_line, total_changes, start_ids != nullptr, final_ids, st);
   }
 

@@ -59,10 +59,10 @@ struct Stays {
 
 // Is the row of a run head (first access of its row, in iteration `first`) in the start state?
 // Fresh superbatch: C_0 is the `cap` smallest (first access, id), the last of them *last_head.
-// Carried cache: the address table says.
+// Carried cache: the bitmap of the rows it holds says.
 __device__ __forceinline__ bool in_start_state(uint32_t v, int32_t first, const uint64_t* last_head,
-                                               const int32_t* addr) {
-  return last_head ? (((uint64_t)(uint32_t)first << 32) | v) <= *last_head : addr[v] >= 0;
+                                               const uint32_t* held) {
+  return last_head ? (((uint64_t)(uint32_t)first << 32) | v) <= *last_head : held[v >> 5] >> (v & 31) & 1u;
 }
 
 // One pass over the node-sorted pairs: the ends of every access's stays, written at its position
@@ -70,7 +70,7 @@ __device__ __forceinline__ bool in_start_state(uint32_t v, int32_t first, const 
 __global__ __launch_bounds__(TB) void k_stay_ends(const uint64_t* __restrict__ sorted, int64_t n,
                                                   const int64_t* __restrict__ off, int32_t S,
                                                   const uint64_t* __restrict__ last_head,
-                                                  const int32_t* __restrict__ addr,
+                                                  const uint32_t* __restrict__ held,
                                                   uint64_t* __restrict__ ends) {
   extern __shared__ int32_t lds_off[];
   load_offsets(lds_off, off, S);
@@ -86,7 +86,7 @@ __global__ __launch_bounds__(TB) void k_stay_ends(const uint64_t* __restrict__ s
     if ((uint32_t)(left >> 32) == v) {
       prev_pos = (uint32_t)left;
       prev = (uint32_t)iter_of(lds_off, S, (int32_t)prev_pos);
-    } else if (in_start_state(v, last_head ? iter_of(lds_off, S, (int32_t)p) : 0, last_head, addr)) {
+    } else if (in_start_state(v, last_head ? iter_of(lds_off, S, (int32_t)p) : 0, last_head, held)) {
       prev = FROM_START;
     }
     if (j + 1 < n) {
@@ -596,6 +596,7 @@ static_assert(LINK_CHUNKS * TB == LOOK_TILE, "a block works on one tile of the r
 __global__ __launch_bounds__(TB) void k_stays_links(Stays q, const uint64_t* __restrict__ sorted, int64_t n,
                                                     const uint32_t* __restrict__ head_bases,
                                                     const uint64_t* __restrict__ last_head,
+                                                    const uint32_t* __restrict__ held,
                                                     const int32_t* __restrict__ addr, Never nv,
                                                     uint64_t* __restrict__ hit_words,
                                                     uint64_t* __restrict__ ins_words,
@@ -666,7 +667,7 @@ __global__ __launch_bounds__(TB) void k_stays_links(Stays q, const uint64_t* __r
     bool h = reached;
     if (head >> k & 1u) {
       h = false;
-      if ((int32_t)p < start_end && in_start_state(v, it[k], last_head, addr)) {
+      if ((int32_t)p < start_end && in_start_state(v, it[k], last_head, held)) {
         const int32_t e = stay_end(q, FROM_START, it[k], v, nullptr, it[k]);
         h = e == it[k];
         if (!h) leave_start[addr[v]] = (uint32_t)e;
@@ -846,14 +847,15 @@ __global__ __launch_bounds__(TB) void k_stays_walk(Stays q, const uint64_t* __re
   }
 }
 
-// Start-state rows that the superbatch never accesses (carried caches; keys: res_next).
-// leave_start may be the array of keys itself.
+// Start-state rows that the superbatch never accesses (carried caches; accessed: bitmap over ids).
 __global__ __launch_bounds__(TB) void k_stays_idle(Stays q, const int32_t* __restrict__ res_id,
-                                                   const int32_t* res_next, int64_t cap,
-                                                   uint32_t* leave_start) {
+                                                   const uint32_t* __restrict__ accessed, int64_t cap,
+                                                   uint32_t* __restrict__ leave_start) {
   const int64_t l = (int64_t)blockIdx.x * TB + threadIdx.x;
-  if (l >= cap || res_next[l] != q.S) return;
-  const int32_t e = never_end(q.never, q.S, never_levels(q.S), 0, (uint32_t)res_id[l]);
+  if (l >= cap) return;
+  const uint32_t v = (uint32_t)res_id[l];
+  if (accessed[v >> 5] >> (v & 31) & 1u) return;
+  const int32_t e = never_end(q.never, q.S, never_levels(q.S), 0, v);
   leave_start[l] = e < q.S ? (uint32_t)e : STAYS;
 }
 
