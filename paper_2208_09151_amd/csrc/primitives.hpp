@@ -104,7 +104,9 @@ inline hipError_t occurrences_async(const int32_t* values, int64_t n, int64_t bi
 }
 
 // ---------------------------------------------------------------------------------
-// Stable LSD radix sort of uint64 words on bits [bit_lo, bit_hi), 8 bits per pass.
+// Stable LSD radix sort of uint64 words on bits [bit_lo, bit_hi), at most 8 bits per pass and the same
+// number in every pass, or one less in the last ones: 27 bits as 7 + 7 + 7 + 6 instead of 8 + 8 + 8 + 3 halve the
+// counters that are scanned and double the runs that are written (33 M pairs: 1.22 -> 1.02 ms).
 // Each pass: (1) per-tile digit histogram, (2) exclusive scan of the digit-major
 // histogram, (3) scatter.  In the scatter a wave owns a contiguous run of its tile and
 // ranks its 64 keys per step with ballot-built peer masks, so equal digits keep their
@@ -114,7 +116,8 @@ constexpr int RS_THREADS = 256;
 constexpr int RS_WAVES = RS_THREADS / WAVE;
 constexpr int RS_ITEMS = 16;                    // keys per thread
 constexpr int RS_TILE = RS_THREADS * RS_ITEMS;  // 4096 keys, 32 KB of LDS staging
-constexpr int RS_BINS = 256;
+constexpr int RS_BITS = 8;
+constexpr int RS_BINS = 1 << RS_BITS;           // at most
 
 // Where a pass reads its words: an array of words, or (the first pass of a sort of
 // (value, position) pairs) an array of 32-bit values, word j = value j << 32 | j, so that the
@@ -130,36 +133,39 @@ struct RadixValuesWithPositions {
   }
 };
 
-template <typename Source>
+template <typename Source, int BITS>
 static __global__ __launch_bounds__(RS_THREADS) void k_radix_hist(Source in, int64_t n, int shift,
                                                                   int64_t tiles,
                                                                   uint32_t* __restrict__ hist) {
-  __shared__ uint32_t bins[RS_BINS];
-  bins[threadIdx.x] = 0;
+  constexpr int BINS = 1 << BITS;
+  __shared__ uint32_t bins[BINS];
+  if (threadIdx.x < BINS) bins[threadIdx.x] = 0;
   __syncthreads();
   const int64_t base = (int64_t)blockIdx.x * RS_TILE;
 #pragma unroll
   for (int i = 0; i < RS_ITEMS; ++i) {
     const int64_t j = base + i * RS_THREADS + threadIdx.x;
-    if (j < n) atomicAdd(&bins[(in(j) >> shift) & (RS_BINS - 1)], 1u);
+    if (j < n) atomicAdd(&bins[(in(j) >> shift) & (BINS - 1)], 1u);
   }
   __syncthreads();
-  hist[(int64_t)threadIdx.x * tiles + blockIdx.x] = bins[threadIdx.x];
+  if (threadIdx.x < BINS) hist[(int64_t)threadIdx.x * tiles + blockIdx.x] = bins[threadIdx.x];
 }
 
-template <typename Source>
+template <typename Source, int BITS>
 static __global__ __launch_bounds__(RS_THREADS) void k_radix_scatter(
     Source in, uint64_t* __restrict__ out, int64_t n, int shift, int64_t tiles,
     const uint32_t* __restrict__ hist_scanned) {
+  constexpr int BINS = 1 << BITS;
+  static_assert(BINS <= RS_THREADS, "a thread per digit");
   __shared__ uint64_t staged[RS_TILE];
-  __shared__ uint32_t wave_count[RS_WAVES][RS_BINS];
-  __shared__ uint32_t digit_start[RS_BINS];   // start of each digit inside the tile
-  __shared__ int64_t digit_dst[RS_BINS];      // global destination of the digit's run
+  __shared__ uint32_t wave_count[RS_WAVES][BINS];
+  __shared__ uint32_t digit_start[BINS];   // start of each digit inside the tile
+  __shared__ int64_t digit_dst[BINS];      // global destination of the digit's run
   __shared__ uint32_t scan_smem[RS_THREADS / WAVE + 1];
 
   const int w = threadIdx.x / WAVE;
   const int lane = lane_id();
-  for (int i = threadIdx.x; i < RS_WAVES * RS_BINS; i += RS_THREADS) (&wave_count[0][0])[i] = 0;
+  for (int i = threadIdx.x; i < RS_WAVES * BINS; i += RS_THREADS) (&wave_count[0][0])[i] = 0;
   __syncthreads();
 
   const int64_t tile_base = (int64_t)blockIdx.x * RS_TILE;
@@ -171,10 +177,10 @@ static __global__ __launch_bounds__(RS_THREADS) void k_radix_scatter(
     const int64_t j = wave_base + i * WAVE + lane;
     const bool valid = j < n;
     key[i] = valid ? in(j) : 0;
-    const uint32_t d = (uint32_t)(key[i] >> shift) & (RS_BINS - 1);
+    const uint32_t d = (uint32_t)(key[i] >> shift) & (BINS - 1);
     uint64_t peers = __ballot(valid);
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
+    for (int b = 0; b < BITS; ++b) {
       const uint64_t m = __ballot((d >> b) & 1);
       peers &= ((d >> b) & 1) ? m : ~m;
     }
@@ -195,16 +201,19 @@ static __global__ __launch_bounds__(RS_THREADS) void k_radix_scatter(
   {
     const int d = threadIdx.x;
     uint32_t run = 0;
+    if (d < BINS)
 #pragma unroll
-    for (int ww = 0; ww < RS_WAVES; ++ww) {
-      const uint32_t c = wave_count[ww][d];
-      wave_count[ww][d] = run;
-      run += c;
-    }
+      for (int ww = 0; ww < RS_WAVES; ++ww) {
+        const uint32_t c = wave_count[ww][d];
+        wave_count[ww][d] = run;
+        run += c;
+      }
     uint32_t total;
     const uint32_t start = block_exclusive_scan<uint32_t, RS_THREADS>(run, scan_smem, total);
-    digit_start[d] = start;
-    digit_dst[d] = (int64_t)hist_scanned[(int64_t)d * tiles + blockIdx.x] - (int64_t)start;
+    if (d < BINS) {
+      digit_start[d] = start;
+      digit_dst[d] = (int64_t)hist_scanned[(int64_t)d * tiles + blockIdx.x] - (int64_t)start;
+    }
   }
   __syncthreads();
 
@@ -212,7 +221,7 @@ static __global__ __launch_bounds__(RS_THREADS) void k_radix_scatter(
   for (int i = 0; i < RS_ITEMS; ++i) {
     const int64_t j = wave_base + i * WAVE + lane;
     if (j < n) {
-      const uint32_t d = (uint32_t)(key[i] >> shift) & (RS_BINS - 1);
+      const uint32_t d = (uint32_t)(key[i] >> shift) & (BINS - 1);
       staged[digit_start[d] + wave_count[w][d] + rank[i]] = key[i];
     }
   }
@@ -222,7 +231,7 @@ static __global__ __launch_bounds__(RS_THREADS) void k_radix_scatter(
   const int count = remaining < RS_TILE ? (int)remaining : RS_TILE;
   for (int i = threadIdx.x; i < count; i += RS_THREADS) {
     const uint64_t k = staged[i];
-    const uint32_t d = (uint32_t)(k >> shift) & (RS_BINS - 1);
+    const uint32_t d = (uint32_t)(k >> shift) & (BINS - 1);
     out[digit_dst[d] + i] = k;
   }
 }
@@ -243,19 +252,36 @@ inline RadixPlan radix_plan(int64_t n) {
 // Sorts `n` words by bits [bit_lo, bit_hi).  `a` holds the input, `b` is a buffer of the
 // same size; returns (through *sorted) which of the two holds the result.  The total
 // number of keys must stay below 2^32 (uint32 histogram).
-template <typename Source>
-inline hipError_t radix_pass(Source in, uint64_t* out, int64_t n, int shift, const RadixPlan& p,
-                             uint32_t* hist, hipStream_t st) {
-  const int64_t h = p.tiles * RS_BINS;
-  hipLaunchKernelGGL(k_radix_hist<Source>, dim3((unsigned)p.tiles), dim3(RS_THREADS), 0, st, in, n,
+template <typename Source, int BITS>
+inline hipError_t radix_pass_bits(Source in, uint64_t* out, int64_t n, int shift, const RadixPlan& p,
+                                  uint32_t* hist, hipStream_t st) {
+  const int64_t h = p.tiles << BITS;
+  hipLaunchKernelGGL((k_radix_hist<Source, BITS>), dim3((unsigned)p.tiles), dim3(RS_THREADS), 0, st, in, n,
                      shift, p.tiles, hist);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   e = exclusive_scan_inplace<uint32_t>(hist, h, hist + h, st);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_radix_scatter<Source>, dim3((unsigned)p.tiles), dim3(RS_THREADS), 0, st, in,
+  hipLaunchKernelGGL((k_radix_scatter<Source, BITS>), dim3((unsigned)p.tiles), dim3(RS_THREADS), 0, st, in,
                      out, n, shift, p.tiles, hist);
   return hipGetLastError();
+}
+
+// A pass over `bits` bits (the digit may be wider than that: the bits above are zero or not sorted by).
+template <typename Source>
+inline hipError_t radix_pass(Source in, uint64_t* out, int64_t n, int shift, int bits, const RadixPlan& p,
+                             uint32_t* hist, hipStream_t st) {
+  if (bits >= 8) return radix_pass_bits<Source, 8>(in, out, n, shift, p, hist, st);
+  if (bits == 7) return radix_pass_bits<Source, 7>(in, out, n, shift, p, hist, st);
+  if (bits == 6) return radix_pass_bits<Source, 6>(in, out, n, shift, p, hist, st);
+  return radix_pass_bits<Source, 5>(in, out, n, shift, p, hist, st);
+}
+
+// Bits of pass `k` of the passes that cover `bits`: as even as possible, the wider ones first.
+inline int radix_passes(int bits) { return (bits + RS_BITS - 1) / RS_BITS; }
+inline int radix_pass_width(int bits, int k) {
+  const int passes = radix_passes(bits);
+  return bits / passes + (k < bits % passes ? 1 : 0);
 }
 
 inline hipError_t radix_sort_u64(uint64_t* a, uint64_t* b, int64_t n, int bit_lo, int bit_hi,
@@ -263,10 +289,12 @@ inline hipError_t radix_sort_u64(uint64_t* a, uint64_t* b, int64_t n, int bit_lo
   *sorted = a;
   if (n <= 1) return hipSuccess;
   const RadixPlan p = radix_plan(n);
-  for (int shift = bit_lo; shift < bit_hi; shift += 8) {
-    const hipError_t e = radix_pass(RadixWords{a}, b, n, shift, p, hist, st);
+  for (int k = 0, shift = bit_lo; k < radix_passes(bit_hi - bit_lo); ++k) {
+    const int bits = radix_pass_width(bit_hi - bit_lo, k);
+    const hipError_t e = radix_pass(RadixWords{a}, b, n, shift, bits, p, hist, st);
     if (e != hipSuccess) return e;
     uint64_t* t = a; a = b; b = t;
+    shift += bits;
   }
   *sorted = a;
   return hipSuccess;
@@ -281,12 +309,18 @@ inline hipError_t radix_sort_values_with_positions(const int32_t* values, uint64
   *sorted = a;
   if (n <= 0) return hipSuccess;
   const RadixPlan p = radix_plan(n);
-  hipError_t e = radix_pass(RadixValuesWithPositions{values}, a, n, 32, p, hist, st);
-  if (e != hipSuccess) return e;
-  for (int shift = 40; shift < bit_hi; shift += 8) {
-    e = radix_pass(RadixWords{a}, b, n, shift, p, hist, st);
+  int shift = 32;
+  for (int k = 0; k < radix_passes(bit_hi - 32); ++k) {
+    const int bits = radix_pass_width(bit_hi - 32, k);
+    hipError_t e;
+    if (k == 0) {
+      e = radix_pass(RadixValuesWithPositions{values}, a, n, shift, bits, p, hist, st);
+    } else {
+      e = radix_pass(RadixWords{a}, b, n, shift, bits, p, hist, st);
+      uint64_t* t = a; a = b; b = t;
+    }
     if (e != hipSuccess) return e;
-    uint64_t* t = a; a = b; b = t;
+    shift += bits;
   }
   *sorted = a;
   return hipSuccess;
