@@ -66,7 +66,8 @@ __device__ __forceinline__ bool in_start_state(uint32_t v, int32_t first, const 
 }
 
 // One pass over the node-sorted pairs: the ends of every access's stays, written at its position
-// (one scattered word per access; bound by that store).
+// (one scattered word per access; bound by that store).  A wave takes LOOK_ITEMS * 64 consecutive pairs
+// and passes positions and iterations on to the neighbours, so that each is read and searched once.
 __global__ __launch_bounds__(TB) void k_stay_ends(const uint64_t* __restrict__ sorted, int64_t n,
                                                   const int64_t* __restrict__ off, int32_t S,
                                                   const uint64_t* __restrict__ last_head,
@@ -74,25 +75,49 @@ __global__ __launch_bounds__(TB) void k_stay_ends(const uint64_t* __restrict__ s
                                                   uint64_t* __restrict__ ends) {
   extern __shared__ int32_t lds_off[];
   load_offsets(lds_off, off, S);
-  const int64_t base = (int64_t)blockIdx.x * LOOK_TILE;
+  const int lane = lane_id();
+  const int64_t base = (int64_t)blockIdx.x * LOOK_TILE + (threadIdx.x / WAVE) * (WAVE * LOOK_ITEMS);
+  if (base >= n) return;                           // uniform over the wave
+  // behind n: an id that no access has; chunk LOOK_ITEMS holds the pair behind the stretch
+  uint64_t cur[LOOK_ITEMS + 1];
 #pragma unroll
-  for (int i = 0; i < LOOK_ITEMS; ++i) {
-    const int64_t j = base + i * TB + threadIdx.x;
-    if (j >= n) continue;
-    const uint64_t cur = sorted[j];
-    const uint32_t v = (uint32_t)(cur >> 32), p = (uint32_t)cur;
-    uint32_t prev_pos = 0, prev = NO_STAY, next = (uint32_t)S;
-    const uint64_t left = j > 0 ? sorted[j - 1] : ~cur;
-    if ((uint32_t)(left >> 32) == v) {
-      prev_pos = (uint32_t)left;
-      prev = (uint32_t)iter_of(lds_off, S, (int32_t)prev_pos);
-    } else if (in_start_state(v, last_head ? iter_of(lds_off, S, (int32_t)p) : 0, last_head, held)) {
+  for (int k = 0; k <= LOOK_ITEMS; ++k) {
+    const int64_t x = base + k * WAVE + (k < LOOK_ITEMS ? lane : 0);
+    cur[k] = x < n ? sorted[x] : ~0ull;
+  }
+  uint64_t before = base > 0 ? sorted[base - 1] : ~0ull;
+  int32_t it[LOOK_ITEMS + 1];
+#pragma unroll
+  for (int k = 0; k <= LOOK_ITEMS; ++k)
+    it[k] = (cur[k] >> 32) != 0xFFFFFFFFull ? iter_of(lds_off, S, (int32_t)(uint32_t)cur[k]) : S;
+  int32_t before_it = (before >> 32) != 0xFFFFFFFFull ? iter_of(lds_off, S, (int32_t)(uint32_t)before) : S;
+#pragma unroll
+  for (int k = 0; k < LOOK_ITEMS; ++k) {
+    const uint32_t v = (uint32_t)(cur[k] >> 32), p = (uint32_t)cur[k];
+    uint32_t lv = __shfl_up(v, 1, WAVE), lp = __shfl_up(p, 1, WAVE), rv = __shfl_down(v, 1, WAVE);
+    int32_t li = __shfl_up(it[k], 1, WAVE), ri = __shfl_down(it[k], 1, WAVE);
+    const uint32_t ov = __shfl((uint32_t)(cur[k + 1] >> 32), 0, WAVE);
+    const int32_t oi = __shfl(it[k + 1], 0, WAVE);
+    if (lane == 0) {
+      lv = (uint32_t)(before >> 32);
+      lp = (uint32_t)before;
+      li = before_it;
+    }
+    if (lane == WAVE - 1) {
+      rv = ov;
+      ri = oi;
+    }
+    before = shfl_u64(cur[k], WAVE - 1);
+    before_it = __shfl(it[k], WAVE - 1, WAVE);
+    if (base + k * WAVE + lane >= n) continue;
+    uint32_t prev_pos = 0, prev = NO_STAY;
+    if (lv == v) {
+      prev_pos = lp;
+      prev = (uint32_t)li;
+    } else if (in_start_state(v, it[k], last_head, held)) {
       prev = FROM_START;
     }
-    if (j + 1 < n) {
-      const uint64_t r = sorted[j + 1];
-      if ((uint32_t)(r >> 32) == v) next = (uint32_t)iter_of(lds_off, S, (int32_t)(uint32_t)r);
-    }
+    const uint32_t next = rv == v ? (uint32_t)ri : (uint32_t)S;
     ends[p] = ((uint64_t)next << 48) | ((uint64_t)prev << 32) | prev_pos;
   }
 }
