@@ -2227,8 +2227,11 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
     longest = std::max<int64_t>(longest, ids_offsets[i + 1] - ids_offsets[i]);
 
   // both ends of every stay, the thresholds, the table
-  hipLaunchKernelGGL(k_stay_ends, dim3((unsigned)w.look_tiles), dim3(TB), off_lds, st, sorted, total,
-                     w.d_offsets, S, last_head, held_bits, ends);
+  const int64_t windows = ceil_div(total, ENDS_WINDOW), window = ceil_div(total, windows);
+  for (int64_t from = 0; from < total; from += window)
+    hipLaunchKernelGGL(k_stay_ends, dim3((unsigned)w.look_tiles), dim3(TB), off_lds, st, sorted, total,
+                       w.d_offsets, S, last_head, held_bits, (uint32_t)from,
+                       (uint32_t)std::min(total, from + window), ends);
   GINEX_HIP(fill_async<uint32_t>(w.key_hists, (int64_t)S * (S + 1), 0u, st));
   hipLaunchKernelGGL(k_key_hists, dim3((unsigned)ceil_div(longest, TB * TOUCH_ITEMS), (unsigned)S),
                      dim3(TB), sizeof(uint32_t) * (S + 1), st, ends, w.d_offsets, S, w.key_hists);
