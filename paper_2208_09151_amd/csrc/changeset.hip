@@ -2379,6 +2379,10 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
     const bool large = state.cap >= LARGE_CACHE;
     s.tile_shift = large ? 12 : 9;
     s.tiles = ceil_div(state.cap, int64_t(1) << s.tile_shift);
+    // and there four counters to a 128-byte line, on which additions queue up (0.2 G/s per line;
+    // 13 M lines: 29.9 -> 28.0 us per iteration)
+    s.cnt_shift = large ? 3 : 0;
+    const int64_t stride = s.tiles << s.cnt_shift;
     // flag words: evict_words, and the scratch bitmap over ids, which has room for them (cap is at
     // most num_nodes, and the arrays of the workspace are padded to 256 bytes); the counters sit in
     // the second scratch bitmap, one counter for 512 lines or more against one word for 32 ids
@@ -2386,7 +2390,7 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
     uint32_t* counts = state.bitmap_in;
     GINEX_HIP(fill_async<uint64_t>(flags[0], s.words, 0ull, st));
     GINEX_HIP(fill_async<uint64_t>(flags[1], s.words, 0ull, st));
-    GINEX_HIP(fill_async<uint32_t>(counts, 3 * s.tiles, 0u, st));
+    GINEX_HIP(fill_async<uint32_t>(counts, 3 * stride, 0u, st));
     s.leaving = leaving;
     s.leave_ins = leave_ins;
     s.in_ids = in_ids;
@@ -2404,9 +2408,9 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
     for (int32_t t = 0; t < S; ++t) {
       s.now = flags[t & 1];
       s.next = flags[(t + 1) & 1];
-      s.cnt_now = counts + (t % 3) * s.tiles;
-      s.cnt_next = counts + ((t + 1) % 3) * s.tiles;
-      s.cnt_clear = counts + ((t + 2) % 3) * s.tiles;
+      s.cnt_now = counts + (t % 3) * stride;
+      s.cnt_next = counts + ((t + 1) % 3) * stride;
+      s.cnt_clear = counts + ((t + 2) % 3) * stride;
       s.emit_blocks = M > 0 ? ceil_div(s.words, large ? 256 : 64) : 0;
       s.flag_blocks = flag_blocks(t + 1);
       s.dst = cs[t];

@@ -933,7 +933,7 @@ struct Step {
   uint64_t *now, *next;        // flag words: lines evicted by this iteration / the next one
   uint32_t *cnt_now, *cnt_next, *cnt_clear;   // set flags per tile of 2^tile_shift lines; cnt_clear: to be zeroed
   int64_t words, tiles;
-  int32_t tile_shift;
+  int32_t tile_shift, cnt_shift;   // a counter every 2^cnt_shift words
   int64_t emit_blocks, flag_blocks;
   int64_t dst, n_change;       // this iteration's records
   int64_t next_dst, next_n;    // the next iteration's
@@ -949,7 +949,7 @@ struct Step {
 
 __device__ __forceinline__ void flag_line(const Step& s, int32_t line) {
   atomicOr((unsigned long long*)&s.next[line >> 6], 1ull << (line & 63));
-  atomicAdd(&s.cnt_next[line >> s.tile_shift], 1u);
+  atomicAdd(&s.cnt_next[line >> s.tile_shift << s.cnt_shift], 1u);
 }
 
 // The flagged lines in line order take the iteration's insertions (a list known up front).  Roles
@@ -995,7 +995,7 @@ __global__ __launch_bounds__(TB) void k_step_lines(State st, Step s) {
   const int64_t first_tile = (first_word * 64) >> s.tile_shift;
   const int64_t own_tiles = (LINE_WORDS * 64) >> s.tile_shift;
   if (threadIdx.x < own_tiles && first_tile + threadIdx.x < s.tiles)
-    s.cnt_clear[first_tile + threadIdx.x] = 0;
+    s.cnt_clear[(first_tile + threadIdx.x) << s.cnt_shift] = 0;
   if (s.n_change == 0) return;
   uint64_t word = 0;
   if (threadIdx.x < LINE_WORDS) {                  // whole waves
@@ -1009,7 +1009,9 @@ __global__ __launch_bounds__(TB) void k_step_lines(State st, Step s) {
   const uint32_t ahead = block_exclusive_scan<uint32_t, TB>(flags, smem, total);
   if (threadIdx.x < LINE_WORDS) s_incl[threadIdx.x] = ahead + flags;
   if (total == 0) return;                          // uniform
-  const int64_t before = block_prefix_of(s.cnt_now, first_tile, red);
+  uint32_t counted = 0;
+  for (int64_t q = threadIdx.x; q < first_tile; q += TB) counted += s.cnt_now[q << s.cnt_shift];
+  const int64_t before = block_sum_u32(counted, red);
   for (uint32_t k = threadIdx.x; k < total; k += TB) {
     int lo = 0, hi = LINE_WORDS - 1;               // the word of the k-th flag
 #pragma unroll
