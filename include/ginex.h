@@ -25,12 +25,13 @@
  *      GINEX_TRACE=1          ginex_changeset_resume reports on stderr which way it went
  *      GINEX_SAMPLER_LDS=0    all hops through hash tables in HBM, none through tables in LDS
  *      GINEX_SAMPLER_TILES=n  at most n tiles of a batch per workgroup column of the sampler
- *      GINEX_DEAD_SCATTER=0/1 evictions among dead rows from a pass over the lines / from the id bitmap
  *      GINEX_LIVE_SELECT=1    no shortcut that relies on the cache holding the whole superbatch
  *      GINEX_STATIC_THRESHOLDS=0  Belady changesets from a loop over the cache state, iteration by
  *                             iteration, instead of from the trace alone
- *      GINEX_PLANNED=0/2      a carried cache that holds the whole superbatch: still the general
- *                             loop / the three-launch steps also where the replay would do
+ *      GINEX_DEAD_SCATTER=0/1 in that loop, evictions among dead rows from a pass over the lines / from
+ *                             the id bitmap
+ *      GINEX_PLANNED=0/2      a carried cache that holds the whole superbatch: as any other cache /
+ *                             the three-launch steps also where the replay would do
  */
 #ifndef GINEX_H
 #define GINEX_H
@@ -235,7 +236,7 @@ int32_t ginex_changeset_noalloc(
  * evicts a row that is still needed: hits, misses and insertions are known up front and only
  * the choice of the evicted rows follows the iterations, replayed by one workgroup or, for
  * more candidates or evictions than that holds, in three small launches per iteration
- * (same result; GINEX_PLANNED=0 in the environment keeps the general loop, 2 takes the
+ * (same result; GINEX_PLANNED=0 in the environment treats it as any other cache, 2 takes the
  * three-launch way also where the replay would do, GINEX_TRACE=1 reports on stderr which way
  * a call went). */
 int32_t ginex_changeset_resume(

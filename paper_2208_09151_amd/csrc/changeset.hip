@@ -6,7 +6,11 @@
 //   accessed iteration, the head of each node's run tells the node's first access.
 // Part 2, C_0: run heads (first iteration, node) sorted by first iteration; the first
 //   `cap` of them fill cache lines 0..cap-1.
-// Part 3, the recurrence C_{i+1} = f_Belady(union(C_i, ids_i)), serial over iterations and
+// Part 3, the recurrence C_{i+1} = f_Belady(union(C_i, ids_i)).  For up to 2 048 iterations
+//   hits, misses, insertions and evictions follow from the trace and the start state at once,
+//   and only the lines are handed on iteration by iteration (stays.hpp; a carried cache that
+//   holds every row of the superbatch: the part "no loop" below).  For LRU, and beyond 2 048
+//   iterations, a loop over the state, serial over iterations and
 //   parallel inside one.  The cache is full from C_0 on (otherwise everything fitted and
 //   nothing ever changes), so iteration i must drop exactly as many candidates as it had
 //   misses.  Keys are (next iteration, incoming?, node id); next iterations take only
@@ -303,7 +307,13 @@ __global__ __launch_bounds__(TB) void k_init_state_resume(const int32_t* __restr
 // come in no order, so every access below is to a random place; the kernel above makes three of
 // them per line, two of them atomics on the memory side (2.05 ms for 27.75 M lines of 111 M nodes),
 // these one read of a 14 MB bitmap, one byte stored, and a table entry stored for the rows that are
-// accessed (k_hold 0.99 ms, the passes around it 0.15).  Whether all rows are distinct and in range shows in the number of bytes set.
+// accessed (0.99 ms in the order of the lines; dealt by the upper eight bits of the id first: 0.17 + 0.41
+// ms; the passes around it 0.15).  Whether all rows are distinct and in range shows in the number of bytes set.
+constexpr int HOLD_ITEMS = 8;
+// Lines are dealt from here on, and where the free buffer of the sort has a word for each.  2^20 lines:
+// dealt 16 + 11 us and the scans of the counters (10), in their own order 19; 2^21: 20 + 28 (and 10)
+// against 51; 2^22: 28 + 54 (and 10) against 128.
+constexpr int64_t HOLD_DEAL_MIN = int64_t(1) << 22;
 
 // bit v of `bits` for every head (heads in id order, so a word's bits are neighbours: a wave
 // gathers them and stores words that are its own)
@@ -327,31 +337,35 @@ __global__ __launch_bounds__(TB) void k_accessed_bits(const uint64_t* __restrict
   else bits[w] = word;
 }
 
-// held[v] = 1 and, for the rows that are accessed, addr[v] = line
-__global__ __launch_bounds__(TB) void k_hold(const int32_t* __restrict__ start_ids, int64_t cap,
-                                             int64_t num_nodes, const uint32_t* __restrict__ accessed,
-                                             uint8_t* __restrict__ held, int32_t* __restrict__ res_id,
-                                             int32_t* __restrict__ addr) {
-  constexpr int ITEMS = 8;
-  const int64_t base = (int64_t)blockIdx.x * (TB * ITEMS) + threadIdx.x;
-  int32_t v[ITEMS];
-  uint32_t word[ITEMS];
+// held[v] = 1 and, for the rows that are accessed, addr[v] = line, for the words (v << 32 | line).
+// In the order of the lines every access is a random one.  Where the words come dealt by the upper bits
+// of v (DEALT), an XCD takes an eighth of them, and what its blocks touch at a time stays in its L2.
+template <bool DEALT, typename Source>
+__global__ __launch_bounds__(TB) void k_hold(Source in, int64_t cap, int64_t num_nodes,
+                                             const uint32_t* __restrict__ accessed,
+                                             uint8_t* __restrict__ held, int32_t* __restrict__ addr) {
+  // (blocks go to the eight XCDs in turn)
+  const int64_t b = DEALT ? (int64_t)(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8 : blockIdx.x;
+  const int64_t base = b * (TB * HOLD_ITEMS) + threadIdx.x;
+  int32_t v[HOLD_ITEMS], line[HOLD_ITEMS];
+  uint32_t word[HOLD_ITEMS];
 #pragma unroll
-  for (int t = 0; t < ITEMS; ++t) {
+  for (int t = 0; t < HOLD_ITEMS; ++t) {
     const int64_t s = base + t * TB;
-    v[t] = s < cap ? start_ids[s] : -1;
+    const uint64_t w = s < cap ? in(s) : ~0ull;
+    v[t] = (int32_t)(w >> 32);
+    line[t] = (int32_t)w;
   }
 #pragma unroll
-  for (int t = 0; t < ITEMS; ++t) {
+  for (int t = 0; t < HOLD_ITEMS; ++t) {
     if (v[t] >= num_nodes) v[t] = -1;    // shows in the number of rows held
     word[t] = v[t] >= 0 ? accessed[(uint32_t)v[t] >> 5] : 0u;
   }
 #pragma unroll
-  for (int t = 0; t < ITEMS; ++t) {
+  for (int t = 0; t < HOLD_ITEMS; ++t) {
     if (v[t] < 0) continue;
     held[v[t]] = 1;
-    res_id[base + t * TB] = v[t];
-    if (word[t] >> (v[t] & 31) & 1u) addr[v[t]] = (int32_t)(base + t * TB);
+    if (word[t] >> (v[t] & 31) & 1u) addr[v[t]] = line[t];
   }
 }
 
@@ -464,7 +478,8 @@ __global__ __launch_bounds__(TB) void k_copy_init(const uint64_t* __restrict__ h
 
 // ---- part 3 -----------------------------------------------------------------------
 //
-// One iteration of the recurrence is six dependent launches:
+// The loop over the state (LRU, more iterations than stays.hpp takes).  One iteration of the
+// recurrence is six dependent launches:
 //   k_touch      hits get their new key, hits and misses are histogrammed by key, the line of
 //                every access (or -1) is kept for the later phases and for the executor
 //   k_threshold  one block: walks the histograms down from "never", fixes the threshold
@@ -2644,8 +2659,20 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
         GINEX_HIP(fill_async<uint64_t>(reinterpret_cast<uint64_t*>(held), state.words * 4, 0ull, st));
         hipLaunchKernelGGL(k_accessed_bits, dim3((unsigned)ceil_div(distinct, TB)), dim3(TB), 0, st, heads,
                            distinct, accessed);
-        hipLaunchKernelGGL(k_hold, dim3((unsigned)ceil_div(cap, TB * 8)), dim3(TB), 0, st, start_ids, cap,
-                           num_nodes, accessed, held, state.res_id, state.addr);
+        GINEX_HIP(hipMemcpyAsync(state.res_id, start_ids, sizeof(int32_t) * cap, hipMemcpyDeviceToDevice, st));
+        const unsigned hold_blocks = (unsigned)ceil_div(ceil_div(cap, TB * HOLD_ITEMS), 8) * 8;
+        const RadixValuesWithPositions lines{start_ids};
+        if (cap >= HOLD_DEAL_MIN && cap <= total) {
+          uint64_t* const dealt = sorted == w.pairs_a ? w.pairs_b : w.pairs_a;
+          const int id_bits = bits_for(num_nodes);
+          GINEX_HIP(radix_pass(lines, dealt, cap, 32 + (id_bits > 8 ? id_bits - 8 : 0), 8, radix_plan(cap),
+                               w.hist, st));
+          hipLaunchKernelGGL(k_hold<true>, dim3(hold_blocks), dim3(TB), 0, st, RadixWords{dealt}, cap,
+                             num_nodes, accessed, held, state.addr);
+        } else {
+          hipLaunchKernelGGL(k_hold<false>, dim3(hold_blocks), dim3(TB), 0, st, lines, cap, num_nodes,
+                             accessed, held, state.addr);
+        }
         hipLaunchKernelGGL(k_held_words, dim3((unsigned)state.parts), dim3(TB), 0, st, held, state,
                            accessed, held_bits, w.d_counts);
       }
