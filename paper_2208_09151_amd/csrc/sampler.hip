@@ -724,6 +724,16 @@ int64_t meta_elems(int32_t S, int32_t H) {
   return (int64_t)(S + 1) + (int64_t)S * (H + 1) + 2 * ((int64_t)S * H + 1) + 4;
 }
 
+// Pinned host memory, read by the kernels over the link?
+bool in_host_memory(const void* p) {
+  hipPointerAttribute_t a;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+    (void)hipGetLastError();   // memory the runtime does not know
+    return false;
+  }
+  return a.type == hipMemoryTypeHost;
+}
+
 // with_buckets: room for the buckets as well, which on a small graph (where a list cannot outgrow the
 // graph but its candidates can) is more than the tables take.  A workspace without it still serves,
 // through the tables.
@@ -1253,6 +1263,7 @@ extern "C" int32_t ginex_sample_superbatch(
                        S, w.nfront, w.nlist_a);
     GINEX_LAUNCH_CHECK();
   }
+  const bool over_link = buckets_fit && lds && in_host_memory(g->indices);
   for (int stage = first_stage; stage < H; ++stage) {
     const int k = stage < 0 ? 1 : fanout[stage];
     const int64_t front = stage < 0 ? (max_batch > 0 ? max_batch : 1) : p.stride_front[stage];
@@ -1261,8 +1272,11 @@ extern "C" int32_t ginex_sample_superbatch(
     const int64_t tpb = capped(ceil_div(front, TB), tile_cap(SLOT_TILES));
     const dim3 grid_slots(grid_blocks(S, tpb));
     // later hops: the hash sets in the LDS of a workgroup per bucket, where the picks of a node fit a
-    // thread's registers and the workspace has room (GINEX_SAMPLER_LDS=0: the tables in HBM)
-    const bool buckets = stage >= 0 && k <= BUCKET_K_MAX && buckets_fit && lds;
+    // thread's registers and the workspace has room (GINEX_SAMPLER_LDS=0: the tables in HBM).  Not
+    // where the neighbour ids come over the host link: there the group of lanes that k_pick gives a
+    // node reads the neighbouring ids of its row in one go, a thread per node asks for each by itself
+    // (1.6 G edges, 42.7 M picks: 83 against 101 ms; 3.6 G edges: 265 against 362)
+    const bool buckets = stage >= 0 && k <= BUCKET_K_MAX && buckets_fit && lds && !over_link;
     if (buckets) {
       if (g->nc_address_table) {
         if (g->offsets_64)

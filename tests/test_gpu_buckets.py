@@ -102,3 +102,23 @@ def test_workspace_without_room_for_buckets(ginex):  # noqa: F811
         else:
             lo = mid + 1
     assert lo < need
+
+
+# neighbour ids behind the host link keep the group of lanes per node; with a neighbour cache in HBM in
+# front of them, and with the same ids in HBM, the lists are the same
+@pytest.mark.parametrize("k", [1, 16, 32])
+def test_neighbour_ids_in_host_memory(ginex, k):  # noqa: F811
+    off, ind = small_graph(n=6000, e=150_000)
+    rng = np.random.default_rng(k)
+    batches = [rng.choice(6000, size=n, replace=False) for n in (1025, 2305, 3)]
+    seeds = np.concatenate(batches).astype(np.int32)
+    so = np.cumsum([0] + [len(b) for b in batches])
+    ref = oracle.sample_superbatch(off.numpy(), ind.numpy(), seeds, so, (k, 3), rng_seed=5,
+                                   first_batch_index=2)
+    pinned = torch.empty(ind.numel(), dtype=torch.int32, pin_memory=True)
+    pinned.copy_(ind)
+    nc = ginex.neighbor_cache_build(dev(off.numpy()), pinned, 40_000)
+    for indices, cache in ((pinned, None), (pinned, nc), (ind.cuda(), nc)):
+        res = ginex.sample_superbatch(dev(off.numpy()), indices, dev(seeds), so, (k, 3), rng_seed=5,
+                                      first_batch_index=2, neighbor_cache=cache)
+        check_sample(res, ref, len(batches), 2)
