@@ -10,13 +10,13 @@ superbatches.  Prints ONE JSON line.
 
 Besides the timed steps the same run times, by default, the legs in which the parts of the
 path that configuration 4's own cache size never exercises do run (--legs):
-  pressure   the last superbatch again with a cache of distinct/16 rows: the Belady loop
-             evicts every iteration, the executor updates the cache and reads misses from
+  pressure   the last superbatch again with a cache of distinct/16 rows: every
+             iteration evicts, the executor updates the cache and reads misses from
              the slow tier (gather "G3": real hit/miss mix against the two-term bound)
   carried    the cache carried from superbatch to superbatch (ginex_changeset_resume), steady
              state: no initialization; where the cache holds every row of a superbatch
-             (configurations 3 and 4) the changesets follow without the loop over the state,
-             elsewhere the loop runs from the carried state
+             (configurations 3 and 4) only the choice of the evicted rows follows the
+             iterations
   allmiss    the gather kernel with nothing resident (gather "G2": pure host link)
 The gathers of the timed steps are "G1" whenever the configuration never misses (3 and 4).
 
@@ -49,7 +49,7 @@ SAMPLER_LINES_PER_EDGE = 2.0
 SAMPLER_BYTES_PER_EDGE = 20.0
 # changeset, per access: four radix passes of the (node, position) pairs (8-byte histogram
 # read, 8 read, 8 written each; the first pass reads the 4-byte ids instead, twice) and the
-# look-right pass (12); then the loop's id, key, address-table probe and key refresh (16)
+# pass that finds next uses (12); then id, key, address-table probe and line (16)
 CHANGESET_BUILD_BYTES_PER_ACCESS = 100
 CHANGESET_LOOP_BYTES_PER_ACCESS = 16
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
@@ -210,12 +210,10 @@ def two_term_bound_s(hits, misses, row_bytes):
         misses * row_bytes / (HOST_LINK_GBPS * 1e9)
 
 
-def changeset_roofline(name, accesses, iterations, cap, changes, seconds, line_passes, traffic):
-    """Algorithmic bytes of a changeset call whose loop ran: build + per-access loop work +
-    one 4-byte key per cache line and iteration for every pass over the lines + 12 bytes per
-    changeset record."""
-    algo = accesses * (CHANGESET_BUILD_BYTES_PER_ACCESS + CHANGESET_LOOP_BYTES_PER_ACCESS) + \
-        iterations * cap * 4 * line_passes + 12 * changes
+def changeset_roofline(name, accesses, changes, seconds, traffic):
+    """Algorithmic bytes of a changeset call that evicts: build + per-access work + 12 bytes per
+    changeset record (no pass over the cache lines)."""
+    algo = accesses * (CHANGESET_BUILD_BYTES_PER_ACCESS + CHANGESET_LOOP_BYTES_PER_ACCESS) + 12 * changes
     r = {"kernel": name, "bound": "hbm", "achieved": algo / seconds / 1e9, "peak": HBM_PEAK_GBPS,
          "unit": "GB/s", "traffic": traffic, "algorithmic_bytes": algo,
          "call_ms": seconds * 1e3, "accesses_per_s": accesses / seconds}
@@ -272,8 +270,8 @@ def pressure_leg(ginex, w, run, samp, divisor, reps=3):
           "avg_launch_ms": float(np.mean(gather_ms)), "launches": S,
           "frac": float(np.sum(bound_ms)) / float(np.sum(gather_ms)),
           "miss_fraction": misses / accesses}
-    roof = changeset_roofline("ginex_changeset (build + Belady loop, every iteration evicts)",
-                              accesses, S, cap, changes, t, 1,
+    roof = changeset_roofline("ginex_changeset (build + stays and lines, every iteration evicts)",
+                              accesses, changes, t,
                               measured_traffic(cfg.name, "changeset_pressure"))
     del cache, ex
     return leg, g3, roof
@@ -323,7 +321,7 @@ def carried_leg(ginex, w, run, first_sb, warm=3, timed=3):
            "edges_per_s": med(rows["edges"]) / (med(rows["total_ms"]) / 1e3)}
     roof = changeset_roofline("ginex_changeset_resume (next-use sort + changesets of a carried cache "
                               "that holds the superbatch: no loop over the state)",
-                              acc, run.S, 0, med(rows["changes"]), t, 0,
+                              acc, med(rows["changes"]), t,
                               measured_traffic(cfg.name, "changeset_carried"))
     del cache, ex
     return leg, roof
@@ -679,9 +677,9 @@ def main():
         "changeset_accesses_per_s": accesses / mid["changeset_s"],
         "changeset_ms": mid["changeset_s"] * 1e3,
         "changeset_note": ("every row of the superbatch fits the cache: next-use sort and C_0 only, "
-                           "the Belady loop does not run (it does in legs.pressure)"
+                           "nothing is evicted (it is in legs.pressure)"
                            if int(np.sum(timers["changes"])) == 0 and all_hit else
-                           "the Belady loop runs in the timed steps"),
+                           "iterations of the timed steps evict"),
         "cache_init_ms": mid["cache_init_s"] * 1e3,
         "cache_init_GBps": fill_GBps,
         "gather_update_ms": mid["gather_update_s"] * 1e3,   # what is left after the fill ends
