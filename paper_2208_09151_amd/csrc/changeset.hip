@@ -2313,17 +2313,19 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
   if (never) {
     static_assert(NEVER_COUNTS <= PLAN_CAND_MAX && NEVER_LEVELS * (STATIC_S_MAX + 1) + NEVER_PARTS <= PLAN_CAND_MAX,
                   "counters and limits sit in the candidate arrays of the planned path");
-    nv.counts = reinterpret_cast<uint32_t*>(pl.cand_line);
     nv.idle = carried ? state.dead_bits : nullptr;
     nv.distinct = distinct;
     nv.num_nodes = state.num_nodes;
-    // parts, a power of two: [S x parts] counters, and a few thousand rows to a part (a cut looks at the
-    // rows of one part)
-    int64_t most = NEVER_PARTS;
+    // parts, a power of two of ids: a few thousand rows to a part where the graph is small, so that
+    // there are few parts to walk over, but never more ids than its bitmap has room for
+    int64_t most = NEVER_THREADS;
     while (most > 1 && (most * S > NEVER_COUNTS || most * 4096 > distinct)) most /= 2;
     nv.shift = 5;                           // (whole words of the bitmap)
-    while (ceil_div(state.num_nodes, int64_t(1) << nv.shift) > most) ++nv.shift;
+    while (nv.shift < NEVER_SHIFT && ceil_div(state.num_nodes, int64_t(1) << nv.shift) > most) ++nv.shift;
     nv.parts = (int32_t)ceil_div(state.num_nodes, int64_t(1) << nv.shift);
+    // (the array of first accesses: the bits of the rows held sat in it, which were read last by k_stays_links)
+    nv.counts = (int64_t)S * nv.parts <= NEVER_COUNTS ? reinterpret_cast<uint32_t*>(pl.cand_line)
+                                                      : reinterpret_cast<uint32_t*>(w.first_of);
     uint32_t* const idle_counts = reinterpret_cast<uint32_t*>(pl.cand_id) + NEVER_LEVELS * (STATIC_S_MAX + 1);
     GINEX_HIP(fill_async<uint32_t>(nv.counts, (int64_t)S * nv.parts, 0u, st));
     const int64_t count_blocks = std::min<int64_t>(ceil_div(distinct, TB * 8), 2048);
@@ -2331,10 +2333,14 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
                        nv, S);
     if (carried)
       hipLaunchKernelGGL(k_never_idle, dim3((unsigned)nv.parts), dim3(TB), 0, st, nv, idle_counts);
-    hipLaunchKernelGGL(k_never_parts, dim3(1), dim3(NEVER_PARTS), 0, st, nv, S, w.cuts,
-                       carried ? idle_counts : (const uint32_t*)nullptr);
-    hipLaunchKernelGGL(k_never_select, dim3((unsigned)nv.parts), dim3(BIG), sizeof(int32_t) * S, st, nv,
-                       S, w.cuts);
+    const uint32_t* const idle_rows = carried ? idle_counts : nullptr;
+    if (nv.parts <= NEVER_THREADS)
+      hipLaunchKernelGGL((k_never_parts<1, 4>), dim3(1), dim3(NEVER_THREADS), 0, st, nv, S, w.cuts, idle_rows);
+    else if (nv.parts <= 4 * NEVER_THREADS)
+      hipLaunchKernelGGL((k_never_parts<4, 4>), dim3(1), dim3(NEVER_THREADS), 0, st, nv, S, w.cuts, idle_rows);
+    else
+      hipLaunchKernelGGL((k_never_parts<16, 2>), dim3(1), dim3(NEVER_THREADS), 0, st, nv, S, w.cuts, idle_rows);
+    hipLaunchKernelGGL(k_never_select, dim3((unsigned)nv.parts), dim3(NEVER_THREADS), 0, st, nv, S, w.cuts);
     GINEX_LAUNCH_CHECK();
   }
   hipLaunchKernelGGL(k_never_lift, dim3(1), dim3(BIG), 0, st, w.cuts, S, pl.cand_id);

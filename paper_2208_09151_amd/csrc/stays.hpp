@@ -430,14 +430,26 @@ __global__ __launch_bounds__(TB) void k_stays_mark(Stays q, int64_t n, int32_t* 
 // The rows of the bucket are those whose last access hit (from that iteration on) and the
 // start-state rows the superbatch never accesses.  Iteration t, if it cuts the bucket, keeps the
 // keep_t of them with the smallest ids (keep_t is known from the thresholds), so one cut follows from
-// the one before.  The ids are divided into at most NEVER_PARTS parts; how many rows each part holds
+// the one before.  The ids are divided into parts; how many rows each part holds
 // after every cut needs no ids: the parts below the one that is cut keep all, the parts above lose
 // all.  One block walks the iterations over the parts' counts (k_never_parts: 0.7 us per iteration), and
-// what id the cut falls on is then found for all parts side by side, each from its own rows
-// (k_never_select).  Setting bits, counting, finding and clearing on one bitmap over all ids, cut
-// after cut, took 43 us per cut.
-constexpr int NEVER_PARTS = 1024;
-constexpr int64_t NEVER_COUNTS = int64_t(1) << 19;   // [S x parts] counters: fewer parts for many iterations
+// what id the cut falls on is then found for all parts side by side (k_never_select).  Setting bits,
+// counting, finding and clearing on one bitmap over all ids, cut after cut, took 43 us per cut.
+//
+// A part spans at most 2^NEVER_SHIFT ids, whatever the superbatch accesses and whatever the cache
+// carries, so that the rows it still holds are a bitmap in LDS: the block of a part takes the
+// idle rows in once, reads the part's accessed rows once per cut and adds those that arrived since the cut
+// before.  (Looking up every id of a part for every cut, three times, with parts as wide as the
+// superbatch was small: a carried cache of 12 000 lines, 20 iterations of 10 000 accesses to 25 000 rows of
+// 60 M nodes took 11.4 ms; 1.1 ms this way, 1.7 through the loop over the state.)
+constexpr int NEVER_THREADS = 1024;
+constexpr int NEVER_SHIFT = 17;
+constexpr int NEVER_WORDS = 1 << (NEVER_SHIFT - 5);    // 16 KB
+constexpr int NEVER_PARTS = 1 << (31 - NEVER_SHIFT);   // at most
+// [S x parts] counters up to here sit in an array of the candidates that stays_run does not use.  More of
+// them take more than 2^25 ids (S is at most 2 048), and are then fewer than the words of the array of
+// first accesses.
+constexpr int64_t NEVER_COUNTS = int64_t(1) << 19;
 
 struct Never {
   uint64_t* rows;          // [distinct] id << 32 | iteration of its last access, if that hits (else NOT_HERE), by id
@@ -448,18 +460,28 @@ struct Never {
 };
 constexpr uint32_t NOT_HERE = 0xFFFFFFFFu;
 
-// counts[i][part], a block per stretch of rows (by id, so a block meets one or a few parts: it
-// counts per iteration in LDS and hands over where the part changes)
+// counts[i][part], a block per stretch of rows (by id).  A stretch that meets up to NEVER_ROUNDS parts
+// counts per iteration in LDS and hands over where the part changes; rows that are
+// thinner than that are added one by one (each part has few of them, so no counter sees many).
+constexpr int NEVER_ROUNDS = 4;
 __global__ __launch_bounds__(TB) void k_never_counts(Never nv, int32_t S) {
   extern __shared__ uint32_t s_cnt[];     // [S]
   const int64_t per = (((nv.distinct + gridDim.x - 1) / gridDim.x + TB - 1) / TB) * TB;
   const int64_t first = (int64_t)blockIdx.x * per;
   const int64_t last = first + per < nv.distinct ? first + per : nv.distinct;
   if (first >= last) return;
-  for (int i = threadIdx.x; i < S; i += TB) s_cnt[i] = 0;
-  __syncthreads();
   int32_t part = (int32_t)((nv.rows[first] >> 32) >> nv.shift);
   const int32_t last_part = (int32_t)((nv.rows[last - 1] >> 32) >> nv.shift);
+  if (last_part - part >= NEVER_ROUNDS) {  // uniform
+    for (int64_t x = first + threadIdx.x; x < last; x += TB) {
+      const uint64_t row = nv.rows[x];
+      const uint32_t i = (uint32_t)row;
+      if (i != NOT_HERE) atomicAdd(&nv.counts[(int64_t)i * nv.parts + (int32_t)((row >> 32) >> nv.shift)], 1u);
+    }
+    return;
+  }
+  for (int i = threadIdx.x; i < S; i += TB) s_cnt[i] = 0;
+  __syncthreads();
   int64_t from = first;
   while (true) {                          // uniform: one round per part of the stretch
     int64_t lo = from, hi = last;         // the first row behind the part
@@ -496,43 +518,48 @@ __global__ __launch_bounds__(TB) void k_never_idle(Never nv, uint32_t* __restric
   if (threadIdx.x == 0) idle_counts[blockIdx.x] = total;
 }
 
-// One block, a part per thread: which part every cut falls into and how many of its rows stay.
-__global__ __launch_bounds__(NEVER_PARTS) void k_never_parts(Never nv, int32_t S, Cut* __restrict__ cuts,
-                                                             const uint32_t* __restrict__ idle_counts) {
-  __shared__ uint32_t slots[2][NEVER_PARTS / WAVE];
+// One block, PER neighbouring parts to a thread: which part every cut falls into and how many of its
+// rows stay.  Arrivals and thresholds are requested AHEAD iterations early.
+template <int PER, int AHEAD>
+__global__ __launch_bounds__(NEVER_THREADS) void k_never_parts(Never nv, int32_t S, Cut* __restrict__ cuts,
+                                                               const uint32_t* __restrict__ idle_counts) {
+  __shared__ uint32_t slots[2][NEVER_THREADS / WAVE];
   int set = 0;                            // the two sets of slots take turns: one barrier per cut
-  const int32_t me = threadIdx.x;
-  const bool mine = me < nv.parts;
-  uint32_t have = mine && idle_counts ? idle_counts[me] : 0u;
-  constexpr int AHEAD = 4;                // arrivals and thresholds are requested AHEAD iterations early
-  uint32_t arrive[AHEAD];
+  const int32_t me = threadIdx.x, first = me * PER;
+  uint32_t have[PER], arrive[AHEAD][PER];
   Cut cut[AHEAD];
+  auto request = [&](int a, int32_t t) {
+#pragma unroll
+    for (int p = 0; p < PER; ++p)
+      arrive[a][p] = first + p < nv.parts ? nv.counts[(int64_t)t * nv.parts + first + p] : 0u;
+    cut[a] = cuts[t];
+  };
+#pragma unroll
+  for (int p = 0; p < PER; ++p) have[p] = idle_counts && first + p < nv.parts ? idle_counts[first + p] : 0u;
 #pragma unroll
   for (int a = 0; a < AHEAD; ++a)
-    if (a < S) {
-      arrive[a] = mine ? nv.counts[(int64_t)a * nv.parts + me] : 0u;
-      cut[a] = cuts[a];
-    }
+    if (a < S) request(a, a);
   for (int32_t t0 = 0; t0 < S; t0 += AHEAD) {
 #pragma unroll
     for (int a = 0; a < AHEAD; ++a) {
       const int32_t t = t0 + a;
       if (t >= S) break;                  // uniform
-      have += arrive[a];
       const Cut c = cut[a];
-      if (t + AHEAD < S) {
-        arrive[a] = mine ? nv.counts[(int64_t)(t + AHEAD) * nv.parts + me] : 0u;
-        cut[a] = cuts[t + AHEAD];
+      uint32_t mine = 0;
+#pragma unroll
+      for (int p = 0; p < PER; ++p) {
+        have[p] = c.jstar < S ? 0u : have[p] + arrive[a][p];
+        mine += have[p];
       }
-      if (c.jstar < S) have = 0;
+      if (t + AHEAD < S) request(a, t + AHEAD);
       if (c.jstar != S) continue;         // uniform
       const uint32_t keep = c.n_res;      // (left there by k_static_roll)
-      uint32_t inc = wave_inclusive_scan(have);
+      uint32_t inc = wave_inclusive_scan(mine);
       if (lane_id() == WAVE - 1) slots[set][me / WAVE] = inc;
       __syncthreads();
-      uint32_t before = inc - have, total = 0;
+      uint32_t before = inc - mine, total = 0;
 #pragma unroll
-      for (int w = 0; w < NEVER_PARTS / WAVE; ++w) {
+      for (int w = 0; w < NEVER_THREADS / WAVE; ++w) {
         const uint32_t s = slots[set][w];
         if (w < me / WAVE) before += s;
         total += s;
@@ -545,45 +572,56 @@ __global__ __launch_bounds__(NEVER_PARTS) void k_never_parts(Never nv, int32_t S
         }
         continue;                         // uniform
       }
-      if (before < keep && before + have >= keep) {
-        cuts[t].kind = CUT_RES;
-        cuts[t].n_res = (uint32_t)me;
-        cuts[t].n_in = keep - before;
-        // the whole part stays: no look at its rows
-        cuts[t].T = keep == before + have ? (int32_t)((((int64_t)me + 1) << nv.shift) - 1) : -1;
+#pragma unroll
+      for (int p = 0; p < PER; ++p) {
+        const uint32_t held = have[p];
+        if (before < keep && before + held >= keep) {
+          cuts[t].kind = CUT_RES;
+          cuts[t].n_res = (uint32_t)(first + p);
+          cuts[t].n_in = keep - before;
+          // the whole part stays: no look at its rows
+          cuts[t].T = keep == before + held ? (int32_t)((((int64_t)(first + p) + 1) << nv.shift) - 1) : -1;
+        }
+        if (before >= keep) have[p] = 0;
+        else if (before + held > keep) have[p] = keep - before;
+        before += held;
       }
-      if (before >= keep) have = 0;
-      else if (before + have > keep) have = keep - before;
     }
   }
 }
 
-// A block per part: the ids of the cuts that fall into it, in order.
-__global__ __launch_bounds__(BIG) void k_never_select(Never nv, int32_t S, Cut* __restrict__ cuts) {
-  extern __shared__ int32_t s_min[];      // [S] smallest limit of the part's cuts from iteration i on
-  __shared__ int32_t s_next, s_emptied;
+// A block per part: the ids of the cuts that fall into it, in order.  `bits` holds the part's rows
+// as they stand after the cut before; a cut costs one read of the part's accessed rows (bound by
+// that, by one workgroup: 200 iterations whose 100 000 rows are all neighbours, in one or two of 848 parts,
+// 37 us for all their cuts; spread over the parts 4 us).
+__global__ __launch_bounds__(NEVER_THREADS) void k_never_select(Never nv, int32_t S, Cut* __restrict__ cuts) {
+  constexpr int WORDS = NEVER_WORDS / NEVER_THREADS, READS = 4;
+  __shared__ uint32_t bits[NEVER_WORDS];
+  __shared__ uint32_t smem[NEVER_THREADS / WAVE + 1];
+  __shared__ int32_t s_next, s_emptied, s_T;
   const int32_t part = blockIdx.x;
+  const int64_t first_word = ((int64_t)part << nv.shift) >> 5, words = (nv.num_nodes + 31) >> 5;
   int64_t from = 0, to = -1;              // the part's rows, found with its first cut
-  for (int i = threadIdx.x; i < S; i += BIG) s_min[i] = INT32_MAX;
   int32_t done = -1;                      // the cut before
   while (true) {
     if (threadIdx.x == 0) {
       s_next = S;
-      s_emptied = -1;
+      s_emptied = s_T = -1;
     }
     __syncthreads();
-    for (int32_t t = done + 1 + threadIdx.x; t < S; t += BIG)
+    for (int32_t t = done + 1 + threadIdx.x; t < S; t += NEVER_THREADS)
       if (cuts[t].jstar == S && cuts[t].kind == CUT_RES && cuts[t].n_res == (uint32_t)part && cuts[t].T < 0)
         atomicMin(&s_next, t);
     __syncthreads();
     const int32_t t = s_next;
     if (t >= S) return;                   // uniform
-    // the last iteration before t that emptied the part
-    for (int32_t e = threadIdx.x; e < t; e += BIG) {
+    // the last iteration since the cut before that emptied the part
+    for (int32_t e = done + 1 + threadIdx.x; e < t; e += NEVER_THREADS) {
       const Cut c = cuts[e];
       if (c.jstar < S || (c.jstar == S && c.kind == CUT_RES && c.n_res < (uint32_t)part)) atomicMax(&s_emptied, e);
     }
-    if (to < 0) {                         // uniform
+    const bool fresh = to < 0;            // uniform
+    if (fresh) {
       const uint64_t lo_id = (uint64_t)part << nv.shift, hi_id = lo_id + (1ull << nv.shift);
       int64_t a = 0, b = nv.distinct;
       while (a < b) {
@@ -599,23 +637,50 @@ __global__ __launch_bounds__(BIG) void k_never_select(Never nv, int32_t S, Cut* 
       to = a;
     }
     __syncthreads();
-    const int32_t emptied = s_emptied;
-    const int64_t n = to - from, first_id = (int64_t)part << nv.shift;
-    const int64_t idle = nv.idle && emptied < 0 ? std::min<int64_t>(int64_t(1) << nv.shift, nv.num_nodes - first_id) : 0;
-    auto id = [&](int64_t x) -> uint32_t {
-      if (x < n) {
-        const uint64_t row = nv.rows[from + x];
-        const uint32_t i = (uint32_t)row, v = (uint32_t)(row >> 32);
-        return i != NOT_HERE && (int32_t)i <= t && (int32_t)i > emptied && (int32_t)v <= s_min[i] ? v : 0xFFFFFFFFu;
-      }
-      const uint32_t v = (uint32_t)(first_id + (x - n));
-      return (nv.idle[v >> 5] >> (v & 31) & 1u) && (int32_t)v <= s_min[0] ? v : 0xFFFFFFFFu;
-    };
-    const int32_t T = p_kth_smallest_id<BIG>(n + idle, cuts[t].n_in, id);
-    for (int32_t i = threadIdx.x; i <= t; i += BIG) s_min[i] = s_min[i] < T ? s_min[i] : T;
-    if (threadIdx.x == 0) cuts[t].T = T;
-    done = t;
+    const int32_t emptied = s_emptied, after = emptied > done ? emptied : done;   // rows that arrived after it
+    if (fresh || emptied > done)
+      for (int w = threadIdx.x; w < NEVER_WORDS; w += NEVER_THREADS)
+        bits[w] = nv.idle && emptied < 0 && w < 1 << (nv.shift - 5) && first_word + w < words
+                      ? nv.idle[first_word + w] : 0u;
     __syncthreads();
+    for (int64_t x0 = from + threadIdx.x; x0 < to; x0 += READS * NEVER_THREADS) {
+      uint64_t row[READS];
+#pragma unroll
+      for (int k = 0; k < READS; ++k)
+        row[k] = nv.rows[x0 + k * NEVER_THREADS < to ? x0 + k * NEVER_THREADS : from];
+#pragma unroll
+      for (int k = 0; k < READS; ++k) {
+        const int32_t i = (int32_t)(uint32_t)row[k];   // (NOT_HERE: -1)
+        const uint32_t v = (uint32_t)(row[k] >> 32) & ((1u << nv.shift) - 1u);
+        if (x0 + k * NEVER_THREADS < to && i > after && i <= t) atomicOr(&bits[v >> 5], 1u << (v & 31));
+      }
+    }
+    __syncthreads();
+    // the row that stays last, WORDS neighbouring words to a thread; the rows above it go
+    uint32_t mine = 0;
+#pragma unroll
+    for (int k = 0; k < WORDS; ++k) mine += __popc(bits[threadIdx.x * WORDS + k]);
+    uint32_t total;
+    uint32_t before = block_exclusive_scan<uint32_t, NEVER_THREADS>(mine, smem, total);
+    const uint32_t keep = cuts[t].n_in;   // at least one, at most `total`
+#pragma unroll
+    for (int k = 0; k < WORDS; ++k) {
+      const int w = threadIdx.x * WORDS + k;
+      const uint32_t word = bits[w], held = __popc(word);
+      if (before >= keep) {
+        bits[w] = 0;
+      } else if (before + held >= keep) {
+        uint32_t rest = word;
+        for (uint32_t skip = keep - before; skip > 1; --skip) rest &= rest - 1;
+        const int bit = __ffs(rest) - 1;
+        bits[w] = word & (uint32_t)((2ull << bit) - 1ull);
+        s_T = (int32_t)(((int64_t)part << nv.shift) + w * 32 + bit);
+      }
+      before += held;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) cuts[t].T = s_T;
+    done = t;
   }
 }
 

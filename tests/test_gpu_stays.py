@@ -1,8 +1,13 @@
-"""Belady changesets whose accesses are laid out in more than one window of positions, against the
-loop over the cache state (tolerance zero): every list, every line."""
+"""Belady changesets from the trace at the sizes where the way they are computed changes, against the
+loop over the cache state and the oracle (tolerance zero): windows of positions, carried caches
+dealt by id, few rows of a large graph."""
+import time
+
 import numpy as np
 import pytest
 import torch
+
+import oracle
 
 from test_gpu_parity import ginex  # noqa: F401
 
@@ -58,3 +63,73 @@ def test_carried_caches_of_many_lines(ginex, cap, total, n, monkeypatch):  # noq
             bad[cap // 2] = wrong
             with pytest.raises(ginex.GinexError, match="1 entries of start_ids"):
                 ginex.changeset_resume(n, ids, off, bad)
+
+
+def thin_trace(n, S, length, span, gen):
+    """Iterations of distinct ids out of a pool of 2.5 * length, spread over `span` neighbouring ids of
+    the graph's n."""
+    pool = torch.unique(torch.randint(span, (5 * length // 2,), generator=gen, device="cuda"))
+    pool = (pool + (n - span) // 2).int()
+    parts = [pool[torch.randperm(pool.numel(), generator=gen, device="cuda")][:length] for _ in range(S)]
+    off = np.cumsum([0] + [x.numel() for x in parts]).astype(np.int64)
+    return torch.cat(parts), off
+
+
+def carried_rows(n, cap, gen):
+    x = torch.unique(torch.randint(n, (cap + cap // 8 + 100,), generator=gen, device="cuda"))
+    return x[torch.randperm(x.numel(), generator=gen, device="cuda")][:cap].int()
+
+
+# few rows of many ids, and many rows of few ids: 229 parts of the ids with a few rows each, the
+# accesses in two or three of them, 458 parts, the same with counters that do not fit the candidate
+# array (1 200 iterations), four and sixteen parts to a thread
+THIN = [(30_000_000, 20, 3_000, 1_500, 30_000_000), (30_000_000, 25, 80_000, 50_000, 200_000),
+        (60_000_000, 20, 10_000, 12_000, 60_000_000), (60_000_000, 1_200, 200, 150, 60_000_000), (140_000_000, 12, 40_000, 20_000, 140_000_000),
+        (600_000_000, 9, 40_000, 20_000, 600_000_000)]
+
+
+@pytest.mark.parametrize("n,S,length,cap,span", THIN)
+def test_few_rows_of_a_large_graph(ginex, n, S, length, cap, span, monkeypatch):  # noqa: F811
+    gen = torch.Generator(device="cuda").manual_seed(n + S)
+    ids, off = thin_trace(n, S, length, span, gen)
+    start = carried_rows(n, cap, gen)
+    assert torch.unique(ids).numel() > cap
+    for run in (lambda: ginex.changeset(n, ids, off, cap),
+                lambda: ginex.changeset_resume(n, ids, off, start)):
+        monkeypatch.setenv("GINEX_STATIC_THRESHOLDS", "0")
+        want = run()
+        monkeypatch.setenv("GINEX_STATIC_THRESHOLDS", "1")
+        got = run()
+        assert np.array_equal(want.miss_count, got.miss_count)
+        assert np.array_equal(want.cs_offsets, got.cs_offsets) and want.cs_offsets[-1] > 0
+        for name in ("in_ids", "out_ids", "in_positions", "src_line", "final_ids"):
+            a, b = getattr(want, name), getattr(got, name)
+            assert (a is None) == (b is None) and (a is None or torch.equal(a, b)), name
+        if n <= 30_000_000:
+            h, o = ids.cpu().numpy(), start.cpu().numpy()
+            ref = oracle.changeset(n, h, off, cap) if got.final_ids is None else \
+                oracle.changeset_resume(n, h, off, cap, o)
+            for name in ("in_ids", "out_ids", "in_positions"):
+                assert np.array_equal(getattr(got, name).cpu().numpy(), ref[name]), name
+            assert np.array_equal(got.miss_count, ref["miss_count"])
+
+
+@pytest.mark.parametrize("n,S,length,cap,span", THIN[1:4])
+def test_few_rows_of_a_large_graph_cost_no_more_than_the_loop(ginex, n, S, length, cap, span,  # noqa: F811
+                                                              monkeypatch):
+    """The way a call takes by itself against the loop over the cache state, best of four (a bucket
+    that was searched id by id took seven times as long as the loop on the second of these)."""
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    ids, off = thin_trace(n, S, length, span, gen)
+    start = carried_rows(n, cap, gen)
+    best = {}
+    for way in ("0", "1"):
+        monkeypatch.setenv("GINEX_STATIC_THRESHOLDS", way)
+        times = []
+        for _ in range(4):
+            torch.cuda.synchronize()
+            began = time.perf_counter()
+            ginex.changeset_resume(n, ids, off, start)
+            times.append(time.perf_counter() - began)
+        best[way] = min(times)
+    assert best["1"] < 1.5 * best["0"], best
