@@ -326,6 +326,7 @@ __global__ __launch_bounds__(BUCKET_THREADS) __attribute__((amdgpu_waves_per_eu(
   if (here.b < 0) return;
   const int b = here.b;
   const int32_t nf = nfront[b];
+  if (nf == 0) return;   // an empty batch has no tiles, and the barriers below are in the loop over them
   const int32_t P = bucket_count(nf, fanout, B.num_nodes, S);
   BucketOf k;
   k.id = B.id + b * B.entries;

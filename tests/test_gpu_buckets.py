@@ -33,6 +33,16 @@ def test_frontiers_around_the_tile_sizes(ginex, k, offsets_64):  # noqa: F811
     both(ginex, off.numpy(), ind.numpy(), batches, (k, 3))
 
 
+# empty batches have no tiles and no buckets; alone, between others, and in front of a first hop that
+# goes through buckets (1025 seeds) or through one workgroup's LDS
+@pytest.mark.parametrize("sizes", [(0,), (0, 0, 0), (0, 1025, 0, 7, 0, 0, 300, 0, 0), (0, 90, 0, 1)])
+def test_empty_batches(ginex, sizes):  # noqa: F811
+    off, ind = small_graph(n=6000, e=150_000)
+    rng = np.random.default_rng(len(sizes))
+    batches = [rng.choice(6000, size=n, replace=False) for n in sizes]
+    both(ginex, off.numpy(), ind.numpy(), batches, (8, 3))
+
+
 def fmix32(h):
     h = h.astype(np.uint32)
     h ^= h >> np.uint32(16)

@@ -84,8 +84,8 @@ def carried_rows(n, cap, gen):
 # accesses in two or three of them, 458 parts, the same with counters that do not fit the candidate
 # array (1 200 iterations), four and sixteen parts to a thread
 THIN = [(30_000_000, 20, 3_000, 1_500, 30_000_000), (30_000_000, 25, 80_000, 50_000, 200_000),
-        (60_000_000, 20, 10_000, 12_000, 60_000_000), (60_000_000, 1_200, 200, 150, 60_000_000), (140_000_000, 12, 40_000, 20_000, 140_000_000),
-        (600_000_000, 9, 40_000, 20_000, 600_000_000)]
+        (60_000_000, 20, 10_000, 12_000, 60_000_000), (60_000_000, 1_200, 200, 150, 60_000_000),
+        (140_000_000, 12, 40_000, 20_000, 140_000_000), (600_000_000, 9, 40_000, 20_000, 600_000_000)]
 
 
 @pytest.mark.parametrize("n,S,length,cap,span", THIN)
