@@ -34,6 +34,12 @@ constexpr uint32_t NO_ID = 0xFFFFFFFFu;  // an unused slot of a tile (ids are be
 constexpr int PICK_READS = 8;            // neighbour reads a thread keeps in flight
 constexpr int BUCKET_K_MAX = 32;         // fanouts up to here: a thread keeps a node's picks in registers
 
+// Buckets serve up to this many ids in a batch, a load factor of 0.72 in MAX_BUCKETS tables.  Beyond that the
+// buckets are done in slices, each of which reads all of the bucket: work that grows with the square of
+// the batch, where that of the tables in HBM is linear (one batch of 4 000 seeds, fanout 10/10/10, 4.4 M ids:
+// 19.5 ms in slices, 2.1 in the tables; 2 000 seeds, 2.3 M ids: 4.5 and 1.1; 16 000 seeds: 211 and 7.9).
+constexpr int64_t BUCKET_IDS_LIMIT = 1'500'000;
+
 struct Buckets {
   uint32_t* id;          // [S][entries] a tile's ids by bucket (tile t of the nodes: from t * TILE_NODES * k on;
                          // list tiles: behind cand_slots)
@@ -47,11 +53,15 @@ struct Buckets {
 };
 
 // Buckets of a batch for a hop that starts with `n` ids in the list (all of them are the frontier): ids of
-// which BUCKET_IDS make a bucket; with few batches more and smaller ones, until the GPU's 256 CUs
+// which (hop_ids: those the batch can have after the hop) BUCKET_IDS make a bucket; with few batches more and smaller ones, until the GPU's 256 CUs
 // have two workgroups each (8 batches of 34 k candidates: 16 us with 5 buckets a batch, 7 us with 64).
+__host__ __device__ __forceinline__ int64_t hop_ids(int64_t n, int k, int64_t num_nodes) {
+  const int64_t ids = n + n * k;
+  return ids < num_nodes ? ids : num_nodes;
+}
+
 __host__ __device__ __forceinline__ int32_t bucket_count(int64_t n, int k, int64_t num_nodes, int32_t S) {
-  int64_t ids = n + n * k;
-  if (ids > num_nodes) ids = num_nodes;
+  const int64_t ids = hop_ids(n, k, num_nodes);
   int64_t p = (ids + BUCKET_IDS - 1) / BUCKET_IDS;
   const int64_t spread = (512 + S - 1) / S, fill = (ids + BUCKET_IDS_MIN - 1) / BUCKET_IDS_MIN;
   const int64_t more = spread < fill ? spread : fill;
@@ -312,7 +322,7 @@ __device__ __forceinline__ void bucket_load(const BucketOf& k, int32_t t0, const
 
 // One workgroup per (batch, bucket): insert, then look up; a bucket of the size it is meant to have
 // stays in the threads' registers in between.  Where more ids fall into a bucket than its table takes
-// (more than MAX_BUCKETS buckets' worth of ids in a batch, or ids made to collide), a search that takes
+// (ids made to collide), a search that takes
 // too long ends the attempt and the bucket is done in slices of the 32-bit space that an odd
 // multiplier spreads the ids over, half as long after every failed attempt (a slice of length one
 // holds a single id).
@@ -383,6 +393,7 @@ __global__ __launch_bounds__(BUCKET_THREADS) __attribute__((amdgpu_waves_per_eu(
       for (int32_t t0 = 0; t0 < k.tiles; t0 += BUCKET_THREADS) {
         total = bucket_shares(k, t0, sh, smem);   // (barriers inside: the table is clear)
         for (uint32_t x0 = 0; x0 < total; x0 += BUCKET_THREADS * BUCKET_ITEMS) {
+          if (*(volatile uint32_t*)&s_full) break;   // (no barrier in this loop)
           uint32_t value[BUCKET_ITEMS];
           bucket_load(k, t0, sh, total, x0, e, value);
 #pragma unroll

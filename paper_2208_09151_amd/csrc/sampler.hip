@@ -38,6 +38,7 @@
 // stages run in one workgroup per batch with the table in LDS instead (k_front_lds, further
 // down); the later hops, whose sets are far too large for one table there, go through tables in
 // LDS bucket by bucket (buckets.hpp) and share scan, emit and col with the way described above.
+#include <algorithm>
 #include <cstdlib>
 #include <cstring>
 #include <vector>
@@ -1276,7 +1277,16 @@ extern "C" int32_t ginex_sample_superbatch(
     // where the neighbour ids come over the host link: there the group of lanes that k_pick gives a
     // node reads the neighbouring ids of its row in one go, a thread per node asks for each by itself
     // (1.6 G edges, 42.7 M picks: 83 against 101 ms; 3.6 G edges: 265 against 362)
-    const bool buckets = stage >= 0 && k <= BUCKET_K_MAX && buckets_fit && lds && !over_link;
+    bool buckets = stage >= 0 && k <= BUCKET_K_MAX && buckets_fit && lds && !over_link;
+    // ... and where a batch's ids fit the buckets.  Where the bound says that they may not, the lists as they
+    // are decide (a wait of some 20 us in front of a hop of a million picks or more)
+    if (buckets && hop_ids(front, k, g->num_nodes) > BUCKET_IDS_LIMIT) {
+      std::vector<int32_t> lists(S);
+      GINEX_HIP(hipMemcpyAsync(lists.data(), nlist, sizeof(int32_t) * S, hipMemcpyDeviceToHost, st));
+      GINEX_HIP(hipStreamSynchronize(st));
+      const int64_t longest = *std::max_element(lists.begin(), lists.end());
+      buckets = hop_ids(longest, k, g->num_nodes) <= BUCKET_IDS_LIMIT;
+    }
     if (buckets) {
       if (g->nc_address_table) {
         if (g->offsets_64)

@@ -2,6 +2,7 @@
 fanouts it keeps in registers, ids that all fall into one bucket, and a workspace without room for
 buckets.  Everything is compared with the oracle element by element (tolerance zero)."""
 import ctypes as C
+import time
 
 import numpy as np
 import pytest
@@ -31,6 +32,41 @@ def test_frontiers_around_the_tile_sizes(ginex, k, offsets_64):  # noqa: F811
     rng = np.random.default_rng(k)
     batches = [rng.choice(6000, size=n, replace=False) for n in (1025, 2047, 2048, 2049, 2303, 2304, 2305, 3)]
     both(ginex, off.numpy(), ind.numpy(), batches, (k, 3))
+
+
+def wide_graph(n, degree):
+    """Every node has `degree` neighbours, drawn with repetitions."""
+    off = np.arange(n + 1, dtype=np.int64) * degree
+    return off, np.random.default_rng(degree).integers(0, n, off[-1]).astype(np.int32)
+
+
+# 1.5 M ids in a batch: the bound on either side, the bound beyond it and the lists below, both beyond
+@pytest.mark.parametrize("seeds,degree", [(12_000, 12), (12_397, 12), (13_000, 6), (13_000, 12)])
+def test_batches_around_the_most_ids_of_the_buckets(ginex, seeds, degree):  # noqa: F811
+    n = 3_000_000
+    off, ind = wide_graph(n, degree)
+    batches = [np.random.default_rng(seeds).choice(n, size=m, replace=False) for m in (5, seeds, 0)]
+    both(ginex, off, ind, batches, (10, 10))
+
+
+def test_large_batches_cost_no_more_than_the_tables(ginex, monkeypatch):  # noqa: F811
+    """A batch far beyond what the buckets hold, against the tables in HBM, best of four (in slices it
+    took nine times as long)."""
+    n = 20_000_000
+    off = torch.arange(n + 1, dtype=torch.int64, device="cuda") * 12
+    ind = torch.randint(n, (12 * n,), dtype=torch.int32, device="cuda")
+    seeds, so = torch.randperm(n, device="cuda")[:4000].int(), np.array([0, 4000])
+    best = {}
+    for lds in ("0", "1"):
+        monkeypatch.setenv("GINEX_SAMPLER_LDS", lds)
+        times = []
+        for _ in range(4):
+            torch.cuda.synchronize()
+            began = time.perf_counter()
+            ginex.sample_superbatch(off, ind, seeds, so, (10, 10, 10))
+            times.append(time.perf_counter() - began)
+        best[lds] = min(times)
+    assert best["1"] < 1.5 * best["0"], best
 
 
 # empty batches have no tiles and no buckets; alone, between others, and in front of a first hop that
