@@ -175,7 +175,8 @@ inline unsigned grid_blocks(int S, int64_t tiles_per_batch) {
 // many tiles per batch and a block strides over the tiles its batch really has.
 constexpr int64_t SLOT_TILES = 128;   // tiles of TB frontier slots
 constexpr int64_t PICK_TILES = 512;   // tiles of TB/G frontier nodes
-constexpr int64_t COPY_TILES = 64;    // blocks that copy a batch's list
+constexpr int64_t COPY_TILES = 64;    // blocks that copy a batch's list ...
+constexpr int64_t COPY_BLOCKS = 12800;   // ... and more where there are few batches (one list of 15 M ids: 0.4 ms with 64 blocks)
 
 // GINEX_SAMPLER_TILES=n in the environment replaces both caps (any n >= 1 gives the same
 // result: only the assignment of tiles to blocks, and with it the order in which candidates
@@ -1364,7 +1365,8 @@ extern "C" int32_t ginex_sample_superbatch(
   if (ids_capacity > 0) {
     // (a capped grid like the others: sized for the longest possible list it was 260 000 blocks for
     // 200 batches, nearly all of them empty)
-    hipLaunchKernelGGL(k_copy_ids, dim3((unsigned)capped(ceil_div(p.stride_ids, TB * 4), COPY_TILES), S),
+    const int64_t copy_tiles = std::max(COPY_TILES, COPY_BLOCKS / S);
+    hipLaunchKernelGGL(k_copy_ids, dim3((unsigned)capped(ceil_div(p.stride_ids, TB * 4), copy_tiles), S),
                        dim3(TB), 0, st, T, M, nlist, ids, ids_capacity);
     GINEX_LAUNCH_CHECK();
   }
