@@ -147,7 +147,9 @@ __device__ __forceinline__ bool place_candidate(const Tables& T, int b, int k, u
 // batch, and with them the batch's lists, candidates and hash table, stay in one XCD's L2
 // instead of being fetched by all eight.  (Only locality depends on the dealing order, not
 // correctness.  The table's inserts gain nothing from it: a device-scope atomic is carried
-// out on the memory side of the fabric whatever the L2 holds; the plain reads do.)
+// out on the memory side of the fabric whatever the L2 holds; the plain reads do.)  Fewer batches than
+// XCDs: their tiles are dealt to all XCDs, one of which has only an eighth of the CUs (1 000 seeds,
+// 10/10/10, 50 M nodes: one batch 667 -> 312 us, four 699 -> 486; one of 16 000 seeds 7.6 -> 1.9 ms).
 constexpr int XCDS = 8;
 
 struct Where {
@@ -159,6 +161,11 @@ __device__ __forceinline__ Where where_am_i(int S, int64_t tiles_per_batch) {
   const int64_t n = blockIdx.x;
   const int64_t m = n / XCDS;
   Where w;
+  if (S < XCDS) {
+    w.b = (int)(n % S);
+    w.tile = n / S;
+    return w;
+  }
   w.tile = m % tiles_per_batch;
   const int64_t b = (m / tiles_per_batch) * XCDS + n % XCDS;
   w.b = b < S ? (int)b : -1;
@@ -166,13 +173,14 @@ __device__ __forceinline__ Where where_am_i(int S, int64_t tiles_per_batch) {
 }
 
 inline unsigned grid_blocks(int S, int64_t tiles_per_batch) {
-  return (unsigned)(XCDS * ceil_div(S, XCDS) * tiles_per_batch);
+  return (unsigned)((S < XCDS ? S : XCDS * ceil_div(S, XCDS)) * tiles_per_batch);
 }
 
 // Launches are sized on the host for the worst case a hop allows (every node so far with a
 // full fanout of new neighbours), which is several times what a frontier really holds, and
 // a block that finds nothing to do still costs its dispatch.  So a grid holds at most this
-// many tiles per batch and a block strides over the tiles its batch really has.
+// many tiles per batch (fewer batches than XCDs: as many as that many batches would have together) and a
+// block strides over the tiles its batch really has.
 constexpr int64_t SLOT_TILES = 128;   // tiles of TB frontier slots
 constexpr int64_t PICK_TILES = 512;   // tiles of TB/G frontier nodes
 constexpr int64_t COPY_TILES = 64;    // blocks that copy a batch's list ...
@@ -181,10 +189,10 @@ constexpr int64_t COPY_BLOCKS = 12800;   // ... and more where there are few bat
 // GINEX_SAMPLER_TILES=n in the environment replaces both caps (any n >= 1 gives the same
 // result: only the assignment of tiles to blocks, and with it the order in which candidates
 // reach the hash tables, changes; the determinism tests use it).
-inline int64_t tile_cap(int64_t standard) {
+inline int64_t tile_cap(int64_t standard, int S) {
   const char* env = getenv("GINEX_SAMPLER_TILES");
   const long n = env ? atol(env) : 0;
-  return n >= 1 ? n : standard;
+  return n >= 1 ? n : S < XCDS ? standard * XCDS / S : standard;
 }
 
 inline int64_t capped(int64_t tiles, int64_t most) { return tiles < most ? tiles : most; }
@@ -797,8 +805,8 @@ int32_t check_shape(int64_t num_nodes, int32_t S, int64_t max_batch, const int32
   return GINEX_OK;
 }
 
-inline int64_t pick_tiles(int64_t front, int group) {
-  return capped(ceil_div(front, TB / group), tile_cap(PICK_TILES));
+inline int64_t pick_tiles(int64_t front, int group, int S) {
+  return capped(ceil_div(front, TB / group), tile_cap(PICK_TILES, S));
 }
 
 // ---- seeds and hop 0 in LDS ------------------------------------------------------------------
@@ -1044,17 +1052,17 @@ void launch_pick(const Tables& T, const Plan& p, const ginex_csr_t* g, const int
   const OffT* off = static_cast<const OffT*>(g->offsets);
   const int64_t front = p.stride_front[hop];
   if (k <= 16) {
-    const int64_t tpb = pick_tiles(front, 16);
+    const int64_t tpb = pick_tiles(front, 16, S);
     hipLaunchKernelGGL((k_pick<16, OffT, NC>), dim3(grid_blocks(S, tpb)), dim3(TB), 0, st, T, off,
                        g->indices, g->nc_address_table, g->nc_cache_array, nfront, k, hop, seed,
                        first_batch, S, tpb);
   } else if (k <= 32) {
-    const int64_t tpb = pick_tiles(front, 32);
+    const int64_t tpb = pick_tiles(front, 32, S);
     hipLaunchKernelGGL((k_pick<32, OffT, NC>), dim3(grid_blocks(S, tpb)), dim3(TB), 0, st, T, off,
                        g->indices, g->nc_address_table, g->nc_cache_array, nfront, k, hop, seed,
                        first_batch, S, tpb);
   } else {
-    const int64_t tpb = pick_tiles(front, 64);
+    const int64_t tpb = pick_tiles(front, 64, S);
     hipLaunchKernelGGL((k_pick<64, OffT, NC>), dim3(grid_blocks(S, tpb)), dim3(TB), 0, st, T, off,
                        g->indices, g->nc_address_table, g->nc_cache_array, nfront, k, hop, seed,
                        first_batch, S, tpb);
@@ -1069,7 +1077,7 @@ template <int K_MAX, typename OffT, typename Pos, bool NC>
 void launch_pick_tiles(const Tables& T, const Buckets& B, int64_t front, const ginex_csr_t* g,
                        const int32_t* nfront, int k, int hop, int32_t S, uint64_t seed,
                        uint32_t first_batch, hipStream_t st) {
-  const int64_t tpb = capped(ceil_div(front, TILE_NODES) + ceil_div(front, LIST_TILE), tile_cap(SLOT_TILES));
+  const int64_t tpb = capped(ceil_div(front, TILE_NODES) + ceil_div(front, LIST_TILE), tile_cap(SLOT_TILES, S));
   const int slots = TILE_NODES * k > LIST_TILE ? TILE_NODES * k : LIST_TILE;
   hipLaunchKernelGGL((k_pick_tiles<K_MAX, OffT, Pos, NC>), dim3(grid_blocks(S, tpb)), dim3(TB),
                      (sizeof(uint32_t) + sizeof(uint16_t)) * slots, st, T, B,
@@ -1271,7 +1279,7 @@ extern "C" int32_t ginex_sample_superbatch(
     const int64_t front = stage < 0 ? (max_batch > 0 ? max_batch : 1) : p.stride_front[stage];
     // in a hop the frontier is the whole list as it stands when the hop starts
     const int32_t* nfront = stage < 0 ? w.nfront : nlist;
-    const int64_t tpb = capped(ceil_div(front, TB), tile_cap(SLOT_TILES));
+    const int64_t tpb = capped(ceil_div(front, TB), tile_cap(SLOT_TILES, S));
     const dim3 grid_slots(grid_blocks(S, tpb));
     // later hops: the hash sets in the LDS of a workgroup per bucket, where the picks of a node fit a
     // thread's registers and the workspace has room (GINEX_SAMPLER_LDS=0: the tables in HBM).  Not
@@ -1304,7 +1312,7 @@ extern "C" int32_t ginex_sample_superbatch(
                                           first_batch_index, st);
       }
       GINEX_LAUNCH_CHECK();
-      const int64_t groups = capped(bucket_count(front, k, g->num_nodes, S), tile_cap(BUCKET_GROUPS));
+      const int64_t groups = capped(bucket_count(front, k, g->num_nodes, S), tile_cap(BUCKET_GROUPS, S));
       hipLaunchKernelGGL(k_bucket_dedup, dim3(grid_blocks(S, groups)), dim3(BUCKET_THREADS), 0, st, T,
                          w.buckets, nfront, k, S, groups);
       GINEX_LAUNCH_CHECK();

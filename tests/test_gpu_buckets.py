@@ -34,6 +34,18 @@ def test_frontiers_around_the_tile_sizes(ginex, k, offsets_64):  # noqa: F811
     both(ginex, off.numpy(), ind.numpy(), batches, (k, 3))
 
 
+# fewer batches than XCDs are dealt to all of them; both ways of a hop, one or several tiles to a block
+@pytest.mark.parametrize("S", [1, 2, 3, 7, 8, 9])
+@pytest.mark.parametrize("lds,tiles", [("1", "0"), ("0", "0"), ("1", "2")])
+def test_numbers_of_batches_around_the_xcds(ginex, S, lds, tiles, monkeypatch):  # noqa: F811
+    monkeypatch.setenv("GINEX_SAMPLER_LDS", lds)
+    monkeypatch.setenv("GINEX_SAMPLER_TILES", tiles)
+    off, ind = small_graph(n=6000, e=150_000)
+    rng = np.random.default_rng(S)
+    batches = [rng.choice(6000, size=int(rng.integers(1, 1500)), replace=False) for _ in range(S)]
+    both(ginex, off.numpy(), ind.numpy(), batches, (7, 5))
+
+
 def wide_graph(n, degree):
     """Every node has `degree` neighbours, drawn with repetitions."""
     off = np.arange(n + 1, dtype=np.int64) * degree
