@@ -2242,7 +2242,8 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
     longest = std::max<int64_t>(longest, ids_offsets[i + 1] - ids_offsets[i]);
 
   // both ends of every stay, the thresholds, the table
-  const int64_t windows = ceil_div(total, ENDS_WINDOW), window = ceil_div(total, windows);
+  const int64_t windows = ceil_div(total, ENDS_WINDOW);
+  const int64_t window = windows <= ENDS_WINDOWS_MAX ? ceil_div(total, windows) : total;
   for (int64_t from = 0; from < total; from += window)
     hipLaunchKernelGGL(k_stay_ends, dim3((unsigned)w.look_tiles), dim3(TB), off_lds, st, sorted, total,
                        w.d_offsets, S, last_head, held_bits, (uint32_t)from,

@@ -78,8 +78,11 @@ __device__ __forceinline__ bool in_start_state(uint32_t v, int32_t first, const 
 // Scattered words are collected in the 256 MB memory-side cache as long as the window of positions
 // [from, to) that a launch writes fits there (33 M accesses: 0.50 ms, 66 G words/s); beyond it they go
 // to memory one by one (154 M: 6.1 ms, 25 G/s).  So one launch per ENDS_WINDOW positions, each reading
-// all pairs: 154 M in 4.5 ms (windows of 80 M: 5.3, of 20 M: 4.6, of 10 M: 8.1).
+// all pairs: 154 M in 4.5 ms (windows of 80 M: 5.3, of 20 M: 4.6, of 10 M: 8.1).  That reading grows with
+// the square of the accesses, so beyond ENDS_WINDOWS_MAX windows there is one (290 M: 9 windows 11.8 ms,
+// one 12.7; 600 M: 18 windows 36.1, one 27.3; 1 000 M: 30 windows 85.2, one 46.4).
 constexpr int64_t ENDS_WINDOW = int64_t(1) << 25;
+constexpr int64_t ENDS_WINDOWS_MAX = 9;
 __global__ __launch_bounds__(TB) void k_stay_ends(const uint64_t* __restrict__ sorted, int64_t n,
                                                   const int64_t* __restrict__ off, int32_t S,
                                                   const uint64_t* __restrict__ last_head,

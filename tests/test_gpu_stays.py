@@ -14,10 +14,12 @@ from test_gpu_parity import ginex  # noqa: F401
 pytestmark = pytest.mark.gpu
 
 
-# 2^25 positions to a window: the last access of the first one, one more, two full ones and a bit
-@pytest.mark.parametrize("total", [2**25, 2**25 + 1, 2**26 + 12345])
+# 2^25 positions to a window: the last access of the first one, one more, two full ones and a bit, nine
+# and, beyond those, one for all
+@pytest.mark.parametrize("total", [2**25, 2**25 + 1, 2**26 + 12345, 9 * 2**25, 9 * 2**25 + 1])
 def test_windows_of_positions(ginex, total, monkeypatch):  # noqa: F811
-    n, S = 9_000_000, 9
+    S = 9
+    n = max(9_000_000, total // S + 1_000_000)
     gen = torch.Generator(device="cuda").manual_seed(total)
     off = np.linspace(0, total, S + 1).astype(np.int64)
     ids = torch.cat([torch.randperm(n, generator=gen, device="cuda")[:k].int() for k in np.diff(off)])
