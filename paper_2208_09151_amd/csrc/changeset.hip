@@ -2402,8 +2402,12 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
     s.tile_shift = large ? 12 : 9;
     s.tiles = ceil_div(state.cap, int64_t(1) << s.tile_shift);
     // and there four counters to a 128-byte line, on which additions queue up (0.2 G/s per line;
-    // 13 M lines: 29.9 -> 28.0 us per iteration)
-    s.cnt_shift = large ? 3 : 0;
+    // 13 M lines: 29.9 -> 28.0 us per iteration), as where most iterations change many lines, as far as
+    // there is room
+    int64_t most = 0;
+    for (int32_t t = 0; t < S; ++t) most = std::max(most, cs[t + 1] - cs[t]);
+    s.cnt_shift = large || most * DENSE_SHARE > state.cap ? 3 : 0;
+    while (s.cnt_shift > 0 && 3 * (s.tiles << s.cnt_shift) > state.words) --s.cnt_shift;
     const int64_t stride = s.tiles << s.cnt_shift;
     // flag words: evict_words, and the scratch bitmap over ids, which has room for them (cap is at
     // most num_nodes, and the arrays of the workspace are padded to 256 bytes); the counters sit in
@@ -2417,37 +2421,43 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
     s.leave_ins = leave_ins;
     s.in_ids = in_ids;
     s.out_ids = out_ids;
-    auto flag_blocks = [&](int32_t t) {
-      return t < S && cs[t + 1] > cs[t] ? std::min<int64_t>(ceil_div(cs[t + 1] - cs[t], TB), 256) : 0;
+    auto changes = [&](int32_t t) { return t < S ? cs[t + 1] - cs[t] : int64_t(0); };
+    auto flag_blocks = [&](int32_t t, bool dense) {
+      return std::min<int64_t>(ceil_div(changes(t), dense ? DENSE_ENTRIES : TB), 256);
     };
     s.next = flags[0];
     s.cnt_next = counts;
     s.next_dst = 0;
     s.next_n = cs[1];
     s.next_filled = pl.arr_cur;
-    if (cs[1] > 0)
-      hipLaunchKernelGGL(k_step_flags, dim3((unsigned)flag_blocks(0)), dim3(TB), 0, st, s);
+    if (cs[1] * DENSE_SHARE > state.cap)
+      hipLaunchKernelGGL(k_step_flags<true>, dim3((unsigned)flag_blocks(0, true)), dim3(TB), 0, st, s);
+    else if (cs[1] > 0)
+      hipLaunchKernelGGL(k_step_flags<false>, dim3((unsigned)flag_blocks(0, false)), dim3(TB), 0, st, s);
     for (int32_t t = 0; t < S; ++t) {
       s.now = flags[t & 1];
       s.next = flags[(t + 1) & 1];
       s.cnt_now = counts + (t % 3) * stride;
       s.cnt_next = counts + ((t + 1) % 3) * stride;
       s.cnt_clear = counts + ((t + 2) % 3) * stride;
-      s.emit_blocks = M > 0 ? ceil_div(s.words, large ? 256 : 64) : 0;
-      s.flag_blocks = flag_blocks(t + 1);
+      const bool dense = std::max(changes(t), changes(t + 1)) * DENSE_SHARE > state.cap;
+      const int64_t line_words = dense ? (large ? 64 : 8) : large ? 256 : 64;
+      s.emit_blocks = M > 0 ? ceil_div(s.words, line_words) : 0;
+      s.flag_blocks = flag_blocks(t + 1, dense);
       s.dst = cs[t];
-      s.n_change = cs[t + 1] - cs[t];
+      s.n_change = changes(t);
       s.next_dst = cs[t + 1];
-      s.next_n = t + 1 < S ? cs[t + 2] - cs[t + 1] : 0;
+      s.next_n = changes(t + 1);
       s.next_filled = pl.arr_cur + t + 1;
       s.ids = ids + ids_offsets[t];
       s.n = ids_offsets[t + 1] - ids_offsets[t];
       s.src_line = src_line ? src_line + ids_offsets[t] : nullptr;
-      const int64_t blocks = s.emit_blocks + s.flag_blocks + (src_line ? ceil_div(s.n, TB * 4) : 0);
-      if (blocks > 0 && large)
-        hipLaunchKernelGGL(k_step_lines<256>, dim3((unsigned)blocks), dim3(TB), 0, st, state, s);
-      else if (blocks > 0)
-        hipLaunchKernelGGL(k_step_lines<64>, dim3((unsigned)blocks), dim3(TB), 0, st, state, s);
+      const dim3 blocks((unsigned)(s.emit_blocks + s.flag_blocks + (src_line ? ceil_div(s.n, TB * 4) : 0)));
+      if (blocks.x == 0) continue;
+      if (dense && large) hipLaunchKernelGGL((k_step_lines<64, true>), blocks, dim3(TB), 0, st, state, s);
+      else if (dense) hipLaunchKernelGGL((k_step_lines<8, true>), blocks, dim3(TB), 0, st, state, s);
+      else if (large) hipLaunchKernelGGL((k_step_lines<256, false>), blocks, dim3(TB), 0, st, state, s);
+      else hipLaunchKernelGGL((k_step_lines<64, false>), blocks, dim3(TB), 0, st, state, s);
     }
     GINEX_LAUNCH_CHECK();
   }

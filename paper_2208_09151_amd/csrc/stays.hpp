@@ -1027,20 +1027,62 @@ __device__ __forceinline__ void flag_line(const Step& s, int32_t line) {
   atomicAdd(&s.cnt_next[line >> s.tile_shift << s.cnt_shift], 1u);
 }
 
+// Where an iteration changes more than a sixteenth of the lines (DENSE), additions to the counters of
+// a few hundred tiles queue up, and blocks of 4 096 lines have many rounds of evictions to go.  A block
+// takes the lines of one tile and counts in LDS first then, as far as the tiles have room there (36 k
+// lines, about 20 k changes: 51 -> 9.5 us per iteration; 1.2 M lines, 0.4 M changes: 112 -> 45).
+constexpr int DENSE_SHARE = 16;
+constexpr int DENSE_TILES = 4096;
+constexpr int64_t DENSE_ENTRIES = 2048;   // of the list of leaving lines, to a block at a time
+
+// The lines the next iteration evicts, as far as they were taken before this one; vb: block of `blocks`.
+template <bool DENSE>
+__device__ __forceinline__ void flag_leaving(const Step& s, int64_t vb, int64_t blocks, uint32_t* s_tiles) {
+  const int64_t have = *s.next_filled < s.next_n ? *s.next_filled : s.next_n;
+  const bool in_lds = DENSE && s.tiles <= DENSE_TILES;
+  if (in_lds) {
+    for (int q = threadIdx.x; q < s.tiles; q += TB) s_tiles[q] = 0;
+    __syncthreads();
+  }
+  constexpr int ITEMS = DENSE ? (int)(DENSE_ENTRIES / TB) : 1;
+  for (int64_t x0 = vb * (TB * ITEMS) + threadIdx.x; x0 < have; x0 += blocks * (TB * ITEMS)) {
+    int32_t line[ITEMS];
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) line[k] = s.leaving[s.next_dst + (x0 + k * TB < have ? x0 + k * TB : x0)];
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+      if (x0 + k * TB >= have) continue;
+      if (in_lds) {
+        atomicOr((unsigned long long*)&s.next[line[k] >> 6], 1ull << (line[k] & 63));
+        atomicAdd(&s_tiles[line[k] >> s.tile_shift], 1u);
+      } else {
+        flag_line(s, line[k]);
+      }
+    }
+  }
+  if (in_lds) {
+    __syncthreads();
+    for (int q = threadIdx.x; q < s.tiles; q += TB)
+      if (s_tiles[q]) atomicAdd(&s.cnt_next[q << s.cnt_shift], s_tiles[q]);
+  }
+}
+
 // The flagged lines in line order take the iteration's insertions (a list known up front).  Roles
 // by block: [0, emit_blocks) lists and lines, LINE_WORDS flag words each; the next flag_blocks flag
 // the lines the next iteration evicts, as far as they were taken before this iteration (the others
 // are flagged by the emit blocks themselves); the rest looks up the lines of the iteration's hits.
 // Nothing one role reads is written by another: a row that hits is not inserted by the same
 // iteration, an evicted row keeps its address-table entry (its next access, a miss, does not
-// read it), and flags and counts alternate between two and three copies.
-template <int LINE_WORDS>   // flag words (64 lines each) a block of the emit role takes
+// read it), and flags and counts alternate between two and three copies.  DENSE: a block takes the lines of
+// one tile, so that its evictions are few rounds of its threads.
+template <int LINE_WORDS, bool DENSE>   // flag words (64 lines each) a block of the emit role takes
 __global__ __launch_bounds__(TB) void k_step_lines(State st, Step s) {
-  constexpr int STEPS = LINE_WORDS == 64 ? 6 : 8;
+  constexpr int STEPS = LINE_WORDS == 8 ? 3 : LINE_WORDS == 64 ? 6 : 8;
   static_assert(1 << STEPS == LINE_WORDS && LINE_WORDS <= TB, "a word per thread, found by bisection");
   __shared__ uint32_t red[TB / WAVE], smem[TB / WAVE + 1];
   __shared__ uint64_t s_word[LINE_WORDS];
   __shared__ uint32_t s_incl[LINE_WORDS];
+  __shared__ uint32_t s_tiles[DENSE ? DENSE_TILES : 1];   // (the emit role: flags for the next iteration)
   const int64_t b = blockIdx.x;
   if (b >= s.emit_blocks + s.flag_blocks) {
     constexpr int ITEMS = 4;
@@ -1061,9 +1103,7 @@ __global__ __launch_bounds__(TB) void k_step_lines(State st, Step s) {
     return;
   }
   if (b >= s.emit_blocks) {
-    const int64_t have = *s.next_filled < s.next_n ? *s.next_filled : s.next_n;
-    for (int64_t x = (b - s.emit_blocks) * TB + threadIdx.x; x < have; x += s.flag_blocks * TB)
-      flag_line(s, s.leaving[s.next_dst + x]);
+    flag_leaving<DENSE>(s, b - s.emit_blocks, s.flag_blocks, s_tiles);
     return;
   }
   const int64_t first_word = b * LINE_WORDS;
@@ -1083,6 +1123,7 @@ __global__ __launch_bounds__(TB) void k_step_lines(State st, Step s) {
   uint32_t total;
   const uint32_t ahead = block_exclusive_scan<uint32_t, TB>(flags, smem, total);
   if (threadIdx.x < LINE_WORDS) s_incl[threadIdx.x] = ahead + flags;
+  if (DENSE && threadIdx.x < 2 * LINE_WORDS) s_tiles[threadIdx.x] = 0;   // two halves of every word
   if (total == 0) return;                          // uniform
   uint32_t counted = 0;
   for (int64_t q = threadIdx.x; q < first_tile; q += TB) counted += s.cnt_now[q << s.cnt_shift];
@@ -1105,14 +1146,30 @@ __global__ __launch_bounds__(TB) void k_step_lines(State st, Step s) {
     s.out_ids[s.dst + at] = gone;
     st.res_id[line] = comes;
     st.addr[comes] = line;
-    if (leaves == LEAVES_NEXT) flag_line(s, line);
-    else if (leaves != STAYS) s.leaving[leaves] = line;
+    if (leaves == LEAVES_NEXT) {
+      if (DENSE) atomicOr(&s_tiles[(line >> 5) - first_word * 2], 1u << (line & 31));   // a line of the block's own
+      else flag_line(s, line);
+    } else if (leaves != STAYS) {
+      s.leaving[leaves] = line;
+    }
+  }
+  if (DENSE) {
+    __syncthreads();
+    if (threadIdx.x < LINE_WORDS) {
+      const uint64_t flagged = ((uint64_t)s_tiles[2 * threadIdx.x + 1] << 32) | s_tiles[2 * threadIdx.x];
+      const int64_t tile = ((first_word + threadIdx.x) * 64) >> s.tile_shift;
+      uint32_t count = (uint32_t)__popcll(flagged);
+      if (count) atomicOr((unsigned long long*)&s.next[first_word + threadIdx.x], flagged);
+      // (a block's words are those of one tile, and fewer than a wave has lanes or as many)
+      for (int d = 1; d < LINE_WORDS; d <<= 1) count += __shfl_xor(count, d, WAVE);
+      if (threadIdx.x == 0 && count) atomicAdd(&s.cnt_next[tile << s.cnt_shift], count);
+    }
   }
 }
 
 // the lines the first iteration evicts
+template <bool DENSE>
 __global__ __launch_bounds__(TB) void k_step_flags(Step s) {
-  const int64_t have = *s.next_filled < s.next_n ? *s.next_filled : s.next_n;
-  for (int64_t x = (int64_t)blockIdx.x * TB + threadIdx.x; x < have; x += (int64_t)gridDim.x * TB)
-    flag_line(s, s.leaving[s.next_dst + x]);
+  __shared__ uint32_t s_tiles[DENSE ? DENSE_TILES : 1];
+  flag_leaving<DENSE>(s, blockIdx.x, gridDim.x, s_tiles);
 }

@@ -135,3 +135,26 @@ def test_few_rows_of_a_large_graph_cost_no_more_than_the_loop(ginex, n, S, lengt
             times.append(time.perf_counter() - began)
         best[way] = min(times)
     assert best["1"] < 1.5 * best["0"], best
+
+
+# iterations longer than the cache, so that most lines change hands every time: tiles of 512 lines, of
+# 4 096 from 2^21 lines on, more of them than are counted in LDS
+@pytest.mark.parametrize("cap,S", [(64, 9), (511, 9), (512, 9), (513, 9), (40_000, 9), (2**21 - 1, 5), (2**21, 5),
+                                   (2**24 + 1, 4)])
+def test_caches_that_turn_over(ginex, cap, S, monkeypatch):  # noqa: F811
+    n = cap * 9 // 4
+    gen = torch.Generator(device="cuda").manual_seed(cap)
+    ids = torch.cat([torch.randperm(n, generator=gen, device="cuda")[:cap * 3 // 2].int() for _ in range(S)])
+    off = np.arange(S + 1, dtype=np.int64) * (cap * 3 // 2)
+    start = torch.randperm(n, generator=gen, device="cuda")[:cap].int()
+    for run in (lambda: ginex.changeset(n, ids, off, cap),
+                lambda: ginex.changeset_resume(n, ids, off, start)):
+        monkeypatch.setenv("GINEX_STATIC_THRESHOLDS", "0")
+        want = run()
+        monkeypatch.setenv("GINEX_STATIC_THRESHOLDS", "1")
+        got = run()
+        assert np.array_equal(want.miss_count, got.miss_count)
+        assert np.array_equal(want.cs_offsets, got.cs_offsets) and want.cs_offsets[-1] > cap // 4
+        for name in ("in_ids", "out_ids", "in_positions", "src_line", "final_ids"):
+            a, b = getattr(want, name), getattr(got, name)
+            assert (a is None) == (b is None) and (a is None or torch.equal(a, b)), name
