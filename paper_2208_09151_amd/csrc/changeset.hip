@@ -2278,21 +2278,38 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
     if ((int32_t)levels.size() <= l) levels.resize(l + 1);
     levels[l].push_back(t);
   }
-  for (const auto& level : levels) jobs.insert(jobs.end(), level.begin(), level.end());
+  auto length = [&](int32_t i) { return ids_offsets[i + 1] - ids_offsets[i]; };
+  auto wide = [&](int32_t t) { return length(cuts[t].jstar) > CUT_WIDE; };
+  for (auto& level : levels) {
+    std::stable_partition(level.begin(), level.end(), wide);
+    jobs.insert(jobs.end(), level.begin(), level.end());
+  }
   int32_t* const d_jobs = reinterpret_cast<int32_t*>(w.d_ready);
   if (!jobs.empty())
     GINEX_HIP(hipMemcpyAsync(d_jobs, jobs.data(), sizeof(int32_t) * jobs.size(), hipMemcpyHostToDevice, st));
-  int64_t at = 0;
+  uint32_t* const digit_counts = reinterpret_cast<uint32_t*>(pl.arr_cand);
+  constexpr int64_t WIDE_AT_ONCE = PLAN_CAND_MAX / (CUT_DIGITS * CUT_BINS);
+  const int32_t* at = d_jobs;
   for (const auto& level : levels) {
-    int64_t blocks = 1;
+    int64_t blocks = 1, longest_bucket = 1, wides = 0;
     for (const int32_t t : level) {
-      const int32_t j = cuts[t].jstar;
-      blocks = std::max(blocks, ceil_div(ids_offsets[t + 1] - ids_offsets[t] + ids_offsets[j + 1] -
-                                             ids_offsets[j], CUT_TILE));
+      blocks = std::max(blocks, ceil_div(length(t) + length(cuts[t].jstar), CUT_TILE));
+      longest_bucket = std::max(longest_bucket, length(cuts[t].jstar));
+      wides += wide(t);
     }
-    const unsigned count = (unsigned)level.size();
-    hipLaunchKernelGGL(k_cut_members, dim3((unsigned)blocks, count), dim3(TB), 0, st, q, d_jobs + at);
-    hipLaunchKernelGGL(k_cut_decide, dim3(count), dim3(BIG), 0, st, q, d_jobs + at);
+    const int64_t count = (int64_t)level.size();
+    hipLaunchKernelGGL(k_cut_members, dim3((unsigned)blocks, (unsigned)count), dim3(TB), 0, st, q, at);
+    for (int64_t first = 0; first < wides; first += WIDE_AT_ONCE) {
+      const int64_t n = std::min(WIDE_AT_ONCE, wides - first);
+      const dim3 grid((unsigned)std::min<int64_t>(ceil_div(longest_bucket, TB * CUT_WIDE_ITEMS), 256), (unsigned)n);
+      GINEX_HIP(fill_async<uint32_t>(digit_counts, n * (CUT_DIGITS * CUT_BINS), 0u, st));
+      hipLaunchKernelGGL(k_cut_wide<0>, grid, dim3(TB), 0, st, q, at + first, digit_counts);
+      hipLaunchKernelGGL(k_cut_wide<1>, grid, dim3(TB), 0, st, q, at + first, digit_counts);
+      hipLaunchKernelGGL(k_cut_wide<2>, grid, dim3(TB), 0, st, q, at + first, digit_counts);
+      hipLaunchKernelGGL(k_cut_wide<CUT_DIGITS>, grid, dim3(TB), 0, st, q, at + first, digit_counts);
+    }
+    if (wides < count)
+      hipLaunchKernelGGL(k_cut_decide, dim3((unsigned)(count - wides)), dim3(BIG), 0, st, q, at + wides);
     GINEX_LAUNCH_CHECK();
     at += count;
   }

@@ -158,3 +158,47 @@ def test_caches_that_turn_over(ginex, cap, S, monkeypatch):  # noqa: F811
         for name in ("in_ids", "out_ids", "in_positions", "src_line", "final_ids"):
             a, b = getattr(want, name), getattr(got, name)
             assert (a is None) == (b is None) and (a is None or torch.equal(a, b)), name
+
+
+def test_buckets_of_long_iterations_are_cut_by_many_blocks(ginex, monkeypatch):  # noqa: F811
+    """Iterations on both sides of the 2^17 accesses from which a cut is decided by many blocks, alone and in
+    the same level, and more of them in a level than fit at once (a cache that is cut in the same bucket
+    distance everywhere), against the loop."""
+    n = 500_000
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    for lengths, cap in (([2**17, 2**17 + 1, 2**17 - 1, 2**17 + 5000, 60_000, 200_000] * 3, 50_000),
+                         ([2**17 + 1] * 200, 300_000), ([140_000, 300] * 30, 100_000)):
+        ids = torch.cat([torch.randperm(n, generator=gen, device="cuda")[:k].int() for k in lengths])
+        off = np.cumsum([0] + lengths).astype(np.int64)
+        start = torch.randperm(n, generator=gen, device="cuda")[:cap].int()
+        for run in (lambda: ginex.changeset(n, ids, off, cap),
+                    lambda: ginex.changeset_resume(n, ids, off, start)):
+            monkeypatch.setenv("GINEX_STATIC_THRESHOLDS", "0")
+            want = run()
+            monkeypatch.setenv("GINEX_STATIC_THRESHOLDS", "1")
+            got = run()
+            assert np.array_equal(want.miss_count, got.miss_count)
+            assert np.array_equal(want.cs_offsets, got.cs_offsets) and want.cs_offsets[-1] > 0
+            for name in ("in_ids", "out_ids", "in_positions", "src_line", "final_ids"):
+                a, b = getattr(want, name), getattr(got, name)
+                assert (a is None) == (b is None) and (a is None or torch.equal(a, b)), name
+
+
+def test_long_iterations_cost_no_more_than_the_loop(ginex, monkeypatch):  # noqa: F811
+    """A cache of half an iteration, best of four (cuts by one block and counters that queue up took 1.6
+    times as long as the loop)."""
+    n, S, length, cap = 111_000_000, 12, 2_400_000, 1_160_000
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    ids, off = thin_trace(n, S, length, n, gen)
+    start = carried_rows(n, cap, gen)
+    best = {}
+    for way in ("0", "1"):
+        monkeypatch.setenv("GINEX_STATIC_THRESHOLDS", way)
+        times = []
+        for _ in range(4):
+            torch.cuda.synchronize()
+            began = time.perf_counter()
+            ginex.changeset_resume(n, ids, off, start)
+            times.append(time.perf_counter() - began)
+        best[way] = min(times)
+    assert best["1"] < 1.25 * best["0"], best
