@@ -2317,6 +2317,26 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
   // hits, misses, insertions
   hipLaunchKernelGGL(k_stays_mark, dim3((unsigned)ceil_div(total, CUT_TILE)), dim3(TB), off_lds, st, q,
                      total, src_line, pl.ins_bits);
+  auto finish = [&]() -> int32_t {
+    if (final_ids)
+      GINEX_HIP(hipMemcpyAsync(final_ids, state.res_id, sizeof(int32_t) * state.cap,
+                               hipMemcpyDeviceToDevice, st));
+    GINEX_HIP(hipStreamSynchronize(st));
+    return GINEX_OK;
+  };
+  if (distinct == total) {
+    // no row is accessed twice (a superbatch of one iteration, for one): nothing is inserted, so the lists stay
+    // empty and the lines are those of the start state (one iteration of 15 k accesses, 2 k lines carried: 457 -> 311 us per call)
+    if (src_line) {
+      Step s{};
+      s.ids = ids;
+      s.n = total;
+      s.src_line = src_line;
+      hipLaunchKernelGGL((k_step_lines<64, false>), dim3((unsigned)ceil_div(total, TB * 4)), dim3(TB), 0, st, state, s);
+      GINEX_LAUNCH_CHECK();
+    }
+    return finish();
+  }
   uint32_t* const leave_start = reinterpret_cast<uint32_t*>(state.res_next);
   // both sets of bits in node order where the members of the cuts were: a quarter byte per access in an
   // array of four (padded to 256 bytes, so the last words have room in the smallest one too)
@@ -2478,11 +2498,7 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
     }
     GINEX_LAUNCH_CHECK();
   }
-  if (final_ids)
-    GINEX_HIP(hipMemcpyAsync(final_ids, state.res_id, sizeof(int32_t) * state.cap,
-                             hipMemcpyDeviceToDevice, st));
-  GINEX_HIP(hipStreamSynchronize(st));
-  return GINEX_OK;
+  return finish();
 }
 
 // Both replacement policies share every kernel: a policy only decides the key an access

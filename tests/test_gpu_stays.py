@@ -9,7 +9,7 @@ import torch
 
 import oracle
 
-from test_gpu_parity import ginex  # noqa: F401
+from test_gpu_parity import check_changeset, check_resumed, ginex  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -202,3 +202,18 @@ def test_long_iterations_cost_no_more_than_the_loop(ginex, monkeypatch):  # noqa
             times.append(time.perf_counter() - began)
         best[way] = min(times)
     assert best["1"] < 1.25 * best["0"], best
+
+
+# no row accessed twice: one iteration, and several disjoint ones (one of them empty)
+@pytest.mark.parametrize("sizes", [(900,), (300, 0, 300, 299)])
+@pytest.mark.parametrize("cap", [1, 64, 500, 898])
+def test_superbatches_without_a_second_access(ginex, sizes, cap):  # noqa: F811
+    n = 2000
+    rng = np.random.default_rng(cap)
+    ids = rng.permutation(n)[:sum(sizes)].astype(np.int32)
+    off = np.cumsum([0] + list(sizes)).astype(np.int64)
+    d = torch.from_numpy(ids).cuda()
+    check_changeset(ginex.changeset(n, d, off, cap), oracle.changeset(n, ids, off, cap), (n, ids, off))
+    start = rng.permutation(n)[:cap].astype(np.int32)
+    check_resumed(ginex.changeset_resume(n, d, off, torch.from_numpy(start).cuda()),
+                  oracle.changeset_resume(n, ids, off, cap, start), (n, ids, off))
