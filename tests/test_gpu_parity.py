@@ -2,6 +2,8 @@
 
 Tolerance is zero: everything on this path is integer work or byte copies.
 """
+import itertools
+
 import numpy as np
 import pytest
 import torch
@@ -923,8 +925,12 @@ def test_carried_cache_over_consecutive_superbatches(ginex, case2):
 @pytest.mark.parametrize("scatter", ["0", "1"])
 def test_both_ways_of_finding_dead_evictions_give_the_same_lists(ginex, case1, case2, scatter,
                                                                  monkeypatch):
-    """Large caches find the evicted dead rows from the id bitmap, small ones by a pass over
-    the cache lines; GINEX_DEAD_SCATTER forces either way at any size."""
+    """The loop over the cache state (more than 2 048 iterations, or GINEX_STATIC_THRESHOLDS=0) finds the
+    evicted dead rows of large caches from the id bitmap, those of small ones by a pass over the cache
+    lines; GINEX_DEAD_SCATTER forces either way at any size, GINEX_PLANNED=0 keeps carried caches that
+    hold the superbatch in the loop."""
+    monkeypatch.setenv("GINEX_STATIC_THRESHOLDS", "0")
+    monkeypatch.setenv("GINEX_PLANNED", "0")
     monkeypatch.setenv("GINEX_DEAD_SCATTER", scatter)
     rng = np.random.default_rng(61)
     for trial in range(40):
@@ -970,10 +976,10 @@ def test_changeset_at_the_largest_superbatch_the_library_accepts(ginex):
 
 @pytest.mark.parametrize("S", [1, 2, 31, 32, 33, 255, 256, 1024, 1025, 2047, 2048, 2049])
 def test_changeset_around_the_sizes_at_which_the_loop_changes_its_way(ginex, S):
-    """Iteration counts around the limits of the per-iteration bookkeeping (one, two or three
-    histogram bins per thread of the block that rolls the thresholds forward; 2 048 iterations,
-    beyond which the thresholds come from the state's histograms), under eviction pressure, for
-    Belady from a fresh and from a given cache."""
+    """Iteration counts around the limits of the per-iteration bookkeeping (one or three histogram bins
+    per thread of the block that rolls the thresholds forward; 2 048 iterations, beyond which the loop
+    over the cache state runs), under eviction pressure, for Belady from a fresh and from a given
+    cache."""
     rng = np.random.default_rng(S)
     n, cap = 700, 55
     ids, off = random_trace(rng, n, S, 9)
@@ -1008,10 +1014,11 @@ def structured_traces():
     return n, out
 
 
-@pytest.mark.parametrize("scatter", ["0", "1"])
-def test_changesets_on_structured_traces(ginex, scatter, monkeypatch):
+# the loop over the cache state with either way to find dead evictions, and changesets from the trace alone
+@pytest.mark.parametrize("static,scatter", [("0", "0"), ("0", "1"), ("1", "0")])
+def test_changesets_on_structured_traces(ginex, static, scatter, monkeypatch):
     monkeypatch.setenv("GINEX_DEAD_SCATTER", scatter)
-    monkeypatch.setenv("GINEX_STATIC_THRESHOLDS", scatter)   # both ways of finding the thresholds
+    monkeypatch.setenv("GINEX_STATIC_THRESHOLDS", static)
     n, traces = structured_traces()
     rng = np.random.default_rng(82)
     for name, tr in traces:
@@ -1299,8 +1306,9 @@ def test_seeds_and_first_hop_in_lds_equal_the_tables_in_hbm(ginex, case1, case2,
 
 
 def test_changeset_is_independent_of_the_eviction_path_and_repeatable(ginex, case2, monkeypatch):
-    """The two ways of finding evictions among dead rows use different grids and atomics; both,
-    and a second run of each, give byte-identical lists, lines and final states."""
+    """Changesets from the trace alone, the loop over the cache state with its two ways of finding evictions
+    among dead rows (different grids and atomics), and the ways of a carried cache that holds every row
+    give byte-identical lists, lines and final states."""
     c = case2
     n = c.cfg.num_nodes
     ids_d = dev(c.samp["ids"])
@@ -1309,13 +1317,13 @@ def test_changeset_is_independent_of_the_eviction_path_and_repeatable(ginex, cas
     big = len(np.unique(c.samp["ids"])) + 1000
     start = dev(np.arange(big, dtype=np.int32)[::-1].copy())
     results = []
-    for scatter, live, planned in (("0", "0", "1"), ("1", "0", "1"), ("0", "1", "1"), ("1", "1", "1"),
-                                   ("0", "0", "0"), ("1", "0", "0"), ("0", "0", "2"), ("1", "0", "2")):
+    for static, scatter, live, planned in itertools.product("01", "01", "01", "012"):
+        if static == "1" and scatter == "1":
+            continue                                    # (no loop, no scatter)
+        monkeypatch.setenv("GINEX_STATIC_THRESHOLDS", static)   # 0: the loop, 1: from the trace alone
         monkeypatch.setenv("GINEX_DEAD_SCATTER", scatter)
-        monkeypatch.setenv("GINEX_LIVE_SELECT", live)   # keeps the live-select launches in the loop
-        monkeypatch.setenv("GINEX_PLANNED", planned)    # 0: the loop also where no loop is needed
-        # the thresholds of the general loop from histograms of the state (0) or in front of it
-        monkeypatch.setenv("GINEX_STATIC_THRESHOLDS", scatter)
+        monkeypatch.setenv("GINEX_LIVE_SELECT", live)   # 1: no shortcut where the cache holds every row
+        monkeypatch.setenv("GINEX_PLANNED", planned)    # 0: as any other cache, 2: the three-launch steps
         a = ginex.changeset(n, ids_d, io, 20000)
         b = ginex.changeset_resume(n, ids_d, io, start)
         results.append((a, b))
