@@ -119,7 +119,7 @@ __device__ __forceinline__ uint32_t block_sum_u32(uint32_t v, uint32_t* red) {
 constexpr int LOOK_ITEMS = 8;
 constexpr int LOOK_TILE = TB * LOOK_ITEMS;
 
-// number of run heads (= distinct nodes) per tile of the sorted pairs
+// number of run heads (= distinct nodes) per tile of the sorted pairs, and a zero behind them
 __global__ __launch_bounds__(TB) void k_count_heads(const uint64_t* __restrict__ sorted, int64_t n,
                                                     uint32_t* __restrict__ head_tiles) {
   __shared__ uint32_t red[TB / WAVE];
@@ -145,6 +145,7 @@ __global__ __launch_bounds__(TB) void k_count_heads(const uint64_t* __restrict__
     uint32_t s = 0;
     for (int w = 0; w < TB / WAVE; ++w) s += red[w];
     head_tiles[blockIdx.x] = s;
+    if (blockIdx.x == 0) head_tiles[gridDim.x] = 0;
   }
 }
 
@@ -1449,13 +1450,14 @@ __global__ __launch_bounds__(BIG) void k_plan_scan(State st, const uint64_t* __r
   }
 }
 
-// set bits per tile of TB words
+// set bits per tile of TB words, and a zero behind them (where the scan leaves their sum)
 __global__ __launch_bounds__(TB) void k_bit_tiles(const uint32_t* __restrict__ bits, int64_t words,
                                                   uint32_t* __restrict__ tiles) {
   __shared__ uint32_t red[TB / WAVE];
   const int64_t w = (int64_t)blockIdx.x * TB + threadIdx.x;
   const uint32_t total = block_sum_u32(w < words ? (uint32_t)__popc(bits[w]) : 0u, red);
   if (threadIdx.x == 0) tiles[blockIdx.x] = total;
+  if (threadIdx.x == 0 && blockIdx.x == 0) tiles[gridDim.x] = 0;
 }
 
 // in_ids / in_positions of the whole superbatch: the set bits of ins_bits in position order
@@ -2248,7 +2250,7 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
     hipLaunchKernelGGL(k_stay_ends, dim3((unsigned)w.look_tiles), dim3(TB), off_lds, st, sorted, total,
                        w.d_offsets, S, last_head, held_bits, (uint32_t)from,
                        (uint32_t)std::min(total, from + window), ends);
-  GINEX_HIP(fill_async<uint32_t>(w.key_hists, (int64_t)S * (S + 1), 0u, st));
+  GINEX_HIP(zero_async(Zeros().add(w.key_hists, (int64_t)S * (S + 1)).add(pl.arr_cur, S + 1), st));
   hipLaunchKernelGGL(k_key_hists, dim3((unsigned)ceil_div(longest, TB * TOUCH_ITEMS), (unsigned)S),
                      dim3(TB), sizeof(uint32_t) * (S + 1), st, ends, w.d_offsets, S, w.key_hists);
   if (S < 256)
@@ -2390,7 +2392,6 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
   GINEX_HIP(hipMemcpyAsync(cs.data(), cs_offsets, sizeof(int64_t) * (S + 1), hipMemcpyDeviceToHost, st));
   hipLaunchKernelGGL(k_bit_tiles, dim3((unsigned)pl.ins_tile_count), dim3(TB), 0, st, pl.ins_bits,
                      pl.ins_words, pl.ins_tiles);
-  GINEX_HIP(fill_async<uint32_t>(pl.ins_tiles + pl.ins_tile_count, 1, 0u, st));
   GINEX_HIP(exclusive_scan_inplace<uint32_t>(pl.ins_tiles, pl.ins_tile_count + 1,
                                              pl.ins_tiles + pl.ins_tile_count + 1, st));
   GINEX_HIP(hipStreamSynchronize(st));
@@ -2422,7 +2423,6 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
       hipLaunchKernelGGL(k_stays_walk<false>, walk_grid, dim3(TB), off_lds, st, q, sorted, total,
                          state.addr, hit_words, ins_words, pl.ins_bits, pl.ins_base, leave_ins,
                          leave_start);
-    GINEX_HIP(fill_async<uint32_t>(pl.arr_cur, S + 1, 0u, st));
     const int64_t place_blocks = std::min<int64_t>(ceil_div(M + state.cap, TB * 8), 512);
     hipLaunchKernelGGL(k_leave_places, dim3((unsigned)place_blocks), dim3(TB), sizeof(uint32_t) * S, st,
                        M, state.cap, S, leave_ins, leave_start, cs_offsets, pl.arr_cur, leaving);
@@ -2451,9 +2451,7 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
     // the second scratch bitmap, one counter for 512 lines or more against one word for 32 ids
     uint64_t* flags[2] = {state.evict_words, reinterpret_cast<uint64_t*>(state.bitmap)};
     uint32_t* counts = state.bitmap_in;
-    GINEX_HIP(fill_async<uint64_t>(flags[0], s.words, 0ull, st));
-    GINEX_HIP(fill_async<uint64_t>(flags[1], s.words, 0ull, st));
-    GINEX_HIP(fill_async<uint32_t>(counts, 3 * stride, 0u, st));
+    GINEX_HIP(zero_async(Zeros().add(flags[0], s.words).add(flags[1], s.words).add(counts, 3 * stride), st));
     s.leaving = leaving;
     s.leave_ins = leave_ins;
     s.in_ids = in_ids;
@@ -2549,8 +2547,7 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
 
   GINEX_HIP(hipMemcpyAsync(w.d_offsets, ids_offsets, sizeof(int64_t) * (S + 1),
                            hipMemcpyHostToDevice, st));
-  GINEX_HIP(fill_async<int64_t>(miss_count, S, 0, st));
-  GINEX_HIP(fill_async<int64_t>(cs_offsets, S + 1, 0, st));
+  GINEX_HIP(zero_async(Zeros().add(miss_count, S).add(cs_offsets, S + 1), st));
   *init_count = start_ids ? cap : 0;
   *total_changes = 0;
   if (init_ready)
@@ -2588,7 +2585,6 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
   hipLaunchKernelGGL(k_count_heads, dim3((unsigned)w.look_tiles), dim3(TB), 0, st, sorted, total,
                      w.head_tiles);
   GINEX_LAUNCH_CHECK();
-  GINEX_HIP(fill_async<uint32_t>(w.head_tiles + w.look_tiles, 1, 0u, st));
   GINEX_HIP(exclusive_scan_inplace<uint32_t>(w.head_tiles, w.look_tiles + 1,
                                              w.head_tiles + w.look_tiles + 1, st));
   uint32_t distinct32 = 0;
@@ -2659,26 +2655,23 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
   const char* static_env = getenv("GINEX_STATIC_THRESHOLDS");
   const bool stays = !lru && S <= STATIC_S_MAX && !(static_env && static_env[0] == '0');
   const bool loop = !stays;   // (the loop still is the last way out of the planned path then)
-  GINEX_HIP(fill_async<uint32_t>(state.rhist, S + 2, 0u, st));
-  GINEX_HIP(fill_async<uint32_t>(state.bitmap, state.words, 0u, st));
-  GINEX_HIP(fill_async<uint32_t>(state.dead_bits, state.words, 0u, st));
-  GINEX_HIP(fill_async<uint32_t>(state.dead_part, state.parts, 0u, st));
-  if (loop || planned) {      // (the steps of the planned path use the fault word and the flag words)
-    GINEX_HIP(fill_async<int32_t>(state.fault, 1, 0, st));
-    if (state.dead_scatter)
-      GINEX_HIP(fill_async<uint64_t>(state.evict_words, w.evict_tiles * WAVE, 0ull, st));
-  }
-  if (loop) {
-    if (!lru && !planned) {   // the next accessed iteration of every access
-      hipLaunchKernelGGL(k_look_right, dim3((unsigned)w.look_tiles), dim3(TB), off_lds, st, sorted,
-                         total, w.d_offsets, S, w.next_iter);
-      GINEX_LAUNCH_CHECK();
+  {
+    Zeros z;
+    z.add(state.rhist, S + 2);
+    if (loop || planned) {    // (the steps of the planned path use the fault word and the flag words)
+      z.add(state.bitmap, state.words).add(state.fault, 1);
+      if (state.dead_scatter) z.add(state.evict_words, w.evict_tiles * WAVE);
     }
-    GINEX_HIP(fill_async<uint32_t>(state.ihist, S + 2, 0u, st));
-    GINEX_HIP(fill_async<uint32_t>(state.sel_part, state.parts, 0u, st));
-    GINEX_HIP(fill_async<uint32_t>(state.bitmap_in, state.words, 0u, st));
-    GINEX_HIP(fill_async<uint32_t>(state.sel_part_in, state.parts, 0u, st));
-    GINEX_HIP(fill_async<uint64_t>(state.pair, w.max_change, 0ull, st));
+    if (loop)
+      z.add(state.dead_bits, state.words).add(state.dead_part, state.parts).add(state.ihist, S + 2)
+          .add(state.sel_part, state.parts).add(state.bitmap_in, state.words)
+          .add(state.sel_part_in, state.parts).add(state.pair, w.max_change);
+    GINEX_HIP(zero_async(z, st));
+  }
+  if (loop && !lru && !planned) {   // the next accessed iteration of every access
+    hipLaunchKernelGGL(k_look_right, dim3((unsigned)w.look_tiles), dim3(TB), off_lds, st, sorted,
+                       total, w.d_offsets, S, w.next_iter);
+    GINEX_LAUNCH_CHECK();
   }
   // the loop looks every access up in the address table, and finds repeated rows of a carried state
   // there; the other ways only read entries that were written
@@ -2694,8 +2687,8 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
     if (blocks > 4096) blocks = 4096;
     if (start_ids) {
       unsigned long long bad = 0;
-      GINEX_HIP(fill_async<unsigned long long>(w.d_counts, 1, 0ull, st));
       if (for_loop) {
+        GINEX_HIP(fill_async<unsigned long long>(w.d_counts, 1, 0ull, st));
         GINEX_HIP(fill_async<int32_t>(w.first_of, num_nodes, S, st));
         hipLaunchKernelGGL(k_scatter_first, dim3((unsigned)ceil_div(distinct, TB)), dim3(TB), 0, st,
                            heads, distinct, w.first_of);
@@ -2705,8 +2698,8 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
         hipLaunchKernelGGL(k_part_count, dim3((unsigned)state.parts), dim3(TB), 0, st,
                            state.dead_bits, state.words, state.dead_part);
       } else {
-        GINEX_HIP(fill_async<uint32_t>(accessed, state.words, 0u, st));
-        GINEX_HIP(fill_async<uint64_t>(reinterpret_cast<uint64_t*>(held), state.words * 4, 0ull, st));
+        GINEX_HIP(zero_async(Zeros().add(accessed, state.words).add(reinterpret_cast<uint64_t*>(held), state.words * 4)
+                                 .add(w.d_counts, 1), st));
         hipLaunchKernelGGL(k_accessed_bits, dim3((unsigned)ceil_div(distinct, TB)), dim3(TB), 0, st, heads,
                            distinct, accessed);
         GINEX_HIP(hipMemcpyAsync(state.res_id, start_ids, sizeof(int32_t) * cap, hipMemcpyDeviceToDevice, st));
@@ -2742,9 +2735,8 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
 
   if (planned) {
     const Plan& pl = w.plan;
-    GINEX_HIP(fill_async<uint32_t>(pl.ins_bits, pl.ins_words, 0u, st));
-    GINEX_HIP(fill_async<uint32_t>(pl.arr_off, S + 2, 0u, st));
-    GINEX_HIP(fill_async<uint32_t>(pl.cand_dead, PLAN_CAND_WORDS, 0u, st));
+    GINEX_HIP(zero_async(Zeros().add(pl.ins_bits, pl.ins_words).add(pl.arr_off, S + 2)
+                             .add(pl.cand_dead, PLAN_CAND_WORDS), st));
     {
       int64_t blocks = w.look_tiles < 1024 ? w.look_tiles : 1024;
       hipLaunchKernelGGL(k_plan_heads, dim3((unsigned)blocks), dim3(TB),
@@ -2795,7 +2787,6 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
         hipLaunchKernelGGL(k_bit_tiles, dim3((unsigned)pl.ins_tile_count), dim3(TB), 0, st,
                            pl.ins_bits, pl.ins_words, pl.ins_tiles);
         GINEX_LAUNCH_CHECK();
-        GINEX_HIP(fill_async<uint32_t>(pl.ins_tiles + pl.ins_tile_count, 1, 0u, st));
         GINEX_HIP(exclusive_scan_inplace<uint32_t>(pl.ins_tiles, pl.ins_tile_count + 1,
                                                    pl.ins_tiles + pl.ins_tile_count + 1, st));
         hipLaunchKernelGGL(k_ins_emit, dim3((unsigned)pl.ins_tile_count), dim3(TB), off_lds, st,
@@ -2863,7 +2854,6 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
         hipLaunchKernelGGL(k_bit_tiles, dim3((unsigned)ctiles), dim3(TB), 0, st,
                            state.bitmap + lo_word, nwords, pl.cand_tiles);
         GINEX_LAUNCH_CHECK();
-        GINEX_HIP(fill_async<uint32_t>(pl.cand_tiles + ctiles, 1, 0u, st));
         GINEX_HIP(exclusive_scan_inplace<uint32_t>(pl.cand_tiles, ctiles + 1,
                                                    pl.cand_tiles + ctiles + 1, st));
         hipLaunchKernelGGL(k_cand_emit, dim3((unsigned)ctiles), dim3(TB), 0, st, state.bitmap,

@@ -106,4 +106,35 @@ inline hipError_t fill_async(T* p, int64_t n, T value, hipStream_t st) {
   return hipGetLastError();
 }
 
+// Several arrays cleared in one launch: calls on few ids are a chain of launches of a few microseconds
+// each (a changeset call clears up to eleven arrays).
+struct Zeros {
+  static constexpr int MOST = 12;
+  uint32_t* at[MOST];
+  int64_t words[MOST];
+  int used = 0;
+  template <typename T>
+  Zeros& add(T* p, int64_t n) {
+    static_assert(sizeof(T) % sizeof(uint32_t) == 0, "whole words");
+    at[used] = reinterpret_cast<uint32_t*>(p);
+    words[used++] = n * (int64_t)(sizeof(T) / sizeof(uint32_t));
+    return *this;
+  }
+};
+
+static __global__ void k_zero(Zeros z) {
+  const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+  for (int a = 0; a < z.used; ++a)
+    for (int64_t i = first; i < z.words[a]; i += stride) z.at[a][i] = 0;
+}
+
+inline hipError_t zero_async(const Zeros& z, hipStream_t st) {
+  int64_t longest = 0;
+  for (int a = 0; a < z.used; ++a) longest = z.words[a] > longest ? z.words[a] : longest;
+  if (longest == 0) return hipSuccess;
+  const int64_t blocks = ceil_div(longest, 256 * 8);
+  hipLaunchKernelGGL(k_zero, dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(256), 0, st, z);
+  return hipGetLastError();
+}
+
 }  // namespace ginex
