@@ -9,8 +9,8 @@
 // Part 3, the recurrence C_{i+1} = f_Belady(union(C_i, ids_i)).  For up to 2 048 iterations
 //   hits, misses, insertions and evictions follow from the trace and the start state at once,
 //   and only the lines are handed on iteration by iteration (stays.hpp; a carried cache that
-//   holds every row of the superbatch: the part "no loop" below).  For LRU, and beyond 2 048
-//   iterations, a loop over the state, serial over iterations and
+//   holds every row of the superbatch: the part "without a loop" below).  For LRU, beyond 2 048
+//   iterations, and for the smallest calls a loop over the state, serial over iterations and
 //   parallel inside one.  The cache is full from C_0 on (otherwise everything fitted and
 //   nothing ever changes), so iteration i must drop exactly as many candidates as it had
 //   misses.  Keys are (next iteration, incoming?, node id); next iterations take only
@@ -20,8 +20,8 @@
 //   members' bits in a bitmap over node ids and locating the k-th set bit through per-part
 //   counts.  Evicted lines and inserted positions are then compacted in line / position
 //   order and paired.
-//   The same loop serves the LRU policy (other keys) and a superbatch that resumes from the
-//   cache state of the previous one (C_0 given instead of computed).
+//   Both ways also serve a superbatch that resumes from the cache state of the previous one
+//   (C_0 given instead of computed); LRU has other keys.
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
@@ -479,8 +479,8 @@ __global__ __launch_bounds__(TB) void k_copy_init(const uint64_t* __restrict__ h
 
 // ---- part 3 -----------------------------------------------------------------------
 //
-// The loop over the state (LRU, more iterations than stays.hpp takes).  One iteration of the
-// recurrence is six dependent launches:
+// The loop over the state (LRU, more iterations than stays.hpp takes, the smallest calls).  One iteration of
+// the recurrence is six dependent launches:
 //   k_touch      hits get their new key, hits and misses are histogrammed by key, the line of
 //                every access (or -1) is kept for the later phases and for the executor
 //   k_threshold  one block: walks the histograms down from "never", fixes the threshold
@@ -1307,7 +1307,7 @@ __global__ __launch_bounds__(TB) void k_part_count(const uint32_t* __restrict__ 
 // read back, iterations later and a workgroup barrier apart, by the thread that evicts it.
 // What the path cannot take (more than PLAN_CAND_MAX candidates, an iteration with more than
 // PLAN_SORT_MAX insertions, S above PLAN_S_MAX, fewer rows dead from the start than
-// insertions) goes through the loop above.
+// insertions) goes the way of any other cache (stays.hpp, or the loop above).
 constexpr int PLAN_CAND_WORDS = 16384;              // LDS bitmap of the replay ...
 constexpr int PLAN_CAND_MAX = PLAN_CAND_WORDS * 32; // ... over at most 524 288 candidates
 constexpr int PLAN_SORT_MAX = 4096;      // evictions of one iteration the replay can order
@@ -1673,7 +1673,7 @@ __device__ __forceinline__ uint32_t block_prefix_one_barrier(uint32_t v, uint32_
 
 // The replay (see the head of this part).  One block.  scalars[PLAN_FAILED] is set, before the
 // state is touched, when there are more candidates than the bitmap holds, and later if an
-// invariant does not hold; the host then runs the loop instead.
+// invariant does not hold; the host then treats the cache as any other.
 // The iteration's offsets sit in LDS, and what an iteration reads from global memory at
 // addresses that do not depend on the selection (the candidates that die in it, its
 // insertions) is requested an iteration ahead, so that the chain of dependent memory accesses
@@ -2543,8 +2543,8 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
   hipStream_t st = (hipStream_t)stream;
   State& state = w.st;
   state.lru = lru ? 1 : 0;
-  // Worth a tenth launch per iteration only where a pass over the cache lines is long;
-  // GINEX_DEAD_SCATTER=0/1 overrides the choice (both ways give the same lists).
+  // The loop only (Belady beyond 2 048 iterations): worth it where a pass over the cache lines is
+  // long; GINEX_DEAD_SCATTER=0/1 overrides the choice (both ways give the same lists).
   const char* scatter_env = getenv("GINEX_DEAD_SCATTER");
   state.dead_scatter = !lru && (scatter_env ? scatter_env[0] == '1' : cap >= (int64_t(1) << 20));
   state.dead_only = 0;
@@ -2645,8 +2645,8 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
   // A carried cache with room for every row of the superbatch never evicts a row that is
   // still needed: each iteration keeps all live candidates, so the threshold bucket is
   // "never" and the select runs on the dead rows.  The changesets then follow without a loop
-  // over the state (the planned path; GINEX_PLANNED=0 switches it off); where that path does
-  // not apply, the loop runs without the two launches of the live select.
+  // over the state (the planned path; GINEX_PLANNED=0 switches it off); the loop, where it runs
+  // all the same, leaves the two launches of the live select out.
   // GINEX_LIVE_SELECT=1 keeps them in, and the planned path out.  All ways give the same lists.
   const char* live_env = getenv("GINEX_LIVE_SELECT");
   const char* plan_env = getenv("GINEX_PLANNED");
@@ -2779,12 +2779,13 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
     // GINEX_TRACE=1: one line on stderr that says which way the call went
     const char* trace_env = getenv("GINEX_TRACE");
     const bool trace = trace_env && trace_env[0] == '1';
+    const char* const otherwise = loop ? "loop" : "from the trace, as any other cache";
     if (trace)
       fprintf(stderr, "[ginex] %s: %lld insertions, at most %lld per iteration, %lld rows dead from "
               "the start, lowest possible victim %lld of %lld ids, %lld candidates: %s\n", who,
               (long long)M, (long long)sc[PLAN_MAX_N], (long long)sc[PLAN_DEAD], (long long)lo_id,
               (long long)num_nodes, (long long)sc[PLAN_CANDS],
-              !fits ? "loop" : stepped ? "stepped path" : "planned path");
+              !fits ? otherwise : stepped ? "stepped path" : "planned path");
     if (fits) {
       *total_changes = M;
       if (M > cs_capacity)
@@ -2892,9 +2893,9 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
       GINEX_HIP(hipStreamSynchronize(st));
       if (!failed[0]) return GINEX_OK;
       if (trace)
-        fprintf(stderr, "[ginex] %s: the replay gave up (reason %lld, iteration %lld), loop\n", who,
-                (long long)failed[0], (long long)failed[1]);
-      // the replay gave up, possibly after it had changed the state: start over, through the loop
+        fprintf(stderr, "[ginex] %s: the replay gave up (reason %lld, iteration %lld): %s\n", who,
+                (long long)failed[0], (long long)failed[1], otherwise);
+      // the replay gave up, possibly after it had changed the state: start over, without it
       return changeset_run(who, lru, num_nodes, ids, ids_offsets, S, cap, init_ids, init_count,
                            in_ids, out_ids, in_positions, cs_capacity, cs_offsets, miss_count,
                            src_line, total_changes, init_ready, start_ids, final_ids, ws, ws_bytes,
