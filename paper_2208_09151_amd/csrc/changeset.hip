@@ -2379,7 +2379,7 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
     else if (nv.parts <= 4 * NEVER_THREADS)
       hipLaunchKernelGGL((k_never_parts<4, 4>), dim3(1), dim3(NEVER_THREADS), 0, st, nv, S, w.cuts, idle_rows);
     else
-      hipLaunchKernelGGL((k_never_parts<16, 2>), dim3(1), dim3(NEVER_THREADS), 0, st, nv, S, w.cuts, idle_rows);
+      hipLaunchKernelGGL((k_never_parts<16, 1>), dim3(1), dim3(NEVER_THREADS), 0, st, nv, S, w.cuts, idle_rows);
     hipLaunchKernelGGL(k_never_select, dim3((unsigned)nv.parts), dim3(NEVER_THREADS), 0, st, nv, S, w.cuts);
     GINEX_LAUNCH_CHECK();
   }
