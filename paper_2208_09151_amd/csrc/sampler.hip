@@ -845,7 +845,9 @@ __device__ __forceinline__ uint32_t lds_place(unsigned long long* tab, uint32_t 
   }
 }
 
-template <int G, typename OffT, typename Pos, bool NC>
+// BY_NODE: a thread draws all picks of a node (see choose_picks; G: the most of them), else a group of G
+// lanes shares them.
+template <int G, typename OffT, typename Pos, bool NC, bool BY_NODE>
 __global__ __launch_bounds__(LDS_BLOCK) void k_front_lds(
     Tables T, const OffT* __restrict__ offsets, const int32_t* __restrict__ indices,
     const int64_t* __restrict__ nc_address_table, const int32_t* __restrict__ nc_cache_array,
@@ -902,7 +904,7 @@ __global__ __launch_bounds__(LDS_BLOCK) void k_front_lds(
     s_deg[tid] = (int32_t)(deg < 0x7FFFFFFF ? deg : 0x7FFFFFFF);
   }
   __syncthreads();
-  if constexpr (G <= BUCKET_K_MAX) {
+  if constexpr (BY_NODE) {
     // one thread per node (see choose_picks): all reads of its neighbours are in flight together
     if (tid < n0) {
       const uint32_t v = (uint32_t)list[tid];
@@ -1110,21 +1112,21 @@ template <typename OffT, bool NC>
 void launch_front(const Tables& T, const ginex_csr_t* g, const int32_t* seeds,
                   const int64_t* seed_off, int k, int32_t S, int32_t H, uint64_t seed,
                   uint32_t first_batch, const Meta& M, int32_t* nlist_seeds, uint64_t* batch_total,
-                  hipStream_t st) {
+                  bool groups, hipStream_t st) {
   const OffT* off = static_cast<const OffT*>(g->offsets);
   const bool wide = sizeof(OffT) == 8 && g->num_edges >= (int64_t(1) << 32);   // see launch_pick_tiles
-#define GINEX_FRONT(G, Pos)                                                                     \
-  hipLaunchKernelGGL((k_front_lds<G, OffT, Pos, NC>), dim3((unsigned)S), dim3(LDS_BLOCK), 0, st, T, \
-                     off, g->indices, g->nc_address_table, g->nc_cache_array, seeds, seed_off, k, \
-                     seed, first_batch, H, M, nlist_seeds, batch_total)
-  if (k > BUCKET_K_MAX || (wide && k > 16)) {   // (32 positions of 64 bits do not fit the registers)
-    GINEX_FRONT(64, uint64_t);
+#define GINEX_FRONT(G, Pos, BY_NODE)                                                            \
+  hipLaunchKernelGGL((k_front_lds<G, OffT, Pos, NC, BY_NODE>), dim3((unsigned)S), dim3(LDS_BLOCK), 0, \
+                     st, T, off, g->indices, g->nc_address_table, g->nc_cache_array, seeds, seed_off, \
+                     k, seed, first_batch, H, M, nlist_seeds, batch_total)
+  if (groups) {
+    if (k <= 16) GINEX_FRONT(16, uint32_t, false);
+    else if (k <= 32) GINEX_FRONT(32, uint32_t, false);
+    else GINEX_FRONT(64, uint32_t, false);
   } else if (wide) {
-    if constexpr (sizeof(OffT) == 8) GINEX_FRONT(16, uint64_t);
-  } else if (k <= 16) {
-    GINEX_FRONT(16, uint32_t);
+    if constexpr (sizeof(OffT) == 8) GINEX_FRONT(16, uint64_t, true);
   } else {
-    GINEX_FRONT(32, uint32_t);
+    GINEX_FRONT(16, uint32_t, true);
   }
 #undef GINEX_FRONT
 }
@@ -1239,21 +1241,29 @@ extern "C" int32_t ginex_sample_superbatch(
   const bool lds = !(lds_env && lds_env[0] == '0');
   const bool front_lds = max_batch <= LDS_BLOCK &&
                          max_batch * (1 + (int64_t)fanout[0]) <= LDS_MAX_IDS && lds;
+  const bool host_ids = in_host_memory(g->indices);
   if (front_lds) {
     const int k0 = fanout[0];
+    // a thread per node, or a group of lanes: a thread has all its reads in flight and needs no shuffles,
+    // but draws one after the other.  One batch, 1 M nodes: fanout 10, 1 000 seeds 108 against 142 us per
+    // call, 256 seeds 74 and 78, 64 seeds 69 and 67, one seed 68 and 65; fanout 5, 64 seeds 66 and 65;
+    // fanouts 25 and 32 (registers for 32 positions) 256 seeds 105 and 114 against 91 and 86.  Over the
+    // host link the group reads neighbouring ids of a row in one go (20 batches of 1 000 seeds, fanout
+    // 10: 231 against 200 us).
+    const bool groups = host_ids || k0 > 16 || max_batch <= 8 * (int64_t)k0;
     if (g->nc_address_table) {
       if (g->offsets_64)
         launch_front<int64_t, true>(T, g, seeds, w.seed_off, k0, S, H, rng_seed, first_batch_index, M,
-                                    w.nlist_b, w.batch_total, st);
+                                    w.nlist_b, w.batch_total, groups, st);
       else
         launch_front<int32_t, true>(T, g, seeds, w.seed_off, k0, S, H, rng_seed, first_batch_index, M,
-                                    w.nlist_b, w.batch_total, st);
+                                    w.nlist_b, w.batch_total, groups, st);
     } else if (g->offsets_64) {
       launch_front<int64_t, false>(T, g, seeds, w.seed_off, k0, S, H, rng_seed, first_batch_index, M,
-                                   w.nlist_b, w.batch_total, st);
+                                   w.nlist_b, w.batch_total, groups, st);
     } else {
       launch_front<int32_t, false>(T, g, seeds, w.seed_off, k0, S, H, rng_seed, first_batch_index, M,
-                                   w.nlist_b, w.batch_total, st);
+                                   w.nlist_b, w.batch_total, groups, st);
     }
     GINEX_LAUNCH_CHECK();
     // the list after the seeds (nlist_b) is the frontier of hop 0; nlist_a receives the list after hop 0
@@ -1273,7 +1283,6 @@ extern "C" int32_t ginex_sample_superbatch(
                        S, w.nfront, w.nlist_a);
     GINEX_LAUNCH_CHECK();
   }
-  const bool over_link = buckets_fit && lds && in_host_memory(g->indices);
   for (int stage = first_stage; stage < H; ++stage) {
     const int k = stage < 0 ? 1 : fanout[stage];
     const int64_t front = stage < 0 ? (max_batch > 0 ? max_batch : 1) : p.stride_front[stage];
@@ -1286,7 +1295,7 @@ extern "C" int32_t ginex_sample_superbatch(
     // where the neighbour ids come over the host link: there the group of lanes that k_pick gives a
     // node reads the neighbouring ids of its row in one go, a thread per node asks for each by itself
     // (1.6 G edges, 42.7 M picks: 83 against 101 ms; 3.6 G edges: 265 against 362)
-    bool buckets = stage >= 0 && k <= BUCKET_K_MAX && buckets_fit && lds && !over_link;
+    bool buckets = stage >= 0 && k <= BUCKET_K_MAX && buckets_fit && lds && !host_ids;
     // ... and where a batch's ids fit the buckets.  Where the bound says that they may not, the lists as they
     // are decide (a wait of some 20 us in front of a hop of a million picks or more)
     if (buckets && hop_ids(front, k, g->num_nodes) > BUCKET_IDS_LIMIT) {

@@ -162,6 +162,19 @@ def test_workspace_without_room_for_buckets(ginex):  # noqa: F811
     assert lo < need
 
 
+# the first hop in LDS: a thread per node beyond eight seeds per pick and up to fanout 16, else groups of
+# 16, 32 or 64 lanes
+@pytest.mark.parametrize("k", [1, 2, 5, 10, 16, 17, 32, 33, 64])
+@pytest.mark.parametrize("offsets_64", [False, True])
+def test_first_hop_by_node_and_by_group(ginex, k, offsets_64):  # noqa: F811
+    off, ind = small_graph(n=6000, e=150_000, offsets_64=offsets_64)
+    rng = np.random.default_rng(k)
+    most = min(1024, 12288 // (k + 1))
+    for widest in {1, min(8 * k, most), min(8 * k + 1, most), most}:
+        batches = [rng.choice(6000, size=n, replace=False) for n in (widest, 0, max(1, widest // 2))]
+        both(ginex, off.numpy(), ind.numpy(), batches, (k,))
+
+
 # neighbour ids behind the host link keep the group of lanes per node; with a neighbour cache in HBM in
 # front of them, and with the same ids in HBM, the lists are the same
 @pytest.mark.parametrize("k", [1, 16, 32])
