@@ -162,6 +162,15 @@ def test_workspace_without_room_for_buckets(ginex):  # noqa: F811
     assert lo < need
 
 
+# fanouts above 16 of up to 4 096 frontier nodes in all (bound: seeds and their picks) keep the tables
+@pytest.mark.parametrize("sizes", [(1024, 300), (1025, 3), (683, 682, 1)])
+@pytest.mark.parametrize("k", [16, 17, 32])
+def test_wide_fanouts_of_few_nodes(ginex, sizes, k):  # noqa: F811
+    off, ind = small_graph(n=6000, e=150_000)
+    rng = np.random.default_rng(k)
+    both(ginex, off.numpy(), ind.numpy(), [rng.choice(6000, size=m, replace=False) for m in sizes], (1, k, k))
+
+
 # the first hop in LDS: a thread per node beyond eight seeds per pick and up to fanout 16, else groups of
 # 16, 32 or 64 lanes
 @pytest.mark.parametrize("k", [1, 2, 5, 10, 16, 17, 32, 33, 64])
