@@ -2501,7 +2501,7 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
 
 // The smallest calls, see changeset_run.
 constexpr int32_t LOOP_S = 6;
-constexpr int64_t LOOP_IDS = 4096, LOOP_NODES = int64_t(1) << 23;
+constexpr int64_t LOOP_IDS = 4096, LOOP_NODES = int64_t(1) << 26;
 
 // Both replacement policies share every kernel: a policy only decides the key an access
 // leaves behind (Belady: its next accessed iteration; LRU: S-1-i, so that the least
@@ -2657,8 +2657,9 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
   // iterations than the table of the stays is kept for, and for the smallest calls, which are a
   // chain of launches either way: the loop has six to an iteration, the other way some 35 and one to
   // an iteration.  2 000 nodes, iterations of 300 accesses, fresh, by lines held: two iterations 335 to 305 us
-  // against 265 to 283, six 483 to 403 against 414 to 379, eight 515 to 413 against 481 to 434.  (Many
-  // nodes: the loop clears two words for each.)  GINEX_STATIC_THRESHOLDS=0/1 chooses the loop / the trace.
+  // against 265 to 283, six 483 to 403 against 414 to 379, eight 515 to 413 against 481 to 434.  Many
+  // nodes: the loop clears two words for each; two iterations of 200 accesses, carried, 66 M nodes 464 against
+  // 434, three on 111 M nodes 507 against 537.  GINEX_STATIC_THRESHOLDS=0/1 chooses the loop / the trace.
   const char* static_env = getenv("GINEX_STATIC_THRESHOLDS");
   const bool smallest = S <= LOOP_S && total <= LOOP_IDS && num_nodes <= LOOP_NODES && distinct < total;
   const bool stays = !lru && S <= STATIC_S_MAX && (static_env ? static_env[0] != '0' : !smallest);

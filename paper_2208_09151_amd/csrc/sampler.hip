@@ -1074,7 +1074,7 @@ void launch_pick(const Tables& T, const Plan& p, const ginex_csr_t* g, const int
 // Buckets are for hops whose picks a thread can keep in registers; the grid holds at most this many
 // workgroups per batch (they stride over the buckets a batch really has).
 constexpr int64_t BUCKET_GROUPS = 64;
-constexpr int64_t FEW_NODES = 4096;   // of all batches together, see ginex_sample_superbatch
+constexpr int64_t FEW_NODES = 2048, FEW_NODES_PER_PICK = 512;   // of all batches, see ginex_sample_superbatch
 
 template <int K_MAX, typename OffT, typename Pos, bool NC>
 void launch_pick_tiles(const Tables& T, const Buckets& B, int64_t front, const ginex_csr_t* g,
@@ -1299,7 +1299,7 @@ extern "C" int32_t ginex_sample_superbatch(
     // Nor for wide fanouts of few nodes, where drawing a node's picks one after the other is what the hop
     // waits for (fanout 32, four batches of 128 nodes: 152 us a call against 139, of 2 048 nodes 183 and
     // 182, of 4 000 197 and 206; fanout 25: 143 and 134, 166 and 171, 179 and 196; fanout 16: even at worst)
-    const bool few_wide = k > 16 && S * front <= FEW_NODES;
+    const bool few_wide = k > 16 && S * front <= FEW_NODES + FEW_NODES_PER_PICK * (k - 16);
     bool buckets = stage >= 0 && k <= BUCKET_K_MAX && buckets_fit && lds && !host_ids && !few_wide;
     // ... and where a batch's ids fit the buckets.  Where the bound says that they may not, the lists as they
     // are decide (a wait of some 20 us in front of a hop of a million picks or more)

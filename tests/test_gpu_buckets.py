@@ -162,8 +162,9 @@ def test_workspace_without_room_for_buckets(ginex):  # noqa: F811
     assert lo < need
 
 
-# fanouts above 16 of up to 4 096 frontier nodes in all (bound: seeds and their picks) keep the tables
-@pytest.mark.parametrize("sizes", [(1024, 300), (1025, 3), (683, 682, 1)])
+# fanouts k above 16 of up to 2 048 + 512 (k - 16) frontier nodes in all (bound: seeds and their picks)
+# keep the tables
+@pytest.mark.parametrize("sizes", [(640, 300), (641, 3), (1024, 1024, 1), (1024, 1023, 1023, 1024, 1023)])
 @pytest.mark.parametrize("k", [16, 17, 32])
 def test_wide_fanouts_of_few_nodes(ginex, sizes, k):  # noqa: F811
     off, ind = small_graph(n=6000, e=150_000)

@@ -219,24 +219,33 @@ def test_superbatches_without_a_second_access(ginex, sizes, cap):  # noqa: F811
                   oracle.changeset_resume(n, ids, off, cap, start), (n, ids, off))
 
 
-# up to six iterations of 4 096 accesses in all on up to 2^23 nodes go through the loop over the state by
+# up to six iterations of 4 096 accesses in all on up to 2^26 nodes go through the loop over the state by
 # themselves; GINEX_STATIC_THRESHOLDS chooses either way
 @pytest.mark.parametrize("n,sizes", [(3000, (900, 1000, 0, 1000, 596, 600)), (3000, (900, 1000, 1000, 597, 600)),
-                                     (3000, (300, 300, 300, 300, 300, 300, 300)), (2**23, (64, 70, 1)),
-                                     (2**23 + 1, (64, 70, 1)), (5, (3, 4))])
+                                     (3000, (300, 300, 300, 300, 300, 300, 300)), (2**26, (64, 70, 1)),
+                                     (2**26 + 1, (64, 70, 1)), (5, (3, 4))])
 def test_smallest_calls(ginex, n, sizes, monkeypatch):  # noqa: F811
     rng = np.random.default_rng(n + len(sizes))
-    pool = rng.permutation(n)[:max(sizes) * 6 // 5 + 1]
+    pool = np.unique(rng.integers(0, n, max(sizes) * 2)) if n > 10**6 else rng.permutation(n)[:max(sizes) * 6 // 5 + 1]
     ids = np.concatenate([rng.permutation(pool)[:k] for k in sizes]).astype(np.int32)
     off = np.cumsum([0] + list(sizes)).astype(np.int64)
     d = torch.from_numpy(ids).cuda()
     distinct = len(np.unique(ids))
-    for way in (None, "0", "1"):
-        monkeypatch.delenv("GINEX_STATIC_THRESHOLDS", raising=False)
-        if way:
-            monkeypatch.setenv("GINEX_STATIC_THRESHOLDS", way)
-        for cap in sorted({1, max(1, distinct // 8), distinct // 2, distinct - 1}):
-            check_changeset(ginex.changeset(n, d, off, cap), oracle.changeset(n, ids, off, cap), (n, ids, off))
-            start = rng.permutation(n)[:cap].astype(np.int32)
-            check_resumed(ginex.changeset_resume(n, d, off, torch.from_numpy(start).cuda()),
-                          oracle.changeset_resume(n, ids, off, cap, start), (n, ids, off))
+    for cap in sorted({1, max(1, distinct // 8), distinct // 2, distinct - 1}) if n < 10**6 else (distinct // 2,):
+        rows = rng.permutation(n)[:cap] if n < 10**6 else np.unique(rng.integers(0, n, 2 * cap + 50))[:cap]
+        start = torch.from_numpy(rows.astype(np.int32)).cuda()
+        made = []
+        for way in (None, "0", "1"):
+            monkeypatch.delenv("GINEX_STATIC_THRESHOLDS", raising=False)
+            if way:
+                monkeypatch.setenv("GINEX_STATIC_THRESHOLDS", way)
+            made.append((ginex.changeset(n, d, off, cap), ginex.changeset_resume(n, d, off, start)))
+        for fresh, carried in made[1:]:
+            for got, want in ((fresh, made[0][0]), (carried, made[0][1])):
+                for name in ("in_ids", "out_ids", "in_positions", "src_line"):
+                    assert torch.equal(getattr(got, name), getattr(want, name)), name
+                assert np.array_equal(got.miss_count, want.miss_count)
+        if n < 10**6:
+            check_changeset(made[0][0], oracle.changeset(n, ids, off, cap), (n, ids, off))
+            check_resumed(made[0][1], oracle.changeset_resume(n, ids, off, cap, start.cpu().numpy()),
+                          (n, ids, off))
