@@ -926,6 +926,7 @@ __global__ __launch_bounds__(NT) void k_static_roll(State st, const uint32_t* __
       c.rem = rem;
       c.T = -1;
       if (jstar == S) c.n_res = (uint32_t)s_cut[now][2];   // for k_never_parts
+      else if (rem > 0) c.T = s_cut[now][2] + rem;         // members of the bucket, for the host
       cuts[i] = c;
       miss_count[i] = drop;
     }
@@ -2281,7 +2282,7 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
     levels[l].push_back(t);
   }
   auto length = [&](int32_t i) { return ids_offsets[i + 1] - ids_offsets[i]; };
-  auto wide = [&](int32_t t) { return length(cuts[t].jstar) > CUT_WIDE; };
+  auto wide = [&](int32_t t) { return cuts[t].T > CUT_WIDE; };   // (members of its bucket, see k_static_roll)
   for (auto& level : levels) {
     std::stable_partition(level.begin(), level.end(), wide);
     jobs.insert(jobs.end(), level.begin(), level.end());
@@ -2293,17 +2294,17 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
   constexpr int64_t WIDE_AT_ONCE = PLAN_CAND_MAX / (CUT_DIGITS * CUT_BINS);
   const int32_t* at = d_jobs;
   for (const auto& level : levels) {
-    int64_t blocks = 1, longest_bucket = 1, wides = 0;
+    int64_t blocks = 1, most_members = 1, wides = 0;
     for (const int32_t t : level) {
       blocks = std::max(blocks, ceil_div(length(t) + length(cuts[t].jstar), CUT_TILE));
-      longest_bucket = std::max(longest_bucket, length(cuts[t].jstar));
+      most_members = std::max<int64_t>(most_members, cuts[t].T);
       wides += wide(t);
     }
     const int64_t count = (int64_t)level.size();
     hipLaunchKernelGGL(k_cut_members, dim3((unsigned)blocks, (unsigned)count), dim3(TB), 0, st, q, at);
     for (int64_t first = 0; first < wides; first += WIDE_AT_ONCE) {
       const int64_t n = std::min(WIDE_AT_ONCE, wides - first);
-      const dim3 grid((unsigned)std::min<int64_t>(ceil_div(longest_bucket, TB * CUT_WIDE_ITEMS), 256), (unsigned)n);
+      const dim3 grid((unsigned)std::min<int64_t>(ceil_div(most_members, TB * CUT_WIDE_ITEMS), 256), (unsigned)n);
       GINEX_HIP(fill_async<uint32_t>(digit_counts, n * (CUT_DIGITS * CUT_BINS), 0u, st));
       hipLaunchKernelGGL(k_cut_wide<0>, grid, dim3(TB), 0, st, q, at + first, digit_counts);
       hipLaunchKernelGGL(k_cut_wide<1>, grid, dim3(TB), 0, st, q, at + first, digit_counts);

@@ -37,7 +37,7 @@ struct Cut {              // one per iteration
   int32_t jstar;          // threshold bucket, S + 1: the iteration drops nothing
   int32_t rem;            // rows to drop from it
   int32_t kind;           // CUT_*
-  int32_t T;
+  int32_t T;              // (until it is decided: the bucket's members, as the thresholds have them)
   uint32_t n_res, n_in;   // members of the bucket by class, while the cut is decided;
                           // bucket "never": the part of the ids that is cut, rows that stay in it
 };
@@ -400,11 +400,12 @@ __global__ __launch_bounds__(BIG) void k_cut_decide(Stays q, const int32_t* __re
   }
 }
 
-// The same for buckets of iterations of more than CUT_WIDE accesses, by many blocks (blockIdx.y = cut): a
-// launch per digit of the ids, which finds the digits before it from the counts its predecessors
-// left, and one that marks.  One block takes 0.23 us per 1 000 accesses of the bucket's iteration (2.4 M:
-// 560 us), these launches 24 us for 150 000 accesses and 30 for 2.4 M.
-constexpr int64_t CUT_WIDE = int64_t(1) << 17;
+// The same for buckets of more than CUT_WIDE members, by many blocks (blockIdx.y = cut): a launch per
+// digit of the ids, which finds the digits before it from the counts its predecessors left, and one that
+// marks.  One block takes about 0.48 us per 1 000 members (1.2 M: 560 us), these launches 24 us for 70 000 and
+// 30 for 1.2 M.  (The members follow from the thresholds.  By the length of the bucket's iteration
+// instead, 17 levels of cuts of few members took 15 us more each.)
+constexpr int64_t CUT_WIDE = 3 << 14;
 constexpr int CUT_DIGITS = 3, CUT_BINS = 2048;         // 11 + 10 + 10 bits
 constexpr int CUT_WIDE_ITEMS = 8;
 

@@ -161,13 +161,14 @@ def test_caches_that_turn_over(ginex, cap, S, monkeypatch):  # noqa: F811
 
 
 def test_buckets_of_long_iterations_are_cut_by_many_blocks(ginex, monkeypatch):  # noqa: F811
-    """Iterations on both sides of the 2^17 accesses from which a cut is decided by many blocks, alone and in
+    """Buckets on both sides of the 49 152 members from which a cut is decided by many blocks, alone and in
     the same level, and more of them in a level than fit at once (a cache that is cut in the same bucket
     distance everywhere), against the loop."""
     n = 500_000
     gen = torch.Generator(device="cuda").manual_seed(5)
     for lengths, cap in (([2**17, 2**17 + 1, 2**17 - 1, 2**17 + 5000, 60_000, 200_000] * 3, 50_000),
-                         ([2**17 + 1] * 200, 300_000), ([140_000, 300] * 30, 100_000)):
+                         ([2**17 + 1] * 200, 300_000), ([140_000, 300] * 30, 100_000),
+                         ([70_000] * 12, 49_152), ([70_000] * 12, 49_153), ([400_000] * 8, 60_000)):
         ids = torch.cat([torch.randperm(n, generator=gen, device="cuda")[:k].int() for k in lengths])
         off = np.cumsum([0] + lengths).astype(np.int64)
         start = torch.randperm(n, generator=gen, device="cuda")[:cap].int()
