@@ -28,7 +28,9 @@ constexpr int BUCKET_THREADS = 512;
 constexpr int BUCKET_SLOTS = 4096;       // 32 KB: four workgroups of 512 threads per CU (two of twice the size: 260 instead of
                                          // 235 us per hop of 200 batches)
 constexpr int BUCKET_IDS = 2000;         // ids a bucket is meant to hold: load factor 0.49
-constexpr int BUCKET_IDS_MIN = 512;      // ... and at least, where there are few batches
+constexpr int BUCKET_IDS_MIN = 512;      // ... and at least, where there are few batches, or, on a small graph whose
+constexpr int BUCKET_ENTRIES_MIN = 1024; // ids come many times over, this many entries (one batch of 26 k entries of
+                                         // 5 000 ids: 17.0 us with 10 buckets, 8.1 with 26)
 constexpr int BUCKET_PROBES = 512;       // a longer search ends the attempt, see k_bucket_dedup
 constexpr uint32_t NO_ID = 0xFFFFFFFFu;  // an unused slot of a tile (ids are below 2^31)
 constexpr int PICK_READS = 8;            // neighbour reads a thread keeps in flight
@@ -52,9 +54,10 @@ struct Buckets {
   int64_t num_nodes;
 };
 
-// Buckets of a batch for a hop that starts with `n` ids in the list (all of them are the frontier): ids of
-// which (hop_ids: those the batch can have after the hop) BUCKET_IDS make a bucket; with few batches more and smaller ones, until the GPU's 256 CUs
-// have two workgroups each (8 batches of 34 k candidates: 16 us with 5 buckets a batch, 7 us with 64).
+// Buckets of a batch for a hop that starts with `n` ids in the list (all of them are the frontier):
+// BUCKET_IDS of the ids that the batch can have after the hop (hop_ids) make a bucket; with few batches more
+// and smaller ones, until the GPU's 256 CUs have two workgroups each (8 batches of 34 k candidates: 16 us
+// with 5 buckets a batch, 7 us with 64).
 __host__ __device__ __forceinline__ int64_t hop_ids(int64_t n, int k, int64_t num_nodes) {
   const int64_t ids = n + n * k;
   return ids < num_nodes ? ids : num_nodes;
@@ -63,7 +66,10 @@ __host__ __device__ __forceinline__ int64_t hop_ids(int64_t n, int k, int64_t nu
 __host__ __device__ __forceinline__ int32_t bucket_count(int64_t n, int k, int64_t num_nodes, int32_t S) {
   const int64_t ids = hop_ids(n, k, num_nodes);
   int64_t p = (ids + BUCKET_IDS - 1) / BUCKET_IDS;
-  const int64_t spread = (512 + S - 1) / S, fill = (ids + BUCKET_IDS_MIN - 1) / BUCKET_IDS_MIN;
+  const int64_t spread = (512 + S - 1) / S;
+  int64_t fill = (ids + BUCKET_IDS_MIN - 1) / BUCKET_IDS_MIN;
+  const int64_t by_entries = (n + n * k + BUCKET_ENTRIES_MIN - 1) / BUCKET_ENTRIES_MIN;
+  if (fill < by_entries) fill = by_entries;
   const int64_t more = spread < fill ? spread : fill;
   if (p < more) p = more;
   return (int32_t)(p < 1 ? 1 : p > MAX_BUCKETS ? MAX_BUCKETS : p);
