@@ -23,7 +23,7 @@
 // 0.83 ms to look right.  Here: k_stay_ends 0.50 ms (scattered words), k_key_hists 0.05,
 // k_static_roll 0.16, 17 levels of k_cut_members + k_cut_decide 0.020 + 0.010 each (two chains of
 // dependent reads), k_stays_mark 0.19 (random words of the table, L2), k_stays_links 0.31 (one random
-// word per pair, 106 G/s), bucket "never" 0.13, k_stays_walk 0.52, k_step_lines 200 x 8.5 us (7 us of
+// word per pair, 106 G/s), bucket "never" 0.11, k_stays_walk 0.53, k_step_lines 200 x 7.7 us (most of
 // it latency: launch, flags, counters, records, each waiting for the one before).
 #pragma once
 
@@ -528,7 +528,7 @@ __global__ __launch_bounds__(TB) void k_stays_mark(Stays q, int64_t n, int32_t* 
 // keep_t of them with the smallest ids (keep_t is known from the thresholds), so one cut follows from
 // the one before.  The ids are divided into parts; how many rows each part holds
 // after every cut needs no ids: the parts below the one that is cut keep all, the parts above lose
-// all.  One block walks the iterations over the parts' counts (k_never_parts: 0.7 us per iteration), and
+// all.  One block walks the iterations over the parts' counts (k_never_parts: 0.24 us per iteration), and
 // what id the cut falls on is then found for all parts side by side (k_never_select).  Setting bits,
 // counting, finding and clearing on one bitmap over all ids, cut after cut, took 43 us per cut.
 //
