@@ -1074,7 +1074,8 @@ void launch_pick(const Tables& T, const Plan& p, const ginex_csr_t* g, const int
 // Buckets are for hops whose picks a thread can keep in registers; the grid holds at most this many
 // workgroups per batch (they stride over the buckets a batch really has).
 constexpr int64_t BUCKET_GROUPS = 64;
-constexpr int64_t FEW_NODES = 2048, FEW_NODES_PER_PICK = 512;   // of all batches, see ginex_sample_superbatch
+// frontier nodes of all batches, see ginex_sample_superbatch
+constexpr int64_t FEW_NODES = 2048, FEW_NODES_PER_PICK = 512, FEW_NODES_SHORT_ROWS = 20000;
 
 template <int K_MAX, typename OffT, typename Pos, bool NC>
 void launch_pick_tiles(const Tables& T, const Buckets& B, int64_t front, const ginex_csr_t* g,
@@ -1297,18 +1298,22 @@ extern "C" int32_t ginex_sample_superbatch(
     // node reads the neighbouring ids of its row in one go, a thread per node asks for each by itself
     // (1.6 G edges, 42.7 M picks: 83 against 101 ms; 3.6 G edges: 265 against 362)
     // Nor for wide fanouts of few nodes, where drawing a node's picks one after the other is what the hop
-    // waits for (fanout 32, four batches of 128 nodes: 152 us a call against 139, of 2 048 nodes 183 and
-    // 182, of 4 000 197 and 206; fanout 25: 143 and 134, 166 and 171, 179 and 196; fanout 16: even at worst)
-    const bool few_wide = k > 16 && S * front <= FEW_NODES + FEW_NODES_PER_PICK * (k - 16);
-    bool buckets = stage >= 0 && k <= BUCKET_K_MAX && buckets_fit && lds && !host_ids && !few_wide;
+    // waits for (40 neighbours to a node, fanout 32, four batches of 128 nodes: 152 us a call against 139, of
+    // 2 048 nodes 183 and 182, of 4 000 197 and 206; fanout 25: 143 and 134, 166 and 171, 179 and 196;
+    // fanout 16: even at worst), the longer the fewer neighbours fill a tile's places (10 to a node, fanout
+    // 25, four batches of 2 606 nodes 194 and 165, of 5 000 189 and 179, 20 of 3 000 206 and 212).
+    const int64_t few = g->num_edges < k * g->num_nodes ? FEW_NODES_SHORT_ROWS
+                                                        : FEW_NODES + FEW_NODES_PER_PICK * (k - 16);
+    auto few_wide = [&](int64_t nodes) { return k > 16 && S * nodes <= few; };
+    bool buckets = stage >= 0 && k <= BUCKET_K_MAX && buckets_fit && lds && !host_ids && !few_wide(front);
     // ... and where a batch's ids fit the buckets.  Where the bound says that they may not, the lists as they
-    // are decide (a wait of some 20 us in front of a hop of a million picks or more)
+    // are decide (a wait of some 15 us in front of a hop of a million picks or more)
     if (buckets && hop_ids(front, k, g->num_nodes) > BUCKET_IDS_LIMIT) {
       std::vector<int32_t> lists(S);
       GINEX_HIP(hipMemcpyAsync(lists.data(), nlist, sizeof(int32_t) * S, hipMemcpyDeviceToHost, st));
       GINEX_HIP(hipStreamSynchronize(st));
       const int64_t longest = *std::max_element(lists.begin(), lists.end());
-      buckets = hop_ids(longest, k, g->num_nodes) <= BUCKET_IDS_LIMIT;
+      buckets = hop_ids(longest, k, g->num_nodes) <= BUCKET_IDS_LIMIT && !few_wide(longest);
     }
     if (buckets) {
       if (g->nc_address_table) {

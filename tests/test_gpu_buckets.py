@@ -162,12 +162,14 @@ def test_workspace_without_room_for_buckets(ginex):  # noqa: F811
     assert lo < need
 
 
-# fanouts k above 16 of up to 2 048 + 512 (k - 16) frontier nodes in all (bound: seeds and their picks)
-# keep the tables
-@pytest.mark.parametrize("sizes", [(640, 300), (641, 3), (1024, 1024, 1), (1024, 1023, 1023, 1024, 1023)])
+# fanouts k above 16 of up to 2 048 + 512 (k - 16) frontier nodes in all (bound: seeds and their picks), or
+# of 20 000 where the rows are shorter than that on the mean, keep the tables
+@pytest.mark.parametrize("sizes", [(640, 300), (641, 3), (1024, 1024, 1), (1024, 1023, 1023, 1024, 1023),
+                                   (3000, 3000, 3000, 1000), (3000, 3000, 3000, 1001)])
 @pytest.mark.parametrize("k", [16, 17, 32])
-def test_wide_fanouts_of_few_nodes(ginex, sizes, k):  # noqa: F811
-    off, ind = small_graph(n=6000, e=150_000)
+@pytest.mark.parametrize("edges", [90_000, 250_000])
+def test_wide_fanouts_of_few_nodes(ginex, sizes, k, edges):  # noqa: F811
+    off, ind = small_graph(n=6000, e=edges)
     rng = np.random.default_rng(k)
     both(ginex, off.numpy(), ind.numpy(), [rng.choice(6000, size=m, replace=False) for m in sizes], (1, k, k))
 
