@@ -2658,11 +2658,14 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
   // iterations than the table of the stays is kept for, and for the smallest calls, which are a
   // chain of launches either way: the loop has six to an iteration, the other way some 35 and one to
   // an iteration.  2 000 nodes, iterations of 300 accesses, fresh, by lines held: two iterations 335 to 305 us
-  // against 265 to 283, six 483 to 403 against 414 to 379, eight 515 to 413 against 481 to 434.  Many
+  // against 265 to 283, six 483 to 403 against 414 to 379, eight 515 to 413 against 481 to 434;
+  // 20 000 nodes, three iterations of 3 000 accesses 411 to 350 against 335 to 368, four of 2 000 463 to 361
+  // against 400 to 406.  Many
   // nodes: the loop clears two words for each; two iterations of 200 accesses, carried, 66 M nodes 464 against
   // 434, three on 111 M nodes 507 against 537.  GINEX_STATIC_THRESHOLDS=0/1 chooses the loop / the trace.
   const char* static_env = getenv("GINEX_STATIC_THRESHOLDS");
-  const bool smallest = S <= LOOP_S && total <= LOOP_IDS && num_nodes <= LOOP_NODES && distinct < total;
+  const bool smallest = S <= LOOP_S && total <= (S <= LOOP_S / 2 ? 4 * LOOP_IDS : LOOP_IDS) &&
+                        num_nodes <= LOOP_NODES && distinct < total;
   const bool stays = !lru && S <= STATIC_S_MAX && (static_env ? static_env[0] != '0' : !smallest);
   const bool loop = !stays;   // (the loop still is the last way out of the planned path then)
   {

@@ -220,11 +220,13 @@ def test_superbatches_without_a_second_access(ginex, sizes, cap):  # noqa: F811
                   oracle.changeset_resume(n, ids, off, cap, start), (n, ids, off))
 
 
-# up to six iterations of 4 096 accesses in all on up to 2^26 nodes go through the loop over the state by
+# up to six iterations of 4 096 accesses in all, or three of 16 384, on up to 2^26 nodes go through the loop over the state by
 # themselves; GINEX_STATIC_THRESHOLDS chooses either way
 @pytest.mark.parametrize("n,sizes", [(3000, (900, 1000, 0, 1000, 596, 600)), (3000, (900, 1000, 1000, 597, 600)),
                                      (3000, (300, 300, 300, 300, 300, 300, 300)), (2**26, (64, 70, 1)),
-                                     (2**26 + 1, (64, 70, 1)), (5, (3, 4))])
+                                     (2**26 + 1, (64, 70, 1)), (5, (3, 4)),
+                                     (9000, (8000, 384, 8000)), (9000, (8000, 385, 8000)),
+                                     (9000, (2000, 96, 1000, 1001))])
 def test_smallest_calls(ginex, n, sizes, monkeypatch):  # noqa: F811
     rng = np.random.default_rng(n + len(sizes))
     pool = np.unique(rng.integers(0, n, max(sizes) * 2)) if n > 10**6 else rng.permutation(n)[:max(sizes) * 6 // 5 + 1]
