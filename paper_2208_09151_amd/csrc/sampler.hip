@@ -149,8 +149,17 @@ __device__ __forceinline__ bool place_candidate(const Tables& T, int b, int k, u
 // correctness.  The table's inserts gain nothing from it: a device-scope atomic is carried
 // out on the memory side of the fabric whatever the L2 holds; the plain reads do.)  Fewer batches than
 // XCDs: their tiles are dealt to all XCDs, one of which has only an eighth of the CUs (1 000 seeds,
-// 10/10/10, 50 M nodes: one batch 667 -> 312 us, four 699 -> 486; one of 16 000 seeds 7.6 -> 1.9 ms).
+// 10/10/10, 50 M nodes: one batch 667 -> 312 us, four 699 -> 486; one of 16 000 seeds 7.6 -> 1.9 ms), but
+// not where a batch has no more tiles than an XCD has CUs: all run at once there as well, and what one
+// kernel writes the next reads from the same L2 (20 seeds, 15/10/5: 160 -> 155 us; seven batches of 100,
+// 10/10: 139 -> 134; 1 to 2 % slower at most, 100 seeds, 10/10/10).
 constexpr int XCDS = 8;
+
+constexpr int64_t XCD_TILES = 32;
+
+__host__ __device__ __forceinline__ bool over_all_xcds(int S, int64_t tiles_per_batch) {
+  return S < XCDS && tiles_per_batch > XCD_TILES;
+}
 
 struct Where {
   int b;          // batch, or -1 if the block has none
@@ -161,7 +170,7 @@ __device__ __forceinline__ Where where_am_i(int S, int64_t tiles_per_batch) {
   const int64_t n = blockIdx.x;
   const int64_t m = n / XCDS;
   Where w;
-  if (S < XCDS) {
+  if (over_all_xcds(S, tiles_per_batch)) {
     w.b = (int)(n % S);
     w.tile = n / S;
     return w;
@@ -173,7 +182,7 @@ __device__ __forceinline__ Where where_am_i(int S, int64_t tiles_per_batch) {
 }
 
 inline unsigned grid_blocks(int S, int64_t tiles_per_batch) {
-  return (unsigned)((S < XCDS ? S : XCDS * ceil_div(S, XCDS)) * tiles_per_batch);
+  return (unsigned)((over_all_xcds(S, tiles_per_batch) ? S : XCDS * ceil_div(S, XCDS)) * tiles_per_batch);
 }
 
 // Launches are sized on the host for the worst case a hop allows (every node so far with a

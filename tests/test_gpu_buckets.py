@@ -34,9 +34,10 @@ def test_frontiers_around_the_tile_sizes(ginex, k, offsets_64):  # noqa: F811
     both(ginex, off.numpy(), ind.numpy(), batches, (k, 3))
 
 
-# fewer batches than XCDs are dealt to all of them; both ways of a hop, one or several tiles to a block
+# fewer batches than XCDs are dealt to all of them, from 33 tiles of a batch on; both ways of a hop, one or
+# several tiles to a block
 @pytest.mark.parametrize("S", [1, 2, 3, 7, 8, 9])
-@pytest.mark.parametrize("lds,tiles", [("1", "0"), ("0", "0"), ("1", "2")])
+@pytest.mark.parametrize("lds,tiles", [("1", "0"), ("0", "0"), ("1", "2"), ("1", "32"), ("1", "33"), ("0", "33")])
 def test_numbers_of_batches_around_the_xcds(ginex, S, lds, tiles, monkeypatch):  # noqa: F811
     monkeypatch.setenv("GINEX_SAMPLER_LDS", lds)
     monkeypatch.setenv("GINEX_SAMPLER_TILES", tiles)
