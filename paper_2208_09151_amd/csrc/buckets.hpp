@@ -11,14 +11,20 @@
 //   k_bucket_dedup  a workgroup per bucket: inserts the bucket's share of every tile (list ids with their
 //                   position, candidates with their rank, the smallest wins), then looks every
 //                   candidate up: list position, or the rank of its id's first occurrence
-//   k_tile_firsts   a block per tile: puts the answers back into candidate order (the permutation
-//                   never leaves the tile, so nothing is scattered in memory), first-occurrence masks
-//                   and tile sums
-// and the lists and adj are emitted as after the tables in HBM.  Every access to memory but the
-// neighbour reads is a run of consecutive entries.  200 batches of 1 000 seeds, fanout 10/10/10, 111 M
-// nodes, 42.7 M picks, both later hops together: k_pick_tiles 1.03 ms (41 M line fetches, 5.1 TB/s of
-// them: bound by the neighbour reads), k_bucket_dedup 0.48 (LDS latency), k_tile_firsts 0.13; with the
-// tables in HBM k_pick 2.44, k_reinsert 0.25, k_table_clear 0.15, k_count 0.03, and 0.08 more in k_col.
+//   k_tile_firsts   a block per tile: first-occurrence masks, the picks and first occurrences in front of
+//                   every node inside its tile, tile and batch sums
+//   k_bucket_emit   a block per tile: where the batch's and the tile's output starts (sums over the batches
+//                   and tiles before it, no launch of their own), then list, rowptr and adj_col, put
+//                   into order in LDS (the permutation never leaves the tile, so nothing is scattered in
+//                   memory); in the last hop straight into the caller's ids
+// Every access to memory but the neighbour reads and the places of repeated ids is a run of consecutive
+// entries.  200 batches of 1 000 seeds, fanout 10/10/10, 111 M nodes, 42.7 M picks, both later hops together:
+// k_pick_tiles 0.95 ms (41 M line fetches: bound by the neighbour reads), k_bucket_dedup 0.47 (LDS latency),
+// k_tile_firsts 0.09, k_bucket_emit 0.27; with the tables in HBM k_pick 2.44, k_reinsert 0.25, k_table_clear 0.15,
+// k_count 0.03, k_emit 0.19, k_col 0.30, k_copy_ids 0.07.  (Answers put back into candidate order by
+// k_tile_firsts, then k_scan_batch, k_stage_offsets, k_emit and k_col as for the tables, and the lists copied
+// at the end: 0.27 more; a superbatch of 33 batches of 777 seeds, fanout 25/10, 300 -> 233 us, of 8 of 256,
+// 10/10/10, 185 -> 155, mostly launches that are gone.)
 #pragma once
 
 constexpr int TILE_NODES = TB;           // frontier nodes per tile (the tiles of k_emit and the scans)
@@ -161,7 +167,8 @@ __global__ __launch_bounds__(TB) void k_pick_tiles(Tables T, Buckets B, const Of
                                                    const int32_t* __restrict__ nc_cache_array,
                                                    const int32_t* __restrict__ nfront, int k, int hop,
                                                    uint64_t seed, uint32_t first_batch, int S,
-                                                   int64_t tpb, int slots) {
+                                                   uint64_t* __restrict__ batch_total, int64_t tpb,
+                                                   int slots) {
   extern __shared__ uint32_t s_id[];                              // [slots] ids, then [slots] ranks
   uint16_t* s_rank = reinterpret_cast<uint16_t*>(s_id + slots);
   __shared__ uint32_t s_count[MAX_BUCKETS], s_start[MAX_BUCKETS];
@@ -169,6 +176,7 @@ __global__ __launch_bounds__(TB) void k_pick_tiles(Tables T, Buckets B, const Of
   const Where here = where_am_i(S, tpb);
   if (here.b < 0) return;
   const int b = here.b;
+  if (here.tile == 0 && threadIdx.x == 0) batch_total[b] = 0;   // k_tile_firsts adds to it
   const int64_t nf = nfront[b];
   const int32_t P = bucket_count(nf, k, B.num_nodes, S);
   const int64_t node_tiles = (nf + TILE_NODES - 1) / TILE_NODES, list_tiles = (nf + LIST_TILE - 1) / LIST_TILE;
@@ -207,14 +215,12 @@ __global__ __launch_bounds__(TB) void k_pick_tiles(Tables T, Buckets B, const Of
       __syncthreads();
       // from here on by candidate: a thread's entries are TB apart, k of them at most
       const int64_t first = tile * TILE_NODES * k;
-      int32_t* cand = T.cand + b * T.cand_slots + first;
       uint32_t u[K_MAX], at[K_MAX];      // at: bucket << 16 | place among the tile's entries of the bucket
 #pragma unroll
       for (int i = 0; i < K_MAX; ++i) {
         const int x = i * TB + threadIdx.x;
         u[i] = x < n_slots ? s_id[x] : NO_ID;
         if (u[i] != NO_ID) {
-          cand[x] = (int32_t)u[i];
           const uint32_t q = __umulhi(bucket_hash(u[i]), (uint32_t)P);
           at[i] = (q << 16) | atomicAdd(&s_count[q], 1u);
         }
@@ -433,44 +439,296 @@ __global__ __launch_bounds__(BUCKET_THREADS) __attribute__((amdgpu_waves_per_eu(
   }
 }
 
-// One block per tile of frontier nodes: the answers back in candidate order (in place: a tile's
-// answers and its candidates share one stretch), masks of first occurrences, tile sums.
+// A frontier slot's word: mask of its picks that are first occurrences, first occurrences and picks of the
+// tile's slots in front of it (below 2^16: a tile has at most 256 * 32 picks).
+__device__ __forceinline__ uint64_t slot_word(uint32_t mask, uint32_t firsts, uint32_t picks) {
+  return (uint64_t)mask | (uint64_t)firsts << 32 | (uint64_t)picks << 48;
+}
+// First occurrences of the tile in front of the slot's pick.
+__device__ __forceinline__ uint32_t firsts_before(uint64_t word, uint32_t pick) {
+  return ((uint32_t)(word >> 32) & 0xFFFFu) + __popc((uint32_t)word & ((1u << pick) - 1u));
+}
+
+// rank / k for ranks of a batch's candidates: at most BUCKET_IDS_LIMIT frontier nodes and fanouts up to 32, so
+// below 2^27, where the high word of rank * ceil(2^32 / k) is exact.
+__device__ __forceinline__ uint32_t slot_of(uint32_t rank, int k, uint32_t inverse) {
+  return k == 1 ? rank : __umulhi(rank, inverse);
+}
+__device__ __forceinline__ uint32_t slot_inverse(int k) { return 0xFFFFFFFFu / (uint32_t)k + 1u; }
+
+constexpr uint32_t NEW_HERE = 0x80000000u;   // (ids and positions are below 2^31)
+constexpr int EMIT_ITEMS = 5;            // entries of a tile a thread has in flight
+
+// One block per tile of frontier nodes, see above.  Bound by reading the answers and ranks (6 bytes per pick).
 __global__ __launch_bounds__(TB) void k_tile_firsts(Tables T, Buckets B, const int32_t* __restrict__ nfront,
                                                     int k, uint64_t* __restrict__ tile_sums, int64_t tiles,
-                                                    int S, int64_t tpb) {
-  extern __shared__ uint32_t s_answer[];                          // [TILE_NODES * k]
-  __shared__ uint64_t red[TB / WAVE];
+                                                    uint64_t* __restrict__ batch_total, int S,
+                                                    int64_t tpb) {
+  __shared__ uint32_t s_mask[TILE_NODES];
+  __shared__ uint32_t smem[TB / WAVE + 1];
   const Where here = where_am_i(S, tpb);
   if (here.b < 0) return;
   const int b = here.b;
   const int64_t nf = nfront[b];
   const int32_t P = bucket_count(nf, k, B.num_nodes, S);
+  const uint32_t inverse = slot_inverse(k);
+  uint64_t sum = 0;                      // of the tiles of this block
   for (int64_t tile = here.tile; tile * TILE_NODES < nf; tile += tpb) {
-    const int64_t first = tile * TILE_NODES * k;
-    uint32_t* ref = T.ref + b * T.cand_slots + first;
+    const uint32_t first = (uint32_t)(tile * TILE_NODES * k);
+    const uint32_t* answer = T.ref + b * T.cand_slots + first;
     const uint16_t* rank = B.rank + b * B.entries + first;
     const uint32_t n = B.start[(b * B.tiles + tile) * B.row + P];
-    for (uint32_t x = threadIdx.x; x < n; x += TB) s_answer[rank[x]] = ref[x];
-    __syncthreads();
     const int64_t idx = tile * TILE_NODES + threadIdx.x;
-    uint64_t mask = 0;
-    int c = 0;
-    if (idx < nf) {
-      c = T.cnt[b * T.fr_slots + idx];
-      for (int s = 0; s < c; ++s)
-        if (s_answer[threadIdx.x * k + s] == (uint32_t)(first + threadIdx.x * k + s)) mask |= 1ull << s;
-      T.first[b * T.fr_slots + idx] = mask;
-    }
-    const int64_t nodes = nf - tile * TILE_NODES < TILE_NODES ? nf - tile * TILE_NODES : TILE_NODES;
-    for (int x = threadIdx.x; x < nodes * k; x += TB) ref[x] = s_answer[x];   // (unused slots: anything)
-    uint64_t packed = wave_reduce_sum(((uint64_t)c << 32) | (uint64_t)__popcll(mask));
-    if (lane_id() == 0) red[threadIdx.x / WAVE] = packed;
+    const uint32_t c = idx < nf ? T.cnt[b * T.fr_slots + idx] : 0u;
+    s_mask[threadIdx.x] = 0;
     __syncthreads();
-    if (threadIdx.x == 0) {
-      uint64_t sum = 0;
-      for (int w = 0; w < TB / WAVE; ++w) sum += red[w];
-      tile_sums[b * tiles + tile] = sum;
+    for (uint32_t x0 = threadIdx.x; x0 < n; x0 += TB * EMIT_ITEMS) {
+      uint32_t a[EMIT_ITEMS], r[EMIT_ITEMS];
+#pragma unroll
+      for (int i = 0; i < EMIT_ITEMS; ++i) {
+        const uint32_t x = x0 + i * TB < n ? x0 + i * TB : x0;   // (beyond the end the first one again)
+        a[i] = answer[x];
+        r[i] = rank[x];
+      }
+#pragma unroll
+      for (int i = 0; i < EMIT_ITEMS; ++i)
+        if (a[i] == first + r[i]) {      // the rank of its id's first occurrence is its own
+          const uint32_t slot = slot_of(r[i], k, inverse);
+          atomicOr(&s_mask[slot], 1u << (r[i] - slot * k));
+        }
     }
-    __syncthreads();                     // `red` and the answers are rewritten for the next tile
+    __syncthreads();
+    const uint32_t mask = s_mask[threadIdx.x];
+    uint32_t total;
+    const uint32_t ex = block_exclusive_scan<uint32_t, TB>(c << 16 | __popc(mask), smem, total);
+    if (idx < nf) T.first[b * T.fr_slots + idx] = slot_word(mask, ex & 0xFFFFu, ex >> 16);
+    const uint64_t here_sum = (uint64_t)(total >> 16) << 32 | (total & 0xFFFFu);
+    if (threadIdx.x == 0) tile_sums[b * tiles + tile] = here_sum;
+    sum += here_sum;
+  }
+  if (threadIdx.x == 0 && sum) atomicAdd((unsigned long long*)&batch_total[b], (unsigned long long)sum);
+}
+
+// What k_front_lds left of the adj of hop 0 (positions of the picks in `cand`, edges in front of every row
+// in `displaced`), still to be put at its place; nlist null: nothing.
+struct FrontAdj {
+  const int32_t* nlist;          // [S] frontier of hop 0: the seeds kept
+  const uint64_t* batch_total;   // [S] its picks and first occurrences
+  int k;
+};
+
+struct EmitTo {
+  int64_t* rowptr;
+  int64_t rowptr_capacity;
+  int32_t* col;
+  int64_t col_capacity;
+  int32_t* ids;                  // the last hop: the caller's list, else null
+  int64_t ids_capacity;
+  // where the batches' outputs start, where k_stage_offsets has laid that out, else null
+  const int64_t *row_base, *col_base;
+};
+
+// The segment of hop 0 of batch b, from block `vb` of `blocks`.
+__device__ __forceinline__ void front_adj_copy(const Tables& T, int b, int n0, int k, int64_t rb, int64_t cb,
+                                               const EmitTo& to, int64_t vb, int64_t blocks) {
+  const int32_t* pos = T.cand + (int64_t)b * T.cand_slots;
+  const uint32_t* edges = reinterpret_cast<const uint32_t*>(T.displaced + (int64_t)b * T.fr_slots);   // [n0 + 1]
+  for (int64_t r = vb * TB + threadIdx.x; r <= n0; r += blocks * TB)
+    if (rb + r < to.rowptr_capacity) to.rowptr[rb + r] = (int64_t)edges[r];
+  const int64_t ncand = (int64_t)n0 * k;
+  for (int64_t r = vb * TB + threadIdx.x; r < ncand; r += blocks * TB) {
+    const uint32_t node = (uint32_t)r / (uint32_t)k, pick = (uint32_t)r - node * (uint32_t)k;
+    const uint32_t e = edges[node];
+    if (pick < edges[node + 1] - e && cb + e + pick < to.col_capacity) to.col[cb + e + pick] = pos[r];
+  }
+}
+
+// Up to here a block adds up the totals of the batches in front of its own by itself (a launch of one block
+// for the prefix sums costs 5 us and another wait for the launch before it); beyond, k_stage_offsets.
+constexpr int EMIT_BATCHES = 1024;
+
+// ... and scans the sums of a batch's tiles; beyond, k_scan_batch (sums as long as the entries of a tile in LDS).
+constexpr int64_t EMIT_TILES = 1024;
+
+// One block per tile of frontier nodes, see above.  Bound by the reads and writes of a few tiles a block (18
+// bytes per pick, 214 us for 37 M picks: 3.1 TB/s) where there are many, by the chain of reads where there are few:
+// batch length, sums and slot words, entries, words of repeated ids.  Dynamic LDS: sums of the tiles in front of each (tiles_in_lds
+// of them), [TILE_NODES * k] positions or new ids, [TILE_NODES * k] places of the new ids.
+__global__ __launch_bounds__(TB) void k_bucket_emit(Tables T, Buckets B, Meta M, const int32_t* __restrict__ nfront,
+                                                    int32_t* __restrict__ nlist_next, int k, int hop, int H,
+                                                    const uint64_t* __restrict__ tile_sums, int64_t tiles,
+                                                    const uint64_t* __restrict__ batch_total, FrontAdj front,
+                                                    EmitTo to, int S, int64_t tpb, int tiles_in_lds) {
+  extern __shared__ uint64_t s_tile[];
+  __shared__ uint64_t smem[TB / WAVE + 1];
+  __shared__ uint64_t s_word[TILE_NODES];
+  const Where here = where_am_i(S, tpb);
+  if (here.b < 0) return;
+  const int b = here.b;
+  const uint32_t nf = (uint32_t)nfront[b];
+  const int64_t tiles_here = ((int64_t)nf + TILE_NODES - 1) / TILE_NODES;
+  const bool last = hop == H - 1;
+  uint32_t* const s_col = reinterpret_cast<uint32_t*>(s_tile + tiles_in_lds);
+  uint16_t* const s_place = reinterpret_cast<uint16_t*>(s_col + TILE_NODES * k);
+
+  // The first reads wait for nothing but the batch's length; those of the sums over batches not even for that.
+  // Sums over the batches in front (of all batches for the block that writes the totals): rows, picks,
+  // list lengths; of hop 0 if it is still to be placed (rows << 32 | picks: at most 1 024 seeds to a batch), of all
+  // and of those in front.
+  uint64_t sums[5] = {};
+  if (!to.row_base) {
+    const int limit = b ? b : S;
+    for (int q = threadIdx.x; q < S; q += TB) {
+      const uint64_t t = batch_total[q], n = (uint64_t)nfront[q];
+      uint64_t f = 0;
+      if (front.nlist) f = (uint64_t)(front.nlist[q] + 1) << 32 | front.batch_total[q] >> 32;
+      if (q < limit) {
+        sums[0] += n + 1;
+        sums[1] += t >> 32;
+        sums[2] += n + (t & 0xFFFFFFFFu);
+      }
+      sums[3] += f;
+      if (q < b) sums[4] += f;
+    }
+  }
+  const int32_t P = bucket_count(nf, k, B.num_nodes, S);
+  uint32_t n = 0;
+  uint64_t word = 0;
+  auto request = [&](int64_t tile) {      // of the tile: its picks, the words of its slots
+    const int64_t idx = tile * TILE_NODES + threadIdx.x;
+    n = tile < tiles_here ? B.start[(b * B.tiles + tile) * B.row + P] : 0u;
+    word = idx < nf ? T.first[b * T.fr_slots + idx] : 0ull;
+  };
+  request(here.tile);
+  // picks and first occurrences of the tiles in front of each tile, and of all
+  const uint64_t* const ahead_of = tiles_in_lds ? s_tile : tile_sums + b * tiles;
+  uint64_t run = 0;
+  if (tiles_in_lds)
+    for (int64_t t0 = 0; t0 < tiles_here; t0 += TB) {
+      const int64_t t = t0 + threadIdx.x;
+      uint64_t total;
+      const uint64_t ex = block_exclusive_scan<uint64_t, TB>(t < tiles_here ? tile_sums[b * tiles + t] : 0ull, smem, total);
+      if (t < tiles_here) s_tile[t] = run + ex;
+      run += total;
+    }
+  else
+    run = batch_total[b];
+  // where the batch's outputs start
+  int64_t rb, cb, ib = 0;
+  if (to.row_base) {
+    rb = to.row_base[b];
+    cb = to.col_base[b];
+    if (last) ib = M.ids_offsets[b];
+  } else {
+    __shared__ uint64_t red[TB / WAVE][5];
+#pragma unroll
+    for (int x = 0; x < 5; ++x) {
+      sums[x] = wave_reduce_sum(sums[x]);
+      if (lane_id() == 0) red[threadIdx.x / WAVE][x] = sums[x];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < 5; ++x) {
+      sums[x] = 0;
+#pragma unroll
+      for (int w = 0; w < TB / WAVE; ++w) sums[x] += red[w][x];
+    }
+    // what the hops before took: hop 0 follows from its sums, later ones left it in the next segment's entry
+    const int64_t row_run = front.nlist ? (int64_t)(sums[3] >> 32) : hop == 0 ? 0 : M.row_off[(int64_t)hop * S];
+    const int64_t col_run = front.nlist ? (int64_t)(sums[3] & 0xFFFFFFFFu) : hop == 0 ? 0 : M.col_off[(int64_t)hop * S];
+    rb = row_run + (b ? (int64_t)sums[0] : 0);
+    cb = col_run + (b ? (int64_t)sums[1] : 0);
+    ib = b ? (int64_t)sums[2] : 0;
+    const int64_t rb0 = (int64_t)(sums[4] >> 32), cb0 = (int64_t)(sums[4] & 0xFFFFFFFFu);
+    if (here.tile == 0 && threadIdx.x == 0) {
+      const int32_t grown = (int32_t)(nf + (uint32_t)run);
+      nlist_next[b] = grown;
+      M.hop_sizes[(int64_t)b * (H + 1) + hop + 1] = grown;
+      if (b > 0 || hop == 0 || front.nlist) {       // (else: the entry read above)
+        M.row_off[(int64_t)hop * S + b] = rb;
+        M.col_off[(int64_t)hop * S + b] = cb;
+      }
+      if (front.nlist) {
+        M.row_off[b] = rb0;
+        M.col_off[b] = cb0;
+      }
+      if (last) M.ids_offsets[b] = ib;
+      if (b == 0) {
+        M.row_off[(int64_t)(hop + 1) * S] = M.totals[1] = row_run + (int64_t)sums[0];
+        M.col_off[(int64_t)(hop + 1) * S] = M.totals[2] = col_run + (int64_t)sums[1];
+        if (last) M.ids_offsets[S] = M.totals[0] = (int64_t)sums[2];
+      }
+    }
+    if (front.nlist && to.rowptr)
+      front_adj_copy(T, b, front.nlist[b], front.k, rb0, cb0, to, here.tile, tpb);
+  }
+  int32_t* const list = T.wlist + b * T.stride_ids;
+  // (the last hop: the list moves to its place as a whole, the others append to it)
+  int32_t* const grow = last ? to.ids + ib : list;
+  const int64_t room = last ? to.ids_capacity - ib : T.stride_ids;
+  if (last)
+    for (int64_t j = here.tile * TB + threadIdx.x; j < nf && j < room; j += tpb * TB) grow[j] = list[j];
+  if (nf == 0 && here.tile == 0 && threadIdx.x == 0 && to.rowptr && rb < to.rowptr_capacity)
+    to.rowptr[rb] = 0;                              // an empty frontier still has a rowptr entry
+  const uint32_t inverse = slot_inverse(k);
+  for (int64_t tile = here.tile; tile < tiles_here; tile += tpb) {
+    const int64_t idx = tile * TILE_NODES + threadIdx.x;
+    const uint32_t first = (uint32_t)(tile * TILE_NODES * k);
+    const uint32_t* answer = T.ref + b * T.cand_slots + first;
+    const uint16_t* rank = B.rank + b * B.entries + first;
+    const uint32_t* id = B.id + b * B.entries + first;
+    __syncthreads();                                // the sums are complete; the tile before is stored
+    s_word[threadIdx.x] = word;
+    const uint64_t ahead = ahead_of[tile];
+    const int64_t edges_ahead = (int64_t)(ahead >> 32);
+    const uint32_t new_at = nf + (uint32_t)ahead;   // list position of the tile's first new id
+    if (to.rowptr) {
+      if (idx < nf && rb + idx < to.rowptr_capacity) to.rowptr[rb + idx] = edges_ahead + (int64_t)(word >> 48);
+      if (idx == (int64_t)nf - 1 && rb + nf < to.rowptr_capacity) to.rowptr[rb + nf] = (int64_t)(run >> 32);
+    }
+    __syncthreads();
+    for (uint32_t x0 = threadIdx.x; x0 < n; x0 += TB * EMIT_ITEMS) {
+      uint32_t a[EMIT_ITEMS], r[EMIT_ITEMS], u[EMIT_ITEMS];
+      uint64_t w2[EMIT_ITEMS];
+#pragma unroll
+      for (int i = 0; i < EMIT_ITEMS; ++i) {
+        const uint32_t x = x0 + i * TB < n ? x0 + i * TB : x0;
+        a[i] = answer[x];
+        r[i] = rank[x];
+        u[i] = id[x];
+      }
+#pragma unroll
+      for (int i = 0; i < EMIT_ITEMS; ++i)          // the slot of the first occurrence, where that is another pick
+        w2[i] = !(a[i] & OLD_ID) && a[i] != first + r[i] ? T.first[b * T.fr_slots + slot_of(a[i], k, inverse)] : 0ull;
+#pragma unroll
+      for (int i = 0; i < EMIT_ITEMS; ++i) {
+        if (x0 + i * TB >= n) continue;
+        const uint32_t slot = slot_of(r[i], k, inverse), pick = r[i] - slot * k;
+        const uint64_t w = s_word[slot];
+        uint32_t pos;
+        if (a[i] & OLD_ID) {
+          pos = a[i] & ~OLD_ID;
+        } else if (a[i] == first + r[i]) {
+          pos = u[i] | NEW_HERE;
+          s_place[(uint32_t)(w >> 48) + pick] = (uint16_t)firsts_before(w, pick);
+        } else {
+          const uint32_t slot2 = slot_of(a[i], k, inverse);
+          pos = nf + (uint32_t)ahead_of[slot2 / TILE_NODES] + firsts_before(w2[i], a[i] - slot2 * k);
+        }
+        s_col[(uint32_t)(w >> 48) + pick] = pos;
+      }
+    }
+    const uint32_t entries = n;
+    if (tile + tpb < tiles_here) request(tile + tpb);
+    __syncthreads();
+    for (uint32_t e = threadIdx.x; e < entries; e += TB) {
+      uint32_t pos = s_col[e];
+      if (pos & NEW_HERE) {
+        const uint32_t u = pos & ~NEW_HERE;
+        pos = new_at + s_place[e];
+        if ((int64_t)pos < room) grow[pos] = (int32_t)u;
+      }
+      if (to.col && cb + edges_ahead + e < to.col_capacity) to.col[cb + edges_ahead + e] = (int32_t)pos;
+    }
   }
 }

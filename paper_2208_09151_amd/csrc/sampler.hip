@@ -37,7 +37,7 @@
 // buckets.  Where the hash set of a batch's seeds and first hop fits LDS (the usual case), those two
 // stages run in one workgroup per batch with the table in LDS instead (k_front_lds, further
 // down); the later hops, whose sets are far too large for one table there, go through tables in
-// LDS bucket by bucket (buckets.hpp) and share scan, emit and col with the way described above.
+// LDS bucket by bucket (buckets.hpp), with a count and an emit of their own.
 #include <algorithm>
 #include <cstdlib>
 #include <cstring>
@@ -332,6 +332,14 @@ __device__ __forceinline__ void group_choose(uint32_t v, int64_t deg, int k, int
   }
 }
 
+struct Meta {            // device mirror of the small host outputs
+  int64_t* ids_offsets;  // [S+1]
+  int64_t* hop_sizes;    // [S*(H+1)]
+  int64_t* row_off;      // [S*H+1]
+  int64_t* col_off;      // [S*H+1]
+  int64_t* totals;       // [0] ids, [1] rowptr entries, [2] col entries
+};
+
 #include "buckets.hpp"
 
 template <int G, typename OffT, bool NC>
@@ -431,14 +439,6 @@ __global__ __launch_bounds__(TB) void k_scan_batch(uint64_t* __restrict__ tile_s
   if (threadIdx.x == 0) batch_total[b] = carry;
 }
 
-struct Meta {            // device mirror of the small host outputs
-  int64_t* ids_offsets;  // [S+1]
-  int64_t* hop_sizes;    // [S*(H+1)]
-  int64_t* row_off;      // [S*H+1]
-  int64_t* col_off;      // [S*H+1]
-  int64_t* totals;       // [0] ids, [1] rowptr entries, [2] col entries
-};
-
 // Single block: per-batch output bases of the stage, new list lengths, running totals.
 // stage < 0 is the seed stage.
 __global__ __launch_bounds__(TB) void k_stage_offsets(
@@ -477,12 +477,8 @@ __global__ __launch_bounds__(TB) void k_stage_offsets(
       M.totals[1] = 0;
       M.totals[2] = 0;
     } else {
-      M.totals[1] = row_run;
-      M.totals[2] = col_run;
-      if (stage == H - 1) {
-        M.row_off[(int64_t)S * H] = row_run;
-        M.col_off[(int64_t)S * H] = col_run;
-      }
+      M.totals[1] = M.row_off[(int64_t)(stage + 1) * S] = row_run;   // (where the next hop starts, or the end)
+      M.totals[2] = M.col_off[(int64_t)(stage + 1) * S] = col_run;
     }
   }
 }
@@ -563,8 +559,6 @@ __global__ __launch_bounds__(TB) void k_emit(Tables T, const int32_t* __restrict
 // An id of an earlier stage carries its list position in its reference; an id that is new in
 // this stage is looked up through its slot, whose final value is PEND + the rank of the id's
 // first occurrence, whose entry in `cand` now holds the position.
-// BUCKETS: after k_bucket_dedup the reference is that rank itself.
-template <bool BUCKETS>
 __global__ __launch_bounds__(TB) void k_col(Tables T, const int32_t* __restrict__ nfront, int k,
                                             const int64_t* __restrict__ rowptr,
                                             int64_t rowptr_capacity,
@@ -580,7 +574,7 @@ __global__ __launch_bounds__(TB) void k_col(Tables T, const int32_t* __restrict_
   if (here.b < 0) return;
   const int b = here.b;
   const int nf = nfront[b];
-  const uint64_t* t = BUCKETS ? nullptr : T.tab + T.tab_off[b];
+  const uint64_t* t = T.tab + T.tab_off[b];
   const int32_t* cand_b = T.cand + b * T.cand_slots;
   for (int64_t tile = here.tile; tile * TB < nf; tile += tpb) {
     const int64_t idx = tile * TB + threadIdx.x;
@@ -610,7 +604,7 @@ __global__ __launch_bounds__(TB) void k_col(Tables T, const int32_t* __restrict_
           if (d < col_capacity) {
             const uint32_t where = ref[r];
             col[d] = where & OLD_ID ? (int32_t)(where & ~OLD_ID)
-                                    : cand_b[BUCKETS ? where : (uint32_t)t[where] - PEND];
+                                    : cand_b[(uint32_t)t[where] - PEND];
           }
         }
       }
@@ -834,11 +828,11 @@ constexpr int LDS_BLOCK = 1024;        // threads, and the most seeds a batch ma
 constexpr int LDS_MAX_IDS = 12288;     // seeds + candidates of hop 0: load factor 0.75 at most
 
 __device__ __forceinline__ uint32_t lds_place(unsigned long long* tab, uint32_t id, uint32_t value,
-                                              uint32_t& old_value) {
+                                              uint32_t& old_value, uint32_t slots = LDS_SLOTS) {
   // Inserts (id, value) unless the id is there; returns the slot; old_value = what the slot
   // held for this id before (all ones if the id was new).  A present id keeps the smaller value.
   const unsigned long long mine = ((unsigned long long)id << 32) | value;
-  uint32_t h = hash_slot(id, LDS_SLOTS);
+  uint32_t h = hash_slot(id, slots);
   while (true) {
     const unsigned long long old = atomicCAS(&tab[h], FREE_SLOT, mine);
     if (old == FREE_SLOT) {
@@ -850,9 +844,19 @@ __device__ __forceinline__ uint32_t lds_place(unsigned long long* tab, uint32_t 
       if (old_value >= PEND && old_value > value) atomicMin(&tab[h], mine);
       return h;
     }
-    h = h + 1 == LDS_SLOTS ? 0 : h + 1;
+    h = h + 1 == slots ? 0 : h + 1;
   }
 }
+
+// Where the seeds of every batch start: in the launch's arguments, as far as they have room (a copy of a few
+// words to the device takes 8 to 10 us, with nothing else to do in between), else in memory.
+constexpr int SEED_OFFSETS = 256;
+
+struct SeedOffsets {
+  const int64_t* far;                    // [S + 1], null: near
+  int32_t near[SEED_OFFSETS + 1];
+  __device__ __forceinline__ int64_t operator[](int b) const { return far ? far[b] : near[b]; }
+};
 
 // BY_NODE: a thread draws all picks of a node (see choose_picks; G: the most of them), else a group of G
 // lanes shares them.
@@ -860,9 +864,9 @@ template <int G, typename OffT, typename Pos, bool NC, bool BY_NODE>
 __global__ __launch_bounds__(LDS_BLOCK) void k_front_lds(
     Tables T, const OffT* __restrict__ offsets, const int32_t* __restrict__ indices,
     const int64_t* __restrict__ nc_address_table, const int32_t* __restrict__ nc_cache_array,
-    const int32_t* __restrict__ seeds, const int64_t* __restrict__ seed_off, int k, uint64_t seed,
+    const int32_t* __restrict__ seeds, SeedOffsets seed_off, int k, uint64_t seed,
     uint32_t first_batch, int H, Meta M, int32_t* __restrict__ nlist_seeds,
-    uint64_t* __restrict__ batch_total) {
+    int32_t* __restrict__ nlist, uint64_t* __restrict__ batch_total) {
   __shared__ unsigned long long tab[LDS_SLOTS];
   __shared__ uint64_t s_first[LDS_BLOCK];
   __shared__ uint32_t s_edges[LDS_BLOCK], s_firsts[LDS_BLOCK];
@@ -1022,39 +1026,71 @@ __global__ __launch_bounds__(LDS_BLOCK) void k_front_lds(
       cand[r] = (int32_t)(where & OLD_ID ? where & ~OLD_ID : (uint32_t)tab[where]);
     }
   }
-  __syncthreads();   // `ref` is free now: it parks the rows' edge offsets
-  if (tid < n0) {
-    ref[tid] = s_edges[tid];
-    T.cnt[(int64_t)b * T.fr_slots + tid] = s_cnt[tid];
+  // the rows' edge offsets (see FrontAdj; n0 + 1 words of 4 bytes in fr_slots >= 1, n0 words of 8)
+  uint32_t* edges = reinterpret_cast<uint32_t*>(T.displaced + (int64_t)b * T.fr_slots);
+  if (tid < n0) edges[tid] = s_edges[tid];
+  if (tid == 0) {
+    const int32_t grown = n0 + (int32_t)total64;
+    edges[n0] = (uint32_t)(total64 >> 32);
+    batch_total[b] = total64;
+    nlist[b] = grown;
+    M.hop_sizes[(int64_t)b * (H + 1) + 1] = grown;
   }
-  if (tid == 0) batch_total[b] = total64;
 }
 
-// adj of hop 0 from the scratch arrays k_front_lds left: rowptr of every frontier node, and
-// the list position of every pick at its place in the batch's segment.
-__global__ __launch_bounds__(TB) void k_adj_copy(Tables T, const int32_t* __restrict__ nfront, int k,
-                                                 const uint64_t* __restrict__ batch_total,
-                                                 int64_t* __restrict__ rowptr, int64_t rowptr_capacity,
-                                                 const int64_t* __restrict__ row_base,
-                                                 int32_t* __restrict__ col, int64_t col_capacity,
-                                                 const int64_t* __restrict__ col_base) {
-  const int b = blockIdx.y;
-  const int n0 = nfront[b];
-  const int32_t* cand = T.cand + (int64_t)b * T.cand_slots;
-  const uint32_t* edges = T.ref + (int64_t)b * T.cand_slots;
-  const int64_t rb = row_base[b], cb = col_base[b];
-  const int64_t span = (int64_t)gridDim.x * TB;
-  for (int64_t r = (int64_t)blockIdx.x * TB + threadIdx.x; r <= n0; r += span)
-    if (rb + r < rowptr_capacity)
-      rowptr[rb + r] = r < n0 ? (int64_t)edges[r] : (int64_t)(batch_total[b] >> 32);
-  const int64_t ncand = (int64_t)n0 * k;
-  for (int64_t r = (int64_t)blockIdx.x * TB + threadIdx.x; r < ncand; r += span) {
-    const int64_t node = r / k, pick = r - node * k;
-    if (pick < T.cnt[(int64_t)b * T.fr_slots + node]) {
-      const int64_t d = cb + edges[node] + pick;
-      if (d < col_capacity) col[d] = cand[r];
-    }
+// The seeds alone, where they fit LDS but the first hop's picks do not fit beside them (33 batches of 777 seeds,
+// fanout 25: one launch of 6 us instead of seven, some 40 us with the waits between them).
+constexpr int SEED_ITEMS = LDS_MAX_IDS / LDS_BLOCK;
+
+__global__ __launch_bounds__(LDS_BLOCK) void k_seeds_lds(Tables T, const int32_t* __restrict__ seeds,
+                                                         SeedOffsets seed_off, int H, Meta M,
+                                                         int32_t* __restrict__ nlist) {
+  __shared__ unsigned long long tab[LDS_SLOTS];
+  __shared__ uint32_t smem[LDS_BLOCK / WAVE + 1];
+  const int b = blockIdx.x;
+  const int ns = (int)(seed_off[b + 1] - seed_off[b]);
+  const int32_t* mine = seeds + seed_off[b];
+  const uint32_t slots = 2 * ns + 32 < LDS_SLOTS ? 2 * ns + 32 : LDS_SLOTS;
+  for (uint32_t i = threadIdx.x; i < slots; i += LDS_BLOCK) tab[i] = FREE_SLOT;
+  if (b == 0 && threadIdx.x == 0) {
+    M.totals[1] = 0;
+    M.totals[2] = 0;
   }
+  uint32_t id[SEED_ITEMS], slot[SEED_ITEMS], before;
+#pragma unroll
+  for (int q = 0; q < SEED_ITEMS; ++q) {
+    const int x = q * LDS_BLOCK + threadIdx.x;
+    id[q] = x < ns ? (uint32_t)mine[x] : 0u;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < SEED_ITEMS; ++q) {
+    const int x = q * LDS_BLOCK + threadIdx.x;
+    if (x < ns) slot[q] = lds_place(tab, id[q], PEND + (uint32_t)x, before, slots);
+  }
+  __syncthreads();
+  int32_t* list = T.wlist + (int64_t)b * T.stride_ids;
+  uint32_t n = 0;
+#pragma unroll
+  for (int q = 0; q < SEED_ITEMS; ++q) {
+    if (q * LDS_BLOCK >= ns) break;       // uniform
+    const int x = q * LDS_BLOCK + threadIdx.x;
+    const bool kept = x < ns && (uint32_t)tab[slot[q]] == PEND + (uint32_t)x;
+    uint32_t total;
+    const uint32_t at = n + block_exclusive_scan<uint32_t, LDS_BLOCK>(kept ? 1u : 0u, smem, total);
+    if (kept) list[at] = (int32_t)id[q];
+    n += total;
+  }
+  if (threadIdx.x == 0) {
+    nlist[b] = (int32_t)n;
+    M.hop_sizes[(int64_t)b * (H + 1)] = n;
+  }
+}
+
+// adj of hop 0 from what k_front_lds left, where no k_bucket_emit takes it along.
+__global__ __launch_bounds__(TB) void k_adj_copy(Tables T, FrontAdj front, EmitTo to) {
+  const int b = blockIdx.y;
+  front_adj_copy(T, b, front.nlist[b], front.k, to.row_base[b], to.col_base[b], to, blockIdx.x, gridDim.x);
 }
 
 template <typename OffT, bool NC>
@@ -1089,23 +1125,23 @@ constexpr int64_t FEW_NODES = 2048, FEW_NODES_PER_PICK = 512, FEW_NODES_SHORT_RO
 template <int K_MAX, typename OffT, typename Pos, bool NC>
 void launch_pick_tiles(const Tables& T, const Buckets& B, int64_t front, const ginex_csr_t* g,
                        const int32_t* nfront, int k, int hop, int32_t S, uint64_t seed,
-                       uint32_t first_batch, hipStream_t st) {
+                       uint32_t first_batch, uint64_t* batch_total, hipStream_t st) {
   const int64_t tpb = capped(ceil_div(front, TILE_NODES) + ceil_div(front, LIST_TILE), tile_cap(SLOT_TILES, S));
   const int slots = TILE_NODES * k > LIST_TILE ? TILE_NODES * k : LIST_TILE;
   hipLaunchKernelGGL((k_pick_tiles<K_MAX, OffT, Pos, NC>), dim3(grid_blocks(S, tpb)), dim3(TB),
                      (sizeof(uint32_t) + sizeof(uint16_t)) * slots, st, T, B,
                      static_cast<const OffT*>(g->offsets), g->indices, g->nc_address_table,
-                     g->nc_cache_array, nfront, k, hop, seed, first_batch, S, tpb, slots);
+                     g->nc_cache_array, nfront, k, hop, seed, first_batch, S, batch_total, tpb, slots);
 }
 
 template <typename OffT, bool NC>
 void launch_pick_tiles(const Tables& T, const Buckets& B, int64_t front, const ginex_csr_t* g,
                        const int32_t* nfront, int k, int hop, int32_t S, uint64_t seed,
-                       uint32_t first_batch, hipStream_t st) {
+                       uint32_t first_batch, uint64_t* batch_total, hipStream_t st) {
   // row positions in 32 bits, unless a row could be longer than that
   const bool wide = sizeof(OffT) == 8 && g->num_edges >= (int64_t(1) << 32);
 #define GINEX_TILES(K_MAX, Pos) \
-  launch_pick_tiles<K_MAX, OffT, Pos, NC>(T, B, front, g, nfront, k, hop, S, seed, first_batch, st)
+  launch_pick_tiles<K_MAX, OffT, Pos, NC>(T, B, front, g, nfront, k, hop, S, seed, first_batch, batch_total, st)
   if (wide) {
     if constexpr (sizeof(OffT) == 8) {
       if (k <= 16) GINEX_TILES(16, uint64_t);
@@ -1121,15 +1157,15 @@ void launch_pick_tiles(const Tables& T, const Buckets& B, int64_t front, const g
 
 template <typename OffT, bool NC>
 void launch_front(const Tables& T, const ginex_csr_t* g, const int32_t* seeds,
-                  const int64_t* seed_off, int k, int32_t S, int32_t H, uint64_t seed,
-                  uint32_t first_batch, const Meta& M, int32_t* nlist_seeds, uint64_t* batch_total,
-                  bool groups, hipStream_t st) {
+                  const SeedOffsets& seed_off, int k, int32_t S, int32_t H, uint64_t seed,
+                  uint32_t first_batch, const Meta& M, int32_t* nlist_seeds, int32_t* nlist,
+                  uint64_t* batch_total, bool groups, hipStream_t st) {
   const OffT* off = static_cast<const OffT*>(g->offsets);
   const bool wide = sizeof(OffT) == 8 && g->num_edges >= (int64_t(1) << 32);   // see launch_pick_tiles
 #define GINEX_FRONT(G, Pos, BY_NODE)                                                            \
   hipLaunchKernelGGL((k_front_lds<G, OffT, Pos, NC, BY_NODE>), dim3((unsigned)S), dim3(LDS_BLOCK), 0, \
                      st, T, off, g->indices, g->nc_address_table, g->nc_cache_array, seeds, seed_off, \
-                     k, seed, first_batch, H, M, nlist_seeds, batch_total)
+                     k, seed, first_batch, H, M, nlist_seeds, nlist, batch_total)
   if (groups) {
     if (k <= 16) GINEX_FRONT(16, uint32_t, false);
     else if (k <= 32) GINEX_FRONT(32, uint32_t, false);
@@ -1212,8 +1248,6 @@ extern "C" int32_t ginex_sample_superbatch(
   M.col_off = M.row_off + ((int64_t)S * H + 1);
   M.totals = M.col_off + ((int64_t)S * H + 1);
 
-  GINEX_HIP(hipMemcpyAsync(w.seed_off, seed_offsets, sizeof(int64_t) * (S + 1),
-                           hipMemcpyHostToDevice, st));
   const char* validate_env = getenv("GINEX_VALIDATE");
   if (validate_env && validate_env[0] == '1' && seed_offsets[S] > 0) {
     // the first slot of the (not yet used) batch_total array serves as the counter
@@ -1253,6 +1287,18 @@ extern "C" int32_t ginex_sample_superbatch(
   const bool front_lds = max_batch <= LDS_BLOCK &&
                          max_batch * (1 + (int64_t)fanout[0]) <= LDS_MAX_IDS && lds;
   const bool host_ids = in_host_memory(g->indices);
+  const bool seeds_lds = max_batch <= LDS_MAX_IDS && lds;
+  SeedOffsets offs{w.seed_off, {}};
+  if (seeds_lds && S <= SEED_OFFSETS && seed_offsets[S] <= INT32_MAX) {
+    offs.far = nullptr;
+    for (int b = 0; b <= S; ++b) offs.near[b] = (int32_t)seed_offsets[b];
+  } else {
+    GINEX_HIP(hipMemcpyAsync(w.seed_off, seed_offsets, sizeof(int64_t) * (S + 1),
+                             hipMemcpyHostToDevice, st));
+  }
+  // (a hop through buckets has no use for tab_off, and hop 0's sums are read by the next one at the latest)
+  uint64_t* const front_total = reinterpret_cast<uint64_t*>(w.tab_off);
+  FrontAdj front{};
   if (front_lds) {
     const int k0 = fanout[0];
     // a thread per node, or a group of lanes: a thread has all its reads in flight and needs no shuffles,
@@ -1264,42 +1310,55 @@ extern "C" int32_t ginex_sample_superbatch(
     const bool groups = host_ids || k0 > 16 || max_batch <= 8 * (int64_t)k0;
     if (g->nc_address_table) {
       if (g->offsets_64)
-        launch_front<int64_t, true>(T, g, seeds, w.seed_off, k0, S, H, rng_seed, first_batch_index, M,
-                                    w.nlist_b, w.batch_total, groups, st);
+        launch_front<int64_t, true>(T, g, seeds, offs, k0, S, H, rng_seed, first_batch_index, M,
+                                    w.nfront, w.nlist_a, front_total, groups, st);
       else
-        launch_front<int32_t, true>(T, g, seeds, w.seed_off, k0, S, H, rng_seed, first_batch_index, M,
-                                    w.nlist_b, w.batch_total, groups, st);
+        launch_front<int32_t, true>(T, g, seeds, offs, k0, S, H, rng_seed, first_batch_index, M,
+                                    w.nfront, w.nlist_a, front_total, groups, st);
     } else if (g->offsets_64) {
-      launch_front<int64_t, false>(T, g, seeds, w.seed_off, k0, S, H, rng_seed, first_batch_index, M,
-                                   w.nlist_b, w.batch_total, groups, st);
+      launch_front<int64_t, false>(T, g, seeds, offs, k0, S, H, rng_seed, first_batch_index, M,
+                                   w.nfront, w.nlist_a, front_total, groups, st);
     } else {
-      launch_front<int32_t, false>(T, g, seeds, w.seed_off, k0, S, H, rng_seed, first_batch_index, M,
-                                   w.nlist_b, w.batch_total, groups, st);
+      launch_front<int32_t, false>(T, g, seeds, offs, k0, S, H, rng_seed, first_batch_index, M,
+                                   w.nfront, w.nlist_a, front_total, groups, st);
     }
     GINEX_LAUNCH_CHECK();
-    // the list after the seeds (nlist_b) is the frontier of hop 0; nlist_a receives the list after hop 0
-    hipLaunchKernelGGL(k_stage_offsets, dim3(1), dim3(TB), 0, st, M, S, H, 0, w.batch_total,
-                       w.nlist_b, w.nlist_b, w.nlist_a, w.row_base, w.col_base);
-    GINEX_LAUNCH_CHECK();
-    if (adj_rowptr) {
-      const int64_t per_batch = ceil_div(max_batch * (int64_t)k0 + 1, TB);
-      hipLaunchKernelGGL(k_adj_copy, dim3((unsigned)(per_batch < 16 ? per_batch : 16), (unsigned)S),
-                         dim3(TB), 0, st, T, w.nlist_b, k0, w.batch_total, adj_rowptr,
-                         rowptr_capacity, w.row_base, adj_col, col_capacity, w.col_base);
-      GINEX_LAUNCH_CHECK();
-    }
+    // the list after the seeds (nfront) is the frontier of hop 0; nlist_a holds the list after hop 0
+    front = FrontAdj{w.nfront, front_total, k0};
     first_stage = 1;
+  } else if (seeds_lds) {
+    hipLaunchKernelGGL(k_seeds_lds, dim3((unsigned)S), dim3(LDS_BLOCK), 0, st, T, seeds, offs, H, M,
+                       w.nlist_a);
+    GINEX_LAUNCH_CHECK();
+    first_stage = 0;
   } else {
     hipLaunchKernelGGL(k_seed_counts, dim3((unsigned)ceil_div(S, TB)), dim3(TB), 0, st, w.seed_off,
                        S, w.nfront, w.nlist_a);
     GINEX_LAUNCH_CHECK();
   }
+  const EmitTo to{adj_rowptr, rowptr_capacity, adj_col, col_capacity, ids, ids_capacity, nullptr, nullptr};
+  EmitTo based = to;
+  based.row_base = w.row_base;
+  based.col_base = w.col_base;
+  auto place_front = [&]() -> int32_t {   // hop 0's adj to its place by launches of its own
+    hipLaunchKernelGGL(k_stage_offsets, dim3(1), dim3(TB), 0, st, M, S, H, 0, front.batch_total, front.nlist,
+                       front.nlist, w.nlist_a, w.row_base, w.col_base);
+    if (adj_rowptr) {
+      const int64_t per_batch = ceil_div(max_batch * (int64_t)front.k + 1, TB);
+      hipLaunchKernelGGL(k_adj_copy, dim3((unsigned)(per_batch < 16 ? per_batch : 16), (unsigned)S), dim3(TB), 0,
+                         st, T, front, based);
+    }
+    GINEX_LAUNCH_CHECK();
+    front = FrontAdj{};
+    return GINEX_OK;
+  };
+  bool ids_placed = false;
   for (int stage = first_stage; stage < H; ++stage) {
     const int k = stage < 0 ? 1 : fanout[stage];
-    const int64_t front = stage < 0 ? (max_batch > 0 ? max_batch : 1) : p.stride_front[stage];
+    const int64_t most = stage < 0 ? (max_batch > 0 ? max_batch : 1) : p.stride_front[stage];
     // in a hop the frontier is the whole list as it stands when the hop starts
     const int32_t* nfront = stage < 0 ? w.nfront : nlist;
-    const int64_t tpb = capped(ceil_div(front, TB), tile_cap(SLOT_TILES, S));
+    const int64_t tpb = capped(ceil_div(most, TB), tile_cap(SLOT_TILES, S));
     const dim3 grid_slots(grid_blocks(S, tpb));
     // later hops: the hash sets in the LDS of a workgroup per bucket, where the picks of a node fit a
     // thread's registers and the workspace has room (GINEX_SAMPLER_LDS=0: the tables in HBM).  Not
@@ -1314,10 +1373,10 @@ extern "C" int32_t ginex_sample_superbatch(
     const int64_t few = g->num_edges < k * g->num_nodes ? FEW_NODES_SHORT_ROWS
                                                         : FEW_NODES + FEW_NODES_PER_PICK * (k - 16);
     auto few_wide = [&](int64_t nodes) { return k > 16 && S * nodes <= few; };
-    bool buckets = stage >= 0 && k <= BUCKET_K_MAX && buckets_fit && lds && !host_ids && !few_wide(front);
+    bool buckets = stage >= 0 && k <= BUCKET_K_MAX && buckets_fit && lds && !host_ids && !few_wide(most);
     // ... and where a batch's ids fit the buckets.  Where the bound says that they may not, the lists as they
     // are decide (a wait of some 15 us in front of a hop of a million picks or more)
-    if (buckets && hop_ids(front, k, g->num_nodes) > BUCKET_IDS_LIMIT) {
+    if (buckets && hop_ids(most, k, g->num_nodes) > BUCKET_IDS_LIMIT) {
       std::vector<int32_t> lists(S);
       GINEX_HIP(hipMemcpyAsync(lists.data(), nlist, sizeof(int32_t) * S, hipMemcpyDeviceToHost, st));
       GINEX_HIP(hipStreamSynchronize(st));
@@ -1327,30 +1386,53 @@ extern "C" int32_t ginex_sample_superbatch(
     if (buckets) {
       if (g->nc_address_table) {
         if (g->offsets_64)
-          launch_pick_tiles<int64_t, true>(T, w.buckets, front, g, nfront, k, stage, S, rng_seed,
-                                           first_batch_index, st);
+          launch_pick_tiles<int64_t, true>(T, w.buckets, most, g, nfront, k, stage, S, rng_seed,
+                                           first_batch_index, w.batch_total, st);
         else
-          launch_pick_tiles<int32_t, true>(T, w.buckets, front, g, nfront, k, stage, S, rng_seed,
-                                           first_batch_index, st);
+          launch_pick_tiles<int32_t, true>(T, w.buckets, most, g, nfront, k, stage, S, rng_seed,
+                                           first_batch_index, w.batch_total, st);
       } else if (g->offsets_64) {
-        launch_pick_tiles<int64_t, false>(T, w.buckets, front, g, nfront, k, stage, S, rng_seed,
-                                          first_batch_index, st);
+        launch_pick_tiles<int64_t, false>(T, w.buckets, most, g, nfront, k, stage, S, rng_seed,
+                                          first_batch_index, w.batch_total, st);
       } else {
-        launch_pick_tiles<int32_t, false>(T, w.buckets, front, g, nfront, k, stage, S, rng_seed,
-                                          first_batch_index, st);
+        launch_pick_tiles<int32_t, false>(T, w.buckets, most, g, nfront, k, stage, S, rng_seed,
+                                          first_batch_index, w.batch_total, st);
       }
       GINEX_LAUNCH_CHECK();
-      const int64_t groups = capped(bucket_count(front, k, g->num_nodes, S), tile_cap(BUCKET_GROUPS, S));
+      const int64_t groups = capped(bucket_count(most, k, g->num_nodes, S), tile_cap(BUCKET_GROUPS, S));
       hipLaunchKernelGGL(k_bucket_dedup, dim3(grid_blocks(S, groups)), dim3(BUCKET_THREADS), 0, st, T,
                          w.buckets, nfront, k, S, groups);
       GINEX_LAUNCH_CHECK();
-      hipLaunchKernelGGL(k_tile_firsts, grid_slots, dim3(TB), sizeof(uint32_t) * TILE_NODES * k, st, T,
-                         w.buckets, nfront, k, w.tile_sums, p.tiles, S, tpb);
+      hipLaunchKernelGGL(k_tile_firsts, grid_slots, dim3(TB), 0, st, T, w.buckets, nfront, k, w.tile_sums,
+                         p.tiles, w.batch_total, S, tpb);
+      const bool last = stage == H - 1;
+      const int64_t tiles = ceil_div(most, TILE_NODES);
+      if (tiles > EMIT_TILES)
+        hipLaunchKernelGGL(k_scan_batch, dim3(S), dim3(TB), 0, st, w.tile_sums, p.tiles, nfront, w.batch_total);
+      if (S > EMIT_BATCHES) {
+        if (front.nlist)
+          if (int32_t rc = place_front()) return rc;
+        hipLaunchKernelGGL(k_stage_offsets, dim3(1), dim3(TB), 0, st, M, S, H, stage, w.batch_total, nfront, nlist,
+                           nlist_next, w.row_base, w.col_base);
+        if (last) hipLaunchKernelGGL(k_ids_offsets, dim3(1), dim3(TB), 0, st, M, S, nlist_next);
+      }
+      const int tiles_in_lds = tiles > EMIT_TILES ? 0 : (int)tiles;
+      hipLaunchKernelGGL(k_bucket_emit, grid_slots, dim3(TB),
+                         sizeof(uint64_t) * tiles_in_lds + (sizeof(uint32_t) + sizeof(uint16_t)) * TILE_NODES * k,
+                         st, T, w.buckets, M, nfront, nlist_next, k, stage, H, w.tile_sums, p.tiles,
+                         w.batch_total, front, S > EMIT_BATCHES ? based : to, S, tpb, tiles_in_lds);
       GINEX_LAUNCH_CHECK();
-    } else {
+      front = FrontAdj{};
+      ids_placed = last;
+      std::swap(nlist, nlist_next);
+      continue;
+    }
+    if (front.nlist)
+      if (int32_t rc = place_front()) return rc;
+    {
       hipLaunchKernelGGL(k_table_plan, dim3(1), dim3(TB), 0, st, T, S, g->num_nodes, k, nfront,
                          nlist, w.tab_total);
-      hipLaunchKernelGGL(k_table_clear, dim3(4096), dim3(TB), 0, st, T, w.tab_total, nfront, S, front);
+      hipLaunchKernelGGL(k_table_clear, dim3(4096), dim3(TB), 0, st, T, w.tab_total, nfront, S, most);
       GINEX_LAUNCH_CHECK();
       if (stage >= 0) {
         hipLaunchKernelGGL(k_reinsert, grid_slots, dim3(TB), 0, st, T, nlist, S, tpb);
@@ -1386,19 +1468,19 @@ extern "C" int32_t ginex_sample_superbatch(
                        adj ? adj_col : (int32_t*)nullptr, col_capacity, w.col_base, S, tpb);
     GINEX_LAUNCH_CHECK();
     if (adj) {
-      if (buckets)
-        hipLaunchKernelGGL(k_col<true>, grid_slots, dim3(TB), 0, st, T, nfront, k, adj_rowptr,
-                           rowptr_capacity, w.row_base, adj_col, col_capacity, w.col_base, S, tpb);
-      else
-        hipLaunchKernelGGL(k_col<false>, grid_slots, dim3(TB), 0, st, T, nfront, k, adj_rowptr,
-                           rowptr_capacity, w.row_base, adj_col, col_capacity, w.col_base, S, tpb);
+      hipLaunchKernelGGL(k_col, grid_slots, dim3(TB), 0, st, T, nfront, k, adj_rowptr, rowptr_capacity,
+                         w.row_base, adj_col, col_capacity, w.col_base, S, tpb);
       GINEX_LAUNCH_CHECK();
     }
-    int32_t* t = nlist; nlist = nlist_next; nlist_next = t;
+    std::swap(nlist, nlist_next);
   }
-  hipLaunchKernelGGL(k_ids_offsets, dim3(1), dim3(TB), 0, st, M, S, nlist);
-  GINEX_LAUNCH_CHECK();
-  if (ids_capacity > 0) {
+  if (front.nlist)
+    if (int32_t rc = place_front()) return rc;
+  if (!ids_placed) {
+    hipLaunchKernelGGL(k_ids_offsets, dim3(1), dim3(TB), 0, st, M, S, nlist);
+    GINEX_LAUNCH_CHECK();
+  }
+  if (ids_capacity > 0 && !ids_placed) {
     // (a capped grid like the others: sized for the longest possible list it was 260 000 blocks for
     // 200 batches, nearly all of them empty)
     const int64_t copy_tiles = std::max(COPY_TILES, COPY_BLOCKS / S);
