@@ -26,7 +26,7 @@
  *      GINEX_SAMPLER_LDS=0    all hops through hash tables in HBM, none through tables in LDS
  *      GINEX_SAMPLER_TILES=n  at most n tiles of a batch per workgroup column of the sampler
  *      GINEX_LIVE_SELECT=1    no shortcut that relies on the cache holding the whole superbatch
- *      GINEX_STATIC_THRESHOLDS=0/1  Belady changesets from a loop over the cache state, iteration by
+ *      GINEX_STATIC_THRESHOLDS=0/1  changesets from a loop over the cache state, iteration by
  *                             iteration / from the trace alone, where the sizes would choose the other
  *      GINEX_DEAD_SCATTER=0/1 in that loop, evictions among dead rows from a pass over the lines / from
  *                             the id bitmap

@@ -9,9 +9,9 @@
 // Part 3, the recurrence C_{i+1} = f_Belady(union(C_i, ids_i)).  For up to 2 048 iterations
 //   hits, misses, insertions and evictions follow from the trace and the start state at once,
 //   and only the lines are handed on iteration by iteration (stays.hpp; a carried cache that
-//   holds every row of the superbatch: the part "without a loop" below).  For LRU, beyond 2 048
-//   iterations, and for the smallest calls a loop over the state, serial over iterations and
-//   parallel inside one.  The cache is full from C_0 on (otherwise everything fitted and
+//   holds every row of the superbatch: the part "without a loop" below).  Beyond 2 048
+//   iterations, for LRU where an iteration is longer than the cache, and for the smallest calls a loop
+//   over the state, serial over iterations and parallel inside one.  The cache is full from C_0 on (otherwise everything fitted and
 //   nothing ever changes), so iteration i must drop exactly as many candidates as it had
 //   misses.  Keys are (next iteration, incoming?, node id); next iterations take only
 //   S-i distinct values, so a histogram per next iteration (kept incrementally for the
@@ -21,7 +21,7 @@
 //   counts.  Evicted lines and inserted positions are then compacted in line / position
 //   order and paired.
 //   Both ways also serve a superbatch that resumes from the cache state of the previous one
-//   (C_0 given instead of computed); LRU has other keys.
+//   (C_0 given instead of computed, Belady only); LRU has other keys.
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
@@ -479,7 +479,8 @@ __global__ __launch_bounds__(TB) void k_copy_init(const uint64_t* __restrict__ h
 
 // ---- part 3 -----------------------------------------------------------------------
 //
-// The loop over the state (LRU, more iterations than stays.hpp takes, the smallest calls).  One iteration of
+// The loop over the state (more iterations than stays.hpp takes, LRU with iterations longer than the cache,
+// the smallest calls).  One iteration of
 // the recurrence is six dependent launches:
 //   k_touch      hits get their new key, hits and misses are histogrammed by key, the line of
 //                every access (or -1) is kept for the later phases and for the executor
@@ -2226,34 +2227,12 @@ extern "C" size_t ginex_changeset_workspace_bytes(int64_t num_nodes, int64_t tot
 namespace ginex {
 namespace {
 
-// The changesets of a full cache whose state (res_id, addr of the accessed rows, rhist and, for a
-// carried cache, dead_bits) is set up, from the node-sorted accesses (see stays.hpp).
-// `ends`: the other buffer of the sort, `rows`: a word per distinct row.  last_head: the last row of
-// C_0, null for a carried cache, whose rows are in held_bits; accessed: the superbatch's.
-int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, uint64_t* ends,
-                  uint64_t* rows, int64_t distinct, const uint64_t* last_head,
-                  const uint32_t* held_bits, const uint32_t* accessed, const int32_t* ids,
-                  const int64_t* ids_offsets, int64_t total, int32_t S, int32_t* in_ids, int32_t* out_ids, int32_t* in_positions,
-                  int64_t cs_capacity, int64_t* cs_offsets, int64_t* miss_count, int32_t* src_line,
-                  int64_t* total_changes, bool carried, int32_t* final_ids, hipStream_t st) {
+// Belady's thresholds and cuts, from the histograms (see stays.hpp); *never: bucket "never" is cut.
+int32_t stays_cuts(const Workspace& w, const Stays& q, const int64_t* ids_offsets, int64_t* miss_count, bool* never,
+                   hipStream_t st) {
   const State& state = w.st;
   const Plan& pl = w.plan;
-  const size_t off_lds = sizeof(int32_t) * (S + 1);
-  Stays q{ends, w.d_offsets, ids, w.key_hists, w.cuts, w.next_iter, pl.cand_id, S};
-  int64_t longest = 0;
-  for (int32_t i = 0; i < S; ++i)
-    longest = std::max<int64_t>(longest, ids_offsets[i + 1] - ids_offsets[i]);
-
-  // both ends of every stay, the thresholds, the table
-  const int64_t windows = ceil_div(total, ENDS_WINDOW);
-  const int64_t window = windows <= ENDS_WINDOWS_MAX ? ceil_div(total, windows) : total;
-  for (int64_t from = 0; from < total; from += window)
-    hipLaunchKernelGGL(k_stay_ends, dim3((unsigned)w.look_tiles), dim3(TB), off_lds, st, sorted, total,
-                       w.d_offsets, S, last_head, held_bits, (uint32_t)from,
-                       (uint32_t)std::min(total, from + window), ends);
-  GINEX_HIP(zero_async(Zeros().add(w.key_hists, (int64_t)S * (S + 1)).add(pl.arr_cur, S + 1), st));
-  hipLaunchKernelGGL(k_key_hists, dim3((unsigned)ceil_div(longest, TB * TOUCH_ITEMS), (unsigned)S),
-                     dim3(TB), sizeof(uint32_t) * (S + 1), st, ends, w.d_offsets, S, w.key_hists);
+  const int32_t S = q.S;
   if (S < 256)
     hipLaunchKernelGGL((k_static_roll<256, 1>), dim3(1), dim3(256), 0, st, state, w.key_hists,
                        w.d_offsets, w.cuts, miss_count);
@@ -2271,10 +2250,9 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
   // the earlier cuts of its bucket
   std::vector<int32_t> jobs, level_of_bucket(S + 1, 0);
   std::vector<std::vector<int32_t>> levels;
-  bool never = false;
   for (int32_t t = 0; t < S; ++t) {
     const Cut& c = cuts[t];
-    if (c.jstar == S) never = true;
+    if (c.jstar == S) *never = true;
     if (c.jstar >= S || c.rem == 0) continue;
     const int32_t l = std::max(level_of_bucket[t], level_of_bucket[c.jstar]);   // (levels count from 1)
     level_of_bucket[c.jstar] = l + 1;
@@ -2316,10 +2294,53 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
     GINEX_LAUNCH_CHECK();
     at += count;
   }
+  return GINEX_OK;
+}
+
+// The changesets of a full cache whose state (res_id, addr of the accessed rows, rhist and, for a
+// carried cache, dead_bits) is set up, from the node-sorted accesses (see stays.hpp).
+// `ends`: the other buffer of the sort, `rows`: a word per distinct row.  last_head: the last row of
+// C_0, null for a carried cache, whose rows are in held_bits; accessed: the superbatch's.
+int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, uint64_t* ends,
+                  uint64_t* rows, int64_t distinct, const uint64_t* last_head,
+                  const uint32_t* held_bits, const uint32_t* accessed, const int32_t* ids,
+                  const int64_t* ids_offsets, int64_t total, int32_t S, int32_t* in_ids, int32_t* out_ids, int32_t* in_positions,
+                  int64_t cs_capacity, int64_t* cs_offsets, int64_t* miss_count, int32_t* src_line,
+                  int64_t* total_changes, bool carried, int32_t* final_ids, hipStream_t st) {
+  const State& state = w.st;
+  const Plan& pl = w.plan;
+  const size_t off_lds = sizeof(int32_t) * (S + 1);
+  const bool lru = state.lru;
+  uint64_t* const limits = reinterpret_cast<uint64_t*>(w.cuts);   // (there are no cuts then)
+  Stays q{ends, w.d_offsets, ids, w.key_hists, w.cuts, w.next_iter, pl.cand_id, limits, S,
+          bits_for(state.num_nodes)};
+  int64_t longest = 0;
+  for (int32_t i = 0; i < S; ++i)
+    longest = std::max<int64_t>(longest, ids_offsets[i + 1] - ids_offsets[i]);
+
+  // both ends of every stay, the thresholds, the table
+  const int64_t windows = ceil_div(total, ENDS_WINDOW);
+  const int64_t window = windows <= ENDS_WINDOWS_MAX ? ceil_div(total, windows) : total;
+  for (int64_t from = 0; from < total; from += window)
+    hipLaunchKernelGGL(k_stay_ends, dim3((unsigned)w.look_tiles), dim3(TB), off_lds, st, sorted, total,
+                       w.d_offsets, S, last_head, held_bits, (uint32_t)from,
+                       (uint32_t)std::min(total, from + window), ends);
+  GINEX_HIP(zero_async(Zeros().add(w.key_hists, (int64_t)S * (S + 1)).add(pl.arr_cur, S + 1), st));
+  hipLaunchKernelGGL(k_key_hists, dim3((unsigned)ceil_div(longest, TB * TOUCH_ITEMS), (unsigned)S),
+                     dim3(TB), sizeof(uint32_t) * (S + 1), st, ends, w.d_offsets, S, w.key_hists);
+  bool never = false;      // bucket "never" is cut
+  if (lru) {
+    hipLaunchKernelGGL(k_lru_counts, dim3((unsigned)S), dim3(WAVE), 0, st, S, w.key_hists);
+    hipLaunchKernelGGL(k_lru_limits, dim3((unsigned)S), dim3(BIG), 0, st, q, w.key_hists, state.cap, limits);
+    GINEX_LAUNCH_CHECK();
+  } else if (int32_t rc = stays_cuts(w, q, ids_offsets, miss_count, &never, st)) {
+    return rc;
+  }
 
   // hits, misses, insertions
-  hipLaunchKernelGGL(k_stays_mark, dim3((unsigned)ceil_div(total, CUT_TILE)), dim3(TB), off_lds, st, q,
-                     total, src_line, pl.ins_bits);
+  const dim3 mark_grid((unsigned)ceil_div(total, CUT_TILE));
+  if (lru) hipLaunchKernelGGL(k_stays_mark<true>, mark_grid, dim3(TB), off_lds, st, q, total, src_line, pl.ins_bits);
+  else hipLaunchKernelGGL(k_stays_mark<false>, mark_grid, dim3(TB), off_lds, st, q, total, src_line, pl.ins_bits);
   auto finish = [&]() -> int32_t {
     if (final_ids)
       GINEX_HIP(hipMemcpyAsync(final_ids, state.res_id, sizeof(int32_t) * state.cap,
@@ -2327,7 +2348,7 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
     GINEX_HIP(hipStreamSynchronize(st));
     return GINEX_OK;
   };
-  if (distinct == total) {
+  if (distinct == total && !lru) {
     // no row is accessed twice (a superbatch of one iteration, for one): nothing is inserted, so the lists stay
     // empty and the lines are those of the start state (one iteration of 15 k accesses, 2 k lines carried: 457 -> 311 us per call)
     if (src_line) {
@@ -2348,8 +2369,9 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
   uint64_t* const ins_words = hit_words + words;
   Never nv{};
   nv.rows = rows;
-  hipLaunchKernelGGL(k_stays_links, dim3((unsigned)w.look_tiles), dim3(TB), off_lds, st, q, sorted, total,
-                     w.head_tiles, last_head, held_bits, state.addr, nv, hit_words, ins_words, leave_start);
+  if (!lru)
+    hipLaunchKernelGGL(k_stays_links, dim3((unsigned)w.look_tiles), dim3(TB), off_lds, st, q, sorted, total,
+                       w.head_tiles, last_head, held_bits, state.addr, nv, hit_words, ins_words, leave_start);
   // bucket "never"
   if (never) {
     static_assert(NEVER_COUNTS <= PLAN_CAND_MAX && NEVER_LEVELS * (STATIC_S_MAX + 1) + NEVER_PARTS <= PLAN_CAND_MAX,
@@ -2384,9 +2406,9 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
     hipLaunchKernelGGL(k_never_select, dim3((unsigned)nv.parts), dim3(NEVER_THREADS), 0, st, nv, S, w.cuts);
     GINEX_LAUNCH_CHECK();
   }
-  hipLaunchKernelGGL(k_never_lift, dim3(1), dim3(BIG), 0, st, w.cuts, S, pl.cand_id);
+  if (!lru) hipLaunchKernelGGL(k_never_lift, dim3(1), dim3(BIG), 0, st, w.cuts, S, pl.cand_id);
   hipLaunchKernelGGL(k_ins_count, dim3((unsigned)S), dim3(TB), 0, st, pl.ins_bits, w.d_offsets,
-                     cs_offsets);
+                     cs_offsets, lru ? miss_count : (int64_t*)nullptr);
   hipLaunchKernelGGL(k_ins_offsets, dim3(1), dim3(BIG), 0, st, cs_offsets, S);
   GINEX_LAUNCH_CHECK();
   std::vector<int64_t> cs(S + 1);
@@ -2416,7 +2438,10 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
     int levels = 1;
     while ((1 << levels) <= S) ++levels;
     const dim3 walk_grid((unsigned)ceil_div(total, WALK_TILE));
-    if (S <= NEVER_LDS_S)
+    if (lru)
+      hipLaunchKernelGGL(k_lru_walk, walk_grid, dim3(TB), sizeof(uint64_t) * S + off_lds, st, q, sorted, total,
+                         last_head, state.addr, pl.ins_bits, pl.ins_base, leave_ins, leave_start);
+    else if (S <= NEVER_LDS_S)
       hipLaunchKernelGGL(k_stays_walk<true>, walk_grid, dim3(TB), off_lds * (1 + levels), st, q, sorted,
                          total, state.addr, hit_words, ins_words, pl.ins_bits, pl.ins_base, leave_ins,
                          leave_start);
@@ -2503,6 +2528,8 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
 // The smallest calls, see changeset_run.
 constexpr int32_t LOOP_S = 6;
 constexpr int64_t LOOP_IDS = 4096, LOOP_NODES = int64_t(1) << 26;
+constexpr int32_t LOOP_LRU_S = 2;
+constexpr int64_t LOOP_LRU_IDS = 1 << 16;
 
 // Both replacement policies share every kernel: a policy only decides the key an access
 // leaves behind (Belady: its next accessed iteration; LRU: S-1-i, so that the least
@@ -2664,9 +2691,12 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
   // nodes: the loop clears two words for each; two iterations of 200 accesses, carried, 66 M nodes 464 against
   // 434, three on 111 M nodes 507 against 537.  GINEX_STATIC_THRESHOLDS=0/1 chooses the loop / the trace.
   const char* static_env = getenv("GINEX_STATIC_THRESHOLDS");
-  const bool smallest = S <= LOOP_S && total <= (S <= LOOP_S / 2 ? 4 * LOOP_IDS : LOOP_IDS) &&
+  // LRU (the trace's way has no cuts): 20 000 nodes, iterations of 3 000 accesses, two 311 against 332, three 355
+  // and 342, six 472 and 396; 200 000 nodes, of 20 000, two 344 and 380, three 406 and 412.
+  const bool smallest = lru ? S <= LOOP_LRU_S && total <= LOOP_LRU_IDS && num_nodes <= LOOP_NODES : S <= LOOP_S && total <= (S <= LOOP_S / 2 ? 4 * LOOP_IDS : LOOP_IDS) &&
                         num_nodes <= LOOP_NODES && distinct < total;
-  const bool stays = !lru && S <= STATIC_S_MAX && (static_env ? static_env[0] != '0' : !smallest);
+  const bool stays = S <= STATIC_S_MAX && (!lru || max_n <= cap) &&
+                     (static_env ? static_env[0] != '0' : !smallest);
   const bool loop = !stays;   // (the loop still is the last way out of the planned path then)
   {
     Zeros z;

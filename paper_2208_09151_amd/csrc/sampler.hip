@@ -820,8 +820,8 @@ inline int64_t pick_tiles(int64_t front, int group, int S) {
 // (same slot word and the same rule as the tables in HBM: the smallest candidate rank per id
 // wins), appends the first occurrences to the batch's list and resolves every pick's list
 // position, all without a table access outside the CU.  What crosses batches (where a
-// batch's adj segment starts) is left to k_stage_offsets; the picks' positions and the rows'
-// edge counts wait in the batch's scratch arrays until k_adj_copy moves them there.
+// batch's adj segment starts) is left to the next hop's k_bucket_emit (or k_stage_offsets and k_adj_copy); the
+// picks' positions and the rows' edge counts wait in the batch's scratch arrays until then.
 // The later hops do not fit (a batch's set reaches 10^5 ids).
 constexpr int LDS_SLOTS = 16384;       // 128 KB
 constexpr int LDS_BLOCK = 1024;        // threads, and the most seeds a batch may have here

@@ -19,6 +19,8 @@
 // an inserted row gets: one launch per iteration, whose work is the iteration's changes.
 // Before, an iteration was four launches that passed over its accesses and over all lines.
 //
+// LRU goes the same way with other thresholds, see "LRU" below.
+//
 // 200 iterations of 163 840 accesses, 111 M nodes, every iteration evicts: that loop 200 x 41 us, and
 // 0.83 ms to look right.  Here: k_stay_ends 0.50 ms (scattered words), k_key_hists 0.05,
 // k_static_roll 0.16, 17 levels of k_cut_members + k_cut_decide 0.020 + 0.010 each (two chains of
@@ -61,7 +63,8 @@ struct Stays {
   Cut* cuts;               // [S]
   int32_t* members;        // [total] members of the buckets that are being cut, bucket j at off[j]
   const int32_t* never;    // [NEVER_LEVELS * (S + 1)] see k_never_lift
-  int32_t S;
+  const uint64_t* limits;  // [S] LRU, see below
+  int32_t S, id_bits;      // ids are below 2^id_bits
 };
 
 // Is the row of a run head (first access of its row, in iteration `first`) in the start state?
@@ -310,43 +313,54 @@ __global__ __launch_bounds__(TB) void k_cut_members(Stays q, const int32_t* __re
 }
 
 // One block of NT threads: the keep-th smallest (1-based) of the ids id(x), 0 <= x < n; entries with bit
-// 31 set do not count.  Radix select from the top, 11 + 10 + 10 bits.  0 < keep <= ids that count.
-template <int NT, typename Id>
-__device__ int32_t p_kth_smallest_id(int64_t n, int64_t keep, Id id) {
-  __shared__ uint32_t s_hist[2048];
+// 31 set do not count.  Radix select from the top, over the `bits` bits that ids have here, at most 11 to a
+// pass and the same number in each.  0 < keep <= ids that count.
+// (Always 11 + 10 + 10 bits, the first pass over a million ids added everything to one counter: 76 000 entries
+// of two words 71 us, 32 this way, either with four reads in flight to a thread.)
+// ITEMS: reads in flight; one where a thread has few (with four, 17 selects of some 5 000 members took 14 us more).
+constexpr int KTH_BINS = 2048;
+
+template <int NT, int ITEMS, typename Id>
+__device__ int32_t p_kth_smallest_id(int64_t n, int64_t keep, int bits, Id id) {
+  __shared__ uint32_t s_hist[KTH_BINS];
   __shared__ uint32_t s_scan[NT / WAVE + 1];
   __shared__ uint32_t s_pick, s_below;
   uint32_t prefix = 0;
-  int shift = 20, bits = 11;
   uint32_t left = (uint32_t)keep;
-  for (int pass = 0; pass < 3; ++pass) {
-    for (int b = threadIdx.x; b < 2048; b += NT) s_hist[b] = 0;
+  int shift = bits;
+  for (int passes = (bits + 10) / 11; passes > 0; --passes) {
+    const int width = (shift + passes - 1) / passes, bins = 1 << width;
+    const int above = shift;               // the bits from here up are known
+    shift -= width;
+    for (int b = threadIdx.x; b < bins; b += NT) s_hist[b] = 0;
     if (threadIdx.x == 0) s_pick = s_below = 0;
     __syncthreads();
-    for (int64_t x = threadIdx.x; x < n; x += NT) {
-      const uint32_t v = id(x);
-      if (v >> 31) continue;
-      if (pass == 0 || (v >> (shift + bits)) == prefix) atomicAdd(&s_hist[(v >> shift) & ((1u << bits) - 1u)], 1u);
+    for (int64_t x0 = threadIdx.x; x0 < n; x0 += NT * ITEMS) {
+      uint32_t v[ITEMS];
+#pragma unroll
+      for (int k = 0; k < ITEMS; ++k) v[k] = id(x0 + k * NT < n ? x0 + k * NT : x0);
+#pragma unroll
+      for (int k = 0; k < ITEMS; ++k)
+        if (x0 + k * NT < n && !(v[k] >> 31) && (v[k] >> above) == prefix)
+          atomicAdd(&s_hist[(v[k] >> shift) & (uint32_t)(bins - 1)], 1u);
     }
     __syncthreads();
-    constexpr int PER = 2048 / NT;
+    constexpr int PER = KTH_BINS / NT;
     uint32_t mine = 0;
-    for (int b = 0; b < PER; ++b) mine += s_hist[threadIdx.x * PER + b];
+    for (int b = threadIdx.x * PER; b < (int)(threadIdx.x + 1) * PER && b < bins; ++b) mine += s_hist[b];
     uint32_t total;
     uint32_t run = block_exclusive_scan<uint32_t, NT>(mine, s_scan, total);
-    for (int b = 0; b < PER; ++b) {
-      const uint32_t c = s_hist[threadIdx.x * PER + b];
+    for (int b = threadIdx.x * PER; b < (int)(threadIdx.x + 1) * PER && b < bins; ++b) {
+      const uint32_t c = s_hist[b];
       if (run < left && run + c >= left) {
-        s_pick = (uint32_t)(threadIdx.x * PER + b);
+        s_pick = (uint32_t)b;
         s_below = run;
       }
       run += c;
     }
     __syncthreads();
-    prefix = (prefix << bits) | s_pick;
+    prefix = (prefix << width) | s_pick;
     left -= s_below;
-    shift -= 10;
-    bits = 10;
     __syncthreads();
   }
   return (int32_t)prefix;
@@ -391,7 +405,7 @@ __global__ __launch_bounds__(BIG) void k_cut_decide(Stays q, const int32_t* __re
   const CutChoice ch = cut_choice(c, room);
   int32_t T = -1;
   if (ch.keep > 0)
-    T = p_kth_smallest_id<BIG>(ch.n, ch.keep, [&](int64_t x) { return cut_member(q, ch.kind, region, room, x); });
+    T = p_kth_smallest_id<BIG, 1>(ch.n, ch.keep, q.id_bits, [&](int64_t x) { return cut_member(q, ch.kind, region, room, x); });
   cut_mark(q, c, ch.kind, T, region, room, threadIdx.x, BIG);
   __syncthreads();   // every thread has read the cut
   if (threadIdx.x == 0) {
@@ -476,12 +490,93 @@ __global__ __launch_bounds__(TB) void k_cut_wide(Stays q, const int32_t* __restr
   }
 }
 
+// ---- LRU ----------------------------------------------------------------------------------------------
+//
+// After iteration i the cache holds the `cap` rows that were accessed last, among those of one
+// iteration the ones with the smaller ids, as long as no iteration accesses more rows than the cache has lines
+// (then incoming rows of the running iteration would be dropped as well, before those that hit): what an
+// iteration drops are the last rows of that order, and a row only falls back in it until it is accessed again.  So
+// (last access, id) of the last row that stays, limits[i], says for every row whether it is there. Rows of C_0 that
+// are still to be accessed for the first time never go: C_0 is the first `cap` rows of the superbatch, so
+// nothing is missed before all of them were accessed.  limits[i] follows from how many rows accessed in
+// iteration t are accessed next after i, for all t <= i (sums over the histograms that Belady's thresholds
+// come from), and a select among the accesses of the one iteration that the limit falls into: all
+// iterations side by side.  A hit is an access whose row is not below the limit of the iteration before,
+// every miss is inserted, and the iteration that evicts a row is found by bisection.
+// 20 iterations of 76 000 accesses, 104 857 lines: the loop over the state, six launches an iteration, 1 347 us
+// a call, this way 765 (k_lru_limits 32, k_stays_mark 11, k_lru_walk 23, k_step_lines 20 x 13); 100 of 100 000 on
+// 30 M nodes, 0.85 M lines: 10.5 ms and 3.8.
+
+// The place of a row in the order, larger: stays longer.
+__device__ __forceinline__ uint64_t lru_key(uint32_t iteration, uint32_t v) {
+  return (uint64_t)iteration << 32 | (0x7FFFFFFFu - v);
+}
+
+// The iteration from i on that drops a row with this key, S if none.
+__device__ __forceinline__ int32_t lru_end(const uint64_t* limits, int32_t S, int32_t i, uint64_t key) {
+  int32_t lo = i, hi = S;
+  while (lo < hi) {
+    const int32_t mid = (lo + hi) >> 1;
+    if (limits[mid] > key) hi = mid; else lo = mid + 1;
+  }
+  return lo;
+}
+
+// hists[t][i] <- accesses of iteration t whose row is accessed next after iteration i.  A wave per t.
+__global__ __launch_bounds__(WAVE) void k_lru_counts(int32_t S, uint32_t* __restrict__ hists) {
+  uint32_t* row = hists + (int64_t)blockIdx.x * (S + 1);
+  const int lane = lane_id();
+  uint32_t behind = 0;
+  for (int32_t r0 = 0; r0 <= S; r0 += WAVE) {      // from the right
+    const int32_t j = S - r0 - lane;
+    const uint32_t c = j >= 0 ? row[j] : 0u;
+    const uint32_t incl = wave_inclusive_scan(c);
+    if (j >= 0) row[j] = behind + incl - c;
+    behind += __shfl(incl, WAVE - 1, WAVE);
+  }
+}
+
+// A block per iteration: the iteration whose rows are the last to stay, and which of them do.
+__global__ __launch_bounds__(BIG) void k_lru_limits(Stays q, const uint32_t* __restrict__ counts, int64_t cap,
+                                                    uint64_t* __restrict__ limits) {
+  __shared__ int64_t smem[BIG / WAVE + 1];
+  __shared__ int32_t s_t;
+  __shared__ int64_t s_keep;
+  const int32_t i = blockIdx.x;
+  if (threadIdx.x == 0) s_t = -1;
+  int64_t before = 0;
+  for (int32_t r0 = 0; r0 <= i && before <= cap; r0 += BIG) {   // uniform; from iteration i downwards
+    const int32_t t = i - r0 - (int32_t)threadIdx.x;
+    const int64_t c = t >= 0 ? counts[(int64_t)t * (q.S + 1) + i] : 0;
+    int64_t total;
+    const int64_t ahead = before + block_exclusive_scan<int64_t, BIG>(c, smem, total);
+    if (ahead <= cap && ahead + c > cap) {         // (one thread at most)
+      s_t = t;
+      s_keep = cap - ahead;
+    }
+    before += total;
+    __syncthreads();
+  }
+  const int32_t t = s_t;
+  if (t < 0 || s_keep == 0) {                      // uniform: nothing has to go, or all rows of t
+    if (threadIdx.x == 0) limits[i] = (uint64_t)(t + 1) << 32;
+    return;
+  }
+  const int64_t to = q.off[t], n = q.off[t + 1] - to;
+  const int32_t T = p_kth_smallest_id<BIG, 4>(n, s_keep, q.id_bits, [&](int64_t x) {
+    const uint32_t v = (uint32_t)q.ids[to + x];    // (both reads at once)
+    return stay_next(q.ends[to + x]) > i ? v : 0x80000000u;
+  });
+  if (threadIdx.x == 0) limits[i] = lru_key((uint32_t)t, (uint32_t)T);
+}
+
 // ---- the lists and the evicting iterations ----------------------------------------------------------
 
 // Every access: hit or miss (src_line: 0 / -1, the lines follow), and whether a miss is an insertion
 // (bit p of ins_bits).  A miss that is never accessed again is none: where
 // bucket "never" is the one that is cut, the iteration drops as many rows as it has misses, incoming
 // rows of the bucket first.
+template <bool LRU>
 __global__ __launch_bounds__(TB) void k_stays_mark(Stays q, int64_t n, int32_t* __restrict__ src_line,
                                                    uint32_t* __restrict__ ins_bits) {
   extern __shared__ int32_t lds_off[];
@@ -501,13 +596,21 @@ __global__ __launch_bounds__(TB) void k_stays_mark(Stays q, int64_t n, int32_t* 
     if (p < n) {
       while (i + 1 < q.S && lds_off[i + 1] <= (int32_t)p) ++i;
       const uint32_t prev = stay_prev(w[k]);
-      if (prev != NO_STAY) {
+      if (LRU) {
+        hit = prev == FROM_START;
+        if (prev < FROM_START) {
+          const uint64_t limit = q.limits[i > 0 ? i - 1 : 0];   // (i > 0: an earlier iteration accessed the row)
+          hit = prev == (uint32_t)(limit >> 32) ? lru_key(prev, (uint32_t)q.ids[p]) >= limit
+                                                : prev > (uint32_t)(limit >> 32);
+        }
+        inserted = !hit;
+      } else if (prev != NO_STAY) {
         const uint32_t e = q.table[(int64_t)i * q.S + (prev == FROM_START ? 0u : prev)];
         // (the id is read only where a cut has to be looked at)
         hit = (e >> 16) == NO_CUT ? (int32_t)(e & 0xFFFFu) == i
                                   : stay_hits(q, w[k], i, (uint32_t)q.ids[p]);
       }
-      if (!hit) {
+      if (!LRU && !hit) {
         const Cut c = q.cuts[i];
         const int32_t next = stay_next(w[k]);
         inserted = stay_inserts(q, c, next, next == c.jstar ? (uint32_t)q.ids[p] : 0u);
@@ -899,10 +1002,11 @@ __global__ __launch_bounds__(TB) void k_stays_links(Stays q, const uint64_t* __r
   }
 }
 
-// insertions of iteration i = set bits of its positions (blockIdx.x = i)
+// insertions of iteration i = set bits of its positions (blockIdx.x = i); miss_count: where all misses are inserted
 __global__ __launch_bounds__(TB) void k_ins_count(const uint32_t* __restrict__ ins_bits,
                                                   const int64_t* __restrict__ off,
-                                                  int64_t* __restrict__ cs_offsets) {
+                                                  int64_t* __restrict__ cs_offsets,
+                                                  int64_t* __restrict__ miss_count) {
   __shared__ uint32_t red[TB / WAVE];
   const int64_t lo = off[blockIdx.x], hi = off[blockIdx.x + 1];
   uint32_t cnt = 0;
@@ -914,7 +1018,10 @@ __global__ __launch_bounds__(TB) void k_ins_count(const uint32_t* __restrict__ i
       cnt += __popc(word);
     }
   const uint32_t total = block_sum_u32(cnt, red);
-  if (threadIdx.x == 0) cs_offsets[blockIdx.x + 1] = total;
+  if (threadIdx.x == 0) {
+    cs_offsets[blockIdx.x + 1] = total;
+    if (miss_count) miss_count[blockIdx.x] = total;
+  }
 }
 
 // cs_offsets[1 .. S] <- inclusive sums
@@ -1041,6 +1148,102 @@ __global__ __launch_bounds__(TB) void k_stays_walk(Stays q, const uint64_t* __re
     const uint64_t before = k > 0 ? shfl_u64(cur[k > 0 ? k - 1 : 0], WAVE - 1) : left_of;
     if (lane == 0) lv = (uint32_t)(before >> 32);
     if ((hit[k] >> lane & 1) && lv != v) leave_start[addr[v]] = leaves;
+    carry = __shfl(leaves, 0, WAVE);
+  }
+}
+
+// The same for LRU, where hits follow from the limits (copied to LDS) and the neighbour in node order, so that one
+// pass does what k_stays_links and the kernel above do.
+__global__ __launch_bounds__(TB) void k_lru_walk(Stays q, const uint64_t* __restrict__ sorted, int64_t n,
+                                                 const uint64_t* __restrict__ last_head,
+                                                 const int32_t* __restrict__ addr,
+                                                 const uint32_t* __restrict__ ins_bits,
+                                                 const uint32_t* __restrict__ ins_base,
+                                                 uint32_t* __restrict__ leave_ins,
+                                                 uint32_t* __restrict__ leave_start) {
+  extern __shared__ uint64_t lds_limits[];         // [S], then the offsets [S + 1]
+  int32_t* const lds_off = reinterpret_cast<int32_t*>(lds_limits + q.S);
+  for (int x = threadIdx.x; x < q.S; x += TB) lds_limits[x] = q.limits[x];
+  load_offsets(lds_off, q.off, q.S);
+  const int lane = lane_id();
+  const int64_t base = ((int64_t)blockIdx.x * (TB / WAVE) + threadIdx.x / WAVE) * (WAVE * WALK_CHUNKS);
+  if (base >= n) return;                           // uniform over the wave
+  auto iteration = [&](uint64_t pair) {
+    return (pair >> 32) != 0xFFFFFFFFull ? iter_of(lds_off, q.S, (int32_t)(uint32_t)pair) : q.S;
+  };
+  // the stay of an access of row v in iteration i reaches the row's next access, in iteration j
+  auto reaches = [&](uint32_t v, int32_t i, int32_t j) { return lru_key((uint32_t)i, v) >= lds_limits[j > 0 ? j - 1 : 0]; };
+  auto leaves_at = [&](uint32_t v, int32_t i) {
+    const int32_t e = lru_end(lds_limits, q.S, i, lru_key((uint32_t)i, v));
+    return e < q.S ? (uint32_t)e : STAYS;
+  };
+  uint64_t cur[WALK_CHUNKS + 1];                   // behind n: an id that no access has
+  int32_t it[WALK_CHUNKS + 1];
+#pragma unroll
+  for (int k = 0; k <= WALK_CHUNKS; ++k) {
+    const int64_t x = base + k * WAVE + (k < WALK_CHUNKS ? lane : 0);
+    cur[k] = x < n ? sorted[x] : ~0ull;
+  }
+  const uint64_t left_of = base > 0 ? sorted[base - 1] : ~0ull;
+#pragma unroll
+  for (int k = 0; k <= WALK_CHUNKS; ++k) it[k] = iteration(cur[k]);
+  uint64_t stops[WALK_CHUNKS];                     // the stays that do not reach a hit
+  uint32_t leave_of[WALK_CHUNKS];
+#pragma unroll
+  for (int k = 0; k < WALK_CHUNKS; ++k) {
+    const uint32_t v = (uint32_t)(cur[k] >> 32);
+    uint32_t rv = __shfl_down(v, 1, WAVE);
+    int32_t rj = __shfl_down(it[k], 1, WAVE);
+    const uint32_t ov = __shfl((uint32_t)(cur[k + 1] >> 32), 0, WAVE);
+    const int32_t oj = __shfl(it[k + 1], 0, WAVE);
+    if (lane == WAVE - 1) {
+      rv = ov;
+      rj = oj;
+    }
+    const bool valid = v != 0xFFFFFFFFu;
+    const bool end = !(valid && rv == v && reaches(v, it[k], rj));
+    stops[k] = __ballot(end);
+    leave_of[k] = valid && end ? leaves_at(v, it[k]) : STAYS;
+  }
+  bool left_reaches = false;                       // (uniform: chunk 0's first pair is in range)
+  {
+    const uint32_t v = __shfl((uint32_t)(cur[0] >> 32), 0, WAVE);
+    if ((uint32_t)(left_of >> 32) == v) left_reaches = reaches(v, iteration(left_of), __shfl(it[0], 0, WAVE));
+  }
+  uint32_t carry = STAYS;
+#pragma unroll
+  for (int k = WALK_CHUNKS - 1; k >= 0; --k) {
+    if (k == WALK_CHUNKS - 1 && !(stops[k] >> (WAVE - 1))) {
+      // the stretch's last access is linked to the next stretch: on to the row's next stay that ends
+      for (int64_t ahead = base + WALK_CHUNKS * WAVE; ; ahead += WAVE) {
+        const int64_t y = ahead + lane;
+        const uint64_t a = y < n ? sorted[y] : ~0ull, r = y + 1 < n ? sorted[y + 1] : ~0ull;
+        const int32_t i = iteration(a);
+        const bool end = !(y + 1 < n && (r >> 32) == (a >> 32) && reaches((uint32_t)(a >> 32), i, iteration(r)));
+        const uint64_t m = __ballot(end);
+        if (!m) continue;                          // (an access at or behind n ends)
+        const int at = __ffsll((unsigned long long)m) - 1;
+        uint32_t leaves = STAYS;
+        if (lane == at && y < n) leaves = leaves_at((uint32_t)(a >> 32), i);
+        carry = __shfl(leaves, at, WAVE);
+        break;
+      }
+    }
+    const uint64_t mine = stops[k] >> lane;        // stays that end, from this lane's on
+    const uint32_t found = __shfl(leave_of[k], mine ? lane + __ffsll((unsigned long long)mine) - 1 : lane, WAVE);
+    const uint32_t leaves = mine ? found : carry;
+    const uint32_t v = (uint32_t)(cur[k] >> 32), p = (uint32_t)cur[k];
+    uint32_t lv = (uint32_t)__shfl_up(v, 1, WAVE);
+    const uint64_t before = k > 0 ? shfl_u64(cur[k > 0 ? k - 1 : 0], WAVE - 1) : left_of;
+    bool linked = lane > 0 ? !(stops[k] >> (lane - 1) & 1) : k > 0 ? !(stops[k > 0 ? k - 1 : 0] >> (WAVE - 1)) : left_reaches;
+    if (lane == 0) lv = (uint32_t)(before >> 32);
+    if (v != 0xFFFFFFFFu) {
+      if (lv == v ? !linked : !in_start_state(v, it[k], last_head, nullptr))   // a miss: inserted
+        leave_ins[ins_base[p >> 5] + __popc(ins_bits[p >> 5] & ((1u << (p & 31)) - 1u))] =
+            leaves == (uint32_t)(it[k] + 1) ? LEAVES_NEXT : leaves;
+      else if (lv != v)                            // a first access that hits is one of a start-state row
+        leave_start[addr[v]] = leaves;
+    }
     carry = __shfl(leaves, 0, WAVE);
   }
 }
