@@ -1,0 +1,344 @@
+// A fresh cache that holds every row of the superbatch, without a sort.  Included by changeset.hip only.
+//
+// Nothing is ever missed then: C_0 is all distinct rows by (first access, id), and every access finds its row in
+// the line of that rank.  Which iteration accesses a row first and what its rank is takes no order among the
+// accesses of a row, so the ids are only dealt to buckets, 2^shift neighbouring ids each, small enough for a bitmap
+// and the lines of a bucket's rows in LDS:
+//   k_fit_deal   a block per tile of FIT_TILE accesses of an iteration: sorts them by bucket in LDS, writes ids
+//                and their places in the tile in that order, and the start of every bucket inside the tile
+//   k_fit_rows   a block per bucket: the bits of its ids, then the first iteration of every row (the smallest), then
+//                its rank among the bucket's rows of that iteration
+//   (scan of the numbers of new rows by iteration, then bucket: the rank of each of these lists' pieces)
+//   k_fit_lines  a block per bucket: line of every row into LDS, C_0; then of every access, in the tiles' order
+//   k_fit_place  a block per tile: the lines back in the order of the accesses
+// 33 M accesses, 9 M rows of 111 M nodes, 200 iterations: k_fit_deal 79 us (4 bytes read and 6 written per access,
+// 4.2 TB/s), k_fit_rows 253 and k_fit_lines 191 (7.4 M shares of four or five ids, the latency of their reads),
+// k_fit_place 53; 729 a call.  Through the sorted accesses 2 004: four radix passes 0.72 ms, heads 0.23, the rows' lines
+// scattered to a table over all nodes and looked up there for every access 0.82 (random words).
+// (A wave per bucket that takes the iterations one after the other, without a table of first iterations: 626 us for
+// k_fit_rows, 83 000 vector instructions in a chain of 6 per CU.)
+#pragma once
+
+// An id to a bucket of a tile on the mean, below which nearly all of the work is looking at empty shares.  No lower
+// limit on the accesses otherwise (2 iterations of 500: 206 -> 160 us, 8 of 4 000 on 16 384 nodes 204 -> 178).
+constexpr int64_t FIT_SHARE_MIN = 1;
+constexpr int64_t FIT_GUESS_MIN = 1 << 20;             // see changeset_run
+
+constexpr int FIT_THREADS = 512;
+constexpr int FIT_ITEMS = 16;
+constexpr int FIT_TILE = FIT_THREADS * FIT_ITEMS;
+constexpr int FIT_SHIFT_MIN = 11, FIT_SHIFT_MAX = 16;  // ids of a bucket: ranks among them have 16 bits
+constexpr int FIT_BUCKETS = 4096;                      // at most, 2^28 nodes
+constexpr int FIT_LINE_THREADS = 1024;
+constexpr int FIT_ROWS = 7168;                         // rows of a bucket in LDS at a time (above: 5 300)
+constexpr int FIT_SHARES = 2048;                       // tiles whose shares are laid out at a time
+constexpr int FIT_SHARE_LANES = 8, FIT_SHARE_ITEMS = 4;
+
+constexpr uint32_t FIT_DONE = 0x80000000u;             // a line in the place of an id (both are below 2^31)
+
+struct Fit {
+  const int64_t* off;      // [S + 1]
+  uint32_t* ids;           // [total] the ids of a tile by bucket, at the tile's own place; later their lines
+  uint16_t* rank;          // [total] their places in the tile
+  uint16_t* start;         // [tiles][buckets + 1] start of every bucket inside the tile
+  uint32_t* counts;        // [S][buckets] new rows, later the sum of all in front; and one more
+  uint32_t* list;          // [buckets][2^shift] of a row, in id order: first iteration << 16 | rank in it and the bucket
+  uint32_t* bits;          // [words] rows accessed, by id
+  uint32_t* bad;           // set where an id is out of range
+  int64_t num_nodes, words;
+  int32_t S, per_iteration, tiles;   // tiles of an iteration, of all
+  int32_t buckets, shift;
+};
+
+inline int32_t fit_shift(int64_t num_nodes) {
+  int32_t shift = FIT_SHIFT_MIN;
+  while (shift < FIT_SHIFT_MAX && ceil_div(num_nodes, int64_t(1) << shift) > FIT_BUCKETS / 2) ++shift;
+  return shift;
+}
+
+// neighbouring buckets on one XCD (blocks go to the eight XCDs in turn), as their shares share cache lines
+__device__ __forceinline__ int32_t fit_bucket() { return blockIdx.x % 8 * (gridDim.x / 8) + blockIdx.x / 8; }
+
+__global__ __launch_bounds__(FIT_THREADS) void k_fit_deal(Fit f, const int32_t* __restrict__ ids) {
+  extern __shared__ uint32_t s_count[];              // [buckets]
+  __shared__ uint32_t s_id[FIT_TILE];
+  __shared__ uint16_t s_rank[FIT_TILE];
+  __shared__ uint32_t smem[FIT_THREADS / WAVE + 1];
+  const int64_t pos = f.off[blockIdx.y] + (int64_t)blockIdx.x * FIT_TILE, left = f.off[blockIdx.y + 1] - pos;
+  const int32_t n = left < 0 ? 0 : left < FIT_TILE ? (int32_t)left : FIT_TILE;
+  for (int q = threadIdx.x; q < f.buckets; q += FIT_THREADS) s_count[q] = 0;
+  __syncthreads();
+  uint32_t v[FIT_ITEMS], at[FIT_ITEMS];              // at: bucket << 16 | place among the tile's ids of the bucket
+#pragma unroll
+  for (int k = 0; k < FIT_ITEMS; ++k) {
+    const int32_t x = k * FIT_THREADS + threadIdx.x;
+    v[k] = x < n ? (uint32_t)ids[pos + x] : 0u;
+  }
+#pragma unroll
+  for (int k = 0; k < FIT_ITEMS; ++k) {
+    if (k * FIT_THREADS + (int32_t)threadIdx.x >= n) continue;
+    uint32_t q = v[k] >> f.shift;
+    if (v[k] >= (uint64_t)f.num_nodes) *f.bad = 1;
+    if (q >= (uint32_t)f.buckets) q = f.buckets - 1;   // (stays inside the arrays)
+    at[k] = q << 16 | atomicAdd(&s_count[q], 1u);
+  }
+  __syncthreads();
+  // (buckets are at most eight to a thread)
+  const int32_t per = (f.buckets + FIT_THREADS - 1) / FIT_THREADS, q0 = threadIdx.x * per;
+  uint32_t mine = 0;
+  for (int32_t q = q0; q < q0 + per && q < f.buckets; ++q) mine += s_count[q];
+  uint32_t total;
+  uint32_t run = block_exclusive_scan<uint32_t, FIT_THREADS>(mine, smem, total);
+  uint16_t* const start = f.start + ((int64_t)blockIdx.y * f.per_iteration + blockIdx.x) * (f.buckets + 1);
+  for (int32_t q = q0; q < q0 + per && q < f.buckets; ++q) {
+    const uint32_t c = s_count[q];
+    s_count[q] = run;
+    run += c;
+  }
+  __syncthreads();
+  for (int q = threadIdx.x; q < f.buckets; q += FIT_THREADS) start[q] = (uint16_t)s_count[q];
+  if (threadIdx.x == 0) start[f.buckets] = (uint16_t)total;
+#pragma unroll
+  for (int k = 0; k < FIT_ITEMS; ++k) {
+    if (k * FIT_THREADS + (int32_t)threadIdx.x >= n) continue;
+    const uint32_t x = s_count[at[k] >> 16] + (at[k] & 0xFFFFu);
+    s_id[x] = v[k];
+    s_rank[x] = (uint16_t)(k * FIT_THREADS + threadIdx.x);
+  }
+  __syncthreads();
+  for (int32_t x = threadIdx.x; x < n; x += FIT_THREADS) {
+    f.ids[pos + x] = s_id[x];
+    f.rank[pos + x] = s_rank[x];
+  }
+}
+
+// What the two kernels that take a bucket each have in LDS.
+struct FitLds {
+  uint32_t* bits;            // [words of the bucket] its rows
+  uint32_t* row;             // [FIT_ROWS] of a row, by its rank in the bucket: first iteration, or line
+  uint32_t* at;              // [FIT_SHARES] a tile's share: its place among all accesses ...
+  uint32_t* share;           // [FIT_SHARES] ... entries | iteration << 16
+  uint16_t* base;            // [words] rows in front of the word (a bucket has at most 2^16)
+  uint32_t* rest;
+};
+__device__ __forceinline__ FitLds fit_lds(uint32_t* lds, const Fit& f) {
+  const int32_t words = 1 << (f.shift - 5);
+  uint32_t* const row = lds + words;
+  uint32_t* const at = row + FIT_ROWS;
+  uint32_t* const base = at + 2 * FIT_SHARES;
+  return {lds, row, at, at + FIT_SHARES, reinterpret_cast<uint16_t*>(base), base + words / 2};
+}
+__device__ __forceinline__ uint32_t fit_rank(const FitLds& l, uint32_t v) {
+  return l.base[v >> 5] + __popc(l.bits[v >> 5] & ((1u << (v & 31)) - 1u));
+}
+
+// fn(place among all accesses, what is there, iteration) for the bucket's share of every tile, by the block: a share
+// (five ids on the mean where there are most buckets) to a group of lanes.
+template <typename Fn>
+__device__ __forceinline__ void fit_shares(const Fit& f, int32_t q, const FitLds& l, const Fn& fn) {
+  constexpr int GROUPS = FIT_LINE_THREADS / FIT_SHARE_LANES;
+  static_assert(FIT_SHARES == 2 * FIT_LINE_THREADS, "two tiles to a thread");
+  const int32_t sub = threadIdx.x % FIT_SHARE_LANES;
+  uint32_t at[2], share[2];
+  auto request = [&](int32_t t0) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int32_t t = t0 + h * FIT_LINE_THREADS + threadIdx.x;
+      at[h] = share[h] = 0;
+      if (t >= f.tiles) continue;
+      const uint16_t* start = f.start + (int64_t)t * (f.buckets + 1) + q;
+      const uint32_t lo = start[0], hi = start[1];
+      const int32_t i = t / f.per_iteration;
+      at[h] = (uint32_t)f.off[i] + (uint32_t)((t - i * f.per_iteration) * FIT_TILE) + lo;
+      share[h] = (hi - lo) | (uint32_t)i << 16;
+    }
+  };
+  request(0);
+  for (int32_t t0 = 0; t0 < f.tiles; t0 += FIT_SHARES) {
+    const int32_t n = f.tiles - t0 < FIT_SHARES ? f.tiles - t0 : FIT_SHARES;
+    __syncthreads();                                 // what the calls need is there, the shares are free
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      l.at[h * FIT_LINE_THREADS + threadIdx.x] = at[h];
+      l.share[h * FIT_LINE_THREADS + threadIdx.x] = share[h];
+    }
+    __syncthreads();
+    request(t0 + FIT_SHARES);
+    for (int32_t g = threadIdx.x / FIT_SHARE_LANES; g < n; g += GROUPS * FIT_SHARE_ITEMS) {
+      uint32_t id[FIT_SHARE_ITEMS], p[FIT_SHARE_ITEMS], sh[FIT_SHARE_ITEMS];
+#pragma unroll
+      for (int k = 0; k < FIT_SHARE_ITEMS; ++k) {    // (FIT_SHARES is a multiple of the groups' stride)
+        p[k] = l.at[g + k * GROUPS] + sub;
+        sh[k] = l.share[g + k * GROUPS];
+        if (sub < (int32_t)(sh[k] & 0xFFFFu)) id[k] = f.ids[p[k]];
+      }
+#pragma unroll
+      for (int k = 0; k < FIT_SHARE_ITEMS; ++k) {
+        const int32_t entries = sh[k] & 0xFFFFu, i = sh[k] >> 16;
+        if (sub < entries) fn(p[k], id[k], i);
+        for (int32_t e = FIT_SHARE_LANES; e + sub < entries; e += FIT_SHARE_LANES) fn(p[k] + e, f.ids[p[k] + e], i);
+      }
+    }
+  }
+  __syncthreads();
+}
+static_assert(FIT_SHARES % (FIT_LINE_THREADS / FIT_SHARE_LANES * FIT_SHARE_ITEMS) == 0, "whole rounds");
+
+// The rows in front of every word, from s_bits; returns their number.
+__device__ __forceinline__ uint32_t fit_bases(const Fit& f, const FitLds& l, uint32_t* smem) {
+  static_assert((1 << (FIT_SHIFT_MAX - 5)) <= 2 * FIT_LINE_THREADS, "two words to a thread");
+  const int32_t w = 2 * threadIdx.x, words = 1 << (f.shift - 5);
+  const uint32_t a = w < words ? __popc(l.bits[w]) : 0u, b = w < words ? __popc(l.bits[w + 1]) : 0u;
+  uint32_t total;
+  const uint32_t at = block_exclusive_scan<uint32_t, FIT_LINE_THREADS>(a + b, smem, total);
+  if (w < words) {
+    l.base[w] = (uint16_t)at;
+    l.base[w + 1] = (uint16_t)(at + a);
+  }
+  return total;
+}
+
+// Where a wave's counters of k_fit_rows sit: 16 bits per iteration, in the room of the shares, so fewer waves rank where there are many iterations.
+__host__ __device__ __forceinline__ int32_t fit_rank_waves(int32_t S) {
+  const int32_t waves = 2 * FIT_SHARES * 2 / S;
+  return waves < FIT_LINE_THREADS / WAVE ? waves : FIT_LINE_THREADS / WAVE;
+}
+
+__global__ __launch_bounds__(FIT_LINE_THREADS) __attribute__((amdgpu_waves_per_eu(8))) void k_fit_rows(Fit f) {
+  extern __shared__ uint32_t lds[];
+  __shared__ uint32_t smem[FIT_LINE_THREADS / WAVE + 1];
+  const int32_t q = fit_bucket();
+  if (q >= f.buckets) return;
+  const FitLds l = fit_lds(lds, f);
+  const int32_t words = 1 << (f.shift - 5);
+  const uint32_t mask = (1u << f.shift) - 1u;
+  for (int32_t w = threadIdx.x; w < words; w += FIT_LINE_THREADS) l.bits[w] = 0;
+  if (q == 0 && threadIdx.x == 0) f.counts[(int64_t)f.S * f.buckets] = 0;
+  fit_shares(f, q, l, [&](uint32_t, uint32_t id, int32_t) {
+    const uint32_t v = id & mask;
+    atomicOr(&l.bits[v >> 5], 1u << (v & 31));
+  });
+  const int64_t word0 = ((int64_t)q << f.shift) >> 5;
+  for (int32_t w = threadIdx.x; w < words; w += FIT_LINE_THREADS) {
+    if (word0 + w < f.words) f.bits[word0 + w] = l.bits[w];
+    else l.bits[w] = 0;                              // (an id out of range)
+  }
+  __syncthreads();
+  const uint32_t rows = fit_bases(f, l, smem);
+  uint32_t* const seen = f.counts + q;               // rows of an iteration, in the slices so far: at seen[i * buckets]
+  for (int32_t i = threadIdx.x; i < f.S; i += FIT_LINE_THREADS) seen[(int64_t)i * f.buckets] = 0;
+  uint16_t* const s_count = reinterpret_cast<uint16_t*>(l.at);   // [waves][S]
+  const int32_t waves = fit_rank_waves(f.S), wave = threadIdx.x / WAVE, lane = lane_id();
+  const int32_t bits = 32 - __clz(f.S);
+  for (uint32_t from = 0; from < rows; from += FIT_ROWS) {   // more rows than fit LDS: in slices by id
+    const int32_t n = rows - from < FIT_ROWS ? (int32_t)(rows - from) : FIT_ROWS;
+    for (int32_t r = threadIdx.x; r < n; r += FIT_LINE_THREADS) l.row[r] = 0xFFFFFFFFu;
+    fit_shares(f, q, l, [&](uint32_t, uint32_t id, int32_t i) {
+      const uint32_t r = fit_rank(l, id & mask) - from;      // (wraps below)
+      if (r < (uint32_t)n && l.row[r] > (uint32_t)i) atomicMin(&l.row[r], (uint32_t)i);
+    });
+    // every row's rank among the rows of its first iteration: a wave takes a stretch of rows, twice, for
+    // the iterations' numbers in it and, with those of the stretches in front, for the ranks
+    for (int32_t x = threadIdx.x; x < waves * f.S; x += FIT_LINE_THREADS) s_count[x] = 0;
+    __syncthreads();
+    const int32_t stretch = ((n + waves - 1) / waves + WAVE - 1) / WAVE * WAVE;
+    uint16_t* const mine = s_count + wave * f.S;
+    for (int pass = 0; pass < 2; ++pass) {
+      if (wave < waves)
+        for (int32_t r0 = wave * stretch; r0 < (wave + 1) * stretch && r0 < n; r0 += WAVE) {
+          const int32_t r = r0 + lane;
+          const uint32_t i = r < n ? l.row[r] : 0u;
+          uint64_t peers = __ballot(r < n);
+          for (int b = 0; b < bits; ++b) {
+            const uint64_t m = __ballot((i >> b) & 1);
+            peers &= (i >> b) & 1 ? m : ~m;
+          }
+          if (r < n) {
+            const uint32_t before = __popcll(peers & ((1ull << lane) - 1));
+            const uint32_t rank = mine[i] + before;  // (read by all lanes before the last of them writes)
+            if (before + 1 == (uint32_t)__popcll(peers)) mine[i] = (uint16_t)(rank + 1);
+            if (pass) f.list[((int64_t)q << f.shift) + from + r] = i << 16 | rank;
+          }
+        }
+      __syncthreads();
+      if (pass) continue;
+      for (int32_t i = threadIdx.x; i < f.S; i += FIT_LINE_THREADS) {
+        uint32_t run = seen[(int64_t)i * f.buckets];
+        for (int32_t w = 0; w < waves; ++w) {
+          const uint32_t c = s_count[w * f.S + i];
+          s_count[w * f.S + i] = (uint16_t)run;
+          run += c;
+        }
+        seen[(int64_t)i * f.buckets] = run;
+      }
+      __syncthreads();
+    }
+  }
+}
+
+// ready[i] = rows first accessed in iterations 0..i, -1: an id was out of range
+__global__ __launch_bounds__(TB) void k_fit_ready(Fit f, int64_t* __restrict__ ready) {
+  const int32_t i = blockIdx.x * TB + threadIdx.x;
+  if (i < f.S) ready[i] = *f.bad ? -1 : (int64_t)f.counts[(int64_t)(i + 1) * f.buckets];
+}
+
+constexpr size_t FIT_LDS = 65000;                    // at most (k_fit_lines; iterations: up to some 1 900)
+inline size_t fit_rows_lds(const Fit& f) { return 6 * ((size_t)1 << (f.shift - 5)) + sizeof(uint32_t) * (FIT_ROWS + 2 * FIT_SHARES); }
+inline size_t fit_lines_lds(const Fit& f) { return fit_rows_lds(f) + sizeof(uint32_t) * f.S; }
+
+// with_lines: C_0 alone, or every access's line, too
+__global__ __launch_bounds__(FIT_LINE_THREADS) __attribute__((amdgpu_waves_per_eu(8))) void k_fit_lines(Fit f, int32_t* __restrict__ init_ids, bool with_lines) {
+  extern __shared__ uint32_t lds[];
+  __shared__ uint32_t smem[FIT_LINE_THREADS / WAVE + 1];
+  const int32_t q = fit_bucket();
+  if (q >= f.buckets) return;
+  const FitLds l = fit_lds(lds, f);
+  uint32_t* const s_first = l.rest;                  // [S] line of the bucket's first row of the iteration
+  const int32_t words = 1 << (f.shift - 5);
+  const uint32_t mask = (1u << f.shift) - 1u;
+  const int64_t word0 = ((int64_t)q << f.shift) >> 5;
+  for (int32_t w = threadIdx.x; w < words; w += FIT_LINE_THREADS) l.bits[w] = word0 + w < f.words ? f.bits[word0 + w] : 0u;
+  for (int32_t i = threadIdx.x; i < f.S; i += FIT_LINE_THREADS) s_first[i] = f.counts[(int64_t)i * f.buckets + q];
+  __syncthreads();
+  const uint32_t rows = fit_bases(f, l, smem);
+  const uint32_t* const list = f.list + ((int64_t)q << f.shift);
+  for (uint32_t from = 0; from < rows; from += FIT_ROWS) {   // more rows than fit LDS: in slices by id
+    const uint32_t n = rows - from < FIT_ROWS ? rows - from : FIT_ROWS;
+    for (uint32_t r = threadIdx.x; r < n; r += FIT_LINE_THREADS) {
+      const uint32_t row = list[from + r];
+      l.row[r] = s_first[row >> 16] + (row & 0xFFFFu);
+    }
+    __syncthreads();
+    for (int32_t w = threadIdx.x; w < words; w += FIT_LINE_THREADS) {
+      uint32_t r = l.base[w] - from;                 // (wraps below)
+      for (uint32_t left = l.bits[w]; left; left &= left - 1, ++r)
+        if (r < n) init_ids[l.row[r]] = (int32_t)(((uint32_t)q << f.shift) + (uint32_t)(w * 32 + __ffs(left) - 1));
+    }
+    if (with_lines)                                  // (a line in the place of an id: not an id of a later slice)
+      fit_shares(f, q, l, [&](uint32_t at, uint32_t id, int32_t) {
+        const uint32_t r = fit_rank(l, id & mask) - from;
+        if (r < n && !(id & FIT_DONE)) f.ids[at] = l.row[r] | FIT_DONE;
+      });
+    __syncthreads();
+  }
+}
+
+__global__ __launch_bounds__(FIT_THREADS) void k_fit_place(Fit f, int32_t* __restrict__ src_line) {
+  __shared__ uint32_t s_line[FIT_TILE];
+  const int64_t pos = f.off[blockIdx.y] + (int64_t)blockIdx.x * FIT_TILE, left = f.off[blockIdx.y + 1] - pos;
+  const int32_t n = left < 0 ? 0 : left < FIT_TILE ? (int32_t)left : FIT_TILE;
+  uint32_t line[FIT_ITEMS], rank[FIT_ITEMS];
+#pragma unroll
+  for (int k = 0; k < FIT_ITEMS; ++k) {
+    const int32_t x = k * FIT_THREADS + threadIdx.x;
+    if (x < n) {
+      line[k] = f.ids[pos + x];
+      rank[k] = f.rank[pos + x];
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < FIT_ITEMS; ++k)
+    if (k * FIT_THREADS + (int32_t)threadIdx.x < n) s_line[rank[k]] = line[k] & ~FIT_DONE;
+  __syncthreads();
+  for (int32_t x = threadIdx.x; x < n; x += FIT_THREADS) src_line[pos + x] = (int32_t)s_line[x];
+}
