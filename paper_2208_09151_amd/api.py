@@ -240,8 +240,8 @@ def changeset(num_nodes, ids, ids_offsets, cap, workspace=None, policy="belady",
     in_ids = torch.empty(cs_cap, dtype=torch.int32, device=dev)
     out_ids = torch.empty(cs_cap, dtype=torch.int32, device=dev)
     in_pos = torch.empty(cs_cap, dtype=torch.int32, device=dev)
-    cs_off = torch.empty(S + 1, dtype=torch.int64, device=dev)
-    miss = torch.empty(max(S, 1), dtype=torch.int64, device=dev)
+    small = torch.empty(S + 1 + max(S, 1), dtype=torch.int64, device=dev)
+    cs_off, miss = small[:S + 1], small[S + 1:]     # (one copy to the host for both)
     init_count = np.zeros(1, dtype=np.int64)
     total_changes = np.zeros(1, dtype=np.int64)
     init_ready = np.zeros(max(S, 1), dtype=np.int64)
@@ -258,8 +258,9 @@ def changeset(num_nodes, ids, ids_offsets, cap, workspace=None, policy="belady",
                    _np_ptr(init_ready), _ptr(ws), ws.numel(), _stream())
     _check(rc)
     n = int(total_changes[0])
+    small = small.cpu().numpy()
     return ChangesetResult(init_ids[:int(init_count[0])], in_ids[:n], out_ids[:n], in_pos[:n],
-                           cs_off.cpu().numpy(), miss[:S].cpu().numpy(), init_ready[:S],
+                           small[:S + 1], small[S + 1:2 * S + 1], init_ready[:S],
                            src_line=lines[:total] if with_lines else None)
 
 
@@ -284,8 +285,8 @@ def changeset_resume(num_nodes, ids, ids_offsets, start_ids, workspace=None, wit
     in_ids = torch.empty(cs_cap, dtype=torch.int32, device=dev)
     out_ids = torch.empty(cs_cap, dtype=torch.int32, device=dev)
     in_pos = torch.empty(cs_cap, dtype=torch.int32, device=dev)
-    cs_off = torch.empty(S + 1, dtype=torch.int64, device=dev)
-    miss = torch.empty(max(S, 1), dtype=torch.int64, device=dev)
+    small = torch.empty(S + 1 + max(S, 1), dtype=torch.int64, device=dev)
+    cs_off, miss = small[:S + 1], small[S + 1:]     # (one copy to the host for both)
     total_changes = np.zeros(1, dtype=np.int64)
     lines = torch.empty(cs_cap, dtype=torch.int32, device=dev) if with_lines else None
     rc = lib.ginex_changeset_resume(num_nodes, _ptr(ids), _np_ptr(io), S, cap, _ptr(start_ids),
@@ -294,8 +295,9 @@ def changeset_resume(num_nodes, ids, ids_offsets, start_ids, workspace=None, wit
                                     _np_ptr(total_changes), _ptr(ws), ws.numel(), _stream())
     _check(rc)
     n = int(total_changes[0])
-    return ChangesetResult(start_ids, in_ids[:n], out_ids[:n], in_pos[:n], cs_off.cpu().numpy(),
-                           miss[:S].cpu().numpy(), np.full(S, cap, dtype=np.int64), final_ids,
+    small = small.cpu().numpy()
+    return ChangesetResult(start_ids, in_ids[:n], out_ids[:n], in_pos[:n], small[:S + 1],
+                           small[S + 1:2 * S + 1], np.full(S, cap, dtype=np.int64), final_ids,
                            src_line=lines[:total] if with_lines else None)
 
 

@@ -119,6 +119,20 @@ __device__ __forceinline__ uint32_t block_sum_u32(uint32_t v, uint32_t* red) {
 constexpr int LOOK_ITEMS = 8;
 constexpr int LOOK_TILE = TB * LOOK_ITEMS;
 
+// The offsets of the iterations, in the launch's arguments as far as they have room, and what is to be cleared: one
+// launch instead of a copy to the device and one (a copy costs the host as much as two launches, and the
+// device the wait for it).
+struct NearOffsets {
+  static constexpr int MOST = 384;
+  int32_t at[MOST + 1];                // (accesses are below 2^31)
+};
+
+__global__ __launch_bounds__(TB) void k_begin(NearOffsets near, int32_t S, int64_t* __restrict__ off, Zeros z) {
+  for (int i = threadIdx.x; i <= S; i += TB) off[i] = near.at[i];
+  for (int a = 0; a < z.used; ++a)
+    for (int64_t i = threadIdx.x; i < z.words[a]; i += TB) z.at[a][i] = 0;
+}
+
 // number of run heads (= distinct nodes) per tile of the sorted pairs, and a zero behind them
 __global__ __launch_bounds__(TB) void k_count_heads(const uint64_t* __restrict__ sorted, int64_t n,
                                                     uint32_t* __restrict__ head_tiles) {
@@ -2113,7 +2127,7 @@ struct Workspace {
   int32_t* next_iter;
   int32_t* first_of;
   int64_t* d_offsets;
-  int64_t* d_ready;
+  int64_t* d_ready;         // [S], and behind it
   int64_t* d_cs_offsets;
   unsigned long long* d_counts;
   State st;
@@ -2146,8 +2160,8 @@ Workspace carve(void* base, int64_t num_nodes, int64_t total, int32_t S, int64_t
   w.cuts = a.take<Cut>(S);
   w.first_of = a.take<int32_t>(num_nodes);   // resumed superbatches only
   w.d_offsets = a.take<int64_t>(S + 1);
-  w.d_ready = a.take<int64_t>(S);
-  w.d_cs_offsets = a.take<int64_t>(S + 1);
+  w.d_ready = a.take<int64_t>(S + S + 1);
+  w.d_cs_offsets = w.d_ready ? w.d_ready + S : nullptr;
   w.d_counts = a.take<unsigned long long>(2);
   State& st = w.st;
   const int64_t c = cap > 0 ? cap : 1;
@@ -2262,12 +2276,14 @@ int32_t stays_cuts(const Workspace& w, const Stays& q, const int64_t* ids_offset
   }
   auto length = [&](int32_t i) { return ids_offsets[i + 1] - ids_offsets[i]; };
   auto wide = [&](int32_t t) { return cuts[t].T > CUT_WIDE; };   // (members of its bucket, see k_static_roll)
+  size_t most_jobs = 0;
   for (auto& level : levels) {
     std::stable_partition(level.begin(), level.end(), wide);
     jobs.insert(jobs.end(), level.begin(), level.end());
+    most_jobs = std::max(most_jobs, level.size());
   }
-  int32_t* const d_jobs = reinterpret_cast<int32_t*>(w.d_ready);
-  if (!jobs.empty())
+  int32_t* const d_jobs = reinterpret_cast<int32_t*>(pl.arr_off);   // [S + 2], not used on this way
+  if (most_jobs > Jobs::MOST)
     GINEX_HIP(hipMemcpyAsync(d_jobs, jobs.data(), sizeof(int32_t) * jobs.size(), hipMemcpyHostToDevice, st));
   uint32_t* const digit_counts = reinterpret_cast<uint32_t*>(pl.arr_cand);
   constexpr int64_t WIDE_AT_ONCE = PLAN_CAND_MAX / (CUT_DIGITS * CUT_BINS);
@@ -2280,18 +2296,20 @@ int32_t stays_cuts(const Workspace& w, const Stays& q, const int64_t* ids_offset
       wides += wide(t);
     }
     const int64_t count = (int64_t)level.size();
-    hipLaunchKernelGGL(k_cut_members, dim3((unsigned)blocks, (unsigned)count), dim3(TB), 0, st, q, at);
+    Jobs now{most_jobs > Jobs::MOST ? at : nullptr, {}};
+    if (!now.far) std::copy(level.begin(), level.end(), now.near);
+    hipLaunchKernelGGL(k_cut_members, dim3((unsigned)blocks, (unsigned)count), dim3(TB), 0, st, q, now);
     for (int64_t first = 0; first < wides; first += WIDE_AT_ONCE) {
       const int64_t n = std::min(WIDE_AT_ONCE, wides - first);
       const dim3 grid((unsigned)std::min<int64_t>(ceil_div(most_members, TB * CUT_WIDE_ITEMS), 256), (unsigned)n);
       GINEX_HIP(fill_async<uint32_t>(digit_counts, n * (CUT_DIGITS * CUT_BINS), 0u, st));
-      hipLaunchKernelGGL(k_cut_wide<0>, grid, dim3(TB), 0, st, q, at + first, digit_counts);
-      hipLaunchKernelGGL(k_cut_wide<1>, grid, dim3(TB), 0, st, q, at + first, digit_counts);
-      hipLaunchKernelGGL(k_cut_wide<2>, grid, dim3(TB), 0, st, q, at + first, digit_counts);
-      hipLaunchKernelGGL(k_cut_wide<CUT_DIGITS>, grid, dim3(TB), 0, st, q, at + first, digit_counts);
+      hipLaunchKernelGGL(k_cut_wide<0>, grid, dim3(TB), 0, st, q, now, (int)first, digit_counts);
+      hipLaunchKernelGGL(k_cut_wide<1>, grid, dim3(TB), 0, st, q, now, (int)first, digit_counts);
+      hipLaunchKernelGGL(k_cut_wide<2>, grid, dim3(TB), 0, st, q, now, (int)first, digit_counts);
+      hipLaunchKernelGGL(k_cut_wide<CUT_DIGITS>, grid, dim3(TB), 0, st, q, now, (int)first, digit_counts);
     }
     if (wides < count)
-      hipLaunchKernelGGL(k_cut_decide, dim3((unsigned)(count - wides)), dim3(BIG), 0, st, q, at + wides);
+      hipLaunchKernelGGL(k_cut_decide, dim3((unsigned)(count - wides)), dim3(BIG), 0, st, q, now, (int)wides);
     GINEX_LAUNCH_CHECK();
     at += count;
   }
@@ -2307,7 +2325,7 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
                   const uint32_t* held_bits, const uint32_t* accessed, const int32_t* ids,
                   const int64_t* ids_offsets, int64_t total, int32_t S, int32_t* in_ids, int32_t* out_ids, int32_t* in_positions,
                   int64_t cs_capacity, int64_t* cs_offsets, int64_t* miss_count, int32_t* src_line,
-                  int64_t* total_changes, bool carried, int32_t* final_ids, hipStream_t st) {
+                  int64_t* total_changes, int64_t* init_ready, bool carried, int32_t* final_ids, hipStream_t st) {
   const State& state = w.st;
   const Plan& pl = w.plan;
   const size_t off_lds = sizeof(int32_t) * (S + 1);
@@ -2342,7 +2360,10 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
   const dim3 mark_grid((unsigned)ceil_div(total, CUT_TILE));
   if (lru) hipLaunchKernelGGL(k_stays_mark<true>, mark_grid, dim3(TB), off_lds, st, q, total, src_line, pl.ins_bits);
   else hipLaunchKernelGGL(k_stays_mark<false>, mark_grid, dim3(TB), off_lds, st, q, total, src_line, pl.ins_bits);
+  // (init_ready: null, or waiting on the device for the next copy to the host)
   auto finish = [&]() -> int32_t {
+    if (init_ready)
+      GINEX_HIP(hipMemcpyAsync(init_ready, w.d_ready, sizeof(int64_t) * S, hipMemcpyDeviceToHost, st));
     if (final_ids)
       GINEX_HIP(hipMemcpyAsync(final_ids, state.res_id, sizeof(int32_t) * state.cap,
                                hipMemcpyDeviceToDevice, st));
@@ -2410,15 +2431,18 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
   if (!lru) hipLaunchKernelGGL(k_never_lift, dim3(1), dim3(BIG), 0, st, w.cuts, S, pl.cand_id);
   hipLaunchKernelGGL(k_ins_count, dim3((unsigned)S), dim3(TB), 0, st, pl.ins_bits, w.d_offsets,
                      cs_offsets, lru ? miss_count : (int64_t*)nullptr);
-  hipLaunchKernelGGL(k_ins_offsets, dim3(1), dim3(BIG), 0, st, cs_offsets, S);
+  hipLaunchKernelGGL(k_ins_offsets, dim3(1), dim3(BIG), 0, st, cs_offsets, S, w.d_cs_offsets);
   GINEX_LAUNCH_CHECK();
-  std::vector<int64_t> cs(S + 1);
-  GINEX_HIP(hipMemcpyAsync(cs.data(), cs_offsets, sizeof(int64_t) * (S + 1), hipMemcpyDeviceToHost, st));
+  std::vector<int64_t> host(2 * S + 1);
+  GINEX_HIP(hipMemcpyAsync(host.data(), w.d_ready, sizeof(int64_t) * host.size(), hipMemcpyDeviceToHost, st));
   hipLaunchKernelGGL(k_bit_tiles, dim3((unsigned)pl.ins_tile_count), dim3(TB), 0, st, pl.ins_bits,
                      pl.ins_words, pl.ins_tiles);
   GINEX_HIP(exclusive_scan_inplace<uint32_t>(pl.ins_tiles, pl.ins_tile_count + 1,
                                              pl.ins_tiles + pl.ins_tile_count + 1, st));
   GINEX_HIP(hipStreamSynchronize(st));
+  if (init_ready) std::copy_n(host.begin(), S, init_ready);
+  init_ready = nullptr;
+  const int64_t* const cs = host.data() + S;
   const int64_t M = cs[S];
   *total_changes = M;
   if (M > cs_capacity)
@@ -2627,9 +2651,18 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
   state.dead_scatter = !lru && (scatter_env ? scatter_env[0] == '1' : cap >= (int64_t(1) << 20));
   state.dead_only = 0;
 
-  GINEX_HIP(hipMemcpyAsync(w.d_offsets, ids_offsets, sizeof(int64_t) * (S + 1),
-                           hipMemcpyHostToDevice, st));
-  GINEX_HIP(zero_async(Zeros().add(miss_count, S).add(cs_offsets, S + 1).add(w.d_counts, 1), st));
+  {
+    const Zeros z = Zeros().add(miss_count, S).add(cs_offsets, S + 1).add(w.d_counts, 1);
+    if (S <= NearOffsets::MOST) {
+      NearOffsets near;
+      for (int32_t i = 0; i <= S; ++i) near.at[i] = (int32_t)ids_offsets[i];
+      hipLaunchKernelGGL(k_begin, dim3(1), dim3(TB), 0, st, near, S, w.d_offsets, z);
+      GINEX_LAUNCH_CHECK();
+    } else {
+      GINEX_HIP(hipMemcpyAsync(w.d_offsets, ids_offsets, sizeof(int64_t) * (S + 1), hipMemcpyHostToDevice, st));
+      GINEX_HIP(zero_async(z, st));
+    }
+  }
   *init_count = start_ids ? cap : 0;
   *total_changes = 0;
   if (init_ready)
@@ -2713,9 +2746,14 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
     hipLaunchKernelGGL(k_init_ready, dim3((unsigned)ceil_div(S, TB)), dim3(TB), 0, st, heads, n_init,
                        S, w.d_ready);
     GINEX_LAUNCH_CHECK();
-    GINEX_HIP(hipMemcpyAsync(init_ready, w.d_ready, sizeof(int64_t) * S, hipMemcpyDeviceToHost,
-                             st));
+  } else {
+    init_ready = nullptr;
   }
+  // (to the host with the next copy that has to be waited for anyway)
+  auto bring_ready = [&]() {
+    return init_ready ? hipMemcpyAsync(init_ready, w.d_ready, sizeof(int64_t) * S, hipMemcpyDeviceToHost, st)
+                      : hipSuccess;
+  };
   if (!start_ids && (distinct <= cap || cap == 0)) {
     // everything fits (no row ever misses), or there is no cache (every row misses and
     // nothing is inserted): all changesets are empty
@@ -2737,6 +2775,7 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
                          ids, total, state.addr, src_line);
       GINEX_LAUNCH_CHECK();
     }
+    GINEX_HIP(bring_ready());
     GINEX_HIP(hipStreamSynchronize(st));
     return GINEX_OK;
   }
@@ -3027,7 +3066,7 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
     return stays_run(who, w, sorted, ends, rows, distinct, start_ids ? nullptr : heads + (cap - 1),
                      held_bits, accessed, ids, ids_offsets, total, S, in_ids, out_ids, in_positions,
                      cs_capacity, cs_offsets, miss_count,
-                     src_line, total_changes, start_ids != nullptr, final_ids, st);
+                     src_line, total_changes, init_ready, start_ids != nullptr, final_ids, st);
   }
 
   // part 3: the recurrence, with no host round trip between iterations
@@ -3076,6 +3115,7 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
                              hipMemcpyDeviceToDevice, st));
   GINEX_HIP(hipMemcpyAsync(total_changes, cs_offsets + S, sizeof(int64_t), hipMemcpyDeviceToHost,
                            st));
+  GINEX_HIP(bring_ready());
   int32_t fault = 0;
   GINEX_HIP(hipMemcpyAsync(&fault, state.fault, sizeof(fault), hipMemcpyDeviceToHost, st));
   GINEX_HIP(hipStreamSynchronize(st));

@@ -245,11 +245,20 @@ __device__ __forceinline__ bool stay_inserts(const Stays& q, const Cut& c, int32
 constexpr int CUT_ITEMS = 8;
 constexpr int CUT_TILE = TB * CUT_ITEMS;
 
+// The iterations of a level's cuts: in the launch's arguments as far as they have room (a copy to the device is a
+// launch's time and a wait), else in memory.
+struct Jobs {
+  static constexpr int MOST = 96;
+  const int32_t* far;                  // null: near
+  int16_t near[MOST];                  // (iterations are at most STATIC_S_MAX)
+  __device__ __forceinline__ int32_t operator[](int k) const { return far ? far[k] : near[k]; }
+};
+
 // Members of the buckets of a level's cuts (blockIdx.y = cut, jobs[] its iteration): the accesses of
 // iteration j whose row is resident since before t (class resident), and the accesses of
 // iteration t with key j (resident if they hit, else incoming).  Both lists are kept, residents as
 // ids from the front of bucket j's region, incoming rows as positions from its end.
-__global__ __launch_bounds__(TB) void k_cut_members(Stays q, const int32_t* __restrict__ jobs) {
+__global__ __launch_bounds__(TB) void k_cut_members(Stays q, Jobs jobs) {
   __shared__ uint32_t smem[TB / WAVE + 1];
   __shared__ uint32_t s_at[2];
   const int32_t t = jobs[blockIdx.y];
@@ -398,8 +407,8 @@ __device__ __forceinline__ void cut_mark(const Stays& q, const Cut& c, int32_t k
 }
 
 // One block per cut of the level: which class is cut and where.
-__global__ __launch_bounds__(BIG) void k_cut_decide(Stays q, const int32_t* __restrict__ jobs) {
-  Cut* cut = &q.cuts[jobs[blockIdx.x]];
+__global__ __launch_bounds__(BIG) void k_cut_decide(Stays q, Jobs jobs, int first) {
+  Cut* cut = &q.cuts[jobs[first + blockIdx.x]];
   const Cut c = *cut;
   const int64_t region = q.off[c.jstar], room = q.off[c.jstar + 1] - region;
   const CutChoice ch = cut_choice(c, room);
@@ -424,12 +433,12 @@ constexpr int CUT_DIGITS = 3, CUT_BINS = 2048;         // 11 + 10 + 10 bits
 constexpr int CUT_WIDE_ITEMS = 8;
 
 template <int DIGIT>   // CUT_DIGITS: all are known
-__global__ __launch_bounds__(TB) void k_cut_wide(Stays q, const int32_t* __restrict__ jobs,
+__global__ __launch_bounds__(TB) void k_cut_wide(Stays q, Jobs jobs, int first,
                                                  uint32_t* __restrict__ hists) {
   __shared__ uint32_t s_hist[CUT_BINS];
   __shared__ uint32_t smem[TB / WAVE + 1];
   __shared__ uint32_t s_pick, s_below;
-  Cut* cut = &q.cuts[jobs[blockIdx.y]];
+  Cut* cut = &q.cuts[jobs[first + blockIdx.y]];
   const Cut c = *cut;                                  // (kind and T are not used: the last launch writes them)
   const int64_t region = q.off[c.jstar], room = q.off[c.jstar + 1] - region;
   const CutChoice ch = cut_choice(c, room);
@@ -1024,8 +1033,9 @@ __global__ __launch_bounds__(TB) void k_ins_count(const uint32_t* __restrict__ i
   }
 }
 
-// cs_offsets[1 .. S] <- inclusive sums
-__global__ __launch_bounds__(BIG) void k_ins_offsets(int64_t* __restrict__ cs_offsets, int32_t S) {
+// cs_offsets[1 .. S] <- inclusive sums, and the same for the host
+__global__ __launch_bounds__(BIG) void k_ins_offsets(int64_t* __restrict__ cs_offsets, int32_t S,
+                                                     int64_t* __restrict__ copy) {
   __shared__ int64_t smem[BIG / WAVE + 1];
   const int32_t per = (S + BIG - 1) / BIG, j0 = threadIdx.x * per;
   int64_t mine = 0;
@@ -1035,7 +1045,9 @@ __global__ __launch_bounds__(BIG) void k_ins_offsets(int64_t* __restrict__ cs_of
   for (int32_t j = j0; j < j0 + per && j < S; ++j) {
     run += cs_offsets[j + 1];
     cs_offsets[j + 1] = run;
+    copy[j + 1] = run;
   }
+  if (threadIdx.x == 0) copy[0] = 0;
 }
 
 // What becomes of the line of an inserted row (or of a start-state row): the iteration that evicts
