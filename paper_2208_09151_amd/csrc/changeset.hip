@@ -2550,38 +2550,58 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
   return finish();
 }
 
-// A fresh cache that holds every row (see fits.hpp): *distinct rows of the superbatch, and if they fit `cap`, the
-// results; -1 where this way does not serve the shape or met an id out of range.
-int32_t fits_run(const Workspace& w, int64_t num_nodes, const int32_t* ids, const int64_t* ids_offsets, int64_t total,
-                 int32_t S, int64_t max_n, int64_t cap, int32_t* init_ids, int32_t* src_line, int64_t* init_ready,
-                 int64_t* distinct, hipStream_t st) {
-  *distinct = -1;
+// The tiles and buckets of a call (see fits.hpp): ids, places and starts in `buffer`, 8 bytes per access, and up to
+// `spare` bytes behind the starts for the caller.  buckets = 0 where this way does not serve the shape.
+Fit fit_shape(const Workspace& w, int64_t num_nodes, int64_t total, int32_t S, int64_t max_n, uint64_t* ids_buffer,
+              uint64_t* start_buffer, size_t start_room, size_t* start_bytes) {
   Fit f{};
   f.shift = fit_shift(num_nodes);
   f.S = S;
   const int64_t buckets = ceil_div(num_nodes, int64_t(1) << f.shift), per_iteration = ceil_div(max_n, FIT_TILE);
-  const int64_t tiles = S * per_iteration, counts = S * buckets + 1;
-  const size_t start_bytes = (sizeof(uint16_t) * (size_t)(tiles * (buckets + 1)) + 255) & ~size_t(255);
-  if (buckets > FIT_BUCKETS || total < FIT_SHARE_MIN * tiles * buckets ||
-      fit_lines_lds(f) > FIT_LDS ||
-      start_bytes + sizeof(uint32_t) * (counts + scan_scratch_elems(counts)) > sizeof(uint64_t) * total)
-    return GINEX_OK;
+  const int64_t tiles = S * per_iteration;
+  *start_bytes = (sizeof(uint16_t) * (size_t)(tiles * (buckets + 1)) + 255) & ~size_t(255);
+  if (buckets > FIT_BUCKETS || total < FIT_SHARE_MIN * tiles * buckets || fit_lines_lds(f) > FIT_LDS ||
+      *start_bytes > start_room)
+    return f;
   f.off = w.d_offsets;
-  f.ids = reinterpret_cast<uint32_t*>(w.pairs_a);
+  f.ids = reinterpret_cast<uint32_t*>(ids_buffer);
   f.rank = reinterpret_cast<uint16_t*>(f.ids + total);
-  f.start = reinterpret_cast<uint16_t*>(w.pairs_b);
-  f.counts = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(w.pairs_b) + start_bytes);
-  f.list = reinterpret_cast<uint32_t*>(w.st.addr);
-  f.bits = w.st.dead_bits;
-  f.bad = reinterpret_cast<uint32_t*>(w.d_counts);   // (zero)
+  f.start = reinterpret_cast<uint16_t*>(start_buffer);
+  f.bad = reinterpret_cast<uint32_t*>(w.d_counts);
   f.num_nodes = num_nodes;
   f.words = w.st.words;
   f.per_iteration = (int32_t)per_iteration;
   f.tiles = (int32_t)tiles;
   f.buckets = (int32_t)buckets;
-  const dim3 tile_grid((unsigned)per_iteration, (unsigned)S), bucket_grid((unsigned)(ceil_div(buckets, 8) * 8));
-  hipLaunchKernelGGL(k_fit_deal, tile_grid, dim3(FIT_THREADS), sizeof(uint32_t) * buckets, st, f, ids);
-  hipLaunchKernelGGL(k_fit_rows, bucket_grid, dim3(FIT_LINE_THREADS), fit_rows_lds(f), st, f);
+  return f;
+}
+
+void fit_deal_async(const Fit& f, const int32_t* ids, hipStream_t st) {
+  hipLaunchKernelGGL(k_fit_deal, dim3((unsigned)f.per_iteration, (unsigned)f.S), dim3(FIT_THREADS),
+                     sizeof(uint32_t) * f.buckets, st, f, ids);
+}
+void fit_place_async(const Fit& f, int32_t* src_line, hipStream_t st) {
+  hipLaunchKernelGGL(k_fit_place, dim3((unsigned)f.per_iteration, (unsigned)f.S), dim3(FIT_THREADS), 0, st, f,
+                     src_line);
+}
+dim3 fit_grid(const Fit& f) { return dim3((unsigned)(ceil_div(f.buckets, 8) * 8)); }
+
+// A fresh cache that holds every row (see fits.hpp): *distinct rows of the superbatch, and if they fit `cap`, the
+// results; -1 where this way does not serve the shape or met an id out of range.
+int32_t fits_run(const Workspace& w, int64_t num_nodes, const int32_t* ids, int64_t total, int32_t S, int64_t max_n,
+                 int64_t cap, int32_t* init_ids, int32_t* src_line, int64_t* init_ready, int64_t* distinct,
+                 hipStream_t st) {
+  *distinct = -1;
+  size_t start_bytes;
+  const size_t room = sizeof(uint64_t) * total;
+  Fit f = fit_shape(w, num_nodes, total, S, max_n, w.pairs_a, w.pairs_b, room, &start_bytes);
+  const int64_t counts = (int64_t)S * f.buckets + 1;
+  if (f.buckets == 0 || start_bytes + sizeof(uint32_t) * (counts + scan_scratch_elems(counts)) > room) return GINEX_OK;
+  f.counts = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(w.pairs_b) + start_bytes);
+  f.list = reinterpret_cast<uint32_t*>(w.st.addr);
+  f.bits = w.st.dead_bits;
+  fit_deal_async(f, ids, st);                     // (the word for ids out of range was cleared)
+  hipLaunchKernelGGL(k_fit_rows, fit_grid(f), dim3(FIT_LINE_THREADS), fit_rows_lds(f), st, f);
   GINEX_HIP(exclusive_scan_inplace<uint32_t>(f.counts, counts, f.counts + counts, st));
   hipLaunchKernelGGL(k_fit_ready, dim3((unsigned)ceil_div(S, TB)), dim3(TB), 0, st, f, w.d_ready);
   GINEX_LAUNCH_CHECK();
@@ -2591,9 +2611,9 @@ int32_t fits_run(const Workspace& w, int64_t num_nodes, const int32_t* ids, cons
   *distinct = ready[S - 1];
   if (*distinct < 0 || *distinct > cap) return GINEX_OK;
   if (init_ready) std::copy(ready.begin(), ready.end(), init_ready);
-  hipLaunchKernelGGL(k_fit_lines, bucket_grid, dim3(FIT_LINE_THREADS), fit_lines_lds(f), st, f, init_ids,
+  hipLaunchKernelGGL(k_fit_lines, fit_grid(f), dim3(FIT_LINE_THREADS), fit_lines_lds(f), st, f, init_ids,
                      src_line != nullptr);
-  if (src_line) hipLaunchKernelGGL(k_fit_place, tile_grid, dim3(FIT_THREADS), 0, st, f, src_line);
+  if (src_line) fit_place_async(f, src_line, st);
   GINEX_LAUNCH_CHECK();
   GINEX_HIP(hipStreamSynchronize(st));
   return GINEX_OK;
@@ -2685,7 +2705,7 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
   int64_t rows = -1;
   const bool certain = cap >= std::min(total, num_nodes);
   if (!start_ids && cap > 0 && !validate && (certain || (4 * cap >= 3 * total && total >= FIT_GUESS_MIN))) {
-    if (int32_t rc = fits_run(w, num_nodes, ids, ids_offsets, total, S, max_n, cap, init_ids, src_line, init_ready,
+    if (int32_t rc = fits_run(w, num_nodes, ids, total, S, max_n, cap, init_ids, src_line, init_ready,
                               &rows, st))
       return rc;
     if (rows >= 0 && rows <= cap) {
@@ -3020,9 +3040,21 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
         }
       }
       if (src_line) {
-        // every row has one line for the whole superbatch: the start state's or the one it was given
-        hipLaunchKernelGGL(k_lookup_lines, dim3((unsigned)ceil_div(total, TB * 4)), dim3(TB), 0, st,
-                           ids, total, state.addr, src_line);
+        // every row has one line for the whole superbatch: the start state's or the one it was given.  Through
+        // buckets where the table is larger than the caches (random words of 55 G/s then): the accesses are
+        // sorted still in one buffer, the other and the heads have room for them
+        size_t start_bytes;
+        Fit f = fit_shape(w, num_nodes, total, S, max_n, sorted == w.pairs_a ? w.pairs_b : w.pairs_a,
+                          w.heads_a, sizeof(uint64_t) * w.max_heads, &start_bytes);
+        if (f.buckets > 0 && total >= FIT_LOOKUP_MIN && total * FIT_LOOKUP_NODES >= num_nodes) {
+          f.bits = accessed;
+          fit_deal_async(f, ids, st);
+          hipLaunchKernelGGL(k_fit_lookup, fit_grid(f), dim3(FIT_LINE_THREADS), fit_rows_lds(f), st, f, state.addr);
+          fit_place_async(f, src_line, st);
+        } else {
+          hipLaunchKernelGGL(k_lookup_lines, dim3((unsigned)ceil_div(total, TB * 4)), dim3(TB), 0, st,
+                             ids, total, state.addr, src_line);
+        }
         if (M > 0)
           hipLaunchKernelGGL(k_ins_lines, dim3((unsigned)pl.ins_tile_count), dim3(TB), 0, st,
                              pl.ins_bits, pl.ins_words, src_line);

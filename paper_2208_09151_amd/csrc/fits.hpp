@@ -11,6 +11,7 @@
 //   (scan of the numbers of new rows by iteration, then bucket: the rank of each of these lists' pieces)
 //   k_fit_lines  a block per bucket: line of every row into LDS, C_0; then of every access, in the tiles' order
 //   k_fit_place  a block per tile: the lines back in the order of the accesses
+// A carried cache that holds every row takes its lines the same way, with k_fit_lookup in the place of the two.
 // 33 M accesses, 9 M rows of 111 M nodes, 200 iterations: k_fit_deal 79 us (4 bytes read and 6 written per access,
 // 4.2 TB/s), k_fit_rows 253 and k_fit_lines 191 (7.4 M shares of four or five ids, the latency of their reads),
 // k_fit_place 53; 729 a call.  Through the sorted accesses 2 004: four radix passes 0.72 ms, heads 0.23, the rows' lines
@@ -23,6 +24,11 @@
 // limit on the accesses otherwise (2 iterations of 500: 206 -> 160 us, 8 of 4 000 on 16 384 nodes 204 -> 178).
 constexpr int64_t FIT_SHARE_MIN = 1;
 constexpr int64_t FIT_GUESS_MIN = 1 << 20;             // see changeset_run
+// k_fit_lookup (33 M accesses, 9 M rows of 111 M nodes: 82 + 272 + 55 us against 626 for a random word per access):
+// accesses, and nodes to an access, beyond which few entries of a line of the table are used (carried caches,
+// calls in all: 10 M nodes, 1 M accesses 903 -> 889 us, 8.4 M 1 746 -> 1 672; 100 M nodes, 2 M 892 and 917, 8.4 M
+// 2 018 and 2 013, 17 M 5 427 -> 5 382; 1 M nodes, 0.5 M accesses 632 and 644, 2 M 400 -> 391).
+constexpr int64_t FIT_LOOKUP_MIN = 1 << 20, FIT_LOOKUP_NODES = 8;
 
 constexpr int FIT_THREADS = 512;
 constexpr int FIT_ITEMS = 16;
@@ -323,6 +329,46 @@ __global__ __launch_bounds__(FIT_LINE_THREADS) __attribute__((amdgpu_waves_per_e
   }
 }
 
+// The lines of the accesses from a table over all nodes, for rows that keep one line (f.bits: rows accessed): the
+// bucket's entries go to LDS in id order, not one random word per access.
+__global__ __launch_bounds__(FIT_LINE_THREADS) __attribute__((amdgpu_waves_per_eu(8))) void k_fit_lookup(
+    Fit f, const int32_t* __restrict__ addr) {
+  extern __shared__ uint32_t lds[];
+  __shared__ uint32_t smem[FIT_LINE_THREADS / WAVE + 1];
+  const int32_t q = fit_bucket();
+  if (q >= f.buckets) return;
+  const FitLds l = fit_lds(lds, f);
+  const int32_t words = 1 << (f.shift - 5);
+  const uint32_t mask = (1u << f.shift) - 1u;
+  const int64_t word0 = ((int64_t)q << f.shift) >> 5;
+  for (int32_t w = threadIdx.x; w < words; w += FIT_LINE_THREADS) l.bits[w] = word0 + w < f.words ? f.bits[word0 + w] : 0u;
+  __syncthreads();
+  const uint32_t rows = fit_bases(f, l, smem);
+  __syncthreads();
+  for (uint32_t from = 0; from < rows; from += FIT_ROWS) {   // more rows than fit LDS: in slices by id
+    const uint32_t n = rows - from < FIT_ROWS ? rows - from : FIT_ROWS;
+    // the rows' ids first, so that neighbours read neighbouring entries, several at a time
+    for (int32_t w = threadIdx.x; w < words; w += FIT_LINE_THREADS) {
+      uint32_t r = l.base[w] - from;                 // (wraps below)
+      for (uint32_t left = l.bits[w]; left; left &= left - 1, ++r)
+        if (r < n) l.row[r] = (uint32_t)(w * 32 + __ffs(left) - 1);
+    }
+    __syncthreads();
+    const int32_t* const entries = addr + ((int64_t)q << f.shift);
+    uint32_t line[FIT_ROWS / FIT_LINE_THREADS];
+#pragma unroll
+    for (int k = 0; k < FIT_ROWS / FIT_LINE_THREADS; ++k)
+      if (k * FIT_LINE_THREADS + threadIdx.x < n) line[k] = (uint32_t)entries[l.row[k * FIT_LINE_THREADS + threadIdx.x]];
+#pragma unroll
+    for (int k = 0; k < FIT_ROWS / FIT_LINE_THREADS; ++k)
+      if (k * FIT_LINE_THREADS + threadIdx.x < n) l.row[k * FIT_LINE_THREADS + threadIdx.x] = line[k];
+    fit_shares(f, q, l, [&](uint32_t at, uint32_t id, int32_t) {
+      const uint32_t r = fit_rank(l, id & mask) - from;
+      if (r < n && !(id & FIT_DONE)) f.ids[at] = l.row[r] | FIT_DONE;
+    });
+  }
+}
+
 __global__ __launch_bounds__(FIT_THREADS) void k_fit_place(Fit f, int32_t* __restrict__ src_line) {
   __shared__ uint32_t s_line[FIT_TILE];
   const int64_t pos = f.off[blockIdx.y] + (int64_t)blockIdx.x * FIT_TILE, left = f.off[blockIdx.y + 1] - pos;
@@ -338,7 +384,8 @@ __global__ __launch_bounds__(FIT_THREADS) void k_fit_place(Fit f, int32_t* __res
   }
 #pragma unroll
   for (int k = 0; k < FIT_ITEMS; ++k)
-    if (k * FIT_THREADS + (int32_t)threadIdx.x < n) s_line[rank[k]] = line[k] & ~FIT_DONE;
+    if (k * FIT_THREADS + (int32_t)threadIdx.x < n)
+      s_line[rank[k]] = line[k] == 0xFFFFFFFFu ? line[k] : line[k] & ~FIT_DONE;   // (-1: no line; lines are below 2^31 - 1)
   __syncthreads();
   for (int32_t x = threadIdx.x; x < n; x += FIT_THREADS) src_line[pos + x] = (int32_t)s_line[x];
 }

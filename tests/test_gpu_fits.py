@@ -84,3 +84,23 @@ def test_ids_out_of_range_go_the_other_way(ginex):  # noqa: F811
     ids = torch.arange(90, 190, dtype=torch.int32, device="cuda")
     with pytest.raises(ginex.GinexError, match="out of range"):
         ginex.changeset(64, ids, np.array([0, 50, 100]), 64)
+
+
+# a carried cache that holds every row: its lines by bucket, up to three slices to one, rows that are not inserted;
+# against the way that takes it as any other cache
+@pytest.mark.parametrize("n,low,length,cap", [(20_000_000, 200_000, 150_000, 400_000), (20_000_000, 9000, 9000, 12_000),
+                                              (3_000_017, 3_000_017, 80_000, 2_500_000)])
+def test_lines_of_a_carried_cache(ginex, n, low, length, cap, monkeypatch):  # noqa: F811
+    ids, off = trace(n, (length, 0, length - 1) * max(9, (n // 8 + (1 << 20)) // (3 * length) + 1), n, low)
+    gen = torch.Generator(device="cuda").manual_seed(cap)
+    start = torch.cat([torch.randperm(low, generator=gen, device="cuda")[:cap // 3],
+                       n - 1 - torch.arange(cap, device="cuda")]).int().unique()
+    start = start[torch.randperm(start.numel(), generator=gen, device="cuda")][:max(cap, int(ids.unique().numel()))]
+    want = None
+    for planned in ("0", "1"):
+        monkeypatch.setenv("GINEX_PLANNED", planned)
+        got = ginex.changeset_resume(n, ids, off, start)
+        want = want or got
+        for name in ("in_ids", "out_ids", "in_positions", "src_line", "final_ids"):
+            assert torch.equal(getattr(want, name), getattr(got, name)), name
+    assert (want.src_line < 0).any() and want.cs_offsets[-1] > 0
