@@ -10,8 +10,9 @@
 //   hits, misses, insertions and evictions follow from the trace and the start state at once,
 //   and only the lines are handed on iteration by iteration (stays.hpp; a carried cache that
 //   holds every row of the superbatch: the part "without a loop" below).  Beyond 2 048
-//   iterations, for LRU where an iteration is longer than the cache, and for the smallest calls a loop
-//   over the state, serial over iterations and parallel inside one.  The cache is full from C_0 on (otherwise everything fitted and
+//   iterations, for LRU where an iteration is longer than the cache, and for the smallest carried caches a loop
+//   over the state, serial over iterations and parallel inside one (small.hpp: the same in one
+//   workgroup, for the smallest fresh caches).  The cache is full from C_0 on (otherwise everything fitted and
 //   nothing ever changes), so iteration i must drop exactly as many candidates as it had
 //   misses.  Keys are (next iteration, incoming?, node id); next iterations take only
 //   S-i distinct values, so a histogram per next iteration (kept incrementally for the
@@ -846,6 +847,7 @@ constexpr int MARK_ITEMS = 8;   // lines / accesses per thread in the mark phase
 // histograms of the trace.  stays.hpp turns them into the changesets.
 #include "stays.hpp"
 #include "fits.hpp"
+#include "small.hpp"
 
 // H[i][k] = accesses of iteration i whose next accessed iteration is k.  blockIdx.y = iteration.
 __global__ __launch_bounds__(TB) void k_key_hists(const uint64_t* __restrict__ ends,
@@ -2751,6 +2753,30 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
     return fail(GINEX_ERR_INPUT, "%s: %lld distinct ids among %lld nodes: ids out of range?", who,
                 (long long)distinct, (long long)num_nodes);
 
+  // the smallest calls whose rows do not fit (GINEX_STATIC_THRESHOLDS chooses one of the other ways)
+  const char* static_env = getenv("GINEX_STATIC_THRESHOLDS");
+  if (!start_ids && !lru && !static_env && cap > 0 && cap < distinct && distinct <= SMALL_ROWS && S <= SMALL_S &&
+      total <= SMALL_IDS) {
+    const Small small{reinterpret_cast<uint32_t*>(w.next_iter), reinterpret_cast<int32_t*>(w.heads_a),
+                      reinterpret_cast<uint32_t*>(w.heads_b), w.d_offsets, (int32_t)distinct, (int32_t)cap, S,
+                      init_ids, in_ids, out_ids, in_positions, cs_capacity, cs_offsets, miss_count, src_line,
+                      w.d_ready, w.d_cs_offsets};
+    hipLaunchKernelGGL(k_small_ranks, dim3((unsigned)w.look_tiles), dim3(TB), 0, st, sorted, total, w.head_tiles,
+                       small);
+    hipLaunchKernelGGL(k_small_belady, dim3(1), dim3(BIG), 0, st, small);
+    GINEX_LAUNCH_CHECK();
+    std::vector<int64_t> host(2 * S + 1);
+    GINEX_HIP(hipMemcpyAsync(host.data(), w.d_ready, sizeof(int64_t) * host.size(), hipMemcpyDeviceToHost, st));
+    GINEX_HIP(hipStreamSynchronize(st));
+    *init_count = cap;
+    if (init_ready) std::copy_n(host.begin(), S, init_ready);
+    *total_changes = host[2 * S];
+    if (*total_changes > cs_capacity)
+      return fail(GINEX_ERR_CAPACITY, "%s: %lld changeset records, capacity %lld", who, (long long)*total_changes,
+                  (long long)cs_capacity);
+    return GINEX_OK;
+  }
+
   // part 2: C_0
   const size_t off_lds = sizeof(int32_t) * (S + 1);
   hipLaunchKernelGGL(k_heads_write, dim3((unsigned)w.look_tiles), dim3(TB), off_lds, st, sorted,
@@ -2819,7 +2845,6 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
   // against 400 to 406.  Many
   // nodes: the loop clears two words for each; two iterations of 200 accesses, carried, 66 M nodes 464 against
   // 434, three on 111 M nodes 507 against 537.  GINEX_STATIC_THRESHOLDS=0/1 chooses the loop / the trace.
-  const char* static_env = getenv("GINEX_STATIC_THRESHOLDS");
   // LRU (the trace's way has no cuts): 20 000 nodes, iterations of 3 000 accesses, two 311 against 332, three 355
   // and 342, six 472 and 396; 200 000 nodes, of 20 000, two 344 and 380, three 406 and 412.
   const bool smallest = lru ? S <= LOOP_LRU_S && total <= LOOP_LRU_IDS && num_nodes <= LOOP_NODES : S <= LOOP_S && total <= (S <= LOOP_S / 2 ? 4 * LOOP_IDS : LOOP_IDS) &&
