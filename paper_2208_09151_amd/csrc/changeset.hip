@@ -1494,6 +1494,7 @@ __global__ __launch_bounds__(TB) void k_ins_emit(const uint32_t* __restrict__ bi
                                                  int32_t* __restrict__ in_ids,
                                                  int32_t* __restrict__ in_positions,
                                                  uint32_t* __restrict__ ins_base,
+                                                 uint64_t* __restrict__ ins_pairs,
                                                  int32_t* __restrict__ ins_cand) {
   extern __shared__ int32_t lds_off[];
   __shared__ uint32_t smem[TB / WAVE + 1];
@@ -1504,12 +1505,15 @@ __global__ __launch_bounds__(TB) void k_ins_emit(const uint32_t* __restrict__ bi
   uint32_t word = w < words ? bits[w] : 0u;
   uint32_t total;
   uint32_t rank = first + block_exclusive_scan<uint32_t, TB>((uint32_t)__popc(word), smem, total);
-  if (w < words) ins_base[w] = rank;
+  if (w < words && ins_pairs) ins_pairs[w] = (uint64_t)rank << 32 | word;   // (see InsIndex)
+  if (w < words && !ins_pairs) ins_base[w] = rank;
+  int32_t i = word ? iter_of(lds_off, S, (int32_t)(w * 32)) : 0;
   while (word) {
     const int32_t p = (int32_t)(w * 32 + (__ffs(word) - 1));
     word &= word - 1;
+    while (i + 1 < S && lds_off[i + 1] <= p) ++i;
     in_ids[rank] = ids[p];
-    in_positions[rank] = p - lds_off[iter_of(lds_off, S, p)];
+    in_positions[rank] = p - lds_off[i];
     if (ins_cand) ins_cand[rank] = -1;
     ++rank;
   }
@@ -2460,10 +2464,14 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
   // (the ends are not read any more)
   uint32_t* const leave_ins = reinterpret_cast<uint32_t*>(ends);
   int32_t* const leaving = reinterpret_cast<int32_t*>(leave_ins + total);
+  // (the numbers of candidates are the planned path's)
+  uint64_t* const ins_pairs = sizeof(int32_t) * w.max_heads >= sizeof(uint64_t) * pl.ins_words
+                                  ? reinterpret_cast<uint64_t*>(pl.ins_cand) : nullptr;
+  const InsIndex at_ins{ins_pairs, pl.ins_bits, pl.ins_base};
   if (M > 0) {
     hipLaunchKernelGGL(k_ins_emit, dim3((unsigned)pl.ins_tile_count), dim3(TB), off_lds, st, pl.ins_bits,
                        pl.ins_words, pl.ins_tiles, ids, w.d_offsets, S, in_ids, in_positions,
-                       pl.ins_base, (int32_t*)nullptr);
+                       pl.ins_base, ins_pairs, (int32_t*)nullptr);
     if (carried)
       hipLaunchKernelGGL(k_stays_idle, dim3((unsigned)ceil_div(state.cap, TB)), dim3(TB), 0, st, q,
                          state.res_id, accessed, state.cap, leave_start);
@@ -2472,14 +2480,14 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
     const dim3 walk_grid((unsigned)ceil_div(total, WALK_TILE));
     if (lru)
       hipLaunchKernelGGL(k_lru_walk, walk_grid, dim3(TB), sizeof(uint64_t) * S + off_lds, st, q, sorted, total,
-                         last_head, state.addr, pl.ins_bits, pl.ins_base, leave_ins, leave_start);
+                         last_head, state.addr, at_ins, leave_ins, leave_start);
     else if (S <= NEVER_LDS_S)
       hipLaunchKernelGGL(k_stays_walk<true>, walk_grid, dim3(TB), off_lds * (1 + levels), st, q, sorted,
-                         total, state.addr, hit_words, ins_words, pl.ins_bits, pl.ins_base, leave_ins,
+                         total, state.addr, hit_words, ins_words, at_ins, leave_ins,
                          leave_start);
     else
       hipLaunchKernelGGL(k_stays_walk<false>, walk_grid, dim3(TB), off_lds, st, q, sorted, total,
-                         state.addr, hit_words, ins_words, pl.ins_bits, pl.ins_base, leave_ins,
+                         state.addr, hit_words, ins_words, at_ins, leave_ins,
                          leave_start);
     const int64_t place_blocks = std::min<int64_t>(ceil_div(M + state.cap, TB * 8), 512);
     hipLaunchKernelGGL(k_leave_places, dim3((unsigned)place_blocks), dim3(TB), sizeof(uint32_t) * S, st,
@@ -2994,7 +3002,7 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
                                                    pl.ins_tiles + pl.ins_tile_count + 1, st));
         hipLaunchKernelGGL(k_ins_emit, dim3((unsigned)pl.ins_tile_count), dim3(TB), off_lds, st,
                            pl.ins_bits, pl.ins_words, pl.ins_tiles, ids, w.d_offsets, S, in_ids,
-                           in_positions, pl.ins_base, pl.ins_cand);
+                           in_positions, pl.ins_base, (uint64_t*)nullptr, pl.ins_cand);
         GINEX_LAUNCH_CHECK();
         hipLaunchKernelGGL(k_dead_lines, dim3((unsigned)(ceil_div(cap, TB * 8) > 4096 ? 4096 : ceil_div(cap, TB * 8))),
                            dim3(TB), 0, st, state, accessed, lo_id);

@@ -1055,6 +1055,20 @@ __global__ __launch_bounds__(BIG) void k_ins_offsets(int64_t* __restrict__ cs_of
 constexpr uint32_t STAYS = 0xFFFFFFFFu;
 constexpr uint32_t LEAVES_NEXT = 0xFFFFFFFEu;
 
+// The insertions' bits and the number of them in front of each word: side by side where the workspace has room (one
+// random word per insertion instead of two), else in two arrays.
+struct InsIndex {
+  const uint64_t* pairs;   // [words] bits | in front << 32, or null
+  const uint32_t *bits, *base;
+  __device__ __forceinline__ uint64_t word(uint32_t p) const {
+    return pairs ? pairs[p >> 5] : (uint64_t)base[p >> 5] << 32 | bits[p >> 5];
+  }
+  // The insertion at position p, from its word.
+  static __device__ __forceinline__ uint32_t index(uint64_t word, uint32_t p) {
+    return (uint32_t)(word >> 32) + __popc((uint32_t)word & ((1u << (p & 31)) - 1u));
+  }
+};
+
 // The second pass in node order: for every insertion, and for the first access of every start-state row
 // that hits, the iteration that evicts the row.  A resident access is linked to its right neighbour if
 // that is a hit of the same row; the first stay that does not reach a hit gives the iteration for
@@ -1085,9 +1099,7 @@ __global__ __launch_bounds__(TB) void k_stays_walk(Stays q, const uint64_t* __re
                                                    int64_t n, const int32_t* __restrict__ addr,
                                                    const uint64_t* __restrict__ hit_words,
                                                    const uint64_t* __restrict__ ins_words,
-                                                   const uint32_t* __restrict__ ins_bits,
-                                                   const uint32_t* __restrict__ ins_base,
-                                                   uint32_t* __restrict__ leave_ins,
+                                                   InsIndex at_ins, uint32_t* __restrict__ leave_ins,
                                                    uint32_t* __restrict__ leave_start) {
   extern __shared__ int32_t lds_off[];    // offsets [S + 1], limits [levels * (S + 1)]
   const int32_t* never = q.never;
@@ -1110,6 +1122,16 @@ __global__ __launch_bounds__(TB) void k_stays_walk(Stays q, const uint64_t* __re
     if (k < WALK_CHUNKS) ins[k] = w < words ? ins_words[w] : 0ull;
   }
   const uint64_t left_of = base > 0 ? sorted[base - 1] : ~0ull;
+  // the insertions' places in their list, all read at once
+  uint32_t slot[WALK_CHUNKS];
+  {
+    uint64_t word[WALK_CHUNKS];
+#pragma unroll
+    for (int k = 0; k < WALK_CHUNKS; ++k)
+      if (ins[k] >> lane & 1) word[k] = at_ins.word((uint32_t)cur[k]);
+#pragma unroll
+    for (int k = 0; k < WALK_CHUNKS; ++k) slot[k] = InsIndex::index(word[k], (uint32_t)cur[k]);
+  }
   uint64_t stops[WALK_CHUNKS];                     // the stays that do not reach a hit
   uint32_t leave_of[WALK_CHUNKS];
 #pragma unroll
@@ -1153,8 +1175,7 @@ __global__ __launch_bounds__(TB) void k_stays_walk(Stays q, const uint64_t* __re
     const uint32_t leaves = mine ? found : carry;
     const uint32_t v = (uint32_t)(cur[k] >> 32), p = (uint32_t)cur[k];
     if (ins[k] >> lane & 1)
-      leave_ins[ins_base[p >> 5] + __popc(ins_bits[p >> 5] & ((1u << (p & 31)) - 1u))] =
-          leaves == (uint32_t)(iter_of(lds_off, q.S, (int32_t)p) + 1) ? LEAVES_NEXT : leaves;
+      leave_ins[slot[k]] = leaves == (uint32_t)(iter_of(lds_off, q.S, (int32_t)p) + 1) ? LEAVES_NEXT : leaves;
     // a first access that hits is one of a start-state row
     uint32_t lv = (uint32_t)__shfl_up(v, 1, WAVE);
     const uint64_t before = k > 0 ? shfl_u64(cur[k > 0 ? k - 1 : 0], WAVE - 1) : left_of;
@@ -1169,9 +1190,7 @@ __global__ __launch_bounds__(TB) void k_stays_walk(Stays q, const uint64_t* __re
 __global__ __launch_bounds__(TB) void k_lru_walk(Stays q, const uint64_t* __restrict__ sorted, int64_t n,
                                                  const uint64_t* __restrict__ last_head,
                                                  const int32_t* __restrict__ addr,
-                                                 const uint32_t* __restrict__ ins_bits,
-                                                 const uint32_t* __restrict__ ins_base,
-                                                 uint32_t* __restrict__ leave_ins,
+                                                 InsIndex at_ins, uint32_t* __restrict__ leave_ins,
                                                  uint32_t* __restrict__ leave_start) {
   extern __shared__ uint64_t lds_limits[];         // [S], then the offsets [S + 1]
   int32_t* const lds_off = reinterpret_cast<int32_t*>(lds_limits + q.S);
@@ -1251,8 +1270,7 @@ __global__ __launch_bounds__(TB) void k_lru_walk(Stays q, const uint64_t* __rest
     if (lane == 0) lv = (uint32_t)(before >> 32);
     if (v != 0xFFFFFFFFu) {
       if (lv == v ? !linked : !in_start_state(v, it[k], last_head, nullptr))   // a miss: inserted
-        leave_ins[ins_base[p >> 5] + __popc(ins_bits[p >> 5] & ((1u << (p & 31)) - 1u))] =
-            leaves == (uint32_t)(it[k] + 1) ? LEAVES_NEXT : leaves;
+        leave_ins[InsIndex::index(at_ins.word(p), p)] = leaves == (uint32_t)(it[k] + 1) ? LEAVES_NEXT : leaves;
       else if (lv != v)                            // a first access that hits is one of a start-state row
         leave_start[addr[v]] = leaves;
     }
