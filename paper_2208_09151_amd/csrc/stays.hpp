@@ -913,7 +913,8 @@ __global__ __launch_bounds__(TB) void k_stays_links(Stays q, const uint64_t* __r
                                                     uint32_t* __restrict__ leave_start) {
   extern __shared__ int32_t lds_off[];
   __shared__ uint32_t s_heads[TB / WAVE];
-  load_offsets(lds_off, q.off, q.S);
+  __shared__ uint16_t s_coarse[IterFinder::COARSE + 1];
+  const IterFinder iteration = iter_finder(lds_off, s_coarse, q.off, q.S);
   const int lane = lane_id(), wave = threadIdx.x / WAVE;
   const int64_t base = (int64_t)blockIdx.x * LOOK_TILE + wave * (WAVE * LINK_CHUNKS);
   const int32_t start_end = last_head ? lds_off[(int32_t)(*last_head >> 32) + 1] : INT32_MAX;
@@ -928,7 +929,7 @@ __global__ __launch_bounds__(TB) void k_stays_links(Stays q, const uint64_t* __r
   int32_t it[LINK_CHUNKS + 1];
 #pragma unroll
   for (int k = 0; k <= LINK_CHUNKS; ++k)
-    it[k] = (cur[k] >> 32) != 0xFFFFFFFFull ? iter_of(lds_off, q.S, (int32_t)(uint32_t)cur[k]) : q.S;
+    it[k] = (cur[k] >> 32) != 0xFFFFFFFFull ? iteration((uint32_t)cur[k]) : q.S;
   // the next access of every pair's row, and whether the stay reaches it
   int32_t next[LINK_CHUNKS];
   uint32_t word[LINK_CHUNKS], more = 0, reach = 0, head = 0;      // bit k: chunk k
@@ -964,7 +965,7 @@ __global__ __launch_bounds__(TB) void k_stays_links(Stays q, const uint64_t* __r
   bool left_reaches = false;
   if ((left >> 32) != 0xFFFFFFFFull && (uint32_t)(left >> 32) == __shfl((uint32_t)(cur[0] >> 32), 0, WAVE)) {
     const int32_t j = __shfl(it[0], 0, WAVE);
-    left_reaches = stay_end(q, (uint32_t)iter_of(lds_off, q.S, (int32_t)(uint32_t)left), j,
+    left_reaches = stay_end(q, (uint32_t)iteration((uint32_t)left), j,
                             (uint32_t)(left >> 32), &q.ends[(uint32_t)left], j) == j;
   }
   uint32_t hit = 0, heads = 0;
@@ -1083,9 +1084,9 @@ constexpr int64_t WALK_TILE = (int64_t)TB * WALK_CHUNKS;
 
 // The iteration that ends a resident's stay from iteration i on, which does not reach a hit (right: the
 // position of the row's next access, if there is one), as a record.
-__device__ __forceinline__ uint32_t walk_leaves(const Stays& q, const int32_t* lds_off, const int32_t* never,
+__device__ __forceinline__ uint32_t walk_leaves(const Stays& q, const IterFinder& iteration, const int32_t* never,
                                                 uint32_t v, int32_t i, bool more, uint32_t right) {
-  const int32_t e = more ? stay_end(q, (uint32_t)i, iter_of(lds_off, q.S, (int32_t)right), v, nullptr, q.S)
+  const int32_t e = more ? stay_end(q, (uint32_t)i, iteration(right), v, nullptr, q.S)
                          : never_end(never, q.S, never_levels(q.S), i, v);
   return e < q.S ? (uint32_t)e : STAYS;
 }
@@ -1108,7 +1109,8 @@ __global__ __launch_bounds__(TB) void k_stays_walk(Stays q, const uint64_t* __re
     for (int x = threadIdx.x; x < never_levels(q.S) * (q.S + 1); x += TB) mine[x] = q.never[x];
     never = mine;
   }
-  load_offsets(lds_off, q.off, q.S);
+  __shared__ uint16_t s_coarse[IterFinder::COARSE + 1];
+  const IterFinder iteration = iter_finder(lds_off, s_coarse, q.off, q.S);
   const int lane = lane_id();
   const int64_t base = ((int64_t)blockIdx.x * (TB / WAVE) + threadIdx.x / WAVE) * (WAVE * WALK_CHUNKS);
   if (base >= n) return;                           // uniform over the wave
@@ -1146,7 +1148,7 @@ __global__ __launch_bounds__(TB) void k_stays_walk(Stays q, const uint64_t* __re
     stops[k] = __ballot(end);
     leave_of[k] = STAYS;
     if (end && ((hit[k] | ins[k]) >> lane & 1))
-      leave_of[k] = walk_leaves(q, lds_off, never, v, iter_of(lds_off, q.S, (int32_t)p), more, (uint32_t)right);
+      leave_of[k] = walk_leaves(q, iteration, never, v, iteration(p), more, (uint32_t)right);
   }
   uint32_t carry = STAYS;
 #pragma unroll
@@ -1164,7 +1166,7 @@ __global__ __launch_bounds__(TB) void k_stays_walk(Stays q, const uint64_t* __re
         const int at = __ffsll((unsigned long long)m) - 1;
         uint32_t leaves = STAYS;
         if (lane == at && y < n)
-          leaves = walk_leaves(q, lds_off, never, (uint32_t)(a >> 32), iter_of(lds_off, q.S, (int32_t)(uint32_t)a),
+          leaves = walk_leaves(q, iteration, never, (uint32_t)(a >> 32), iteration((uint32_t)a),
                                more, (uint32_t)r);
         carry = __shfl(leaves, at, WAVE);
         break;
@@ -1175,7 +1177,7 @@ __global__ __launch_bounds__(TB) void k_stays_walk(Stays q, const uint64_t* __re
     const uint32_t leaves = mine ? found : carry;
     const uint32_t v = (uint32_t)(cur[k] >> 32), p = (uint32_t)cur[k];
     if (ins[k] >> lane & 1)
-      leave_ins[slot[k]] = leaves == (uint32_t)(iter_of(lds_off, q.S, (int32_t)p) + 1) ? LEAVES_NEXT : leaves;
+      leave_ins[slot[k]] = leaves == (uint32_t)(iteration(p) + 1) ? LEAVES_NEXT : leaves;
     // a first access that hits is one of a start-state row
     uint32_t lv = (uint32_t)__shfl_up(v, 1, WAVE);
     const uint64_t before = k > 0 ? shfl_u64(cur[k > 0 ? k - 1 : 0], WAVE - 1) : left_of;
@@ -1195,12 +1197,13 @@ __global__ __launch_bounds__(TB) void k_lru_walk(Stays q, const uint64_t* __rest
   extern __shared__ uint64_t lds_limits[];         // [S], then the offsets [S + 1]
   int32_t* const lds_off = reinterpret_cast<int32_t*>(lds_limits + q.S);
   for (int x = threadIdx.x; x < q.S; x += TB) lds_limits[x] = q.limits[x];
-  load_offsets(lds_off, q.off, q.S);
+  __shared__ uint16_t s_coarse[IterFinder::COARSE + 1];
+  const IterFinder find = iter_finder(lds_off, s_coarse, q.off, q.S);
   const int lane = lane_id();
   const int64_t base = ((int64_t)blockIdx.x * (TB / WAVE) + threadIdx.x / WAVE) * (WAVE * WALK_CHUNKS);
   if (base >= n) return;                           // uniform over the wave
   auto iteration = [&](uint64_t pair) {
-    return (pair >> 32) != 0xFFFFFFFFull ? iter_of(lds_off, q.S, (int32_t)(uint32_t)pair) : q.S;
+    return (pair >> 32) != 0xFFFFFFFFull ? find((uint32_t)pair) : q.S;
   };
   // the stay of an access of row v in iteration i reaches the row's next access, in iteration j
   auto reaches = [&](uint32_t v, int32_t i, int32_t j) { return lru_key((uint32_t)i, v) >= lds_limits[j > 0 ? j - 1 : 0]; };
