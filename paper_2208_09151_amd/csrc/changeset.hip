@@ -292,9 +292,10 @@ __global__ __launch_bounds__(TB) void k_heads_write(const uint64_t* __restrict__
 
 // ---- part 2 -----------------------------------------------------------------------
 
+// (*last: the last of them, for the way that needs the heads' room)
 __global__ __launch_bounds__(TB) void k_init_state(const uint64_t* __restrict__ heads,
                                                    int64_t count, int32_t* __restrict__ init_ids,
-                                                   State st) {
+                                                   State st, uint64_t* __restrict__ last) {
   extern __shared__ uint32_t lds_hist[];  // S+1 bins
   for (int j = threadIdx.x; j <= st.S; j += TB) lds_hist[j] = 0;
   __syncthreads();
@@ -305,6 +306,7 @@ __global__ __launch_bounds__(TB) void k_init_state(const uint64_t* __restrict__ 
     // Belady: the key of a prefetched row is its first access; LRU: it has not been used
     // yet, which is the oldest possible key
     const int32_t first = st.lru ? st.S : (int32_t)(h >> 32);
+    if (s == count - 1) *last = h;
     init_ids[s] = v;
     st.res_id[s] = v;
     st.res_next[s] = first;
@@ -880,6 +882,7 @@ constexpr int MARK_ITEMS = 8;   // lines / accesses per thread in the mark phase
 // to drop is the iteration's length minus R_i[i], the residents keyed to it.  So the threshold
 // bucket j* of every iteration, the number of rows to drop from it, and R_{i+1} follow from S
 // histograms of the trace.  stays.hpp turns them into the changesets.
+#include "deal.hpp"
 #include "stays.hpp"
 #include "fits.hpp"
 #include "small.hpp"
@@ -2196,12 +2199,12 @@ Workspace carve(void* base, int64_t num_nodes, int64_t total, int32_t S, int64_t
   w.max_heads = t < num_nodes ? t : num_nodes;
   w.pairs_a = a.take<uint64_t>(t);
   w.pairs_b = a.take<uint64_t>(t);
-  w.heads_a = a.take<uint64_t>(w.max_heads);
+  w.heads_a = a.take<uint64_t>(w.max_heads);   // (these three side by side, see stays_run)
   w.heads_b = a.take<uint64_t>(w.max_heads);
+  w.next_iter = a.take<int32_t>(t);
   w.hist = a.take<uint32_t>(radix_plan(t).hist_elems);
   w.look_tiles = ceil_div(t, LOOK_TILE);
   w.head_tiles = a.take<uint32_t>(w.look_tiles + 1 + scan_scratch_elems(w.look_tiles + 1));
-  w.next_iter = a.take<int32_t>(t);
   w.key_hists = a.take<uint32_t>(S <= STATIC_S_MAX ? (size_t)S * (S + 1) : 0);
   w.cuts = a.take<Cut>(S);
   w.first_of = a.take<int32_t>(num_nodes);   // resumed superbatches only
@@ -2384,12 +2387,24 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
     longest = std::max<int64_t>(longest, ids_offsets[i + 1] - ids_offsets[i]);
 
   // both ends of every stay, the thresholds, the table
-  const int64_t windows = ceil_div(total, ENDS_WINDOW);
-  const int64_t window = windows <= ENDS_WINDOWS_MAX ? ceil_div(total, windows) : total;
-  for (int64_t from = 0; from < total; from += window)
-    hipLaunchKernelGGL(k_stay_ends, dim3((unsigned)w.look_tiles), dim3(TB), off_lds, st, sorted, total,
-                       w.d_offsets, S, last_head, held_bits, (uint32_t)from,
-                       (uint32_t)std::min(total, from + window), ends);
+  // many of them through windows of positions, where the results have room in between: in the heads and the array of
+  // next iterations, neither of which holds anything here (the last head was put aside), the tiles' starts in the
+  // counters of the sort
+  const Dealt dealt{w.heads_a, reinterpret_cast<uint16_t*>(w.hist), total, (int32_t)deal_windows(total)};
+  const int64_t room = reinterpret_cast<uint64_t*>(w.next_iter + total) - w.heads_a;
+  if (total >= DEAL_MIN && total <= DEAL_TOTAL_MAX && total <= room &&
+      deal_start_bytes(total) <= sizeof(uint32_t) * radix_plan(total).hist_elems) {
+    hipLaunchKernelGGL(k_stay_deal, dim3((unsigned)deal_tiles(total)), dim3(DEAL_THREADS), 0, st, sorted, total,
+                       w.d_offsets, S, last_head, held_bits, dealt);
+    collect_async(dealt, PutEnds{ends, w.d_offsets, S}, off_lds, st);
+  } else {
+    const int64_t windows = ceil_div(total, ENDS_WINDOW);
+    const int64_t window = windows <= ENDS_WINDOWS_MAX ? ceil_div(total, windows) : total;
+    for (int64_t from = 0; from < total; from += window)
+      hipLaunchKernelGGL(k_stay_ends, dim3((unsigned)w.look_tiles), dim3(TB), off_lds, st, sorted, total,
+                         w.d_offsets, S, last_head, held_bits, (uint32_t)from,
+                         (uint32_t)std::min(total, from + window), ends);
+  }
   GINEX_HIP(zero_async(Zeros().add(w.key_hists, (int64_t)S * (S + 1)).add(pl.arr_cur, S + 1), st));
   hipLaunchKernelGGL(k_key_hists, dim3((unsigned)ceil_div(longest, TB * TOUCH_ITEMS), (unsigned)S),
                      dim3(TB), sizeof(uint32_t) * (S + 1), st, ends, w.d_offsets, S, w.key_hists);
@@ -2973,7 +2988,8 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
                     who, bad);
     } else {
       hipLaunchKernelGGL(k_init_state, dim3((unsigned)blocks), dim3(TB),
-                         sizeof(uint32_t) * (S + 1), st, heads, cap, init_ids, state);
+                         sizeof(uint32_t) * (S + 1), st, heads, cap, init_ids, state,
+                         reinterpret_cast<uint64_t*>(w.d_counts));
       GINEX_LAUNCH_CHECK();
     }
   }
@@ -3168,7 +3184,7 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
     }
     uint64_t* const ends = sorted == w.pairs_a ? w.pairs_b : w.pairs_a;
     uint64_t* const rows = heads == w.heads_a ? w.heads_b : w.heads_a;
-    return stays_run(who, w, sorted, ends, rows, distinct, start_ids ? nullptr : heads + (cap - 1),
+    return stays_run(who, w, sorted, ends, rows, distinct, start_ids ? nullptr : reinterpret_cast<uint64_t*>(w.d_counts),
                      held_bits, accessed, ids, ids_offsets, total, S, in_ids, out_ids, in_positions,
                      cs_capacity, cs_offsets, miss_count,
                      src_line, total_changes, init_ready, start_ids != nullptr, final_ids, st);

@@ -78,6 +78,7 @@ __device__ __forceinline__ bool in_start_state(uint32_t v, int32_t first, const 
 // One pass over the node-sorted pairs: the ends of every access's stays, written at its position
 // (one scattered word per access; bound by that store).  A wave takes LOOK_ITEMS * 64 consecutive pairs
 // and passes positions and iterations on to the neighbours, so that each is read and searched once.
+// For up to 2^26 accesses, or where the results have no room between two kernels (see deal.hpp).
 // Scattered words are collected in the 256 MB memory-side cache as long as the window of positions
 // [from, to) that a launch writes fits there (33 M accesses: 0.50 ms, 66 G words/s); beyond it they go
 // to memory one by one (154 M: 6.1 ms, 25 G/s).  So one launch per ENDS_WINDOW positions, each reading
@@ -139,6 +140,77 @@ __global__ __launch_bounds__(TB) void k_stay_ends(const uint64_t* __restrict__ s
     ends[p] = ((uint64_t)next << 48) | ((uint64_t)prev << 32) | prev_pos;
   }
 }
+
+// The same dealt by windows of positions (see deal.hpp): place in the window, next (12 bits: S is at most 2 048),
+// previous access (its position + 2, or one of the two below).  The iteration of the previous access is
+// searched anew when the word is put to its place.
+constexpr uint32_t DEAL_NO_STAY = 0, DEAL_FROM_START = 1;
+
+__global__ __launch_bounds__(DEAL_THREADS) void k_stay_deal(const uint64_t* __restrict__ sorted, int64_t n,
+                                                            const int64_t* __restrict__ off, int32_t S,
+                                                            const uint64_t* __restrict__ last_head,
+                                                            const uint32_t* __restrict__ held, Dealt d) {
+  __shared__ DealShared sh;
+  __shared__ int32_t lds_off[STATIC_S_MAX + 1];
+  __shared__ uint16_t s_coarse[IterFinder::COARSE + 1];
+  deal_clear(d, sh);
+  const IterFinder find = iter_finder(lds_off, s_coarse, off, S);
+  const int lane = lane_id();
+  const int64_t base = (int64_t)blockIdx.x * DEAL_TILE + (threadIdx.x / WAVE) * (WAVE * DEAL_ITEMS);
+  uint64_t cur[DEAL_ITEMS + 1];                    // as in k_stay_ends
+#pragma unroll
+  for (int k = 0; k <= DEAL_ITEMS; ++k) {
+    const int64_t x = base + k * WAVE + (k < DEAL_ITEMS ? lane : 0);
+    cur[k] = x < n ? sorted[x] : ~0ull;
+  }
+  uint64_t before = base > 0 && base - 1 < n ? sorted[base - 1] : ~0ull;
+  auto iteration = [&](uint64_t pair) { return (pair >> 32) != 0xFFFFFFFFull ? find((uint32_t)pair) : S; };
+  uint32_t at[DEAL_ITEMS];
+  uint64_t word[DEAL_ITEMS];
+  int32_t it = iteration(cur[0]);
+#pragma unroll
+  for (int k = 0; k < DEAL_ITEMS; ++k) {
+    const int32_t it_next = iteration(cur[k + 1]);
+    const uint32_t v = (uint32_t)(cur[k] >> 32), p = (uint32_t)cur[k];
+    const bool valid = base + k * WAVE + lane < n;
+    uint32_t lv = __shfl_up(v, 1, WAVE), lp = __shfl_up(p, 1, WAVE), rv = __shfl_down(v, 1, WAVE);
+    int32_t ri = __shfl_down(it, 1, WAVE);
+    const uint32_t ov = __shfl((uint32_t)(cur[k + 1] >> 32), 0, WAVE);
+    const int32_t oi = __shfl(it_next, 0, WAVE);
+    if (lane == 0) {
+      lv = (uint32_t)(before >> 32);
+      lp = (uint32_t)before;
+    }
+    if (lane == WAVE - 1) {
+      rv = ov;
+      ri = oi;
+    }
+    before = shfl_u64(cur[k], WAVE - 1);
+    uint32_t prev = DEAL_NO_STAY;
+    if (lv == v) prev = lp + 2;
+    else if (valid && in_start_state(v, it, last_head, held)) prev = DEAL_FROM_START;
+    const uint32_t next = rv == v ? (uint32_t)ri : (uint32_t)S;
+    word[k] = (uint64_t)(p & ((1u << WINDOW_SHIFT) - 1u)) << 44 | (uint64_t)next << 32 | prev;
+    at[k] = valid ? deal_place(sh, p) : NOT_DEALT;
+    it = it_next;
+  }
+  deal_out(d, sh, word, at);
+}
+
+struct PutEnds {
+  uint64_t* ends;
+  const int64_t* off;
+  int32_t S;
+  __device__ __forceinline__ void operator()(int64_t first, uint64_t word, const IterFinder& iteration) const {
+    const uint32_t code = (uint32_t)word;
+    uint32_t prev_pos = 0, prev = code == DEAL_NO_STAY ? NO_STAY : FROM_START;
+    if (code > DEAL_FROM_START) {
+      prev_pos = code - 2;
+      prev = (uint32_t)iteration(prev_pos);
+    }
+    ends[first + (int64_t)(word >> 44)] = ((word >> 32 & 0xFFFu) << 48) | ((uint64_t)prev << 32) | prev_pos;
+  }
+};
 
 // table[j][s], for a stay that ends at j and is followed from iteration s on: low half the first
 // t in [s, j) with j*_t < j (j if there is none), high half the first cut of bucket j in front of
