@@ -2615,8 +2615,8 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
   return finish();
 }
 
-// The tiles and buckets of a call (see fits.hpp): ids, places and starts in `buffer`, 8 bytes per access, and up to
-// `spare` bytes behind the starts for the caller.  buckets = 0 where this way does not serve the shape.
+// The tiles and buckets of a call (see fits.hpp): ids and places in ids_buffer, 6 bytes per access, the starts in
+// start_buffer (*start_bytes of its start_room).  buckets = 0 where this way does not serve the shape.
 Fit fit_shape(const Workspace& w, int64_t num_nodes, int64_t total, int32_t S, int64_t max_n, uint64_t* ids_buffer,
               uint64_t* start_buffer, size_t start_room, size_t* start_bytes) {
   Fit f{};

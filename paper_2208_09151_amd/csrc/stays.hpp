@@ -22,10 +22,10 @@
 // LRU goes the same way with other thresholds, see "LRU" below.
 //
 // 200 iterations of 163 840 accesses, 111 M nodes, every iteration evicts: that loop 200 x 41 us, and
-// 0.83 ms to look right.  Here: k_stay_ends 0.50 ms (scattered words), k_key_hists 0.05,
+// 0.83 ms to look right.  Here: k_stay_ends 0.49 ms (scattered words), k_key_hists 0.05,
 // k_static_roll 0.16, 17 levels of k_cut_members + k_cut_decide 0.020 + 0.010 each (two chains of
-// dependent reads), k_stays_mark 0.19 (random words of the table, L2), k_stays_links 0.31 (one random
-// word per pair, 106 G/s), bucket "never" 0.11, k_stays_walk 0.53, k_step_lines 200 x 7.7 us (most of
+// dependent reads), k_stays_mark 0.14 (random words of the table, L2), k_stays_links 0.28 (one random
+// word per pair, 117 G/s), bucket "never" 0.11, k_stays_walk 0.40, k_ins_emit 0.06, k_step_lines 200 x 7.7 us (most of
 // it latency: launch, flags, counters, records, each waiting for the one before).
 #pragma once
 
@@ -241,11 +241,14 @@ __global__ __launch_bounds__(WAVE) void k_stay_table(const Cut* __restrict__ cut
 
 // The iteration that drops row v during its stay [i, j), j if none does; cuts from `limit` on are
 // not looked at (they may not have been decided yet).  own: the access that began the stay, as a
-// word of `ends` (its BYPASSED bit is read only if the cut of its own iteration is in bucket j).
-__device__ __forceinline__ int32_t stay_end(const Stays& q, uint32_t i, int32_t j, uint32_t v,
+// word of `ends` (its BYPASSED bit is read only if the cut of its own iteration is in bucket j).  w: the
+// table's word for them.
+__device__ __forceinline__ uint32_t stay_word(const Stays& q, uint32_t i, int32_t j) {
+  return q.table[(int64_t)j * q.S + (i >= FROM_START ? 0u : i)];
+}
+__device__ __forceinline__ int32_t stay_end(const Stays& q, uint32_t w, uint32_t i, int32_t j, uint32_t v,
                                             const uint64_t* own, int32_t limit) {
   const uint32_t* row = q.table + (int64_t)j * q.S;
-  const uint32_t w = row[i == FROM_START ? 0u : i];
   uint32_t t = w >> 16;
   while (t != NO_CUT && (int32_t)t < limit) {
     const Cut c = q.cuts[t];
@@ -255,6 +258,11 @@ __device__ __forceinline__ int32_t stay_end(const Stays& q, uint32_t i, int32_t 
     t = row[t + 1] >> 16;
   }
   return (int32_t)(w & 0xFFFFu);
+}
+
+__device__ __forceinline__ int32_t stay_end(const Stays& q, uint32_t i, int32_t j, uint32_t v,
+                                            const uint64_t* own, int32_t limit) {
+  return stay_end(q, stay_word(q, i, j), i, j, v, own, limit);
 }
 
 // Rows that are never accessed again sit in the bucket that most of the last iterations cut, so
@@ -296,11 +304,11 @@ __device__ __forceinline__ int32_t never_end(const int32_t* never, int32_t S, in
 
 __device__ __forceinline__ int never_levels(int32_t S) { return 32 - __clz(S); }   // 2^levels > S
 
-// Does the access with these ends (iteration j, row v) hit?
-__device__ __forceinline__ bool stay_hits(const Stays& q, uint64_t ends, int32_t j, uint32_t v) {
+// Does the access with these ends (iteration j, row v; w as above) hit?
+__device__ __forceinline__ bool stay_hits(const Stays& q, uint32_t w, uint64_t ends, int32_t j, uint32_t v) {
   const uint32_t prev = stay_prev(ends);
   if (prev == NO_STAY) return false;
-  return stay_end(q, prev, j, v, prev == FROM_START ? nullptr : &q.ends[stay_prev_pos(ends)], j) == j;
+  return stay_end(q, w, prev, j, v, prev == FROM_START ? nullptr : &q.ends[stay_prev_pos(ends)], j) == j;
 }
 
 // Is a miss of an iteration with cut c, next accessed in iteration `next`, inserted?  (One that is never
@@ -362,7 +370,7 @@ __global__ __launch_bounds__(TB) void k_cut_members(Stays q, Jobs jobs) {
                                    prev == FROM_START ? nullptr : &q.ends[stay_prev_pos(w[k])], t);
       kind[k] = end >= t ? 1u : 0u;
     } else if (stay_next(w[k]) == j) {            // an access of iteration t that begins one
-      kind[k] = stay_hits(q, w[k], t, v[k]) ? 1u : 2u;
+      kind[k] = stay_hits(q, stay_word(q, stay_prev(w[k]), t), w[k], t, v[k]) ? 1u : 2u;
       if (kind[k] == 2) v[k] = (uint32_t)(to + (x - nj));
     }
     n_res += kind[k] == 1;
@@ -663,38 +671,52 @@ __global__ __launch_bounds__(TB) void k_stays_mark(Stays q, int64_t n, int32_t* 
   extern __shared__ int32_t lds_off[];
   load_offsets(lds_off, q.off, q.S);
   const int64_t base = (int64_t)blockIdx.x * CUT_TILE;
-  int32_t i = iter_of(lds_off, q.S, (int32_t)base);   // of the tile's first access; advanced below
+  const int32_t i0 = iter_of(lds_off, q.S, (int32_t)base);   // of the tile's first access; advanced below
+  // what every access has to read is asked for first, level by level; only where a cut decides is there more
+  // (one access after the other: 192 us for 33 M accesses, 141 this way, 4 TB/s)
   uint64_t w[CUT_ITEMS];
+  uint32_t v[CUT_ITEMS], e[CUT_ITEMS];
 #pragma unroll
   for (int k = 0; k < CUT_ITEMS; ++k) {
     const int64_t p = base + k * TB + threadIdx.x;
     w[k] = q.ends[p < n ? p : base];
+    v[k] = (uint32_t)q.ids[p < n ? p : base];
   }
+  if (!LRU) {
+    int32_t i = i0;
+#pragma unroll
+    for (int k = 0; k < CUT_ITEMS; ++k) {
+      const int64_t p = base + k * TB + threadIdx.x;
+      while (i + 1 < q.S && lds_off[i + 1] <= (int32_t)p) ++i;
+      e[k] = stay_word(q, stay_prev(w[k]), i);
+    }
+  }
+  int32_t i = i0;
+  Cut c{};
+  uint64_t limit = 0;                              // of the iteration in front (an earlier one accessed the row)
+  if (LRU) limit = q.limits[i > 0 ? i - 1 : 0];
+  else c = q.cuts[i];
 #pragma unroll
   for (int k = 0; k < CUT_ITEMS; ++k) {
     const int64_t p = base + k * TB + threadIdx.x;
     bool inserted = false, hit = false;
     if (p < n) {
+      const int32_t before = i;
       while (i + 1 < q.S && lds_off[i + 1] <= (int32_t)p) ++i;
+      if (i != before) {
+        if (LRU) limit = q.limits[i - 1];
+        else c = q.cuts[i];
+      }
       const uint32_t prev = stay_prev(w[k]);
       if (LRU) {
         hit = prev == FROM_START;
-        if (prev < FROM_START) {
-          const uint64_t limit = q.limits[i > 0 ? i - 1 : 0];   // (i > 0: an earlier iteration accessed the row)
-          hit = prev == (uint32_t)(limit >> 32) ? lru_key(prev, (uint32_t)q.ids[p]) >= limit
-                                                : prev > (uint32_t)(limit >> 32);
-        }
+        if (prev < FROM_START)
+          hit = prev == (uint32_t)(limit >> 32) ? lru_key(prev, v[k]) >= limit : prev > (uint32_t)(limit >> 32);
         inserted = !hit;
-      } else if (prev != NO_STAY) {
-        const uint32_t e = q.table[(int64_t)i * q.S + (prev == FROM_START ? 0u : prev)];
-        // (the id is read only where a cut has to be looked at)
-        hit = (e >> 16) == NO_CUT ? (int32_t)(e & 0xFFFFu) == i
-                                  : stay_hits(q, w[k], i, (uint32_t)q.ids[p]);
-      }
-      if (!LRU && !hit) {
-        const Cut c = q.cuts[i];
-        const int32_t next = stay_next(w[k]);
-        inserted = stay_inserts(q, c, next, next == c.jstar ? (uint32_t)q.ids[p] : 0u);
+      } else {
+        if (prev != NO_STAY)
+          hit = (e[k] >> 16) == NO_CUT ? (int32_t)(e[k] & 0xFFFFu) == i : stay_hits(q, e[k], w[k], i, v[k]);
+        if (!hit) inserted = stay_inserts(q, c, stay_next(w[k]), v[k]);
       }
       if (src_line) src_line[p] = hit ? 0 : -1;
     }
