@@ -2567,6 +2567,10 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
     // the second scratch bitmap, one counter for 512 lines or more against one word for 32 ids
     uint64_t* flags[2] = {state.evict_words, reinterpret_cast<uint64_t*>(state.bitmap)};
     uint32_t* counts = state.bitmap_in;
+    // (see DENSE_SHARE)
+    auto is_dense = [&](int64_t n) {
+      return n * DENSE_SHARE > state.cap || (lru && n > 0 && s.tiles <= DENSE_TILES);
+    };
     GINEX_HIP(zero_async(Zeros().add(flags[0], s.words).add(flags[1], s.words).add(counts, 3 * stride), st));
     s.leaving = leaving;
     s.leave_ins = leave_ins;
@@ -2581,7 +2585,7 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
     s.next_dst = 0;
     s.next_n = cs[1];
     s.next_filled = pl.arr_cur;
-    if (cs[1] * DENSE_SHARE > state.cap)
+    if (is_dense(cs[1]))
       hipLaunchKernelGGL(k_step_flags<true>, dim3((unsigned)flag_blocks(0, true)), dim3(TB), 0, st, s);
     else if (cs[1] > 0)
       hipLaunchKernelGGL(k_step_flags<false>, dim3((unsigned)flag_blocks(0, false)), dim3(TB), 0, st, s);
@@ -2591,7 +2595,7 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
       s.cnt_now = counts + (t % 3) * stride;
       s.cnt_next = counts + ((t + 1) % 3) * stride;
       s.cnt_clear = counts + ((t + 2) % 3) * stride;
-      const bool dense = std::max(changes(t), changes(t + 1)) * DENSE_SHARE > state.cap;
+      const bool dense = is_dense(std::max(changes(t), changes(t + 1)));
       const int64_t line_words = dense ? (large ? 64 : 8) : large ? 256 : 64;
       s.emit_blocks = M > 0 ? ceil_div(s.words, line_words) : 0;
       s.flag_blocks = flag_blocks(t + 1, dense);

@@ -1454,6 +1454,11 @@ __device__ __forceinline__ void flag_line(const Step& s, int32_t line) {
 // a few hundred tiles queue up, and blocks of 4 096 lines have many rounds of evictions to go.  A block
 // takes the lines of one tile and counts in LDS first then, as far as the tiles have room there (36 k
 // lines, about 20 k changes: 51 -> 9.5 us per iteration; 1.2 M lines, 0.4 M changes: 112 -> 45).
+// LRU gives lines up in the order in which they were taken, so that an iteration's lie side by side and meet in
+// a few counters however few they are: DENSE as long as the tiles' counters are in LDS (100 x 150 000 accesses, 1.4 M
+// lines, 22 k changes: 4 588 -> 2 863 us a call; 60 x 600 000, 4.9 M lines: 8 989 -> 4 491; 567 changes in 2.7 M lines:
+// 1 716 -> 1 611).  Belady's are spread, and the small tiles of DENSE cost more than they save (1.4 M lines, 4 k changes:
+// 2 192 against 2 545).
 constexpr int DENSE_SHARE = 16;
 constexpr int DENSE_TILES = 4096;
 constexpr int64_t DENSE_ENTRIES = 2048;   // of the list of leaving lines, to a block at a time

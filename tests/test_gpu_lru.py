@@ -45,7 +45,10 @@ def test_caches_around_the_longest_iteration(ginex, S, longest, hot, monkeypatch
 
 # few large iterations, where blocks of lines and tiles have many entries; sizes beyond the oracle's reach
 @pytest.mark.parametrize("n,S,length,cap", [(4_000_000, 12, 400_000, 1_000_000), (9_000_000, 6, 2_500_000, 4_500_000),
-                                            (9_000_000, 6, 2_500_000, 2_500_000), (60_000_000, 40, 30_000, 31_000)])
+                                            (9_000_000, 6, 2_500_000, 2_500_000), (60_000_000, 40, 30_000, 31_000),
+                                            # few changes, few of many lines; counters of 2^24 lines fit LDS, of more not
+                                            (3_000_000, 40, 60_000, 1_000_000), (20_000_000, 12, 600_000, 4_000_000),
+                                            (40_000_000, 5, 8_000_000, 2**24), (40_000_000, 5, 8_000_000, 2**24 + 1)])
 def test_large_traces_equal_the_loop(ginex, n, S, length, cap, monkeypatch):  # noqa: F811
     gen = torch.Generator(device="cuda").manual_seed(cap)
     off = np.arange(S + 1, dtype=np.int64) * length
