@@ -676,7 +676,7 @@ def main():
         "sample_ms": mid["sample_s"] * 1e3,
         "changeset_accesses_per_s": accesses / mid["changeset_s"],
         "changeset_ms": mid["changeset_s"] * 1e3,
-        "changeset_note": ("every row of the superbatch fits the cache: next-use sort and C_0 only, "
+        "changeset_note": ("every row of the superbatch fits the cache: C_0 and every access's line only, "
                            "nothing is evicted (it is in legs.pressure)"
                            if int(np.sum(timers["changes"])) == 0 and all_hit else
                            "iterations of the timed steps evict"),
