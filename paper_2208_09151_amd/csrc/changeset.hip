@@ -2372,7 +2372,8 @@ int32_t stays_cuts(const Workspace& w, const Stays& q, const int64_t* ids_offset
 int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, uint64_t* ends,
                   uint64_t* rows, int64_t distinct, const uint64_t* last_head,
                   const uint32_t* held_bits, const uint32_t* accessed, const int32_t* ids,
-                  const int64_t* ids_offsets, int64_t total, int32_t S, int32_t* in_ids, int32_t* out_ids, int32_t* in_positions,
+                  const int64_t* ids_offsets, int64_t total, int32_t S, int32_t* in_ids, int32_t* out_ids,
+                  int32_t* in_positions,
                   int64_t cs_capacity, int64_t* cs_offsets, int64_t* miss_count, int32_t* src_line,
                   int64_t* total_changes, int64_t* init_ready, bool carried, int32_t* final_ids, hipStream_t st) {
   const State& state = w.st;
@@ -2433,7 +2434,8 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
   };
   if (distinct == total && !lru) {
     // no row is accessed twice (a superbatch of one iteration, for one): nothing is inserted, so the lists stay
-    // empty and the lines are those of the start state (one iteration of 15 k accesses, 2 k lines carried: 457 -> 311 us per call)
+    // empty and the lines are those of the start state (one iteration of 15 k accesses, 2 k lines carried:
+    // 457 -> 311 us per call)
     if (src_line) {
       Step s{};
       s.ids = ids;
@@ -2914,8 +2916,10 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
   // 434, three on 111 M nodes 507 against 537.  GINEX_STATIC_THRESHOLDS=0/1 chooses the loop / the trace.
   // LRU (the trace's way has no cuts): 20 000 nodes, iterations of 3 000 accesses, two 311 against 332, three 355
   // and 342, six 472 and 396; 200 000 nodes, of 20 000, two 344 and 380, three 406 and 412.
-  const bool smallest = lru ? S <= LOOP_LRU_S && total <= LOOP_LRU_IDS && num_nodes <= LOOP_NODES : S <= LOOP_S && total <= (S <= LOOP_S / 2 ? 4 * LOOP_IDS : LOOP_IDS) &&
-                        num_nodes <= LOOP_NODES && distinct < total;
+  const bool smallest =
+      num_nodes <= LOOP_NODES &&
+      (lru ? S <= LOOP_LRU_S && total <= LOOP_LRU_IDS
+           : S <= LOOP_S && total <= (S <= LOOP_S / 2 ? 4 * LOOP_IDS : LOOP_IDS) && distinct < total);
   const bool stays = S <= STATIC_S_MAX && (!lru || max_n <= cap) &&
                      (static_env ? static_env[0] != '0' : !smallest);
   const bool loop = !stays;   // (the loop still is the last way out of the planned path then)
