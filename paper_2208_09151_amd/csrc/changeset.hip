@@ -2291,9 +2291,10 @@ extern "C" size_t ginex_changeset_workspace_bytes(int64_t num_nodes, int64_t tot
 namespace ginex {
 namespace {
 
-// Belady's thresholds and cuts, from the histograms (see stays.hpp); *never: bucket "never" is cut.
+// Belady's thresholds and cuts, from the histograms (see stays.hpp); *never: bucket "never" is cut.  jobs: read by a
+// copy to the device that is not waited for here, so the caller keeps it until it has waited.
 int32_t stays_cuts(const Workspace& w, const Stays& q, const int64_t* ids_offsets, int64_t* miss_count, bool* never,
-                   hipStream_t st) {
+                   std::vector<int32_t>& jobs, hipStream_t st) {
   const State& state = w.st;
   const Plan& pl = w.plan;
   const int32_t S = q.S;
@@ -2312,7 +2313,7 @@ int32_t stays_cuts(const Workspace& w, const Stays& q, const int64_t* ids_offset
 
   // the levels: a cut waits for the cuts of the bucket its own iteration's accesses come from, and for
   // the earlier cuts of its bucket
-  std::vector<int32_t> jobs, level_of_bucket(S + 1, 0);
+  std::vector<int32_t> level_of_bucket(S + 1, 0);
   std::vector<std::vector<int32_t>> levels;
   for (int32_t t = 0; t < S; ++t) {
     const Cut& c = cuts[t];
@@ -2410,11 +2411,12 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
   hipLaunchKernelGGL(k_key_hists, dim3((unsigned)ceil_div(longest, TB * TOUCH_ITEMS), (unsigned)S),
                      dim3(TB), sizeof(uint32_t) * (S + 1), st, ends, w.d_offsets, S, w.key_hists);
   bool never = false;      // bucket "never" is cut
+  std::vector<int32_t> jobs;   // of the cuts
   if (lru) {
     hipLaunchKernelGGL(k_lru_counts, dim3((unsigned)S), dim3(WAVE), 0, st, S, w.key_hists);
     hipLaunchKernelGGL(k_lru_limits, dim3((unsigned)S), dim3(BIG), 0, st, q, w.key_hists, state.cap, limits);
     GINEX_LAUNCH_CHECK();
-  } else if (int32_t rc = stays_cuts(w, q, ids_offsets, miss_count, &never, st)) {
+  } else if (int32_t rc = stays_cuts(w, q, ids_offsets, miss_count, &never, jobs, st)) {
     return rc;
   }
 

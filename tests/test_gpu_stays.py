@@ -252,3 +252,16 @@ def test_smallest_calls(ginex, n, sizes, monkeypatch):  # noqa: F811
             check_changeset(made[0][0], oracle.changeset(n, ids, off, cap), (n, ids, off))
             check_resumed(made[0][1], oracle.changeset_resume(n, ids, off, cap, start.cpu().numpy()),
                           (n, ids, off))
+
+
+def test_levels_of_many_cuts(ginex, monkeypatch):  # noqa: F811
+    """182 cuts in the largest level (counted by a simulation of the trace): more than go in a launch's arguments."""
+    rng = np.random.default_rng(1)
+    n, S, length, cap = 20_000, 2000, 40, 5000
+    off = np.arange(S + 1, dtype=np.int64) * length
+    ids = np.concatenate([rng.choice(n, length, replace=False) for _ in range(S)]).astype(np.int32)
+    ref = oracle.changeset(n, ids, off, cap)
+    assert ref["miss_count"].sum() > 0
+    for way in ("1", "0"):
+        monkeypatch.setenv("GINEX_STATIC_THRESHOLDS", way)
+        check_changeset(ginex.changeset(n, torch.from_numpy(ids).cuda(), off, cap), ref, (n, ids, off))
