@@ -168,7 +168,8 @@ int32_t ginex_neighbor_cache_build(const ginex_csr_t* g /*host struct*/, int64_t
  * and start iteration i as soon as that prefix is in place, provided no changeset has been
  * applied yet (a changeset may evict a row that was not loaded yet).
  * Preconditions (ids in range, ids distinct inside an iteration) are the caller's duty and
- * unchecked by default; with GINEX_VALIDATE=1 in the environment they are checked on the
+ * unchecked by default, but for ids out of range where the way that a call takes meets them (GINEX_ERR_INPUT
+ * then too); with GINEX_VALIDATE=1 in the environment they are checked on the
  * device first and a violation returns GINEX_ERR_INPUT before anything else runs.
  * Limits: 1 <= S <= 8191, total ids < 2^31.
  * ------------------------------------------------------------------------------- */

@@ -2660,10 +2660,10 @@ void fit_place_async(const Fit& f, int32_t* src_line, hipStream_t st) {
 dim3 fit_grid(const Fit& f) { return dim3((unsigned)(ceil_div(f.buckets, 8) * 8)); }
 
 // A fresh cache that holds every row (see fits.hpp): *distinct rows of the superbatch, and if they fit `cap`, the
-// results; -1 where this way does not serve the shape or met an id out of range.
-int32_t fits_run(const Workspace& w, int64_t num_nodes, const int32_t* ids, int64_t total, int32_t S, int64_t max_n,
-                 int64_t cap, int32_t* init_ids, int32_t* src_line, int64_t* init_ready, int64_t* distinct,
-                 hipStream_t st) {
+// results; -1 where this way does not serve the shape.
+int32_t fits_run(const char* who, const Workspace& w, int64_t num_nodes, const int32_t* ids, int64_t total, int32_t S,
+                 int64_t max_n, int64_t cap, int32_t* init_ids, int32_t* src_line, int64_t* init_ready,
+                 int64_t* distinct, hipStream_t st) {
   *distinct = -1;
   size_t start_bytes;
   const size_t room = sizeof(uint64_t) * total;
@@ -2682,7 +2682,10 @@ int32_t fits_run(const Workspace& w, int64_t num_nodes, const int32_t* ids, int6
   GINEX_HIP(hipMemcpyAsync(ready.data(), w.d_ready, sizeof(int64_t) * S, hipMemcpyDeviceToHost, st));
   GINEX_HIP(hipStreamSynchronize(st));
   *distinct = ready[S - 1];
-  if (*distinct < 0 || *distinct > cap) return GINEX_OK;
+  // (the other ways would use such an id as an index)
+  if (*distinct < 0)
+    return fail(GINEX_ERR_INPUT, "%s: ids out of range, there are %lld nodes", who, (long long)num_nodes);
+  if (*distinct > cap) return GINEX_OK;
   if (init_ready) std::copy(ready.begin(), ready.end(), init_ready);
   hipLaunchKernelGGL(k_fit_lines, fit_grid(f), dim3(FIT_LINE_THREADS), fit_lines_lds(f), st, f, init_ids,
                      src_line != nullptr);
@@ -2778,7 +2781,7 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
   int64_t rows = -1;
   const bool certain = cap >= std::min(total, num_nodes);
   if (!start_ids && cap > 0 && !validate && (certain || (4 * cap >= 3 * total && total >= FIT_GUESS_MIN))) {
-    if (int32_t rc = fits_run(w, num_nodes, ids, total, S, max_n, cap, init_ids, src_line, init_ready,
+    if (int32_t rc = fits_run(who, w, num_nodes, ids, total, S, max_n, cap, init_ids, src_line, init_ready,
                               &rows, st))
       return rc;
     if (rows >= 0 && rows <= cap) {

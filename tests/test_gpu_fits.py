@@ -86,6 +86,20 @@ def test_ids_out_of_range_go_the_other_way(ginex):  # noqa: F811
         ginex.changeset(64, ids, np.array([0, 50, 100]), 64)
 
 
+# fewer distinct ids than nodes, so that their number says nothing: beyond the last node in its word of the bitmap, its
+# bucket, the last bucket, negative
+@pytest.mark.parametrize("bad", [1000, 1023, 1024, 2047, 2048, 2**31 - 1, -1])
+def test_ids_out_of_range_are_refused(ginex, bad):  # noqa: F811
+    ids, off = trace(1000, (100, 0, 200), 7)
+    for policy in ("belady", "lru"):
+        ginex.changeset(1000, ids, off, 1000, policy=policy)
+    ids[150] = bad
+    for policy in ("belady", "lru"):
+        for with_lines in (True, False):
+            with pytest.raises(ginex.GinexError, match="out of range"):
+                ginex.changeset(1000, ids, off, 1000, policy=policy, with_lines=with_lines)
+
+
 # a carried cache that holds every row: its lines by bucket, up to three slices to one, rows that are not inserted;
 # against the way that takes it as any other cache
 @pytest.mark.parametrize("n,low,length,cap", [(20_000_000, 200_000, 150_000, 400_000), (20_000_000, 9000, 9000, 12_000),
