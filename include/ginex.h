@@ -21,13 +21,16 @@
  *    outputs and the contents of the output arrays are unspecified.
  *  - Node ids are int32 in [0, num_nodes); CSR offsets are int32 or int64.
  *  - Environment switches, read at every call; none changes a result, only the way to it:
- *      GINEX_VALIDATE=1       check the documented preconditions on the device first
- *      GINEX_TRACE=1          ginex_changeset_resume reports on stderr which way it went
+ *      GINEX_VALIDATE=1       check the documented preconditions on the device first; a fresh cache that
+ *                             holds every row then goes on from the accesses sorted for that, where other
+ *                             calls need no sort
+ *      GINEX_TRACE=1          the changeset calls report on stderr which way they went
  *      GINEX_SAMPLER_LDS=0    all hops through hash tables in HBM, none through tables in LDS
  *      GINEX_SAMPLER_TILES=n  at most n tiles of a batch per workgroup column of the sampler
  *      GINEX_LIVE_SELECT=1    no shortcut that relies on the cache holding the whole superbatch
  *      GINEX_STATIC_THRESHOLDS=0/1  changesets from a loop over the cache state, iteration by
- *                             iteration / from the trace alone, where the sizes would choose the other
+ *                             iteration / from the trace alone, where the sizes would choose the other; with
+ *                             either, no call in one workgroup
  *      GINEX_DEAD_SCATTER=0/1 in that loop, evictions among dead rows from a pass over the lines / from
  *                             the id bitmap
  *      GINEX_PLANNED=0/2      a carried cache that holds the whole superbatch: as any other cache /

@@ -2704,6 +2704,19 @@ constexpr int64_t LOOP_LRU_IDS = 1 << 16;
 // Both replacement policies share every kernel: a policy only decides the key an access
 // leaves behind (Belady: its next accessed iteration; LRU: S-1-i, so that the least
 // recently used rows hold the largest keys) and the key of the prefetched rows.
+//
+// The ways to the lists, in the order in which they are looked at (GINEX_TRACE=1 says which one a call took; what a
+// rule costs on its either side stands at the rule):
+//   1  nothing is accessed
+//   2  fresh, every row fits, or is likely to: fits.hpp, no sort.  Not with GINEX_VALIDATE=1, which goes on with the
+//      accesses it has sorted; may turn out not to serve the call, which goes on to the next then
+//   3  fresh Belady, few rows that do not fit: one workgroup, small.hpp.  Not with GINEX_STATIC_THRESHOLDS
+//   4  fresh, every row fits, or there is no cache: from the sorted accesses
+//   5  carried, every row fits: the planned path (replay or steps); gives way to 6 or 7 where its arrays do not hold
+//      the call.  Not with GINEX_PLANNED=0 or GINEX_LIVE_SELECT=1
+//   6  from the trace, stays.hpp (of many accesses through the windows of deal.hpp): up to 2 048 iterations, LRU with
+//      lines for the longest of them, but not the smallest calls (GINEX_STATIC_THRESHOLDS=1: these, too)
+//   7  the loop over the state (GINEX_STATIC_THRESHOLDS=0: in the place of 6)
 int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_t* ids,
                       const int64_t* ids_offsets, int32_t S, int64_t cap, int32_t* init_ids,
                       int64_t* init_count, int32_t* in_ids, int32_t* out_ids,
@@ -2759,11 +2772,18 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
       GINEX_HIP(zero_async(z, st));
     }
   }
+  // GINEX_TRACE=1: a line on stderr that says which way the call goes
+  const char* trace_env = getenv("GINEX_TRACE");
+  const bool trace = trace_env && trace_env[0] == '1';
+  auto say = [&](const char* way) {
+    if (trace) fprintf(stderr, "[ginex] %s: %s\n", who, way);
+  };
   *init_count = start_ids ? cap : 0;
   *total_changes = 0;
   if (init_ready)
     for (int32_t i = 0; i < S; ++i) init_ready[i] = start_ids ? cap : 0;
   if (total == 0) {
+    say("nothing is accessed");
     if (start_ids && final_ids)
       GINEX_HIP(hipMemcpyAsync(final_ids, start_ids, sizeof(int32_t) * cap,
                                hipMemcpyDeviceToDevice, st));
@@ -2785,6 +2805,7 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
                               &rows, st))
       return rc;
     if (rows >= 0 && rows <= cap) {
+      say("every row fits, no sort");
       *init_count = rows;
       return GINEX_OK;
     }
@@ -2831,6 +2852,7 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
   const char* static_env = getenv("GINEX_STATIC_THRESHOLDS");
   if (!start_ids && !lru && !static_env && cap > 0 && cap < distinct && distinct <= SMALL_ROWS && S <= SMALL_S &&
       total <= SMALL_IDS) {
+    say("one workgroup");
     const Small small{reinterpret_cast<uint32_t*>(w.next_iter), reinterpret_cast<int32_t*>(w.heads_a),
                       reinterpret_cast<uint32_t*>(w.heads_b), w.d_offsets, (int32_t)distinct, (int32_t)cap, S,
                       init_ids, in_ids, out_ids, in_positions, cs_capacity, cs_offsets, miss_count, src_line,
@@ -2877,6 +2899,7 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
   if (!start_ids && (distinct <= cap || cap == 0)) {
     // everything fits (no row ever misses), or there is no cache (every row misses and
     // nothing is inserted): all changesets are empty
+    say(cap == 0 ? "no cache" : "every row fits, from the sorted accesses");
     if (n_init > 0) {
       hipLaunchKernelGGL(k_copy_init, dim3((unsigned)ceil_div(n_init, TB)), dim3(TB), 0, st, heads,
                          n_init, init_ids);
@@ -3042,9 +3065,6 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
                          ((plan_env && plan_env[0] == '2') || sc[PLAN_MAX_N] > PLAN_SORT_MAX ||
                           sc[PLAN_CANDS] > PLAN_CAND_MAX);
     const bool fits = M == 0 || lo_id >= 0;
-    // GINEX_TRACE=1: one line on stderr that says which way the call went
-    const char* trace_env = getenv("GINEX_TRACE");
-    const bool trace = trace_env && trace_env[0] == '1';
     const char* const otherwise = loop ? "loop" : "from the trace, as any other cache";
     if (trace)
       fprintf(stderr, "[ginex] %s: %lld insertions, at most %lld per iteration, %lld rows dead from "
@@ -3195,6 +3215,7 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
                          heads, distinct, held_bits, state);
       GINEX_LAUNCH_CHECK();
     }
+    say("from the trace");
     uint64_t* const ends = sorted == w.pairs_a ? w.pairs_b : w.pairs_a;
     uint64_t* const rows = heads == w.heads_a ? w.heads_b : w.heads_a;
     return stays_run(who, w, sorted, ends, rows, distinct, start_ids ? nullptr : reinterpret_cast<uint64_t*>(w.d_counts),
@@ -3204,6 +3225,7 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
   }
 
   // part 3: the recurrence, with no host round trip between iterations
+  say("loop");
   const size_t touch_lds = sizeof(uint32_t) * 2 * (S + 1);
   Outputs outs{in_ids, out_ids, in_positions, cs_capacity, cs_offsets, miss_count};
   {
