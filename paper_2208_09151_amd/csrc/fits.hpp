@@ -12,6 +12,11 @@
 //   k_fit_lines  a block per bucket: line of every row into LDS, C_0; then of every access, in the tiles' order
 //   k_fit_place  a block per tile: the lines back in the order of the accesses
 // A carried cache that holds every row takes its lines the same way, with k_fit_lookup in the place of the two.
+// Ids in order (a bucket's share lies in one tile of every iteration then, some hundred ids long) and ids that crowd in few
+// buckets make long shares; they go to whole waves, with several reads in flight, and lanes that meet in a
+// bucket count together in k_fit_deal.  In order: 24 M accesses, 339 268 nodes, 143 iterations 2 714 -> 699 us a call
+// (701 through the sorted accesses), 40 M on 5.1 M nodes 4 164 -> 1 540 (1 707), 72 560 on 49 M nodes in 2
+// iterations 1 772 -> 365; in no order, 10 M on 11 M nodes, 303 and 303.
 // 33 M accesses, 9 M rows of 111 M nodes, 200 iterations: k_fit_deal 79 us (4 bytes read and 6 written per access,
 // 4.2 TB/s), k_fit_rows 253 and k_fit_lines 191 (7.4 M shares of four or five ids, the latency of their reads),
 // k_fit_place 53; 729 a call.  Through the sorted accesses 2 004: four radix passes 0.72 ms, heads 0.23, the rows' lines
@@ -39,6 +44,8 @@ constexpr int FIT_LINE_THREADS = 1024;
 constexpr int FIT_ROWS = 7168;                         // rows of a bucket in LDS at a time (above: 5 300)
 constexpr int FIT_SHARES = 2048;                       // tiles whose shares are laid out at a time
 constexpr int FIT_SHARE_LANES = 8, FIT_SHARE_ITEMS = 4;
+constexpr int FIT_TOGETHER = 8;                        // lanes of a wave, see k_fit_deal
+constexpr int FIT_LONG_SHARE = 128;                    // what a share has beyond this goes to a whole wave
 
 constexpr uint32_t FIT_DONE = 0x80000000u;             // a line in the place of an id (both are below 2^31)
 
@@ -80,13 +87,30 @@ __global__ __launch_bounds__(FIT_THREADS) void k_fit_deal(Fit f, const int32_t* 
     const int32_t x = k * FIT_THREADS + threadIdx.x;
     v[k] = x < n ? (uint32_t)ids[pos + x] : 0u;
   }
+  // Lanes of one bucket count together where a wave has many of them (ids in order, or few buckets): their additions
+  // to its counter would follow one another.
+  const int lane = lane_id();
+  bool together = false;
 #pragma unroll
   for (int k = 0; k < FIT_ITEMS; ++k) {
-    if (k * FIT_THREADS + (int32_t)threadIdx.x >= n) continue;
+    const bool valid = k * FIT_THREADS + (int32_t)threadIdx.x < n;
     uint32_t q = v[k] >> f.shift;
-    if (v[k] >= (uint64_t)f.num_nodes) *f.bad = 1;
+    if (valid && v[k] >= (uint64_t)f.num_nodes) *f.bad = 1;
     if (q >= (uint32_t)f.buckets) q = f.buckets - 1;   // (stays inside the arrays)
-    at[k] = q << 16 | atomicAdd(&s_count[q], 1u);
+    uint64_t left = __ballot(valid);
+    if (k == 0) together = __popcll(__ballot(q == __shfl(q, 0)) & left) >= FIT_TOGETHER;
+    while (together && left) {
+      const int first = __ffsll((unsigned long long)left) - 1;
+      const uint32_t q0 = __shfl(q, first);
+      const uint64_t same = __ballot(q == q0) & left;
+      if (__popcll(same) < FIT_TOGETHER) break;
+      uint32_t base = 0;
+      if (lane == first) base = atomicAdd(&s_count[q0], (uint32_t)__popcll(same));
+      base = __shfl(base, first);
+      if (same >> lane & 1) at[k] = q0 << 16 | (base + (uint32_t)__popcll(same & ((1ull << lane) - 1)));
+      left &= ~same;
+    }
+    if (left >> lane & 1) at[k] = q << 16 | atomicAdd(&s_count[q], 1u);
   }
   __syncthreads();
   // (buckets are at most eight to a thread)
@@ -142,9 +166,23 @@ __device__ __forceinline__ uint32_t fit_rank(const FitLds& l, uint32_t v) {
 // (five ids on the mean where there are most buckets) to a group of lanes.
 template <typename Fn>
 __device__ __forceinline__ void fit_shares(const Fit& f, int32_t q, const FitLds& l, const Fn& fn) {
-  constexpr int GROUPS = FIT_LINE_THREADS / FIT_SHARE_LANES;
+  constexpr int GROUPS = FIT_LINE_THREADS / FIT_SHARE_LANES, WAVES = FIT_LINE_THREADS / WAVE;
+  constexpr int PER_WAVE = WAVE / FIT_SHARE_LANES;
   static_assert(FIT_SHARES == 2 * FIT_LINE_THREADS, "two tiles to a thread");
-  const int32_t sub = threadIdx.x % FIT_SHARE_LANES;
+  const int32_t lane = lane_id(), wave = threadIdx.x / WAVE, sub = lane % FIT_SHARE_LANES, group = lane / FIT_SHARE_LANES;
+  // few tiles: neighbouring ones to different waves, and those at the same place of the iterations, too
+  const bool few = f.tiles <= GROUPS;
+  const int32_t first = few ? group * WAVES + ((wave - 3 * group) & (WAVES - 1)) : group;
+  // entries e, e + step, ... of the share at p, below `end`
+  auto several = [&](uint32_t p, int32_t e, int32_t end, int32_t step, int32_t i) {
+    uint32_t id[FIT_SHARE_ITEMS];
+#pragma unroll
+    for (int k = 0; k < FIT_SHARE_ITEMS; ++k)
+      if (e + k * step < end) id[k] = f.ids[p + e + k * step];
+#pragma unroll
+    for (int k = 0; k < FIT_SHARE_ITEMS; ++k)
+      if (e + k * step < end) fn(p + e + k * step, id[k], i);
+  };
   uint32_t at[2], share[2];
   auto request = [&](int32_t t0) {
 #pragma unroll
@@ -170,19 +208,39 @@ __device__ __forceinline__ void fit_shares(const Fit& f, int32_t q, const FitLds
     }
     __syncthreads();
     request(t0 + FIT_SHARES);
-    for (int32_t g = threadIdx.x / FIT_SHARE_LANES; g < n; g += GROUPS * FIT_SHARE_ITEMS) {
-      uint32_t id[FIT_SHARE_ITEMS], p[FIT_SHARE_ITEMS], sh[FIT_SHARE_ITEMS];
+    // (whole waves; behind the last tile there are empty shares)
+    for (int32_t g0 = few ? 0 : wave * PER_WAVE; g0 < n; g0 += GROUPS * FIT_SHARE_ITEMS) {
+      const int32_t g = g0 + first;
+      uint32_t id[FIT_SHARE_ITEMS], id2[FIT_SHARE_ITEMS], p[FIT_SHARE_ITEMS], sh[FIT_SHARE_ITEMS];
+      bool longer = false;
 #pragma unroll
       for (int k = 0; k < FIT_SHARE_ITEMS; ++k) {    // (FIT_SHARES is a multiple of the groups' stride)
         p[k] = l.at[g + k * GROUPS] + sub;
         sh[k] = l.share[g + k * GROUPS];
-        if (sub < (int32_t)(sh[k] & 0xFFFFu)) id[k] = f.ids[p[k]];
+        const int32_t entries = sh[k] & 0xFFFFu;
+        if (sub < entries) id[k] = f.ids[p[k]];
+        if (sub + FIT_SHARE_LANES < entries) id2[k] = f.ids[p[k] + FIT_SHARE_LANES];
+        longer |= entries > 2 * FIT_SHARE_LANES;
       }
 #pragma unroll
       for (int k = 0; k < FIT_SHARE_ITEMS; ++k) {
         const int32_t entries = sh[k] & 0xFFFFu, i = sh[k] >> 16;
         if (sub < entries) fn(p[k], id[k], i);
-        for (int32_t e = FIT_SHARE_LANES; e + sub < entries; e += FIT_SHARE_LANES) fn(p[k] + e, f.ids[p[k] + e], i);
+        if (sub + FIT_SHARE_LANES < entries) fn(p[k] + FIT_SHARE_LANES, id2[k], i);
+      }
+      if (!__any(longer)) continue;
+#pragma unroll 1
+      for (int k = 0; k < FIT_SHARE_ITEMS; ++k) {
+        const uint32_t at = l.at[g + k * GROUPS], share = l.share[g + k * GROUPS];
+        const int32_t entries = share & 0xFFFFu, near = entries < FIT_LONG_SHARE ? entries : FIT_LONG_SHARE;
+        for (int32_t e = 2 * FIT_SHARE_LANES + sub; e < near; e += FIT_SHARE_LANES * FIT_SHARE_ITEMS)
+          several(at, e, near, FIT_SHARE_LANES, share >> 16);
+        for (uint64_t left = __ballot(sub == 0 && entries > FIT_LONG_SHARE); left; left &= left - 1) {
+          const int from = __ffsll((unsigned long long)left) - 1;
+          const uint32_t at2 = __shfl(at, from), share2 = __shfl(share, from);
+          const int32_t end = share2 & 0xFFFFu;
+          for (int32_t e = FIT_LONG_SHARE + lane; e < end; e += WAVE * FIT_SHARE_ITEMS) several(at2, e, end, WAVE, share2 >> 16);
+        }
       }
     }
   }

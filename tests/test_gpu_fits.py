@@ -60,6 +60,24 @@ def test_numbers_of_buckets(ginex, n, monkeypatch):  # noqa: F811
     same(ginex, n, ids, off, ids.numel(), monkeypatch)
 
 
+# a bucket's ids in a tile: 8 lanes take 8 at once, then 8 more, four times 8 up to 128, a wave the rest; ids in order (a
+# bucket's lie side by side, lanes count together) and not; 128 tiles and more
+@pytest.mark.parametrize("S", [11, 128, 129])
+@pytest.mark.parametrize("order", ["mixed", "sorted"])
+def test_shares_of_any_length(ginex, S, order, monkeypatch):  # noqa: F811
+    n, bucket = 1 << 26, 1 << 15
+    gen = torch.Generator(device="cuda").manual_seed(S)
+    parts = []
+    for i in range(S):
+        k = (0, 8, 9, 16, 17, 127, 128, 129, 384, 385, 1500, 5000)[i * 7 % 12]
+        near = 5 * bucket + torch.randperm(bucket, generator=gen, device="cuda")[:k]
+        far = 6 * bucket + (torch.arange(3000 if k < 5000 else 3192, device="cuda") * 20011 + i * 7919) % (n - 6 * bucket)
+        ids = torch.cat([near, far]).int()
+        parts.append(ids.sort()[0] if order == "sorted" else ids[torch.randperm(len(ids), generator=gen, device="cuda")])
+    off = np.concatenate([[0], np.cumsum([len(x) for x in parts])]).astype(np.int64)
+    same(ginex, n, torch.cat(parts), off, int(off[-1]), monkeypatch)
+
+
 # 7 168 rows of a bucket in LDS: all rows among the first ids, up to ten slices in a bucket and thousands of
 # its ids in a tile
 @pytest.mark.parametrize("low", [7168, 7169, 65_536, 65_537, 200_000])
