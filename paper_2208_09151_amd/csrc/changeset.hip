@@ -1373,7 +1373,7 @@ constexpr int PLAN_RANK_DIRECT = 256;    // up to here every eviction is compare
 // of this GPU may use up to 160 KB)
 constexpr int PLAN_S_MAX = 2048;         // iterations (LDS histograms of k_plan_heads)
 enum { PLAN_M = 0, PLAN_MAX_N = 1, PLAN_LO_ID = 2, PLAN_DEAD = 3, PLAN_TAIL = 4, PLAN_FAILED = 5,
-       PLAN_WHERE = 6, PLAN_CANDS = 7, PLAN_SCALARS = 8 };
+       PLAN_WHERE = 6, PLAN_CANDS = 7, PLAN_FULLEST = 8, PLAN_SCALARS = 9 };
 
 struct Plan {
   uint32_t* ins_bits;    // [ceil(total / 32)] bit p: access p (flat position) is an insertion
@@ -2624,9 +2624,10 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
 }
 
 // The tiles and buckets of a call (see fits.hpp): ids and places in ids_buffer, 6 bytes per access, the starts in
-// start_buffer (*start_bytes of its start_room).  buckets = 0 where this way does not serve the shape.
-Fit fit_shape(const Workspace& w, int64_t num_nodes, int64_t total, int32_t S, int64_t max_n, uint64_t* ids_buffer,
-              uint64_t* start_buffer, size_t start_room, size_t* start_bytes) {
+// start_buffer (*start_bytes of its start_room).  buckets = 0 where this way does not serve the shape, or where even
+// buckets that are equally full are too full.  lookup: for k_fit_lookup.
+Fit fit_shape(const Workspace& w, int64_t num_nodes, int64_t total, int32_t S, int64_t max_n, bool lookup,
+              uint64_t* ids_buffer, uint64_t* start_buffer, size_t start_room, size_t* start_bytes) {
   Fit f{};
   f.shift = fit_shift(num_nodes);
   f.S = S;
@@ -2636,6 +2637,12 @@ Fit fit_shape(const Workspace& w, int64_t num_nodes, int64_t total, int32_t S, i
   if (buckets > FIT_BUCKETS || total < FIT_SHARE_MIN * tiles * buckets || fit_lines_lds(f) > FIT_LDS ||
       *start_bytes > start_room)
     return f;
+  const int64_t allowed = fit_ids_allowed(total, f.shift, lookup);
+  if (ceil_div(total, buckets) > allowed) return f;
+  f.sampled = total >= FIT_SAMPLE_MIN && allowed < total;
+  f.sample = reinterpret_cast<uint32_t*>(w.next_iter);
+  f.most = reinterpret_cast<uint32_t*>(w.d_counts + 1);
+  f.most_allowed = (uint32_t)(allowed * FIT_SAMPLES / total);
   f.off = w.d_offsets;
   f.ids = reinterpret_cast<uint32_t*>(ids_buffer);
   f.rank = reinterpret_cast<uint16_t*>(f.ids + total);
@@ -2649,6 +2656,9 @@ Fit fit_shape(const Workspace& w, int64_t num_nodes, int64_t total, int32_t S, i
   return f;
 }
 
+void fit_sample_async(const Fit& f, const int32_t* ids, int64_t total, hipStream_t st) {
+  hipLaunchKernelGGL(k_fit_sample, dim3(FIT_SAMPLE_BLOCKS), dim3(FIT_SAMPLE_THREADS), 0, st, f, ids, total);
+}
 void fit_deal_async(const Fit& f, const int32_t* ids, hipStream_t st) {
   hipLaunchKernelGGL(k_fit_deal, dim3((unsigned)f.per_iteration, (unsigned)f.S), dim3(FIT_THREADS),
                      sizeof(uint32_t) * f.buckets, st, f, ids);
@@ -2660,30 +2670,32 @@ void fit_place_async(const Fit& f, int32_t* src_line, hipStream_t st) {
 dim3 fit_grid(const Fit& f) { return dim3((unsigned)(ceil_div(f.buckets, 8) * 8)); }
 
 // A fresh cache that holds every row (see fits.hpp): *distinct rows of the superbatch, and if they fit `cap`, the
-// results; -1 where this way does not serve the shape.
+// results; -1 where this way does not serve the shape, or the ids crowd in a bucket.
 int32_t fits_run(const char* who, const Workspace& w, int64_t num_nodes, const int32_t* ids, int64_t total, int32_t S,
                  int64_t max_n, int64_t cap, int32_t* init_ids, int32_t* src_line, int64_t* init_ready,
                  int64_t* distinct, hipStream_t st) {
   *distinct = -1;
   size_t start_bytes;
   const size_t room = sizeof(uint64_t) * total;
-  Fit f = fit_shape(w, num_nodes, total, S, max_n, w.pairs_a, w.pairs_b, room, &start_bytes);
+  Fit f = fit_shape(w, num_nodes, total, S, max_n, false, w.pairs_a, w.pairs_b, room, &start_bytes);
   const int64_t counts = (int64_t)S * f.buckets + 1;
   if (f.buckets == 0 || start_bytes + sizeof(uint32_t) * (counts + scan_scratch_elems(counts)) > room) return GINEX_OK;
   f.counts = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(w.pairs_b) + start_bytes);
   f.list = reinterpret_cast<uint32_t*>(w.st.addr);
   f.bits = w.st.dead_bits;
-  fit_deal_async(f, ids, st);                     // (the word for ids out of range was cleared)
+  // (the words for ids out of range and the fullest bucket were cleared, and the sample)
+  if (f.sampled) fit_sample_async(f, ids, total, st);
+  fit_deal_async(f, ids, st);
   hipLaunchKernelGGL(k_fit_rows, fit_grid(f), dim3(FIT_LINE_THREADS), fit_rows_lds(f), st, f);
-  GINEX_HIP(exclusive_scan_inplace<uint32_t>(f.counts, counts, f.counts + counts, st));
-  hipLaunchKernelGGL(k_fit_ready, dim3((unsigned)ceil_div(S, TB)), dim3(TB), 0, st, f, w.d_ready);
+  GINEX_HIP(exclusive_scan_inplace<uint32_t>(f.counts, counts, f.counts + counts, st, FitReady{f, w.d_ready}));
   GINEX_LAUNCH_CHECK();
   std::vector<int64_t> ready(S);
   GINEX_HIP(hipMemcpyAsync(ready.data(), w.d_ready, sizeof(int64_t) * S, hipMemcpyDeviceToHost, st));
   GINEX_HIP(hipStreamSynchronize(st));
   *distinct = ready[S - 1];
+  if (*distinct == FIT_CROWDED) return GINEX_OK;
   // (the other ways would use such an id as an index)
-  if (*distinct < 0)
+  if (*distinct == FIT_BAD)
     return fail(GINEX_ERR_INPUT, "%s: ids out of range, there are %lld nodes", who, (long long)num_nodes);
   if (*distinct > cap) return GINEX_OK;
   if (init_ready) std::copy(ready.begin(), ready.end(), init_ready);
@@ -2709,7 +2721,7 @@ constexpr int64_t LOOP_LRU_IDS = 1 << 16;
 // rule costs on its either side stands at the rule):
 //   1  nothing is accessed
 //   2  fresh, every row fits, or is likely to: fits.hpp, no sort.  Not with GINEX_VALIDATE=1, which goes on with the
-//      accesses it has sorted; may turn out not to serve the call, which goes on to the next then
+//      accesses it has sorted; where the ids crowd in few buckets, or the rows do not fit, the call goes on to the next
 //   3  fresh Belady, few rows that do not fit: one workgroup, small.hpp.  Not with GINEX_STATIC_THRESHOLDS
 //   4  fresh, every row fits, or there is no cache: from the sorted accesses
 //   5  carried, every row fits: the planned path (replay or steps); gives way to 6 or 7 where its arrays do not hold
@@ -2761,7 +2773,8 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
   state.dead_only = 0;
 
   {
-    const Zeros z = Zeros().add(miss_count, S).add(cs_offsets, S + 1).add(w.d_counts, 1);
+    Zeros z = Zeros().add(miss_count, S).add(cs_offsets, S + 1).add(w.d_counts, 2);
+    if (total >= FIT_SAMPLE_MIN) z.add(w.next_iter, FIT_BUCKETS);   // (see fit_shape)
     if (S <= NearOffsets::MOST) {
       NearOffsets near;
       for (int32_t i = 0; i <= S; ++i) near.at[i] = (int32_t)ids_offsets[i];
@@ -3033,7 +3046,7 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
   if (planned) {
     const Plan& pl = w.plan;
     GINEX_HIP(zero_async(Zeros().add(pl.ins_bits, pl.ins_words).add(pl.arr_off, S + 2)
-                             .add(pl.cand_dead, PLAN_CAND_WORDS), st));
+                             .add(pl.cand_dead, PLAN_CAND_WORDS).add(pl.scalars + PLAN_FULLEST, 1), st));
     {
       int64_t blocks = w.look_tiles < 1024 ? w.look_tiles : 1024;
       hipLaunchKernelGGL(k_plan_heads, dim3((unsigned)blocks), dim3(TB),
@@ -3054,6 +3067,18 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
       hipLaunchKernelGGL(k_plan_arrival_offsets, dim3(1), dim3(BIG), 0, st, pl.arr_off,
                          pl.arr_cur, S, pl.scalars);
       GINEX_LAUNCH_CHECK();
+    }
+    // Every row has one line for the whole superbatch: the start state's or the one it is given.  Through
+    // buckets where the table is larger than the caches (random words of 55 G/s then): the accesses are
+    // sorted still in one buffer, the other and the heads have room for them
+    size_t start_bytes;
+    Fit fit{};
+    if (src_line && total >= FIT_LOOKUP_MIN && num_nodes >= FIT_LOOKUP_TABLE && total * FIT_LOOKUP_NODES >= num_nodes)
+      fit = fit_shape(w, num_nodes, total, S, max_n, true, sorted == w.pairs_a ? w.pairs_b : w.pairs_a, w.heads_a,
+                      sizeof(uint64_t) * w.max_heads, &start_bytes);
+    if (fit.buckets > 0) {
+      fit.most = reinterpret_cast<uint32_t*>(pl.scalars + PLAN_FULLEST);
+      if (fit.sampled) fit_sample_async(fit, ids, total, st);
     }
     int64_t sc[PLAN_SCALARS] = {};
     GINEX_HIP(hipMemcpyAsync(sc, pl.scalars, sizeof(sc), hipMemcpyDeviceToHost, st));
@@ -3162,17 +3187,13 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
         }
       }
       if (src_line) {
-        // every row has one line for the whole superbatch: the start state's or the one it was given.  Through
-        // buckets where the table is larger than the caches (random words of 55 G/s then): the accesses are
-        // sorted still in one buffer, the other and the heads have room for them
-        size_t start_bytes;
-        Fit f = fit_shape(w, num_nodes, total, S, max_n, sorted == w.pairs_a ? w.pairs_b : w.pairs_a,
-                          w.heads_a, sizeof(uint64_t) * w.max_heads, &start_bytes);
-        if (f.buckets > 0 && total >= FIT_LOOKUP_MIN && total * FIT_LOOKUP_NODES >= num_nodes) {
-          f.bits = accessed;
-          fit_deal_async(f, ids, st);
-          hipLaunchKernelGGL(k_fit_lookup, fit_grid(f), dim3(FIT_LINE_THREADS), fit_rows_lds(f), st, f, state.addr);
-          fit_place_async(f, src_line, st);
+        if (fit.buckets > 0 && sc[PLAN_FULLEST] <= (int64_t)fit.most_allowed) {
+          say("lines by bucket");
+          fit.bits = accessed;
+          fit_deal_async(fit, ids, st);
+          hipLaunchKernelGGL(k_fit_lookup, fit_grid(fit), dim3(FIT_LINE_THREADS), fit_rows_lds(fit), st, fit,
+                             state.addr);
+          fit_place_async(fit, src_line, st);
         } else {
           hipLaunchKernelGGL(k_lookup_lines, dim3((unsigned)ceil_div(total, TB * 4)), dim3(TB), 0, st,
                              ids, total, state.addr, src_line);

@@ -8,7 +8,7 @@
 //                and their places in the tile in that order, and the start of every bucket inside the tile
 //   k_fit_rows   a block per bucket: the bits of its ids, then the first iteration of every row (the smallest), then
 //                its rank among the bucket's rows of that iteration
-//   (scan of the numbers of new rows by iteration, then bucket: the rank of each of these lists' pieces)
+//   (scan of the numbers of new rows by iteration, then bucket: the rank of each of these lists' pieces; FitReady)
 //   k_fit_lines  a block per bucket: line of every row into LDS, C_0; then of every access, in the tiles' order
 //   k_fit_place  a block per tile: the lines back in the order of the accesses
 // A carried cache that holds every row takes its lines the same way, with k_fit_lookup in the place of the two.
@@ -30,10 +30,12 @@
 constexpr int64_t FIT_SHARE_MIN = 1;
 constexpr int64_t FIT_GUESS_MIN = 1 << 20;             // see changeset_run
 // k_fit_lookup (33 M accesses, 9 M rows of 111 M nodes: 82 + 272 + 55 us against 626 for a random word per access):
-// accesses, and nodes to an access, beyond which few entries of a line of the table are used (carried caches,
+// accesses, nodes to an access, beyond which few entries of a line of the table are used (carried caches,
 // calls in all: 10 M nodes, 1 M accesses 903 -> 889 us, 8.4 M 1 746 -> 1 672; 100 M nodes, 2 M 892 and 917, 8.4 M
-// 2 018 and 2 013, 17 M 5 427 -> 5 382; 1 M nodes, 0.5 M accesses 632 and 644, 2 M 400 -> 391).
-constexpr int64_t FIT_LOOKUP_MIN = 1 << 20, FIT_LOOKUP_NODES = 8;
+// 2 018 and 2 013, 17 M 5 427 -> 5 382), and nodes from which the table is larger than an L2 (in no order 2.1 M nodes,
+// 40 M accesses 2 509 -> 2 356, 0.8 M, 7 M 2 752 and 2 740, 0.2 M, 11 M 573 and 581; ids in order, whose entries lie side by
+// side: 5.1 M nodes, 40 M 6 018 and 6 125, 0.3 M, 24 M 837 and 1 010).
+constexpr int64_t FIT_LOOKUP_MIN = 1 << 20, FIT_LOOKUP_NODES = 8, FIT_LOOKUP_TABLE = 1 << 21;
 
 constexpr int FIT_THREADS = 512;
 constexpr int FIT_ITEMS = 16;
@@ -46,6 +48,21 @@ constexpr int FIT_SHARES = 2048;                       // tiles whose shares are
 constexpr int FIT_SHARE_LANES = 8, FIT_SHARE_ITEMS = 4;
 constexpr int FIT_TOGETHER = 8;                        // lanes of a wave, see k_fit_deal
 constexpr int FIT_LONG_SHARE = 128;                    // what a share has beyond this goes to a whole wave
+
+// How full the fullest bucket may be.  One workgroup takes it, so its ids follow one another where the others'
+// are taken side by side: ids that crowd (in order of degree, or of a part of the graph) or few buckets make one
+// workgroup the whole call (all among the 354 000 lowest of 111 M ids, 35 M accesses: 61 ms, 1.4 through the sorted
+// accesses).  The measure is ids of the bucket times passes over them, one for its bits and two for every FIT_ROWS
+// rows.  Calls in order and not, 62 720 to 40 M accesses on 2 027 to 98 M nodes: up to FIT_CHAIN + accesses / 32 never slower than
+// through the sorted accesses (0.4 to 1.0 times), from there to twice that 0.9 to 1.4 times, further up to 11 times.
+// k_fit_lookup: against a random word per access, with one pass for every FIT_ROWS rows; up to 25 000 + accesses / 128
+// 0.93 to 1.0 times, from 300 000 + accesses / 32 on 1.04 to 1.4 times.
+constexpr int64_t FIT_CHAIN = 250'000, FIT_CHAIN_SHARE = 32, FIT_LOOKUP_CHAIN = 25'000, FIT_LOOKUP_SHARE = 128;
+// A sample of the accesses says so before anything else is done, where that many accesses could crowd too much and are
+// not so few that the gain is gone (some 6 us).
+constexpr int64_t FIT_SAMPLE_MIN = 1 << 15;
+constexpr int FIT_SAMPLE_BLOCKS = 64, FIT_SAMPLE_THREADS = 512;
+constexpr int64_t FIT_SAMPLES = FIT_SAMPLE_BLOCKS * FIT_SAMPLE_THREADS;
 
 constexpr uint32_t FIT_DONE = 0x80000000u;             // a line in the place of an id (both are below 2^31)
 
@@ -61,7 +78,54 @@ struct Fit {
   int64_t num_nodes, words;
   int32_t S, per_iteration, tiles;   // tiles of an iteration, of all
   int32_t buckets, shift;
+  uint32_t* sample;        // [buckets] sampled ids, zero before
+  uint32_t* most;          // the fullest bucket's, zero before
+  uint32_t most_allowed;   // beyond: not this way
+  bool sampled;
 };
+
+// Passes over a bucket of that many ids (lines: k_fit_lookup's).
+__host__ __device__ __forceinline__ int64_t fit_chain(int64_t ids, int32_t shift, bool lookup) {
+  const int64_t rows = ids < (int64_t(1) << shift) ? ids : int64_t(1) << shift, slices = (rows + FIT_ROWS - 1) / FIT_ROWS;
+  return lookup ? ids * slices : ids * (1 + 2 * slices);
+}
+inline int64_t fit_chain_allowed(int64_t total, bool lookup) {
+  return lookup ? FIT_LOOKUP_CHAIN + total / FIT_LOOKUP_SHARE : FIT_CHAIN + total / FIT_CHAIN_SHARE;
+}
+// The most ids that a bucket may have.
+inline int64_t fit_ids_allowed(int64_t total, int32_t shift, bool lookup) {
+  int64_t lo = 0, hi = total;
+  while (lo < hi) {
+    const int64_t mid = (lo + hi + 1) / 2;
+    if (fit_chain(mid, shift, lookup) <= fit_chain_allowed(total, lookup)) lo = mid; else hi = mid - 1;
+  }
+  return lo;
+}
+
+// How many of FIT_SAMPLES accesses fall into the fullest bucket.
+__global__ __launch_bounds__(FIT_SAMPLE_THREADS) void k_fit_sample(Fit f, const int32_t* __restrict__ ids, int64_t total) {
+  __shared__ uint32_t s_count[FIT_BUCKETS];
+  __shared__ uint32_t s_most;
+  const uint32_t q = (uint32_t)ids[((int64_t)blockIdx.x * FIT_SAMPLE_THREADS + threadIdx.x) * total / FIT_SAMPLES] >> f.shift;
+  for (int b = threadIdx.x; b < f.buckets; b += FIT_SAMPLE_THREADS) s_count[b] = 0;
+  if (threadIdx.x == 0) s_most = 0;
+  __syncthreads();
+  atomicAdd(&s_count[q < (uint32_t)f.buckets ? q : f.buckets - 1], 1u);
+  __syncthreads();
+  constexpr int PER = FIT_BUCKETS / FIT_SAMPLE_THREADS;
+  uint32_t c[PER], most = 0;                         // (all additions on their way together)
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int b = k * FIT_SAMPLE_THREADS + threadIdx.x;
+    c[k] = b < f.buckets ? s_count[b] : 0u;
+    if (c[k]) c[k] += atomicAdd(&f.sample[b], c[k]);
+  }
+#pragma unroll
+  for (int k = 0; k < PER; ++k) most = c[k] > most ? c[k] : most;
+  if (most) atomicMax(&s_most, most);
+  __syncthreads();
+  if (threadIdx.x == 0) atomicMax(f.most, s_most);
+}
 
 inline int32_t fit_shift(int64_t num_nodes) {
   int32_t shift = FIT_SHIFT_MIN;
@@ -77,6 +141,7 @@ __global__ __launch_bounds__(FIT_THREADS) void k_fit_deal(Fit f, const int32_t* 
   __shared__ uint32_t s_id[FIT_TILE];
   __shared__ uint16_t s_rank[FIT_TILE];
   __shared__ uint32_t smem[FIT_THREADS / WAVE + 1];
+  if (*f.most > f.most_allowed) return;              // (nothing writes it while this runs)
   const int64_t pos = f.off[blockIdx.y] + (int64_t)blockIdx.x * FIT_TILE, left = f.off[blockIdx.y + 1] - pos;
   const int32_t n = left < 0 ? 0 : left < FIT_TILE ? (int32_t)left : FIT_TILE;
   for (int q = threadIdx.x; q < f.buckets; q += FIT_THREADS) s_count[q] = 0;
@@ -273,6 +338,7 @@ __global__ __launch_bounds__(FIT_LINE_THREADS) __attribute__((amdgpu_waves_per_e
   __shared__ uint32_t smem[FIT_LINE_THREADS / WAVE + 1];
   const int32_t q = fit_bucket();
   if (q >= f.buckets) return;
+  if (*f.most > f.most_allowed) return;
   const FitLds l = fit_lds(lds, f);
   const int32_t words = 1 << (f.shift - 5);
   const uint32_t mask = (1u << f.shift) - 1u;
@@ -340,11 +406,22 @@ __global__ __launch_bounds__(FIT_LINE_THREADS) __attribute__((amdgpu_waves_per_e
   }
 }
 
-// ready[i] = rows first accessed in iterations 0..i, -1: an id was out of range
-__global__ __launch_bounds__(TB) void k_fit_ready(Fit f, int64_t* __restrict__ ready) {
-  const int32_t i = blockIdx.x * TB + threadIdx.x;
-  if (i < f.S) ready[i] = *f.bad ? -1 : (int64_t)f.counts[(int64_t)(i + 1) * f.buckets];
-}
+// ready[i] = rows first accessed in iterations 0..i, FIT_BAD: an id was out of range, FIT_CROWDED: a bucket is too full
+constexpr int64_t FIT_BAD = -1, FIT_CROWDED = -2;
+struct FitReady {          // with the scan of the counts: the last of an iteration is what all up to it have
+  Fit f;
+  int64_t* ready;
+  __device__ __forceinline__ void operator()(int64_t base, const uint32_t (&v)[SCAN_ITEMS], int64_t n) const {
+    int64_t i = (base + f.buckets - 1) / f.buckets, at = i * f.buckets;
+#pragma unroll
+    for (int k = 0; k < SCAN_ITEMS; ++k) {
+      if (base + k != at || at >= n) continue;
+      if (i > 0) ready[i - 1] = *f.bad ? FIT_BAD : *f.most > f.most_allowed ? FIT_CROWDED : (int64_t)v[k];
+      ++i;
+      at += f.buckets;
+    }
+  }
+};
 
 constexpr size_t FIT_LDS = 65000;                    // at most (k_fit_lines; iterations: up to some 1 900)
 inline size_t fit_rows_lds(const Fit& f) { return 6 * ((size_t)1 << (f.shift - 5)) + sizeof(uint32_t) * (FIT_ROWS + 2 * FIT_SHARES); }

@@ -14,9 +14,16 @@ constexpr int SCAN_THREADS = 256;
 constexpr int SCAN_ITEMS = 16;
 constexpr int SCAN_TILE = SCAN_THREADS * SCAN_ITEMS;
 
-template <typename T>
+// What else is done with the results, SCAN_ITEMS of them from `base` on at a time (a launch for a few words of them
+// costs 4 us, and some 30 where it is the seventh before a wait).
+struct ScanOnly {
+  template <typename T>
+  __device__ __forceinline__ void operator()(int64_t, const T (&)[SCAN_ITEMS], int64_t) const {}
+};
+
+template <typename T, typename Done>
 __global__ __launch_bounds__(SCAN_THREADS) void k_scan_tiles(T* __restrict__ data, int64_t n,
-                                                             T* __restrict__ tile_sums) {
+                                                             T* __restrict__ tile_sums, Done done) {
   __shared__ T smem[SCAN_THREADS / WAVE + 1];
   const int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_ITEMS;
   T v[SCAN_ITEMS];
@@ -30,9 +37,12 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_tiles(T* __restrict__ dat
   T run = block_exclusive_scan<T, SCAN_THREADS>(sum, smem, total);
 #pragma unroll
   for (int i = 0; i < SCAN_ITEMS; ++i) {
+    const T next = run + v[i];
+    v[i] = run;
     if (base + i < n) data[base + i] = run;
-    run += v[i];
+    run = next;
   }
+  done(base, v, n);
   if (threadIdx.x == 0 && tile_sums) tile_sums[blockIdx.x] = total;
 }
 
@@ -41,9 +51,9 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_tiles(T* __restrict__ dat
 // the wait for the one before; by one block altogether 45 056 counters took 42 us, three launches 14).
 constexpr int64_t SCAN_SUMS = 1024;
 
-template <typename T, bool SCANNED>
+template <typename T, bool SCANNED, typename Done>
 __global__ __launch_bounds__(SCAN_THREADS) void k_scan_add(T* __restrict__ data, int64_t n,
-                                                           const T* __restrict__ tile_bases) {
+                                                           const T* __restrict__ tile_bases, Done done) {
   T add = 0;
   if (SCANNED) {
     add = tile_bases[blockIdx.x];
@@ -55,9 +65,13 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_add(T* __restrict__ data,
     add = total;
   }
   const int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_ITEMS;
+  T v[SCAN_ITEMS];
 #pragma unroll
-  for (int i = 0; i < SCAN_ITEMS; ++i)
-    if (base + i < n) data[base + i] += add;
+  for (int i = 0; i < SCAN_ITEMS; ++i) {
+    v[i] = add;
+    if (base + i < n) data[base + i] = v[i] += data[base + i];
+  }
+  done(base, v, n);
 }
 
 // Scratch elements needed by exclusive_scan_inplace for n elements.
@@ -71,26 +85,27 @@ inline int64_t scan_scratch_elems(int64_t n) {
 }
 
 // data[i] <- sum of data[0..i).  `scratch` holds scan_scratch_elems(n) elements.
-template <typename T>
-inline hipError_t exclusive_scan_inplace(T* data, int64_t n, T* scratch, hipStream_t st) {
+template <typename T, typename Done = ScanOnly>
+inline hipError_t exclusive_scan_inplace(T* data, int64_t n, T* scratch, hipStream_t st, Done done = Done{}) {
   if (n <= 0) return hipSuccess;
   const int64_t tiles = ceil_div(n, SCAN_TILE);
   if (tiles == 1) {
-    hipLaunchKernelGGL(k_scan_tiles<T>, dim3(1), dim3(SCAN_THREADS), 0, st, data, n, (T*)nullptr);
+    hipLaunchKernelGGL((k_scan_tiles<T, Done>), dim3(1), dim3(SCAN_THREADS), 0, st, data, n, (T*)nullptr, done);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(k_scan_tiles<T>, dim3((unsigned)tiles), dim3(SCAN_THREADS), 0, st, data, n,
-                     scratch);
+  hipLaunchKernelGGL((k_scan_tiles<T, ScanOnly>), dim3((unsigned)tiles), dim3(SCAN_THREADS), 0, st, data, n,
+                     scratch, ScanOnly{});
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (tiles <= SCAN_SUMS) {
-    hipLaunchKernelGGL((k_scan_add<T, false>), dim3((unsigned)tiles), dim3(SCAN_THREADS), 0, st, data, n, scratch);
+    hipLaunchKernelGGL((k_scan_add<T, false, Done>), dim3((unsigned)tiles), dim3(SCAN_THREADS), 0, st, data, n,
+                       scratch, done);
     return hipGetLastError();
   }
   e = exclusive_scan_inplace<T>(scratch, tiles, scratch + tiles, st);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_scan_add<T, true>), dim3((unsigned)tiles), dim3(SCAN_THREADS), 0, st, data, n,
-                     scratch);
+  hipLaunchKernelGGL((k_scan_add<T, true, Done>), dim3((unsigned)tiles), dim3(SCAN_THREADS), 0, st, data, n,
+                     scratch, done);
   return hipGetLastError();
 }
 

@@ -44,3 +44,67 @@ def test_nothing_accessed(ginex, monkeypatch, capfd):  # noqa: F811
     none = torch.zeros(0, dtype=torch.int32, device="cuda")
     got, said = way(lambda: ginex.changeset(10, none, np.zeros(4, dtype=np.int64), 5), monkeypatch, capfd)
     assert "nothing is accessed" in said and got.miss_count.sum() == 0
+
+
+def crowd(n, S, spread, near, order="mixed"):
+    """S iterations: `spread` ids from all of n, and near[i % len(near)] of the ids from n // 3 on."""
+    gen = torch.Generator(device="cuda").manual_seed(S)
+    first, parts = n // 3, []
+    for i in range(S):
+        far = (torch.arange(spread, device="cuda") * (n // spread) + 7919 * i) % n
+        far = far[(far < first) | (far >= first + 65_536)]
+        k = near[i % len(near)]
+        ids = torch.cat([far, first + torch.randperm(65_536, generator=gen, device="cuda")[:k] if k else far[:0]]).int()
+        parts.append(ids.sort()[0] if order == "sorted" else ids[torch.randperm(len(ids), generator=gen, device="cuda")])
+    return torch.cat(parts), np.concatenate([[0], np.cumsum([len(x) for x in parts])]).astype(np.int64)
+
+
+NO_SORT, SORTED = "every row fits, no sort", "every row fits, from the sorted accesses"
+
+
+# a workgroup takes a bucket: not where one has too many ids, found by a sample of the accesses or, for few
+# buckets, from the sizes; calls that are too small for that; up to ten slices of a bucket's rows
+@pytest.mark.parametrize("n,S,spread,near,expected", [
+    (20_000_000, 40, 20_000, (0,), NO_SORT), (20_000_000, 40, 20_000, (15_000,), SORTED),
+    (20_000_000, 40, 20_000, (0, 0, 0, 9000, 0, 0, 0, 0), NO_SORT),        # two slices
+    (100_000_000, 20, 60_000, (60_000,), SORTED), (100_000_000, 3, 60_000, (60_000, 0, 0), SORTED),
+    (100_000_000, 2, 6000, (10_000, 0), NO_SORT),                          # 22 000 accesses are not sampled
+    (100_000_000, 130, 280_000, (65_536,) + (0,) * 129, NO_SORT),          # ten slices of a whole bucket
+    (100_000_000, 65, 560_000, (65_536,), SORTED),
+    (3000, 300, 1000, (0,), SORTED), (3000, 30, 1000, (0,), NO_SORT)])
+@pytest.mark.parametrize("order", ["mixed", "sorted"])
+def test_ids_that_crowd(ginex, n, S, spread, near, expected, order, monkeypatch, capfd):  # noqa: F811
+    ids, off = crowd(n, S, spread, near, order)
+    cap = min(n, int(off[-1]))
+    got, said = way(lambda: ginex.changeset(n, ids, off, cap), monkeypatch, capfd)
+    assert said.strip().endswith(": " + expected), said
+    monkeypatch.setenv("GINEX_VALIDATE", "1")
+    want, said = way(lambda: ginex.changeset(n, ids, off, cap), monkeypatch, capfd)
+    assert said.strip().endswith(": " + SORTED), said
+    for name in ("init_ids", "src_line"):
+        assert torch.equal(getattr(want, name), getattr(got, name)), name
+    assert np.array_equal(want.init_ready, got.init_ready) and got.miss_count.sum() == 0
+
+
+# the lines of a carried cache, the same way (from 2^21 nodes and 2^20 accesses on)
+@pytest.mark.parametrize("n,S,spread,near,by_bucket", [
+    (20_000_000, 60, 60_000, (0,), True), (20_000_000, 60, 60_000, (9000,) * 2 + (0,) * 58, True),
+    (20_000_000, 60, 60_000, (15_000,), False), (2_097_151, 60, 60_000, (0,), False), (2_097_152, 60, 60_000, (0,), True)])
+def test_lines_of_ids_that_crowd(ginex, n, S, spread, near, by_bucket, monkeypatch, capfd):  # noqa: F811
+    ids, off = crowd(n, S, spread, near)
+    rows = torch.unique(ids)
+    rest = torch.arange(0, n, 11, device="cuda", dtype=torch.int32)
+    start = torch.unique(torch.cat([rows[::2], rest]))
+    start = torch.cat([start, rows[1::2]]).unique() if len(start) < len(rows) else start
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    start = start[torch.randperm(len(start), generator=gen, device="cuda")]
+    want = None
+    for planned in ("1", "0"):
+        monkeypatch.setenv("GINEX_PLANNED", planned)
+        got, said = way(lambda: ginex.changeset_resume(n, ids, off, start), monkeypatch, capfd)
+        if planned == "1":
+            assert "planned path" in said or "stepped path" in said, said
+            assert ("lines by bucket" in said) == by_bucket, said
+        want = want or got
+        for name in ("in_ids", "out_ids", "in_positions", "src_line", "final_ids"):
+            assert torch.equal(getattr(want, name), getattr(got, name)), name
