@@ -81,15 +81,6 @@ __host__ __device__ __forceinline__ int32_t bucket_count(int64_t n, int k, int64
   return (int32_t)(p < 1 ? 1 : p > MAX_BUCKETS ? MAX_BUCKETS : p);
 }
 
-// A full mix (the finaliser of MurmurHash3): the high bits choose the bucket, the low bits the slot.
-__device__ __forceinline__ uint32_t bucket_hash(uint32_t h) {
-  h ^= h >> 16;
-  h *= 0x85EBCA6Bu;
-  h ^= h >> 13;
-  h *= 0xC2B2AE35u;
-  return h ^ (h >> 16);
-}
-
 // The picks of one node by one thread: a[i] = row position of draw i, i < min(deg, k) (deg <= k: the
 // whole row); all other entries compare larger.  Floyd's subset rule in draw order: a position that an
 // earlier draw took is replaced by the rule's own j.  The array stays in registers (every index is
@@ -221,7 +212,7 @@ __global__ __launch_bounds__(TB) void k_pick_tiles(Tables T, Buckets B, const Of
         const int x = i * TB + threadIdx.x;
         u[i] = x < n_slots ? s_id[x] : NO_ID;
         if (u[i] != NO_ID) {
-          const uint32_t q = __umulhi(bucket_hash(u[i]), (uint32_t)P);
+          const uint32_t q = __umulhi(hash_mix(u[i]), (uint32_t)P);
           at[i] = (q << 16) | atomicAdd(&s_count[q], 1u);
         }
       }
@@ -247,7 +238,7 @@ __global__ __launch_bounds__(TB) void k_pick_tiles(Tables T, Buckets B, const Of
 #pragma unroll
       for (int i = 0; i < ITEMS; ++i)
         if (u[i] != NO_ID) {
-          const uint32_t q = __umulhi(bucket_hash(u[i]), (uint32_t)P);
+          const uint32_t q = __umulhi(hash_mix(u[i]), (uint32_t)P);
           at[i] = (q << 16) | atomicAdd(&s_count[q], 1u);
         }
       __syncthreads();
@@ -371,7 +362,7 @@ __global__ __launch_bounds__(BUCKET_THREADS) __attribute__((amdgpu_waves_per_eu(
       };
       auto place = [&](uint32_t u, uint32_t value) {
         const unsigned long long word = ((unsigned long long)u << 32) | value;
-        uint32_t h = bucket_hash(u) & (BUCKET_SLOTS - 1);
+        uint32_t h = hash_mix(u) & (BUCKET_SLOTS - 1);
         for (int probe = 0; probe < BUCKET_PROBES; ++probe) {
           // a plain look first: the ids of hubs come by the hundred, and equal addresses of a wave's
           // reads cost nothing while its atomics on them are carried out one after the other
@@ -390,7 +381,7 @@ __global__ __launch_bounds__(BUCKET_THREADS) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
         for (int i = 0; i < BUCKET_ITEMS; ++i) {
           if (!mine(e.u[i]) || e.at[i] < 0) continue;
-          uint32_t h = bucket_hash(e.u[i]) & (BUCKET_SLOTS - 1);
+          uint32_t h = hash_mix(e.u[i]) & (BUCKET_SLOTS - 1);
           unsigned long long word = tab[h];
           for (int probe = 1; probe < BUCKET_PROBES && (uint32_t)(word >> 32) != e.u[i]; ++probe) {
             h = (h + 1) & (BUCKET_SLOTS - 1);

@@ -24,6 +24,7 @@
 //   Both ways also serve a superbatch that resumes from the cache state of the previous one
 //   (C_0 given instead of computed, Belady only); LRU has other keys.
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <mutex>
@@ -2670,10 +2671,11 @@ void fit_place_async(const Fit& f, int32_t* src_line, hipStream_t st) {
 dim3 fit_grid(const Fit& f) { return dim3((unsigned)(ceil_div(f.buckets, 8) * 8)); }
 
 // A fresh cache that holds every row (see fits.hpp): *distinct rows of the superbatch, and if they fit `cap`, the
-// results; -1 where this way does not serve the shape, or the ids crowd in a bucket.
+// results; -1 where this way does not serve the shape, the ids crowd in a bucket or (not certain) too many rows are
+// estimated.
 int32_t fits_run(const char* who, const Workspace& w, int64_t num_nodes, const int32_t* ids, int64_t total, int32_t S,
-                 int64_t max_n, int64_t cap, int32_t* init_ids, int32_t* src_line, int64_t* init_ready,
-                 int64_t* distinct, hipStream_t st) {
+                 int64_t max_n, int64_t cap, bool certain, int32_t* init_ids, int32_t* src_line,
+                 int64_t* init_ready, int64_t* distinct, hipStream_t st) {
   *distinct = -1;
   size_t start_bytes;
   const size_t room = sizeof(uint64_t) * total;
@@ -2683,7 +2685,15 @@ int32_t fits_run(const char* who, const Workspace& w, int64_t num_nodes, const i
   f.counts = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(w.pairs_b) + start_bytes);
   f.list = reinterpret_cast<uint32_t*>(w.st.addr);
   f.bits = w.st.dead_bits;
-  // (the words for ids out of range and the fullest bucket were cleared, and the sample)
+  f.marked = f.most + 1;
+  f.marked_allowed = 0xFFFFFFFFu;
+  if (!certain) {
+    while (f.mark_shift < 32 - FIT_MARK_LOG && total >> f.mark_shift >= FIT_MARKS) ++f.mark_shift;
+    f.marks = f.sample + FIT_BUCKETS;
+    const double ids_marked = (double)(cap + cap / 128) / (double)(1 << f.mark_shift);
+    f.marked_allowed = (uint32_t)(-FIT_MARK_BITS * std::expm1(-ids_marked / FIT_MARK_BITS));
+  }
+  // (the words for ids out of range, the fullest bucket and the marks were cleared, and the sample)
   if (f.sampled) fit_sample_async(f, ids, total, st);
   fit_deal_async(f, ids, st);
   hipLaunchKernelGGL(k_fit_rows, fit_grid(f), dim3(FIT_LINE_THREADS), fit_rows_lds(f), st, f);
@@ -2693,7 +2703,7 @@ int32_t fits_run(const char* who, const Workspace& w, int64_t num_nodes, const i
   GINEX_HIP(hipMemcpyAsync(ready.data(), w.d_ready, sizeof(int64_t) * S, hipMemcpyDeviceToHost, st));
   GINEX_HIP(hipStreamSynchronize(st));
   *distinct = ready[S - 1];
-  if (*distinct == FIT_CROWDED) return GINEX_OK;
+  if (*distinct == FIT_NOT) return GINEX_OK;
   // (the other ways would use such an id as an index)
   if (*distinct == FIT_BAD)
     return fail(GINEX_ERR_INPUT, "%s: ids out of range, there are %lld nodes", who, (long long)num_nodes);
@@ -2806,22 +2816,22 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
 
   const char* validate_env = getenv("GINEX_VALIDATE");
   const bool validate = validate_env && validate_env[0] == '1';
-  // Where every row fits, or is likely to, a way that needs no sort.  Whether they do is known after its first half
-  // (33 M accesses: 0.35 of 0.6 ms), which is lost if they do not: not tried for less than three lines to four
+  // Where every row fits, or is likely to, a way that needs no sort.  It ends when the ids were dealt where too many rows
+  // are estimated (see FIT_MARKS): not tried for less than three lines to four
   // accesses, where the rows would have to be accessed less than 4/3 times on the mean not to fit, nor for few
-  // accesses unless it is certain (just too small a cache: 131 072 accesses 380 -> 443 us, 4 M 843 -> 955, 33 M
-  // 5 389 -> 6 090; large enough: 223 -> 137, 507 -> 267, 3 180 -> 1 434).
+  // accesses unless it is certain.
   int64_t rows = -1;
   const bool certain = cap >= std::min(total, num_nodes);
   if (!start_ids && cap > 0 && !validate && (certain || (4 * cap >= 3 * total && total >= FIT_GUESS_MIN))) {
-    if (int32_t rc = fits_run(who, w, num_nodes, ids, total, S, max_n, cap, init_ids, src_line, init_ready,
-                              &rows, st))
+    if (int32_t rc = fits_run(who, w, num_nodes, ids, total, S, max_n, cap, certain, init_ids, src_line,
+                              init_ready, &rows, st))
       return rc;
     if (rows >= 0 && rows <= cap) {
       say("every row fits, no sort");
       *init_count = rows;
       return GINEX_OK;
     }
+    if (rows >= 0) say("too many rows, to the sort");
   }
 
   // part 1: sort (node, position) by node, then look right

@@ -108,6 +108,15 @@ inline hipError_t fill_async(T* p, int64_t n, T value, hipStream_t st) {
 
 // Several arrays cleared in one launch: calls on few ids are a chain of launches of a few microseconds
 // each (a changeset call clears up to eleven arrays).
+// A full mix (the finaliser of MurmurHash3).
+__device__ __forceinline__ uint32_t hash_mix(uint32_t h) {
+  h ^= h >> 16;
+  h *= 0x85EBCA6Bu;
+  h ^= h >> 13;
+  h *= 0xC2B2AE35u;
+  return h ^ (h >> 16);
+}
+
 struct Zeros {
   static constexpr int MOST = 12;
   uint32_t* at[MOST];

@@ -108,3 +108,23 @@ def test_lines_of_ids_that_crowd(ginex, n, S, spread, near, by_bucket, monkeypat
         want = want or got
         for name in ("in_ids", "out_ids", "in_positions", "src_line", "final_ids"):
             assert torch.equal(getattr(want, name), getattr(got, name)), name
+
+
+# three lines to four accesses and more, but not certain: the rows are estimated
+@pytest.mark.parametrize("n,S,length", [(10_000_000, 20, 60_000), (60_000_000, 40, 100_000), (50_000_000, 4, 2_000_001)])
+def test_caches_that_may_hold_every_row(ginex, n, S, length, monkeypatch, capfd):  # noqa: F811
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    ids = torch.cat([torch.randperm(n, generator=gen, device="cuda")[:length].int() for _ in range(S)])
+    off = np.arange(S + 1, dtype=np.int64) * length
+    rows = int(torch.unique(ids).numel())
+    assert rows * 96 // 100 * 4 >= 3 * len(ids)
+    for cap, fits, tried in ((rows, True, True), (rows - 1, False, True), (rows * 97 // 100, False, False)):
+        monkeypatch.delenv("GINEX_VALIDATE", raising=False)
+        got, said = way(lambda: ginex.changeset(n, ids, off, cap), monkeypatch, capfd)
+        assert ("no sort" in said) == fits and ("too many rows" in said) == (tried and not fits), said
+        monkeypatch.setenv("GINEX_VALIDATE", "1")
+        want = ginex.changeset(n, ids, off, cap)
+        assert np.array_equal(want.miss_count, got.miss_count) and np.array_equal(want.cs_offsets, got.cs_offsets)
+        assert np.array_equal(want.init_ready, got.init_ready)
+        for name in ("init_ids", "in_ids", "out_ids", "in_positions", "src_line"):
+            assert torch.equal(getattr(want, name), getattr(got, name)), name
