@@ -1189,9 +1189,11 @@ __device__ __forceinline__ uint32_t walk_leaves(const Stays& q, const IterFinder
 // while that leaves room for eight blocks per CU.
 constexpr int32_t NEVER_LDS_S = 400;
 
+// (five waves per SIMD: 96 registers; with one more, which the compiler takes or not as other code in
+// the file changes, four, and 466 us instead of 401 for 33 M accesses)
 template <bool NEVER_LDS>
-__global__ __launch_bounds__(TB) void k_stays_walk(Stays q, const uint64_t* __restrict__ sorted,
-                                                   int64_t n, const int32_t* __restrict__ addr,
+__global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(5))) void k_stays_walk(
+    Stays q, const uint64_t* __restrict__ sorted, int64_t n, const int32_t* __restrict__ addr,
                                                    const uint64_t* __restrict__ hit_words,
                                                    const uint64_t* __restrict__ ins_words,
                                                    InsIndex at_ins, uint32_t* __restrict__ leave_ins,
