@@ -1523,6 +1523,8 @@ __global__ __launch_bounds__(TB) void k_bit_tiles(const uint32_t* __restrict__ b
   if (threadIdx.x == 0 && blockIdx.x == 0) tiles[gridDim.x] = 0;
 }
 
+constexpr uint32_t INS_DENSE = TB * 4;     // insertions of a tile of TB words
+
 // in_ids / in_positions of the whole superbatch: the set bits of ins_bits in position order
 // (iterations are consecutive stretches of positions, so this is iteration by iteration and
 // inside an iteration by position, as the lists are defined).
@@ -1546,6 +1548,27 @@ __global__ __launch_bounds__(TB) void k_ins_emit(const uint32_t* __restrict__ bi
   uint32_t rank = first + block_exclusive_scan<uint32_t, TB>((uint32_t)__popc(word), smem, total);
   if (w < words && ins_pairs) ins_pairs[w] = (uint64_t)rank << 32 | word;   // (see InsIndex)
   if (w < words && !ins_pairs) ins_base[w] = rank;
+  if (total > INS_DENSE) {   // uniform
+    // many of a word's bits are set: a position to a thread, so that neighbours write side by side (a word to a
+    // thread: LRU of 24 x 800 000 accesses, nearly all inserted, 550 us)
+    __shared__ uint32_t s_word[TB], s_rank[TB];
+    s_word[threadIdx.x] = word;
+    s_rank[threadIdx.x] = rank;
+    __syncthreads();
+    const int64_t p0 = (int64_t)blockIdx.x * TB * 32;
+    int32_t i = iter_of(lds_off, S, (int32_t)(p0 + threadIdx.x));
+    for (int x = threadIdx.x; x < TB * 32; x += TB) {
+      const uint32_t bits_here = s_word[x >> 5];
+      if (!(bits_here >> (x & 31) & 1u)) continue;     // (positions behind the last one have none)
+      const int32_t p = (int32_t)(p0 + x);
+      const uint32_t at = s_rank[x >> 5] + __popc(bits_here & ((1u << (x & 31)) - 1u));
+      while (i + 1 < S && lds_off[i + 1] <= p) ++i;
+      in_ids[at] = ids[p];
+      in_positions[at] = p - lds_off[i];
+      if (ins_cand) ins_cand[at] = -1;
+    }
+    return;
+  }
   int32_t i = word ? iter_of(lds_off, S, (int32_t)(w * 32)) : 0;
   while (word) {
     const int32_t p = (int32_t)(w * 32 + (__ffs(word) - 1));
@@ -2292,6 +2315,9 @@ extern "C" size_t ginex_changeset_workspace_bytes(int64_t num_nodes, int64_t tot
 namespace ginex {
 namespace {
 
+// Selects by many blocks at a time: their counters sit in an array of the planned path.
+constexpr int64_t WIDE_AT_ONCE = PLAN_CAND_MAX / (CUT_DIGITS * CUT_BINS);
+
 // Belady's thresholds and cuts, from the histograms (see stays.hpp); *never: bucket "never" is cut.  jobs: read by a
 // copy to the device that is not waited for here, so the caller keeps it until it has waited.
 int32_t stays_cuts(const Workspace& w, const Stays& q, const int64_t* ids_offsets, int64_t* miss_count, bool* never,
@@ -2337,7 +2363,6 @@ int32_t stays_cuts(const Workspace& w, const Stays& q, const int64_t* ids_offset
   if (most_jobs > Jobs::MOST)
     GINEX_HIP(hipMemcpyAsync(d_jobs, jobs.data(), sizeof(int32_t) * jobs.size(), hipMemcpyHostToDevice, st));
   uint32_t* const digit_counts = reinterpret_cast<uint32_t*>(pl.arr_cand);
-  constexpr int64_t WIDE_AT_ONCE = PLAN_CAND_MAX / (CUT_DIGITS * CUT_BINS);
   const int32_t* at = d_jobs;
   for (const auto& level : levels) {
     int64_t blocks = 1, most_members = 1, wides = 0;
@@ -2415,7 +2440,20 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
   std::vector<int32_t> jobs;   // of the cuts
   if (lru) {
     hipLaunchKernelGGL(k_lru_counts, dim3((unsigned)S), dim3(WAVE), 0, st, S, w.key_hists);
-    hipLaunchKernelGGL(k_lru_limits, dim3((unsigned)S), dim3(BIG), 0, st, q, w.key_hists, state.cap, limits);
+    // (more iterations fill the GPU with a block each)
+    const bool wide = longest > LRU_WIDE && S <= WIDE_AT_ONCE;
+    LruJob* const lru_jobs = wide ? reinterpret_cast<LruJob*>(pl.cand_line) : nullptr;
+    hipLaunchKernelGGL(k_lru_limits, dim3((unsigned)S), dim3(BIG), 0, st, q, w.key_hists, state.cap, limits, lru_jobs);
+    if (wide) {
+      uint32_t* const digit_counts = reinterpret_cast<uint32_t*>(pl.arr_cand);
+      const dim3 grid((unsigned)std::min<int64_t>(ceil_div(longest, TB * CUT_WIDE_ITEMS), 256), (unsigned)S);
+      GINEX_HIP(fill_async<uint32_t>(digit_counts, (int64_t)S * (CUT_DIGITS * CUT_BINS), 0u, st));
+      hipLaunchKernelGGL(k_lru_wide<0>, grid, dim3(TB), 0, st, q, lru_jobs, limits, digit_counts);
+      hipLaunchKernelGGL(k_lru_wide<1>, grid, dim3(TB), 0, st, q, lru_jobs, limits, digit_counts);
+      hipLaunchKernelGGL(k_lru_wide<2>, grid, dim3(TB), 0, st, q, lru_jobs, limits, digit_counts);
+      hipLaunchKernelGGL(k_lru_wide<CUT_DIGITS>, dim3(1, (unsigned)S), dim3(TB), 0, st, q, lru_jobs, limits,
+                         digit_counts);
+    }
     GINEX_LAUNCH_CHECK();
   } else if (int32_t rc = stays_cuts(w, q, ids_offsets, miss_count, &never, jobs, st)) {
     return rc;
@@ -2495,8 +2533,8 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
     GINEX_LAUNCH_CHECK();
   }
   if (!lru) hipLaunchKernelGGL(k_never_lift, dim3(1), dim3(BIG), 0, st, w.cuts, S, pl.cand_id);
-  hipLaunchKernelGGL(k_ins_count, dim3((unsigned)S), dim3(TB), 0, st, pl.ins_bits, w.d_offsets,
-                     cs_offsets, lru ? miss_count : (int64_t*)nullptr);
+  hipLaunchKernelGGL(k_ins_count, dim3((unsigned)S, (unsigned)std::min<int64_t>(ceil_div(longest, 32 * TB * 8), 64)),
+                     dim3(TB), 0, st, pl.ins_bits, w.d_offsets, cs_offsets, lru ? miss_count : (int64_t*)nullptr);
   hipLaunchKernelGGL(k_ins_offsets, dim3(1), dim3(BIG), 0, st, cs_offsets, S, w.d_cs_offsets);
   GINEX_LAUNCH_CHECK();
   std::vector<int64_t> host(2 * S + 1);
@@ -2721,7 +2759,7 @@ int32_t fits_run(const char* who, const Workspace& w, int64_t num_nodes, const i
 constexpr int32_t LOOP_S = 6;
 constexpr int64_t LOOP_IDS = 4096, LOOP_NODES = int64_t(1) << 26;
 constexpr int32_t LOOP_LRU_S = 2;
-constexpr int64_t LOOP_LRU_IDS = 1 << 16;
+constexpr int64_t LOOP_LRU_IDS = 1 << 16, LOOP_LRU_LINES = 1 << 22;
 
 // Both replacement policies share every kernel: a policy only decides the key an access
 // leaves behind (Belady: its next accessed iteration; LRU: S-1-i, so that the least
@@ -2966,13 +3004,16 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
   // nodes: the loop clears two words for each; two iterations of 200 accesses, carried, 66 M nodes 464 against
   // 434, three on 111 M nodes 507 against 537.  GINEX_STATIC_THRESHOLDS=0/1 chooses the loop / the trace.
   // LRU (the trace's way has no cuts): 20 000 nodes, iterations of 3 000 accesses, two 311 against 332, three 355
-  // and 342, six 472 and 396; 200 000 nodes, of 20 000, two 344 and 380, three 406 and 412.
-  const bool smallest =
-      num_nodes <= LOOP_NODES &&
-      (lru ? S <= LOOP_LRU_S && total <= LOOP_LRU_IDS
-           : S <= LOOP_S && total <= (S <= LOOP_S / 2 ? 4 * LOOP_IDS : LOOP_IDS) && distinct < total);
+  // and 342, six 472 and 396; 200 000 nodes, of 20 000, two 344 and 380, three 406 and 412.  And a large cache of just
+  // the lines that an iteration accesses: the loop gives all of them up without a select (5 iterations of 8 M 4.7 and
+  // 5.8 ms, 8 of 4 M 3.26 and 3.39; of 2 M 2.0 and 1.8; with 6 % more lines 14.8 and 6.0).
+  const bool by_loop =
+      (lru && max_n == cap && cap >= LOOP_LRU_LINES) ||
+      (num_nodes <= LOOP_NODES &&
+       (lru ? S <= LOOP_LRU_S && total <= LOOP_LRU_IDS
+            : S <= LOOP_S && total <= (S <= LOOP_S / 2 ? 4 * LOOP_IDS : LOOP_IDS) && distinct < total));
   const bool stays = S <= STATIC_S_MAX && (!lru || max_n <= cap) &&
-                     (static_env ? static_env[0] != '0' : !smallest);
+                     (static_env ? static_env[0] != '0' : !by_loop);
   const bool loop = !stays;   // (the loop still is the last way out of the planned path then)
   {
     Zeros z;

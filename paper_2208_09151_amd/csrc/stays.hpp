@@ -512,44 +512,73 @@ constexpr int64_t CUT_WIDE = 3 << 14;
 constexpr int CUT_DIGITS = 3, CUT_BINS = 2048;         // 11 + 10 + 10 bits
 constexpr int CUT_WIDE_ITEMS = 8;
 
+// The digits above DIGIT of the keep-th smallest id, from their counts (keep > 0; the whole block).
+template <int DIGIT>
+__device__ __forceinline__ uint32_t wide_digits(const uint32_t* __restrict__ counts, uint32_t keep) {
+  __shared__ uint32_t smem[TB / WAVE + 1];
+  __shared__ uint32_t s_pick, s_below;
+  uint32_t prefix = 0, left = keep;
+#pragma unroll
+  for (int d = 0; d < DIGIT; ++d) {
+    constexpr int PER = CUT_BINS / TB;
+    uint32_t mine[PER], sum = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      mine[k] = counts[d * CUT_BINS + threadIdx.x * PER + k];
+      sum += mine[k];
+    }
+    if (threadIdx.x == 0) s_pick = s_below = 0;
+    uint32_t total;
+    uint32_t run = block_exclusive_scan<uint32_t, TB>(sum, smem, total);   // (barriers inside)
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      if (run < left && run + mine[k] >= left) {
+        s_pick = (uint32_t)(threadIdx.x * PER + k);
+        s_below = run;
+      }
+      run += mine[k];
+    }
+    __syncthreads();
+    prefix = (prefix << (d ? 10 : 11)) | s_pick;
+    left -= s_below;
+    __syncthreads();
+  }
+  return prefix;
+}
+
+// Counts of digit DIGIT of the ids id(x), 0 <= x < n, whose digits above it are `prefix`, by the blocks of a column;
+// ids with bit 31 set do not count.
+template <int DIGIT, typename Id>
+__device__ __forceinline__ void wide_counts(uint32_t* __restrict__ counts, int64_t n, uint32_t prefix, Id id) {
+  __shared__ uint32_t s_hist[CUT_BINS];
+  constexpr int SHIFT = DIGIT == 0 ? 20 : DIGIT == 1 ? 10 : 0, BITS = DIGIT == 0 ? 11 : 10;
+  const int64_t first = (int64_t)blockIdx.x * (TB * CUT_WIDE_ITEMS);
+  if (first >= n) return;                              // uniform
+  for (int b = threadIdx.x; b < CUT_BINS; b += TB) s_hist[b] = 0;
+  __syncthreads();
+  for (int64_t x0 = first + threadIdx.x; x0 < n; x0 += (int64_t)gridDim.x * (TB * CUT_WIDE_ITEMS)) {
+    uint32_t v[CUT_WIDE_ITEMS];
+#pragma unroll
+    for (int k = 0; k < CUT_WIDE_ITEMS; ++k) v[k] = id(x0 + k * TB < n ? x0 + k * TB : x0);
+#pragma unroll
+    for (int k = 0; k < CUT_WIDE_ITEMS; ++k)
+      if (x0 + k * TB < n && !(v[k] >> 31) && (DIGIT == 0 || v[k] >> (SHIFT + BITS) == prefix))
+        atomicAdd(&s_hist[(v[k] >> SHIFT) & ((1u << BITS) - 1u)], 1u);
+  }
+  __syncthreads();
+  for (int b = threadIdx.x; b < CUT_BINS; b += TB)
+    if (s_hist[b]) atomicAdd(&counts[DIGIT * CUT_BINS + b], s_hist[b]);
+}
+
 template <int DIGIT>   // CUT_DIGITS: all are known
 __global__ __launch_bounds__(TB) void k_cut_wide(Stays q, Jobs jobs, int first,
                                                  uint32_t* __restrict__ hists) {
-  __shared__ uint32_t s_hist[CUT_BINS];
-  __shared__ uint32_t smem[TB / WAVE + 1];
-  __shared__ uint32_t s_pick, s_below;
   Cut* cut = &q.cuts[jobs[first + blockIdx.y]];
   const Cut c = *cut;                                  // (kind and T are not used: the last launch writes them)
   const int64_t region = q.off[c.jstar], room = q.off[c.jstar + 1] - region;
   const CutChoice ch = cut_choice(c, room);
   uint32_t* const counts = hists + (int64_t)blockIdx.y * (CUT_DIGITS * CUT_BINS);
-  uint32_t prefix = 0, left = (uint32_t)ch.keep;
-  if (ch.keep > 0)                                     // uniform
-#pragma unroll
-    for (int d = 0; d < DIGIT; ++d) {
-      constexpr int PER = CUT_BINS / TB;
-      uint32_t mine[PER], sum = 0;
-#pragma unroll
-      for (int k = 0; k < PER; ++k) {
-        mine[k] = counts[d * CUT_BINS + threadIdx.x * PER + k];
-        sum += mine[k];
-      }
-      if (threadIdx.x == 0) s_pick = s_below = 0;
-      uint32_t total;
-      uint32_t run = block_exclusive_scan<uint32_t, TB>(sum, smem, total);   // (barriers inside)
-#pragma unroll
-      for (int k = 0; k < PER; ++k) {
-        if (run < left && run + mine[k] >= left) {
-          s_pick = (uint32_t)(threadIdx.x * PER + k);
-          s_below = run;
-        }
-        run += mine[k];
-      }
-      __syncthreads();
-      prefix = (prefix << (d ? 10 : 11)) | s_pick;
-      left -= s_below;
-      __syncthreads();
-    }
+  const uint32_t prefix = ch.keep > 0 ? wide_digits<DIGIT>(counts, (uint32_t)ch.keep) : 0u;   // uniform
   if constexpr (DIGIT == CUT_DIGITS) {
     const int32_t T = ch.keep > 0 ? (int32_t)prefix : -1;
     cut_mark(q, c, ch.kind, T, region, room, (int64_t)blockIdx.x * TB + threadIdx.x, (int64_t)gridDim.x * TB);
@@ -557,25 +586,8 @@ __global__ __launch_bounds__(TB) void k_cut_wide(Stays q, Jobs jobs, int first,
       cut->kind = ch.kind;
       cut->T = T;
     }
-  } else {
-    constexpr int SHIFT = DIGIT == 0 ? 20 : DIGIT == 1 ? 10 : 0, BITS = DIGIT == 0 ? 11 : 10;
-    const int64_t first = (int64_t)blockIdx.x * (TB * CUT_WIDE_ITEMS);
-    if (ch.keep == 0 || first >= ch.n) return;         // uniform
-    for (int b = threadIdx.x; b < CUT_BINS; b += TB) s_hist[b] = 0;
-    __syncthreads();
-    for (int64_t x0 = first + threadIdx.x; x0 < ch.n; x0 += (int64_t)gridDim.x * (TB * CUT_WIDE_ITEMS)) {
-      uint32_t v[CUT_WIDE_ITEMS];
-#pragma unroll
-      for (int k = 0; k < CUT_WIDE_ITEMS; ++k)
-        v[k] = cut_member(q, ch.kind, region, room, x0 + k * TB < ch.n ? x0 + k * TB : x0);
-#pragma unroll
-      for (int k = 0; k < CUT_WIDE_ITEMS; ++k)
-        if (x0 + k * TB < ch.n && (DIGIT == 0 || v[k] >> (SHIFT + BITS) == prefix))
-          atomicAdd(&s_hist[(v[k] >> SHIFT) & ((1u << BITS) - 1u)], 1u);
-    }
-    __syncthreads();
-    for (int b = threadIdx.x; b < CUT_BINS; b += TB)
-      if (s_hist[b]) atomicAdd(&counts[DIGIT * CUT_BINS + b], s_hist[b]);
+  } else if (ch.keep > 0) {
+    wide_counts<DIGIT>(counts, ch.n, prefix, [&](int64_t x) { return cut_member(q, ch.kind, region, room, x); });
   }
 }
 
@@ -625,9 +637,24 @@ __global__ __launch_bounds__(WAVE) void k_lru_counts(int32_t S, uint32_t* __rest
   }
 }
 
-// A block per iteration: the iteration whose rows are the last to stay, and which of them do.
+// Of an iteration's limit: the iteration t whose rows are the last to stay, and how many of them do.
+struct LruJob {
+  int32_t t, keep;         // keep 0: the limit is known
+};
+
+// What a row of iteration t counts as in the select for iteration i: its id, if it is accessed next after i.
+__device__ __forceinline__ uint32_t lru_member(const Stays& q, int64_t p, int32_t i) {
+  const uint32_t v = (uint32_t)q.ids[p];               // (both reads at once)
+  return stay_next(q.ends[p]) > i ? v : 0x80000000u;
+}
+
+// A block per iteration: the iteration whose rows are the last to stay, and which of them do.  jobs: null, or where
+// selects among more than LRU_WIDE accesses are left to k_lru_wide: one block takes 0.55 us per 1 000 accesses (3
+// iterations of 4 M, nine tenths of the rows held: 2.15 ms of a call of 3.55, now 1.39), those five launches some
+// 50 us (20 iterations of 76 000: 32 us by a block each, 26 and the launches this way).
+constexpr int64_t LRU_WIDE = 1 << 17;
 __global__ __launch_bounds__(BIG) void k_lru_limits(Stays q, const uint32_t* __restrict__ counts, int64_t cap,
-                                                    uint64_t* __restrict__ limits) {
+                                                    uint64_t* __restrict__ limits, LruJob* __restrict__ jobs) {
   __shared__ int64_t smem[BIG / WAVE + 1];
   __shared__ int32_t s_t;
   __shared__ int64_t s_keep;
@@ -648,15 +675,39 @@ __global__ __launch_bounds__(BIG) void k_lru_limits(Stays q, const uint32_t* __r
   }
   const int32_t t = s_t;
   if (t < 0 || s_keep == 0) {                      // uniform: nothing has to go, or all rows of t
-    if (threadIdx.x == 0) limits[i] = (uint64_t)(t + 1) << 32;
+    if (threadIdx.x == 0) {
+      limits[i] = (uint64_t)(t + 1) << 32;
+      if (jobs) jobs[i] = {t, 0};
+    }
     return;
   }
   const int64_t to = q.off[t], n = q.off[t + 1] - to;
-  const int32_t T = p_kth_smallest_id<BIG, 4>(n, s_keep, q.id_bits, [&](int64_t x) {
-    const uint32_t v = (uint32_t)q.ids[to + x];    // (both reads at once)
-    return stay_next(q.ends[to + x]) > i ? v : 0x80000000u;
-  });
-  if (threadIdx.x == 0) limits[i] = lru_key((uint32_t)t, (uint32_t)T);
+  if (jobs && n > LRU_WIDE) {                      // uniform
+    if (threadIdx.x == 0) jobs[i] = {t, (int32_t)s_keep};
+    return;
+  }
+  const int32_t T = p_kth_smallest_id<BIG, 4>(n, s_keep, q.id_bits, [&](int64_t x) { return lru_member(q, to + x, i); });
+  if (threadIdx.x == 0) {
+    limits[i] = lru_key((uint32_t)t, (uint32_t)T);
+    if (jobs) jobs[i] = {t, 0};
+  }
+}
+
+// The selects left, by many blocks (blockIdx.y = iteration), digit by digit as k_cut_wide.
+template <int DIGIT>   // CUT_DIGITS: all are known
+__global__ __launch_bounds__(TB) void k_lru_wide(Stays q, const LruJob* __restrict__ jobs,
+                                                 uint64_t* __restrict__ limits, uint32_t* __restrict__ hists) {
+  const int32_t i = blockIdx.y;
+  const LruJob job = jobs[i];
+  if (job.keep == 0) return;                       // uniform
+  uint32_t* const counts = hists + (int64_t)i * (CUT_DIGITS * CUT_BINS);
+  const uint32_t prefix = wide_digits<DIGIT>(counts, (uint32_t)job.keep);
+  if constexpr (DIGIT == CUT_DIGITS) {
+    if (threadIdx.x == 0) limits[i] = lru_key((uint32_t)job.t, prefix);
+  } else {
+    const int64_t to = q.off[job.t];
+    wide_counts<DIGIT>(counts, q.off[job.t + 1] - to, prefix, [&](int64_t x) { return lru_member(q, to + x, i); });
+  }
 }
 
 // ---- the lists and the evicting iterations ----------------------------------------------------------
@@ -1106,7 +1157,8 @@ __global__ __launch_bounds__(TB) void k_stays_links(Stays q, const uint64_t* __r
   }
 }
 
-// insertions of iteration i = set bits of its positions (blockIdx.x = i); miss_count: where all misses are inserted
+// insertions of iteration i = set bits of its positions (blockIdx.x = i, by the blocks of the column, added to
+// zeros); miss_count: where all misses are inserted
 __global__ __launch_bounds__(TB) void k_ins_count(const uint32_t* __restrict__ ins_bits,
                                                   const int64_t* __restrict__ off,
                                                   int64_t* __restrict__ cs_offsets,
@@ -1115,16 +1167,16 @@ __global__ __launch_bounds__(TB) void k_ins_count(const uint32_t* __restrict__ i
   const int64_t lo = off[blockIdx.x], hi = off[blockIdx.x + 1];
   uint32_t cnt = 0;
   if (hi > lo)
-    for (int64_t w = (lo >> 5) + threadIdx.x; w <= (hi - 1) >> 5; w += TB) {
+    for (int64_t w = (lo >> 5) + blockIdx.y * TB + threadIdx.x; w <= (hi - 1) >> 5; w += (int64_t)gridDim.y * TB) {
       uint32_t word = ins_bits[w];
       if (w == lo >> 5) word &= ~((1u << (lo & 31)) - 1u);
       if (w == (hi - 1) >> 5 && (hi & 31)) word &= (1u << (hi & 31)) - 1u;
       cnt += __popc(word);
     }
   const uint32_t total = block_sum_u32(cnt, red);
-  if (threadIdx.x == 0) {
-    cs_offsets[blockIdx.x + 1] = total;
-    if (miss_count) miss_count[blockIdx.x] = total;
+  if (threadIdx.x == 0 && total) {
+    atomicAdd((unsigned long long*)&cs_offsets[blockIdx.x + 1], (unsigned long long)total);
+    if (miss_count) atomicAdd((unsigned long long*)&miss_count[blockIdx.x], (unsigned long long)total);
   }
 }
 

@@ -62,3 +62,28 @@ def test_large_traces_equal_the_loop(ginex, n, S, length, cap, monkeypatch):  # 
     assert np.array_equal(want.cs_offsets, got.cs_offsets)
     for name in ("init_ids", "in_ids", "out_ids", "in_positions", "src_line"):
         assert torch.equal(getattr(want, name), getattr(got, name)), name
+
+
+# selects among more than 131 072 accesses by many blocks, for up to 85 iterations; the limit in the iteration itself
+# and in earlier ones, all rows of one, ids of up to 31 bits; tiles of insertions with nearly every position
+@pytest.mark.parametrize("S", [3, 85, 86])
+@pytest.mark.parametrize("n", [150_000, 2_000_000_000])
+def test_limits_in_long_iterations(ginex, S, n, monkeypatch):  # noqa: F811
+    if n > 1 << 30 and S != 3:
+        pytest.skip("one size of a table over all nodes is enough")
+    gen = torch.Generator(device="cuda").manual_seed(S)
+    lengths = [131_073 if i % 3 == 0 else 131_072 if i % 3 == 1 else 145_000 for i in range(S)]
+    off = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    pool = torch.randperm(150_000, generator=gen, device="cuda") * (n // 150_000) + (n // 150_000 - 1)
+    ids = torch.cat([pool[torch.randperm(len(pool), generator=gen, device="cuda")[:k]].int() for k in lengths])
+    distinct = int(torch.unique(ids).numel())
+    for cap in (max(lengths), max(lengths) + 1, 148_000, distinct - 1):
+        results = []
+        for way in ("0", "1"):
+            monkeypatch.setenv("GINEX_STATIC_THRESHOLDS", way)
+            results.append(ginex.changeset(n, ids, off, cap, policy="lru"))
+        want, got = results
+        assert np.array_equal(want.miss_count, got.miss_count) and want.miss_count.sum() > 0
+        assert np.array_equal(want.cs_offsets, got.cs_offsets)
+        for name in ("init_ids", "in_ids", "out_ids", "in_positions", "src_line"):
+            assert torch.equal(getattr(want, name), getattr(got, name)), name

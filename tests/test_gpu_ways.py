@@ -128,3 +128,20 @@ def test_caches_that_may_hold_every_row(ginex, n, S, length, monkeypatch, capfd)
         assert np.array_equal(want.init_ready, got.init_ready)
         for name in ("init_ids", "in_ids", "out_ids", "in_positions", "src_line"):
             assert torch.equal(getattr(want, name), getattr(got, name)), name
+
+
+# LRU with just the lines that an iteration accesses: from 2^22 lines on the loop
+@pytest.mark.parametrize("length,lines,expected", [(2**22, 2**22, "loop"), (2**22, 2**22 + 1, "from the trace"),
+                                                   (2**22 - 1, 2**22 - 1, "from the trace")])
+def test_lru_of_an_iterations_lines(ginex, length, lines, expected, monkeypatch, capfd):  # noqa: F811
+    n, S = 12_000_000, 3
+    gen = torch.Generator(device="cuda").manual_seed(lines)
+    ids = torch.cat([torch.randperm(n, generator=gen, device="cuda")[:length].int() for _ in range(S)])
+    off = np.arange(S + 1, dtype=np.int64) * length
+    got, said = way(lambda: ginex.changeset(n, ids, off, lines, policy="lru"), monkeypatch, capfd)
+    assert said.strip().endswith(": " + expected), said
+    monkeypatch.setenv("GINEX_STATIC_THRESHOLDS", "1" if expected == "loop" else "0")
+    want = ginex.changeset(n, ids, off, lines, policy="lru")
+    assert np.array_equal(want.miss_count, got.miss_count) and np.array_equal(want.cs_offsets, got.cs_offsets)
+    for name in ("init_ids", "in_ids", "out_ids", "in_positions", "src_line"):
+        assert torch.equal(getattr(want, name), getattr(got, name)), name
