@@ -32,10 +32,11 @@ constexpr int64_t FIT_GUESS_MIN = 1 << 20;             // see changeset_run
 // k_fit_lookup (33 M accesses, 9 M rows of 111 M nodes: 82 + 272 + 55 us against 626 for a random word per access):
 // accesses, nodes to an access, beyond which few entries of a line of the table are used (carried caches,
 // calls in all: 10 M nodes, 1 M accesses 903 -> 889 us, 8.4 M 1 746 -> 1 672; 100 M nodes, 2 M 892 and 917, 8.4 M
-// 2 018 and 2 013, 17 M 5 427 -> 5 382), and nodes from which the table is larger than an L2 (in no order 2.1 M nodes,
+// 2 018 and 2 013, 17 M 5 427 -> 5 382), and rows, whose entries are more than an L2 holds (in no order 2.1 M rows,
 // 40 M accesses 2 509 -> 2 356, 0.8 M, 7 M 2 752 and 2 740, 0.2 M, 11 M 573 and 581; ids in order, whose entries lie side by
-// side: 5.1 M nodes, 40 M 6 018 and 6 125, 0.3 M, 24 M 837 and 1 010).
-constexpr int64_t FIT_LOOKUP_MIN = 1 << 20, FIT_LOOKUP_NODES = 8, FIT_LOOKUP_TABLE = 1 << 21;
+// side: 5.1 M rows, 40 M 6 018 and 6 125, 1.1 M neighbours among 2.8 M nodes, 27 M 3 650 and 3 945, 0.3 M, 24 M 837
+// and 1 010).
+constexpr int64_t FIT_LOOKUP_MIN = 1 << 20, FIT_LOOKUP_NODES = 8, FIT_LOOKUP_ROWS = 1 << 21;
 
 constexpr int FIT_THREADS = 512;
 constexpr int FIT_ITEMS = 16;

@@ -86,10 +86,10 @@ def test_ids_that_crowd(ginex, n, S, spread, near, expected, order, monkeypatch,
     assert np.array_equal(want.init_ready, got.init_ready) and got.miss_count.sum() == 0
 
 
-# the lines of a carried cache, the same way (from 2^21 nodes and 2^20 accesses on)
+# the lines of a carried cache, the same way (from 2^21 rows on)
 @pytest.mark.parametrize("n,S,spread,near,by_bucket", [
     (20_000_000, 60, 60_000, (0,), True), (20_000_000, 60, 60_000, (9000,) * 2 + (0,) * 58, True),
-    (20_000_000, 60, 60_000, (15_000,), False), (2_097_151, 60, 60_000, (0,), False), (2_097_152, 60, 60_000, (0,), True)])
+    (20_000_000, 60, 60_000, (15_000,), False), (16_000_000, 34, 60_000, (0,), False), (16_000_000, 36, 60_000, (0,), True)])
 def test_lines_of_ids_that_crowd(ginex, n, S, spread, near, by_bucket, monkeypatch, capfd):  # noqa: F811
     ids, off = crowd(n, S, spread, near)
     rows = torch.unique(ids)
