@@ -535,10 +535,14 @@ __device__ __forceinline__ void front_adj_copy(const Tables& T, int b, int n0, i
 }
 
 // Up to here a block adds up the totals of the batches in front of its own by itself (a launch of one block
-// for the prefix sums costs 5 us and another wait for the launch before it); beyond, k_stage_offsets.
+// for the prefix sums costs 5 us and another wait for the launch before it); beyond, k_stage_offsets.  Superbatches of 1
+// to 1 000 seeds a batch, two and three hops on 20 000 to 50 M nodes, with the launch against without: 64 batches
+// 1.03 to 1.43 times, 256 0.99 to 1.48, 512 0.99 to 1.43, 1 024 0.96 to 1.37 (1.11 on the mean; 1 000 batches of
+// 100 seeds, 10/10/10, 2 906 us and 2 840, of 16 seeds, 10/10, 187 and 234).
 constexpr int EMIT_BATCHES = 1024;
 
-// ... and scans the sums of a batch's tiles; beyond, k_scan_batch (sums as long as the entries of a tile in LDS).
+// ... and scans the sums of a batch's tiles; beyond, k_scan_batch (sums as long as the entries of a tile in LDS).  The
+// launch against none, the same calls and 1 to 8 batches of up to 300 000 seeds: 1.00 to 1.18 times, 1.03 on the mean.
 constexpr int64_t EMIT_TILES = 1024;
 
 // One block per tile of frontier nodes, see above.  Bound by the reads and writes of a few tiles a block (18

@@ -4,6 +4,7 @@
 // the line of that rank.  Which iteration accesses a row first and what its rank is takes no order among the
 // accesses of a row, so the ids are only dealt to buckets, 2^shift neighbouring ids each, small enough for a bitmap
 // and the lines of a bucket's rows in LDS:
+//   k_fit_sample how full the fullest bucket is, from some of the accesses: where the ids crowd, not this way
 //   k_fit_deal   a block per tile of FIT_TILE accesses of an iteration: sorts them by bucket in LDS, writes ids
 //                and their places in the tile in that order, and the start of every bucket inside the tile
 //   k_fit_rows   a block per bucket: the bits of its ids, then the first iteration of every row (the smallest), then
@@ -12,14 +13,14 @@
 //   k_fit_lines  a block per bucket: line of every row into LDS, C_0; then of every access, in the tiles' order
 //   k_fit_place  a block per tile: the lines back in the order of the accesses
 // A carried cache that holds every row takes its lines the same way, with k_fit_lookup in the place of the two.
-// Ids in order (a bucket's share lies in one tile of every iteration then, some hundred ids long) and ids that crowd in few
-// buckets make long shares; they go to whole waves, with several reads in flight, and lanes that meet in a
+// Ids in order (a bucket's share lies in one tile of every iteration then, some hundred ids long) and ids that crowd
+// in few buckets make long shares; they go to whole waves, with several reads in flight, and lanes that meet in a
 // bucket count together in k_fit_deal.  In order: 24 M accesses, 339 268 nodes, 143 iterations 2 714 -> 699 us a call
 // (701 through the sorted accesses), 40 M on 5.1 M nodes 4 164 -> 1 540 (1 707), 72 560 on 49 M nodes in 2
 // iterations 1 772 -> 365; in no order, 10 M on 11 M nodes, 303 and 303.
-// 33 M accesses, 9 M rows of 111 M nodes, 200 iterations: k_fit_deal 79 us (4 bytes read and 6 written per access,
-// 4.2 TB/s), k_fit_rows 253 and k_fit_lines 191 (7.4 M shares of four or five ids, the latency of their reads),
-// k_fit_place 53; 729 a call.  Through the sorted accesses 2 004: four radix passes 0.72 ms, heads 0.23, the rows' lines
+// 33 M accesses, 9 M rows of 111 M nodes, 200 iterations: k_fit_sample 7, k_fit_deal 85 us (4 bytes read
+// and 6 written per access, 3.9 TB/s), k_fit_rows 253 and k_fit_lines 191 (7.4 M shares of four or five ids, the latency of their reads),
+// k_fit_place 53; 730 a call.  Through the sorted accesses 2 004: four radix passes 0.72 ms, heads 0.23, the rows' lines
 // scattered to a table over all nodes and looked up there for every access 0.82 (random words).
 // (A wave per bucket that takes the iterations one after the other, without a table of first iterations: 626 us for
 // k_fit_rows, 83 000 vector instructions in a chain of 6 per CU.)

@@ -20,7 +20,7 @@ constexpr int SMALL_S = 256;               // iterations at most (LDS counters o
 // loop against this way: 2 x 40 (half) 293 to 162 us, 256 x 600 (0.3) 2 863 to 1 588, (0.9) 2 180 to 1 603, 32 x 3 500
 // (0.3) 826 to 548, 16 x 10 000 (0.7) 691 to 634; beyond: 128 x 3 500 (0.3) 2 210 and 1 649, but 256 x 3 500 (0.8)
 // 2 926 and 3 415, 100 x 10 000 (0.9) 2 148 and 2 862.
-constexpr int64_t SMALL_IDS = 10 << 14;
+constexpr int64_t SMALL_IDS = 163'840;     // (16 x 10 000, some more)
 constexpr uint32_t NOT_RESIDENT = 0xFFFFu;
 
 struct Small {
