@@ -885,6 +885,7 @@ constexpr int MARK_ITEMS = 8;   // lines / accesses per thread in the mark phase
 // histograms of the trace.  stays.hpp turns them into the changesets.
 #include "deal.hpp"
 #include "stays.hpp"
+#include "lines.hpp"
 #include "fits.hpp"
 #include "small.hpp"
 
@@ -2408,14 +2409,16 @@ int32_t stays_cuts(const Workspace& w, const Stays& q, const int64_t* ids_offset
 // The changesets of a full cache whose state (res_id, addr of the accessed rows, rhist and, for a
 // carried cache, dead_bits) is set up, from the node-sorted accesses (see stays.hpp).
 // `ends`: the other buffer of the sort, `rows`: a word per distinct row.  last_head: the last row of
-// C_0, null for a carried cache, whose rows are in held_bits; accessed: the superbatch's.
+// C_0, null for a carried cache, whose rows are in held_bits; accessed: the superbatch's; start: the rows of the start
+// state by line.
 int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, uint64_t* ends,
                   uint64_t* rows, int64_t distinct, const uint64_t* last_head,
                   const uint32_t* held_bits, const uint32_t* accessed, const int32_t* ids,
                   const int64_t* ids_offsets, int64_t total, int32_t S, int32_t* in_ids, int32_t* out_ids,
                   int32_t* in_positions,
                   int64_t cs_capacity, int64_t* cs_offsets, int64_t* miss_count, int32_t* src_line,
-                  int64_t* total_changes, int64_t* init_ready, bool carried, int32_t* final_ids, hipStream_t st) {
+                  int64_t* total_changes, int64_t* init_ready, bool carried, const int32_t* start,
+                  int32_t* final_ids, hipStream_t st) {
   const State& state = w.st;
   const Plan& pl = w.plan;
   const size_t off_lds = sizeof(int32_t) * (S + 1);
@@ -2446,7 +2449,11 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
                          w.d_offsets, S, last_head, held_bits, (uint32_t)from,
                          (uint32_t)std::min(total, from + window), ends);
   }
-  GINEX_HIP(zero_async(Zeros().add(w.key_hists, (int64_t)S * (S + 1)).add(pl.arr_cur, S + 1), st));
+  // (and the words that the blocks of k_move_lines exchange, in an array of the planned path)
+  constexpr int MOVE_STATE = 2 * MOVE_BLOCKS + 1;
+  static_assert(MOVE_STATE <= PLAN_CAND_WORDS, "room for them");
+  GINEX_HIP(zero_async(Zeros().add(w.key_hists, (int64_t)S * (S + 1)).add(pl.arr_cur, S + 1)
+                           .add(pl.cand_dead, MOVE_STATE), st));
   hipLaunchKernelGGL(k_key_hists, dim3((unsigned)ceil_div(longest, TB * TOUCH_ITEMS), (unsigned)S),
                      dim3(TB), sizeof(uint32_t) * (S + 1), st, ends, w.d_offsets, S, w.key_hists);
   bool never = false;      // bucket "never" is cut
@@ -2486,10 +2493,8 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
     GINEX_HIP(hipStreamSynchronize(st));
     return GINEX_OK;
   };
-  if (distinct == total && !lru) {
-    // no row is accessed twice (a superbatch of one iteration, for one): nothing is inserted, so the lists stay
-    // empty and the lines are those of the start state (one iteration of 15 k accesses, 2 k lines carried:
-    // 457 -> 311 us per call)
+  // nothing is inserted: the lines are those of the start state
+  auto lines_of_start = [&]() -> int32_t {
     if (src_line) {
       Step s{};
       s.ids = ids;
@@ -2499,6 +2504,11 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
       GINEX_LAUNCH_CHECK();
     }
     return finish();
+  };
+  if (distinct == total && !lru) {
+    // no row is accessed twice (a superbatch of one iteration, for one), so the lists stay empty (one iteration of
+    // 15 k accesses, 2 k lines carried: 457 -> 311 us per call)
+    return lines_of_start();
   }
   uint32_t* const leave_start = reinterpret_cast<uint32_t*>(state.res_next);
   // both sets of bits in node order where the members of the cuts were: a quarter byte per access in an
@@ -2568,110 +2578,130 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
 
   // the insertion lists, and when every line is given up again
   // (the ends are not read any more)
-  uint32_t* const leave_ins = reinterpret_cast<uint32_t*>(ends);
-  int32_t* const leaving = reinterpret_cast<int32_t*>(leave_ins + total);
+  uint64_t* const leave_ins = ends;
   // (the numbers of candidates are the planned path's)
   uint64_t* const ins_pairs = sizeof(int32_t) * w.max_heads >= sizeof(uint64_t) * pl.ins_words
                                   ? reinterpret_cast<uint64_t*>(pl.ins_cand) : nullptr;
   const InsIndex at_ins{ins_pairs, pl.ins_bits, pl.ins_base};
-  if (M > 0) {
-    hipLaunchKernelGGL(k_ins_emit, dim3((unsigned)pl.ins_tile_count), dim3(TB), off_lds, st, pl.ins_bits,
-                       pl.ins_words, pl.ins_tiles, ids, w.d_offsets, S, in_ids, in_positions,
-                       pl.ins_base, ins_pairs, (int32_t*)nullptr);
-    if (carried)
-      hipLaunchKernelGGL(k_stays_idle, dim3((unsigned)ceil_div(state.cap, TB)), dim3(TB), 0, st, q,
-                         state.res_id, accessed, state.cap, leave_start);
-    int levels = 1;
-    while ((1 << levels) <= S) ++levels;
-    const dim3 walk_grid((unsigned)ceil_div(total, WALK_TILE));
-    if (lru)
-      hipLaunchKernelGGL(k_lru_walk, walk_grid, dim3(TB), sizeof(uint64_t) * S + off_lds, st, q, sorted, total,
-                         last_head, state.addr, at_ins, leave_ins, leave_start);
-    else if (S <= NEVER_LDS_S)
-      hipLaunchKernelGGL(k_stays_walk<true>, walk_grid, dim3(TB), off_lds * (1 + levels), st, q, sorted,
-                         total, state.addr, hit_words, ins_words, at_ins, leave_ins,
-                         leave_start);
-    else
-      hipLaunchKernelGGL(k_stays_walk<false>, walk_grid, dim3(TB), off_lds, st, q, sorted, total,
-                         state.addr, hit_words, ins_words, at_ins, leave_ins,
-                         leave_start);
-    const int64_t place_blocks = std::min<int64_t>(ceil_div(M + state.cap, TB * 8), 512);
-    hipLaunchKernelGGL(k_leave_places, dim3((unsigned)place_blocks), dim3(TB), sizeof(uint32_t) * S, st,
-                       M, state.cap, S, leave_ins, leave_start, cs_offsets, pl.arr_cur, leaving);
-    GINEX_LAUNCH_CHECK();
-  }
+  if (M == 0) return lines_of_start();
+  hipLaunchKernelGGL(k_ins_emit, dim3((unsigned)pl.ins_tile_count), dim3(TB), off_lds, st, pl.ins_bits,
+                     pl.ins_words, pl.ins_tiles, ids, w.d_offsets, S, in_ids, in_positions,
+                     pl.ins_base, ins_pairs, (int32_t*)nullptr);
+  if (carried)
+    hipLaunchKernelGGL(k_stays_idle, dim3((unsigned)ceil_div(state.cap, TB)), dim3(TB), 0, st, q,
+                       state.res_id, accessed, state.cap, leave_start);
+  int levels = 1;
+  while ((1 << levels) <= S) ++levels;
+  Moves moves{};
+  if (int32_t rc = moves_shape(state, longest, &moves)) return rc;
+  int32_t* const hand_over = moves.blocks > 0 ? src_line : nullptr;
+  const dim3 walk_grid((unsigned)ceil_div(total, WALK_TILE));
+  if (lru)
+    hipLaunchKernelGGL(k_lru_walk, walk_grid, dim3(TB), sizeof(uint64_t) * S + off_lds, st, q, sorted, total,
+                       last_head, state.addr, at_ins, leave_ins, leave_start, hand_over);
+  else if (S <= NEVER_LDS_S)
+    hipLaunchKernelGGL(k_stays_walk<true>, walk_grid, dim3(TB), off_lds * (1 + levels), st, q, sorted,
+                       total, state.addr, hit_words, ins_words, at_ins, leave_ins,
+                       leave_start, hand_over);
+  else
+    hipLaunchKernelGGL(k_stays_walk<false>, walk_grid, dim3(TB), off_lds, st, q, sorted, total,
+                       state.addr, hit_words, ins_words, at_ins, leave_ins,
+                       leave_start, hand_over);
+  GINEX_LAUNCH_CHECK();
 
   // the lines
-  if (M > 0 || src_line) {
-    Step s{};
-    s.words = ceil_div(state.cap, 64);
-    // tiles of 512 lines while there are few of them (their counters are atomics that share cache
-    // lines), of 4096 for large caches (every block adds up the counters in front of its own)
-    const bool large = state.cap >= LARGE_CACHE;
-    s.tile_shift = large ? 12 : 9;
-    s.tiles = ceil_div(state.cap, int64_t(1) << s.tile_shift);
-    // and there four counters to a 128-byte line, on which additions queue up (0.2 G/s per line;
-    // 13 M lines: 29.9 -> 28.0 us per iteration), as where most iterations change many lines, as far as
-    // there is room
-    int64_t most = 0;
-    for (int32_t t = 0; t < S; ++t) most = std::max(most, cs[t + 1] - cs[t]);
-    s.cnt_shift = large || most * DENSE_SHARE > state.cap ? 3 : 0;
-    while (s.cnt_shift > 0 && 3 * (s.tiles << s.cnt_shift) > state.words) --s.cnt_shift;
-    const int64_t stride = s.tiles << s.cnt_shift;
-    // flag words: evict_words, and the scratch bitmap over ids, which has room for them (cap is at
-    // most num_nodes, and the arrays of the workspace are padded to 256 bytes); the counters sit in
-    // the second scratch bitmap, one counter for 512 lines or more against one word for 32 ids
-    uint64_t* flags[2] = {state.evict_words, reinterpret_cast<uint64_t*>(state.bitmap)};
-    uint32_t* counts = state.bitmap_in;
-    // (see DENSE_SHARE)
-    auto is_dense = [&](int64_t n) {
-      return n * DENSE_SHARE > state.cap || (lru && n > 0 && s.tiles <= DENSE_TILES);
-    };
-    GINEX_HIP(zero_async(Zeros().add(flags[0], s.words).add(flags[1], s.words).add(counts, 3 * stride), st));
-    s.leaving = leaving;
-    s.leave_ins = leave_ins;
-    s.in_ids = in_ids;
-    s.out_ids = out_ids;
-    auto changes = [&](int32_t t) { return t < S ? cs[t + 1] - cs[t] : int64_t(0); };
-    auto flag_blocks = [&](int32_t t, bool dense) {
-      return std::min<int64_t>(ceil_div(changes(t), dense ? DENSE_ENTRIES : TB), 256);
-    };
-    s.next = flags[0];
-    s.cnt_next = counts;
-    s.next_dst = 0;
-    s.next_n = cs[1];
-    s.next_filled = pl.arr_cur;
-    if (is_dense(cs[1]))
-      hipLaunchKernelGGL(k_step_flags<true>, dim3((unsigned)flag_blocks(0, true)), dim3(TB), 0, st, s);
-    else if (cs[1] > 0)
-      hipLaunchKernelGGL(k_step_flags<false>, dim3((unsigned)flag_blocks(0, false)), dim3(TB), 0, st, s);
-    for (int32_t t = 0; t < S; ++t) {
-      s.now = flags[t & 1];
-      s.next = flags[(t + 1) & 1];
-      s.cnt_now = counts + (t % 3) * stride;
-      s.cnt_next = counts + ((t + 1) % 3) * stride;
-      s.cnt_clear = counts + ((t + 2) % 3) * stride;
-      const bool dense = is_dense(std::max(changes(t), changes(t + 1)));
-      const int64_t line_words = dense ? (large ? 64 : 8) : large ? 256 : 64;
-      s.emit_blocks = M > 0 ? ceil_div(s.words, line_words) : 0;
-      s.flag_blocks = flag_blocks(t + 1, dense);
-      s.dst = cs[t];
-      s.n_change = changes(t);
-      s.next_dst = cs[t + 1];
-      s.next_n = changes(t + 1);
-      s.next_filled = pl.arr_cur + t + 1;
-      s.ids = ids + ids_offsets[t];
-      s.n = ids_offsets[t + 1] - ids_offsets[t];
-      s.src_line = src_line ? src_line + ids_offsets[t] : nullptr;
-      const dim3 blocks((unsigned)(s.emit_blocks + s.flag_blocks + (src_line ? ceil_div(s.n, TB * 4) : 0)));
-      if (blocks.x == 0) continue;
-      if (dense && large) hipLaunchKernelGGL((k_step_lines<64, true>), blocks, dim3(TB), 0, st, state, s);
-      else if (dense) hipLaunchKernelGGL((k_step_lines<8, true>), blocks, dim3(TB), 0, st, state, s);
-      else if (large) hipLaunchKernelGGL((k_step_lines<256, false>), blocks, dim3(TB), 0, st, state, s);
-      else hipLaunchKernelGGL((k_step_lines<64, false>), blocks, dim3(TB), 0, st, state, s);
-    }
+  if (moves.blocks > 0) {
+    moves.words = pl.cand_dead;
+    moves.gave_up = pl.cand_dead + 2 * MOVE_BLOCKS;
+    moves.leave_start = leave_start;
+    moves.leave_ins = leave_ins;
+    moves.ids = ids;
+    moves.in_ids = in_ids;
+    moves.out_ids = out_ids;
+    moves.src_line = src_line;
+    move_lines_async(state, moves, w.d_offsets, cs_offsets, st);
+    GINEX_LAUNCH_CHECK();
+    uint32_t gave_up = 1;
+    GINEX_HIP(hipMemcpyAsync(&gave_up, moves.gave_up, sizeof(gave_up), hipMemcpyDeviceToHost, st));
+    if (int32_t rc = finish()) return rc;
+    if (!gave_up) return GINEX_OK;
+    hipLaunchKernelGGL(k_start_lines, dim3((unsigned)ceil_div(std::max(state.cap, total), TB)), dim3(TB), 0, st, state,
+                       start, total, src_line);
     GINEX_LAUNCH_CHECK();
   }
+  int32_t* const leaving = reinterpret_cast<int32_t*>(ends == w.pairs_a ? w.pairs_b : w.pairs_a);   // (nor the accesses)
+  const int64_t place_blocks = std::min<int64_t>(ceil_div(M + state.cap, TB * 8), 512);
+  hipLaunchKernelGGL(k_leave_places, dim3((unsigned)place_blocks), dim3(TB), sizeof(uint32_t) * S, st,
+                     M, state.cap, S, leave_ins, leave_start, cs_offsets, pl.arr_cur, leaving);
+  GINEX_LAUNCH_CHECK();
+  Step s{};
+  s.words = ceil_div(state.cap, 64);
+  // tiles of 512 lines while there are few of them (their counters are atomics that share cache
+  // lines), of 4096 for large caches (every block adds up the counters in front of its own)
+  const bool large = state.cap >= LARGE_CACHE;
+  s.tile_shift = large ? 12 : 9;
+  s.tiles = ceil_div(state.cap, int64_t(1) << s.tile_shift);
+  // and there four counters to a 128-byte line, on which additions queue up (0.2 G/s per line;
+  // 13 M lines: 29.9 -> 28.0 us per iteration), as where most iterations change many lines, as far as
+  // there is room
+  int64_t most = 0;
+  for (int32_t t = 0; t < S; ++t) most = std::max(most, cs[t + 1] - cs[t]);
+  s.cnt_shift = large || most * DENSE_SHARE > state.cap ? 3 : 0;
+  while (s.cnt_shift > 0 && 3 * (s.tiles << s.cnt_shift) > state.words) --s.cnt_shift;
+  const int64_t stride = s.tiles << s.cnt_shift;
+  // flag words: evict_words, and the scratch bitmap over ids, which has room for them (cap is at
+  // most num_nodes, and the arrays of the workspace are padded to 256 bytes); the counters sit in
+  // the second scratch bitmap, one counter for 512 lines or more against one word for 32 ids
+  uint64_t* flags[2] = {state.evict_words, reinterpret_cast<uint64_t*>(state.bitmap)};
+  uint32_t* counts = state.bitmap_in;
+  // (see DENSE_SHARE)
+  auto is_dense = [&](int64_t n) {
+    return n * DENSE_SHARE > state.cap || (lru && n > 0 && s.tiles <= DENSE_TILES);
+  };
+  GINEX_HIP(zero_async(Zeros().add(flags[0], s.words).add(flags[1], s.words).add(counts, 3 * stride), st));
+  s.leaving = leaving;
+  s.leave_ins = leave_ins;
+  s.in_ids = in_ids;
+  s.out_ids = out_ids;
+  auto changes = [&](int32_t t) { return t < S ? cs[t + 1] - cs[t] : int64_t(0); };
+  auto flag_blocks = [&](int32_t t, bool dense) {
+    return std::min<int64_t>(ceil_div(changes(t), dense ? DENSE_ENTRIES : TB), 256);
+  };
+  s.next = flags[0];
+  s.cnt_next = counts;
+  s.next_dst = 0;
+  s.next_n = cs[1];
+  s.next_filled = pl.arr_cur;
+  if (is_dense(cs[1]))
+    hipLaunchKernelGGL(k_step_flags<true>, dim3((unsigned)flag_blocks(0, true)), dim3(TB), 0, st, s);
+  else if (cs[1] > 0)
+    hipLaunchKernelGGL(k_step_flags<false>, dim3((unsigned)flag_blocks(0, false)), dim3(TB), 0, st, s);
+  for (int32_t t = 0; t < S; ++t) {
+    s.now = flags[t & 1];
+    s.next = flags[(t + 1) & 1];
+    s.cnt_now = counts + (t % 3) * stride;
+    s.cnt_next = counts + ((t + 1) % 3) * stride;
+    s.cnt_clear = counts + ((t + 2) % 3) * stride;
+    const bool dense = is_dense(std::max(changes(t), changes(t + 1)));
+    const int64_t line_words = dense ? (large ? 64 : 8) : large ? 256 : 64;
+    s.emit_blocks = ceil_div(s.words, line_words);
+    s.flag_blocks = flag_blocks(t + 1, dense);
+    s.dst = cs[t];
+    s.n_change = changes(t);
+    s.next_dst = cs[t + 1];
+    s.next_n = changes(t + 1);
+    s.next_filled = pl.arr_cur + t + 1;
+    s.ids = ids + ids_offsets[t];
+    s.n = ids_offsets[t + 1] - ids_offsets[t];
+    s.src_line = src_line ? src_line + ids_offsets[t] : nullptr;
+    const dim3 blocks((unsigned)(s.emit_blocks + s.flag_blocks + (src_line ? ceil_div(s.n, TB * 4) : 0)));
+    if (blocks.x == 0) continue;
+    if (dense && large) hipLaunchKernelGGL((k_step_lines<64, true>), blocks, dim3(TB), 0, st, state, s);
+    else if (dense) hipLaunchKernelGGL((k_step_lines<8, true>), blocks, dim3(TB), 0, st, state, s);
+    else if (large) hipLaunchKernelGGL((k_step_lines<256, false>), blocks, dim3(TB), 0, st, state, s);
+    else hipLaunchKernelGGL((k_step_lines<64, false>), blocks, dim3(TB), 0, st, state, s);
+  }
+  GINEX_LAUNCH_CHECK();
   return finish();
 }
 
@@ -3306,7 +3336,8 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
     return stays_run(who, w, sorted, ends, rows, distinct, start_ids ? nullptr : reinterpret_cast<uint64_t*>(w.d_counts),
                      held_bits, accessed, ids, ids_offsets, total, S, in_ids, out_ids, in_positions,
                      cs_capacity, cs_offsets, miss_count,
-                     src_line, total_changes, init_ready, start_ids != nullptr, final_ids, st);
+                     src_line, total_changes, init_ready, start_ids != nullptr, start_ids ? start_ids : init_ids,
+                     final_ids, st);
   }
 
   // part 3: the recurrence, with no host round trip between iterations

@@ -16,7 +16,7 @@
 // last iterations) decide no hit and no insertion; they follow after the others, see below.
 // With all cuts decided, hits, misses, insertions and the iteration that evicts every row
 // follow for all accesses at once, and the only thing left that is sequential is which line
-// an inserted row gets: one launch per iteration, whose work is the iteration's changes.
+// an inserted row gets: lines.hpp.
 // Before, an iteration was four launches that passed over its accesses and over all lines.
 //
 // LRU goes the same way with other thresholds, see "LRU" below.
@@ -25,8 +25,7 @@
 // 0.83 ms to look right.  Here: k_stay_ends 0.49 ms (scattered words), k_key_hists 0.05,
 // k_static_roll 0.16, 17 levels of k_cut_members + k_cut_decide 0.020 + 0.010 each (two chains of
 // dependent reads), k_stays_mark 0.14 (random words of the table, L2), k_stays_links 0.28 (one random
-// word per pair, 117 G/s), bucket "never" 0.11, k_stays_walk 0.40, k_ins_emit 0.06, k_step_lines 200 x 7.7 us (most of
-// it latency: launch, flags, counters, records, each waiting for the one before).
+// word per pair, 117 G/s), bucket "never" 0.11, k_stays_walk 0.40, k_ins_emit 0.06, k_move_lines 0.89.
 #pragma once
 
 constexpr int STATIC_S_MAX = 2048;      // iterations up to which the (S + 1) x S table is kept
@@ -712,7 +711,11 @@ __global__ __launch_bounds__(TB) void k_lru_wide(Stays q, const LruJob* __restri
 
 // ---- the lists and the evicting iterations ----------------------------------------------------------
 
-// Every access: hit or miss (src_line: 0 / -1, the lines follow), and whether a miss is an insertion
+// In the place of an access's line until it is known.  No line has this number: there are at most INT32_MAX.
+constexpr int32_t LOOK_UP = INT32_MAX;   // a hit
+constexpr int32_t HANDED_OVER = -2;      // a hit whose line comes with the row's insertion, in the iteration before it
+
+// Every access: hit or miss (src_line: LOOK_UP / -1, the lines follow), and whether a miss is an insertion
 // (bit p of ins_bits).  A miss that is never accessed again is none: where
 // bucket "never" is the one that is cut, the iteration drops as many rows as it has misses, incoming
 // rows of the bucket first.
@@ -769,7 +772,7 @@ __global__ __launch_bounds__(TB) void k_stays_mark(Stays q, int64_t n, int32_t* 
           hit = (e[k] >> 16) == NO_CUT ? (int32_t)(e[k] & 0xFFFFu) == i : stay_hits(q, e[k], w[k], i, v[k]);
         if (!hit) inserted = stay_inserts(q, c, stay_next(w[k]), v[k]);
       }
-      if (src_line) src_line[p] = hit ? 0 : -1;
+      if (src_line) src_line[p] = hit ? LOOK_UP : -1;
     }
     const uint64_t m = __ballot(inserted);
     const int64_t first = base + k * TB + (threadIdx.x & ~(WAVE - 1));
@@ -1202,6 +1205,13 @@ __global__ __launch_bounds__(BIG) void k_ins_offsets(int64_t* __restrict__ cs_of
 constexpr uint32_t STAYS = 0xFFFFFFFFu;
 constexpr uint32_t LEAVES_NEXT = 0xFFFFFFFEu;
 
+// The record of an insertion: that, and the position of the row's next access where this is a hit of the iteration
+// after the insertion and marked HANDED_OVER (see k_move_lines).
+constexpr uint32_t NO_POSITION = 0xFFFFFFFFu;
+__device__ __forceinline__ uint64_t ins_record(uint32_t leaves, uint32_t next_position) {
+  return (uint64_t)next_position << 32 | leaves;
+}
+
 // The insertions' bits and the number of them in front of each word: side by side where the workspace has room (one
 // random word per insertion instead of two), else in two arrays.
 struct InsIndex {
@@ -1248,8 +1258,9 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(5))) void k_
     Stays q, const uint64_t* __restrict__ sorted, int64_t n, const int32_t* __restrict__ addr,
                                                    const uint64_t* __restrict__ hit_words,
                                                    const uint64_t* __restrict__ ins_words,
-                                                   InsIndex at_ins, uint32_t* __restrict__ leave_ins,
-                                                   uint32_t* __restrict__ leave_start) {
+                                                   InsIndex at_ins, uint64_t* __restrict__ leave_ins,
+                                                   uint32_t* __restrict__ leave_start,
+                                                   int32_t* __restrict__ hand_over) {
   extern __shared__ int32_t lds_off[];    // offsets [S + 1], limits [levels * (S + 1)]
   const int32_t* never = q.never;
   if (NEVER_LDS) {
@@ -1324,8 +1335,16 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(5))) void k_
     const uint32_t found = __shfl(leave_of[k], mine ? lane + __ffsll((unsigned long long)mine) - 1 : lane, WAVE);
     const uint32_t leaves = mine ? found : carry;
     const uint32_t v = (uint32_t)(cur[k] >> 32), p = (uint32_t)cur[k];
-    if (ins[k] >> lane & 1)
-      leave_ins[slot[k]] = leaves == (uint32_t)(iteration(p) + 1) ? LEAVES_NEXT : leaves;
+    uint32_t rp = __shfl_down(p, 1, WAVE);         // the next access, if it is one of the row
+    const uint32_t op = __shfl((uint32_t)cur[k + 1], 0, WAVE);
+    if (lane == WAVE - 1) rp = op;
+    if (ins[k] >> lane & 1) {
+      const int32_t i = iteration(p);
+      uint32_t next = NO_POSITION;
+      // (no end here: a hit of the row)
+      if (hand_over && !(stops[k] >> lane & 1) && (int32_t)rp < lds_off[i + 2]) hand_over[next = rp] = HANDED_OVER;
+      leave_ins[slot[k]] = ins_record(leaves == (uint32_t)(i + 1) ? LEAVES_NEXT : leaves, next);
+    }
     // a first access that hits is one of a start-state row
     uint32_t lv = (uint32_t)__shfl_up(v, 1, WAVE);
     const uint64_t before = k > 0 ? shfl_u64(cur[k > 0 ? k - 1 : 0], WAVE - 1) : left_of;
@@ -1340,8 +1359,9 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(5))) void k_
 __global__ __launch_bounds__(TB) void k_lru_walk(Stays q, const uint64_t* __restrict__ sorted, int64_t n,
                                                  const uint64_t* __restrict__ last_head,
                                                  const int32_t* __restrict__ addr,
-                                                 InsIndex at_ins, uint32_t* __restrict__ leave_ins,
-                                                 uint32_t* __restrict__ leave_start) {
+                                                 InsIndex at_ins, uint64_t* __restrict__ leave_ins,
+                                                 uint32_t* __restrict__ leave_start,
+                                                 int32_t* __restrict__ hand_over) {
   extern __shared__ uint64_t lds_limits[];         // [S], then the offsets [S + 1]
   int32_t* const lds_off = reinterpret_cast<int32_t*>(lds_limits + q.S);
   for (int x = threadIdx.x; x < q.S; x += TB) lds_limits[x] = q.limits[x];
@@ -1419,10 +1439,17 @@ __global__ __launch_bounds__(TB) void k_lru_walk(Stays q, const uint64_t* __rest
     const uint64_t before = k > 0 ? shfl_u64(cur[k > 0 ? k - 1 : 0], WAVE - 1) : left_of;
     bool linked = lane > 0 ? !(stops[k] >> (lane - 1) & 1) : k > 0 ? !(stops[k > 0 ? k - 1 : 0] >> (WAVE - 1)) : left_reaches;
     if (lane == 0) lv = (uint32_t)(before >> 32);
+    uint32_t rp = __shfl_down(p, 1, WAVE);         // the next access, if it is one of the row
+    const uint32_t op = __shfl((uint32_t)cur[k + 1], 0, WAVE);
+    if (lane == WAVE - 1) rp = op;
     if (v != 0xFFFFFFFFu) {
-      if (lv == v ? !linked : !in_start_state(v, it[k], last_head, nullptr))   // a miss: inserted
-        leave_ins[InsIndex::index(at_ins.word(p), p)] = leaves == (uint32_t)(it[k] + 1) ? LEAVES_NEXT : leaves;
-      else if (lv != v)                            // a first access that hits is one of a start-state row
+      if (lv == v ? !linked : !in_start_state(v, it[k], last_head, nullptr)) {   // a miss: inserted
+        uint32_t next = NO_POSITION;
+        if (hand_over && !(stops[k] >> lane & 1) && (int32_t)rp < lds_off[it[k] + 2])
+          hand_over[next = rp] = HANDED_OVER;
+        leave_ins[InsIndex::index(at_ins.word(p), p)] =
+            ins_record(leaves == (uint32_t)(it[k] + 1) ? LEAVES_NEXT : leaves, next);
+      } else if (lv != v)                            // a first access that hits is one of a start-state row
         leave_start[addr[v]] = leaves;
     }
     carry = __shfl(leaves, 0, WAVE);
@@ -1446,7 +1473,7 @@ __global__ __launch_bounds__(TB) void k_stays_idle(Stays q, const int32_t* __res
 // an insertion's record keeps the place for the step that learns its line.  A block counts per
 // iteration in LDS first, so that a counter sees one atomic per block.
 __global__ __launch_bounds__(TB) void k_leave_places(int64_t n_ins, int64_t cap, int32_t S,
-                                                     uint32_t* __restrict__ leave_ins,
+                                                     uint64_t* __restrict__ leave_ins,
                                                      const uint32_t* __restrict__ leave_start,
                                                      const int64_t* __restrict__ cs_offsets,
                                                      uint32_t* __restrict__ filled,
@@ -1458,7 +1485,7 @@ __global__ __launch_bounds__(TB) void k_leave_places(int64_t n_ins, int64_t cap,
   const int64_t per = ((n + gridDim.x - 1) / gridDim.x + TB - 1) / TB * TB;
   const int64_t first = (int64_t)blockIdx.x * per, last = first + per < n ? first + per : n;
   for (int64_t x = first + threadIdx.x; x < last; x += TB) {
-    const uint32_t e = x < n_ins ? leave_ins[x] : leave_start[x - n_ins];
+    const uint32_t e = x < n_ins ? (uint32_t)leave_ins[x] : leave_start[x - n_ins];
     if (e < (uint32_t)S) atomicAdd(&s_cnt[e], 1u);
   }
   __syncthreads();
@@ -1468,7 +1495,7 @@ __global__ __launch_bounds__(TB) void k_leave_places(int64_t n_ins, int64_t cap,
   }
   __syncthreads();
   for (int64_t x = first + threadIdx.x; x < last; x += TB) {
-    const uint32_t e = x < n_ins ? leave_ins[x] : leave_start[x - n_ins];
+    const uint32_t e = x < n_ins ? (uint32_t)leave_ins[x] : leave_start[x - n_ins];
     if (e >= (uint32_t)S) continue;
     const uint32_t at = atomicAdd(&s_cnt[e], 1u);
     const bool room = (int64_t)at < cs_offsets[e + 1];   // (always, for distinct ids)
@@ -1478,6 +1505,8 @@ __global__ __launch_bounds__(TB) void k_leave_places(int64_t n_ins, int64_t cap,
 }
 
 // ---- the lines: one launch per iteration -----------------------------------------------------------
+//
+// For more lines than the blocks of k_move_lines hold in LDS, and where these did not all run (see lines.hpp).
 
 constexpr int64_t LARGE_CACHE = int64_t(1) << 21;   // lines from which tiles and blocks of the steps are larger
 
@@ -1491,7 +1520,7 @@ struct Step {
   int64_t next_dst, next_n;    // the next iteration's
   const uint32_t* next_filled; // entries of the next iteration's list that stem from earlier iterations
   int32_t* leaving;            // lists of evicted lines
-  const uint32_t* leave_ins;   // per insertion: place in `leaving`, LEAVES_NEXT or STAYS
+  const uint64_t* leave_ins;   // per insertion: place in `leaving`, LEAVES_NEXT or STAYS (the lower half)
   const int32_t* in_ids;
   int32_t* out_ids;
   const int32_t* ids;          // this iteration's accesses
@@ -1624,7 +1653,7 @@ __global__ __launch_bounds__(TB) void k_step_lines(State st, Step s) {
     if (at >= s.n_change) continue;                // (as many lines as insertions, for distinct ids)
     const int32_t gone = st.res_id[line];
     const int32_t comes = s.in_ids[s.dst + at];
-    const uint32_t leaves = s.leave_ins[s.dst + at];
+    const uint32_t leaves = (uint32_t)s.leave_ins[s.dst + at];
     s.out_ids[s.dst + at] = gone;
     st.res_id[line] = comes;
     st.addr[comes] = line;

@@ -1,0 +1,82 @@
+"""Lines of inserted rows by blocks that wait for each other, against a launch per iteration, the loop over the cache
+state and the oracle (tolerance zero): caches around the lines of a block and around what its LDS holds, iterations that
+change more lines than a block hands over at a time or access more rows than it looks up at a time, waits
+that are given up."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+
+from test_gpu_parity import check_changeset, dev, ginex  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+NAMES = ("in_ids", "out_ids", "in_positions", "src_line", "final_ids")
+
+
+def same(a, b):
+    assert np.array_equal(a.miss_count, b.miss_count) and np.array_equal(a.cs_offsets, b.cs_offsets)
+    for name in NAMES:
+        x, y = getattr(a, name), getattr(b, name)
+        assert (x is None) == (y is None) and (x is None or torch.equal(x, y)), name
+
+
+# one line, around a block's 512, two blocks and a half
+@pytest.mark.parametrize("policy", ["belady", "lru"])
+@pytest.mark.parametrize("cap", [1, 2, 511, 512, 513, 1280])
+def test_small_caches_equal_the_oracle(ginex, policy, cap, monkeypatch):  # noqa: F811
+    rng = np.random.default_rng(cap)
+    S, n = 11, 4 * cap + 40
+    lengths = rng.integers(0, cap + 1, S)
+    lengths[3], lengths[7] = cap, 0
+    parts = [rng.permutation(n)[:k] for k in lengths]
+    parts[5] = parts[4][::-1].copy()        # every row again in the iteration behind
+    ids = np.concatenate(parts).astype(np.int32)
+    off = np.concatenate([[0], np.cumsum([len(p) for p in parts])]).astype(np.int64)
+    monkeypatch.setenv("GINEX_STATIC_THRESHOLDS", "1")
+    for polls in (None, "1", "0"):
+        if polls:
+            monkeypatch.setenv("GINEX_MOVE_POLLS", polls)
+        ref = (oracle.changeset if policy == "belady" else oracle.changeset_lru)(n, ids, off, cap)
+        check_changeset(ginex.changeset(n, dev(ids), off, cap, policy=policy), ref, (n, ids, off))
+
+
+# the lines up to which a thread has 1, 3, 9, 17 and 35 words of LDS, and one block's more, of which the last goes back
+# to a launch per iteration; iterations of up to 1.2 M accesses are looked up in one go, longer ones in several
+@pytest.mark.parametrize("cap,length", [(2**19, 400_000), (2**19 + 2, 400_000), (3 * 2**19 + 2, 700_000),
+                                        (9 * 2**19 + 2, 3_000_000), (17 * 2**19 + 2, 4_000_000),
+                                        (35 * 2**19, 6_000_000), (35 * 2**19 + 1, 6_000_000)])
+def test_large_caches_equal_a_launch_per_iteration(ginex, cap, length, monkeypatch):  # noqa: F811
+    S, n = 7, 2 * cap
+    gen = torch.Generator(device="cuda").manual_seed(cap)
+    off = np.arange(S + 1, dtype=np.int64) * length
+    ids = torch.cat([torch.randperm(n, generator=gen, device="cuda")[:length].int() for _ in range(S)])
+    ids[4 * length:5 * length] = ids[3 * length:4 * length].flip(0)   # every row again in the iteration behind
+    start = torch.randperm(n, generator=gen, device="cuda")[:cap].int()
+    monkeypatch.setenv("GINEX_STATIC_THRESHOLDS", "1")
+    monkeypatch.setenv("GINEX_PLANNED", "0")
+    for run in (lambda lines=True: ginex.changeset(n, ids, off, cap, with_lines=lines),
+                lambda lines=True: ginex.changeset(n, ids, off, cap, policy="lru", with_lines=lines),
+                lambda lines=True: ginex.changeset_resume(n, ids, off, start, with_lines=lines)):
+        monkeypatch.setenv("GINEX_MOVE_POLLS", "0")
+        want, bare = run(), run(False)
+        assert want.cs_offsets[-1] > 0
+        for polls in ("1", None):
+            if polls:
+                monkeypatch.setenv("GINEX_MOVE_POLLS", polls)
+            else:
+                monkeypatch.delenv("GINEX_MOVE_POLLS")
+            same(want, run())
+            same(bare, run(False))
+
+
+def test_most_iterations(ginex, monkeypatch):  # noqa: F811
+    rng = np.random.default_rng(0)
+    S, n, cap = 2048, 4000, 600
+    parts = [rng.permutation(n)[:rng.integers(0, 300)] for _ in range(S)]
+    ids = np.concatenate(parts).astype(np.int32)
+    off = np.concatenate([[0], np.cumsum([len(p) for p in parts])]).astype(np.int64)
+    monkeypatch.setenv("GINEX_STATIC_THRESHOLDS", "1")
+    for policy, ref in (("belady", oracle.changeset), ("lru", oracle.changeset_lru)):
+        check_changeset(ginex.changeset(n, dev(ids), off, cap, policy=policy), ref(n, ids, off, cap), (n, ids, off))
