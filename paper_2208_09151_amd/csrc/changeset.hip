@@ -272,9 +272,9 @@ __global__ __launch_bounds__(TB) void k_heads_write(const uint64_t* __restrict__
 #pragma unroll
   for (int i = 0; i < LOOK_ITEMS; ++i) {
     const uint32_t v = (uint32_t)(here[i] >> 32);
-    uint32_t left = __shfl_up(v, 1, WAVE);
+    uint32_t left = from_left(v);
     if (lane == 0) left = before;
-    before = __shfl(v, WAVE - 1, WAVE);
+    before = of_lane(v, WAVE - 1);
     is_head[i] = __ballot(v != left && v != 0xFFFFFFFFu);
     count += __popcll(is_head[i]);
   }
@@ -383,9 +383,9 @@ __global__ __launch_bounds__(TB) void k_accessed_bits(const uint64_t* __restrict
     const uint32_t other = __shfl_down(word, d, WAVE), ow = __shfl_down(w, d, WAVE);
     if (lane + d < WAVE && ow == w) word |= other;
   }
-  const uint32_t left = __shfl_up(w, 1, WAVE);   // (every lane takes part)
+  const uint32_t left = from_left(w);   // (every lane takes part)
   const bool leads = lane == 0 || left != w;
-  const uint32_t last = __shfl(w, WAVE - 1, WAVE);
+  const uint32_t last = of_lane(w, WAVE - 1);
   if (r >= count || !leads) return;
   if (lane == 0 || w == last) atomicOr(&bits[w], word);   // the word may have bits in the next wave, too
   else bits[w] = word;
@@ -1227,7 +1227,7 @@ __device__ void p_evict_emit(const State& st, const Ctrl& c, const Iter& it, con
   if (st.dead_scatter && word) st.evict_words[word_at] = 0;   // consumed: zero for the next scatter
   const uint32_t mine = (uint32_t)__popcll(word);
   const uint32_t incl = wave_inclusive_scan(mine);
-  const uint32_t total = __shfl(incl, WAVE - 1, WAVE);
+  const uint32_t total = of_lane(incl, WAVE - 1);
   const int64_t dst = o.cs_offsets[it.i];
   const uint64_t tag = pair_tag(it.i);
   for (uint32_t k0 = share * WAVE; k0 < total; k0 += split * WAVE) {   // uniform trip count: shuffles inside
@@ -2089,7 +2089,7 @@ __device__ __forceinline__ void step_arrivals(const State& st, const int32_t* __
     const uint32_t v = valid ? (uint32_t)arr_ids[a] : 0u;
     const uint32_t part = valid ? v >> PART_SHIFT : 0xFFFFFFFFu;
     if (valid) atomicOr(&st.dead_bits[v >> 5], 1u << (v & 31));
-    const uint32_t prev = __shfl_up(part, 1, WAVE);
+    const uint32_t prev = from_left(part);
     const bool leader = valid && (lane == 0 || prev != part);
     const uint64_t leaders = __ballot(leader);
     const int valid_lanes = __popcll(__ballot(valid));   // the valid lanes are the lowest ones

@@ -89,6 +89,22 @@ __device__ __forceinline__ T wave_reduce_sum(T v) {
   else return (T)((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), WAVE - 1) << 32 | lo);
 }
 
+// The value of the lane to the left (right); the first (last) lane keeps its own.  All lanes active.
+__device__ __forceinline__ uint32_t from_left(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x138, 0xF, 0xF, false);   // wave_shr:1
+}
+__device__ __forceinline__ uint32_t from_right(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x130, 0xF, 0xF, false);   // wave_shl:1
+}
+// The value of one lane, the same for all.
+__device__ __forceinline__ uint32_t of_lane(uint32_t v, int lane) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
+}
+__device__ __forceinline__ uint64_t of_lane(uint64_t v, int lane) {
+  return (uint64_t)of_lane((uint32_t)(v >> 32), lane) << 32 | of_lane((uint32_t)v, lane);
+}
+__device__ __forceinline__ int32_t of_lane(int32_t v, int lane) { return (int32_t)of_lane((uint32_t)v, lane); }
+
 // Exclusive scan over a block of THREADS threads (a multiple of 64, at most 1024).
 // `total` receives the block sum in every thread.  `smem` needs THREADS/64 + 1 slots.
 template <typename T, int THREADS>
@@ -127,8 +143,6 @@ inline hipError_t fill_async(T* p, int64_t n, T value, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Several arrays cleared in one launch: calls on few ids are a chain of launches of a few microseconds
-// each (a changeset call clears up to eleven arrays).
 // A full mix (the finaliser of MurmurHash3).
 __device__ __forceinline__ uint32_t hash_mix(uint32_t h) {
   h ^= h >> 16;
@@ -138,6 +152,8 @@ __device__ __forceinline__ uint32_t hash_mix(uint32_t h) {
   return h ^ (h >> 16);
 }
 
+// Several arrays cleared in one launch: calls on few ids are a chain of launches of a few microseconds
+// each (a changeset call clears up to eleven arrays).
 struct Zeros {
   static constexpr int MOST = 12;
   uint32_t* at[MOST];

@@ -56,9 +56,9 @@ __global__ __launch_bounds__(TB) void k_small_ranks(const uint64_t* __restrict__
 #pragma unroll
   for (int k = 0; k < LOOK_ITEMS; ++k) {
     const uint32_t v = (uint32_t)(cur[k] >> 32);
-    uint32_t left = __shfl_up(v, 1, WAVE);
+    uint32_t left = from_left(v);
     if (lane == 0) left = before;
-    before = __shfl(v, WAVE - 1, WAVE);
+    before = of_lane(v, WAVE - 1);
     heads[k] = __ballot(v != left && v != 0xFFFFFFFFu);
     count += __popcll(heads[k]);
   }
@@ -70,8 +70,8 @@ __global__ __launch_bounds__(TB) void k_small_ranks(const uint64_t* __restrict__
 #pragma unroll
   for (int k = 0; k < LOOK_ITEMS; ++k) {
     const uint32_t v = (uint32_t)(cur[k] >> 32), p = (uint32_t)cur[k];
-    uint32_t rv = __shfl_down(v, 1, WAVE), rp = __shfl_down(p, 1, WAVE);
-    const uint64_t other = shfl_u64(cur[k + 1], 0);
+    uint32_t rv = from_right(v), rp = from_right(p);
+    const uint64_t other = of_lane(cur[k + 1], 0);
     if (lane == WAVE - 1) {
       rv = (uint32_t)(other >> 32);
       rp = (uint32_t)other;

@@ -112,10 +112,10 @@ __global__ __launch_bounds__(TB) void k_stay_ends(const uint64_t* __restrict__ s
 #pragma unroll
   for (int k = 0; k < LOOK_ITEMS; ++k) {
     const uint32_t v = (uint32_t)(cur[k] >> 32), p = (uint32_t)cur[k];
-    uint32_t lv = __shfl_up(v, 1, WAVE), lp = __shfl_up(p, 1, WAVE), rv = __shfl_down(v, 1, WAVE);
-    int32_t li = __shfl_up(it[k], 1, WAVE), ri = __shfl_down(it[k], 1, WAVE);
-    const uint32_t ov = __shfl((uint32_t)(cur[k + 1] >> 32), 0, WAVE);
-    const int32_t oi = __shfl(it[k + 1], 0, WAVE);
+    uint32_t lv = from_left(v), lp = from_left(p), rv = from_right(v);
+    int32_t li = from_left(it[k]), ri = from_right(it[k]);
+    const uint32_t ov = of_lane((uint32_t)(cur[k + 1] >> 32), 0);
+    const int32_t oi = of_lane(it[k + 1], 0);
     if (lane == 0) {
       lv = (uint32_t)(before >> 32);
       lp = (uint32_t)before;
@@ -125,8 +125,8 @@ __global__ __launch_bounds__(TB) void k_stay_ends(const uint64_t* __restrict__ s
       rv = ov;
       ri = oi;
     }
-    before = shfl_u64(cur[k], WAVE - 1);
-    before_it = __shfl(it[k], WAVE - 1, WAVE);
+    before = of_lane(cur[k], WAVE - 1);
+    before_it = of_lane(it[k], WAVE - 1);
     if (base + k * WAVE + lane >= n || p < from || p >= to) continue;
     uint32_t prev_pos = 0, prev = NO_STAY;
     if (lv == v) {
@@ -172,10 +172,10 @@ __global__ __launch_bounds__(DEAL_THREADS) void k_stay_deal(const uint64_t* __re
     const int32_t it_next = iteration(cur[k + 1]);
     const uint32_t v = (uint32_t)(cur[k] >> 32), p = (uint32_t)cur[k];
     const bool valid = base + k * WAVE + lane < n;
-    uint32_t lv = __shfl_up(v, 1, WAVE), lp = __shfl_up(p, 1, WAVE), rv = __shfl_down(v, 1, WAVE);
-    int32_t ri = __shfl_down(it, 1, WAVE);
-    const uint32_t ov = __shfl((uint32_t)(cur[k + 1] >> 32), 0, WAVE);
-    const int32_t oi = __shfl(it_next, 0, WAVE);
+    uint32_t lv = from_left(v), lp = from_left(p), rv = from_right(v);
+    int32_t ri = from_right(it);
+    const uint32_t ov = of_lane((uint32_t)(cur[k + 1] >> 32), 0);
+    const int32_t oi = of_lane(it_next, 0);
     if (lane == 0) {
       lv = (uint32_t)(before >> 32);
       lp = (uint32_t)before;
@@ -184,7 +184,7 @@ __global__ __launch_bounds__(DEAL_THREADS) void k_stay_deal(const uint64_t* __re
       rv = ov;
       ri = oi;
     }
-    before = shfl_u64(cur[k], WAVE - 1);
+    before = of_lane(cur[k], WAVE - 1);
     uint32_t prev = DEAL_NO_STAY;
     if (lv == v) prev = lp + 2;
     else if (valid && in_start_state(v, it, last_head, held)) prev = DEAL_FROM_START;
@@ -632,7 +632,7 @@ __global__ __launch_bounds__(WAVE) void k_lru_counts(int32_t S, uint32_t* __rest
     const uint32_t c = j >= 0 ? row[j] : 0u;
     const uint32_t incl = wave_inclusive_scan(c);
     if (j >= 0) row[j] = behind + incl - c;
-    behind += __shfl(incl, WAVE - 1, WAVE);
+    behind += of_lane(incl, WAVE - 1);
   }
 }
 
@@ -1084,11 +1084,11 @@ __global__ __launch_bounds__(TB) void k_stays_links(Stays q, const uint64_t* __r
 #pragma unroll
   for (int k = 0; k < LINK_CHUNKS; ++k) {
     const uint32_t v = (uint32_t)(cur[k] >> 32);
-    uint32_t rv = __shfl_down(v, 1, WAVE), lv = __shfl_up(v, 1, WAVE);
-    int32_t rj = __shfl_down(it[k], 1, WAVE);
-    const uint32_t ov = __shfl((uint32_t)(cur[k + 1] >> 32), 0, WAVE);
-    const int32_t oj = __shfl(it[k + 1], 0, WAVE);
-    const uint32_t bv = k > 0 ? __shfl((uint32_t)(cur[k > 0 ? k - 1 : 0] >> 32), WAVE - 1, WAVE) : (uint32_t)(left >> 32);
+    uint32_t rv = from_right(v), lv = from_left(v);
+    int32_t rj = from_right(it[k]);
+    const uint32_t ov = of_lane((uint32_t)(cur[k + 1] >> 32), 0);
+    const int32_t oj = of_lane(it[k + 1], 0);
+    const uint32_t bv = k > 0 ? of_lane((uint32_t)(cur[k > 0 ? k - 1 : 0] >> 32), WAVE - 1) : (uint32_t)(left >> 32);
     if (lane == WAVE - 1) {
       rv = ov;
       rj = oj;
@@ -1111,8 +1111,8 @@ __global__ __launch_bounds__(TB) void k_stays_links(Stays q, const uint64_t* __r
     }
   // the pair in front of the wave's stretch
   bool left_reaches = false;
-  if ((left >> 32) != 0xFFFFFFFFull && (uint32_t)(left >> 32) == __shfl((uint32_t)(cur[0] >> 32), 0, WAVE)) {
-    const int32_t j = __shfl(it[0], 0, WAVE);
+  if ((left >> 32) != 0xFFFFFFFFull && (uint32_t)(left >> 32) == of_lane((uint32_t)(cur[0] >> 32), 0)) {
+    const int32_t j = of_lane(it[0], 0);
     left_reaches = stay_end(q, (uint32_t)iteration((uint32_t)left), j,
                             (uint32_t)(left >> 32), &q.ends[(uint32_t)left], j) == j;
   }
@@ -1120,8 +1120,8 @@ __global__ __launch_bounds__(TB) void k_stays_links(Stays q, const uint64_t* __r
 #pragma unroll
   for (int k = 0; k < LINK_CHUNKS; ++k) {
     const uint32_t v = (uint32_t)(cur[k] >> 32), p = (uint32_t)cur[k];
-    bool reached = __shfl_up(reach, 1, WAVE) >> k & 1u;
-    const bool other = k > 0 ? __shfl(reach, WAVE - 1, WAVE) >> (k > 0 ? k - 1 : 0) & 1u : left_reaches;
+    bool reached = from_left(reach) >> k & 1u;
+    const bool other = k > 0 ? of_lane(reach, WAVE - 1) >> (k > 0 ? k - 1 : 0) & 1u : left_reaches;
     if (lane == 0) reached = other;
     bool h = reached;
     if (head >> k & 1u) {
@@ -1298,8 +1298,8 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(5))) void k_
 #pragma unroll
   for (int k = 0; k < WALK_CHUNKS; ++k) {
     const uint32_t v = (uint32_t)(cur[k] >> 32), p = (uint32_t)cur[k];
-    uint64_t right = ((uint64_t)__shfl_down(v, 1, WAVE) << 32) | __shfl_down(p, 1, WAVE);
-    const uint64_t other = shfl_u64(cur[k + 1], 0);
+    uint64_t right = ((uint64_t)from_right(v) << 32) | from_right(p);
+    const uint64_t other = of_lane(cur[k + 1], 0);
     if (lane == WAVE - 1) right = other;
     const uint64_t right_hits = (hit[k] >> 1) | (hit[k + 1] << (WAVE - 1));
     const bool more = (uint32_t)(right >> 32) == v;
@@ -1335,8 +1335,8 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(5))) void k_
     const uint32_t found = __shfl(leave_of[k], mine ? lane + __ffsll((unsigned long long)mine) - 1 : lane, WAVE);
     const uint32_t leaves = mine ? found : carry;
     const uint32_t v = (uint32_t)(cur[k] >> 32), p = (uint32_t)cur[k];
-    uint32_t rp = __shfl_down(p, 1, WAVE);         // the next access, if it is one of the row
-    const uint32_t op = __shfl((uint32_t)cur[k + 1], 0, WAVE);
+    uint32_t rp = from_right(p);         // the next access, if it is one of the row
+    const uint32_t op = of_lane((uint32_t)cur[k + 1], 0);
     if (lane == WAVE - 1) rp = op;
     if (ins[k] >> lane & 1) {
       const int32_t i = iteration(p);
@@ -1346,11 +1346,11 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(5))) void k_
       leave_ins[slot[k]] = ins_record(leaves == (uint32_t)(i + 1) ? LEAVES_NEXT : leaves, next);
     }
     // a first access that hits is one of a start-state row
-    uint32_t lv = (uint32_t)__shfl_up(v, 1, WAVE);
-    const uint64_t before = k > 0 ? shfl_u64(cur[k > 0 ? k - 1 : 0], WAVE - 1) : left_of;
+    uint32_t lv = (uint32_t)from_left(v);
+    const uint64_t before = k > 0 ? of_lane(cur[k > 0 ? k - 1 : 0], WAVE - 1) : left_of;
     if (lane == 0) lv = (uint32_t)(before >> 32);
     if ((hit[k] >> lane & 1) && lv != v) leave_start[addr[v]] = leaves;
-    carry = __shfl(leaves, 0, WAVE);
+    carry = of_lane(leaves, 0);
   }
 }
 
@@ -1394,10 +1394,10 @@ __global__ __launch_bounds__(TB) void k_lru_walk(Stays q, const uint64_t* __rest
 #pragma unroll
   for (int k = 0; k < WALK_CHUNKS; ++k) {
     const uint32_t v = (uint32_t)(cur[k] >> 32);
-    uint32_t rv = __shfl_down(v, 1, WAVE);
-    int32_t rj = __shfl_down(it[k], 1, WAVE);
-    const uint32_t ov = __shfl((uint32_t)(cur[k + 1] >> 32), 0, WAVE);
-    const int32_t oj = __shfl(it[k + 1], 0, WAVE);
+    uint32_t rv = from_right(v);
+    int32_t rj = from_right(it[k]);
+    const uint32_t ov = of_lane((uint32_t)(cur[k + 1] >> 32), 0);
+    const int32_t oj = of_lane(it[k + 1], 0);
     if (lane == WAVE - 1) {
       rv = ov;
       rj = oj;
@@ -1409,8 +1409,8 @@ __global__ __launch_bounds__(TB) void k_lru_walk(Stays q, const uint64_t* __rest
   }
   bool left_reaches = false;                       // (uniform: chunk 0's first pair is in range)
   {
-    const uint32_t v = __shfl((uint32_t)(cur[0] >> 32), 0, WAVE);
-    if ((uint32_t)(left_of >> 32) == v) left_reaches = reaches(v, iteration(left_of), __shfl(it[0], 0, WAVE));
+    const uint32_t v = of_lane((uint32_t)(cur[0] >> 32), 0);
+    if ((uint32_t)(left_of >> 32) == v) left_reaches = reaches(v, iteration(left_of), of_lane(it[0], 0));
   }
   uint32_t carry = STAYS;
 #pragma unroll
@@ -1435,12 +1435,12 @@ __global__ __launch_bounds__(TB) void k_lru_walk(Stays q, const uint64_t* __rest
     const uint32_t found = __shfl(leave_of[k], mine ? lane + __ffsll((unsigned long long)mine) - 1 : lane, WAVE);
     const uint32_t leaves = mine ? found : carry;
     const uint32_t v = (uint32_t)(cur[k] >> 32), p = (uint32_t)cur[k];
-    uint32_t lv = (uint32_t)__shfl_up(v, 1, WAVE);
-    const uint64_t before = k > 0 ? shfl_u64(cur[k > 0 ? k - 1 : 0], WAVE - 1) : left_of;
+    uint32_t lv = (uint32_t)from_left(v);
+    const uint64_t before = k > 0 ? of_lane(cur[k > 0 ? k - 1 : 0], WAVE - 1) : left_of;
     bool linked = lane > 0 ? !(stops[k] >> (lane - 1) & 1) : k > 0 ? !(stops[k > 0 ? k - 1 : 0] >> (WAVE - 1)) : left_reaches;
     if (lane == 0) lv = (uint32_t)(before >> 32);
-    uint32_t rp = __shfl_down(p, 1, WAVE);         // the next access, if it is one of the row
-    const uint32_t op = __shfl((uint32_t)cur[k + 1], 0, WAVE);
+    uint32_t rp = from_right(p);         // the next access, if it is one of the row
+    const uint32_t op = of_lane((uint32_t)cur[k + 1], 0);
     if (lane == WAVE - 1) rp = op;
     if (v != 0xFFFFFFFFu) {
       if (lv == v ? !linked : !in_start_state(v, it[k], last_head, nullptr)) {   // a miss: inserted
@@ -1452,7 +1452,7 @@ __global__ __launch_bounds__(TB) void k_lru_walk(Stays q, const uint64_t* __rest
       } else if (lv != v)                            // a first access that hits is one of a start-state row
         leave_start[addr[v]] = leaves;
     }
-    carry = __shfl(leaves, 0, WAVE);
+    carry = of_lane(leaves, 0);
   }
 }
 
