@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import ctypes as C
+import threading
 from dataclasses import dataclass
 
 import numpy as np
@@ -212,6 +213,23 @@ class ChangesetResult:
     src_line: torch.Tensor = None   # int32 device [total ids]: cache line of every access, -1 = miss
 
 
+_STAGED = 1 << 14               # words a thread's pinned buffer holds (the offsets of 8 191 iterations)
+_staging = threading.local()
+
+
+def _to_host(words):
+    """A few int64 words of the device as a host array: through the thread's pinned buffer, 14 us
+    against 24 for a copy to pageable memory."""
+    n = words.numel()
+    if n > _STAGED:
+        return words.cpu().numpy()
+    if not hasattr(_staging, "buffer"):
+        _staging.buffer = torch.empty(_STAGED, dtype=torch.int64, pin_memory=True)
+    _staging.buffer[:n].copy_(words, non_blocking=True)
+    torch.cuda.current_stream(words.device).synchronize()
+    return _staging.buffer[:n].numpy().copy()
+
+
 def changeset(num_nodes, ids, ids_offsets, cap, workspace=None, policy="belady",
               builtin_scratch=False, with_lines=True):
     """ginex_changeset (``policy="belady"``) or ginex_changeset_lru (``policy="lru"``).
@@ -258,7 +276,7 @@ def changeset(num_nodes, ids, ids_offsets, cap, workspace=None, policy="belady",
                    _np_ptr(init_ready), _ptr(ws), ws.numel(), _stream())
     _check(rc)
     n = int(total_changes[0])
-    small = small.cpu().numpy()
+    small = _to_host(small)
     return ChangesetResult(init_ids[:int(init_count[0])], in_ids[:n], out_ids[:n], in_pos[:n],
                            small[:S + 1], small[S + 1:2 * S + 1], init_ready[:S],
                            src_line=lines[:total] if with_lines else None)
@@ -295,7 +313,7 @@ def changeset_resume(num_nodes, ids, ids_offsets, start_ids, workspace=None, wit
                                     _np_ptr(total_changes), _ptr(ws), ws.numel(), _stream())
     _check(rc)
     n = int(total_changes[0])
-    small = small.cpu().numpy()
+    small = _to_host(small)
     return ChangesetResult(start_ids, in_ids[:n], out_ids[:n], in_pos[:n], small[:S + 1],
                            small[S + 1:2 * S + 1], np.full(S, cap, dtype=np.int64), final_ids,
                            src_line=lines[:total] if with_lines else None)

@@ -32,6 +32,7 @@
 
 #include "common.hpp"
 #include "primitives.hpp"
+#include "returns.hpp"
 
 namespace ginex {
 namespace {
@@ -2335,7 +2336,7 @@ constexpr int64_t WIDE_AT_ONCE = PLAN_CAND_MAX / (CUT_DIGITS * CUT_BINS);
 // Belady's thresholds and cuts, from the histograms (see stays.hpp); *never: bucket "never" is cut.  jobs: read by a
 // copy to the device that is not waited for here, so the caller keeps it until it has waited.
 int32_t stays_cuts(const Workspace& w, const Stays& q, const int64_t* ids_offsets, int64_t* miss_count, bool* never,
-                   std::vector<int32_t>& jobs, hipStream_t st) {
+                   std::vector<int32_t>& jobs, Returns& back, hipStream_t st) {
   const State& state = w.st;
   const Plan& pl = w.plan;
   const int32_t S = q.S;
@@ -2349,8 +2350,8 @@ int32_t stays_cuts(const Workspace& w, const Stays& q, const int64_t* ids_offset
                      sizeof(int32_t) * S, st, w.cuts, S, w.key_hists);
   GINEX_LAUNCH_CHECK();
   std::vector<Cut> cuts(S);
-  GINEX_HIP(hipMemcpyAsync(cuts.data(), w.cuts, sizeof(Cut) * S, hipMemcpyDeviceToHost, st));
-  GINEX_HIP(hipStreamSynchronize(st));
+  back.get(cuts.data(), w.cuts, S);
+  GINEX_HIP(back.wait(st));
 
   // the levels: a cut waits for the cuts of the bucket its own iteration's accesses come from, and for
   // the earlier cuts of its bucket
@@ -2418,7 +2419,7 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
                   int32_t* in_positions,
                   int64_t cs_capacity, int64_t* cs_offsets, int64_t* miss_count, int32_t* src_line,
                   int64_t* total_changes, int64_t* init_ready, bool carried, const int32_t* start,
-                  int32_t* final_ids, hipStream_t st) {
+                  int32_t* final_ids, Returns& back, hipStream_t st) {
   const State& state = w.st;
   const Plan& pl = w.plan;
   const size_t off_lds = sizeof(int32_t) * (S + 1);
@@ -2475,7 +2476,7 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
                          digit_counts);
     }
     GINEX_LAUNCH_CHECK();
-  } else if (int32_t rc = stays_cuts(w, q, ids_offsets, miss_count, &never, jobs, st)) {
+  } else if (int32_t rc = stays_cuts(w, q, ids_offsets, miss_count, &never, jobs, back, st)) {
     return rc;
   }
 
@@ -2485,12 +2486,11 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
   else hipLaunchKernelGGL(k_stays_mark<false>, mark_grid, dim3(TB), off_lds, st, q, total, src_line, pl.ins_bits);
   // (init_ready: null, or waiting on the device for the next copy to the host)
   auto finish = [&]() -> int32_t {
-    if (init_ready)
-      GINEX_HIP(hipMemcpyAsync(init_ready, w.d_ready, sizeof(int64_t) * S, hipMemcpyDeviceToHost, st));
+    if (init_ready) back.get(init_ready, w.d_ready, S);
     if (final_ids)
       GINEX_HIP(hipMemcpyAsync(final_ids, state.res_id, sizeof(int32_t) * state.cap,
                                hipMemcpyDeviceToDevice, st));
-    GINEX_HIP(hipStreamSynchronize(st));
+    GINEX_HIP(back.wait(st));
     return GINEX_OK;
   };
   // nothing is inserted: the lines are those of the start state
@@ -2561,12 +2561,12 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
   hipLaunchKernelGGL(k_ins_offsets, dim3(1), dim3(BIG), 0, st, cs_offsets, S, w.d_cs_offsets);
   GINEX_LAUNCH_CHECK();
   std::vector<int64_t> host(2 * S + 1);
-  GINEX_HIP(hipMemcpyAsync(host.data(), w.d_ready, sizeof(int64_t) * host.size(), hipMemcpyDeviceToHost, st));
+  back.get(host.data(), w.d_ready, host.size());
   hipLaunchKernelGGL(k_bit_tiles, dim3((unsigned)pl.ins_tile_count), dim3(TB), 0, st, pl.ins_bits,
                      pl.ins_words, pl.ins_tiles);
   GINEX_HIP(exclusive_scan_inplace<uint32_t>(pl.ins_tiles, pl.ins_tile_count + 1,
                                              pl.ins_tiles + pl.ins_tile_count + 1, st));
-  GINEX_HIP(hipStreamSynchronize(st));
+  GINEX_HIP(back.wait(st));
   if (init_ready) std::copy_n(host.begin(), S, init_ready);
   init_ready = nullptr;
   const int64_t* const cs = host.data() + S;
@@ -2622,7 +2622,7 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
     move_lines_async(state, moves, w.d_offsets, cs_offsets, st);
     GINEX_LAUNCH_CHECK();
     uint32_t gave_up = 1;
-    GINEX_HIP(hipMemcpyAsync(&gave_up, moves.gave_up, sizeof(gave_up), hipMemcpyDeviceToHost, st));
+    back.get(&gave_up, moves.gave_up);
     if (int32_t rc = finish()) return rc;
     if (!gave_up) return GINEX_OK;
     hipLaunchKernelGGL(k_start_lines, dim3((unsigned)ceil_div(std::max(state.cap, total), TB)), dim3(TB), 0, st, state,
@@ -2756,7 +2756,7 @@ dim3 fit_grid(const Fit& f) { return dim3((unsigned)(ceil_div(f.buckets, 8) * 8)
 // estimated.
 int32_t fits_run(const char* who, const Workspace& w, int64_t num_nodes, const int32_t* ids, int64_t total, int32_t S,
                  int64_t max_n, int64_t cap, bool certain, int32_t* init_ids, int32_t* src_line,
-                 int64_t* init_ready, int64_t* distinct, hipStream_t st) {
+                 int64_t* init_ready, int64_t* distinct, Returns& back, hipStream_t st) {
   *distinct = -1;
   size_t start_bytes;
   const size_t room = sizeof(uint64_t) * total;
@@ -2781,8 +2781,8 @@ int32_t fits_run(const char* who, const Workspace& w, int64_t num_nodes, const i
   GINEX_HIP(exclusive_scan_inplace<uint32_t>(f.counts, counts, f.counts + counts, st, FitReady{f, w.d_ready}));
   GINEX_LAUNCH_CHECK();
   std::vector<int64_t> ready(S);
-  GINEX_HIP(hipMemcpyAsync(ready.data(), w.d_ready, sizeof(int64_t) * S, hipMemcpyDeviceToHost, st));
-  GINEX_HIP(hipStreamSynchronize(st));
+  back.get(ready.data(), w.d_ready, S);
+  GINEX_HIP(back.wait(st));
   *distinct = ready[S - 1];
   if (*distinct == FIT_NOT) return GINEX_OK;
   // (the other ways would use such an id as an index)
@@ -2826,7 +2826,7 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
                       int32_t* in_positions, int64_t cs_capacity, int64_t* cs_offsets,
                       int64_t* miss_count, int32_t* src_line, int64_t* total_changes,
                       int64_t* init_ready, const int32_t* start_ids, int32_t* final_ids, void* ws,
-                      size_t ws_bytes, void* stream, bool allow_planned = true) {
+                      size_t ws_bytes, void* stream, bool pinned = true, bool allow_planned = true) {
   if (!ids_offsets || !init_count || !cs_offsets || !miss_count || !total_changes || !ws)
     return fail(GINEX_ERR_ARG, "%s: a required pointer is null", who);
   if (S >= 1 && ids_offsets[0] != 0)
@@ -2855,6 +2855,7 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
                 w.bytes);
   if ((uintptr_t)ws & 255) return fail(GINEX_ERR_ARG, "%s: workspace must be 256-byte aligned", who);
   hipStream_t st = (hipStream_t)stream;
+  Returns back(pinned);
   State& state = w.st;
   state.lru = lru ? 1 : 0;
   // The loop only (Belady beyond 2 048 iterations): worth it where a pass over the cache lines is
@@ -2905,7 +2906,7 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
   const bool certain = cap >= std::min(total, num_nodes);
   if (!start_ids && cap > 0 && !validate && (certain || (4 * cap >= 3 * total && total >= FIT_GUESS_MIN))) {
     if (int32_t rc = fits_run(who, w, num_nodes, ids, total, S, max_n, cap, certain, init_ids, src_line,
-                              init_ready, &rows, st))
+                              init_ready, &rows, back, st))
       return rc;
     if (rows >= 0 && rows <= cap) {
       say("every row fits, no sort");
@@ -2929,8 +2930,8 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
                        sizeof(int32_t) * (S + 1), st, sorted, total, w.d_offsets, S, num_nodes,
                        w.d_counts);
     GINEX_LAUNCH_CHECK();
-    GINEX_HIP(hipMemcpyAsync(bad, w.d_counts, sizeof(bad), hipMemcpyDeviceToHost, st));
-    GINEX_HIP(hipStreamSynchronize(st));
+    back.get(bad, w.d_counts, 2);
+    GINEX_HIP(back.wait(st));
     if (bad[0] || bad[1])
       return fail(GINEX_ERR_INPUT, "%s: %llu ids outside [0, %lld), %llu ids repeated inside an "
                   "iteration", who, bad[0], (long long)num_nodes, bad[1]);
@@ -2943,9 +2944,8 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
   int64_t distinct = rows;
   if (rows < 0) {
     uint32_t distinct32 = 0;
-    GINEX_HIP(hipMemcpyAsync(&distinct32, w.head_tiles + w.look_tiles, sizeof(uint32_t),
-                             hipMemcpyDeviceToHost, st));
-    GINEX_HIP(hipStreamSynchronize(st));
+    back.get(&distinct32, w.head_tiles + w.look_tiles);
+    GINEX_HIP(back.wait(st));
     distinct = distinct32;
   }
   if (distinct > w.max_heads)
@@ -2966,8 +2966,8 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
     hipLaunchKernelGGL(k_small_belady, dim3(1), dim3(BIG), 0, st, small);
     GINEX_LAUNCH_CHECK();
     std::vector<int64_t> host(2 * S + 1);
-    GINEX_HIP(hipMemcpyAsync(host.data(), w.d_ready, sizeof(int64_t) * host.size(), hipMemcpyDeviceToHost, st));
-    GINEX_HIP(hipStreamSynchronize(st));
+    back.get(host.data(), w.d_ready, host.size());
+    GINEX_HIP(back.wait(st));
     *init_count = cap;
     if (init_ready) std::copy_n(host.begin(), S, init_ready);
     *total_changes = host[2 * S];
@@ -2997,8 +2997,7 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
   }
   // (to the host with the next copy that has to be waited for anyway)
   auto bring_ready = [&]() {
-    return init_ready ? hipMemcpyAsync(init_ready, w.d_ready, sizeof(int64_t) * S, hipMemcpyDeviceToHost, st)
-                      : hipSuccess;
+    if (init_ready) back.get(init_ready, w.d_ready, S);
   };
   if (!start_ids && (distinct <= cap || cap == 0)) {
     // everything fits (no row ever misses), or there is no cache (every row misses and
@@ -3022,8 +3021,8 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
                          ids, total, state.addr, src_line);
       GINEX_LAUNCH_CHECK();
     }
-    GINEX_HIP(bring_ready());
-    GINEX_HIP(hipStreamSynchronize(st));
+    bring_ready();
+    GINEX_HIP(back.wait(st));
     return GINEX_OK;
   }
   // A carried cache with room for every row of the superbatch never evicts a row that is
@@ -3123,8 +3122,8 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
                            accessed, held_bits, w.d_counts);
       }
       GINEX_LAUNCH_CHECK();
-      GINEX_HIP(hipMemcpyAsync(&bad, w.d_counts, sizeof(bad), hipMemcpyDeviceToHost, st));
-      GINEX_HIP(hipStreamSynchronize(st));
+      back.get(&bad, w.d_counts);
+      GINEX_HIP(back.wait(st));
       if (!for_loop) bad = (unsigned long long)cap - bad;   // (rows held, so far)
       if (bad)
         return fail(GINEX_ERR_INPUT, "%s: %llu entries of start_ids are out of range or repeated",
@@ -3175,8 +3174,8 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
       if (fit.sampled) fit_sample_async(fit, ids, total, st);
     }
     int64_t sc[PLAN_SCALARS] = {};
-    GINEX_HIP(hipMemcpyAsync(sc, pl.scalars, sizeof(sc), hipMemcpyDeviceToHost, st));
-    GINEX_HIP(hipStreamSynchronize(st));
+    back.get(sc, pl.scalars, PLAN_SCALARS);
+    GINEX_HIP(back.wait(st));
     const int64_t M = sc[PLAN_M], lo_id = sc[PLAN_LO_ID];
     // the replay in LDS where its arrays hold the call, else (or with GINEX_PLANNED=2) the
     // steps on the bitmap in global memory; neither with fewer dead rows than insertions
@@ -3221,11 +3220,9 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
           GINEX_LAUNCH_CHECK();
           std::vector<int64_t> cs(S + 1);
           std::vector<uint32_t> arr(S + 2);
-          GINEX_HIP(hipMemcpyAsync(cs.data(), cs_offsets, sizeof(int64_t) * (S + 1),
-                                   hipMemcpyDeviceToHost, st));
-          GINEX_HIP(hipMemcpyAsync(arr.data(), pl.arr_off, sizeof(uint32_t) * (S + 1),
-                                   hipMemcpyDeviceToHost, st));
-          GINEX_HIP(hipStreamSynchronize(st));
+          back.get(cs.data(), cs_offsets, S + 1);
+          back.get(arr.data(), pl.arr_off, S + 1);
+          GINEX_HIP(back.wait(st));
           arr[S + 1] = arr[S];
           if (!state.dead_scatter)
             GINEX_HIP(fill_async<uint64_t>(state.evict_words, w.evict_tiles * WAVE, 0ull, st));
@@ -3301,9 +3298,8 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
         GINEX_HIP(hipMemcpyAsync(final_ids, state.res_id, sizeof(int32_t) * cap,
                                  hipMemcpyDeviceToDevice, st));
       int64_t failed[2] = {0, 0};
-      GINEX_HIP(hipMemcpyAsync(failed, pl.scalars + PLAN_FAILED, sizeof(failed),
-                               hipMemcpyDeviceToHost, st));
-      GINEX_HIP(hipStreamSynchronize(st));
+      back.get(failed, pl.scalars + PLAN_FAILED, 2);
+      GINEX_HIP(back.wait(st));
       if (!failed[0]) return GINEX_OK;
       if (trace)
         fprintf(stderr, "[ginex] %s: the replay gave up (reason %lld, iteration %lld): %s\n", who,
@@ -3312,14 +3308,14 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
       return changeset_run(who, lru, num_nodes, ids, ids_offsets, S, cap, init_ids, init_count,
                            in_ids, out_ids, in_positions, cs_capacity, cs_offsets, miss_count,
                            src_line, total_changes, init_ready, start_ids, final_ids, ws, ws_bytes,
-                           stream, false);
+                           stream, pinned, false);
     }
     // not for this path
     if (loop)
       return changeset_run(who, lru, num_nodes, ids, ids_offsets, S, cap, init_ids, init_count,
                            in_ids, out_ids, in_positions, cs_capacity, cs_offsets, miss_count,
                            src_line, total_changes, init_ready, start_ids, final_ids, ws, ws_bytes,
-                           stream, false);
+                           stream, pinned, false);
     GINEX_HIP(fill_async<int64_t>(cs_offsets, S + 1, 0, st));
   }
 
@@ -3337,7 +3333,7 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
                      held_bits, accessed, ids, ids_offsets, total, S, in_ids, out_ids, in_positions,
                      cs_capacity, cs_offsets, miss_count,
                      src_line, total_changes, init_ready, start_ids != nullptr, start_ids ? start_ids : init_ids,
-                     final_ids, st);
+                     final_ids, back, st);
   }
 
   // part 3: the recurrence, with no host round trip between iterations
@@ -3385,12 +3381,11 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
   if (start_ids && final_ids)
     GINEX_HIP(hipMemcpyAsync(final_ids, state.res_id, sizeof(int32_t) * cap,
                              hipMemcpyDeviceToDevice, st));
-  GINEX_HIP(hipMemcpyAsync(total_changes, cs_offsets + S, sizeof(int64_t), hipMemcpyDeviceToHost,
-                           st));
-  GINEX_HIP(bring_ready());
+  back.get(total_changes, cs_offsets + S);
+  bring_ready();
   int32_t fault = 0;
-  GINEX_HIP(hipMemcpyAsync(&fault, state.fault, sizeof(fault), hipMemcpyDeviceToHost, st));
-  GINEX_HIP(hipStreamSynchronize(st));
+  back.get(&fault, state.fault);
+  GINEX_HIP(back.wait(st));
   if (fault)
     return fail(GINEX_ERR_INPUT, "%s: an iteration needed a select among live rows although all "
                 "%lld rows of the superbatch fit the cache of %lld lines: ids repeated inside an "
@@ -3507,5 +3502,5 @@ extern "C" int32_t ginex_changeset_noalloc(int64_t num_nodes, const int32_t* ids
   return changeset_run(who, false, num_nodes, ids, ids_offsets, S, cap, init_ids, init_count,
                        in_ids, out_ids, in_positions, cs_capacity, cs_offsets, miss_count,
                        src_line, total_changes, init_ready, nullptr, nullptr, ws,
-                       (size_t)GINEX_NOALLOC_SCRATCH_BYTES, stream);
+                       (size_t)GINEX_NOALLOC_SCRATCH_BYTES, stream, false);   // (no pinned block either)
 }

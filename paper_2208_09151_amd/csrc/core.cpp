@@ -1,8 +1,10 @@
-// Error reporting and version of the library (host only).
+// Error reporting, the pinned blocks and version of the library (host only).
 #include <cstdarg>
 #include <cstdio>
+#include <mutex>
 
 #include "ginex.h"
+#include "returns.hpp"
 
 namespace ginex {
 
@@ -21,6 +23,31 @@ int32_t fail(int32_t code, const char* fmt, ...) {
   vsnprintf(g_error, sizeof(g_error), fmt, ap);
   va_end(ap);
   return code;
+}
+
+// (kept until the process ends, when the runtime may be gone already)
+static std::mutex g_block_mutex;
+static void* g_free_blocks[HOST_BLOCKS];
+static int g_free = 0, g_made = 0;
+
+void* host_block_take() {
+  {
+    std::lock_guard<std::mutex> lock(g_block_mutex);
+    if (g_free > 0) return g_free_blocks[--g_free];
+    if (g_made >= HOST_BLOCKS) return nullptr;
+    ++g_made;
+  }
+  void* block = nullptr;
+  if (hipHostMalloc(&block, HOST_BLOCK_BYTES, hipHostMallocPortable) == hipSuccess && block) return block;
+  (void)hipGetLastError();
+  std::lock_guard<std::mutex> lock(g_block_mutex);
+  --g_made;
+  return nullptr;
+}
+
+void host_block_give(void* block) {
+  std::lock_guard<std::mutex> lock(g_block_mutex);
+  g_free_blocks[g_free++] = block;
 }
 
 }  // namespace ginex

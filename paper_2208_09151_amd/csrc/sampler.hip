@@ -44,6 +44,7 @@
 #include <vector>
 
 #include "common.hpp"
+#include "returns.hpp"
 
 namespace ginex {
 namespace {
@@ -1277,6 +1278,7 @@ extern "C" int32_t ginex_sample_superbatch(
                   "num_edges without a decrease, indices inside [0, %lld))", who, bad,
                   (long long)g->num_nodes);
   }
+  Returns back;
   int32_t* nlist = w.nlist_a;
   int32_t* nlist_next = w.nlist_b;
   int first_stage = -1;
@@ -1378,8 +1380,8 @@ extern "C" int32_t ginex_sample_superbatch(
     // are decide (a wait of some 15 us in front of a hop of a million picks or more)
     if (buckets && hop_ids(most, k, g->num_nodes) > BUCKET_IDS_LIMIT) {
       std::vector<int32_t> lists(S);
-      GINEX_HIP(hipMemcpyAsync(lists.data(), nlist, sizeof(int32_t) * S, hipMemcpyDeviceToHost, st));
-      GINEX_HIP(hipStreamSynchronize(st));
+      back.get(lists.data(), nlist, S);
+      GINEX_HIP(back.wait(st));
       const int64_t longest = *std::max_element(lists.begin(), lists.end());
       buckets = hop_ids(longest, k, g->num_nodes) <= BUCKET_IDS_LIMIT && !few_wide(longest);
     }
@@ -1491,9 +1493,8 @@ extern "C" int32_t ginex_sample_superbatch(
   // the small host outputs sit back to back in the workspace: one copy brings them all over
   {
     std::vector<int64_t> host(meta_elems(S, H));
-    GINEX_HIP(hipMemcpyAsync(host.data(), w.meta, sizeof(int64_t) * host.size(),
-                             hipMemcpyDeviceToHost, st));
-    GINEX_HIP(hipStreamSynchronize(st));
+    back.get(host.data(), w.meta, host.size());
+    GINEX_HIP(back.wait(st));
     const int64_t* at = host.data();
     memcpy(ids_offsets, at, sizeof(int64_t) * (S + 1));
     at += S + 1;
