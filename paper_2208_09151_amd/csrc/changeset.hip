@@ -1359,21 +1359,15 @@ __global__ __launch_bounds__(TB) void k_part_count(const uint32_t* __restrict__ 
 // dead from the start (they alone would supply M victims, and later arrivals only raise the
 // thresholds).  The rows from lo_id up that are ever dead residents (the M rows dead from the
 // start, and the rows that die during the superbatch: a few thousand, however wide that id
-// range has become) are the candidates; they are numbered in id order, and one workgroup
-// replays the S iterations on a bitmap over these numbers in LDS: it sets the bits of the
-// rows that die in the iteration, takes the top n_i set bits out, orders these rows by cache
-// line and pairs them with the insertions.  A candidate that is itself inserted during this
-// call gets its line written into the candidates' line array by the thread that pairs it and
-// read back, iterations later and a workgroup barrier apart, by the thread that evicts it.
+// range has become) are the candidates; they are numbered in id order, and which iteration evicts
+// which of them, and from which line, follows for all iterations together (victims.hpp).
 // What the path cannot take (more than PLAN_CAND_MAX candidates, an iteration with more than
 // PLAN_SORT_MAX insertions, S above PLAN_S_MAX, fewer rows dead from the start than
 // insertions) goes the way of any other cache (stays.hpp, or the loop above).
-constexpr int PLAN_CAND_WORDS = 16384;              // LDS bitmap of the replay ...
+constexpr int PLAN_CAND_WORDS = 16384;              // words of a bitmap ...
 constexpr int PLAN_CAND_MAX = PLAN_CAND_WORDS * 32; // ... over at most 524 288 candidates
-constexpr int PLAN_SORT_MAX = 4096;      // evictions of one iteration the replay can order
+constexpr int PLAN_SORT_MAX = 4096;      // evictions of one iteration that are ordered in LDS
 constexpr int PLAN_RANK_DIRECT = 256;    // up to here every eviction is compared with every other
-// (the replay's LDS: 64 KB of bitmap, 32 KB for the ordering, 16 KB of offsets; a workgroup
-// of this GPU may use up to 160 KB)
 constexpr int PLAN_S_MAX = 2048;         // iterations (LDS histograms of k_plan_heads)
 enum { PLAN_M = 0, PLAN_MAX_N = 1, PLAN_LO_ID = 2, PLAN_DEAD = 3, PLAN_TAIL = 4, PLAN_FAILED = 5,
        PLAN_WHERE = 6, PLAN_CANDS = 7, PLAN_FULLEST = 8, PLAN_SCALARS = 9 };
@@ -1391,7 +1385,7 @@ struct Plan {
   uint32_t* cand_dead;   // [PLAN_CAND_WORDS] bit c: candidate c is dead from the start
   uint32_t* arr_off;     // [S + 2] candidates that die in iteration d: count at d + 1, then offsets
   uint32_t* arr_cur;     // [S + 1] fill cursors
-  int32_t* arr_cand;     // [PLAN_CAND_MAX] their numbers, grouped by iteration
+  int32_t* arr_cand;     // [PLAN_CAND_MAX] their numbers, grouped by iteration; then the evicted ones (victims.hpp)
   int64_t ins_words, ins_tile_count, cand_tile_count;
 };
 
@@ -1642,7 +1636,7 @@ __device__ __forceinline__ bool plan_arrival(const uint64_t* __restrict__ sorted
 
 // ... then (PLACE = false) the rows >= lo_id that die during the superbatch, counted per
 // iteration at arr_off[d + 1].  PLACE = true, after the candidates are numbered: their numbers
-// go to arr_cand at the cursors, and a row that is inserted during this call leaves its number
+// go to arr_cand at the cursors, d to `when`, and a row that is inserted during this call leaves its number
 // with its insertion record (with arr_ids, the rows themselves go there instead, and nothing
 // else is written).  A block works on one stretch of the sorted pairs and counts
 // per iteration in LDS first, so that the counters and cursors in global memory, a few
@@ -1655,7 +1649,7 @@ __global__ __launch_bounds__(TB) void k_plan_arrivals(const uint64_t* __restrict
                                                       const int64_t* __restrict__ off, int32_t S,
                                                       uint32_t* __restrict__ cand_bits,
                                                       const uint32_t* __restrict__ cand_base,
-                                                      int64_t num_nodes, Plan pl,
+                                                      int64_t num_nodes, Plan pl, int32_t* __restrict__ when,
                                                       int32_t* __restrict__ arr_ids) {
   extern __shared__ int32_t lds_off[];
   uint32_t* s_cnt = reinterpret_cast<uint32_t*>(lds_off + S + 1);
@@ -1697,8 +1691,10 @@ __global__ __launch_bounds__(TB) void k_plan_arrivals(const uint64_t* __restrict
     const uint32_t below = (1u << (v & 31)) - 1u;
     const uint32_t c = cand_base[((uint32_t)v >> 5) - lo_word] + __popc(cand_bits[(uint32_t)v >> 5] & below);
     // (the host takes this path only with at most PLAN_CAND_MAX candidates: c is below that)
+    if (c >= (uint32_t)PLAN_CAND_MAX) continue;
     pl.arr_cand[atomicAdd(&s_cnt[d], 1u)] = (int32_t)c;
-    if (inserted && c < (uint32_t)PLAN_CAND_MAX) {
+    when[c] = d;
+    if (inserted) {
       int64_t h = j;                                 // the row's first access is its insertion
       while (h > 0 && (int32_t)(sorted[h - 1] >> 32) == v) --h;
       const uint32_t p = (uint32_t)(sorted[h] & 0xFFFFFFFFu);
@@ -1708,12 +1704,14 @@ __global__ __launch_bounds__(TB) void k_plan_arrivals(const uint64_t* __restrict
 }
 
 // Numbers the candidates in id order: cand_base per bitmap word, id, start line (-1 for a row
-// that is inserted during this call) and the dead-from-the-start flag per candidate.
+// that is inserted during this call), the dead-from-the-start flag and, for these, when they die (before iteration
+// 0; the others: S until their own is known) per candidate.
 __global__ __launch_bounds__(TB) void k_cand_emit(const uint32_t* __restrict__ cand_bits,
                                                   const uint32_t* __restrict__ dead_bits,
                                                   int64_t lo_word, int64_t nwords,
                                                   const uint32_t* __restrict__ tile_base,
-                                                  const int32_t* __restrict__ addr, Plan pl) {
+                                                  const int32_t* __restrict__ addr, Plan pl,
+                                                  int32_t* __restrict__ when, int32_t S) {
   __shared__ uint32_t smem[TB / WAVE + 1];
   const int64_t w = (int64_t)blockIdx.x * TB + threadIdx.x;
   uint32_t word = w < nwords ? cand_bits[lo_word + w] : 0u;
@@ -1728,6 +1726,7 @@ __global__ __launch_bounds__(TB) void k_cand_emit(const uint32_t* __restrict__ c
       const int32_t v = (int32_t)((lo_word + w) * 32 + b);
       pl.cand_id[c] = v;
       pl.cand_line[c] = addr[v];
+      when[c] = dead >> b & 1 ? 0 : S;
       if (dead >> b & 1) atomicOr(&pl.cand_dead[c >> 5], 1u << (c & 31));
     }
     ++c;
@@ -1756,319 +1755,9 @@ __global__ __launch_bounds__(BIG) void k_plan_arrival_offsets(uint32_t* __restri
   if (threadIdx.x == 0) scalars[PLAN_CANDS] = scalars[PLAN_M] + (int64_t)total;
 }
 
-// Exclusive prefix of v over the BIG threads of the block, and the block total, with a single
-// barrier: every thread adds up the totals of the waves in front of its own.  `slots` (one
-// per wave) must not be rewritten before a later barrier.
-__device__ __forceinline__ uint32_t block_prefix_one_barrier(uint32_t v, uint32_t* slots,
-                                                             uint32_t& total) {
-  const uint32_t inc = wave_inclusive_scan(v);
-  const int w = threadIdx.x / WAVE;
-  if (lane_id() == WAVE - 1) slots[w] = inc;
-  __syncthreads();
-  uint32_t before = 0, all = 0;
-#pragma unroll
-  for (int q = 0; q < BIG / WAVE; ++q) {
-    const uint32_t t = slots[q];
-    all += t;
-    if (q < w) before += t;
-  }
-  total = all;
-  return before + inc - v;
-}
+#include "victims.hpp"
 
-// The replay (see the head of this part).  One block.  scalars[PLAN_FAILED] is set, before the
-// state is touched, when there are more candidates than the bitmap holds, and later if an
-// invariant does not hold; the host then treats the cache as any other.
-// The iteration's offsets sit in LDS, and what an iteration reads from global memory at
-// addresses that do not depend on the selection (the candidates that die in it, its
-// insertions) is requested an iteration ahead, so that the chain of dependent memory accesses
-// per iteration is: selection in LDS -> id and line of the selected candidates -> stores.
-__global__ __launch_bounds__(BIG) void k_plan_replay(State st, Plan pl, int64_t n_cand_tiles,
-                                                     const int64_t* __restrict__ cs_offsets,
-                                                     const int32_t* __restrict__ in_ids,
-                                                     int32_t* __restrict__ out_ids) {
-  __shared__ uint32_t bits[PLAN_CAND_WORDS + BIG];   // room for one more word per thread, see WPT
-  __shared__ int32_t s_a[PLAN_SORT_MAX];
-  __shared__ int32_t s_b[PLAN_SORT_MAX];
-  __shared__ uint32_t s_arr[PLAN_S_MAX + 1];       // arr_off
-  __shared__ int32_t s_cs[PLAN_S_MAX + 1];         // cs_offsets (below 2^31: they index int32 lists)
-  __shared__ uint32_t slots_select[BIG / WAVE], slots_rank[BIG / WAVE];
-  __shared__ int32_t slots_lo[BIG / WAVE], slots_hi[BIG / WAVE];
-  __shared__ int32_t s_failed;
-  static_assert(PLAN_CAND_WORDS + BIG <= (1 << 26), "a noted word packs its index and a count up to 32");
-  static_assert(BIG + PLAN_SORT_MAX / 2 <= PLAN_SORT_MAX && 2 * BIG <= PLAN_SORT_MAX,
-                "the fine buckets of the ranking and the coarse buckets' records fit the two arrays");
-  constexpr int EPT = PLAN_SORT_MAX / BIG;         // evictions of a thread
-  const int32_t S = st.S;
-  const uint32_t n_cand = pl.cand_tiles[n_cand_tiles];
-  if (n_cand > (uint32_t)PLAN_CAND_MAX) {          // uniform
-    if (threadIdx.x == 0) pl.scalars[PLAN_FAILED] = 4;
-    return;
-  }
-  // consecutive bitmap words of a thread: as many as the candidates there are need, and an
-  // odd number, so that the threads of a wave that read their t-th word hit different banks
-  int WPT = (int)(((n_cand + 31) / 32 + BIG - 1) / BIG);
-  if (WPT > 1) WPT |= 1;
-  for (int w = threadIdx.x; w < WPT * BIG; w += BIG) bits[w] = w < PLAN_CAND_WORDS ? pl.cand_dead[w] : 0u;
-  for (int j = threadIdx.x; j <= S; j += BIG) {
-    s_arr[j] = pl.arr_off[j];
-    s_cs[j] = (int32_t)cs_offsets[j];
-  }
-  if (threadIdx.x == 0) s_failed = 0;
-  __syncthreads();
-  // requested ahead for iteration 0
-  int32_t next_arr[EPT], next_in[EPT], next_ic[EPT];
-#pragma unroll
-  for (int e = 0; e < EPT; ++e) {
-    const int32_t k = threadIdx.x + e * BIG;
-    next_arr[e] = (uint32_t)k < s_arr[1] ? pl.arr_cand[k] : -1;
-    const bool have = k < s_cs[1];
-    next_in[e] = have ? in_ids[k] : -1;
-    next_ic[e] = have ? pl.ins_cand[k] : -1;
-  }
-  for (int32_t i = 0; i < S; ++i) {
-    const uint32_t a0 = s_arr[i], a1 = s_arr[i + 1];
-    const int32_t c0 = s_cs[i];
-    const int32_t n = s_cs[i + 1] - c0;
-    // the rows whose last access is in this iteration are dead from here on
-#pragma unroll
-    for (int e = 0; e < EPT; ++e)
-      if (next_arr[e] >= 0) atomicOr(&bits[(uint32_t)next_arr[e] >> 5], 1u << (next_arr[e] & 31));
-    for (uint32_t a = a0 + EPT * BIG + threadIdx.x; a < a1; a += BIG) {
-      const uint32_t c = (uint32_t)pl.arr_cand[a];
-      atomicOr(&bits[c >> 5], 1u << (c & 31));
-    }
-    int32_t my_in[EPT], my_ic[EPT];
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-      my_in[e] = next_in[e];
-      my_ic[e] = next_ic[e];
-    }
-    if (i + 1 < S) {        // the requests for the next iteration
-      const int32_t c1 = s_cs[i + 1], n1 = s_cs[i + 2] - c1;
-#pragma unroll
-      for (int e = 0; e < EPT; ++e) {
-        const int32_t k = threadIdx.x + e * BIG;
-        next_arr[e] = a1 + (uint32_t)k < s_arr[i + 2] ? pl.arr_cand[a1 + k] : -1;
-        next_in[e] = k < n1 ? in_ids[c1 + k] : -1;
-        next_ic[e] = k < n1 ? pl.ins_cand[c1 + k] : -1;
-      }
-    }
-    if (n == 0) continue;   // uniform; the next barrier orders the bits set above
-    if (WPT > 1)            // (s_b is free: the barrier that ended the iteration before)
-      for (int32_t q = threadIdx.x; q < n; q += BIG) s_b[q] = -1;
-    __syncthreads();
-    // the top n set bits: set bits of the chunks above a thread's own, from a block scan
-    uint32_t cnt = 0;
-    for (int t = 0; t < WPT; ++t) cnt += __popc(bits[threadIdx.x * WPT + t]);
-    uint32_t total;
-    const uint32_t below = block_prefix_one_barrier(cnt, slots_select, total);
-    const uint32_t above = total - below - cnt;
-    if (total < (uint32_t)n) {                      // cannot happen (see the head of this part)
-      s_failed = 1;
-      pl.scalars[PLAN_WHERE] = i;
-    } else if (above < (uint32_t)n) {
-      uint32_t take = cnt < (uint32_t)n - above ? cnt : (uint32_t)n - above;
-      uint32_t k = above;
-      if (WPT == 1) {
-        uint32_t word = bits[threadIdx.x];
-        while (take) {
-          const int b = 31 - __clz(word);
-          word &= ~(1u << b);
-          s_a[k++] = (int32_t)(threadIdx.x * 32 + b);
-          --take;
-        }
-        bits[threadIdx.x] = word;
-      } else {
-        // Several words per thread: the selection falls on the few threads at the upper end,
-        // hundreds of bits each.  They only note their words (word and bits to take from its
-        // top, in s_b at the word's first place in s_a; the other entries of s_b are -1), and
-        // the whole block then takes the words apart, one a thread.
-        for (int t = WPT - 1; t >= 0 && take; --t) {
-          const uint32_t wi = threadIdx.x * WPT + t;
-          const uint32_t pc = (uint32_t)__popc(bits[wi]);
-          if (!pc) continue;
-          const uint32_t tw = pc < take ? pc : take;
-          s_b[k] = (int32_t)((wi << 5) | (tw - 1));
-          k += tw;
-          take -= tw;
-        }
-      }
-    }
-    __syncthreads();
-    if (s_failed) break;                            // uniform
-    if (WPT > 1) {
-      for (uint32_t q = threadIdx.x; q < (uint32_t)n; q += BIG) {
-        const int32_t d = s_b[q];
-        if (d < 0) continue;
-        const uint32_t wi = (uint32_t)d >> 5, tw = ((uint32_t)d & 31u) + 1u;
-        uint32_t word = bits[wi];
-        for (uint32_t r = 0; r < tw; ++r) {
-          const int b = 31 - __clz(word);
-          word &= ~(1u << b);
-          s_a[q + r] = (int32_t)(wi * 32 + b);
-        }
-        bits[wi] = word;
-      }
-      __syncthreads();
-    }
-    // the evicted rows and their lines
-    int32_t my_v[EPT], my_line[EPT];
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-      const int32_t k = threadIdx.x + e * BIG;
-      my_v[e] = my_line[e] = -1;
-      if (k >= n) continue;
-      const int32_t c = s_a[k];
-      my_v[e] = pl.cand_id[c];
-      my_line[e] = pl.cand_line[c];
-      s_b[k] = my_line[e];
-      if (my_line[e] < 0) {                         // a dead resident has a line: cannot happen
-        s_failed = 2;
-        pl.scalars[PLAN_WHERE] = i;
-      }
-    }
-    if (n > PLAN_RANK_DIRECT) {                     // uniform: the range of the evicted lines
-      int32_t lo = INT32_MAX, hi = 0;
-#pragma unroll
-      for (int e = 0; e < EPT; ++e)
-        if (my_v[e] >= 0) {
-          lo = my_line[e] < lo ? my_line[e] : lo;
-          hi = my_line[e] > hi ? my_line[e] : hi;
-        }
-#pragma unroll
-      for (int d = WAVE / 2; d > 0; d >>= 1) {
-        const int32_t olo = __shfl_xor(lo, d, WAVE), ohi = __shfl_xor(hi, d, WAVE);
-        lo = olo < lo ? olo : lo;
-        hi = ohi > hi ? ohi : hi;
-      }
-      if (lane_id() == 0) {
-        slots_lo[threadIdx.x / WAVE] = lo;
-        slots_hi[threadIdx.x / WAVE] = hi;
-      }
-    }
-    __syncthreads();
-    if (s_failed) break;                            // uniform; no line may be used as an index then
-    // out_ids in line order: the rank of a line is the number of smaller ones
-    int32_t my_rank[EPT];
-    if (n <= PLAN_RANK_DIRECT) {                    // uniform: every thread counts over all lines
-#pragma unroll
-      for (int e = 0; e < EPT; ++e) {
-        my_rank[e] = 0;
-        if (my_v[e] < 0) continue;
-        int32_t r = 0;
-        for (int32_t q = 0; q < n; ++q) r += s_b[q] < my_line[e];
-        my_rank[e] = r;
-      }
-    } else {
-      // Many evictions: the lines are dealt to buckets that grow with the line, a scan of the
-      // bucket sizes gives the number of lines in the buckets below, and a line is compared
-      // with the members of its own bucket only.  The evicted lines crowd where rows come and
-      // go, so buckets of equal width over their range would leave most of them in a few:
-      // BIG coarse buckets of equal width are counted first, and a coarse bucket with m
-      // members is cut into about m/4 fine ones (a power of two, at most one per line), fewer
-      // than BIG + n/2 in all.
-      // s_a is free (every thread has read its candidates): the fine counters; s_b holds the
-      // coarse counts, then first fine bucket and cut of every coarse bucket, then the lines
-      // by fine bucket.
-      int32_t range_lo = INT32_MAX, range_hi = 0;
-#pragma unroll
-      for (int q = 0; q < BIG / WAVE; ++q) {
-        range_lo = slots_lo[q] < range_lo ? slots_lo[q] : range_lo;
-        range_hi = slots_hi[q] > range_hi ? slots_hi[q] : range_hi;
-      }
-      int coarse_shift = 0;                         // (line - range_lo) >> coarse_shift < BIG
-      while (((range_hi - range_lo) >> coarse_shift) >= BIG) ++coarse_shift;
-      s_b[threadIdx.x] = 0;
-#pragma unroll
-      for (int e = 0; e < EPT; ++e) s_a[threadIdx.x + e * BIG] = 0;
-      __syncthreads();
-      int32_t coarse[EPT], bucket[EPT], slot[EPT];
-#pragma unroll
-      for (int e = 0; e < EPT; ++e) {
-        coarse[e] = bucket[e] = slot[e] = 0;
-        if (my_v[e] < 0) continue;
-        coarse[e] = (my_line[e] - range_lo) >> coarse_shift;
-        atomicAdd(&s_b[coarse[e]], 1);
-      }
-      __syncthreads();
-      {
-        const uint32_t members = (uint32_t)s_b[threadIdx.x];
-        int cut = 0;                                // the coarse bucket becomes 1 << cut fine ones
-        while ((4u << cut) < members && cut < coarse_shift) ++cut;
-        uint32_t fine_total;
-        const uint32_t fine_first = block_prefix_one_barrier(1u << cut, slots_rank, fine_total);
-        s_b[threadIdx.x] = (int32_t)fine_first;     // (only this thread read the entry)
-        s_b[BIG + threadIdx.x] = cut;
-      }
-      __syncthreads();
-#pragma unroll
-      for (int e = 0; e < EPT; ++e) {
-        if (my_v[e] < 0) continue;
-        const int cut = s_b[BIG + coarse[e]];
-        const int32_t within = (my_line[e] - range_lo) & ((1 << coarse_shift) - 1);
-        bucket[e] = s_b[coarse[e]] + (within >> (coarse_shift - cut));
-        slot[e] = atomicAdd(&s_a[bucket[e]], 1);
-      }
-      __syncthreads();
-      {
-        uint32_t cnt_b[EPT], sum = 0;
-#pragma unroll
-        for (int e = 0; e < EPT; ++e) {
-          cnt_b[e] = (uint32_t)s_a[threadIdx.x * EPT + e];
-          sum += cnt_b[e];
-        }
-        uint32_t all;
-        uint32_t run = block_prefix_one_barrier(sum, slots_select, all);
-#pragma unroll
-        for (int e = 0; e < EPT; ++e) {
-          s_a[threadIdx.x * EPT + e] = (int32_t)run;
-          run += cnt_b[e];
-        }
-      }
-      __syncthreads();
-#pragma unroll
-      for (int e = 0; e < EPT; ++e)
-        if (my_v[e] >= 0) s_b[s_a[bucket[e]] + slot[e]] = my_line[e];
-      __syncthreads();
-#pragma unroll
-      for (int e = 0; e < EPT; ++e) {
-        my_rank[e] = 0;
-        if (my_v[e] < 0) continue;
-        const int32_t first = s_a[bucket[e]];
-        const int32_t end = bucket[e] + 1 < PLAN_SORT_MAX ? s_a[bucket[e] + 1] : n;
-        int32_t r = first;
-        for (int32_t q = first; q < end; ++q) r += s_b[q] < my_line[e];
-        my_rank[e] = r;
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < EPT; ++e)
-      if (my_v[e] >= 0) out_ids[c0 + my_rank[e]] = my_v[e];
-    __syncthreads();   // both arrays are free now: they carry the insertions to the threads that hold their lines
-#pragma unroll
-    for (int e = 0; e < EPT; ++e)
-      if (my_v[e] >= 0) {
-        s_a[threadIdx.x + e * BIG] = my_in[e];
-        s_b[threadIdx.x + e * BIG] = my_ic[e];
-      }
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-      if (my_v[e] < 0) continue;
-      const int32_t w = s_a[my_rank[e]];
-      const int32_t wc = s_b[my_rank[e]];
-      const int32_t line = my_line[e];
-      st.addr[w] = line;
-      st.res_id[line] = w;
-      if (wc >= 0) pl.cand_line[wc] = line;        // read when the row is evicted again
-    }
-    __syncthreads();   // also makes these writes visible to the block's later reads
-  }
-  if (threadIdx.x == 0 && s_failed) pl.scalars[PLAN_FAILED] = s_failed;
-}
-
-// ---- the same regime with more candidates or evictions than the replay holds ------------------
+// ---- the same regime with more candidates or evictions than those arrays hold ------------------
 //
 // Hits, misses and insertions are known up front as above; the choice of the evicted rows runs
 // on the standing bitmap of dead rows in global memory instead, three launches per iteration
@@ -2815,7 +2504,7 @@ constexpr int64_t LOOP_LRU_IDS = 1 << 16, LOOP_LRU_LINES = 1 << 22;
 //      accesses it has sorted; where the ids crowd in few buckets, or the rows do not fit, the call goes on to the next
 //   3  fresh Belady, few rows that do not fit: one workgroup, small.hpp.  Not with GINEX_STATIC_THRESHOLDS
 //   4  fresh, every row fits, or there is no cache: from the sorted accesses
-//   5  carried, every row fits: the planned path (replay or steps); gives way to 6 or 7 where its arrays do not hold
+//   5  carried, every row fits: the planned path (all iterations together, or steps); gives way to 6 or 7 where its arrays do not hold
 //      the call.  Not with GINEX_PLANNED=0 or GINEX_LIVE_SELECT=1
 //   6  from the trace, stays.hpp (of many accesses through the windows of deal.hpp): up to 2 048 iterations, LRU with
 //      lines for the longest of them, but not the smallest calls (GINEX_STATIC_THRESHOLDS=1: these, too)
@@ -3156,7 +2845,7 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
                          state.dead_bits, state.words, num_nodes, pl.scalars, state.bitmap);
       hipLaunchKernelGGL(k_plan_arrivals<false>, dim3((unsigned)tail_blocks), dim3(TB), 2 * off_lds, st,
                          sorted, total, pl.scalars, held_bits, w.d_offsets, S, state.bitmap,
-                         pl.cand_base, num_nodes, pl, (int32_t*)nullptr);
+                         pl.cand_base, num_nodes, pl, (int32_t*)nullptr, (int32_t*)nullptr);
       hipLaunchKernelGGL(k_plan_arrival_offsets, dim3(1), dim3(BIG), 0, st, pl.arr_off,
                          pl.arr_cur, S, pl.scalars);
       GINEX_LAUNCH_CHECK();
@@ -3177,11 +2866,17 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
     back.get(sc, pl.scalars, PLAN_SCALARS);
     GINEX_HIP(back.wait(st));
     const int64_t M = sc[PLAN_M], lo_id = sc[PLAN_LO_ID];
-    // the replay in LDS where its arrays hold the call, else (or with GINEX_PLANNED=2) the
+    // all iterations together where their arrays hold the call, else (or with GINEX_PLANNED=2) the
     // steps on the bitmap in global memory; neither with fewer dead rows than insertions
+    // (the arrays: the candidates, at most twice the distinct rows, in the heads that are not used any more, the
+    // counters in the start state's keys or the table of the stays.  The candidates are also at most twice the lines,
+    // so the counters fit one of the two.)
+    const int64_t parts = ceil_div(sc[PLAN_CANDS], PLAN_PART);
+    const bool in_keys = S * parts <= cap;
     const bool stepped = M > 0 && lo_id >= 0 &&
                          ((plan_env && plan_env[0] == '2') || sc[PLAN_MAX_N] > PLAN_SORT_MAX ||
-                          sc[PLAN_CANDS] > PLAN_CAND_MAX);
+                          sc[PLAN_CANDS] > PLAN_CAND_MAX || sc[PLAN_CANDS] > 2 * w.max_heads ||
+                          (!in_keys && parts > S + 1));
     const bool fits = M == 0 || lo_id >= 0;
     const char* const otherwise = loop ? "loop" : "from the trace, as any other cache";
     if (trace)
@@ -3211,12 +2906,12 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
         int64_t tail_blocks = ceil_div(total - sc[PLAN_TAIL], TB);
         tail_blocks = tail_blocks < 1 ? 1 : (tail_blocks > 1024 ? 1024 : tail_blocks);
         if (stepped) {
-          // the rows that die, as ids grouped by iteration (in the array that holds the
-          // candidate numbers of the insertions for the replay, which does not run)
+          // the rows that die, as ids grouped by iteration (in the array of the candidate numbers of
+          // the insertions, which the steps do not need)
           int32_t* const arr_ids = pl.ins_cand;
           hipLaunchKernelGGL(k_plan_arrivals<true>, dim3((unsigned)tail_blocks), dim3(TB),
                              2 * off_lds, st, sorted, total, pl.scalars, held_bits, w.d_offsets, S,
-                             state.bitmap, pl.cand_base, num_nodes, pl, arr_ids);
+                             state.bitmap, pl.cand_base, num_nodes, pl, (int32_t*)nullptr, arr_ids);
           GINEX_LAUNCH_CHECK();
           std::vector<int64_t> cs(S + 1);
           std::vector<uint32_t> arr(S + 2);
@@ -3254,11 +2949,14 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
           }
           GINEX_LAUNCH_CHECK();
           // (a step that met fewer dead rows than insertions leaves its mark in the word the
-          // copy below brings over beside the replay's)
+          // copy below brings over beside the planned path's)
           hipLaunchKernelGGL(k_step_verdict, dim3(1), dim3(1), 0, st, state.fault, pl.scalars);
           GINEX_LAUNCH_CHECK();
         } else {
         // the candidates numbered in id order
+        const Victims victims{reinterpret_cast<int32_t*>(w.heads_b),
+                              in_keys ? reinterpret_cast<uint32_t*>(state.res_next) : w.key_hists,
+                              pl.arr_cand, state.res_next, pl.arr_cur, (int32_t)parts, S};
         const int64_t lo_word = lo_id >> 5;
         const int64_t nwords = state.words - lo_word;
         const int64_t ctiles = ceil_div(nwords, TB);
@@ -3268,11 +2966,18 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
         GINEX_HIP(exclusive_scan_inplace<uint32_t>(pl.cand_tiles, ctiles + 1,
                                                    pl.cand_tiles + ctiles + 1, st));
         hipLaunchKernelGGL(k_cand_emit, dim3((unsigned)ctiles), dim3(TB), 0, st, state.bitmap,
-                           state.dead_bits, lo_word, nwords, pl.cand_tiles, state.addr, pl);
+                           state.dead_bits, lo_word, nwords, pl.cand_tiles, state.addr, pl, victims.when, S);
         hipLaunchKernelGGL(k_plan_arrivals<true>, dim3((unsigned)tail_blocks), dim3(TB), 2 * off_lds, st,
                            sorted, total, pl.scalars, held_bits, w.d_offsets, S, state.bitmap,
-                           pl.cand_base, num_nodes, pl, (int32_t*)nullptr);
-        hipLaunchKernelGGL(k_plan_replay, dim3(1), dim3(BIG), 0, st, state, pl, ctiles, cs_offsets,
+                           pl.cand_base, num_nodes, pl, victims.when, (int32_t*)nullptr);
+        if (parts > 1)
+          hipLaunchKernelGGL(k_plan_counts, dim3((unsigned)S), dim3(TB), 0, st, pl, victims, sc[PLAN_CANDS]);
+        hipLaunchKernelGGL(k_plan_victims, dim3((unsigned)parts), dim3(WAVE), 0, st, pl, victims, ctiles,
+                           cs_offsets);
+        hipLaunchKernelGGL(k_plan_sort, dim3((unsigned)S), dim3(BIG), 0, st, pl, victims, cs_offsets);
+        if (S >= 4)   // (iteration 0 evicts no row it inserted, the last one inserts none: the third of three waits for none)
+          hipLaunchKernelGGL(k_plan_chain, dim3(1), dim3(BIG), 0, st, pl, victims, cs_offsets);
+        hipLaunchKernelGGL(k_plan_pairs, dim3((unsigned)S), dim3(BIG), 0, st, state, pl, victims, cs_offsets,
                            in_ids, out_ids);
         GINEX_LAUNCH_CHECK();
         }
@@ -3302,9 +3007,9 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
       GINEX_HIP(back.wait(st));
       if (!failed[0]) return GINEX_OK;
       if (trace)
-        fprintf(stderr, "[ginex] %s: the replay gave up (reason %lld, iteration %lld): %s\n", who,
+        fprintf(stderr, "[ginex] %s: the planned path gave up (reason %lld, iteration %lld): %s\n", who,
                 (long long)failed[0], (long long)failed[1], otherwise);
-      // the replay gave up, possibly after it had changed the state: start over, without it
+      // it gave up, possibly after it had changed the state: start over, without it
       return changeset_run(who, lru, num_nodes, ids, ids_offsets, S, cap, init_ids, init_count,
                            in_ids, out_ids, in_positions, cs_capacity, cs_offsets, miss_count,
                            src_line, total_changes, init_ready, start_ids, final_ids, ws, ws_bytes,
