@@ -2799,8 +2799,7 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
         if (cap >= HOLD_DEAL_MIN && cap <= total) {
           uint64_t* const dealt = sorted == w.pairs_a ? w.pairs_b : w.pairs_a;
           const int id_bits = bits_for(num_nodes);
-          GINEX_HIP(radix_pass(lines, dealt, cap, 32 + (id_bits > 8 ? id_bits - 8 : 0), 8, radix_plan(cap),
-                               w.hist, st));
+          GINEX_HIP(radix_pass(lines, dealt, cap, 32 + (id_bits > 8 ? id_bits - 8 : 0), 8, w.hist, st));
           hipLaunchKernelGGL(k_hold<true>, dim3(hold_blocks), dim3(TB), 0, st, RadixWords{dealt}, cap,
                              num_nodes, accessed, held, state.addr);
         } else {

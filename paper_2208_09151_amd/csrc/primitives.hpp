@@ -138,7 +138,7 @@ inline hipError_t occurrences_async(const int32_t* values, int64_t n, int64_t bi
 
 // ---------------------------------------------------------------------------------
 // Stable LSD radix sort of uint64 words on bits [bit_lo, bit_hi), at most 8 bits per pass and the same
-// number in every pass, or one less in the last ones: 27 bits as 7 + 7 + 7 + 6 instead of 8 + 8 + 8 + 3 halve the
+// number in every pass (9 bits: see RS_WIDE_BITS), or one less in the last ones: 27 bits as 7 + 7 + 7 + 6 instead of 8 + 8 + 8 + 3 halve the
 // counters that are scanned and double the runs that are written (33 M pairs: 1.22 -> 1.02 ms).
 // Each pass: (1) per-tile digit histogram, (2) exclusive scan of the digit-major
 // histogram, (3) scatter.  In the scatter a wave owns a contiguous run of its tile and
@@ -146,11 +146,18 @@ inline hipError_t occurrences_async(const int32_t* values, int64_t n, int64_t bi
 // input order; keys are then staged in LDS in digit order and written out in runs.
 // ---------------------------------------------------------------------------------
 constexpr int RS_THREADS = 256;
-constexpr int RS_WAVES = RS_THREADS / WAVE;
 constexpr int RS_ITEMS = 16;                    // keys per thread
 constexpr int RS_TILE = RS_THREADS * RS_ITEMS;  // 4096 keys, 32 KB of LDS staging
 constexpr int RS_BITS = 8;
 constexpr int RS_BINS = 1 << RS_BITS;           // at most
+// Wide tiles, four times the keys (128 KB of LDS staging), have room for a bit more with runs of the same length, which
+// is a pass less for 17, 18 and 25 to 27 bits; one block to a CU hides less, though.  Histogram, scan and scatter of all passes
+// over 27 bits, narrow and wide: 33 M words 710 us and 709, 67 M 1 413 and 1 354, 100 M 2 143 and 1 987; 154 M, 26
+// bits, 3 700 and 2 940.  And whatever the digit where there are so many words that the runs of narrow tiles are written more
+// slowly (a scatter by 7 bits: 33 M 97 and 131 us, 100 M 311 and 367, 154 M 690 and 559).
+constexpr int RS_WIDE_THREADS = 1024;
+constexpr int RS_WIDE_BITS = 9;
+constexpr int64_t RS_WIDE_MIN = int64_t(1) << 26, RS_WIDE_ALWAYS = int64_t(1) << 27;
 
 // Where a pass reads its words: an array of words, or (the first pass of a sort of
 // (value, position) pairs) an array of 32-bit values, word j = value j << 32 | j, so that the
@@ -166,46 +173,47 @@ struct RadixValuesWithPositions {
   }
 };
 
-template <typename Source, int BITS>
-static __global__ __launch_bounds__(RS_THREADS) void k_radix_hist(Source in, int64_t n, int shift,
-                                                                  int64_t tiles,
-                                                                  uint32_t* __restrict__ hist) {
+template <typename Source, int BITS, int THREADS>
+static __global__ __launch_bounds__(THREADS) void k_radix_hist(Source in, int64_t n, int shift,
+                                                               int64_t tiles,
+                                                               uint32_t* __restrict__ hist) {
   constexpr int BINS = 1 << BITS;
   __shared__ uint32_t bins[BINS];
   if (threadIdx.x < BINS) bins[threadIdx.x] = 0;
   __syncthreads();
-  const int64_t base = (int64_t)blockIdx.x * RS_TILE;
+  const int64_t base = (int64_t)blockIdx.x * (THREADS * RS_ITEMS);
   uint32_t digit[RS_ITEMS];
 #pragma unroll
   for (int i = 0; i < RS_ITEMS; ++i) {
-    const int64_t j = base + i * RS_THREADS + threadIdx.x;
+    const int64_t j = base + i * THREADS + threadIdx.x;
     digit[i] = (uint32_t)(in(j < n ? j : n - 1) >> shift) & (BINS - 1);
   }
 #pragma unroll
   for (int i = 0; i < RS_ITEMS; ++i)
-    if (base + i * RS_THREADS + threadIdx.x < n) atomicAdd(&bins[digit[i]], 1u);
+    if (base + i * THREADS + threadIdx.x < n) atomicAdd(&bins[digit[i]], 1u);
   __syncthreads();
   if (threadIdx.x < BINS) hist[(int64_t)threadIdx.x * tiles + blockIdx.x] = bins[threadIdx.x];
 }
 
-template <typename Source, int BITS>
-static __global__ __launch_bounds__(RS_THREADS) void k_radix_scatter(
+template <typename Source, int BITS, int THREADS>
+static __global__ __launch_bounds__(THREADS) void k_radix_scatter(
     Source in, uint64_t* __restrict__ out, int64_t n, int shift, int64_t tiles,
     const uint32_t* __restrict__ hist_scanned) {
-  constexpr int BINS = 1 << BITS;
-  static_assert(BINS <= RS_THREADS, "a thread per digit");
-  __shared__ uint64_t staged[RS_TILE];
-  __shared__ uint32_t wave_count[RS_WAVES][BINS];
+  constexpr int BINS = 1 << BITS, WAVES = THREADS / WAVE, TILE = THREADS * RS_ITEMS;
+  static_assert(BINS <= THREADS, "a thread per digit");
+  typedef typename std::conditional<(WAVES > 4), uint16_t, uint32_t>::type Count;   // (at most 1024; LDS is short for many)
+  __shared__ uint64_t staged[TILE];
+  __shared__ Count wave_count[WAVES][BINS];
   __shared__ uint32_t digit_start[BINS];   // start of each digit inside the tile
-  __shared__ int64_t digit_dst[BINS];      // global destination of the digit's run
-  __shared__ uint32_t scan_smem[RS_THREADS / WAVE + 1];
+  __shared__ uint32_t digit_dst[BINS];     // global destination of the digit's run, less its start (modulo 2^32)
+  __shared__ uint32_t scan_smem[THREADS / WAVE + 1];
 
   const int w = threadIdx.x / WAVE;
   const int lane = lane_id();
-  for (int i = threadIdx.x; i < RS_WAVES * BINS; i += RS_THREADS) (&wave_count[0][0])[i] = 0;
+  for (int i = threadIdx.x; i < WAVES * BINS; i += THREADS) (&wave_count[0][0])[i] = 0;
   __syncthreads();
 
-  const int64_t tile_base = (int64_t)blockIdx.x * RS_TILE;
+  const int64_t tile_base = (int64_t)blockIdx.x * TILE;
   const int64_t wave_base = tile_base + (int64_t)w * (WAVE * RS_ITEMS);
   uint64_t key[RS_ITEMS];
   uint32_t rank[RS_ITEMS];  // rank among the wave's keys with the same digit
@@ -221,18 +229,25 @@ static __global__ __launch_bounds__(RS_THREADS) void k_radix_scatter(
   for (int i = 0; i < RS_ITEMS; ++i) {
     const bool valid = wave_base + i * WAVE + lane < n;
     const uint32_t d = (uint32_t)(key[i] >> shift) & (BINS - 1);
-    uint64_t peers = __ballot(valid);
+    // lanes with the same digit: of every bit's ballot m, or of ~m, as the own bit (all ones or none in x) says.  Five
+    // instructions a bit (with a select between m and ~m, which the compiler makes eight of, 7 bits of 33 M words took 121 us
+    // instead of 97: the kernel is as near its arithmetic as its memory)
+    const uint64_t all = __ballot(valid);
+    uint32_t lo = (uint32_t)all, hi = (uint32_t)(all >> 32);
 #pragma unroll
     for (int b = 0; b < BITS; ++b) {
-      const uint64_t m = __ballot((d >> b) & 1);
-      peers &= ((d >> b) & 1) ? m : ~m;
+      const uint32_t x = (uint32_t)__builtin_amdgcn_sbfe((int)d, b, 1);
+      const uint64_t m = __ballot(x != 0);
+      lo = __builtin_amdgcn_bitop3_b32(lo, (uint32_t)m, x, 0x90);           // lo & ~(m ^ x)
+      hi = __builtin_amdgcn_bitop3_b32(hi, (uint32_t)(m >> 32), x, 0x90);
     }
-    const uint32_t before = __popcll(peers & ((1ull << lane) - 1));
+    const uint64_t peers = (uint64_t)hi << 32 | lo;
+    const uint32_t before = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
     const int leader = __ffsll((unsigned long long)peers) - 1;
     uint32_t prev = 0;
     if (valid && lane == leader) {
       prev = wave_count[w][d];
-      wave_count[w][d] = prev + __popcll(peers);
+      wave_count[w][d] = (Count)(prev + __popcll(peers));
     }
     __builtin_amdgcn_wave_barrier();  // keep the LDS update ahead of the next step's read
     prev = __shfl(prev, leader < 0 ? 0 : leader, WAVE);
@@ -246,16 +261,16 @@ static __global__ __launch_bounds__(RS_THREADS) void k_radix_scatter(
     uint32_t run = 0;
     if (d < BINS)
 #pragma unroll
-      for (int ww = 0; ww < RS_WAVES; ++ww) {
+      for (int ww = 0; ww < WAVES; ++ww) {
         const uint32_t c = wave_count[ww][d];
-        wave_count[ww][d] = run;
+        wave_count[ww][d] = (Count)run;
         run += c;
       }
     uint32_t total;
-    const uint32_t start = block_exclusive_scan<uint32_t, RS_THREADS>(run, scan_smem, total);
+    const uint32_t start = block_exclusive_scan<uint32_t, THREADS>(run, scan_smem, total);
     if (d < BINS) {
       digit_start[d] = start;
-      digit_dst[d] = (int64_t)hist_scanned[(int64_t)d * tiles + blockIdx.x] - (int64_t)start;
+      digit_dst[d] = hist_scanned[(int64_t)d * tiles + blockIdx.x] - start;
     }
   }
   __syncthreads();
@@ -271,11 +286,11 @@ static __global__ __launch_bounds__(RS_THREADS) void k_radix_scatter(
   __syncthreads();
 
   const int64_t remaining = n - tile_base;
-  const int count = remaining < RS_TILE ? (int)remaining : RS_TILE;
-  for (int i = threadIdx.x; i < count; i += RS_THREADS) {
+  const int count = remaining < TILE ? (int)remaining : TILE;
+  for (int i = threadIdx.x; i < count; i += THREADS) {
     const uint64_t k = staged[i];
     const uint32_t d = (uint32_t)(k >> shift) & (BINS - 1);
-    out[digit_dst[d] + i] = k;
+    out[digit_dst[d] + (uint32_t)i] = k;
   }
 }
 
@@ -292,49 +307,52 @@ inline RadixPlan radix_plan(int64_t n) {
   return p;
 }
 
-// Sorts `n` words by bits [bit_lo, bit_hi).  `a` holds the input, `b` is a buffer of the
-// same size; returns (through *sorted) which of the two holds the result.  The total
-// number of keys must stay below 2^32 (uint32 histogram).
-template <typename Source, int BITS>
-inline hipError_t radix_pass_bits(Source in, uint64_t* out, int64_t n, int shift, const RadixPlan& p,
-                                  uint32_t* hist, hipStream_t st) {
-  const int64_t h = p.tiles << BITS;
-  hipLaunchKernelGGL((k_radix_hist<Source, BITS>), dim3((unsigned)p.tiles), dim3(RS_THREADS), 0, st, in, n,
-                     shift, p.tiles, hist);
+template <int BITS, int THREADS, typename Source>
+inline hipError_t radix_pass_bits(Source in, uint64_t* out, int64_t n, int shift, uint32_t* hist, hipStream_t st) {
+  const int64_t tiles = ceil_div(n, THREADS * RS_ITEMS), h = tiles << BITS;
+  hipLaunchKernelGGL((k_radix_hist<Source, BITS, THREADS>), dim3((unsigned)tiles), dim3(THREADS), 0, st, in, n,
+                     shift, tiles, hist);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   e = exclusive_scan_inplace<uint32_t>(hist, h, hist + h, st);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_radix_scatter<Source, BITS>), dim3((unsigned)p.tiles), dim3(RS_THREADS), 0, st, in,
-                     out, n, shift, p.tiles, hist);
+  hipLaunchKernelGGL((k_radix_scatter<Source, BITS, THREADS>), dim3((unsigned)tiles), dim3(THREADS), 0, st, in,
+                     out, n, shift, tiles, hist);
   return hipGetLastError();
 }
 
 // A pass over `bits` bits (the digit may be wider than that: the bits above are zero or not sorted by).
 template <typename Source>
-inline hipError_t radix_pass(Source in, uint64_t* out, int64_t n, int shift, int bits, const RadixPlan& p,
-                             uint32_t* hist, hipStream_t st) {
-  if (bits >= 8) return radix_pass_bits<Source, 8>(in, out, n, shift, p, hist, st);
-  if (bits == 7) return radix_pass_bits<Source, 7>(in, out, n, shift, p, hist, st);
-  if (bits == 6) return radix_pass_bits<Source, 6>(in, out, n, shift, p, hist, st);
-  return radix_pass_bits<Source, 5>(in, out, n, shift, p, hist, st);
+inline hipError_t radix_pass(Source in, uint64_t* out, int64_t n, int shift, int bits, uint32_t* hist, hipStream_t st) {
+  if (bits > RS_BITS) return radix_pass_bits<RS_WIDE_BITS, RS_WIDE_THREADS>(in, out, n, shift, hist, st);
+  if (n >= RS_WIDE_ALWAYS) {
+    if (bits == 8) return radix_pass_bits<8, RS_WIDE_THREADS>(in, out, n, shift, hist, st);
+    return radix_pass_bits<7, RS_WIDE_THREADS>(in, out, n, shift, hist, st);
+  }
+  if (bits == 8) return radix_pass_bits<8, RS_THREADS>(in, out, n, shift, hist, st);
+  if (bits == 7) return radix_pass_bits<7, RS_THREADS>(in, out, n, shift, hist, st);
+  if (bits == 6) return radix_pass_bits<6, RS_THREADS>(in, out, n, shift, hist, st);
+  return radix_pass_bits<5, RS_THREADS>(in, out, n, shift, hist, st);
 }
 
 // Bits of pass `k` of the passes that cover `bits`: as even as possible, the wider ones first.
-inline int radix_passes(int bits) { return (bits + RS_BITS - 1) / RS_BITS; }
-inline int radix_pass_width(int bits, int k) {
-  const int passes = radix_passes(bits);
-  return bits / passes + (k < bits % passes ? 1 : 0);
+inline int radix_passes(int bits, int64_t n) {
+  const int narrow = (bits + RS_BITS - 1) / RS_BITS, wide = (bits + RS_WIDE_BITS - 1) / RS_WIDE_BITS;
+  return n >= RS_WIDE_MIN && wide < narrow ? wide : narrow;
 }
+inline int radix_pass_width(int bits, int passes, int k) { return bits / passes + (k < bits % passes ? 1 : 0); }
 
+// Sorts `n` words by bits [bit_lo, bit_hi).  `a` holds the input, `b` is a buffer of the
+// same size; returns (through *sorted) which of the two holds the result.  The total
+// number of keys must stay below 2^32 (uint32 histogram).
 inline hipError_t radix_sort_u64(uint64_t* a, uint64_t* b, int64_t n, int bit_lo, int bit_hi,
                                  uint32_t* hist, hipStream_t st, uint64_t** sorted) {
   *sorted = a;
   if (n <= 1) return hipSuccess;
-  const RadixPlan p = radix_plan(n);
-  for (int k = 0, shift = bit_lo; k < radix_passes(bit_hi - bit_lo); ++k) {
-    const int bits = radix_pass_width(bit_hi - bit_lo, k);
-    const hipError_t e = radix_pass(RadixWords{a}, b, n, shift, bits, p, hist, st);
+  const int passes = radix_passes(bit_hi - bit_lo, n);
+  for (int k = 0, shift = bit_lo; k < passes; ++k) {
+    const int bits = radix_pass_width(bit_hi - bit_lo, passes, k);
+    const hipError_t e = radix_pass(RadixWords{a}, b, n, shift, bits, hist, st);
     if (e != hipSuccess) return e;
     uint64_t* t = a; a = b; b = t;
     shift += bits;
@@ -351,15 +369,15 @@ inline hipError_t radix_sort_values_with_positions(const int32_t* values, uint64
                                                    hipStream_t st, uint64_t** sorted) {
   *sorted = a;
   if (n <= 0) return hipSuccess;
-  const RadixPlan p = radix_plan(n);
+  const int passes = radix_passes(bit_hi - 32, n);
   int shift = 32;
-  for (int k = 0; k < radix_passes(bit_hi - 32); ++k) {
-    const int bits = radix_pass_width(bit_hi - 32, k);
+  for (int k = 0; k < passes; ++k) {
+    const int bits = radix_pass_width(bit_hi - 32, passes, k);
     hipError_t e;
     if (k == 0) {
-      e = radix_pass(RadixValuesWithPositions{values}, a, n, shift, bits, p, hist, st);
+      e = radix_pass(RadixValuesWithPositions{values}, a, n, shift, bits, hist, st);
     } else {
-      e = radix_pass(RadixWords{a}, b, n, shift, bits, p, hist, st);
+      e = radix_pass(RadixWords{a}, b, n, shift, bits, hist, st);
       uint64_t* t = a; a = b; b = t;
     }
     if (e != hipSuccess) return e;
