@@ -363,12 +363,124 @@ __global__ __launch_bounds__(TB) void k_init_state_resume(const int32_t* __restr
 // them per line, two of them atomics on the memory side (2.05 ms for 27.75 M lines of 111 M nodes),
 // these one read of a 14 MB bitmap, one byte stored, and a table entry stored for the rows that are
 // accessed (0.99 ms in the order of the lines; dealt by the upper eight bits of the id first: 0.17 + 0.41
-// ms; the passes around it 0.15).  Whether all rows are distinct and in range shows in the number of bytes set.
+// ms; the passes around it 0.17).  Where a stretch of ids so dealt has room for its bits in LDS, they are put together
+// there, see k_hold_stretch.  Whether all rows are distinct and in range shows in the number of bytes or bits set.
 constexpr int HOLD_ITEMS = 8;
 // Lines are dealt from here on, and where the free buffer of the sort has a word for each.  2^20 lines:
 // dealt 16 + 11 us and the scans of the counters (10), in their own order 19; 2^21: 20 + 28 (and 10)
 // against 51; 2^22: 28 + 54 (and 10) against 128.
 constexpr int64_t HOLD_DEAL_MIN = int64_t(1) << 22;
+
+// A stretch of the ids as they are dealt is shared by up to four blocks, each of which reads all of its words and takes
+// those of its own ids: the lines crowd where the cache was filled up, every id of some stretches and one in six of the others.
+// A part of the dead rows' counts is not divided.
+constexpr int HOLD_SHIFT_MIN = PART_SHIFT, HOLD_SHIFT_MAX = 19, HOLD_SHARE_MAX = 2;   // (2^17 ids to a block at most)
+
+// how many of the heads have an id below x (a wave: all lanes take part, and get it)
+__device__ __forceinline__ int64_t heads_below(const uint64_t* __restrict__ heads, int64_t count, int64_t x) {
+  int64_t lo = 0, hi = count;            // it is in [lo, hi]
+  while (lo < hi) {
+    const int64_t step = (hi - lo + WAVE - 1) / WAVE, at = lo + lane_id() * step;
+    const int n = __popcll(__ballot(at < hi && (int64_t)(uint32_t)heads[at < hi ? at : lo] < x));
+    if (n == 0) return lo;               // (the lanes below: ids ascend)
+    const int64_t next = lo + n * step;
+    lo += (n - 1) * step + 1;
+    hi = next < hi ? next : hi;
+  }
+  return lo;
+}
+
+// All of it for one share of a stretch of 2^shift ids, 2^share of them: accessed and held rows as bits in LDS, the table entries of rows that
+// are both, then the words, the dead rows and their part counts.  in: the words (v << 32 | line) by stretch, that of digit d
+// from starts[d * tiles] on.  27.75 M lines of 111 M nodes, a third of them in 22 of 212 stretches: 313 us, where
+// k_accessed_bits, k_hold, k_held_words and what they have cleared take 105, 413, 40 and 25 (the call 2 724 -> 2 479);
+// one block to a stretch 414, the fullest 22 at work alone in the end.
+__global__ __launch_bounds__(BIG) void k_hold_stretch(const uint64_t* __restrict__ in, const uint32_t* __restrict__ starts,
+                                                      int64_t tiles, int32_t digits, int shift, int share, State st,
+                                                      const uint64_t* __restrict__ heads, int64_t count,
+                                                      uint32_t* __restrict__ accessed,
+                                                      uint32_t* __restrict__ held_bits,
+                                                      unsigned long long* __restrict__ rows) {
+  constexpr int BITS = HOLD_SHIFT_MAX - HOLD_SHARE_MAX, MOST = 1 << (BITS - 5), PARTS = 1 << (BITS - PART_SHIFT);
+  __shared__ uint32_t s_accessed[MOST], s_held[MOST];
+  __shared__ uint32_t s_dead[PARTS], s_rows;
+  __shared__ int64_t s_range[2];
+  // (blocks go to the eight XCDs in turn; the shares of a stretch to the same one)
+  const int32_t m = blockIdx.x / 8, d = (m >> share) * 8 + blockIdx.x % 8, words = 1 << (shift - share - 5);
+  const int64_t first_id = ((int64_t)d << shift) + ((int64_t)(m & ((1 << share) - 1)) << (shift - share));
+  if (first_id >= st.num_nodes) return;
+  const uint32_t base = (uint32_t)first_id;
+  const int64_t span = st.num_nodes - first_id < words * 32 ? st.num_nodes - first_id : words * 32;
+  for (int x = threadIdx.x; x < words; x += BIG) s_accessed[x] = s_held[x] = 0;
+  if (threadIdx.x < PARTS) s_dead[threadIdx.x] = 0;
+  if (threadIdx.x == 0) s_rows = 0;
+  if (threadIdx.x < 2 * WAVE) {
+    const int64_t at = heads_below(heads, count, (int64_t)base + (threadIdx.x < WAVE ? 0 : span));
+    if (lane_id() == 0) s_range[threadIdx.x / WAVE] = at;
+  }
+  __syncthreads();
+  const int64_t last = s_range[1];
+  for (int64_t r0 = s_range[0] + threadIdx.x; r0 < last; r0 += BIG * HOLD_ITEMS) {
+    uint32_t v[HOLD_ITEMS];
+#pragma unroll
+    for (int t = 0; t < HOLD_ITEMS; ++t) v[t] = (uint32_t)heads[r0 + t * BIG < last ? r0 + t * BIG : r0] - base;
+#pragma unroll
+    for (int t = 0; t < HOLD_ITEMS; ++t)
+      if (r0 + t * BIG < last && v[t] < (uint32_t)span) atomicOr(&s_accessed[v[t] >> 5], 1u << (v[t] & 31));
+  }
+  __syncthreads();
+  const int64_t end = d + 1 < digits ? starts[(d + 1) * tiles] : st.cap;
+  uint64_t next[HOLD_ITEMS];               // (asked for while the ones before are put in)
+  auto ask = [&](int64_t x0) {
+#pragma unroll
+    for (int t = 0; t < HOLD_ITEMS; ++t) next[t] = in[x0 + t * BIG < end ? x0 + t * BIG : 0];   // (a branch would be a wait)
+  };
+  int64_t x0 = starts[d * tiles] + threadIdx.x;
+  ask(x0);
+  for (; x0 < end; x0 += BIG * HOLD_ITEMS) {
+    uint32_t v[HOLD_ITEMS], word[HOLD_ITEMS];
+    int32_t line[HOLD_ITEMS];
+#pragma unroll
+    for (int t = 0; t < HOLD_ITEMS; ++t) {
+      v[t] = (uint32_t)(next[t] >> 32) - base;
+      line[t] = (int32_t)(uint32_t)next[t];
+      // (out of range: shows in the number of rows held)
+      if (x0 + t * BIG >= end || v[t] >= (uint32_t)span) v[t] = 0xFFFFFFFFu;
+    }
+    ask(x0 + BIG * HOLD_ITEMS);
+#pragma unroll
+    for (int t = 0; t < HOLD_ITEMS; ++t) word[t] = s_accessed[v[t] != 0xFFFFFFFFu ? v[t] >> 5 : 0];
+#pragma unroll
+    for (int t = 0; t < HOLD_ITEMS; ++t) {
+      if (v[t] == 0xFFFFFFFFu) continue;
+      atomicOr(&s_held[v[t] >> 5], 1u << (v[t] & 31));
+      if (word[t] >> (v[t] & 31) & 1u) st.addr[base + v[t]] = line[t];
+    }
+  }
+  __syncthreads();
+  uint32_t mine = 0;
+  for (int x0 = 0; x0 < words; x0 += BIG) {                       // (whole waves, each in one part)
+    const int x = x0 + threadIdx.x;
+    const int64_t w = (int64_t)(base >> 5) + x;
+    uint32_t held = 0, dead = 0;
+    if (x < words && w < st.words) {
+      held = s_held[x];
+      dead = held & ~s_accessed[x];
+      accessed[w] = s_accessed[x];
+      held_bits[w] = held;
+      st.dead_bits[w] = dead;
+    }
+    mine += __popc(held);
+    const uint32_t sum = wave_reduce_sum((uint32_t)__popc(dead));
+    if (lane_id() == 0 && sum) atomicAdd(&s_dead[x / PART_WORDS], sum);
+  }
+  mine = wave_reduce_sum(mine);
+  if (lane_id() == 0 && mine) atomicAdd(&s_rows, mine);
+  __syncthreads();
+  const int64_t part = (int64_t)(base >> PART_SHIFT) + threadIdx.x;
+  if (threadIdx.x < (words + PART_WORDS - 1) / PART_WORDS && part < st.parts) st.dead_part[part] = s_dead[threadIdx.x];
+  if (threadIdx.x == 0 && s_rows) atomicAdd(rows, (unsigned long long)s_rows);
+}
 
 // bit v of `bits` for every head (heads in id order, so a word's bits are neighbours: a wave
 // gathers them and stores words that are its own)
@@ -2789,25 +2901,35 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
         hipLaunchKernelGGL(k_part_count, dim3((unsigned)state.parts), dim3(TB), 0, st,
                            state.dead_bits, state.words, state.dead_part);
       } else {
-        GINEX_HIP(zero_async(Zeros().add(accessed, state.words).add(reinterpret_cast<uint64_t*>(held), state.words * 4)
-                                 .add(w.d_counts, 1), st));
-        hipLaunchKernelGGL(k_accessed_bits, dim3((unsigned)ceil_div(distinct, TB)), dim3(TB), 0, st, heads,
-                           distinct, accessed);
         GINEX_HIP(hipMemcpyAsync(state.res_id, start_ids, sizeof(int32_t) * cap, hipMemcpyDeviceToDevice, st));
         const unsigned hold_blocks = (unsigned)ceil_div(ceil_div(cap, TB * HOLD_ITEMS), 8) * 8;
         const RadixValuesWithPositions lines{start_ids};
-        if (cap >= HOLD_DEAL_MIN && cap <= total) {
-          uint64_t* const dealt = sorted == w.pairs_a ? w.pairs_b : w.pairs_a;
-          const int id_bits = bits_for(num_nodes);
-          GINEX_HIP(radix_pass(lines, dealt, cap, 32 + (id_bits > 8 ? id_bits - 8 : 0), 8, w.hist, st));
-          hipLaunchKernelGGL(k_hold<true>, dim3(hold_blocks), dim3(TB), 0, st, RadixWords{dealt}, cap,
-                             num_nodes, accessed, held, state.addr);
+        const int id_bits = bits_for(num_nodes), deal_bits = std::min(8, std::max(1, id_bits - HOLD_SHIFT_MIN));
+        const int shift = id_bits - deal_bits;
+        const bool deals = cap >= HOLD_DEAL_MIN && cap <= total;
+        uint64_t* const dealt = sorted == w.pairs_a ? w.pairs_b : w.pairs_a;
+        if (deals) GINEX_HIP(radix_pass(lines, dealt, cap, 32 + shift, deal_bits, w.hist, st));
+        if (deals && shift <= HOLD_SHIFT_MAX) {
+          GINEX_HIP(fill_async<unsigned long long>(w.d_counts, 1, 0ull, st));
+          const int share = std::min(HOLD_SHARE_MAX, shift - HOLD_SHIFT_MIN);
+          const int64_t stretches = ceil_div(ceil_div(num_nodes, int64_t(1) << shift), 8) * 8;
+          hipLaunchKernelGGL(k_hold_stretch, dim3((unsigned)(stretches << share)), dim3(BIG), 0, st, dealt, w.hist,
+                             radix_tiles(cap, deal_bits), 1 << radix_digit(cap, deal_bits).bits, shift, share, state,
+                             heads, distinct, accessed, held_bits, w.d_counts);
         } else {
-          hipLaunchKernelGGL(k_hold<false>, dim3(hold_blocks), dim3(TB), 0, st, lines, cap, num_nodes,
-                             accessed, held, state.addr);
+          GINEX_HIP(zero_async(Zeros().add(accessed, state.words).add(reinterpret_cast<uint64_t*>(held), state.words * 4)
+                                   .add(w.d_counts, 1), st));
+          hipLaunchKernelGGL(k_accessed_bits, dim3((unsigned)ceil_div(distinct, TB)), dim3(TB), 0, st, heads,
+                             distinct, accessed);
+          if (deals)
+            hipLaunchKernelGGL(k_hold<true>, dim3(hold_blocks), dim3(TB), 0, st, RadixWords{dealt}, cap,
+                               num_nodes, accessed, held, state.addr);
+          else
+            hipLaunchKernelGGL(k_hold<false>, dim3(hold_blocks), dim3(TB), 0, st, lines, cap, num_nodes,
+                               accessed, held, state.addr);
+          hipLaunchKernelGGL(k_held_words, dim3((unsigned)state.parts), dim3(TB), 0, st, held, state,
+                             accessed, held_bits, w.d_counts);
         }
-        hipLaunchKernelGGL(k_held_words, dim3((unsigned)state.parts), dim3(TB), 0, st, held, state,
-                           accessed, held_bits, w.d_counts);
       }
       GINEX_LAUNCH_CHECK();
       back.get(&bad, w.d_counts);

@@ -321,17 +321,34 @@ inline hipError_t radix_pass_bits(Source in, uint64_t* out, int64_t n, int shift
   return hipGetLastError();
 }
 
-// A pass over `bits` bits (the digit may be wider than that: the bits above are zero or not sorted by).
+// A pass over `bits` bits (the digit may be wider than that: the bits above are zero or not sorted by): its digit and
+// whether its tiles are wide.
+struct RadixDigit {
+  int bits;
+  bool wide;
+};
+inline RadixDigit radix_digit(int64_t n, int bits) {
+  if (bits > RS_BITS) return {RS_WIDE_BITS, true};
+  if (n >= RS_WIDE_ALWAYS) return {bits == 8 ? 8 : 7, true};
+  return {bits < 5 ? 5 : bits, false};
+}
+
+// Afterwards hist[d * tiles] is where the words of digit d start.
+inline int64_t radix_tiles(int64_t n, int bits) {
+  return ceil_div(n, (radix_digit(n, bits).wide ? RS_WIDE_THREADS : RS_THREADS) * RS_ITEMS);
+}
+
 template <typename Source>
 inline hipError_t radix_pass(Source in, uint64_t* out, int64_t n, int shift, int bits, uint32_t* hist, hipStream_t st) {
-  if (bits > RS_BITS) return radix_pass_bits<RS_WIDE_BITS, RS_WIDE_THREADS>(in, out, n, shift, hist, st);
-  if (n >= RS_WIDE_ALWAYS) {
-    if (bits == 8) return radix_pass_bits<8, RS_WIDE_THREADS>(in, out, n, shift, hist, st);
+  const RadixDigit d = radix_digit(n, bits);
+  if (d.wide) {
+    if (d.bits == RS_WIDE_BITS) return radix_pass_bits<RS_WIDE_BITS, RS_WIDE_THREADS>(in, out, n, shift, hist, st);
+    if (d.bits == 8) return radix_pass_bits<8, RS_WIDE_THREADS>(in, out, n, shift, hist, st);
     return radix_pass_bits<7, RS_WIDE_THREADS>(in, out, n, shift, hist, st);
   }
-  if (bits == 8) return radix_pass_bits<8, RS_THREADS>(in, out, n, shift, hist, st);
-  if (bits == 7) return radix_pass_bits<7, RS_THREADS>(in, out, n, shift, hist, st);
-  if (bits == 6) return radix_pass_bits<6, RS_THREADS>(in, out, n, shift, hist, st);
+  if (d.bits == 8) return radix_pass_bits<8, RS_THREADS>(in, out, n, shift, hist, st);
+  if (d.bits == 7) return radix_pass_bits<7, RS_THREADS>(in, out, n, shift, hist, st);
+  if (d.bits == 6) return radix_pass_bits<6, RS_THREADS>(in, out, n, shift, hist, st);
   return radix_pass_bits<5, RS_THREADS>(in, out, n, shift, hist, st);
 }
 
