@@ -2533,8 +2533,11 @@ Fit fit_shape(const Workspace& w, int64_t num_nodes, int64_t total, int32_t S, i
   f.bad = reinterpret_cast<uint32_t*>(w.d_counts);
   f.num_nodes = num_nodes;
   f.words = w.st.words;
-  f.per_iteration = (int32_t)per_iteration;
-  f.tiles = (int32_t)tiles;
+  // (whether a call goes this way does not depend on the tiles' width; wide ones have fewer starts)
+  const bool wide = S * ceil_div(max_n, FIT_WIDE_TILE) >= FIT_WIDE_MIN && buckets >= FIT_WIDE_BUCKETS;
+  f.tile = wide ? FIT_WIDE_TILE : FIT_TILE;
+  f.per_iteration = (int32_t)ceil_div(max_n, f.tile);
+  f.tiles = S * f.per_iteration;
   f.buckets = (int32_t)buckets;
   return f;
 }
@@ -2543,12 +2546,19 @@ void fit_sample_async(const Fit& f, const int32_t* ids, int64_t total, hipStream
   hipLaunchKernelGGL(k_fit_sample, dim3(FIT_SAMPLE_BLOCKS), dim3(FIT_SAMPLE_THREADS), 0, st, f, ids, total);
 }
 void fit_deal_async(const Fit& f, const int32_t* ids, hipStream_t st) {
-  hipLaunchKernelGGL(k_fit_deal, dim3((unsigned)f.per_iteration, (unsigned)f.S), dim3(FIT_THREADS),
-                     sizeof(uint32_t) * f.buckets, st, f, ids);
+  const dim3 grid((unsigned)f.per_iteration, (unsigned)f.S);
+  const size_t lds = sizeof(uint32_t) * f.buckets;
+  if (f.tile == FIT_WIDE_TILE)
+    hipLaunchKernelGGL(k_fit_deal<FIT_WIDE_THREADS>, grid, dim3(FIT_WIDE_THREADS), lds, st, f, ids);
+  else
+    hipLaunchKernelGGL(k_fit_deal<FIT_THREADS>, grid, dim3(FIT_THREADS), lds, st, f, ids);
 }
 void fit_place_async(const Fit& f, int32_t* src_line, hipStream_t st) {
-  hipLaunchKernelGGL(k_fit_place, dim3((unsigned)f.per_iteration, (unsigned)f.S), dim3(FIT_THREADS), 0, st, f,
-                     src_line);
+  const dim3 grid((unsigned)f.per_iteration, (unsigned)f.S);
+  if (f.tile == FIT_WIDE_TILE)
+    hipLaunchKernelGGL(k_fit_place<FIT_WIDE_THREADS>, grid, dim3(FIT_WIDE_THREADS), 0, st, f, src_line);
+  else
+    hipLaunchKernelGGL(k_fit_place<FIT_THREADS>, grid, dim3(FIT_THREADS), 0, st, f, src_line);
 }
 dim3 fit_grid(const Fit& f) { return dim3((unsigned)(ceil_div(f.buckets, 8) * 8)); }
 

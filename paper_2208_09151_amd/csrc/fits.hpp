@@ -5,7 +5,7 @@
 // accesses of a row, so the ids are only dealt to buckets, 2^shift neighbouring ids each, small enough for a bitmap
 // and the lines of a bucket's rows in LDS:
 //   k_fit_sample how full the fullest bucket is, from some of the accesses: where the ids crowd, not this way
-//   k_fit_deal   a block per tile of FIT_TILE accesses of an iteration: sorts them by bucket in LDS, writes ids
+//   k_fit_deal   a block per tile of the accesses of an iteration: sorts them by bucket in LDS, writes ids
 //                and their places in the tile in that order, and the start of every bucket inside the tile
 //   k_fit_rows   a block per bucket: the bits of its ids, then the first iteration of every row (the smallest), then
 //                its rank among the bucket's rows of that iteration
@@ -39,9 +39,16 @@ constexpr int64_t FIT_GUESS_MIN = 1 << 20;             // see changeset_run
 // and 1 010).
 constexpr int64_t FIT_LOOKUP_MIN = 1 << 20, FIT_LOOKUP_NODES = 8, FIT_LOOKUP_ROWS = 1 << 21;
 
-constexpr int FIT_THREADS = 512;
+// A tile's accesses.  Wide tiles make half the shares of twice the length, and a share is a line of ids, one of places and one
+// of starts however few it holds: 33 M accesses in 1 695 buckets, shares of 4.9 and 9.8, k_fit_rows 245 -> 197 us,
+// k_fit_lines 196 -> 157, k_fit_lookup 281 -> 234 (the calls 714 -> 631 and 2 479 -> 2 436); 256 x 150 000 on 60 M nodes 726 ->
+// 615, 512 x 30 000 405 -> 359, 40 x 400 000 on 20 M 312 -> 298.  Fewer buckets have shares that fill the lanes already (1 M nodes,
+// 489 buckets, 64 x 120 000 184 and 179 us, 300 x 17 000 173 and 186), and fewer than two wide tiles to a CU leave
+// CUs without work.
+constexpr int FIT_THREADS = 512, FIT_WIDE_THREADS = 1024;
 constexpr int FIT_ITEMS = 16;
-constexpr int FIT_TILE = FIT_THREADS * FIT_ITEMS;
+constexpr int FIT_TILE = FIT_THREADS * FIT_ITEMS, FIT_WIDE_TILE = FIT_WIDE_THREADS * FIT_ITEMS;
+constexpr int64_t FIT_WIDE_MIN = 512, FIT_WIDE_BUCKETS = 1024;   // wide tiles and buckets from which they are taken
 constexpr int FIT_SHIFT_MIN = 11, FIT_SHIFT_MAX = 16;  // ids of a bucket: ranks among them have 16 bits
 constexpr int FIT_BUCKETS = 4096;                      // at most, 2^28 nodes
 constexpr int FIT_LINE_THREADS = 1024;
@@ -87,7 +94,7 @@ struct Fit {
   uint32_t* bits;          // [words] rows accessed, by id
   uint32_t* bad;           // set where an id is out of range
   int64_t num_nodes, words;
-  int32_t S, per_iteration, tiles;   // tiles of an iteration, of all
+  int32_t S, tile, per_iteration, tiles;   // accesses of a tile, tiles of an iteration, of all
   int32_t buckets, shift;
   uint32_t* sample;        // [buckets] sampled ids, zero before
   uint32_t* most;          // the fullest bucket's, zero before
@@ -159,22 +166,26 @@ inline int32_t fit_shift(int64_t num_nodes) {
 // neighbouring buckets on one XCD (blocks go to the eight XCDs in turn), as their shares share cache lines
 __device__ __forceinline__ int32_t fit_bucket() { return blockIdx.x % 8 * (gridDim.x / 8) + blockIdx.x / 8; }
 
-__global__ __launch_bounds__(FIT_THREADS) void k_fit_deal(Fit f, const int32_t* __restrict__ ids) {
+// (the places wait in registers until the ids have left LDS, so that two blocks of wide tiles, which is all waves of
+// a CU, have room side by side: 153 -> 106 us for 33 M accesses, the narrow ones 108 -> 93)
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(THREADS / 128))) void k_fit_deal(Fit f, const int32_t* __restrict__ ids) {
+  constexpr int TILE = THREADS * FIT_ITEMS;
   extern __shared__ uint32_t s_count[];              // [buckets]
-  __shared__ uint32_t s_id[FIT_TILE];
-  __shared__ uint16_t s_rank[FIT_TILE];
-  __shared__ uint32_t smem[FIT_THREADS / WAVE + 1];
+  __shared__ uint32_t s_id[TILE];                    // then the places
+  uint16_t* const s_rank = reinterpret_cast<uint16_t*>(s_id);
+  __shared__ uint32_t smem[THREADS / WAVE + 1];
   if (*f.most > f.most_allowed) return;              // (nothing writes it while this runs)
   __shared__ uint32_t s_new;
   if (threadIdx.x == 0) s_new = 0;
-  const int64_t pos = f.off[blockIdx.y] + (int64_t)blockIdx.x * FIT_TILE, left = f.off[blockIdx.y + 1] - pos;
-  const int32_t n = left < 0 ? 0 : left < FIT_TILE ? (int32_t)left : FIT_TILE;
-  for (int q = threadIdx.x; q < f.buckets; q += FIT_THREADS) s_count[q] = 0;
+  const int64_t pos = f.off[blockIdx.y] + (int64_t)blockIdx.x * TILE, left = f.off[blockIdx.y + 1] - pos;
+  const int32_t n = left < 0 ? 0 : left < TILE ? (int32_t)left : TILE;
+  for (int q = threadIdx.x; q < f.buckets; q += THREADS) s_count[q] = 0;
   __syncthreads();
   uint32_t v[FIT_ITEMS], at[FIT_ITEMS];              // at: bucket << 16 | place among the tile's ids of the bucket
 #pragma unroll
   for (int k = 0; k < FIT_ITEMS; ++k) {
-    const int32_t x = k * FIT_THREADS + threadIdx.x;
+    const int32_t x = k * THREADS + threadIdx.x;
     v[k] = x < n ? (uint32_t)ids[pos + x] : 0u;
   }
   if (f.marks) {
@@ -183,7 +194,7 @@ __global__ __launch_bounds__(FIT_THREADS) void k_fit_deal(Fit f, const int32_t* 
     for (int k = 0; k < FIT_ITEMS; ++k) {
       const uint32_t h = hash_mix(v[k]);
       old[k] = 0xFFFFFFFFu;
-      if (k * FIT_THREADS + (int32_t)threadIdx.x < n && (h & ((1u << f.mark_shift) - 1u)) == 0)
+      if (k * THREADS + (int32_t)threadIdx.x < n && (h & ((1u << f.mark_shift) - 1u)) == 0)
         old[k] = atomicOr(&f.marks[h >> (32 - FIT_MARK_LOG + 5)], 1u << fit_mark(h));
     }
 #pragma unroll
@@ -196,7 +207,7 @@ __global__ __launch_bounds__(FIT_THREADS) void k_fit_deal(Fit f, const int32_t* 
   bool together = false;
 #pragma unroll
   for (int k = 0; k < FIT_ITEMS; ++k) {
-    const bool valid = k * FIT_THREADS + (int32_t)threadIdx.x < n;
+    const bool valid = k * THREADS + (int32_t)threadIdx.x < n;
     uint32_t q = v[k] >> f.shift;
     if (valid && v[k] >= (uint64_t)f.num_nodes) *f.bad = 1;
     if (q >= (uint32_t)f.buckets) q = f.buckets - 1;   // (stays inside the arrays)
@@ -217,11 +228,11 @@ __global__ __launch_bounds__(FIT_THREADS) void k_fit_deal(Fit f, const int32_t* 
   }
   __syncthreads();
   // (buckets are at most eight to a thread)
-  const int32_t per = (f.buckets + FIT_THREADS - 1) / FIT_THREADS, q0 = threadIdx.x * per;
+  const int32_t per = (f.buckets + THREADS - 1) / THREADS, q0 = threadIdx.x * per;
   uint32_t mine = 0;
   for (int32_t q = q0; q < q0 + per && q < f.buckets; ++q) mine += s_count[q];
   uint32_t total;
-  uint32_t run = block_exclusive_scan<uint32_t, FIT_THREADS>(mine, smem, total);
+  uint32_t run = block_exclusive_scan<uint32_t, THREADS>(mine, smem, total);
   uint16_t* const start = f.start + ((int64_t)blockIdx.y * f.per_iteration + blockIdx.x) * (f.buckets + 1);
   for (int32_t q = q0; q < q0 + per && q < f.buckets; ++q) {
     const uint32_t c = s_count[q];
@@ -229,23 +240,25 @@ __global__ __launch_bounds__(FIT_THREADS) void k_fit_deal(Fit f, const int32_t* 
     run += c;
   }
   __syncthreads();
-  for (int q = threadIdx.x; q < f.buckets; q += FIT_THREADS) start[q] = (uint16_t)s_count[q];
+  for (int q = threadIdx.x; q < f.buckets; q += THREADS) start[q] = (uint16_t)s_count[q];
   if (threadIdx.x == 0) {
     start[f.buckets] = (uint16_t)total;
     if (s_new) atomicAdd(f.marked, s_new);
   }
 #pragma unroll
   for (int k = 0; k < FIT_ITEMS; ++k) {
-    if (k * FIT_THREADS + (int32_t)threadIdx.x >= n) continue;
-    const uint32_t x = s_count[at[k] >> 16] + (at[k] & 0xFFFFu);
-    s_id[x] = v[k];
-    s_rank[x] = (uint16_t)(k * FIT_THREADS + threadIdx.x);
+    if (k * THREADS + (int32_t)threadIdx.x >= n) continue;
+    at[k] = s_count[at[k] >> 16] + (at[k] & 0xFFFFu);
+    s_id[at[k]] = v[k];
   }
   __syncthreads();
-  for (int32_t x = threadIdx.x; x < n; x += FIT_THREADS) {
-    f.ids[pos + x] = s_id[x];
-    f.rank[pos + x] = s_rank[x];
-  }
+  for (int32_t x = threadIdx.x; x < n; x += THREADS) f.ids[pos + x] = s_id[x];
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < FIT_ITEMS; ++k)
+    if (k * THREADS + (int32_t)threadIdx.x < n) s_rank[at[k]] = (uint16_t)(k * THREADS + threadIdx.x);
+  __syncthreads();
+  for (int32_t x = threadIdx.x; x < n; x += THREADS) f.rank[pos + x] = s_rank[x];
 }
 
 // What the two kernels that take a bucket each have in LDS.
@@ -299,7 +312,7 @@ __device__ __forceinline__ void fit_shares(const Fit& f, int32_t q, const FitLds
       const uint16_t* start = f.start + (int64_t)t * (f.buckets + 1) + q;
       const uint32_t lo = start[0], hi = start[1];
       const int32_t i = t / f.per_iteration;
-      at[h] = (uint32_t)f.off[i] + (uint32_t)((t - i * f.per_iteration) * FIT_TILE) + lo;
+      at[h] = (uint32_t)f.off[i] + (uint32_t)((t - i * f.per_iteration) * f.tile) + lo;
       share[h] = (hi - lo) | (uint32_t)i << 16;
     }
   };
@@ -546,14 +559,16 @@ __global__ __launch_bounds__(FIT_LINE_THREADS) __attribute__((amdgpu_waves_per_e
   }
 }
 
-__global__ __launch_bounds__(FIT_THREADS) void k_fit_place(Fit f, int32_t* __restrict__ src_line) {
-  __shared__ uint32_t s_line[FIT_TILE];
-  const int64_t pos = f.off[blockIdx.y] + (int64_t)blockIdx.x * FIT_TILE, left = f.off[blockIdx.y + 1] - pos;
-  const int32_t n = left < 0 ? 0 : left < FIT_TILE ? (int32_t)left : FIT_TILE;
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void k_fit_place(Fit f, int32_t* __restrict__ src_line) {
+  constexpr int TILE = THREADS * FIT_ITEMS;
+  __shared__ uint32_t s_line[TILE];
+  const int64_t pos = f.off[blockIdx.y] + (int64_t)blockIdx.x * TILE, left = f.off[blockIdx.y + 1] - pos;
+  const int32_t n = left < 0 ? 0 : left < TILE ? (int32_t)left : TILE;
   uint32_t line[FIT_ITEMS], rank[FIT_ITEMS];
 #pragma unroll
   for (int k = 0; k < FIT_ITEMS; ++k) {
-    const int32_t x = k * FIT_THREADS + threadIdx.x;
+    const int32_t x = k * THREADS + threadIdx.x;
     if (x < n) {
       line[k] = f.ids[pos + x];
       rank[k] = f.rank[pos + x];
@@ -561,8 +576,8 @@ __global__ __launch_bounds__(FIT_THREADS) void k_fit_place(Fit f, int32_t* __res
   }
 #pragma unroll
   for (int k = 0; k < FIT_ITEMS; ++k)
-    if (k * FIT_THREADS + (int32_t)threadIdx.x < n)
+    if (k * THREADS + (int32_t)threadIdx.x < n)
       s_line[rank[k]] = line[k] == 0xFFFFFFFFu ? line[k] : line[k] & ~FIT_DONE;   // (-1: no line; lines are below 2^31 - 1)
   __syncthreads();
-  for (int32_t x = threadIdx.x; x < n; x += FIT_THREADS) src_line[pos + x] = (int32_t)s_line[x];
+  for (int32_t x = threadIdx.x; x < n; x += THREADS) src_line[pos + x] = (int32_t)s_line[x];
 }
