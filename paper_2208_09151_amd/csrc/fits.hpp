@@ -18,9 +18,9 @@
 // bucket count together in k_fit_deal.  In order: 24 M accesses, 339 268 nodes, 143 iterations 2 714 -> 699 us a call
 // (701 through the sorted accesses), 40 M on 5.1 M nodes 4 164 -> 1 540 (1 707), 72 560 on 49 M nodes in 2
 // iterations 1 772 -> 365; in no order, 10 M on 11 M nodes, 303 and 303.
-// 33 M accesses, 9 M rows of 111 M nodes, 200 iterations: k_fit_sample 7, k_fit_deal 85 us (4 bytes read
-// and 6 written per access, 3.9 TB/s), k_fit_rows 253 and k_fit_lines 191 (7.4 M shares of four or five ids, the latency of their reads),
-// k_fit_place 53; 730 a call.  Through the sorted accesses 2 004: four radix passes 0.72 ms, heads 0.23, the rows' lines
+// 33 M accesses, 9 M rows of 111 M nodes, 200 iterations: k_fit_sample 8, k_fit_deal 106 us (with the marks of the guess; 78
+// without), k_fit_rows 197 and k_fit_lines 157 (3.7 M shares of ten ids, a line or two each in three arrays), k_fit_place 57; 631
+// a call.  Through the sorted accesses 2 004: four radix passes 0.72 ms, heads 0.23, the rows' lines
 // scattered to a table over all nodes and looked up there for every access 0.82 (random words).
 // (A wave per bucket that takes the iterations one after the other, without a table of first iterations: 626 us for
 // k_fit_rows, 83 000 vector instructions in a chain of 6 per CU.)
@@ -30,7 +30,7 @@
 // limit on the accesses otherwise (2 iterations of 500: 206 -> 160 us, 8 of 4 000 on 16 384 nodes 204 -> 178).
 constexpr int64_t FIT_SHARE_MIN = 1;
 constexpr int64_t FIT_GUESS_MIN = 1 << 20;             // see changeset_run
-// k_fit_lookup (33 M accesses, 9 M rows of 111 M nodes: 82 + 272 + 55 us against 626 for a random word per access):
+// k_fit_lookup (33 M accesses, 9 M rows of 111 M nodes: 78 + 234 + 57 us against 626 for a random word per access):
 // accesses, nodes to an access, beyond which few entries of a line of the table are used (carried caches,
 // calls in all: 10 M nodes, 1 M accesses 903 -> 889 us, 8.4 M 1 746 -> 1 672; 100 M nodes, 2 M 892 and 917, 8.4 M
 // 2 018 and 2 013, 17 M 5 427 -> 5 382), and rows, whose entries are more than an L2 holds (in no order 2.1 M rows,
