@@ -1505,43 +1505,54 @@ struct Plan {
 // start state does not hold the row, that access misses, and it is an insertion if the run
 // goes on.  Misses per iteration go to miss_count, insertions per iteration to
 // cs_offsets[i + 1] (scanned afterwards) and to the bitmap over positions.
-__global__ __launch_bounds__(TB) void k_plan_heads(const uint64_t* __restrict__ sorted, int64_t n,
-                                                   const int64_t* __restrict__ off, int32_t S,
-                                                   const uint32_t* __restrict__ held,
-                                                   int32_t* __restrict__ addr,
-                                                   uint32_t* __restrict__ ins_bits,
-                                                   unsigned long long* __restrict__ miss_count,
-                                                   unsigned long long* __restrict__ cs_offsets) {
+// (Large blocks, two to a CU: every block adds its counts to the same few lines in the end, 0.2 G/s for each of them.  A wave
+// takes LOOK_ITEMS * 64 consecutive pairs and passes ids on to the neighbours.  33 M pairs, 200 iterations: 1 024 blocks
+// of 256, each pair read three times, 170 us, this 146)
+constexpr int64_t PLAN_HEADS_TILE = BIG * LOOK_ITEMS, PLAN_HEADS_BLOCKS = 512;
+__global__ __launch_bounds__(BIG) void k_plan_heads(const uint64_t* __restrict__ sorted, int64_t n,
+                                                    const int64_t* __restrict__ off, int32_t S,
+                                                    const uint32_t* __restrict__ held,
+                                                    int32_t* __restrict__ addr,
+                                                    uint32_t* __restrict__ ins_bits,
+                                                    unsigned long long* __restrict__ miss_count,
+                                                    unsigned long long* __restrict__ cs_offsets) {
   extern __shared__ int32_t lds_plan[];   // offsets [S+1], misses [S], insertions [S]
   int32_t* lds_off = lds_plan;
   uint32_t* h_miss = reinterpret_cast<uint32_t*>(lds_plan + S + 1);
   uint32_t* h_ins = h_miss + S;
-  for (int j = threadIdx.x; j < 2 * S; j += TB) h_miss[j] = 0;
+  for (int j = threadIdx.x; j < 2 * S; j += BIG) h_miss[j] = 0;
   load_offsets(lds_off, off, S);
-  const int64_t tiles = (n + LOOK_TILE - 1) / LOOK_TILE;
-  for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-    const int64_t base = tile * LOOK_TILE;
-    // pair, left neighbour and right neighbour of all items first, then the words that say which rows are
-    // held, so that the reads of a kind are in flight together (33 M pairs: with a wait for every such word,
-    // inside a branch, 270 us, 147 this way)
-    uint64_t here[LOOK_ITEMS];
+  const int lane = lane_id();
+  for (int64_t base = blockIdx.x * PLAN_HEADS_TILE + threadIdx.x / WAVE * (WAVE * LOOK_ITEMS); base < n;
+       base += gridDim.x * PLAN_HEADS_TILE) {     // uniform over the wave
+    // all pairs first, then the words that say which rows are held, so that the reads of a kind are in flight
+    // together (with a wait for every such word, inside a branch, 270 us for 33 M pairs instead of 147)
+    uint64_t here[LOOK_ITEMS + 1];
+#pragma unroll
+    for (int i = 0; i <= LOOK_ITEMS; ++i) {
+      const int64_t j = base + i * WAVE + (i < LOOK_ITEMS ? lane : 0);
+      here[i] = sorted[j < n ? j : n - 1];
+    }
+    uint32_t before = (uint32_t)(sorted[base > 0 ? base - 1 : 0] >> 32);
     uint32_t word[LOOK_ITEMS], head = 0, more = 0;   // bit i: item i
 #pragma unroll
     for (int i = 0; i < LOOK_ITEMS; ++i) {
-      const int64_t j = base + i * TB + threadIdx.x;
-      here[i] = j < n ? sorted[j] : ~0ull;
-      const uint64_t left = j > 0 && j < n ? sorted[j - 1] : ~0ull, right = j + 1 < n ? sorted[j + 1] : ~0ull;
+      const int64_t j = base + i * WAVE + lane;
       const uint32_t v = (uint32_t)(here[i] >> 32);
-      head |= (j < n && (uint32_t)(left >> 32) != v ? 1u : 0u) << i;
-      more |= (j < n && (uint32_t)(right >> 32) == v ? 1u : 0u) << i;
+      uint32_t left = from_left(v), right = from_right(v);
+      const uint32_t next = of_lane((uint32_t)(here[i + 1] >> 32), 0);
+      if (lane == 0) left = before;
+      if (lane == WAVE - 1) right = next;
+      before = of_lane(v, WAVE - 1);
+      head |= (j < n && (j == 0 || left != v) ? 1u : 0u) << i;
+      more |= (j + 1 < n && right == v ? 1u : 0u) << i;
     }
 #pragma unroll
-    for (int i = 0; i < LOOK_ITEMS; ++i)
-      word[i] = head >> i & 1u ? held[(uint32_t)(here[i] >> 32) >> 5] : ~0u;
+    for (int i = 0; i < LOOK_ITEMS; ++i) word[i] = held[head >> i & 1u ? (uint32_t)(here[i] >> 32) >> 5 : 0u];
 #pragma unroll
     for (int i = 0; i < LOOK_ITEMS; ++i) {
       const uint32_t v = (uint32_t)(here[i] >> 32);
-      if (word[i] >> (v & 31) & 1u) continue;        // not the head of a run, or held
+      if (!(head >> i & 1u) || (word[i] >> (v & 31) & 1u)) continue;   // not the head of a run, or held
       addr[v] = -1;                       // (until it is inserted, if it is)
       const int32_t p = (int32_t)(uint32_t)here[i];
       const int32_t it = iter_of(lds_off, S, p);
@@ -1553,7 +1564,7 @@ __global__ __launch_bounds__(TB) void k_plan_heads(const uint64_t* __restrict__ 
     }
   }
   __syncthreads();
-  for (int j = threadIdx.x; j < S; j += TB) {
+  for (int j = threadIdx.x; j < S; j += BIG) {
     if (h_miss[j]) atomicAdd(&miss_count[j], (unsigned long long)h_miss[j]);
     if (h_ins[j]) atomicAdd(&cs_offsets[j + 1], (unsigned long long)h_ins[j]);
   }
@@ -2961,8 +2972,8 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
     GINEX_HIP(zero_async(Zeros().add(pl.ins_bits, pl.ins_words).add(pl.arr_off, S + 2)
                              .add(pl.cand_dead, PLAN_CAND_WORDS).add(pl.scalars + PLAN_FULLEST, 1), st));
     {
-      int64_t blocks = w.look_tiles < 1024 ? w.look_tiles : 1024;
-      hipLaunchKernelGGL(k_plan_heads, dim3((unsigned)blocks), dim3(TB),
+      const int64_t blocks = std::min(ceil_div(total, PLAN_HEADS_TILE), PLAN_HEADS_BLOCKS);
+      hipLaunchKernelGGL(k_plan_heads, dim3((unsigned)blocks), dim3(BIG),
                          sizeof(int32_t) * (3 * (size_t)S + 1), st, sorted, total, w.d_offsets, S,
                          held_bits, state.addr, pl.ins_bits, (unsigned long long*)miss_count,
                          (unsigned long long*)cs_offsets);
