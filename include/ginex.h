@@ -35,6 +35,9 @@
  *                             the id bitmap
  *      GINEX_PLANNED=0/2      a carried cache that holds the whole superbatch: as any other cache /
  *                             the three-launch steps also where the replay would do
+ *      GINEX_MOVE_POLLS=n     the blocks that find all iterations' lines in one launch wait for each other
+ *                             for n reads at most; 0: a launch per iteration
+ *      GINEX_MOVE_STOP=t      they give up in iteration t, and the call goes on with a launch per iteration
  */
 #ifndef GINEX_H
 #define GINEX_H
@@ -235,7 +238,8 @@ int32_t ginex_changeset_noalloc(
  * next accessed iteration "never" and is evicted first (larger id first).  The recurrence,
  * the lists and their order are those of ginex_changeset.  final_ids (device, [cap], may be
  * NULL) receives the row of every line after the last iteration: the start_ids of the next
- * superbatch.  No cache initialization is needed between the two superbatches.
+ * superbatch.  It may be start_ids itself, which a call that returns GINEX_OK then leaves
+ * overwritten.  No cache initialization is needed between the two superbatches.
  * When the cache also has a line for every distinct row of the superbatch, no iteration
  * evicts a row that is still needed: hits, misses and insertions are known up front and only
  * the choice of the evicted rows follows the iterations, replayed by one workgroup or, for

@@ -2432,10 +2432,11 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
     moves.out_ids = out_ids;
     moves.src_line = src_line;
     move_lines_async(state, moves, w.d_offsets, cs_offsets, st);
+    if (final_ids) final_lines_async(state, final_ids, moves.gave_up, st);
     GINEX_LAUNCH_CHECK();
     uint32_t gave_up = 1;
     back.get(&gave_up, moves.gave_up);
-    if (int32_t rc = finish()) return rc;
+    GINEX_HIP(back.wait(st));
     if (!gave_up) return GINEX_OK;
     hipLaunchKernelGGL(k_start_lines, dim3((unsigned)ceil_div(std::max(state.cap, total), TB)), dim3(TB), 0, st, state,
                        start, total, src_line);
@@ -2711,7 +2712,7 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
     for (int32_t i = 0; i < S; ++i) init_ready[i] = start_ids ? cap : 0;
   if (total == 0) {
     say("nothing is accessed");
-    if (start_ids && final_ids)
+    if (start_ids && final_ids && final_ids != start_ids)
       GINEX_HIP(hipMemcpyAsync(final_ids, start_ids, sizeof(int32_t) * cap,
                                hipMemcpyDeviceToDevice, st));
     GINEX_HIP(hipStreamSynchronize(st));
@@ -3141,9 +3142,8 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
                              pl.ins_bits, pl.ins_words, src_line);
         GINEX_LAUNCH_CHECK();
       }
-      if (final_ids)
-        GINEX_HIP(hipMemcpyAsync(final_ids, state.res_id, sizeof(int32_t) * cap,
-                                 hipMemcpyDeviceToDevice, st));
+      if (final_ids) final_lines_async(state, final_ids, pl.scalars + PLAN_FAILED, st);
+      GINEX_LAUNCH_CHECK();
       int64_t failed[2] = {0, 0};
       back.get(failed, pl.scalars + PLAN_FAILED, 2);
       GINEX_HIP(back.wait(st));

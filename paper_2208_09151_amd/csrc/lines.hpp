@@ -39,6 +39,7 @@ constexpr int MOVE_POLLS = 1 << 13;           // (a read takes about a microseco
 constexpr int MOVE_WORDS_MAX = 35;            // words of two lines a thread has in LDS, at most (140 KB)
 constexpr int64_t MOVE_CAP_MAX = (int64_t)MOVE_BLOCKS * MOVE_THREADS * 2 * MOVE_WORDS_MAX;
 constexpr uint32_t MOVE_GAVE_UP = 0xFFFFFFFFu;
+constexpr int FINAL_ITEMS = 8;
 constexpr int MOVE_TAG = 18;                  // bits for the lines of a block; above: iteration + 1, at most 2 049
 static_assert(MOVE_THREADS * 2 * MOVE_WORDS_MAX < 1 << MOVE_TAG && STATIC_S_MAX < 1 << (31 - MOVE_TAG), "one word");
 
@@ -49,6 +50,7 @@ struct Moves {
   int64_t per;                 // lines of a block's stretch
   uint64_t per_block;          // 2^32 / blocks, rounded up: n accesses are at most n * per_block / 2^32 to a block
   int32_t polls;
+  int32_t stop;                // iteration in which a block gives up whatever it reads; -1: none
   const uint32_t* leave_start;               // iteration that gives a line of the start state up, STAYS
   const uint64_t* leave_ins;                 // records of the insertions
   const int32_t *ids, *in_ids;
@@ -191,8 +193,9 @@ __global__ __launch_bounds__(MOVE_THREADS) void k_move_lines(State st, Moves m, 
     if (chain) {
       uint32_t w = 0;
       bool here = (int32_t)threadIdx.x >= blocks;
-      int polls = m.polls;
-      while (true) {
+      int polls = t == m.stop && me == blocks / 2 ? -1 : m.polls;
+      if (polls < 0) s_stop = 1;
+      while (polls >= 0) {
         if (!here) {
           w = agent_load(&words[threadIdx.x]);
           here = w >> MOVE_TAG == (uint32_t)(t + 1);
@@ -269,6 +272,25 @@ __global__ __launch_bounds__(MOVE_THREADS) void k_move_lines(State st, Moves m, 
   }
 }
 
+// The rows of the final state to the caller, but not where the call starts over: he may have given the array of the start
+// state for them.
+__global__ __launch_bounds__(TB) void k_final_lines(const int32_t* __restrict__ res_id, int64_t cap,
+                                                    int32_t* __restrict__ final_ids,
+                                                    const uint32_t* __restrict__ gave_up) {
+  if (*gave_up) return;
+  const int64_t base = (int64_t)blockIdx.x * (TB * FINAL_ITEMS) + threadIdx.x;
+  int32_t v[FINAL_ITEMS];
+#pragma unroll
+  for (int k = 0; k < FINAL_ITEMS; ++k) v[k] = res_id[base + k * TB < cap ? base + k * TB : cap - 1];
+#pragma unroll
+  for (int k = 0; k < FINAL_ITEMS; ++k)
+    if (base + k * TB < cap) final_ids[base + k * TB] = v[k];
+}
+void final_lines_async(const State& state, int32_t* final_ids, const void* gave_up, hipStream_t st) {
+  hipLaunchKernelGGL(k_final_lines, dim3((unsigned)ceil_div(state.cap, TB * FINAL_ITEMS)), dim3(TB), 0, st, state.res_id,
+                     state.cap, final_ids, static_cast<const uint32_t*>(gave_up));
+}
+
 // the rows and lines of the start state again, and what is to be looked up, for the launches per iteration
 __global__ __launch_bounds__(TB) void k_start_lines(State st, const int32_t* __restrict__ start, int64_t total,
                                                     int32_t* __restrict__ src_line) {
@@ -282,10 +304,12 @@ __global__ __launch_bounds__(TB) void k_start_lines(State st, const int32_t* __r
 }
 
 // The blocks and their stretches; none for more lines than the blocks' LDS has room for.
-// GINEX_MOVE_POLLS: another bound of the wait, 0 for none of this.
+// GINEX_MOVE_POLLS: another bound of the wait, 0 for none of this; GINEX_MOVE_STOP: the iteration in which they give up.
 int32_t moves_shape(const State& state, int64_t longest, Moves* m) {
   const char* polls = getenv("GINEX_MOVE_POLLS");
   m->polls = polls ? atoi(polls) : MOVE_POLLS;
+  const char* stop = getenv("GINEX_MOVE_STOP");
+  m->stop = stop ? atoi(stop) : -1;
   int device = 0, cus = 0;
   GINEX_HIP(hipGetDevice(&device));
   GINEX_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));

@@ -8,7 +8,7 @@ import torch
 
 import oracle
 
-from test_gpu_parity import check_changeset, dev, ginex  # noqa: F401
+from test_gpu_parity import check_changeset, check_resumed, dev, ginex  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -80,3 +80,39 @@ def test_most_iterations(ginex, monkeypatch):  # noqa: F811
     monkeypatch.setenv("GINEX_STATIC_THRESHOLDS", "1")
     for policy, ref in (("belady", oracle.changeset), ("lru", oracle.changeset_lru)):
         check_changeset(ginex.changeset(n, dev(ids), off, cap, policy=policy), ref(n, ids, off, cap), (n, ids, off))
+
+
+# The rows left behind may take the place of those given (final_ids == start_ids), whichever way the lines are found and
+# whenever it is given up
+@pytest.mark.parametrize("cap,holds_all", [(700, False), (3000, False), (4600, True)])
+@pytest.mark.parametrize("planned", ["0", "1", "2"])
+@pytest.mark.parametrize("stop", [None, 0, 1, 6, 11])
+def test_final_rows_in_the_place_of_the_first(ginex, cap, holds_all, planned, stop, monkeypatch):  # noqa: F811
+    from paper_2208_09151_amd import api
+    lib, n, S = api._lib.load(), 5000, 12
+    rng = np.random.default_rng(cap)
+    # (rows of few ids, so that some are accessed again and again)
+    parts = [rng.permutation(np.unique((rng.random(900) ** 3 * n).astype(np.int32)))[:600] for _ in range(S)]
+    host = np.concatenate(parts).astype(np.int32)
+    off = np.cumsum([0] + [len(p) for p in parts]).astype(np.int64)
+    start = rng.permutation(n)[:cap].astype(np.int32)
+    assert (len(np.unique(host)) <= cap) == holds_all
+    monkeypatch.setenv("GINEX_STATIC_THRESHOLDS", "1")
+    monkeypatch.setenv("GINEX_PLANNED", planned)
+    if stop is not None:
+        monkeypatch.setenv("GINEX_MOVE_STOP", str(stop))
+    ref = oracle.changeset_resume(n, host, off, cap, start)
+    ids, rows, total = dev(host), dev(start), len(host)
+    lists = torch.empty(4, total, dtype=torch.int32, device="cuda")
+    counts = torch.empty(2 * S + 1, dtype=torch.int64, device="cuda")
+    changes = np.zeros(1, dtype=np.int64)
+    ws = torch.empty(lib.ginex_changeset_workspace_bytes(n, total, S, cap), dtype=torch.uint8, device="cuda")
+    p = api._ptr
+    assert lib.ginex_changeset_resume(n, p(ids), api._np_ptr(off), S, cap, p(rows), p(rows), p(lists[0]), p(lists[1]),
+                                      p(lists[2]), total, p(counts), p(counts[S + 1:]), p(lists[3]),
+                                      api._np_ptr(changes), p(ws), ws.numel(), api._stream()) == 0
+    m = int(changes[0])
+    assert m > 0
+    got = ginex.ChangesetResult(dev(start), lists[0, :m], lists[1, :m], lists[2, :m], counts[:S + 1].cpu().numpy(),
+                                counts[S + 1:].cpu().numpy(), np.full(S, cap, dtype=np.int64), rows, lists[3])
+    check_resumed(got, ref, (n, host, off))
