@@ -24,7 +24,8 @@
  *      GINEX_VALIDATE=1       check the documented preconditions on the device first; a fresh cache that
  *                             holds every row then goes on from the accesses sorted for that, where other
  *                             calls need no sort
- *      GINEX_TRACE=1          the changeset calls report on stderr which way they went
+ *      GINEX_TRACE=1/2        the changeset calls report on stderr which way they went / and, where rows are
+ *                             evicted that the trace decides on, how their lines were found
  *      GINEX_SAMPLER_LDS=0    all hops through hash tables in HBM, none through tables in LDS
  *      GINEX_SAMPLER_TILES=n  at most n tiles of a batch per workgroup column of the sampler
  *      GINEX_LIVE_SELECT=1    no shortcut that relies on the cache holding the whole superbatch

@@ -2219,6 +2219,12 @@ int32_t stays_cuts(const Workspace& w, const Stays& q, const int64_t* ids_offset
   return GINEX_OK;
 }
 
+// GINEX_TRACE=1: a line on stderr that says which way the call goes; 2: and another how it finds the lines
+int trace_level() {
+  const char* const env = getenv("GINEX_TRACE");
+  return env && (env[0] == '1' || env[0] == '2') ? env[0] - '0' : 0;
+}
+
 // The changesets of a full cache whose state (res_id, addr of the accessed rows, rhist and, for a
 // carried cache, dead_bits) is set up, from the node-sorted accesses (see stays.hpp).
 // `ends`: the other buffer of the sort, `rows`: a word per distinct row.  last_head: the last row of
@@ -2422,6 +2428,10 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
   GINEX_LAUNCH_CHECK();
 
   // the lines
+  auto say = [&](const char* way) {
+    if (trace_level() > 1) fprintf(stderr, "[ginex] %s: lines: %s\n", who, way);
+  };
+  say(moves.blocks > 0 ? "all iterations together" : "a launch per iteration");
   if (moves.blocks > 0) {
     moves.words = pl.cand_dead;
     moves.gave_up = pl.cand_dead + 2 * MOVE_BLOCKS;
@@ -2438,6 +2448,7 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
     back.get(&gave_up, moves.gave_up);
     GINEX_HIP(back.wait(st));
     if (!gave_up) return GINEX_OK;
+    say("given up, a launch per iteration");
     hipLaunchKernelGGL(k_start_lines, dim3((unsigned)ceil_div(std::max(state.cap, total), TB)), dim3(TB), 0, st, state,
                        start, total, src_line);
     GINEX_LAUNCH_CHECK();
@@ -2700,9 +2711,7 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
       GINEX_HIP(zero_async(z, st));
     }
   }
-  // GINEX_TRACE=1: a line on stderr that says which way the call goes
-  const char* trace_env = getenv("GINEX_TRACE");
-  const bool trace = trace_env && trace_env[0] == '1';
+  const bool trace = trace_level() > 0;
   auto say = [&](const char* way) {
     if (trace) fprintf(stderr, "[ginex] %s: %s\n", who, way);
   };

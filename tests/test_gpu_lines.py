@@ -12,6 +12,19 @@ from test_gpu_parity import check_changeset, check_resumed, dev, ginex  # noqa: 
 
 pytestmark = pytest.mark.gpu
 
+TOGETHER, LAUNCHES, GIVEN_UP = "all iterations together", "a launch per iteration", "given up, a launch per iteration"
+
+
+def found(call, monkeypatch, capfd):
+    """What the call returns, and the ways in which it says the lines were found."""
+    monkeypatch.setenv("GINEX_TRACE", "2")
+    capfd.readouterr()
+    result = call()
+    said = capfd.readouterr().err
+    monkeypatch.delenv("GINEX_TRACE")
+    return result, [line.split(": lines: ")[1] for line in said.splitlines() if ": lines: " in line]
+
+
 NAMES = ("in_ids", "out_ids", "in_positions", "src_line", "final_ids")
 
 
@@ -47,7 +60,7 @@ def test_small_caches_equal_the_oracle(ginex, policy, cap, monkeypatch):  # noqa
 @pytest.mark.parametrize("cap,length", [(2**19, 400_000), (2**19 + 2, 400_000), (3 * 2**19 + 2, 700_000),
                                         (9 * 2**19 + 2, 3_000_000), (17 * 2**19 + 2, 4_000_000),
                                         (35 * 2**19, 6_000_000), (35 * 2**19 + 1, 6_000_000)])
-def test_large_caches_equal_a_launch_per_iteration(ginex, cap, length, monkeypatch):  # noqa: F811
+def test_large_caches_equal_a_launch_per_iteration(ginex, cap, length, monkeypatch, capfd):  # noqa: F811
     S, n = 7, 2 * cap
     gen = torch.Generator(device="cuda").manual_seed(cap)
     off = np.arange(S + 1, dtype=np.int64) * length
@@ -69,6 +82,9 @@ def test_large_caches_equal_a_launch_per_iteration(ginex, cap, length, monkeypat
                 monkeypatch.delenv("GINEX_MOVE_POLLS")
             same(want, run())
             same(bare, run(False))
+        got, said = found(run, monkeypatch, capfd)
+        assert said == [LAUNCHES if cap > 35 * 2**19 else TOGETHER]
+        same(want, got)
 
 
 def test_most_iterations(ginex, monkeypatch):  # noqa: F811
@@ -116,3 +132,33 @@ def test_final_rows_in_the_place_of_the_first(ginex, cap, holds_all, planned, st
     got = ginex.ChangesetResult(dev(start), lists[0, :m], lists[1, :m], lists[2, :m], counts[:S + 1].cpu().numpy(),
                                 counts[S + 1:].cpu().numpy(), np.full(S, cap, dtype=np.int64), rows, lists[3])
     check_resumed(got, ref, (n, host, off))
+
+
+# Blocks that give up in any iteration leave rows, table and lines as they were, and the call says so
+@pytest.mark.parametrize("policy", ["belady", "lru", "resume"])
+@pytest.mark.parametrize("cap", [500, 1280, 40_000])          # one block, a few, all
+def test_given_up_in_any_iteration(ginex, policy, cap, monkeypatch, capfd):  # noqa: F811
+    rng = np.random.default_rng(cap)
+    S, n = 10, 3 * cap
+    parts = [rng.permutation(n)[:rng.integers(cap // 2, cap + 1)] for _ in range(S)]
+    parts[5] = parts[4][::-1].copy()        # every row again in the iteration behind
+    ids = np.concatenate(parts).astype(np.int32)
+    off = np.cumsum([0] + [len(p) for p in parts]).astype(np.int64)
+    start = rng.permutation(n)[:cap].astype(np.int32)
+    monkeypatch.setenv("GINEX_STATIC_THRESHOLDS", "1")
+    if policy == "resume":
+        ref = oracle.changeset_resume(n, ids, off, cap, start)
+        run, check = lambda: ginex.changeset_resume(n, dev(ids), off, dev(start)), check_resumed
+    else:
+        ref = (oracle.changeset if policy == "belady" else oracle.changeset_lru)(n, ids, off, cap)
+        run, check = lambda: ginex.changeset(n, dev(ids), off, cap, policy=policy), check_changeset
+    for stop, polls, expected in [(None, None, [TOGETHER]), (None, "0", [LAUNCHES])] + \
+            [(t, None, [TOGETHER, GIVEN_UP]) for t in (0, 1, S // 2, S - 2, S - 1)] + [(S, None, [TOGETHER])]:
+        for name, value in (("GINEX_MOVE_STOP", stop), ("GINEX_MOVE_POLLS", polls)):
+            if value is None:
+                monkeypatch.delenv(name, raising=False)
+            else:
+                monkeypatch.setenv(name, str(value))
+        got, said = found(run, monkeypatch, capfd)
+        assert said == expected, (stop, polls, said)
+        check(got, ref, (n, ids, off))
