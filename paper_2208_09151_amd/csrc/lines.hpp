@@ -37,7 +37,12 @@ constexpr int MOVE_ITEMS = 5;                 // lookups in flight to a thread
 constexpr int64_t MOVE_LINES = 512;           // of a block, where there are few
 constexpr int MOVE_POLLS = 1 << 13;           // (a read takes about a microsecond)
 constexpr int MOVE_WORDS_MAX = 35;            // words of two lines a thread has in LDS, at most (140 KB)
-constexpr int64_t MOVE_CAP_MAX = (int64_t)MOVE_BLOCKS * MOVE_THREADS * 2 * MOVE_WORDS_MAX;
+// ... and for LRU, which gives lines up in the order in which they were taken, so that an iteration's lie in the stretches of
+// a few blocks, and the larger these are the more one block hands over.  Moved and by a launch per iteration, 300 iterations
+// of 100 000 accesses, 25 000 lines each: of 3 M lines 4 477 and 5 435 us a call, 4 M 5 201 and 5 621, 4.7 M 5 996 and 5 674, 6 M 7 209
+// and 6 032, 8 M 9 382 and 6 496; of 300 000 accesses, 70 000 lines: 4.7 M 3 809 and 4 008, 6 M 4 313 and 4 093.  (Belady's
+// are spread: 10 M rows in a window that moves, 200 iterations of 200 000, 4 897 and 5 824.)
+constexpr int MOVE_LRU_WORDS = 9;
 constexpr uint32_t MOVE_GAVE_UP = 0xFFFFFFFFu;
 constexpr int FINAL_ITEMS = 8;
 constexpr int MOVE_TAG = 18;                  // bits for the lines of a block; above: iteration + 1, at most 2 049
@@ -303,7 +308,7 @@ __global__ __launch_bounds__(TB) void k_start_lines(State st, const int32_t* __r
   if (src_line && l < total && src_line[l] == HANDED_OVER) src_line[l] = LOOK_UP;
 }
 
-// The blocks and their stretches; none for more lines than the blocks' LDS has room for.
+// The blocks and their stretches; none for more lines than the blocks' LDS has room for, or pays for.
 // GINEX_MOVE_POLLS: another bound of the wait, 0 for none of this; GINEX_MOVE_STOP: the iteration in which they give up.
 int32_t moves_shape(const State& state, int64_t longest, Moves* m) {
   const char* polls = getenv("GINEX_MOVE_POLLS");
@@ -317,7 +322,8 @@ int32_t moves_shape(const State& state, int64_t longest, Moves* m) {
   blocks = std::max<int64_t>(1, std::min<int64_t>(blocks, std::min(cus, MOVE_BLOCKS)));
   m->per = (ceil_div(state.cap, blocks) + 1) / 2 * 2;
   m->per_block = (uint64_t)ceil_div(int64_t(1) << 32, blocks);
-  m->blocks = m->polls > 0 && m->per <= MOVE_THREADS * 2 * MOVE_WORDS_MAX ? (int32_t)blocks : 0;
+  const int64_t words = state.lru ? MOVE_LRU_WORDS : MOVE_WORDS_MAX;
+  m->blocks = m->polls > 0 && m->per <= MOVE_THREADS * 2 * words ? (int32_t)blocks : 0;
   return GINEX_OK;
 }
 

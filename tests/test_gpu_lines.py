@@ -56,9 +56,9 @@ def test_small_caches_equal_the_oracle(ginex, policy, cap, monkeypatch):  # noqa
 
 
 # the lines up to which a thread has 1, 3, 9, 17 and 35 words of LDS, and one block's more, of which the last goes back
-# to a launch per iteration; iterations of up to 1.2 M accesses are looked up in one go, longer ones in several
+# to a launch per iteration, LRU's behind 9 words; iterations of up to 1.2 M accesses are looked up in one go, longer ones in several
 @pytest.mark.parametrize("cap,length", [(2**19, 400_000), (2**19 + 2, 400_000), (3 * 2**19 + 2, 700_000),
-                                        (9 * 2**19 + 2, 3_000_000), (17 * 2**19 + 2, 4_000_000),
+                                        (9 * 2**19, 3_000_000), (9 * 2**19 + 2, 3_000_000), (17 * 2**19 + 2, 4_000_000),
                                         (35 * 2**19, 6_000_000), (35 * 2**19 + 1, 6_000_000)])
 def test_large_caches_equal_a_launch_per_iteration(ginex, cap, length, monkeypatch, capfd):  # noqa: F811
     S, n = 7, 2 * cap
@@ -69,9 +69,9 @@ def test_large_caches_equal_a_launch_per_iteration(ginex, cap, length, monkeypat
     start = torch.randperm(n, generator=gen, device="cuda")[:cap].int()
     monkeypatch.setenv("GINEX_STATIC_THRESHOLDS", "1")
     monkeypatch.setenv("GINEX_PLANNED", "0")
-    for run in (lambda lines=True: ginex.changeset(n, ids, off, cap, with_lines=lines),
-                lambda lines=True: ginex.changeset(n, ids, off, cap, policy="lru", with_lines=lines),
-                lambda lines=True: ginex.changeset_resume(n, ids, off, start, with_lines=lines)):
+    for most, run in ((35, lambda lines=True: ginex.changeset(n, ids, off, cap, with_lines=lines)),
+                      (9, lambda lines=True: ginex.changeset(n, ids, off, cap, policy="lru", with_lines=lines)),
+                      (35, lambda lines=True: ginex.changeset_resume(n, ids, off, start, with_lines=lines))):
         monkeypatch.setenv("GINEX_MOVE_POLLS", "0")
         want, bare = run(), run(False)
         assert want.cs_offsets[-1] > 0
@@ -83,7 +83,7 @@ def test_large_caches_equal_a_launch_per_iteration(ginex, cap, length, monkeypat
             same(want, run())
             same(bare, run(False))
         got, said = found(run, monkeypatch, capfd)
-        assert said == [LAUNCHES if cap > 35 * 2**19 else TOGETHER]
+        assert said == [LAUNCHES if cap > most * 2**19 else TOGETHER]
         same(want, got)
 
 
