@@ -24,6 +24,7 @@
 //   Both ways also serve a superbatch that resumes from the cache state of the previous one
 //   (C_0 given instead of computed, Belady only); LRU has other keys.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -2243,6 +2244,9 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
   const size_t off_lds = sizeof(int32_t) * (S + 1);
   const bool lru = state.lru;
   uint64_t* const limits = reinterpret_cast<uint64_t*>(w.cuts);   // (there are no cuts then)
+  int device = 0;
+  GINEX_HIP(hipGetDevice(&device));
+  MoveTurn turn(device);
   Stays q{ends, w.d_offsets, ids, w.key_hists, w.cuts, w.next_iter, pl.cand_id, limits, S,
           bits_for(state.num_nodes)};
   int64_t longest = 0;
@@ -2411,7 +2415,7 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
   int levels = 1;
   while ((1 << levels) <= S) ++levels;
   Moves moves{};
-  if (int32_t rc = moves_shape(state, longest, &moves)) return rc;
+  if (int32_t rc = moves_shape(state, longest, device, &turn, &moves)) return rc;
   int32_t* const hand_over = moves.blocks > 0 ? src_line : nullptr;
   const dim3 walk_grid((unsigned)ceil_div(total, WALK_TILE));
   if (lru)
@@ -2447,6 +2451,7 @@ int32_t stays_run(const char* who, const Workspace& w, const uint64_t* sorted, u
     uint32_t gave_up = 1;
     back.get(&gave_up, moves.gave_up);
     GINEX_HIP(back.wait(st));
+    turn.give();
     if (!gave_up) return GINEX_OK;
     say("given up, a launch per iteration");
     hipLaunchKernelGGL(k_start_lines, dim3((unsigned)ceil_div(std::max(state.cap, total), TB)), dim3(TB), 0, st, state,

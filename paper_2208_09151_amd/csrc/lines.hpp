@@ -17,9 +17,17 @@
 //   * nothing of t + 1 is written yet, and t itself does not write the entry of a row that hits
 // The words sit in two sets in turn: a block publishes t + 2 after all have published t + 1, so after all have read t.
 //
-// The blocks wait for each other, so all of them have to run.  Nothing guarantees it (other kernels may hold the
-// CUs, other calls' blocks of this kernel), so the wait is bounded: after MOVE_POLLS reads a block gives up and says
-// so in its words, which ends the others' waits too, and the host starts over with a launch per iteration (k_step_lines).
+// The blocks wait for each other, so all of them have to run.  One call of the process at a time has them on a GPU, and only
+// where MOVE_CALLS changesets at most are worked on: two calls' blocks with part of the CUs each would wait in vain, and blocks
+// that wait keep many calls' kernels from the CUs.  The others take a launch per iteration (k_step_lines).  Still nothing
+// guarantees it (other kernels may hold the CUs, other processes' blocks), so the wait is bounded: after MOVE_POLLS reads a block
+// gives up and says so in its words, which ends the others' waits too, and the host starts over with the launches.  In the first
+// iteration, where blocks that do not all run fail to meet, the bound is about what the iterations save.
+// A read takes 0.2 us; the first wait 2 us, beside kernels of other streams (gathers, copies, products of 8 192^3) 100 us in 99
+// of 100 calls, and 751 once.  10 M nodes, 100 iterations of 100 000, 300 000 lines, two, three, four and six threads that call all
+// the time: 2 680, 3 650, 4 490 and 6 660 us a call (four, if one of them went this way, 4 680; with no turns 6 040, a third of
+// the calls given up; all by launches 2 860, 3 615, 4 415 and 6 660); three processes 3 750 (with one bound for all waits 3 900, all
+// by launches 3 510).
 //
 // An iteration takes 2.6 us without lookups (the words' way to memory and back 1.3, records and LDS), 4.4 with 96 000 of
 // them from a table of 444 MB, 17.6 with 670 000 (two thirds of it random words at 59 G/s, the chip's rate); a launch
@@ -35,7 +43,10 @@ constexpr int MOVE_BLOCKS = MOVE_CHAIN;       // at most: a word to a thread
 constexpr int MOVE_LIST = 2048;               // lines handed over at a time
 constexpr int MOVE_ITEMS = 5;                 // lookups in flight to a thread
 constexpr int64_t MOVE_LINES = 512;           // of a block, where there are few
-constexpr int MOVE_POLLS = 1 << 13;           // (a read takes about a microsecond)
+constexpr int MOVE_POLLS = 1 << 13;           // reads of a wait; of the first one
+constexpr int MOVE_MEET_MIN = 1 << 10, MOVE_MEET_SAVED = 16;   // at least, and for each iteration
+constexpr int MOVE_DEVICES = 64;              // GPUs that calls take turns on; not this way on others
+constexpr int MOVE_CALLS = 3;                 // calls at once on a GPU up to which one of them goes this way
 constexpr int MOVE_WORDS_MAX = 35;            // words of two lines a thread has in LDS, at most (140 KB)
 // ... and for LRU, which gives lines up in the order in which they were taken, so that an iteration's lie in the stretches of
 // a few blocks, and the larger these are the more one block hands over.  Moved and by a launch per iteration, 300 iterations
@@ -54,7 +65,7 @@ struct Moves {
   uint32_t* gave_up;           // zero
   int64_t per;                 // lines of a block's stretch
   uint64_t per_block;          // 2^32 / blocks, rounded up: n accesses are at most n * per_block / 2^32 to a block
-  int32_t polls;
+  int32_t meet, polls;         // reads of the first iteration's wait, of the others'
   int32_t stop;                // iteration in which a block gives up whatever it reads; -1: none
   const uint32_t* leave_start;               // iteration that gives a line of the start state up, STAYS
   const uint64_t* leave_ins;                 // records of the insertions
@@ -198,7 +209,7 @@ __global__ __launch_bounds__(MOVE_THREADS) void k_move_lines(State st, Moves m, 
     if (chain) {
       uint32_t w = 0;
       bool here = (int32_t)threadIdx.x >= blocks;
-      int polls = t == m.stop && me == blocks / 2 ? -1 : m.polls;
+      int polls = t == m.stop && me == blocks / 2 ? -1 : t == 0 ? m.meet : m.polls;
       if (polls < 0) s_stop = 1;
       while (polls >= 0) {
         if (!here) {
@@ -308,22 +319,56 @@ __global__ __launch_bounds__(TB) void k_start_lines(State st, const int32_t* __r
   if (src_line && l < total && src_line[l] == HANDED_OVER) src_line[l] = LOOK_UP;
 }
 
-// The blocks and their stretches; none for more lines than the blocks' LDS has room for, or pays for.
-// GINEX_MOVE_POLLS: another bound of the wait, 0 for none of this; GINEX_MOVE_STOP: the iteration in which they give up.
-int32_t moves_shape(const State& state, int64_t longest, Moves* m) {
+// A call on its GPU, and its turn to have such blocks there, from their launch until it has waited for them.
+class MoveTurn {
+ public:
+  explicit MoveTurn(int device) : on_(device >= 0 && device < MOVE_DEVICES ? &gpus()[device] : nullptr) {
+    if (on_) ++on_->calls;
+  }
+  ~MoveTurn() {
+    give();
+    if (on_) --on_->calls;
+  }
+  MoveTurn(const MoveTurn&) = delete;
+  MoveTurn& operator=(const MoveTurn&) = delete;
+  bool take() {
+    mine_ = on_ && on_->calls <= MOVE_CALLS && !on_->taken.exchange(true);
+    return mine_;
+  }
+  void give() {
+    if (mine_) on_->taken = false;
+    mine_ = false;
+  }
+
+ private:
+  struct Gpu {
+    std::atomic<int> calls{0};
+    std::atomic<bool> taken{false};
+  };
+  static Gpu* gpus() {
+    static Gpu all[MOVE_DEVICES];
+    return all;
+  }
+  Gpu* const on_;
+  bool mine_ = false;
+};
+
+// The blocks and their stretches; none for more lines than the blocks' LDS has room for, or pays for, nor in another
+// call's turn.  GINEX_MOVE_POLLS: another bound of the waits, 0 for none of this; GINEX_MOVE_STOP: the iteration in which they give up.
+int32_t moves_shape(const State& state, int64_t longest, int device, MoveTurn* turn, Moves* m) {
   const char* polls = getenv("GINEX_MOVE_POLLS");
   m->polls = polls ? atoi(polls) : MOVE_POLLS;
+  m->meet = polls ? m->polls : std::min(MOVE_POLLS, std::max(MOVE_MEET_MIN, MOVE_MEET_SAVED * state.S));
   const char* stop = getenv("GINEX_MOVE_STOP");
   m->stop = stop ? atoi(stop) : -1;
-  int device = 0, cus = 0;
-  GINEX_HIP(hipGetDevice(&device));
+  int cus = 0;
   GINEX_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));
   int64_t blocks = std::max(ceil_div(state.cap, MOVE_LINES), ceil_div(longest, MOVE_ITEMS * MOVE_LOOKUPS));
   blocks = std::max<int64_t>(1, std::min<int64_t>(blocks, std::min(cus, MOVE_BLOCKS)));
   m->per = (ceil_div(state.cap, blocks) + 1) / 2 * 2;
   m->per_block = (uint64_t)ceil_div(int64_t(1) << 32, blocks);
   const int64_t words = state.lru ? MOVE_LRU_WORDS : MOVE_WORDS_MAX;
-  m->blocks = m->polls > 0 && m->per <= MOVE_THREADS * 2 * words ? (int32_t)blocks : 0;
+  m->blocks = m->polls > 0 && m->per <= MOVE_THREADS * 2 * words && turn->take() ? (int32_t)blocks : 0;
   return GINEX_OK;
 }
 

@@ -2,6 +2,8 @@
 state and the oracle (tolerance zero): caches around the lines of a block and around what its LDS holds, iterations that
 change more lines than a block hands over at a time or access more rows than it looks up at a time, waits
 that are given up."""
+from concurrent.futures import ThreadPoolExecutor
+
 import numpy as np
 import pytest
 import torch
@@ -162,3 +164,37 @@ def test_given_up_in_any_iteration(ginex, policy, cap, monkeypatch, capfd):  # n
         got, said = found(run, monkeypatch, capfd)
         assert said == expected, (stop, polls, said)
         check(got, ref, (n, ids, off))
+
+
+# Calls of several streams at once: one of them has the blocks that wait for each other, the others a launch per iteration
+@pytest.mark.parametrize("policy", ["belady", "lru", "resume"])
+def test_calls_at_once(ginex, policy, monkeypatch, capfd):  # noqa: F811
+    n, S, length, cap, threads = 3_000_000, 60, 60_000, 200_000, 4
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    work = []
+    for _ in range(threads):
+        parts = [(torch.rand(length, generator=gen, device="cuda") ** 3 * n).int().clamp(0, n - 1).unique() for _ in range(S)]
+        parts = [p[torch.randperm(len(p), generator=gen, device="cuda")] for p in parts]
+        work.append((torch.cat(parts), np.cumsum([0] + [len(p) for p in parts]).astype(np.int64)))
+    start = torch.randperm(n, generator=gen, device="cuda")[:cap].int()
+
+    def run(k):
+        if policy == "resume":
+            return ginex.changeset_resume(n, *work[k], start)
+        return ginex.changeset(n, *work[k], cap, policy=policy)
+
+    monkeypatch.setenv("GINEX_MOVE_POLLS", "0")
+    want = [run(k) for k in range(threads)]
+    monkeypatch.setenv("GINEX_MOVE_POLLS", str(1 << 16))      # (no wait ends before the other streams' kernels do)
+    torch.cuda.synchronize()
+
+    def one(k):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(15):
+                same(want[k], run(k))
+            torch.cuda.current_stream().synchronize()
+        return True
+    with ThreadPoolExecutor(threads) as pool:
+        done, said = found(lambda: list(pool.map(one, range(threads))), monkeypatch, capfd)
+    assert all(done) and len(said) == 15 * threads
+    assert TOGETHER in said and GIVEN_UP not in said
