@@ -36,6 +36,7 @@
  *                             the id bitmap
  *      GINEX_PLANNED=0/2      a carried cache that holds the whole superbatch: as any other cache /
  *                             the three-launch steps also where the replay would do
+ *      GINEX_PLAN_STOP=t      that way gives up in iteration t, and the call starts over as any other cache's
  *      GINEX_MOVE_POLLS=n     the blocks that find all iterations' lines in one launch (of one call at a time on a
  *                             GPU) wait for each other for n reads at most; 0: a launch per iteration
  *      GINEX_MOVE_STOP=t      they give up in iteration t, and the call goes on with a launch per iteration

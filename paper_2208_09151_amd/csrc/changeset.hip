@@ -3111,9 +3111,10 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
           GINEX_LAUNCH_CHECK();
         } else {
         // the candidates numbered in id order
+        const char* const stop = getenv("GINEX_PLAN_STOP");
         const Victims victims{reinterpret_cast<int32_t*>(w.heads_b),
                               in_keys ? reinterpret_cast<uint32_t*>(state.res_next) : w.key_hists,
-                              pl.arr_cand, state.res_next, pl.arr_cur, (int32_t)parts, S};
+                              pl.arr_cand, state.res_next, pl.arr_cur, (int32_t)parts, S, stop ? atoi(stop) : -1};
         const int64_t lo_word = lo_id >> 5;
         const int64_t nwords = state.words - lo_word;
         const int64_t ctiles = ceil_div(nwords, TB);

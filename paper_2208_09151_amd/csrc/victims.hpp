@@ -33,6 +33,7 @@ struct Victims {
   int32_t* lines;       // [evictions] the lines of those
   uint32_t* fresh;      // [S] evictions of rows inserted in this call; bit 31: an inserted row is evicted again
   int32_t parts, S;
+  int32_t stop;         // iteration in which k_plan_pairs gives up whatever it reads; -1: none
 };
 constexpr uint32_t PLAN_CHAINED = 1u << 31;
 
@@ -421,9 +422,22 @@ __global__ __launch_bounds__(BIG) void k_plan_pairs(State st, Plan pl, Victims q
                                                     int32_t* __restrict__ out_ids) {
   __shared__ RankShared sh;
   __shared__ int32_t s_known[PLAN_SORT_MAX], s_come[PLAN_SORT_MAX];
-  __shared__ int32_t s_failed;
+  __shared__ int32_t s_given_up, s_failed;
   const int32_t t = blockIdx.x, first = (int32_t)cs_offsets[t], n = (int32_t)cs_offsets[t + 1] - first;
-  if (n == 0 || pl.scalars[PLAN_FAILED]) return;    // uniform
+  // (read once: other blocks of this launch may set it, and threads that read different values would part at a barrier)
+  if (threadIdx.x == 0) {
+    s_given_up = pl.scalars[PLAN_FAILED] != 0;
+    s_failed = 0;
+  }
+  __syncthreads();
+  if (n == 0 || s_given_up) return;                 // uniform
+  if (t == q.stop) {
+    if (threadIdx.x == 0) {
+      pl.scalars[PLAN_FAILED] = 3;
+      pl.scalars[PLAN_WHERE] = t;
+    }
+    return;
+  }
   const int32_t fresh = (int32_t)(q.fresh[t] & ~PLAN_CHAINED), known = n - fresh;
   int32_t cand[PLAN_EPT], line[PLAN_EPT], rank[PLAN_EPT];
 #pragma unroll
@@ -434,8 +448,6 @@ __global__ __launch_bounds__(BIG) void k_plan_pairs(State st, Plan pl, Victims q
     rank[e] = k;
   }
   if (fresh > 0) {                                  // uniform
-    if (threadIdx.x == 0) s_failed = 0;
-    __syncthreads();
     int32_t come[PLAN_EPT], among[PLAN_EPT];
 #pragma unroll
     for (int e = 0; e < PLAN_EPT; ++e) {
@@ -446,7 +458,10 @@ __global__ __launch_bounds__(BIG) void k_plan_pairs(State st, Plan pl, Victims q
     }
     __syncthreads();
     if (s_failed) {                                 // uniform
-      if (threadIdx.x == 0) pl.scalars[PLAN_FAILED] = 2;
+      if (threadIdx.x == 0) {
+        pl.scalars[PLAN_FAILED] = 2;
+        pl.scalars[PLAN_WHERE] = t;
+      }
       return;
     }
     rank_lines(sh, fresh, come, among);

@@ -1,7 +1,7 @@
 """Evictions of a carried cache that holds the superbatch, all iterations together, against the oracle and the steps on the
 bitmap in global memory (tolerance zero): rows that are inserted, die and are evicted again, each wave of them from the lines
 of the one before; candidates around the parts a wave takes; more iterations than a wave, or a block, looks at at a time;
-evictions around the number that are compared with each other directly."""
+evictions around the number that are compared with each other directly; calls that give up on the way."""
 import numpy as np
 import pytest
 
@@ -41,3 +41,32 @@ def test_rows_that_come_and_go(ginex, new, S, dead, spread, monkeypatch):  # noq
     for way in ("1", "2"):
         monkeypatch.setenv("GINEX_PLANNED", way)
         check_resumed(ginex.changeset_resume(n, dev(ids), off, dev(start)), ref, (n, ids, off))
+
+
+# The lists' last step gives up in one iteration, while the others' blocks run: the call starts over as any other cache's,
+# from the trace or with the loop, and says so
+@pytest.mark.parametrize("thresholds", ["0", "1"])
+@pytest.mark.parametrize("S", [5, 70])
+def test_given_up_in_any_iteration(ginex, S, thresholds, monkeypatch, capfd):  # noqa: F811
+    rng = np.random.default_rng(S)
+    n, new = 60_000, 300
+    order = rng.permutation(n)
+    parts = [rng.permutation(order[new * t:new * (t + 2)]) for t in range(S)]       # every row twice, then dead
+    ids = np.concatenate(parts).astype(np.int32)
+    off = np.cumsum([0] + [len(p) for p in parts]).astype(np.int64)
+    start = rng.permutation(order[new * (S + 1) - new // 2:]).astype(np.int32)[:max(new * (S + 1), 8000)]
+    ref = oracle.changeset_resume(n, ids, off, len(start), start)
+    evicting = np.nonzero(np.diff(ref["cs_offsets"]))[0]
+    monkeypatch.setenv("GINEX_STATIC_THRESHOLDS", thresholds)
+    monkeypatch.setenv("GINEX_PLANNED", "1")
+    monkeypatch.setenv("GINEX_TRACE", "1")
+    for stop in (None, *evicting[[0, 1, len(evicting) // 2, -1]]):
+        if stop is not None:
+            monkeypatch.setenv("GINEX_PLAN_STOP", str(stop))
+        capfd.readouterr()
+        check_resumed(ginex.changeset_resume(n, dev(ids), off, dev(start)), ref, (n, ids, off))
+        said = capfd.readouterr().err
+        assert "planned path\n" in said
+        assert ("gave up" in said) == (stop is not None)
+        if stop is not None:
+            assert f"gave up (reason 3, iteration {stop})" in said
