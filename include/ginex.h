@@ -7,8 +7,13 @@
  *  - Every pointer is a DEVICE pointer unless its comment says "host".  The structs
  *    themselves live in host memory; the pointers inside them follow the same rule.
  *  - The caller owns every buffer, including the workspace `ws`; the library allocates
- *    nothing.  Workspace sizes come from the matching *_workspace_bytes query called
- *    with the same shape arguments.
+ *    no device memory.  Workspace sizes come from the matching *_workspace_bytes query
+ *    called with the same shape arguments.
+ *  - Host memory: ginex_sample_superbatch and the changeset calls (ginex_changeset_noalloc
+ *    excepted) bring counts and offsets over through 64 KB blocks of pinned memory that the
+ *    library makes with hipHostMalloc when a call finds none free, and keeps until the
+ *    process ends: as many as calls have run at once, at most 16 (1 MB).  With
+ *    GINEX_PINNED=0 there are none, and these results go to pageable memory.
  *  - `stream` is a hipStream_t passed as void* (NULL = the default stream).  All kernels
  *    of a call are enqueued on it.  The executor calls (ginex_cache_init*, ginex_gather,
  *    ginex_cache_update) only enqueue; ginex_sample_superbatch, ginex_changeset*,
@@ -25,7 +30,9 @@
  *                             holds every row then goes on from the accesses sorted for that, where other
  *                             calls need no sort
  *      GINEX_TRACE=1/2        the changeset calls report on stderr which way they went / and, where rows are
- *                             evicted that the trace decides on, how their lines were found
+ *                             evicted that the trace decides on, how their lines were found; every pinned
+ *                             block that is made
+ *      GINEX_PINNED=0         no pinned memory for counts and offsets (see above; some 10 us for each wait)
  *      GINEX_SAMPLER_LDS=0    all hops through hash tables in HBM, none through tables in LDS
  *      GINEX_SAMPLER_TILES=n  at most n tiles of a batch per workgroup column of the sampler
  *      GINEX_LIVE_SELECT=1    no shortcut that relies on the cache holding the whole superbatch

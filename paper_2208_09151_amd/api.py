@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import ctypes as C
+import os
 import threading
 from dataclasses import dataclass
 
@@ -219,9 +220,9 @@ _staging = threading.local()
 
 def _to_host(words):
     """A few int64 words of the device as a host array: through the thread's pinned buffer, 14 us
-    against 24 for a copy to pageable memory."""
+    against 24 for a copy to pageable memory.  The 128 KB stay with the thread; none with GINEX_PINNED=0."""
     n = words.numel()
-    if n > _STAGED:
+    if n > _STAGED or os.environ.get("GINEX_PINNED", "").startswith("0"):
         return words.cpu().numpy()
     if not hasattr(_staging, "buffer"):
         _staging.buffer = torch.empty(_STAGED, dtype=torch.int64, pin_memory=True)

@@ -1,6 +1,7 @@
 // Error reporting, the pinned blocks and version of the library (host only).
 #include <cstdarg>
 #include <cstdio>
+#include <cstdlib>
 #include <mutex>
 
 #include "ginex.h"
@@ -31,14 +32,21 @@ static void* g_free_blocks[HOST_BLOCKS];
 static int g_free = 0, g_made = 0;
 
 void* host_block_take() {
+  const char* const pinned = getenv("GINEX_PINNED");
+  if (pinned && pinned[0] == '0') return nullptr;
+  int made;
   {
     std::lock_guard<std::mutex> lock(g_block_mutex);
     if (g_free > 0) return g_free_blocks[--g_free];
     if (g_made >= HOST_BLOCKS) return nullptr;
-    ++g_made;
+    made = ++g_made;
   }
   void* block = nullptr;
-  if (hipHostMalloc(&block, HOST_BLOCK_BYTES, hipHostMallocPortable) == hipSuccess && block) return block;
+  if (hipHostMalloc(&block, HOST_BLOCK_BYTES, hipHostMallocPortable) == hipSuccess && block) {
+    const char* const trace = getenv("GINEX_TRACE");
+    if (trace && trace[0] == '2') fprintf(stderr, "[ginex] pinned block %d of at most %d\n", made, HOST_BLOCKS);
+    return block;
+  }
   (void)hipGetLastError();
   std::lock_guard<std::mutex> lock(g_block_mutex);
   --g_made;

@@ -12,7 +12,8 @@
 namespace ginex {
 
 // Blocks of pinned memory, made when first needed and kept for later calls of any thread: at most HOST_BLOCKS of them,
-// one to a call at a time.  Null where there is none (the copy then goes to pageable memory).  core.cpp
+// one to a call at a time.  Null where there is none, and with GINEX_PINNED=0 (the copy then goes to pageable memory).
+// core.cpp
 constexpr size_t HOST_BLOCK_BYTES = 64 << 10;
 constexpr int HOST_BLOCKS = 16;
 void* host_block_take();

@@ -1,5 +1,8 @@
 """Results that come to the host through the library's pinned blocks: more calls at once than there are blocks, more
-words than one holds."""
+words than one holds, none of them wanted."""
+import os
+import subprocess
+import sys
 from concurrent.futures import ThreadPoolExecutor
 
 import numpy as np
@@ -11,6 +14,7 @@ import oracle
 from test_gpu_parity import check_changeset, dev, ginex  # noqa: F401
 
 pytestmark = pytest.mark.gpu
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 def trace(seed, S, n, most):
@@ -37,3 +41,41 @@ def test_more_words_than_a_block(ginex, S):  # noqa: F811
     ids, off = trace(S, S, 300, 5)
     got = ginex.changeset(300, dev(ids), off, 40)
     check_changeset(got, oracle.changeset(300, ids, off, 40), (300, ids, off))
+
+
+# Pinned blocks are made where a call needs one and none is free, kept, and not made at all with GINEX_PINNED=0
+SCRIPT = """
+import os, sys
+import numpy as np, torch
+import oracle
+import paper_2208_09151_amd as g
+off = np.arange(9, dtype=np.int64) * 200
+ids = np.concatenate([np.random.default_rng(k).permutation(900)[:200] for k in range(8)]).astype(np.int32)
+ref = oracle.changeset(900, ids, off, 150)
+def call():
+    got = g.changeset(900, torch.from_numpy(ids).cuda(), off, 150)
+    for name in ("init_ids", "in_ids", "out_ids", "in_positions"):
+        assert np.array_equal(getattr(got, name).cpu().numpy(), ref[name]), name
+    assert np.array_equal(got.miss_count, ref["miss_count"]) and np.array_equal(got.cs_offsets, ref["cs_offsets"])
+    offsets = torch.arange(901, device="cuda", dtype=torch.int64) * 3
+    picked = g.sample_superbatch(offsets, torch.arange(2700, device="cuda", dtype=torch.int32) % 900,
+                                 torch.arange(40, device="cuda", dtype=torch.int32), np.array([0, 20, 40]), (2, 2))
+    assert picked.ids_offsets[-1] > 40
+    print("called", file=sys.stderr, flush=True)
+os.environ["GINEX_TRACE"] = "2"
+os.environ["GINEX_PINNED"] = "0"
+call()
+assert not hasattr(g.api._staging, "buffer")
+del os.environ["GINEX_PINNED"]
+call()
+assert hasattr(g.api._staging, "buffer")
+call()
+"""
+
+
+def test_pinned_memory(ginex):  # noqa: F811
+    run = subprocess.run([sys.executable, "-c", SCRIPT], cwd=ROOT, capture_output=True, text=True, timeout=100)
+    assert run.returncode == 0, run.stderr
+    without, made, kept = run.stderr.split("called")[:3]
+    assert "pinned" not in without and "pinned" not in kept
+    assert made.count("[ginex] pinned block 1 of at most 16") == made.count("pinned block") == 1
