@@ -42,8 +42,9 @@
  *      GINEX_DEAD_SCATTER=0/1 in that loop, evictions among dead rows from a pass over the lines / from
  *                             the id bitmap
  *      GINEX_PLANNED=0/2      a carried cache that holds the whole superbatch: as any other cache /
- *                             the three-launch steps also where the replay would do
- *      GINEX_PLAN_STOP=t      that way gives up in iteration t, and the call starts over as any other cache's
+ *                             three launches per iteration also where all iterations together would do
+ *      GINEX_PLAN_STOP=t      all iterations together: given up in iteration t, the call starts over as any
+ *                             other cache's
  *      GINEX_MOVE_POLLS=n     the blocks that find all iterations' lines in one launch (of one call at a time on a
  *                             GPU) wait for each other for n reads at most; 0: a launch per iteration
  *      GINEX_MOVE_STOP=t      they give up in iteration t, and the call goes on with a launch per iteration
@@ -250,12 +251,12 @@ int32_t ginex_changeset_noalloc(
  * superbatch.  It may be start_ids itself, which a call that returns GINEX_OK then leaves
  * overwritten.  No cache initialization is needed between the two superbatches.
  * When the cache also has a line for every distinct row of the superbatch, no iteration
- * evicts a row that is still needed: hits, misses and insertions are known up front and only
- * the choice of the evicted rows follows the iterations, replayed by one workgroup or, for
- * more candidates or evictions than that holds, in three small launches per iteration
- * (same result; GINEX_PLANNED=0 in the environment treats it as any other cache, 2 takes the
- * three-launch way also where the replay would do, GINEX_TRACE=1 reports on stderr which way
- * a call went). */
+ * evicts a row that is still needed: hits, misses and insertions are known up front, and
+ * which rows are evicted when, and from which lines, is found for all iterations together or,
+ * for more candidates or evictions than the arrays of that hold, in three small launches per
+ * iteration (same result; GINEX_PLANNED=0 in the environment treats it as any other cache, 2
+ * takes the three launches also where all iterations together would do, GINEX_TRACE=1 reports
+ * on stderr which way a call went). */
 int32_t ginex_changeset_resume(
     int64_t num_nodes, const int32_t* ids, const int64_t* ids_offsets /*host [S+1]*/,
     int32_t S, int64_t cap, const int32_t* start_ids /*[cap]*/, int32_t* final_ids /*[cap]*/,

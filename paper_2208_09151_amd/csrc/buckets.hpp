@@ -547,8 +547,8 @@ constexpr int64_t EMIT_TILES = 1024;
 
 // One block per tile of frontier nodes, see above.  Bound by the reads and writes of a few tiles a block (18
 // bytes per pick, 214 us for 37 M picks: 3.1 TB/s) where there are many, by the chain of reads where there are few:
-// batch length, sums and slot words, entries, words of repeated ids.  Dynamic LDS: sums of the tiles in front of each (tiles_in_lds
-// of them), [TILE_NODES * k] positions or new ids, [TILE_NODES * k] places of the new ids.
+// batch length, sums and slot words, entries, words of repeated ids.  Dynamic LDS: sums of the tiles in front of each
+// (tiles_in_lds of them), [TILE_NODES * k] positions or new ids, [TILE_NODES * k] places of the new ids.
 __global__ __launch_bounds__(TB) void k_bucket_emit(Tables T, Buckets B, Meta M, const int32_t* __restrict__ nfront,
                                                     int32_t* __restrict__ nlist_next, int k, int hop, int H,
                                                     const uint64_t* __restrict__ tile_sums, int64_t tiles,

@@ -367,9 +367,12 @@ __global__ __launch_bounds__(TB) void k_init_state_resume(const int32_t* __restr
 // ms; the passes around it 0.17).  Where a stretch of ids so dealt has room for its bits in LDS, they are put together
 // there, see k_hold_stretch.  Whether all rows are distinct and in range shows in the number of bytes or bits set.
 constexpr int HOLD_ITEMS = 8;
-// Lines are dealt from here on, and where the free buffer of the sort has a word for each.  2^20 lines:
+// Lines are dealt from here on, and where the free buffer of the sort has a word for each.  k_hold, 2^20 lines:
 // dealt 16 + 11 us and the scans of the counters (10), in their own order 19; 2^21: 20 + 28 (and 10)
-// against 51; 2^22: 28 + 54 (and 10) against 128.
+// against 51; 2^22: 28 + 54 (and 10) against 128.  That is where its line lies; k_hold_stretch, which takes the dealt
+// words up to 2^27 nodes, would pay below it, too: calls of four accesses to a line on 5, 20 and 110 M nodes, in
+// their own order and dealt, 2^18 lines 598, 623, 689 and 592, 619, 659 us; 2^20 827, 933, 1 034 and 800, 892,
+// 956; 2^21 1 355, 1 475, 1 595 and 1 328, 1 409, 1 496.
 constexpr int64_t HOLD_DEAL_MIN = int64_t(1) << 22;
 
 // A stretch of the ids as they are dealt is shared by up to four blocks, each of which reads all of its words and takes
@@ -391,11 +394,11 @@ __device__ __forceinline__ int64_t heads_below(const uint64_t* __restrict__ head
   return lo;
 }
 
-// All of it for one share of a stretch of 2^shift ids, 2^share of them: accessed and held rows as bits in LDS, the table entries of rows that
-// are both, then the words, the dead rows and their part counts.  in: the words (v << 32 | line) by stretch, that of digit d
-// from starts[d * tiles] on.  27.75 M lines of 111 M nodes, a third of them in 22 of 212 stretches: 313 us, where
-// k_accessed_bits, k_hold, k_held_words and what they have cleared take 105, 413, 40 and 25 (the call 2 724 -> 2 479);
-// one block to a stretch 414, the fullest 22 at work alone in the end.
+// All of it for one share of a stretch of 2^shift ids, 2^share of them: accessed and held rows as bits in LDS, the table
+// entries of rows that are both, then the words, the dead rows and their part counts.  in: the words (v << 32 | line) by
+// stretch, that of digit d from starts[d * tiles] on.  27.75 M lines of 111 M nodes, a third of them in 22 of 212
+// stretches: 313 us, where k_accessed_bits, k_hold, k_held_words and what they have cleared take 105, 413, 40 and 25 (the
+// call 2 724 -> 2 479); one block to a stretch 414, the fullest 22 at work alone in the end.
 __global__ __launch_bounds__(BIG) void k_hold_stretch(const uint64_t* __restrict__ in, const uint32_t* __restrict__ starts,
                                                       int64_t tiles, int32_t digits, int shift, int share, State st,
                                                       const uint64_t* __restrict__ heads, int64_t count,
@@ -2654,8 +2657,8 @@ constexpr int64_t LOOP_LRU_IDS = 1 << 16, LOOP_LRU_LINES = 1 << 22;
 //      accesses it has sorted; where the ids crowd in few buckets, or the rows do not fit, the call goes on to the next
 //   3  fresh Belady, few rows that do not fit: one workgroup, small.hpp.  Not with GINEX_STATIC_THRESHOLDS
 //   4  fresh, every row fits, or there is no cache: from the sorted accesses
-//   5  carried, every row fits: the planned path (all iterations together, or steps); gives way to 6 or 7 where its arrays do not hold
-//      the call.  Not with GINEX_PLANNED=0 or GINEX_LIVE_SELECT=1
+//   5  carried, every row fits: the planned path (all iterations together, or steps); gives way to 6 or 7 where its
+//      arrays do not hold the call.  Not with GINEX_PLANNED=0 or GINEX_LIVE_SELECT=1
 //   6  from the trace, stays.hpp (of many accesses through the windows of deal.hpp): up to 2 048 iterations, LRU with
 //      lines for the longest of them, but not the smallest calls (GINEX_STATIC_THRESHOLDS=1: these, too)
 //   7  the loop over the state (GINEX_STATIC_THRESHOLDS=0: in the place of 6)
@@ -3110,34 +3113,34 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
           hipLaunchKernelGGL(k_step_verdict, dim3(1), dim3(1), 0, st, state.fault, pl.scalars);
           GINEX_LAUNCH_CHECK();
         } else {
-        // the candidates numbered in id order
-        const char* const stop = getenv("GINEX_PLAN_STOP");
-        const Victims victims{reinterpret_cast<int32_t*>(w.heads_b),
-                              in_keys ? reinterpret_cast<uint32_t*>(state.res_next) : w.key_hists,
-                              pl.arr_cand, state.res_next, pl.arr_cur, (int32_t)parts, S, stop ? atoi(stop) : -1};
-        const int64_t lo_word = lo_id >> 5;
-        const int64_t nwords = state.words - lo_word;
-        const int64_t ctiles = ceil_div(nwords, TB);
-        hipLaunchKernelGGL(k_bit_tiles, dim3((unsigned)ctiles), dim3(TB), 0, st,
-                           state.bitmap + lo_word, nwords, pl.cand_tiles);
-        GINEX_LAUNCH_CHECK();
-        GINEX_HIP(exclusive_scan_inplace<uint32_t>(pl.cand_tiles, ctiles + 1,
-                                                   pl.cand_tiles + ctiles + 1, st));
-        hipLaunchKernelGGL(k_cand_emit, dim3((unsigned)ctiles), dim3(TB), 0, st, state.bitmap,
-                           state.dead_bits, lo_word, nwords, pl.cand_tiles, state.addr, pl, victims.when, S);
-        hipLaunchKernelGGL(k_plan_arrivals<true>, dim3((unsigned)tail_blocks), dim3(TB), 2 * off_lds, st,
-                           sorted, total, pl.scalars, held_bits, w.d_offsets, S, state.bitmap,
-                           pl.cand_base, num_nodes, pl, victims.when, (int32_t*)nullptr);
-        if (parts > 1)
-          hipLaunchKernelGGL(k_plan_counts, dim3((unsigned)S), dim3(TB), 0, st, pl, victims, sc[PLAN_CANDS]);
-        hipLaunchKernelGGL(k_plan_victims, dim3((unsigned)parts), dim3(WAVE), 0, st, pl, victims, ctiles,
-                           cs_offsets);
-        hipLaunchKernelGGL(k_plan_sort, dim3((unsigned)S), dim3(BIG), 0, st, pl, victims, cs_offsets);
-        if (S >= 4)   // (iteration 0 evicts no row it inserted, the last one inserts none: the third of three waits for none)
-          hipLaunchKernelGGL(k_plan_chain, dim3(1), dim3(BIG), 0, st, pl, victims, cs_offsets);
-        hipLaunchKernelGGL(k_plan_pairs, dim3((unsigned)S), dim3(BIG), 0, st, state, pl, victims, cs_offsets,
-                           in_ids, out_ids);
-        GINEX_LAUNCH_CHECK();
+          // the candidates numbered in id order
+          const char* const stop = getenv("GINEX_PLAN_STOP");
+          const Victims victims{reinterpret_cast<int32_t*>(w.heads_b),
+                                in_keys ? reinterpret_cast<uint32_t*>(state.res_next) : w.key_hists,
+                                pl.arr_cand, state.res_next, pl.arr_cur, (int32_t)parts, S, stop ? atoi(stop) : -1};
+          const int64_t lo_word = lo_id >> 5;
+          const int64_t nwords = state.words - lo_word;
+          const int64_t ctiles = ceil_div(nwords, TB);
+          hipLaunchKernelGGL(k_bit_tiles, dim3((unsigned)ctiles), dim3(TB), 0, st,
+                             state.bitmap + lo_word, nwords, pl.cand_tiles);
+          GINEX_LAUNCH_CHECK();
+          GINEX_HIP(exclusive_scan_inplace<uint32_t>(pl.cand_tiles, ctiles + 1,
+                                                     pl.cand_tiles + ctiles + 1, st));
+          hipLaunchKernelGGL(k_cand_emit, dim3((unsigned)ctiles), dim3(TB), 0, st, state.bitmap,
+                             state.dead_bits, lo_word, nwords, pl.cand_tiles, state.addr, pl, victims.when, S);
+          hipLaunchKernelGGL(k_plan_arrivals<true>, dim3((unsigned)tail_blocks), dim3(TB), 2 * off_lds, st,
+                             sorted, total, pl.scalars, held_bits, w.d_offsets, S, state.bitmap,
+                             pl.cand_base, num_nodes, pl, victims.when, (int32_t*)nullptr);
+          if (parts > 1)
+            hipLaunchKernelGGL(k_plan_counts, dim3((unsigned)S), dim3(TB), 0, st, pl, victims, sc[PLAN_CANDS]);
+          hipLaunchKernelGGL(k_plan_victims, dim3((unsigned)parts), dim3(WAVE), 0, st, pl, victims, ctiles,
+                             cs_offsets);
+          hipLaunchKernelGGL(k_plan_sort, dim3((unsigned)S), dim3(BIG), 0, st, pl, victims, cs_offsets);
+          if (S >= 4)   // (iteration 0 evicts no row it inserted, the last one inserts none: the third of three waits for none)
+            hipLaunchKernelGGL(k_plan_chain, dim3(1), dim3(BIG), 0, st, pl, victims, cs_offsets);
+          hipLaunchKernelGGL(k_plan_pairs, dim3((unsigned)S), dim3(BIG), 0, st, state, pl, victims, cs_offsets,
+                             in_ids, out_ids);
+          GINEX_LAUNCH_CHECK();
         }
       }
       if (src_line) {

@@ -68,8 +68,8 @@ __device__ __forceinline__ T dpp_or_zero(T v) {
 
 // Inclusive scan across the 64 lanes of a wave (all of them active): inside the rows of 16, then the last lane of a
 // row to the next one, and of the first half to the second.  With a shuffle a step, six trips through LDS that wait for
-// each other, the smallest changeset call took 272 us instead of 242 (its one workgroup 103 of them, some 20 barriers and scans an
-// iteration), sampling on a graph of 1 M nodes 297 instead of 286.
+// each other, the smallest changeset call took 272 us instead of 242 (its one workgroup 103 of them, some 20 barriers and
+// scans an iteration), sampling on a graph of 1 M nodes 297 instead of 286.
 template <typename T>
 __device__ __forceinline__ T wave_inclusive_scan(T v) {
   v += dpp_or_zero<0x111, 0xF>(v);   // row_shr:1

@@ -42,9 +42,9 @@ constexpr int64_t FIT_LOOKUP_MIN = 1 << 20, FIT_LOOKUP_NODES = 8, FIT_LOOKUP_ROW
 // A tile's accesses.  Wide tiles make half the shares of twice the length, and a share is a line of ids, one of places and one
 // of starts however few it holds: 33 M accesses in 1 695 buckets, shares of 4.9 and 9.8, k_fit_rows 245 -> 197 us,
 // k_fit_lines 196 -> 157, k_fit_lookup 281 -> 234 (the calls 714 -> 631 and 2 479 -> 2 436); 256 x 150 000 on 60 M nodes 726 ->
-// 615, 512 x 30 000 405 -> 359, 40 x 400 000 on 20 M 312 -> 298.  Fewer buckets have shares that fill the lanes already (1 M nodes,
-// 489 buckets, 64 x 120 000 184 and 179 us, 300 x 17 000 173 and 186), and fewer than two wide tiles to a CU leave
-// CUs without work.
+// 615, 512 x 30 000 405 -> 359, 40 x 400 000 on 20 M 312 -> 298.  Fewer buckets have shares that fill the lanes already
+// (1 M nodes, 489 buckets, 64 x 120 000 184 and 179 us, 300 x 17 000 173 and 186), and fewer than two wide tiles to a CU
+// leave CUs without work.
 constexpr int FIT_THREADS = 512, FIT_WIDE_THREADS = 1024;
 constexpr int FIT_ITEMS = 16;
 constexpr int FIT_TILE = FIT_THREADS * FIT_ITEMS, FIT_WIDE_TILE = FIT_WIDE_THREADS * FIT_ITEMS;
@@ -62,10 +62,10 @@ constexpr int FIT_LONG_SHARE = 128;                    // what a share has beyon
 // are taken side by side: ids that crowd (in order of degree, or of a part of the graph) or few buckets make one
 // workgroup the whole call (all among the 354 000 lowest of 111 M ids, 35 M accesses: 61 ms, 1.4 through the sorted
 // accesses).  The measure is ids of the bucket times passes over them, one for its bits and two for every FIT_ROWS
-// rows.  Calls in order and not, 62 720 to 40 M accesses on 2 027 to 98 M nodes: up to FIT_CHAIN + accesses / 32 never slower than
-// through the sorted accesses (0.4 to 1.0 times), from there to twice that 0.9 to 1.4 times, further up to 11 times.
-// k_fit_lookup: against a random word per access, with one pass for every FIT_ROWS rows; up to 25 000 + accesses / 128
-// 0.93 to 1.0 times, from 300 000 + accesses / 32 on 1.04 to 1.4 times.
+// rows.  Calls in order and not, 62 720 to 40 M accesses on 2 027 to 98 M nodes: up to FIT_CHAIN + accesses / 32 never
+// slower than through the sorted accesses (0.4 to 1.0 times), from there to twice that 0.9 to 1.4 times, further up to 11
+// times.  k_fit_lookup: against a random word per access, with one pass for every FIT_ROWS rows; up to 25 000 + accesses /
+// 128 0.93 to 1.0 times, from 300 000 + accesses / 32 on 1.04 to 1.4 times.
 constexpr int64_t FIT_CHAIN = 250'000, FIT_CHAIN_SHARE = 32, FIT_LOOKUP_CHAIN = 25'000, FIT_LOOKUP_SHARE = 128;
 // A sample of the accesses says so before anything else is done, where that many accesses could crowd too much and are
 // not so few that the gain is gone (some 6 us).
@@ -169,7 +169,8 @@ __device__ __forceinline__ int32_t fit_bucket() { return blockIdx.x % 8 * (gridD
 // (the places wait in registers until the ids have left LDS, so that two blocks of wide tiles, which is all waves of
 // a CU, have room side by side: 153 -> 106 us for 33 M accesses, the narrow ones 108 -> 93)
 template <int THREADS>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(THREADS / 128))) void k_fit_deal(Fit f, const int32_t* __restrict__ ids) {
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(THREADS / 128))) void k_fit_deal(
+    Fit f, const int32_t* __restrict__ ids) {
   constexpr int TILE = THREADS * FIT_ITEMS;
   extern __shared__ uint32_t s_count[];              // [buckets]
   __shared__ uint32_t s_id[TILE];                    // then the places
@@ -381,7 +382,8 @@ __device__ __forceinline__ uint32_t fit_bases(const Fit& f, const FitLds& l, uin
   return total;
 }
 
-// Where a wave's counters of k_fit_rows sit: 16 bits per iteration, in the room of the shares, so fewer waves rank where there are many iterations.
+// Where a wave's counters of k_fit_rows sit: 16 bits per iteration, in the room of the shares, so fewer waves rank where
+// there are many iterations.
 __host__ __device__ __forceinline__ int32_t fit_rank_waves(int32_t S) {
   const int32_t waves = 2 * FIT_SHARES * 2 / S;
   return waves < FIT_LINE_THREADS / WAVE ? waves : FIT_LINE_THREADS / WAVE;
@@ -479,11 +481,14 @@ struct FitReady {          // with the scan of the counts: the last of an iterat
 };
 
 constexpr size_t FIT_LDS = 65000;                    // at most (k_fit_lines; iterations: up to some 1 900)
-inline size_t fit_rows_lds(const Fit& f) { return 6 * ((size_t)1 << (f.shift - 5)) + sizeof(uint32_t) * (FIT_ROWS + 2 * FIT_SHARES); }
+inline size_t fit_rows_lds(const Fit& f) {
+  return 6 * ((size_t)1 << (f.shift - 5)) + sizeof(uint32_t) * (FIT_ROWS + 2 * FIT_SHARES);
+}
 inline size_t fit_lines_lds(const Fit& f) { return fit_rows_lds(f) + sizeof(uint32_t) * f.S; }
 
 // with_lines: C_0 alone, or every access's line, too
-__global__ __launch_bounds__(FIT_LINE_THREADS) __attribute__((amdgpu_waves_per_eu(8))) void k_fit_lines(Fit f, int32_t* __restrict__ init_ids, bool with_lines) {
+__global__ __launch_bounds__(FIT_LINE_THREADS) __attribute__((amdgpu_waves_per_eu(8))) void k_fit_lines(
+    Fit f, int32_t* __restrict__ init_ids, bool with_lines) {
   extern __shared__ uint32_t lds[];
   __shared__ uint32_t smem[FIT_LINE_THREADS / WAVE + 1];
   const int32_t q = fit_bucket();

@@ -24,10 +24,10 @@
 // gives up and says so in its words, which ends the others' waits too, and the host starts over with the launches.  In the first
 // iteration, where blocks that do not all run fail to meet, the bound is about what the iterations save.
 // A read takes 0.2 us; the first wait 2 us, beside kernels of other streams (gathers, copies, products of 8 192^3) 100 us in 99
-// of 100 calls, and 751 once.  10 M nodes, 100 iterations of 100 000, 300 000 lines, two, three, four and six threads that call all
-// the time: 2 680, 3 650, 4 490 and 6 660 us a call (four, if one of them went this way, 4 680; with no turns 6 040, a third of
-// the calls given up; all by launches 2 860, 3 615, 4 415 and 6 660); three processes 3 750 (with one bound for all waits 3 900, all
-// by launches 3 510).
+// of 100 calls, and 751 once.  10 M nodes, 100 iterations of 100 000, 300 000 lines, two, three, four and six threads
+// that call all the time: 2 680, 3 650, 4 490 and 6 660 us a call (four, if one of them went this way, 4 680; with no
+// turns 6 040, a third of the calls given up; all by launches 2 860, 3 615, 4 415 and 6 660); three processes 3 750 (with
+// one bound for all waits 3 900, all by launches 3 510).
 //
 // An iteration takes 2.6 us without lookups (the words' way to memory and back 1.3, records and LDS), 4.4 with 96 000 of
 // them from a table of 444 MB, 17.6 with 670 000 (two thirds of it random words at 59 G/s, the chip's rate); a launch
@@ -50,13 +50,13 @@ constexpr int MOVE_CALLS = 3;                 // calls at once on a GPU up to wh
 constexpr int MOVE_WORDS_MAX = 35;            // words of two lines a thread has in LDS, at most (140 KB)
 // ... and for LRU, which gives lines up in the order in which they were taken, so that an iteration's lie in the stretches of
 // a few blocks, and the larger these are the more one block hands over.  Moved and by a launch per iteration, 300 iterations
-// of 100 000 accesses, 25 000 lines each: of 3 M lines 4 477 and 5 435 us a call, 4 M 5 201 and 5 621, 4.7 M 5 996 and 5 674, 6 M 7 209
-// and 6 032, 8 M 9 382 and 6 496; of 300 000 accesses, 70 000 lines: 4.7 M 3 809 and 4 008, 6 M 4 313 and 4 093.  (Belady's
-// are spread: 10 M rows in a window that moves, 200 iterations of 200 000, 4 897 and 5 824.)
+// of 100 000 accesses, 25 000 lines each: of 3 M lines 4 477 and 5 435 us a call, 4 M 5 201 and 5 621, 4.7 M 5 996 and
+// 5 674, 6 M 7 209 and 6 032, 8 M 9 382 and 6 496; of 300 000 accesses, 70 000 lines: 4.7 M 3 809 and 4 008, 6 M 4 313
+// and 4 093.  (Belady's are spread: 10 M rows in a window that moves, 200 iterations of 200 000, 4 897 and 5 824.)
 constexpr int MOVE_LRU_WORDS = 9;
 constexpr uint32_t MOVE_GAVE_UP = 0xFFFFFFFFu;
 constexpr int FINAL_ITEMS = 8;
-constexpr int MOVE_TAG = 18;                  // bits for the lines of a block; above: iteration + 1, at most 2 049
+constexpr int MOVE_TAG = 18;                  // bits for the lines of a block; above: iteration + 1, at most 2 048
 static_assert(MOVE_THREADS * 2 * MOVE_WORDS_MAX < 1 << MOVE_TAG && STATIC_S_MAX < 1 << (31 - MOVE_TAG), "one word");
 
 struct Moves {
@@ -354,7 +354,8 @@ class MoveTurn {
 };
 
 // The blocks and their stretches; none for more lines than the blocks' LDS has room for, or pays for, nor in another
-// call's turn.  GINEX_MOVE_POLLS: another bound of the waits, 0 for none of this; GINEX_MOVE_STOP: the iteration in which they give up.
+// call's turn.  GINEX_MOVE_POLLS: another bound of the waits, 0 for none of this; GINEX_MOVE_STOP: the iteration in which
+// they give up.
 int32_t moves_shape(const State& state, int64_t longest, int device, MoveTurn* turn, Moves* m) {
   const char* polls = getenv("GINEX_MOVE_POLLS");
   m->polls = polls ? atoi(polls) : MOVE_POLLS;

@@ -138,8 +138,8 @@ inline hipError_t occurrences_async(const int32_t* values, int64_t n, int64_t bi
 
 // ---------------------------------------------------------------------------------
 // Stable LSD radix sort of uint64 words on bits [bit_lo, bit_hi), at most 8 bits per pass and the same
-// number in every pass (9 bits: see RS_WIDE_BITS), or one less in the last ones: 27 bits as 7 + 7 + 7 + 6 instead of 8 + 8 + 8 + 3 halve the
-// counters that are scanned and double the runs that are written (33 M pairs: 1.22 -> 1.02 ms).
+// number in every pass (9 bits: see RS_WIDE_BITS), or one less in the last ones: 27 bits as 7 + 7 + 7 + 6 instead of 8 +
+// 8 + 8 + 3 halve the counters that are scanned and double the runs that are written (33 M pairs: 1.22 -> 1.02 ms).
 // Each pass: (1) per-tile digit histogram, (2) exclusive scan of the digit-major
 // histogram, (3) scatter.  In the scatter a wave owns a contiguous run of its tile and
 // ranks its 64 keys per step with ballot-built peer masks, so equal digits keep their
@@ -201,7 +201,8 @@ static __global__ __launch_bounds__(THREADS) void k_radix_scatter(
     const uint32_t* __restrict__ hist_scanned) {
   constexpr int BINS = 1 << BITS, WAVES = THREADS / WAVE, TILE = THREADS * RS_ITEMS;
   static_assert(BINS <= THREADS, "a thread per digit");
-  typedef typename std::conditional<(WAVES > 4), uint16_t, uint32_t>::type Count;   // (at most 1024; LDS is short for many)
+  typedef typename std::conditional<(WAVES > 4), uint16_t, uint32_t>::type Count;   // (LDS is short for many waves)
+  static_assert(WAVES <= 4 || TILE - WAVE * RS_ITEMS <= 0xFFFF, "keys of a digit in the waves in front");
   __shared__ uint64_t staged[TILE];
   __shared__ Count wave_count[WAVES][BINS];
   __shared__ uint32_t digit_start[BINS];   // start of each digit inside the tile

@@ -4,19 +4,20 @@
 // candidates from number x on, those waiting at the end of iteration t are
 //   B_x(t) = max(0, B_x(t - 1) + arrivals_x(t) - n_t),
 // whatever the candidates below x are, and the difference of B_x and the next part's says how many an iteration takes
-// from one part of PLAN_PART candidates.  The maxima and sums of the iterations are a scan (the steps x -> max(x + c, d) compose), and
-// with its numbers known a part is a matter of one wave: k_plan_counts, k_plan_victims.
+// from one part of PLAN_PART candidates.  The maxima and sums of the iterations are a scan (the steps x -> max(x + c, d)
+// compose), and with its numbers known a part is a matter of one wave: k_plan_counts, k_plan_victims.
 //
 // The lines.  A row has one line, so a victim's is known unless the row was inserted in this call.  k_plan_sort orders
 // the known ones of each iteration.  Only where an iteration evicts rows with a line to come and inserts rows that
 // are evicted again do iterations wait for each other: k_plan_chain, one workgroup, finds those rows' lines.  k_plan_pairs
 // then pairs all evictions of all iterations with the insertions.
 //
-// 200 iterations of 338 evictions each, 101 000 candidates: one workgroup that went through the iterations, selection, ranks and pairing
-// each behind the other's barriers, took 1 318 us (the call 3 920); now k_plan_counts 6, k_plan_victims 47 (for the
-// uppermost parts a step of 0.2 us per iteration), k_plan_sort 8, k_plan_chain 87 (two reads and some six barriers for each of the
-// iterations that wait), k_plan_pairs 8 (the call 2 805).  The smallest calls have two to four launches more, 5 to 10 of
-// 280 us, more than a hundred iterations gain whatever else they hold (256 of 1 000 accesses 1 160 -> 580).
+// 200 iterations of 338 evictions each, 101 000 candidates: one workgroup that went through the iterations, selection,
+// ranks and pairing each behind the other's barriers, took 1 318 us (the call 3 920); now k_plan_counts 6, k_plan_victims
+// 47 (for the uppermost parts a step of 0.2 us per iteration), k_plan_sort 8, k_plan_chain 87 (two reads and some six
+// barriers for each of the iterations that wait), k_plan_pairs 8 (the call 2 805).  The smallest calls have two to four
+// launches more, 5 to 10 of 280 us, more than a hundred iterations gain whatever else they hold (256 of 1 000 accesses
+// 1 160 -> 580).
 #pragma once
 
 constexpr int PLAN_PART = 1024;                        // candidates of a wave

@@ -4,8 +4,8 @@ The oracle runs the whole superbatch itself (sampling, then changesets on ITS id
 GPU outputs are compared element by element: sampled ids and adjacency, every changeset
 list, the resolved cache line of every access, the gathered bytes of EVERY iteration
 (configurations 3 and 4; every eighth iteration on configuration 5, whose 200 iterations
-gather 156 GB) and every resident cache line at the end.  Configurations 3 and 4 never miss (the rows a superbatch touches fit in the
-cache), so each workload is also run with a cache a sixteenth of the distinct rows, which
+gather 156 GB) and every resident cache line at the end.  Configurations 3 and 4 never miss (the
+rows a superbatch touches fit in the cache), so each workload is also run with a cache a sixteenth of the distinct rows, which
 puts the Belady loop and the slow-tier reads under full-size pressure.
 
 Configuration 3 also carries the rows built after the main path (LRU, resumed changesets,
@@ -161,7 +161,7 @@ def carried_cache_both_ways(ginex, cfg, res, ids, distinct, capfd=None):
     assert start.numel() == cfg.cap
     del rows, outside
     both = []
-    for planned in ("1", "2", "0"):     # the replay in LDS, the steps in global memory, the loop
+    for planned in ("1", "2", "0"):     # all iterations together, the steps in global memory, the loop
         os.environ["GINEX_PLANNED"] = planned
         os.environ["GINEX_TRACE"] = "1"
         if capfd is not None:

@@ -58,7 +58,8 @@ def test_small_caches_equal_the_oracle(ginex, policy, cap, monkeypatch):  # noqa
 
 
 # the lines up to which a thread has 1, 3, 9, 17 and 35 words of LDS, and one block's more, of which the last goes back
-# to a launch per iteration, LRU's behind 9 words; iterations of up to 1.2 M accesses are looked up in one go, longer ones in several
+# to a launch per iteration, LRU's behind 9 words; iterations of up to 1.2 M accesses are looked up in one go, longer ones
+# in several
 @pytest.mark.parametrize("cap,length", [(2**19, 400_000), (2**19 + 2, 400_000), (3 * 2**19 + 2, 700_000),
                                         (9 * 2**19, 3_000_000), (9 * 2**19 + 2, 3_000_000), (17 * 2**19 + 2, 4_000_000),
                                         (35 * 2**19, 6_000_000), (35 * 2**19 + 1, 6_000_000)])

@@ -744,7 +744,7 @@ def planned_cases(rng):
     tr = [rng.permutation(rows), rows[::-1].copy(), rng.permutation(rows)[:1200]]
     off = np.cumsum([0] + [len(t) for t in tr]).astype(np.int64)
     yield "clustered", n, np.concatenate(tr).astype(np.int32), off, np.arange(700000, dtype=np.int32)
-    # 4c. tens of thousands of candidates (several bitmap words per thread of the replay): most
+    # 4c. tens of thousands of candidates (tens of the parts that a wave takes): most
     #     rows of the upper half of the start state are accessed once and die on the way, one
     #     in twenty is dead from the start, and two waves of new rows push rows out
     n = 300000
@@ -767,7 +767,7 @@ def planned_cases(rng):
     rows = np.setdiff1d(rng.choice(n, size=260, replace=False), start)[:200]
     ids, off = revisit(n, 10, rows, 2)
     yield "sparse", n, ids, off, start
-    # 5b. more candidates than the replay's bitmap holds (600 000 resident rows die above the
+    # 5b. more candidates than the planned path's arrays hold (600 000 resident rows die above the
     #     lowest possible victim): not taken
     n = 710000
     start = np.concatenate([np.arange(1000), np.arange(100000, 700000)]).astype(np.int32)
@@ -787,8 +787,8 @@ def planned_cases(rng):
 
 def test_carried_cache_that_holds_the_superbatch_needs_no_loop(ginex, monkeypatch, capfd):
     """A carried cache with a line for every distinct row of the superbatch: hits, misses and
-    insertions are known up front and only the choice of the evicted rows is replayed, by one
-    workgroup in LDS or, for more candidates or evictions than that holds (or GINEX_PLANNED=2),
+    insertions are known up front, and the evicted rows are found for all iterations together or,
+    for more candidates or evictions than the arrays of that hold (or GINEX_PLANNED=2),
     step by step on the bitmap in global memory.  The results equal the oracle's and the
     loop's (GINEX_PLANNED=0), lists, lines and final state."""
     rng = np.random.default_rng(77)
@@ -806,7 +806,7 @@ def test_carried_cache_that_holds_the_superbatch_needs_no_loop(ginex, monkeypatc
         monkeypatch.delenv("GINEX_TRACE")
         check_resumed(res, ref, (n, ids, off))
         if len(ids):      # the way the call went is the one the case was built for
-            big = kind in ("wide", "crowded")   # more than the replay's arrays in LDS hold
+            big = kind in ("wide", "crowded")   # more than those arrays hold
             assert ("stepped path" in said) == big and ("planned path" in said) == (not big), said
             assert "gave up" not in said and ": loop" not in said, said
         # the same through the steps on the bitmap in global memory, whatever the sizes ...
