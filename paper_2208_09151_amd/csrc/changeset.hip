@@ -2878,17 +2878,16 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
                        !(plan_env && plan_env[0] == '0');
   // Belady, otherwise: the changesets from the trace and the start state (stays.hpp), but for more
   // iterations than the table of the stays is kept for, and for the smallest calls, which are a
-  // chain of launches either way: the loop has six to an iteration, the other way some 35 and one to
-  // an iteration.  2 000 nodes, iterations of 300 accesses, fresh, by lines held: two iterations 335 to 305 us
-  // against 265 to 283, six 483 to 403 against 414 to 379, eight 515 to 413 against 481 to 434;
-  // 20 000 nodes, three iterations of 3 000 accesses 411 to 350 against 335 to 368, four of 2 000 463 to 361
-  // against 400 to 406.  Many
-  // nodes: the loop clears two words for each; two iterations of 200 accesses, carried, 66 M nodes 464 against
-  // 434, three on 111 M nodes 507 against 537.  GINEX_STATIC_THRESHOLDS=0/1 chooses the loop / the trace.
-  // LRU (the trace's way has no cuts): 20 000 nodes, iterations of 3 000 accesses, two 311 against 332, three 355
-  // and 342, six 472 and 396; 200 000 nodes, of 20 000, two 344 and 380, three 406 and 412.  And a large cache of just
-  // the lines that an iteration accesses: the loop gives all of them up without a select (5 iterations of 8 M 4.7 and
-  // 5.8 ms, 8 of 4 M 3.26 and 3.39; of 2 M 2.0 and 1.8; with 6 % more lines 14.8 and 6.0).
+  // chain of launches either way: the loop has six to an iteration, the other way some 40.
+  // Carried, lines for a tenth and for eight tenths of the rows, the loop and the trace: 2 000 nodes, iterations of 300
+  // accesses, two 253 and 325 us, 237 and 302, four 292 and 339, 281 and 309, six 349 and 364, 359 and 323, eight 401
+  // and 393, 415 and 339; 20 000 nodes, three of 3 000 accesses 286 and 349, 298 and 318, four of 2 000 332 and 352, 337
+  // and 325.  Many nodes: the loop clears two words for each; three iterations of 200 accesses, 30 M nodes 285 and 350,
+  // 289 and 334, 66 M 358 and 354, 359 and 338.  GINEX_STATIC_THRESHOLDS=0/1 chooses the loop / the trace.
+  // LRU (the trace's way has no cuts): 20 000 nodes, iterations of 3 000 accesses, two 226 and 240, three 276
+  // and 244, six 421 and 259; 200 000 nodes, of 20 000, two 258 and 252, three 318 and 262.  And a large cache of just
+  // the lines that an iteration accesses: the loop gives all of them up without a select (5 iterations of 8 M 4.2 and
+  // 5.0 ms, 8 of 4 M 3.55 and 3.76; of 2 M 2.6 and 2.0; with 6 % more lines 26.9 and 5.1, 19.6 and 3.8).
   const bool by_loop =
       (lru && max_n == cap && cap >= LOOP_LRU_LINES) ||
       (num_nodes <= LOOP_NODES &&

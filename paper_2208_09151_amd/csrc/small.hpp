@@ -1,25 +1,26 @@
 // Belady changesets of the smallest calls: the loop over the iterations in one workgroup.  Included by
 // changeset.hip only.
 //
-// A call on some ten thousand accesses is a chain of launches that do next to nothing, some 35 of them and one to an
-// iteration from the trace, six to an iteration in the loop over the state, with waits for the host in between.
+// A call on some ten thousand accesses is a chain of launches that do next to nothing, some 40 of them from the trace,
+// six to an iteration in the loop over the state, with waits for the host in between.
 // Here the rows are numbered by rank (in id order, so that ids compare as ranks), which makes the whole state of the
 // cache fit LDS as 16-bit words, and one workgroup goes through the iterations: the same steps as the loop
 // (see there), with barriers between them instead of launches.
 //   k_small_ranks   rank and next accessed iteration of every access, id and first iteration of every row
 //   k_small_belady  C_0, then the iterations
-// 8 iterations of 3 500 accesses on 16 384 nodes, 2 048 lines: 35 launches and 8 for the lines, 492 us a call; this
-// way 276, k_small_ranks 8 and k_small_belady 104 (some 20 barriers and two reads of the accesses an iteration,
-// 12 us), the rest the sort, two waits for the host and the outputs' copies.
+// 8 iterations of 3 500 accesses to 10 900 rows, 1 858 lines: from the trace 405 us a call, the loop 480; this way 219.
+// On 16 384 nodes, 2 048 lines: 230, k_small_ranks 9 and k_small_belady 82 (some 20 barriers and two reads of the
+// accesses an iteration, 10 us), the rest the sort and two waits for the host.
 #pragma once
 
 constexpr int SMALL_ROWS = 12288;          // five arrays of 24 KB
 constexpr int SMALL_S = 256;               // iterations at most (LDS counters of a wave per iteration)
-// One workgroup takes 6 us for an iteration of 600 accesses, 28 for one of 10 000; a launch for the lines of an
-// iteration, 5 to 20, more where many iterations have cuts.  By lines held (share of the rows), from the trace or the
-// loop against this way: 2 x 40 (half) 293 to 162 us, 256 x 600 (0.3) 2 863 to 1 588, (0.9) 2 180 to 1 603, 32 x 3 500
-// (0.3) 826 to 548, 16 x 10 000 (0.7) 691 to 634; beyond: 128 x 3 500 (0.3) 2 210 and 1 649, but 256 x 3 500 (0.8)
-// 2 926 and 3 415, 100 x 10 000 (0.9) 2 148 and 2 862.
+// One workgroup takes 5 us for an iteration of 600 accesses, 18 for one of 10 000; all iterations' lines in one launch
+// 3 to 6, more where many iterations have cuts, behind some 250 us of other launches.  Up to 12 200 rows, by lines held
+// (share of the rows), from the trace and this way: 2 x 40 (half) 253 and 134 us, 256 x 600 (0.3) 1 674 and 1 301, (0.9)
+// 1 674 and 1 460, 128 x 1 200 (0.3) 1 040 and 892, 32 x 3 500 (0.3) 599 and 430, 16 x 10 000 (0.3) 643 and 405, (0.7)
+// 465 and 410; beyond: 128 x 3 500 (0.3) 1 578 and 1 281, but 256 x 3 500 (0.8) 1 962 and 2 714, 100 x 10 000 (0.9)
+// 1 081 and 1 801.
 constexpr int64_t SMALL_IDS = 163'840;     // (16 x 10 000, some more)
 constexpr uint32_t NOT_RESIDENT = 0xFFFFu;
 

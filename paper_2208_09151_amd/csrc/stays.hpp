@@ -23,9 +23,9 @@
 //
 // 200 iterations of 163 840 accesses, 111 M nodes, every iteration evicts: that loop 200 x 41 us, and
 // 0.83 ms to look right.  Here: k_stay_ends 0.49 ms (scattered words), k_key_hists 0.05,
-// k_static_roll 0.16, 17 levels of k_cut_members + k_cut_decide 0.020 + 0.010 each (two chains of
+// k_static_roll 0.13, 17 levels of k_cut_members + k_cut_decide 0.023 + 0.010 each (two chains of
 // dependent reads), k_stays_mark 0.14 (random words of the table, L2), k_stays_links 0.28 (one random
-// word per pair, 117 G/s), bucket "never" 0.11, k_stays_walk 0.40, k_ins_emit 0.06, k_move_lines 0.89.
+// word per pair, 117 G/s), bucket "never" 0.11, k_stays_walk 0.43, k_ins_emit 0.05, k_move_lines 0.83.
 #pragma once
 
 constexpr int STATIC_S_MAX = 2048;      // iterations up to which the (S + 1) x S table is kept
@@ -603,9 +603,9 @@ __global__ __launch_bounds__(TB) void k_cut_wide(Stays q, Jobs jobs, int first,
 // come from), and a select among the accesses of the one iteration that the limit falls into: all
 // iterations side by side.  A hit is an access whose row is not below the limit of the iteration before,
 // every miss is inserted, and the iteration that evicts a row is found by bisection.
-// 20 iterations of 76 000 accesses, 104 857 lines: the loop over the state, six launches an iteration, 1 347 us
-// a call, this way 765 (k_lru_limits 32, k_stays_mark 11, k_lru_walk 23, k_step_lines 20 x 13); 100 of 100 000 on
-// 30 M nodes, 0.85 M lines: 10.5 ms and 3.8.
+// 20 iterations of 76 000 accesses, 104 857 lines: the loop over the state, six launches an iteration, 1 263 us
+// a call, this way 449 (k_move_lines 76, k_lru_limits 31, k_lru_walk 21, k_stays_mark 8; the sort 90); 100 of 100 000
+// on 30 M nodes, 0.85 M lines: 15.5 ms and 2.2.
 
 // The place of a row in the order, larger: stays longer.
 __device__ __forceinline__ uint64_t lru_key(uint32_t iteration, uint32_t v) {
