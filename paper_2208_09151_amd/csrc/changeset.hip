@@ -2947,7 +2947,8 @@ int32_t changeset_run(const char* who, bool lru, int64_t num_nodes, const int32_
         const bool deals = cap >= HOLD_DEAL_MIN && cap <= total;
         uint64_t* const dealt = sorted == w.pairs_a ? w.pairs_b : w.pairs_a;
         if (deals) GINEX_HIP(radix_pass(lines, dealt, cap, 32 + shift, deal_bits, w.hist, st));
-        if (deals && shift <= HOLD_SHIFT_MAX) {
+        // (shorter stretches: more lines than nodes, which is refused below)
+        if (deals && shift >= HOLD_SHIFT_MIN && shift <= HOLD_SHIFT_MAX) {
           GINEX_HIP(fill_async<unsigned long long>(w.d_counts, 1, 0ull, st));
           const int share = std::min(HOLD_SHARE_MAX, shift - HOLD_SHIFT_MIN);
           const int64_t stretches = ceil_div(ceil_div(num_nodes, int64_t(1) << shift), 8) * 8;

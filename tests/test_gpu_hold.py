@@ -1,5 +1,6 @@
 """The rows of a large carried cache, put together a stretch of ids at a time in LDS (from 2^22 lines on, up to 2^27 nodes) or
-as bytes (beyond), against the loop over the state, which does neither (tolerance zero), and rows that are refused."""
+as bytes (beyond), against the loop over the state, which does neither (tolerance zero), and rows that are refused, more
+lines than nodes among them."""
 import numpy as np
 import pytest
 import torch
@@ -50,3 +51,20 @@ def test_carried_rows(ginex, nodes, cap, low, monkeypatch):  # noqa: F811
         broken[0] = bad
         with pytest.raises(paper_2208_09151_amd.GinexError):
             ginex.changeset_resume(nodes, ids, off, broken)
+
+
+# more lines than there are nodes: some row is there twice, whatever the rows are, and the call says so
+@pytest.mark.parametrize("nodes", [3000, 40_000, 65_536, 65_537])
+def test_more_lines_than_nodes(ginex, nodes):  # noqa: F811
+    cap = 2**22
+    length = nodes - 1
+    S = -(-cap // length)
+    gen = torch.Generator(device="cuda").manual_seed(nodes)
+    ids = torch.cat([torch.randperm(nodes, generator=gen, device="cuda")[:length].int() for _ in range(S)])
+    start = torch.randint(nodes, (cap,), generator=gen, device="cuda").int()
+    with pytest.raises(paper_2208_09151_amd.GinexError, match="out of range or repeated"):
+        ginex.changeset_resume(nodes, ids, np.arange(S + 1, dtype=np.int64) * length, start)
+    # (and the next call finds nothing of it)
+    off = np.arange(3, dtype=np.int64) * length
+    got = ginex.changeset_resume(nodes, ids[:2 * length], off, torch.arange(nodes, device="cuda").int())
+    assert got.miss_count.sum() == 0
