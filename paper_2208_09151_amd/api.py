@@ -225,7 +225,8 @@ def _to_host(words):
     if n > _STAGED or os.environ.get("GINEX_PINNED", "").startswith("0"):
         return words.cpu().numpy()
     if not hasattr(_staging, "buffer"):
-        _staging.buffer = torch.empty(_STAGED, dtype=torch.int64, pin_memory=True)
+        with torch.inference_mode(False):       # (it serves calls outside of it, too)
+            _staging.buffer = torch.empty(_STAGED, dtype=torch.int64, device="cpu", pin_memory=True)
     _staging.buffer[:n].copy_(words, non_blocking=True)
     torch.cuda.current_stream(words.device).synchronize()
     return _staging.buffer[:n].numpy().copy()

@@ -79,3 +79,19 @@ def test_pinned_memory(ginex):  # noqa: F811
     without, made, kept = run.stderr.split("called")[:3]
     assert "pinned" not in without and "pinned" not in kept
     assert made.count("[ginex] pinned block 1 of at most 16") == made.count("pinned block") == 1
+
+
+# The thread's buffer is made by its first call, in whatever mode that one runs, and serves all of them
+@pytest.mark.parametrize("first,then", [(True, False), (False, True)])
+def test_modes_of_the_first_call(ginex, first, then):  # noqa: F811
+    ids, off = trace(5, 8, 900, 200)
+    ref = oracle.changeset(900, ids, off, 150)
+
+    def calls():
+        for special in (first, then, first):
+            with torch.inference_mode(special), torch.device("cuda" if special else "cpu"):
+                got = ginex.changeset(900, dev(ids), off, 150)
+            check_changeset(got, ref, (900, ids, off))
+        return True
+    with ThreadPoolExecutor(1) as pool:
+        assert pool.submit(calls).result()
