@@ -150,3 +150,13 @@ def test_precondition_and_workspace_errors_are_reported_before_any_launch():
     assert lib.ginex_cache_count_misses(ctypes.byref(c), fake, 3, None, None) == -1
     assert lib.ginex_gather(ctypes.byref(c), fake, 2, ctypes.c_void_p(0x1008), None, None, None,
                             0, None) == -1                                   # out misaligned
+
+
+def test_header_lists_every_switch():
+    folder = os.path.join(ROOT, "paper_2208_09151_amd", "csrc")
+    used = set()
+    for name in os.listdir(folder):
+        used |= set(re.findall(r'getenv\("(GINEX_\w+)"\)', open(os.path.join(folder, name)).read()))
+    header = open(os.path.join(ROOT, "include", "ginex.h")).read()
+    listed = set(re.findall(r"^ \*      (GINEX_\w+)=", header, re.M))
+    assert used and used == listed
